@@ -43,13 +43,8 @@ def kernel_work(net: kstep.KfacNetworkStep):
     shapes = [l.shape for l in net.layers]
     dims = [d for s in shapes for d in (s.d_A, s.d_G)]
 
-    def is_plain(s):
-        return s.kh == 1 and s.kw == 1 and s.stride == 1 and s.pad == 0
-
-    mfma_ok = [s for s in shapes if s.C_in % 8 == 0]
-    fac_conv = sum(kstep.factor_flops(s.R, s.d_A) for s in mfma_ok if not is_plain(s))
-    fac_plain = (sum(kstep.factor_flops(s.R, s.d_A) for s in mfma_ok if is_plain(s)) +
-                 sum(kstep.factor_flops(s.R, s.d_G) for s in shapes))
+    fac_tile = (sum(kstep.factor_flops(s.R, s.d_A) for s in shapes if s.C_in % 8 == 0) +
+                sum(kstep.factor_flops(s.R, s.d_G) for s in shapes))
     w = {
         # all steps of all matrices in one kernel; a matrix's last step (short product, dense mirrored output) is a
         # small part of it; it also inverts the next step's pivot block (fp32 matrix cores) beside the update
@@ -67,8 +62,7 @@ def kernel_work(net: kstep.KfacNetworkStep):
         "inv_planes_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(8.0 * d * d for d in dims)),
         "factor_generic_kernel": ("alu", PEAK["alu_f32"], "TFLOP/s",
                                   sum(kstep.factor_flops(s.R, s.d_A) for s in shapes if s.C_in % 8 != 0)),
-        "factor_dma_kernel<conv>": ("mfma", PEAK["mfma_bf16"], "TFLOP/s", fac_conv),
-        "factor_dma_kernel<plain>": ("mfma", PEAK["mfma_bf16"], "TFLOP/s", fac_plain),
+        "factor_tile_kernel<16-bit>": ("mfma", PEAK["mfma_bf16"], "TFLOP/s", fac_tile),
         "kfac::ema_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(12.0 * d * d for d in dims)),
         "kfac::ema_batched_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(12.0 * d * d for d in dims)),
         "inv_init_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(4.0 * d * (d + 1) for d in dims if d > kstep.INVERSE_BLOCK)),

@@ -1,4 +1,4 @@
-// Matrix-core factor builder for narrow 16-bit NHWC layers whose channel count is not a multiple of 8 (the first
+// Matrix-core factor builder for narrow 16-bit layers whose channel count is not a multiple of 8 (the first
 // convolution: 3 channels, 7 x 7 taps, 148 columns, 401,408 unfolded rows at batch 32): tall and skinny, so one
 // workgroup accumulates the whole (at most 160 x 160) factor for a range of rows.
 //
@@ -6,11 +6,11 @@
 // share out the columns (column -> tap/channel offsets come from a table built once in LDS) and gather the slab
 // element by element into LDS transposed, Ut[column][row]; an MFMA operand (8 consecutive rows of one column) is
 // then one 16-byte LDS read.  The 15 lower 32 x 32 blocks are dealt to the four wavefronts.  Partial factors of
-// all row ranges are summed by factor_reduce_kernel<32>.
+// all row ranges are summed by factor_gather_reduce_kernel.
 #pragma once
 
 #include "common.h"
-#include "factor_dma.h"
+#include "factor_tile.h"
 
 namespace kfac {
 
@@ -40,9 +40,11 @@ __global__ __launch_bounds__(256) void factor_gather_kernel(Unfold u, const void
         const int kdata = u.d - u.has_bias;
         int off = -1, tap = 0;
         if (t < kdata) {
-            const int tp = t / u.C, ch = t - tp * u.C;
+            const int kk = u.kh * u.kw;
+            const bool ckk = u.order == KFAC_ORDER_C_KH_KW;
+            const int tp = ckk ? t % kk : t / u.C, ch = ckk ? t / kk : t - tp * u.C;
             const int ki = tp / u.kw, kj = tp - ki * u.kw;
-            off = (ki * u.W + kj) * u.C + ch;
+            off = u.layout == KFAC_NHWC ? (ki * u.W + kj) * u.C + ch : (ch * u.H + ki) * u.W + kj;
             tap = (ki << 16) | kj;
         } else if (t == kdata && u.has_bias) {
             off = -2;
@@ -77,7 +79,7 @@ __global__ __launch_bounds__(256) void factor_gather_kernel(Unfold u, const void
         const int yo = fast_div(rem, u.Wo, inv_wo);
         const int xo = rem - yo * u.Wo;
         const int y0 = yo * u.stride - u.pad, x0 = xo * u.stride - u.pad;
-        const int pix = ((n * u.H + y0) * u.W + x0) * u.C;
+        const int pix = u.layout == KFAC_NHWC ? ((n * u.H + y0) * u.W + x0) * u.C : (n * u.C * u.H + y0) * u.W + x0;
 #pragma unroll
         for (int i = 0; i < GA_COLS_PER_WAVE; ++i) {
             const int c = wave + 4 * i;

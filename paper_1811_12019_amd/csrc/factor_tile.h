@@ -1,0 +1,615 @@
+// Matrix-core factor builder: tiles of  Xbar^T Xbar  straight from a channels-last tensor, Xbar the implicitly unfolded
+// patch matrix, for 16-bit (v_mfma_f32_32x32x16) and fp32 (v_mfma_f32_32x32x2_f32) inputs.
+//
+// One TW x TW tile (on or below the diagonal) of one range of unfolded rows per workgroup.  The contraction index (the
+// unfolded row) is the slow index in memory, and the 16-bit MFMA wants it contiguous per lane; gfx950 has exactly the two
+// instructions that make this cheap:
+//   * global_load_lds_dwordx4 copies 16 bytes per lane from global memory straight into LDS (lane i lands at
+//     base + 16 i) without passing through registers, so a ring of row slabs can be kept in flight with no register
+//     cost and a single barrier per slab;
+//   * ds_read_b64_tr_b16 reads a 16 x 4 block of 16-bit values transposed: within 16 lanes, lane j receives
+//     element (j % 4) of lanes j/4, j/4 + 4, j/4 + 8, j/4 + 12.  With lanes pointed at 4 rows x 4 column groups
+//     of a raw slab, lane j gets four consecutive unfolded rows of column j: an MFMA operand half.
+// Rows outside a workgroup's range, taps that fall into the zero padding and columns beyond the matrix are fetched from a
+// 16-byte block of zeros, so the slab in LDS is always complete and the inner loop has no special cases.
+//
+// What bounds it and how it is cut.  A TW x TW tile moves 2 TW elements per row through the L1 (64 bytes per cycle and
+// CU) for TW^2 multiply-adds, so with 128-wide tiles the copies alone take as many cycles as the matrix cores: wide
+// matrices get 256-wide tiles (8 wavefronts of 128 x 64, a ring of four 32-row slabs), which halves that.  Matrices of
+// up to 128 (64) columns get one tile of that width.
+//
+// The bias column is not part of the tiled matrix (2048 + 1 columns would cost a ninth row of 256-wide tiles for one
+// column): its row of the result is the column sums, which the wavefronts of a diagonal tile whose part lies above the
+// diagonal form as products with a vector of ones.
+//
+// Column order and padding.  Internally columns run in 16-byte vectors of V = 8 (fp32: 4) channels: (tap, channel) for
+// KFAC_ORDER_KH_KW_C, (channel vector, tap, channel in vector) for KFAC_ORDER_C_KH_KW, and the channels of a tensor that
+// was repacked (other layouts, channel counts that are no multiple of V) may be padded with zeros.  The epilogue puts
+// results where the caller's order wants them (result_index); a vector's V kh kw columns are neighbours in both orders,
+// so a tile's stores stay inside the same few cache lines.
+#pragma once
+
+#include "common.h"
+#include "factor_mfma.h"
+
+namespace kfac {
+
+static __device__ uint4 g_zero_chunk = {0u, 0u, 0u, 0u};
+
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ int fast_div(int a, int d, float inv) {   // exact for 0 <= a < 2^24
+    int q = (int)((float)a * inv);
+    int rem = a - q * d;
+    if (rem < 0) --q;
+    else if (rem >= d) ++q;
+    return q;
+}
+
+#define KFAC_TR_READ(dst, addr, off) \
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off))
+
+template <bool F16>
+__device__ __forceinline__ v16f mfma16_halves(v2u a0, v2u a1, v2u b0, v2u b1, v16f c) {
+    uint4 a = make_uint4(a0.x, a0.y, a1.x, a1.y), b = make_uint4(b0.x, b0.y, b1.x, b1.y);
+    return mfma16<F16>(a, b, c);
+}
+
+// A build as the matrix-core kernels see it.
+struct View {
+    Unfold u;        // the tensor they read: channels last, C a multiple of the 16-byte vector; d = data columns (no bias)
+    int dout;        // rows of the result
+    int cout;        // channels of the caller's tensor
+    int chunked;     // internal column order: (channel vector, tap, channel in vector)
+    int mapped;      // internal column index != result index
+    int repack;      // the tensor is a repacked copy in the build's workspace
+};
+
+// False: the matrix-core kernels cannot take the build.
+static inline __host__ __device__ bool make_view(const Unfold& u, View* v) {
+    if (u.d >= 32768) return false;                                          // byte offsets into the result fit 32 bits
+    const int V = u.dtype == KFAC_F32 ? 4 : 8;
+    const int Cp = (u.C + V - 1) / V * V;
+    if ((long long)u.N * u.H * u.W * Cp > 0x7fffffffLL) return false;        // 32-bit element offsets
+    v->u = u;
+    v->u.C = Cp;
+    v->u.layout = KFAC_NHWC;
+    v->u.d = u.kh * u.kw * Cp;
+    v->dout = u.d;
+    v->cout = u.C;
+    v->chunked = u.order == KFAC_ORDER_C_KH_KW && u.kh * u.kw > 1;
+    v->mapped = v->chunked || Cp != u.C;
+    v->repack = (u.layout == KFAC_NCHW && u.H * u.W > 1) || Cp != u.C;
+    return true;
+}
+
+__device__ __forceinline__ bool is_plain(const Unfold& u) { return u.kh == 1 && u.kw == 1 && u.stride == 1 && u.pad == 0; }
+
+// Result index of internal data column p, or -1 for a padding column.
+__device__ __forceinline__ int result_index(const View& v, int p) {
+    if (p >= v.u.d) return -1;
+    if (!v.mapped) return p;
+    const int kk = v.u.kh * v.u.kw;
+    if (v.chunked) {
+        const int V = v.u.dtype == KFAC_F32 ? 4 : 8;
+        const int q = p / V, c = (q / kk) * V + (p - q * V), tap = q % kk;
+        return c < v.cout ? c * kk + tap : -1;
+    }
+    const int tap = p / v.u.C, c = p - tap * v.u.C;
+    return c < v.cout ? tap * v.cout + c : -1;
+}
+
+// What one thread needs to know about its 16-byte column vector.
+struct ColGroup {
+    bool data;    // false: beyond the matrix
+    int ki, kj;   // kernel tap
+    int off;      // element offset of (ki, kj, c0) relative to the patch's top-left pixel
+};
+
+__device__ __forceinline__ ColGroup decode_group(const View& v, int gcol0) {
+    const Unfold& u = v.u;
+    ColGroup g;
+    g.ki = g.kj = g.off = 0;
+    g.data = gcol0 < u.d;
+    if (g.data) {
+        int tap, c0;
+        if (v.chunked) {
+            const int V = u.dtype == KFAC_F32 ? 4 : 8, kk = u.kh * u.kw;
+            const int q = gcol0 / V;
+            c0 = (q / kk) * V;
+            tap = q % kk;
+        } else {
+            tap = gcol0 / u.C;
+            c0 = gcol0 - tap * u.C;
+        }
+        g.ki = tap / u.kw;
+        g.kj = tap - g.ki * u.kw;
+        g.off = (g.ki * u.W + g.kj) * u.C + c0;
+    }
+    return g;
+}
+
+// Shape of a tile: waves WM x WN of MB x NB 32 x 32 blocks, DK rows per slab, NS slabs in the ring (two panels each; a
+// diagonal tile needs one panel and has a ring twice as long in the same memory).
+template <int TW, int ES>
+struct TileShape;
+template <> struct TileShape<256, 2> { static constexpr int WM = 2, WN = 4, MB = 4, NB = 2, DK = 32, NS = 4; };
+template <> struct TileShape<128, 2> { static constexpr int WM = 2, WN = 2, MB = 2, NB = 2, DK = 32, NS = 3; };
+template <> struct TileShape<64, 2>  { static constexpr int WM = 2, WN = 2, MB = 1, NB = 1, DK = 64, NS = 3; };
+template <> struct TileShape<128, 4> { static constexpr int WM = 2, WN = 2, MB = 2, NB = 2, DK = 16, NS = 3; };
+template <> struct TileShape<64, 4>  { static constexpr int WM = 2, WN = 2, MB = 1, NB = 1, DK = 32, NS = 3; };
+
+template <int TW, int ES> constexpr int tile_threads() { return 64 * TileShape<TW, ES>::WM * TileShape<TW, ES>::WN; }
+
+// Where a tile's partial sums go when the rows are split: the tiles of a split one after another, then (all splits' tiles
+// done) the column sums of every split.
+struct Partial {
+    gfloat* tiles;        // [nsplit][ntiles][TW * TW]: 32 x 32 blocks row by row, each as the MFMA leaves it in the registers:
+                          // float 256 q + 4 lane + i is row 8 q + 4 (lane / 32) + i, column lane % 32
+    gfloat* sums;         // [nsplit][tiles_dim * TW]
+};
+
+template <int TW, int ES> constexpr int tile_ring_bytes() { return TileShape<TW, ES>::NS * 2 * TileShape<TW, ES>::DK * TW * ES; }
+template <int TW, int ES> constexpr int tile_lds_bytes() { return tile_ring_bytes<TW, ES>() + 4 * TW * 4; }
+
+template <int N> struct StaticInt { static constexpr int value = N; };
+
+// What a tile's workgroup works on.
+struct TileJob {
+    int I, J, tile, split;
+    int r_begin, r_end;
+    int tiles_dim, ntiles, nsplit;
+    float scale;
+};
+
+// One tile.  KIND 0: bf16, 1: fp16, 2: fp32.
+template <int TW, int KIND, bool PLAIN, bool DIAG>
+__device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 unsigned char* x, const TileJob& job,
+                                                const OutSpec& os, const Partial& part, unsigned char* smem) {
+    constexpr int ES = KIND == 2 ? 4 : 2, V = 16 / ES;
+    typedef TileShape<TW, ES> S;
+    constexpr int NW = S::WM * S::WN, DK = S::DK;
+    constexpr int PANEL = DK * TW * ES;                        // bytes of one operand panel of one slab
+    constexpr int STAGE = DIAG ? PANEL : 2 * PANEL;
+    constexpr int NS = DIAG ? 2 * S::NS : S::NS;
+    constexpr int PW = DIAG ? NW : NW / 2;                     // wavefronts that fill a panel
+    constexpr int NI = PANEL / 1024 / PW;                      // copies (1 KB each) per wavefront and slab
+    static_assert(NI * PW * 1024 == PANEL && NI >= 1 && (NS - 2) * NI < 64, "every wavefront issues the same number of copies");
+    constexpr int RGS = 8 * TW;                                // 16-bit: bytes of four rows
+    typedef __attribute__((address_space(3))) unsigned char lds_byte;
+    const Unfold& u = v.u;
+    const int t = threadIdx.x;
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave / S::WN, wn = wave % S::WN;
+    const int lm = lane & 31, h = lane >> 5;
+    const int I = job.I, J = job.J, D = u.d;
+    const int r_begin = job.r_begin, r_end = job.r_end;
+    const int nst = (r_end - r_begin + DK - 1) / DK;
+    const int wr = wm * S::MB * 32, wc = wn * S::NB * 32;      // this wavefront's part of the tile
+
+    // ---- producer: this wavefront fills blocks b0, b0 + PW, ... of panel `pan`; block = 64 consecutive 16-byte slots ----
+    // 16-bit slab: slot (row r, vector q) of four rows 4 rg .. 4 rg + 3 is rg (TW / 2) + 8 (q / 2) + 2 (r % 4) + q % 2: every
+    // 16-lane transposed read is then a contiguous 128-byte run.  fp32 slab: row-major.
+    const int pan = DIAG ? 0 : wave / PW;
+    const int b0 = wave % PW;
+    int row0, q;                                               // row inside the slab for block b0, vector
+    constexpr int ROWSTEP = ES == 4 ? PW * 64 / (TW / 4) : PW * 64 / (TW / 2) * 4;    // rows from one block of this wavefront to the next
+    static_assert(ES == 4 ? (PW * 64) % (TW / 4) == 0 : (PW * 64) % (TW / 2) == 0, "a lane keeps its column vector from block to block");
+    if constexpr (ES == 4) {
+        const int L = b0 * 64 + lane;
+        row0 = L / (TW / 4);
+        q = L % (TW / 4);
+    } else {
+        const int L = b0 * 64 + lane, s = L % (TW / 2);
+        row0 = 4 * (L / (TW / 2)) + ((s & 7) >> 1);
+        q = 2 * (s >> 3) + (s & 1);
+    }
+    const ColGroup g = decode_group(v, (pan == 0 ? I : J) * TW + q * V);
+    lds_byte* lds0 = (lds_byte*)smem + pan * PANEL + b0 * 1024;
+    const unsigned long long zero_addr = (unsigned long long)(const KFAC_AS1 unsigned char*)&g_zero_chunk;
+
+    // The NI rows whose vectors this lane copies, advanced by DK rows from slab to slab without divisions: DK rows are
+    // dn images, dy image rows and dx pixels, each with at most one carry into the next.
+    unsigned long long at[NI];                                 // address of the row's vector (patch origin + tap + channels)
+    int ty[NI], tx[NI];                                        // where in the image the row's tap lies
+    const int hw = u.Ho * u.Wo;
+    const int dn = DK / hw, dyr = DK % hw, dy = dyr / u.Wo, dx = dyr % u.Wo;
+    const long long px = (long long)ES * u.C;                  // bytes of a pixel
+    const int st_x = dx * u.stride, st_y = dy * u.stride, wrap_x = u.Wo * u.stride, wrap_y = u.Ho * u.stride;
+    const int end_x = wrap_x - u.pad + g.kj, end_y = wrap_y - u.pad + g.ki;
+    const long long step_bytes = PLAIN ? DK * px : px * ((long long)dn * u.H * u.W + (long long)st_y * u.W + st_x);
+    const long long carry_x = px * ((long long)u.stride * u.W - wrap_x), carry_y = px * ((long long)u.H * u.W - (long long)wrap_y * u.W);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int R = r_begin + row0 + j * ROWSTEP;
+        if constexpr (PLAIN) {
+            at[j] = (unsigned long long)x + (unsigned long long)((long long)R * px + (long long)ES * g.off);
+        } else {
+            const int n = R / hw, rem = R - n * hw, yo = rem / u.Wo, xo = rem - yo * u.Wo;
+            const int y0 = yo * u.stride - u.pad, x0 = xo * u.stride - u.pad;
+            ty[j] = y0 + g.ki;
+            tx[j] = x0 + g.kj;
+            at[j] = (unsigned long long)x + (unsigned long long)(px * (((long long)n * u.H + y0) * u.W + x0) + (long long)ES * g.off);
+        }
+    }
+    int rows_left = r_end - r_begin - row0;                    // valid while positive (row j: while above j ROWSTEP)
+    if (!g.data) rows_left = -0x40000000;                      // a column vector beyond the matrix: never
+
+    // copies of the next slab into the ring at stage_off (branch-free; slabs are issued in order)
+    auto issue = [&](int stage_off) {
+        unsigned long long src[NI];
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            bool ok = rows_left > j * ROWSTEP;
+            if constexpr (!PLAIN) ok = ok & ((unsigned)ty[j] < (unsigned)u.H) & ((unsigned)tx[j] < (unsigned)u.W);
+            src[j] = ok ? at[j] : zero_addr;
+            at[j] += (unsigned long long)step_bytes;
+            if constexpr (!PLAIN) {
+                tx[j] += st_x;
+                const bool cx = tx[j] >= end_x;
+                tx[j] -= cx ? wrap_x : 0;
+                ty[j] += st_y + (cx ? u.stride : 0);
+                const bool cy = ty[j] >= end_y;
+                ty[j] -= cy ? wrap_y : 0;
+                at[j] += (unsigned long long)((cx ? carry_x : 0) + (cy ? carry_y : 0));
+            }
+        }
+        rows_left -= DK;
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src[j],
+                                             (__attribute__((address_space(3))) void*)(lds0 + stage_off + j * PW * 1024), 16, 0, 0);
+    };
+
+    // ---- pipeline ----
+    // A slab is multiplied in STEPS steps; the operands of the next step are on their way from LDS while one is multiplied
+    // (read: starts them into one of two register sets; multiply: uses a set).  The barrier sits before a slab's last step:
+    // this wavefront has then read all of the slab, so that once everybody is there the slab's place is refilled, and
+    // the first operands of the next slab, whose copies have landed, are read during the last step's products.
+    constexpr int STEPS = ES == 2 ? DK / 16 : DK / 4;
+    static_assert(STEPS % 2 == 0, "the register sets alternate across slabs");
+    // (The scheduling fences keep a step's products between the waits: left alone, they sink below the next ones.)
+    auto pipeline = [&](auto reads_per_step, auto&& read, auto&& arrived, auto&& multiply) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) issue(s * STAGE);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((NS - 1) * NI) : "memory");
+        read(0u, StaticInt<0>{}, 0);
+        int cur = 0;                                            // ring offset of slab s
+        for (int s = 0; s < nst; ++s) {
+            auto step = [&](auto e) {                           // multiply step e, fetch the operands of step e + 1
+                if constexpr (decltype(e)::value + 1 < STEPS) {
+                    read((unsigned)cur, StaticInt<decltype(e)::value + 1>{}, (decltype(e)::value + 1) & 1);
+                    asm volatile("s_waitcnt lgkmcnt(%0)" :: "n"(decltype(reads_per_step)::value));
+                    arrived(decltype(e)::value & 1);
+                    multiply(decltype(e)::value & 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            step(StaticInt<0>{}); step(StaticInt<1>{}); step(StaticInt<2>{}); step(StaticInt<3>{}); step(StaticInt<4>{});
+            step(StaticInt<5>{}); step(StaticInt<6>{});
+            static_assert(STEPS <= 8, "steps written out above");
+            // everything of this slab is in registers, this wavefront's copies of the next one have landed (NS - 2 later slabs
+            // may still be in flight), and so for everybody
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((NS - 2) * NI) : "memory");
+            arrived(1);
+            const int freed = cur;
+            cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
+            read((unsigned)cur, StaticInt<0>{}, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(1);
+            __builtin_amdgcn_sched_barrier(0);
+            issue(freed);                                       // (after the products: before them, 3 to 5 % slower)
+        }
+        // trailing (all-zero) slabs must not land later, and everybody is done with the ring
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        arrived(0);                                             // (the last read's registers are not free before that wait)
+    };
+
+    // ---- consumer: LDS byte address of this lane's operand pieces in stage 0, from tile column c0 on ----
+    auto operand_addr = [&](int c0) -> unsigned {
+        if constexpr (ES == 2) {
+            const int grp = lane >> 4, p = lane & 15, r = p >> 2, cg4 = p & 3;
+            return (unsigned)((2 * (grp >> 1)) * RGS + (2 * r + (cg4 >> 1)) * 16 + (cg4 & 1) * 8 + (grp & 1) * 128 + c0 / 16 * 128);
+        } else {
+            return (unsigned)((h * TW + c0 + lm) * 4);
+        }
+    };
+    // operands of N 32-column blocks for the e-th K step of a slab: 16-bit: 16 rows; fp32: the 4 rows of two
+    // v_mfma_f32_32x32x2_f32 (k = 2 s + h), one read bringing the operands of both
+    constexpr int PIECES = ES == 2 ? 2 : 1;
+    constexpr int U = TW / 64;                                 // fp32: units of 256 bytes per slab row
+#define KFAC_TILE_READ(dst, i, addr, step)                                                                                        \
+    do {                                                                                                                         \
+        if constexpr (ES == 2) {                                                                                                 \
+            KFAC_TR_READ(dst[i][0], addr, (i) * 256 + (4 * decltype(step)::value + 0) * RGS);                                                       \
+            KFAC_TR_READ(dst[i][PIECES - 1], addr, (i) * 256 + (4 * decltype(step)::value + 1) * RGS);                                              \
+        } else {                                                                                                                 \
+            asm volatile("ds_read2st64_b32 %0, %1 offset0:%2 offset1:%3"                                                          \
+                         : "=v"(dst[i][0]) : "v"(addr + (i) * 128), "n"(4 * U * decltype(step)::value), "n"(4 * U * decltype(step)::value + 2 * U));               \
+        }                                                                                                                        \
+    } while (0)
+#define KFAC_TILE_ARRIVED(dst, i)                                                                                                \
+    do {                                                                                                                         \
+        asm volatile("" : "+v"(dst[i][0]));                                                                                      \
+        if constexpr (PIECES == 2) asm volatile("" : "+v"(dst[i][PIECES - 1]));                                                   \
+    } while (0)
+
+    // A wavefront whose part lies beyond the matrix or (diagonal tile) wholly above the diagonal only takes part in the
+    // copies; the latter form the column sums instead, BB 32-column blocks each.
+    constexpr int BB = TW == 64 ? 2 : 4;
+    constexpr int FIRST_ABOVE = S::MB / S::NB;                 // first such wavefront of wave row 0
+    static_assert(S::WN - FIRST_ABOVE == TW / (BB * 32), "the wavefronts above the diagonal cover the tile's columns");
+    const bool above = DIAG && wm == 0 && wn >= FIRST_ABOVE;
+    const int d = v.dout;
+    gfloat* __restrict__ out = os.dst;
+    const bool packed = os.mode == OUT_PACKED, ema = os.mode == OUT_EMA;
+    const bool split = job.nsplit > 1;
+    // result row of each of the tile's rows and columns (-1: none), and the same times the result's width
+    int* rmap = (int*)(smem + tile_ring_bytes<TW, ES>());
+    int* cmap = rmap + TW;
+    int* rmapd = rmap + 2 * TW;
+    int* cmapd = rmap + 3 * TW;
+    if (!split) {
+        for (int e = t; e < 2 * TW; e += 64 * NW) {
+            const int ri = result_index(v, e < TW ? I * TW + e : J * TW + e - TW);
+            rmap[e] = ri;
+            rmapd[e] = ri < 0 ? -1 : ri * d;
+        }
+        __syncthreads();
+    }
+    if (above) {
+        const int c0 = (wn - FIRST_ABOVE) * BB * 32;
+        if (!u.has_bias || J * TW + c0 >= D) {
+            pipeline(StaticInt<0>{}, [](unsigned, auto, int) {}, [](int) {}, [](int) {});
+            return;
+        }
+        v16f acc[BB];
+#pragma unroll
+        for (int i = 0; i < BB; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+        const unsigned addr0 = operand_addr(c0);
+        v2u b[2][BB][PIECES];
+        pipeline(StaticInt<BB * PIECES>{}, [&](unsigned stage_off, auto e, int set) {
+            const unsigned ba = addr0 + stage_off;
+#pragma unroll
+            for (int i = 0; i < BB; ++i) KFAC_TILE_READ(b[set], i, ba, e);
+        }, [&](int set) {
+#pragma unroll
+            for (int i = 0; i < BB; ++i) KFAC_TILE_ARRIVED(b[set], i);
+        }, [&](int set) {
+#pragma unroll
+            for (int i = 0; i < BB; ++i) {
+                if constexpr (ES == 2) {
+                    const unsigned one2 = KIND == 1 ? 0x3C003C00u : 0x3F803F80u;
+                    const v2u ones = {one2, one2};
+                    acc[i] = mfma16_halves<KIND == 1>(ones, ones, b[set][i][0], b[set][i][PIECES - 1], acc[i]);
+                } else {
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(1.0f, __uint_as_float(b[set][i][0][0]), acc[i], 0, 0, 0);
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(1.0f, __uint_as_float(b[set][i][0][1]), acc[i], 0, 0, 0);
+                }
+            }
+        });
+        if (h == 0) {                                           // (all rows of the products are the sums)
+            if (split) {
+                gfloat* dst = part.sums + (size_t)job.split * (job.tiles_dim * TW) + J * TW + c0;
+#pragma unroll
+                for (int i = 0; i < BB; ++i) dst[i * 32 + lm] = acc[i][0];
+            } else {
+#pragma unroll
+                for (int i = 0; i < BB; ++i) {
+                    const int co = cmap[c0 + i * 32 + lm];
+                    if (co >= 0) emit_sym(os, d, d - 1, co, acc[i][0] * job.scale, true);
+                }
+                if (J == 0 && c0 == 0 && lane == 0) emit_sym(os, d, d - 1, d - 1, (float)u.R * job.scale, false);   // R ones
+            }
+        }
+        return;
+    }
+    if (I * TW + wr >= D || J * TW + wc >= D) {
+        pipeline(StaticInt<0>{}, [](unsigned, auto, int) {}, [](int) {}, [](int) {});
+        return;
+    }
+    v16f acc[S::MB][S::NB];
+#pragma unroll
+    for (int i = 0; i < S::MB; ++i)
+#pragma unroll
+        for (int n = 0; n < S::NB; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][n][r] = 0.f;
+    const unsigned a_addr = operand_addr(wr), b_addr = operand_addr(wc) + (DIAG ? 0u : (unsigned)PANEL);
+    v2u a[2][S::MB][PIECES], b[2][S::NB][PIECES];
+    pipeline(StaticInt<(S::MB + S::NB) * PIECES>{}, [&](unsigned stage_off, auto e, int set) {
+        const unsigned aa = a_addr + stage_off, ba = b_addr + stage_off;
+#pragma unroll
+        for (int i = 0; i < S::NB; ++i) KFAC_TILE_READ(b[set], i, ba, e);
+#pragma unroll
+        for (int i = 0; i < S::MB; ++i) KFAC_TILE_READ(a[set], i, aa, e);
+    }, [&](int set) {
+#pragma unroll
+        for (int i = 0; i < S::NB; ++i) KFAC_TILE_ARRIVED(b[set], i);
+#pragma unroll
+        for (int i = 0; i < S::MB; ++i) KFAC_TILE_ARRIVED(a[set], i);
+    }, [&](int set) {
+#pragma unroll
+        for (int e = 0; e < (ES == 2 ? 1 : 2); ++e)
+#pragma unroll
+            for (int i = 0; i < S::MB; ++i)
+#pragma unroll
+                for (int n = 0; n < S::NB; ++n) {
+                    if constexpr (ES == 2)
+                        acc[i][n] = mfma16_halves<KIND == 1>(a[set][i][0], a[set][i][PIECES - 1], b[set][n][0], b[set][n][PIECES - 1], acc[i][n]);
+                    else
+                        acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[set][i][0][e]), __uint_as_float(b[set][n][0][e]), acc[i][n], 0, 0, 0);
+                }
+    });
+
+    // ---- epilogue ----
+    // Stores leave a CU at four lanes per cycle, whatever a lane stores: 16-byte stores wherever four neighbours are there
+    // (4-byte ones took 30 us of a tile's life).
+    if (split) {                                                   // partial sums: in register order, see Partial
+        gfloat* dst = part.tiles + ((size_t)job.split * job.ntiles + job.tile) * (TW * TW) + (size_t)lane * 4;
+#pragma unroll
+        for (int p = 0; p < S::MB; ++p)
+#pragma unroll
+            for (int n = 0; n < S::NB; ++n)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const v4f o = {acc[p][n][4 * q4], acc[p][n][4 * q4 + 1], acc[p][n][4 * q4 + 2], acc[p][n][4 * q4 + 3]};
+                    *(KFAC_AS1 v4f*)(dst + ((wm * S::MB + p) * (TW / 32) + wn * S::NB + n) * 1024 + q4 * 256) = o;
+                }
+        return;
+    }
+    // One 32-row block row at a time through LDS (this wavefront's own part of it): its rows go out along result rows, then
+    // its columns along the rows of the mirror image.  (From the registers the stores would need an address each, which
+    // costs the product loop its registers.)
+    constexpr int W = S::NB * 32, LD = W + 4;
+    static_assert(NW * 32 * LD * 4 <= tile_ring_bytes<TW, ES>(), "the epilogue's staging fits the ring");
+    float* epi = (float*)smem + wave * (32 * LD);
+    constexpr int NV = 32 * W / 256;                               // 16-byte vectors per lane of one block row
+    // A block row that is all there, below the diagonal and in the caller's column order (nearly all of a large factor's).
+    auto whole = [&](int p) {
+        const int rb = wr + p * 32;
+        return !v.mapped && !packed && I * TW + rb + 32 <= D && J * TW + wc + W <= D && (!DIAG || rb >= wc + W);
+    };
+    constexpr int VPR = W / 4;                                     // vectors per row
+    const int vr = lane / VPR, vc = lane % VPR * 4;                // this lane's vector of the first rows
+    gfloat* direct0 = out + (size_t)(I * TW + wr + vr) * d + J * TW + wc + vc;
+    const size_t row_step = (size_t)(64 / VPR) * d;
+    // Running average: the old values of block row p, fetched one block row ahead, so that a tile waits for memory once
+    // and not once per block row.  (Two ahead do not fit the registers beside the accumulators.)
+    v4f old[2][NV];
+    auto fetch_old = [&](int p, v4f (&o)[NV]) {
+        if (!whole(p)) return;
+        const gfloat* src = direct0 + (size_t)(p * 32) * d;
+#pragma unroll
+        for (int k = 0; k < NV; ++k) o[k] = *(const KFAC_AS1 v4f_a4*)(src + k * row_step);
+    };
+    // Elsewhere: element by element.  Elements that are not there (beyond the matrix, padding, the other half of a diagonal
+    // tile) get an offset outside the buffer, which the hardware drops: no branches, so that many are in flight.
+    const int dc = lane % W, dr = lane / W;
+    constexpr int RPP = 64 / W;                                    // rows per pass of the wavefront's lanes
+    const int cod = cmap[wc + dc];
+    const unsigned out_bytes = packed ? 2u * d * (d + 1) : 4u * d * d;      // (d < 32768)
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)out, 0, out_bytes, 0x00027000);
+    auto direct_off = [&](int rl, int rd) -> unsigned {            // element (row rl of the tile, this lane's column)
+        return rd >= 0 && cod >= 0 && !(DIAG && rl < wc + dc) ? (unsigned)(rd + cod) * 4u : ~0u;
+    };
+    if (ema) fetch_old(0, old[0]);
+#pragma unroll
+    for (int p = 0; p < S::MB; ++p) {
+        const int rb = wr + p * 32;
+#pragma unroll
+        for (int n = 0; n < S::NB; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) epi[((r >> 2) * 8 + h * 4 + (r & 3)) * LD + n * 32 + lm] = acc[p][n][r] * job.scale;
+        if (ema && p + 1 < S::MB) fetch_old(p + 1, old[(p + 1) & 1]);
+        if (whole(p)) {
+            gfloat* dst = direct0 + (size_t)(p * 32) * d;
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                float* e = &epi[(k * (64 / VPR) + vr) * LD + vc];
+                v4f val = *(const v4f*)e;
+                if (ema) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) val[i] = fmaf(os.decay, old[p & 1][k][i], os.one_minus * val[i]);
+                    *(v4f*)e = val;                                // (the mirror image gets the same new values)
+                }
+                *(KFAC_AS1 v4f_a4*)(dst + k * row_step) = val;
+            }
+            // mirror image: lane = four rows of one column, eight columns per pass
+            gfloat* mir = out + (size_t)(J * TW + wc + (lane >> 3)) * d + I * TW + rb + (lane & 7) * 4;
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                const float* e = &epi[(lane & 7) * 4 * LD + k * 8 + (lane >> 3)];
+                const v4f val = {e[0], e[LD], e[2 * LD], e[3 * LD]};
+                *(KFAC_AS1 v4f_a4*)(mir + (size_t)(k * 8) * d) = val;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            continue;
+        }
+        if (!packed) {
+#pragma unroll
+            for (int k0 = 0; k0 < 32 / RPP; k0 += 16) {
+                int rd[16];
+                float val[16];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    rd[k] = rmapd[rb + (k0 + k) * RPP + dr];
+                    val[k] = epi[((k0 + k) * RPP + dr) * LD + dc];
+                }
+                if (ema) {
+                    float o[16];
+#pragma unroll
+                    for (int k = 0; k < 16; ++k)
+                        o[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, direct_off(rb + (k0 + k) * RPP + dr, rd[k]), 0, 0));
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) {
+                        val[k] = fmaf(os.decay, o[k], os.one_minus * val[k]);
+                        epi[((k0 + k) * RPP + dr) * LD + dc] = val[k];
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 16; ++k)
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val[k]), rsrc, direct_off(rb + (k0 + k) * RPP + dr, rd[k]), 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        const int row = rb + lm, ro = rmap[row];
+#pragma unroll
+        for (int c0 = 0; c0 < W; c0 += 32) {
+            int cd[16];
+            float val[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const int c = c0 + 2 * k + h;
+                cd[k] = (packed ? cmap : cmapd)[wc + c];
+                val[k] = epi[lm * LD + c];
+            }
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const int col = wc + c0 + 2 * k + h;
+                const bool ok = ro >= 0 && cd[k] >= 0 && !(DIAG && (packed ? row < col : row <= col));
+                const unsigned e = packed ? (unsigned)(packed_row_base(min(ro, cd[k]), d) + max(ro, cd[k])) : (unsigned)(cd[k] + ro);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val[k]), rsrc, ok ? e * 4u : ~0u, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+// One tile (workgroup `wg` of ntiles * nsplit, padded to a multiple of 8) of one factor build.
+template <int TW, int KIND>
+__device__ __forceinline__ void factor_tile(const View& v, const KFAC_AS1 unsigned char* x, float scale, const OutSpec& os,
+                                            const Partial& part, int rows_per_split, int tiles_dim, int ntiles, int nsplit,
+                                            int wg, unsigned char* smem) {
+    // The caller pads every build's workgroup count to a multiple of 8 and starts it at a multiple of 8, so that
+    // wg % 8 is the XCD this workgroup runs on (workgroups are dealt to the 8 XCDs round-robin).  XCD x takes the
+    // x-th contiguous eighth of the build's work list (row ranges in order, tiles in blocked order inside a range): the
+    // tiles of a row range, which all read the same rows, share one L2 instead of fetching them eight times.
+    TileJob job;
+    {
+        const int work = ntiles * nsplit;
+        const int per_xcd = (work + 7) >> 3;
+        const int unit = (wg & 7) * per_xcd + (wg >> 3);
+        if ((wg >> 3) >= per_xcd || unit >= work) return;          // padding workgroup (uniform, before any barrier)
+        job.split = unit / ntiles;
+        job.tile = unit - job.split * ntiles;
+    }
+    tri_decode_blocked<4>(tiles_dim, job.tile, job.I, job.J);      // (tiles that share row panels run together: see the function)
+    job.r_begin = job.split * rows_per_split;
+    job.r_end = min(v.u.R, job.r_begin + rows_per_split);
+    job.tiles_dim = tiles_dim;
+    job.ntiles = ntiles;
+    job.nsplit = nsplit;
+    job.scale = scale;
+    const bool plain = is_plain(v.u);
+    if (job.I == job.J) {
+        if (plain) factor_tile_run<TW, KIND, true, true>(v, x, job, os, part, smem);
+        else factor_tile_run<TW, KIND, false, true>(v, x, job, os, part, smem);
+    } else if constexpr (TW > 64) {                                // (64-wide matrices are one tile)
+        if (plain) factor_tile_run<TW, KIND, true, false>(v, x, job, os, part, smem);
+        else factor_tile_run<TW, KIND, false, false>(v, x, job, os, part, smem);
+    }
+}
+
+}  // namespace kfac

@@ -1,0 +1,77 @@
+"""Matrix-core factor builder at the sizes where it can go wrong: tile widths 64 / 128 / 256 and one column either side,
+padded channels, both column orders and layouts, every dtype, split and unsplit rows, every kind of output."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import kfac_oracle as ko
+from paper_1811_12019_amd import binding as kb
+from paper_1811_12019_amd import synth
+from tests.test_parity_gpu import DEV, FACTOR_TOL, _NP_ROUND, check_factor_pair, rel_fro, rel_max
+
+pytestmark = pytest.mark.gpu
+
+NHWC, NCHW = kb.KFAC_NHWC, kb.KFAC_NCHW
+CKK, KKC = kb.KFAC_ORDER_C_KH_KW, kb.KFAC_ORDER_KH_KW_C
+
+EDGE_SHAPES = [
+    synth.LayerShape("w64", 2, 64, 9, 9, 64, 1, 1, 1, 0),                  # exactly one narrow tile; odd pixel count
+    synth.LayerShape("w65", 3, 65, 5, 7, 127, 1, 1, 1, 0),
+    synth.LayerShape("w128", 1, 128, 6, 6, 128, 1, 1, 1, 0),
+    synth.LayerShape("w129", 2, 129, 3, 5, 136, 1, 1, 1, 0),
+    synth.LayerShape("w256long", 8, 256, 48, 47, 257, 1, 1, 1, 0),         # 18,048 rows: split
+    synth.LayerShape("k3c16", 4, 16, 19, 18, 24, 3, 3, 1, 1),              # 144 columns
+    synth.LayerShape("k3c57s2", 4, 57, 23, 21, 40, 3, 3, 2, 1),            # 64 padded channels, stride 2: 576 columns
+    synth.LayerShape("k5c12", 2, 12, 14, 15, 9, 5, 5, 1, 2, has_bias=False),
+    synth.LayerShape("fc1", 1, 520, 1, 1, 10, 1, 1, 1, 0),                 # one row
+    synth.LayerShape("k3long", 8, 72, 41, 40, 33, 3, 3, 1, 1),             # 13,120 rows x 648 columns: 256-wide tiles, split
+]
+
+
+@pytest.mark.parametrize("shape", EDGE_SHAPES, ids=lambda s: s.name)
+@pytest.mark.parametrize("layout,dtype,order", [
+    (NHWC, kb.KFAC_BF16, KKC), (NHWC, kb.KFAC_F16, CKK), (NCHW, kb.KFAC_BF16, CKK), (NCHW, kb.KFAC_F16, KKC),
+    (NHWC, kb.KFAC_F32, CKK), (NCHW, kb.KFAC_F32, CKK), (NCHW, kb.KFAC_F32, KKC)])
+def test_factor_tile_edges(shape, layout, dtype, order):
+    check_factor_pair(shape, layout, dtype, order, seed=7)
+
+
+@pytest.mark.parametrize("layout,dtype,order", [(NCHW, kb.KFAC_BF16, CKK), (NHWC, kb.KFAC_BF16, KKC), (NCHW, kb.KFAC_F32, CKK)])
+def test_narrow_layer_in_any_layout(layout, dtype, order):
+    """conv1-like: 3 channels, 4,900 rows (16-bit: gathered element by element; fp32: repacked)."""
+    check_factor_pair(synth.LayerShape("g", 4, 3, 70, 70, 16, 7, 7, 2, 3, relu_input=False), layout, dtype, order, seed=3)
+
+
+@pytest.mark.parametrize("many", [False, True])
+@pytest.mark.parametrize("layout,dtype,order", [(NHWC, kb.KFAC_BF16, KKC), (NCHW, kb.KFAC_BF16, CKK), (NCHW, kb.KFAC_F32, CKK)])
+def test_factor_outputs(many, layout, dtype, order):
+    """Running average and packed triangle against the plain build, bit for bit, and the plain build against the oracle;
+    alone (fine row splits) and among enough builds for the coarse splits and the 256-wide tiles."""
+    shapes = [EDGE_SHAPES[i] for i in (1, 3, 5, 6, 9)] + [synth.LayerShape("k1long", 6, 48, 50, 50, 304, 1, 1, 1, 0)]
+    builds, refs = [], []
+    for s in shapes:
+        act, gout = _NP_ROUND[dtype](synth.make_act(s, 2)), _NP_ROUND[dtype](synth.make_gout(s, 2))
+        desc = kb.make_desc(s, layout, dtype, order)
+        builds.append((kb.KFAC_OP_FACTOR_A, desc, kb.to_device_tensor(act, layout, dtype, DEV), s.d_A))
+        builds.append((kb.KFAC_OP_FACTOR_G, desc, kb.to_device_tensor(gout, layout, dtype, DEV), s.d_G))
+        refs += [ko.factor_A(act, s.kh, s.kw, s.stride, s.pad, True, order), ko.factor_G(gout)]
+    reps = 2 if many else 1                                                # 24 builds, or 12
+    builds, refs = builds * reps, refs * reps
+    if not many:
+        builds, refs = builds[:10], refs[:10]
+    full = [torch.full((d, d), float("nan"), device=DEV) for _, _, _, d in builds]
+    packed = [torch.full((kb.packed_elems(d),), float("nan"), device=DEV) for _, _, _, d in builds]
+    S0 = [torch.eye(d, device=DEV) * 2.0 + 0.25 for _, _, _, d in builds]
+    run, plain = [s.clone() for s in S0], [s.clone() for s in S0]
+    items = lambda outs: [(op, desc, x, o, 0.0) for (op, desc, x, _), o in zip(builds, outs)]
+    kb.kfac_factor_batched(kb.FactorBatch(items(full), device=DEV))
+    kb.kfac_factor_batched(kb.FactorBatch(items(packed), device=DEV, packed=True))
+    kb.kfac_factor_batched(kb.FactorBatch(items(full), device=DEV, running=run, decay=0.9))
+    kb.kfac_ema_batched(kb.EmaBatch(plain, full), 0.9)
+    torch.cuda.synchronize()
+    for ref, f, p, r, want_r in zip(refs, full, packed, run, plain):
+        got = f.cpu().numpy()
+        assert rel_fro(got, ref) < FACTOR_TOL and rel_max(got, ref) < FACTOR_TOL
+        np.testing.assert_array_equal(got, got.T)
+        np.testing.assert_array_equal(p.cpu().numpy(), ko.pack_upper(got).astype(np.float32))
+        np.testing.assert_array_equal(r.cpu().numpy(), want_r.cpu().numpy())
