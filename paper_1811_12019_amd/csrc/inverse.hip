@@ -290,7 +290,8 @@ __device__ inline WsView ws_view(gfloat* ws, int dim) {
     return v;
 }
 
-// W(lower) = S(lower) + lambda I; info = 0.
+// W(lower) = S(lower) + lambda I; info = 0.  Tiles on the diagonal get both triangles (of S's lower one): the pivot code
+// works on whole 32 x 32 diagonal blocks, which the updates keep whole.
 __global__ __launch_bounds__(256) void inv_init_kernel(Batch b) {
     int m, tile;
     locate(b, blockIdx.x, m, tile);
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(256) void inv_init_kernel(Batch b) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {                    // loads only: arithmetic on a guarded load would make the
             const int row = I * NB + r8 + 2 * i + rh;    // compiler wait for each load in turn
-            v[i] = (row < d && col <= row) ? S[(size_t)row * d + col] : 0.f;
+            v[i] = (row < d && col < d && (I == J || col <= row)) ? S[(size_t)max(row, col) * d + min(row, col)] : 0.f;
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -321,89 +322,86 @@ __global__ __launch_bounds__(256) void inv_init_kernel(Batch b) {
 }
 
 // ---- pivot block -----------------------------------------------------------------------------------------------
-// Inverse of the (at most 128 x 128) pivot block by a symmetric sweep in 16-wide sub-blocks.  The block D lives in
-// registers in MFMA accumulator layout (4 wavefronts x 64 x 64 quadrants); per sub-block j:
-//   1. the owners of D's columns j copy them to LDS (U16, 128 x 16);
-//   2. wavefront 0 inverts the 16 x 16 diagonal sub-block with a register sweep (quad broadcasts + bpermute);
-//   3. every thread computes its part of T16 = U16 . P16; the rows of the sub-block itself are set to -P16;
-//   4. D -= T16 . U16^T on the matrix cores (K = 16), then rows / columns j of D are overwritten with T16.
+// Inverse of the (at most 128 x 128) pivot block by a symmetric sweep in 16-wide sub-blocks.  The lower triangle of the
+// block D lives in registers in MFMA accumulator layout (wavefronts 0, 2, 3: the 64 x 64 quadrants on and below the
+// diagonal, as whole 32 x 32 blocks); wavefront 1, whose quadrant lies above the diagonal, looks ahead: it inverts the next
+// 16 x 16 diagonal sub-block while the others update D.  Per sub-block j:
+//   1. T16 = U16 . P16 (all wavefronts; U16 = D's columns j, in LDS; the rows of the sub-block itself become -P16);
+//   2. wavefronts 0, 2, 3: D -= T16 . U16^T on the matrix cores, columns / rows j of D become T16, and the owners copy
+//      columns / rows j + 1 and diagonal sub-block j + 2 to LDS for the next round;
+//      wavefront 1: takes sub-block j + 1, which the round before left in LDS, through this round's update and inverts it.
 // Padding with the identity makes ragged blocks (fewer than 128 rows) need no special cases.
+// One workgroup, bound by its chain of dependent steps.  Look-ahead, the row-broadcast elimination (invert16_wave) and
+// keeping the lower triangle alone took an update launch that a full block's sweep paces from 36.3 to 27.5 us (2049 wide,
+// one matrix alone).
 constexpr int PSB = 16;          // sub-block
 constexpr int PLD = 20;          // LDS row stride of the 16-wide panels (float4 aligned)
 
-__device__ __forceinline__ float quad_bcast(float x, int k) {   // value of lane (4*(lane/4) + k)
-    const int v = __float_as_int(x);
-    int r;
-    switch (k) {
-        case 0: r = __builtin_amdgcn_update_dpp(v, v, 0x00, 0xf, 0xf, false); break;
-        case 1: r = __builtin_amdgcn_update_dpp(v, v, 0x55, 0xf, 0xf, false); break;
-        case 2: r = __builtin_amdgcn_update_dpp(v, v, 0xAA, 0xf, 0xf, false); break;
-        default: r = __builtin_amdgcn_update_dpp(v, v, 0xFF, 0xf, 0xf, false); break;
-    }
-    return __int_as_float(r);
+// x of lane S of the lane's own row of 16 lanes
+template <int S>
+__device__ __forceinline__ float row_bcast(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + S, 0xf, 0xf, true));
+}
+// x of the same lane of row G (of the four rows of 16 lanes), in every row
+template <int G>
+__device__ __forceinline__ float group_bcast(float x) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);   // rows 0 1 0 1 / 2 3 2 3
+    const unsigned y = a[G >> 1];
+    const auto b = __builtin_amdgcn_permlane16_swap(y, y, false, false);                                     // the even / the odd one
+    return __uint_as_float(b[G & 1]);
 }
 
-// One wavefront: Ps = inverse of the symmetric positive definite 16 x 16 block D16 (rows of Us), lower triangle
-// taken as the truth.  Lane (i = lane/4, g = lane%4) holds E[i][4g..4g+3].  Returns the 1-based index of the first
-// non-positive pivot, or 0.
-__device__ __forceinline__ int invert16_wave(const float* __restrict__ D16, int ld, float* __restrict__ Ps) {
-    const int lane = threadIdx.x & 63, i = lane >> 2, g = lane & 3;
-    float E[4];
+// One elimination step of invert16_wave.  With r = 1 / sqrt(p) and u = r E(., S) the rank-1 update is -u u^T, the same
+// product on both sides of the diagonal: E stays symmetric to the last bit, so that row S may stand for column S.  (Rows and
+// columns that drift apart by rounding cost an ill-conditioned block most of its accuracy.)
+template <int S>
+__device__ __forceinline__ void invert16_step(float (&E)[4], int i, int g, float (&piv)[16]) {
+    constexpr int gs = S >> 2, qs = S & 3;
+    const float vi = group_bcast<gs>(E[qs]);               // E(i, S)
+    const float p = row_bcast<S>(vi);                      // E(S, S)
+    piv[S] = p;
+    float r = __builtin_amdgcn_rsqf(p);                    // 1 ulp estimate + one Newton step
+    r = fmaf(0.5f * r, fmaf(-p * r, r, 1.0f), r);
+    const bool prow = i == S;
+    const float u = vi * r, m = prow ? r : -u;             // row S becomes u r, the others lose u times it
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int c = 4 * g + q;
-        E[q] = D16[max(i, c) * ld + min(i, c)];
-    }
+    for (int q = 0; q < 4; ++q) E[q] = fmaf(row_bcast<S>(E[q]) * r, m, prow ? 0.f : E[q]);
+    E[qs] = g == gs ? (prow ? -(r * r) : u * r) : E[qs];
+}
+
+// One wavefront: Ps = inverse of the symmetric positive definite 16 x 16 block whose element (i, 4 g + q) lane
+// (i = lane % 16, g = lane / 16) holds in E[q], lower triangle taken as the truth.  Returns the 1-based index of the first
+// non-positive pivot, or 0.  A step is about 30 instructions, none of them through LDS.
+__device__ __forceinline__ int invert16_wave(float (&E)[4], float* __restrict__ Ps) {
+    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    float piv[16];
+    *(v4f*)&Ps[i * PLD + 4 * g] = v4f{E[0], E[1], E[2], E[3]};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) E[q] = Ps[max(i, 4 * g + q) * PLD + min(i, 4 * g + q)];
+    invert16_step<0>(E, i, g, piv);  invert16_step<1>(E, i, g, piv);  invert16_step<2>(E, i, g, piv);  invert16_step<3>(E, i, g, piv);
+    invert16_step<4>(E, i, g, piv);  invert16_step<5>(E, i, g, piv);  invert16_step<6>(E, i, g, piv);  invert16_step<7>(E, i, g, piv);
+    invert16_step<8>(E, i, g, piv);  invert16_step<9>(E, i, g, piv);  invert16_step<10>(E, i, g, piv); invert16_step<11>(E, i, g, piv);
+    invert16_step<12>(E, i, g, piv); invert16_step<13>(E, i, g, piv); invert16_step<14>(E, i, g, piv); invert16_step<15>(E, i, g, piv);
+    *(v4f*)&Ps[i * PLD + 4 * g] = v4f{-E[0], -E[1], -E[2], -E[3]};
     int bad = 0;
 #pragma unroll
-    for (int s = 0; s < 16; ++s) {
-        const float vi = quad_bcast(E[s & 3], s >> 2);                                    // E(i, s)
-        const float p = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(vi), 4 * s));   // E(s, s)
-        if (!(p > 0.f) && bad == 0) bad = s + 1;
-        float ip = __builtin_amdgcn_rcpf(p);              // 1 ulp estimate + one Newton step: ample for a pivot
-        ip = ip * fmaf(-p, ip, 2.0f);
-        float vc[4];                                                                      // E(4g+q, s) = E(s, 4g+q)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            vc[q] = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (4 * (4 * g + q)), __float_as_int(vi)));
-        const float wi = vi * ip;
-        // (selects, not branches: the pivot row's lanes would otherwise run a path of their own after everybody else's)
-        const bool prow = i == s, pcol = g == (s >> 2);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float upd = fmaf(-wi, vc[q], E[q]), piv = vc[q] * ip;
-            E[q] = prow ? piv : upd;
-        }
-        E[s & 3] = pcol ? (prow ? -ip : wi) : E[s & 3];
-    }
-    // E = -P16 up to rounding asymmetry: publish, then re-read the lower triangle so that P16 is exactly symmetric
-#pragma unroll
-    for (int q = 0; q < 4; ++q) Ps[i * PLD + 4 * g + q] = -E[q];
-    float sym[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int c = 4 * g + q;
-        sym[q] = Ps[max(i, c) * PLD + min(i, c)];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) Ps[i * PLD + 4 * g + q] = sym[q];
+    for (int s = 15; s >= 0; --s) bad = piv[s] > 0.f ? bad : s + 1;
     return bad;
 }
 
-// LDS of the pivot code: the block's packed lower triangle (row r holds columns 0..r) while it is brought into or
-// out of the registers, and the sweep's panels in between, in the same memory.
-constexpr int TRI_FLOATS = NB * (NB + 1) / 2;                        // 33,024 bytes
-constexpr int PIV_US = 0, PIV_TS = NB * PLD, PIV_PS = 2 * NB * PLD, PIV_BAD = PIV_PS + PSB * PLD;
-constexpr int PIV_LDS_FLOATS = TRI_FLOATS;
-static_assert(PIV_BAD + 1 <= PIV_LDS_FLOATS, "the sweep's panels must fit the triangle's memory");
+// LDS of the pivot code: the sweep's panels (U16 and P16 of two sub-blocks, T16, two diagonal sub-blocks); before and after
+// it, in the same memory, the block's packed lower triangle (row r holds columns 0..r).
+constexpr int TRI_FLOATS = NB * (NB + 1) / 2;
+constexpr int PIV_US = 0, PIV_TS = 2 * NB * PLD, PIV_PS = 3 * NB * PLD, PIV_DG = PIV_PS + 2 * PSB * PLD,
+              PIV_BAD = PIV_DG + 2 * PSB * PSB;
+constexpr int PIV_LDS_FLOATS = PIV_BAD + 4;
+static_assert(TRI_FLOATS <= PIV_LDS_FLOATS, "one buffer serves both uses");
 
 __device__ __forceinline__ int tri_at(int r, int c) { return ((r * (r + 1)) >> 1) + c; }          // r >= c
 __device__ __forceinline__ int tri_sym(int r, int c) { return r >= c ? tri_at(r, c) : tri_at(c, r); }
 
 // D (accumulator layout, all four quadrants) <- the symmetric block whose lower triangle is in tri, bordered by the
-// identity beyond nb.  HAVE_LOWER: the registers already hold the lower triangle, only the rest is fetched.
-// Ends with a barrier: tri may be overwritten afterwards.
-template <bool HAVE_LOWER = false>
+// identity beyond nb.  Ends with a barrier: tri may be overwritten afterwards.
 __device__ __forceinline__ void pivot_fill(v16f (&acc)[2][2], const float* __restrict__ tri, int nb) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
 #pragma unroll
@@ -414,173 +412,223 @@ __device__ __forceinline__ void pivot_fill(v16f (&acc)[2][2], const float* __res
             for (int r = 0; r < 16; ++r) {
                 const int row = acc_row(wm, mb, r, lane), col = acc_col(wn, nbk, lane);
                 if (!(row < nb && col < nb)) acc[mb][nbk][r] = row == col ? 1.f : 0.f;
-                else if (!HAVE_LOWER || row < col) acc[mb][nbk][r] = tri[tri_sym(row, col)];
+                else acc[mb][nbk][r] = tri[tri_sym(row, col)];
             }
     __syncthreads();
 }
 
-// D (accumulator layout) holds a symmetric block's lower triangle; the rest is filled in from it, bordered by the
-// identity beyond nb.  Three 64 x 64 transposes through LDS (3 x 4096 floats): the quadrant below the diagonal goes,
-// transposed, to the wavefront that owns the quadrant above it, and each diagonal quadrant to itself.  Element (a, b)
-// of a quadrant is kept at b * 64 + (a ^ b): writes (lanes along b) and reads (lanes along a) both touch 32 different
-// banks.  Ends with a barrier: lds may be overwritten afterwards.
-__device__ __forceinline__ void pivot_symmetrize(v16f (&acc)[2][2], float* __restrict__ lds, int nb) {
+// identity beyond nb
+__device__ __forceinline__ void pivot_border(v16f (&acc)[2][2], int nb) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
-    const int lm = lane & 31, h = lane >> 5;
-    // writers: wavefronts (0,0), (1,0), (1,1) -> squares 0, 1, 2
-    if (!(wm == 0 && wn == 1)) {
-        float* sq = lds + (wm + wn) * 4096;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+    for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
+        for (int nbk = 0; nbk < 2; ++nbk)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int a = mb * 32 + (r >> 2) * 8 + h * 4 + (r & 3), b = nbk * 32 + lm;
-                    sq[b * 64 + (a ^ b)] = acc[mb][nbk][r];
-                }
-    }
-    __syncthreads();
-    // readers: target (a, b) of a quadrant takes source (b, a) of square (0,0) -> 0, (0,1) -> 1, (1,1) -> 2
-    if (!(wm == 1 && wn == 0)) {
-        const float* sq = lds + (wm + wn) * 4096;
-        const bool whole = wm != wn;                     // the quadrant above the diagonal: every element
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int a = mb * 32 + (r >> 2) * 8 + h * 4 + (r & 3), b = nbk * 32 + lm;
-                    const float v = sq[a * 64 + (b ^ a)];
-                    acc[mb][nbk][r] = (whole || a < b) ? v : acc[mb][nbk][r];
-                }
-    }
-    if (nb < NB) {                                       // (uniform) ragged block: identity beyond nb
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = acc_row(wm, mb, r, lane), col = acc_col(wn, nbk, lane);
-                    if (!(row < nb && col < nb)) acc[mb][nbk][r] = row == col ? 1.f : 0.f;
-                }
-    }
-    __syncthreads();
+            for (int r = 0; r < 16; ++r) {
+                const int row = acc_row(wm, mb, r, lane), col = acc_col(wn, nbk, lane);
+                if (!(row < nb && col < nb)) acc[mb][nbk][r] = row == col ? 1.f : 0.f;
+            }
 }
 
-// The symmetric sweep of D in 16-wide sub-blocks (see above); lds: PIV_LDS_FLOATS floats.  Returns (to every thread)
-// the 1-based index inside the block of the first non-positive pivot, or 0.  Ends with a barrier.
+// T16 = U16 . P16 for the 32 rows of this wavefront (v_mfma_f32_16x16x4_f32: lane l supplies A[l % 16][l / 16] and
+// B[l / 16][l % 16] and receives C[4 (l / 16) + i][l % 16], i < 4); the rows of sub-block jb itself become -P16.
+__device__ __forceinline__ void sweep_panel(const float* __restrict__ Us, const float* __restrict__ Ps, float* __restrict__ Ts,
+                                            int wave, int jb) {
+    const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+    float a[2][4], b[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        b[kk] = Ps[(4 * kk + lq) * PLD + l16];
+#pragma unroll
+        for (int rbi = 0; rbi < 2; ++rbi) a[rbi][kk] = Us[((2 * wave + rbi) * PSB + l16) * PLD + 4 * kk + lq];
+    }
+    v4f c4[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int rbi = 0; rbi < 2; ++rbi) c4[rbi] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rbi][kk], b[kk], c4[rbi], 0, 0, 0);
+#pragma unroll
+    for (int rbi = 0; rbi < 2; ++rbi) {
+        const int rb = 2 * wave + rbi;
+        if (rb == jb) {                                        // (uniform)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Ts[(rb * PSB + 4 * lq + i) * PLD + l16] = -Ps[(4 * lq + i) * PLD + l16];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Ts[(rb * PSB + 4 * lq + i) * PLD + l16] = c4[rbi][i];
+        }
+    }
+}
+
+// Between the phases of the sweep: everybody's LDS accesses are done.
+__device__ __forceinline__ void sweep_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// U16 of sub-block jb: D's columns 16 jb .. + 15, rows above the 32 x 32 diagonal block from D's rows (transposed).
+__device__ __forceinline__ void sweep_publish(const v16f (&acc)[2][2], int wm, int wn, int jb, float* __restrict__ Us) {
+    const int lane = threadIdx.x & 63, lm = lane & 31, h = lane >> 5;
+    const int ow = jb >> 2, ob = (jb >> 1) & 1, oh = jb & 1;   // wavefront row / column, block inside it, half of the block
+    if (wn == ow && wm >= ow && (lm >> 4) == oh) {
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+            if (wm > ow || mb >= ob) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) Us[acc_row(wm, mb, r, lane) * PLD + (lm & 15)] = acc[mb][ob][r];
+            }
+    }
+    if (wm == ow && wn <= ow) {
+#pragma unroll
+        for (int nbk = 0; nbk < 2; ++nbk)
+            if (wn < ow || nbk < ob) {
+#pragma unroll
+                for (int r8 = 0; r8 < 8; r8 += 4) {            // four consecutive rows of D: one 16-byte store
+                    const v4f x = {acc[ob][nbk][oh * 8 + r8], acc[ob][nbk][oh * 8 + r8 + 1], acc[ob][nbk][oh * 8 + r8 + 2], acc[ob][nbk][oh * 8 + r8 + 3]};
+                    *(v4f*)&Us[acc_col(wn, nbk, lane) * PLD + (r8 >> 2) * 8 + h * 4] = x;
+                }
+            }
+    }
+}
+
+// Diagonal sub-block jb, as v_mfma_f32_16x16x4_f32 would leave it: float 4 lane + i is row 4 (lane / 16) + i, column lane % 16.
+__device__ __forceinline__ void sweep_publish_diagonal(const v16f (&acc)[2][2], int wm, int wn, int jb, float* __restrict__ DG) {
+    const int lane = threadIdx.x & 63, lm = lane & 31, h = lane >> 5;
+    const int ob = (jb >> 1) & 1, oh = jb & 1;
+    if (wm == (jb >> 2) && wn == wm && (lm >> 4) == oh) {
+#pragma unroll
+        for (int r8 = 0; r8 < 8; r8 += 4) {
+            const int r = oh * 8 + r8;
+            const v4f x = {acc[ob][ob][r], acc[ob][ob][r + 1], acc[ob][ob][r + 2], acc[ob][ob][r + 3]};
+            *(v4f*)&DG[(((r8 >> 2) * 2 + h) * 16 + (lm & 15)) * 4] = x;
+        }
+    }
+}
+
+// The symmetric sweep of D in 16-wide sub-blocks (see above); lds: PIV_LDS_FLOATS floats, free on entry.  Returns (to every
+// thread) the 1-based index inside the block of the first non-positive pivot, or 0.  Ends with a barrier.
+// Of acc, the 32 x 32 blocks on and below the diagonal are used and valid afterwards.
 __device__ __forceinline__ int pivot_sweep(v16f (&acc)[2][2], int nb, float* __restrict__ lds) {
-    float* __restrict__ Us = lds + PIV_US;
     float* __restrict__ Ts = lds + PIV_TS;
-    float* __restrict__ Ps = lds + PIV_PS;
+    float* __restrict__ DG = lds + PIV_DG;
     int* bad = (int*)(lds + PIV_BAD);
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1;
     const int lm = lane & 31, h = lane >> 5;
-    if (t == 0) *bad = 0;
-#pragma unroll
-    for (int jb = 0; jb < NB / PSB; ++jb) {
-        const int j0 = jb * PSB;
-        if (j0 >= nb) break;                         // uniform
-        const int own_w = jb >> 2;                   // wn (for columns) / wm (for rows) that owns sub-block jb
-        const int own_b = (jb >> 1) & 1;             // nbk / mb inside the quadrant
-        const int own_h = jb & 1;                    // which 16 of the block's 32
-        __syncthreads();                             // previous sub-step's readers of Us / Ts are done
-        // 1. U16 = D[:, j0 : j0+16]
-        if (wn == own_w && (lm >> 4) == own_h) {
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    Us[acc_row(wm, mb, r, lane) * PLD + (lm & 15)] = acc[mb][own_b][r];
-        }
-        __syncthreads();
-        // 2. P16
-        if (wave == 0) {
-            const int f = invert16_wave(Us + j0 * PLD, PLD, Ps);
-            if (f != 0 && lane == 0 && *bad == 0) *bad = j0 + f;
-        }
-        __syncthreads();
-        // 3. T16 = U16 . P16 on the matrix cores (v_mfma_f32_16x16x4_f32: lane l supplies A[l % 16][l / 16] and
-        //    B[l / 16][l % 16] and receives C[4 (l / 16) + i][l % 16], i < 4); a wavefront takes 32 of the 128 rows.
-        //    The rows of the sub-block itself are replaced by -P16.
+    const int nsb = (nb + PSB - 1) / PSB;
+    if (wave == 1) {
+        const int l16 = lane & 15, lq = lane >> 4;
+        sweep_barrier();                                       // the first U16 and the diagonal sub-blocks are there
+        int first_bad = 0;
         {
-            const int l16 = lane & 15, lq = lane >> 4;
+            const v4f c4 = *(const v4f*)&DG[lane * 4];
+            float E[4] = {c4[0], c4[1], c4[2], c4[3]};
+            first_bad = invert16_wave(E, lds + PIV_PS);
+        }
+        sweep_barrier();
+#pragma unroll 1
+        for (int jb = 0; jb < nsb; ++jb) {
+            const float* Us = lds + PIV_US + (jb & 1) * (NB * PLD);
+            sweep_panel(Us, lds + PIV_PS + (jb & 1) * (PSB * PLD), Ts, 1, jb);
+            sweep_barrier();
+            const int n = jb + 1;
+            if (n < nsb) {                                     // diagonal sub-block n -= T16 . U16^T, and its inverse
+                v4f c4 = *(const v4f*)&DG[(n & 1) * (PSB * PSB) + lane * 4];
+                float a[4], b[4];
 #pragma unroll
-            for (int rbi = 0; rbi < 2; ++rbi) {
-                const int rb0 = (2 * wave + rbi) * PSB;          // first row of this 16-row block
-                v4f c4 = {0.f, 0.f, 0.f, 0.f};
+                for (int i = 0; i < 4; ++i) {
+                    a[i] = -Ts[(n * PSB + l16) * PLD + 4 * i + lq];
+                    b[i] = Us[(n * PSB + l16) * PLD + 4 * i + lq];
+                }
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk)
-                    c4 = __builtin_amdgcn_mfma_f32_16x16x4f32(Us[(rb0 + l16) * PLD + 4 * kk + lq], Ps[(4 * kk + lq) * PLD + l16],
-                                                               c4, 0, 0, 0);
-                const bool own = rb0 == j0;                      // (uniform)
+                for (int kk = 0; kk < 4; ++kk) c4 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], b[kk], c4, 0, 0, 0);
+                // the accumulator layout holds (row 4 lq + i, column l16): by symmetry element (l16, 4 lq + i)
+                float E[4] = {c4[0], c4[1], c4[2], c4[3]};
+                const int f = invert16_wave(E, lds + PIV_PS + (n & 1) * (PSB * PLD));
+                first_bad = f != 0 && first_bad == 0 ? n * PSB + f : first_bad;
+            }
+            if (jb + 1 == nsb && lane == 0) *bad = first_bad;
+            sweep_barrier();
+        }
+    } else {
+        sweep_publish(acc, wm, wn, 0, lds + PIV_US);
+        sweep_publish_diagonal(acc, wm, wn, 0, DG);
+        sweep_publish_diagonal(acc, wm, wn, 1, DG + PSB * PSB);
+        sweep_barrier();
+        sweep_barrier();                                       // wavefront 1 has inverted the first diagonal sub-block
 #pragma unroll
-                for (int i2 = 0; i2 < 4; ++i2) {
-                    const int rl = 4 * lq + i2;
-                    Ts[(rb0 + rl) * PLD + l16] = own ? -Ps[rl * PLD + l16] : c4[i2];
+        for (int jb = 0; jb < NB / PSB; ++jb) {
+            if (jb >= nsb) break;                              // uniform
+            const float* Us = lds + PIV_US + (jb & 1) * (NB * PLD);
+            sweep_panel(Us, lds + PIV_PS + (jb & 1) * (PSB * PLD), Ts, wave, jb);
+            sweep_barrier();
+            // D -= T16 . U16^T  (lane (lm, h) takes k = 8s + 4h .. +3 of both operands), then the fix-ups
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2) {
+                v4f a[2], bb[2];
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb) a[mb] = *(const v4f*)&Ts[(wm * 64 + mb * 32 + lm) * PLD + 8 * s2 + 4 * h];
+#pragma unroll
+                for (int nbk = 0; nbk < 2; ++nbk) bb[nbk] = *(const v4f*)&Us[(wn * 64 + nbk * 32 + lm) * PLD + 8 * s2 + 4 * h];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                    for (int mb = 0; mb < 2; ++mb)
+                        acc[mb][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(-a[mb][i], bb[0][i], acc[mb][0], 0, 0, 0);
+                    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(-a[1][i], bb[1][i], acc[1][1], 0, 0, 0);
+                }
+                if (wm != wn) {                                // (uniform: the quadrant below the diagonal has four blocks)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(-a[0][i], bb[1][i], acc[0][1], 0, 0, 0);
                 }
             }
-        }
-        __syncthreads();
-        // 4. D -= T16 . U16^T  (lane (lm, h) takes k = 8s + 4h .. +3 of both operands), then the fix-ups
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-            v4f a[2], bb[2];
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb) a[mb] = *(const v4f*)&Ts[(wm * 64 + mb * 32 + lm) * PLD + 8 * s2 + 4 * h];
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk) bb[nbk] = *(const v4f*)&Us[(wn * 64 + nbk * 32 + lm) * PLD + 8 * s2 + 4 * h];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
+            const int ow = jb >> 2, ob = (jb >> 1) & 1, oh = jb & 1;
+            // columns j of D <- T16 (and -P16 on the sub-block's own rows)
+            if (wn == ow && wm >= ow && (lm >> 4) == oh) {
 #pragma unroll
                 for (int mb = 0; mb < 2; ++mb)
+                    if (wm > ow || mb >= ob) {
 #pragma unroll
-                    for (int nbk = 0; nbk < 2; ++nbk)
-                        acc[mb][nbk] = __builtin_amdgcn_mfma_f32_32x32x2f32(-a[mb][i], bb[nbk][i], acc[mb][nbk], 0, 0, 0);
-        }
-        // columns j of D <- T16 (and -P16 on the sub-block's own rows)
-        if (wn == own_w && (lm >> 4) == own_h) {
+                        for (int r = 0; r < 16; ++r) acc[mb][ob][r] = Ts[acc_row(wm, mb, r, lane) * PLD + (lm & 15)];
+                    }
+            }
+            // rows j of D <- T16^T
+            if (wm == ow && wn <= ow) {
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
+                for (int nbk = 0; nbk < 2; ++nbk)
+                    if (wn < ow || nbk <= ob) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    acc[mb][own_b][r] = Ts[acc_row(wm, mb, r, lane) * PLD + (lm & 15)];
-        }
-        // rows j of D <- T16^T
-        if (wm == own_w) {
+                        for (int r8 = 0; r8 < 8; r8 += 4) {
+                            const v4f x = *(const v4f*)&Ts[acc_col(wn, nbk, lane) * PLD + (r8 >> 2) * 8 + h * 4];
 #pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r8 = 0; r8 < 8; ++r8) {
-                    const int r = own_h * 8 + r8;                    // registers holding rows 16*own_h .. +15 of block own_b
-                    const int rloc = (r8 >> 2) * 8 + h * 4 + (r8 & 3);   // row inside the sub-block
-                    acc[own_b][nbk][r] = Ts[acc_col(wn, nbk, lane) * PLD + rloc];
-                }
+                            for (int i = 0; i < 4; ++i) acc[ob][nbk][oh * 8 + r8 + i] = x[i];
+                        }
+                    }
+            }
+            if (jb + 1 < NB / PSB) sweep_publish(acc, wm, wn, jb + 1, lds + PIV_US + ((jb + 1) & 1) * (NB * PLD));
+            if (jb + 2 < NB / PSB) sweep_publish_diagonal(acc, wm, wn, jb + 2, DG + (jb & 1) * (PSB * PSB));
+            sweep_barrier();
         }
     }
-    __syncthreads();
     const int f = *bad;
-    __syncthreads();                                 // everybody has read the flag: the memory may be reused
+    sweep_barrier();                                           // everybody has read the flag: the memory may be reused
     return f;
 }
 
-// D holds -P up to rounding asymmetry; its lower triangle is taken as the truth so that P is exactly symmetric.
-// The working copy gets -P; on the matrix's last step the caller's output gets +P (the final sign flip) instead.
-// The workspace gets +P for the panel product.
+// D holds -P up to rounding asymmetry in its lower 32 x 32 blocks.  The working copy gets -P; on the matrix's last step the
+// caller's output gets +P (the final sign flip; lower triangle taken as the truth, so that it is exactly symmetric) instead.
+// The workspace gets +P for the panel product, all of it.
 __device__ __forceinline__ void pivot_write(const v16f (&acc)[2][2], float* __restrict__ tri, const Item& it,
                                             const WsView& ws, int k0, int nb, bool last, bool from_S) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
     const int d = it.dim;
     if (!last && !from_S && nb == NB) {
-        // A full block inside the sweep (the look-ahead pivot's usual case): the registers hold the whole symmetric block,
-        // and a half-wave's 32 lanes hold 32 consecutive floats of a row, so it goes out as it is.
+        // A full block inside the sweep (the look-ahead pivot's usual case) goes out as it lies in the registers: a half-wave's
+        // 32 lanes hold 32 consecutive floats of a row, and four registers four consecutive floats of the mirror image's.
+        if (wave == 1) return;
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
+            for (int nbk = 0; nbk < 2; ++nbk) {
+                if (wm == wn && nbk > mb) continue;            // above the diagonal: not kept
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int row = acc_row(wm, mb, r, lane), col = acc_col(wn, nbk, lane);
@@ -588,6 +636,13 @@ __device__ __forceinline__ void pivot_write(const v16f (&acc)[2][2], float* __re
                     ws.W[(size_t)(k0 + row) * ws.ldw + k0 + col] = x;
                     ws.P[row * NB + col] = -x;
                 }
+                if (wm == wn && nbk == mb) continue;           // a block on the diagonal is its own mirror image
+#pragma unroll
+                for (int r = 0; r < 16; r += 4) {
+                    const v4f x = {-acc[mb][nbk][r], -acc[mb][nbk][r + 1], -acc[mb][nbk][r + 2], -acc[mb][nbk][r + 3]};
+                    *(KFAC_AS1 v4f*)&ws.P[acc_col(wn, nbk, lane) * NB + acc_row(wm, mb, r, lane)] = x;
+                }
+            }
         return;
     }
 #pragma unroll
@@ -1156,7 +1211,7 @@ __device__ __forceinline__ void upd_next_pivot(const Item& it, int step, float* 
     upd_regular_mid_split<false>(c, o, pl, (unsigned char*)lds, acc);
     __syncthreads();                                     // the product's LDS stages are free
     const int t = threadIdx.x;
-    pivot_symmetrize(acc.c, lds, nb);
+    if (nb < NB) pivot_border(acc.c, nb);                // (uniform)
     const int f = pivot_sweep(acc.c, nb, lds);
     if (t == 0 && it.info && f != 0) atomicCAS((int*)it.info, 0, k0 + f);
     pivot_write(acc.c, lds, it, ws, k0, nb, k0 + NB >= d, false);
