@@ -171,16 +171,30 @@ __global__ __launch_bounds__(256) void bn_reduce_kernel(BnReduceBatch b) {
 }
 
 // diag(F)[j] = (1/N) sum_n g[n][j]^2 ;  out[j] = grad[j] / (diag(F)[j] + damping)
+// A small, latency-bound launch (one per layer): 64 columns x 4 groups of samples per workgroup, eight loads in flight per
+// thread, so that 32 samples cost one trip to memory (9.4 us with one thread walking down a column).
 __global__ __launch_bounds__(256) void bn_diag_kernel(const float* g_, int N, int C2, const float* grad, float damping,
                                                       float* fisher_diag, float* out) {
+    __shared__ float part[3][64];
     const gfloat* __restrict__ g = as_global(g_);
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= C2) return;
+    const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+    const int j = blockIdx.x * 64 + lane, jc = min(j, C2 - 1);
+    const float gr = grp == 0 && out ? as_global(grad)[jc] : 0.f;
     float s = 0.f;
-    for (int n = 0; n < N; ++n) { const float v = g[(size_t)n * C2 + j]; s = fmaf(v, v, s); }
+    for (int n0 = grp; n0 < N; n0 += 32) {
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = g[(size_t)min(n0 + 4 * k, N - 1) * C2 + jc];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s = n0 + 4 * k < N ? fmaf(v[k], v[k], s) : s;
+    }
+    if (grp > 0) part[grp - 1][lane] = s;
+    __syncthreads();
+    if (grp > 0 || j >= C2) return;
+    s = (s + part[0][lane]) + (part[1][lane] + part[2][lane]);
     s /= (float)N;
     if (fisher_diag) fisher_diag[j] = s;
-    if (out) out[j] = grad[j] / (s + damping);
+    if (out) out[j] = gr / (s + damping);
 }
 
 }  // namespace kfac
@@ -289,6 +303,6 @@ extern "C" int kfac_bn_diag_precondition(const float* g, int32_t N, int32_t C2, 
                                          float* fisher_diag, float* out, void* stream) {
     if (!g || N <= 0 || C2 <= 0 || (!fisher_diag && !out) || (out && !grad)) return KFAC_ERR_INVALID_ARG;
     if (!(damping >= 0.f)) return KFAC_ERR_INVALID_ARG;
-    KFAC_LAUNCH(bn_diag_kernel, dim3((C2 + 255) / 256), dim3(256), (hipStream_t)stream, g, N, C2, grad, damping, fisher_diag, out);
+    KFAC_LAUNCH(bn_diag_kernel, dim3((C2 + 63) / 64), dim3(256), (hipStream_t)stream, g, N, C2, grad, damping, fisher_diag, out);
     return KFAC_OK;
 }

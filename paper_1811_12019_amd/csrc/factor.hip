@@ -7,7 +7,6 @@
 //                          (workgroup -> (build, tile) through a prefix table).
 //   factor_repack_kernel   brings tensors in other layouts, or with channel counts that are no multiple of a 16-byte
 //                          vector, into that form first (factor_repack.h).
-//   factor_gather_kernel   narrow 16-bit layers with such channel counts and many rows: gathered directly (factor_gather.h).
 //   factor_generic_kernel  small builds that would have to be repacked, and whatever the others cannot take (tensors at
 //                          odd addresses, 32,768 columns), fp32 FMA.
 // All enumerate only the lower-triangular tiles of the symmetric output and mirror them, and all can split the R unfolded
@@ -19,7 +18,6 @@
 #include "common.h"
 #include "factor_tile.h"
 #include "factor_repack.h"
-#include "factor_gather.h"
 
 namespace kfac {
 
@@ -267,7 +265,7 @@ static FactorPlan plan_generic(const Unfold& u) {
 
 // Tile width and row split of a matrix-core build.  `many`: it shares its launch with many others.
 // Width: 256 halves the operand traffic per product against 128; a matrix of up to 128 (64) columns is one tile of that
-// width.  A build launched alone that cannot give every CU a 256-wide tile of at least 2048 rows takes 128-wide ones (4609 columns
+// width.  A build launched alone that cannot give every CU a 256-wide tile of at least 1024 rows takes 128-wide ones (4609 columns
 // of 1568 rows: 171 workgroups of about 90 us, or 666 of three to a CU: 75 us).
 // Split: alone, about two workgroups per CU (one of the 8-wavefront 256-wide ones); among many builds that fill the chip
 // together, only as many as keep a workgroup's share of rows bounded, since every split adds a tile of partial sums to HBM.
@@ -284,7 +282,7 @@ static inline __host__ __device__ FactorPlan plan_tiles(const View& v, bool many
     if (D <= 64) p.tw = 64;
     else if (D <= 128 || f32) p.tw = 128;
     else {
-        const int n = ceil_div(D, 256), splits = R / 2048 > 1 ? R / 2048 : 1;
+        const int n = ceil_div(D, 256), splits = R / 1024 > 1 ? R / 1024 : 1;
         p.tw = many || (long long)n * (n + 1) / 2 * splits >= 256 ? 256 : 128;
     }
     p.tiles_dim = ceil_div(D, p.tw);
@@ -310,26 +308,6 @@ static inline __host__ __device__ Partial partial_of(const View& v, const Factor
 // Whether the matrix-core kernels take a build whose tensor lies at x.
 static bool tile_eligible(const Unfold& u, const void* x, View* v) {
     return make_view(u, v) && ((uintptr_t)x & (v->repack ? (u.dtype == KFAC_F32 ? 3 : 1) : 15)) == 0;
-}
-
-// Narrow 16-bit layers with many rows whose channels are not a multiple of 8.
-static bool gather_eligible(const Unfold& u) {
-    if (u.dtype != KFAC_BF16 && u.dtype != KFAC_F16) return false;
-    if ((u.C & 7) == 0) return false;
-    return u.d <= GA_DMAX && u.R >= 4096 && u.R < (1 << 24);
-}
-
-static FactorPlan plan_gather(const Unfold& u) {
-    FactorPlan p;
-    p.tiles_dim = ceil_div(u.d, GA_T);
-    p.ntiles = p.tiles_dim * (p.tiles_dim + 1) / 2;
-    int ns = u.R / (4 * GA_ROWS);                   // at least 256 rows per workgroup
-    if (ns > 512) ns = 512;                         // two workgroups per CU
-    if (ns < 1) ns = 1;
-    p.rows_per_split = ceil_div(ceil_div(u.R, ns), GA_ROWS) * GA_ROWS;
-    p.nsplit = ceil_div(u.R, p.rows_per_split);
-    p.ws_bytes = (size_t)p.nsplit * p.ntiles * GA_T * GA_T * sizeof(float);
-    return p;
 }
 
 // Where an item's result goes.
@@ -396,7 +374,8 @@ __global__ __launch_bounds__(256) void factor_repack_kernel(FBatch b) {
     Unfold u;
     View v;
     fbatch_item(b, m, it, u, v);
-    if (u.dtype == KFAC_F32) repack_tile<float>(u, v, (const gfloat*)it.x, (KFAC_AS1 unsigned*)it.ws, local, smem);
+    if (v.rows) repack_rows(u, v, (const KFAC_AS1 unsigned short*)it.x, (KFAC_AS1 unsigned*)it.ws, local);
+    else if (u.dtype == KFAC_F32) repack_tile<float>(u, v, (const gfloat*)it.x, (KFAC_AS1 unsigned*)it.ws, local, smem);
     else repack_tile<unsigned short>(u, v, (const KFAC_AS1 unsigned short*)it.x, (KFAC_AS1 unsigned*)it.ws, local, smem);
 }
 
@@ -407,8 +386,12 @@ static inline __host__ __device__ int reduce_wgs(const View& v, const FactorPlan
     return p.ntiles * (p.tw / 32) * (p.tw / 32) + (v.u.has_bias ? ceil_div(v.u.d, 256) : 0);
 }
 
-__global__ __launch_bounds__(256) void factor_tile_reduce_kernel(FBatch b) {
+// GROUPS: groups of 256 threads that share out the splits (narrow matrices of many rows: few sub-blocks, hundreds of splits).
+template <int GROUPS>
+__global__ __launch_bounds__(256 * GROUPS) void factor_tile_reduce_kernel(FBatch b) {
     __shared__ float tr[32][33];
+    __shared__ v4f gsum[GROUPS > 1 ? (GROUPS - 1) * 256 : 1];
+    const int t = threadIdx.x & 255, grp = threadIdx.x >> 8;
     int local;
     const int m = fbatch_locate(b, blockIdx.x, local);
     kfac_factor_item it;
@@ -421,7 +404,8 @@ __global__ __launch_bounds__(256) void factor_tile_reduce_kernel(FBatch b) {
     const Partial part = partial_of(v, pl, it.ws);
     const int D = v.u.d, d = v.dout, T = pl.tw, SB = T / 32, subs = SB * SB;
     if (local >= pl.ntiles * subs) {
-        const int wg = local - pl.ntiles * subs, c = wg * 256 + threadIdx.x;
+        const int wg = local - pl.ntiles * subs, c = wg * 256 + t;
+        if (grp > 0) return;
         if (c == 0) emit_sym(os, d, d - 1, d - 1, (float)u.R * scale, false);
         const int co = result_index(v, c);
         if (co < 0) return;
@@ -439,26 +423,33 @@ __global__ __launch_bounds__(256) void factor_tile_reduce_kernel(FBatch b) {
     const int row0 = I * T + si * 32, col0 = J * T + sj * 32;
     if (row0 < col0 || row0 >= D || col0 >= D) return;               // above the diagonal, or outside the matrix
     const bool dg = row0 == col0;
-    const gfloat* src = part.tiles + (size_t)tile * (T * T) + (si * SB + sj) * 1024 + threadIdx.x * 4;
+    const gfloat* src = part.tiles + (size_t)tile * (T * T) + (si * SB + sj) * 1024 + t * 4;
     const size_t stride = (size_t)pl.ntiles * (T * T);
     v4f s = {0.f, 0.f, 0.f, 0.f};
-    int sp = 0;
-    for (; sp + 4 <= pl.nsplit; sp += 4) {
-        const v4f p0 = *(const KFAC_AS1 v4f*)(src + (size_t)sp * stride);
-        const v4f p1 = *(const KFAC_AS1 v4f*)(src + (size_t)(sp + 1) * stride);
-        const v4f p2 = *(const KFAC_AS1 v4f*)(src + (size_t)(sp + 2) * stride);
-        const v4f p3 = *(const KFAC_AS1 v4f*)(src + (size_t)(sp + 3) * stride);
-        s += p0; s += p1; s += p2; s += p3;
+    int sp = grp;
+    for (; sp + 7 * GROUPS < pl.nsplit; sp += 8 * GROUPS) {
+        v4f p[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) p[k] = *(const KFAC_AS1 v4f*)(src + (size_t)(sp + k * GROUPS) * stride);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += p[k];
     }
-    for (; sp < pl.nsplit; ++sp) s += *(const KFAC_AS1 v4f*)(src + (size_t)sp * stride);
+    for (; sp < pl.nsplit; sp += GROUPS) s += *(const KFAC_AS1 v4f*)(src + (size_t)sp * stride);
+    if constexpr (GROUPS > 1) {                                      // the groups' sums, in a fixed order
+        if (grp > 0) gsum[(grp - 1) * 256 + t] = s;
+        __syncthreads();
+        if (grp > 0) return;
+#pragma unroll
+        for (int k = 0; k < GROUPS - 1; ++k) s += gsum[k * 256 + t];
+    }
     // from the registers' order (Partial) to four columns of one row per thread
     {
-        const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        const int q = t >> 6, lane = t & 63;
 #pragma unroll
         for (int i = 0; i < 4; ++i) tr[8 * q + 4 * (lane >> 5) + i][lane & 31] = s[i];
     }
     __syncthreads();
-    const int lr = threadIdx.x >> 3, lc = (threadIdx.x & 7) * 4;
+    const int lr = t >> 3, lc = (t & 7) * 4;
 #pragma unroll
     for (int i = 0; i < 4; ++i) s[i] = tr[lr][lc + i];
     __syncthreads();
@@ -516,10 +507,6 @@ static size_t item_ws_bytes(const Unfold& u) {
             if (n > need) need = n;
         }
     }
-    if (gather_eligible(u)) {
-        const size_t n = plan_gather(u).ws_bytes;
-        if (n > need) need = n;
-    }
     return align_up(need, 256);
 }
 
@@ -549,19 +536,6 @@ static int launch_tiles(const FBatch& b, hipStream_t stream) {
     return KFAC_OK;
 }
 
-static int run_gather(const Unfold& u, const kfac_factor_item& it, hipStream_t stream) {
-    const float scale = it.scale == 0.f ? 1.0f / (float)u.R : it.scale;
-    const FactorPlan p = plan_gather(u);
-    if (u.dtype == KFAC_F16) {
-        KFAC_LAUNCH(factor_gather_kernel<true>, dim3(p.nsplit), dim3(256), stream, u, it.x, (float*)it.ws, p.rows_per_split);
-    } else {
-        KFAC_LAUNCH(factor_gather_kernel<false>, dim3(p.nsplit), dim3(256), stream, u, it.x, (float*)it.ws, p.rows_per_split);
-    }
-    KFAC_LAUNCH(factor_gather_reduce_kernel, dim3(p.ntiles * GA_T), dim3(256), stream, (const float*)it.ws, p.nsplit, p.ntiles,
-                u.d, scale, out_spec(it));
-    return KFAC_OK;
-}
-
 static int run_generic(const Unfold& u, const kfac_factor_item& it, hipStream_t stream) {
     const float scale = it.scale == 0.f ? 1.0f / (float)u.R : it.scale;
     FactorPlan p = plan_generic(u);
@@ -575,7 +549,7 @@ static int run_generic(const Unfold& u, const kfac_factor_item& it, hipStream_t 
 }
 
 // How a build is served.
-enum Route { ROUTE_TILE, ROUTE_GATHER, ROUTE_GENERIC };
+enum Route { ROUTE_TILE, ROUTE_GENERIC };
 
 // A build that would have to be repacked first is left to the generic kernel while it is so small that the launch this
 // saves weighs more than the arithmetic (512 rows x 145 columns: 13.6 + 3.7 us against 4.6 + 12.4 + 6.3), unless many
@@ -583,7 +557,6 @@ enum Route { ROUTE_TILE, ROUTE_GATHER, ROUTE_GENERIC };
 constexpr long long GENERIC_MACS = 1 << 25;
 
 static Route route_of(const Unfold& u, const void* x, bool many, View* v) {
-    if (gather_eligible(u) && ((uintptr_t)x & 1) == 0) return ROUTE_GATHER;
     if (!tile_eligible(u, x, v)) return ROUTE_GENERIC;
     return v->repack && !many && (long long)u.R * u.d * u.d <= GENERIC_MACS ? ROUTE_GENERIC : ROUTE_TILE;
 }
@@ -613,7 +586,7 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
         n_tile += route_of(u, host[i].x, true, &v) == ROUTE_TILE;
     }
     const int many = n_tile >= 16;
-    FBatch b, r;
+    FBatch b, r, rmany;                                // rmany: builds of many splits (factor_tile_reduce_kernel<4>)
     auto repack = [&]() -> int {
         if (b.count) KFAC_LAUNCH(factor_repack_kernel, dim3(b.prefix[b.count]), dim3(256), stream, b);
         fbatch_clear(b, dev, many);
@@ -641,7 +614,8 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
         while (next < count) {
             fbatch_clear(b, dev, many);
             fbatch_clear(r, dev, many);
-            struct Pick { int item, rows, wgs, reduce; } pick[FMAXB];
+            fbatch_clear(rmany, dev, many);
+            struct Pick { int item, rows, wgs, reduce, nsplit; } pick[FMAXB];
             int n = 0;
             for (; next < count && n < FMAXB; ++next) {
                 Unfold u;
@@ -651,14 +625,14 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
                 const FactorPlan p = plan_tiles(v, many);
                 if (p.tw != VAR_TW[var]) continue;
                 pick[n++] = {next, p.rows_per_split, (int)align_up(p.ntiles * p.nsplit, 8),   // (a multiple of 8: see factor_tile)
-                             p.nsplit > 1 ? reduce_wgs(v, p) : 0};
+                             p.nsplit > 1 ? reduce_wgs(v, p) : 0, p.nsplit};
             }
             if (n == 0) continue;
             // the longest workgroups first: the short ones fill the end of the launch
             std::stable_sort(pick, pick + n, [](const Pick& a, const Pick& c) { return a.rows > c.rows; });
             for (int i = 0; i < n; ++i) {
                 fbatch_add(b, host, pick[i].item, pick[i].wgs);
-                if (pick[i].reduce) fbatch_add(r, host, pick[i].item, pick[i].reduce);
+                if (pick[i].reduce) fbatch_add(pick[i].nsplit >= 32 ? rmany : r, host, pick[i].item, pick[i].reduce);
             }
             switch (var) {
                 case 0: rc = launch_tiles<64, 0>(b, stream); break;
@@ -671,8 +645,11 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
                 default: rc = launch_tiles<128, 2>(b, stream); break;
             }
             if (rc != KFAC_OK) return rc;
+            if (rmany.count > 0) {
+                KFAC_LAUNCH(factor_tile_reduce_kernel<4>, dim3(rmany.prefix[rmany.count]), dim3(1024), stream, rmany);
+            }
             if (r.count > 0) {
-                KFAC_LAUNCH(factor_tile_reduce_kernel, dim3(r.prefix[r.count]), dim3(256), stream, r);
+                KFAC_LAUNCH(factor_tile_reduce_kernel<1>, dim3(r.prefix[r.count]), dim3(256), stream, r);
             }
         }
     }
@@ -680,9 +657,8 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
         Unfold u;
         View v;
         item_unfold(host[i], &u);
-        const Route route = route_of(u, host[i].x, many, &v);
-        if (route == ROUTE_TILE) continue;
-        rc = route == ROUTE_GATHER ? run_gather(u, host[i], stream) : run_generic(u, host[i], stream);
+        if (route_of(u, host[i].x, many, &v) == ROUTE_TILE) continue;
+        rc = run_generic(u, host[i], stream);
         if (rc != KFAC_OK) return rc;
     }
     return KFAC_OK;

@@ -12,6 +12,7 @@ constexpr int RP_T = 64;
 constexpr int RP_LDS_BYTES = RP_T * (RP_T + 1) * 4;
 
 static inline __host__ __device__ int repack_wgs(const Unfold& u, const View& v) {     // u: the caller's tensor
+    if (v.rows) return ceil_div(v.u.N * v.u.H * (v.u.W / 2), 256);
     return u.N * ceil_div(u.H * u.W, RP_T) * ceil_div(v.u.C, RP_T);
 }
 static inline __host__ __device__ size_t repack_bytes(const View& v) {
@@ -64,6 +65,28 @@ __device__ __forceinline__ void repack_tile(const Unfold& u, const View& v, cons
         if (p0 + p < hw && c0 + q * 4 * EPD < Cp)
             *(KFAC_AS1 v4u*)(dst + (((size_t)n * hw + p0 + p) * Cp + c0) / EPD + 4 * q) = o;
     }
+}
+
+// View::rows: the image with its zero padding, four channels to a pixel; one thread per pair of pixels (16 bytes).
+__device__ __forceinline__ void repack_rows(const Unfold& u, const View& v, const KFAC_AS1 unsigned short* __restrict__ x,
+                                            KFAC_AS1 unsigned* __restrict__ dst, int wg) {
+    const int W2 = v.u.W / 2;
+    const int id = wg * 256 + (int)threadIdx.x;
+    if (id >= v.u.N * v.u.H * W2) return;
+    const int row = id / W2, x2 = id - row * W2, n = row / v.u.H, y = row - n * v.u.H - u.pad;
+    const size_t cs = u.layout == KFAC_NHWC ? 1 : (size_t)u.H * u.W, ps = u.layout == KFAC_NHWC ? u.C : 1;
+    unsigned val[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {                                   // (element 0 stands in for the padding: no branches)
+        const int xx = 2 * x2 + (e >> 2) - u.pad, c = e & 3;
+        const bool ok = (unsigned)y < (unsigned)u.H && (unsigned)xx < (unsigned)u.W && c < u.C;
+        const size_t at = (size_t)n * u.C * u.H * u.W + ((size_t)y * u.W + xx) * ps + c * cs;
+        val[e] = ok ? 1u : 0u;
+        val[e] *= x[ok ? at : 0];
+    }
+    typedef unsigned v4u __attribute__((ext_vector_type(4)));
+    const v4u o = {val[0] | val[1] << 16, val[2] | val[3] << 16, val[4] | val[5] << 16, val[6] | val[7] << 16};
+    *(KFAC_AS1 v4u*)(dst + (size_t)id * 4) = o;
 }
 
 }  // namespace kfac

@@ -24,7 +24,9 @@
 //
 // Column order and padding.  Internally columns run in 16-byte vectors of V = 8 (fp32: 4) channels: (tap, channel) for
 // KFAC_ORDER_KH_KW_C, (channel vector, tap, channel in vector) for KFAC_ORDER_C_KH_KW, and the channels of a tensor that
-// was repacked (other layouts, channel counts that are no multiple of V) may be padded with zeros.  The epilogue puts
+// was repacked (other layouts, channel counts that are no multiple of V) may be padded with zeros; with up to four channels
+// and an even stride a vector is two neighbouring pixels instead (View::rows: the 147 columns of a 7 x 7 convolution over
+// three channels become 224 instead of 392).  The epilogue puts
 // results where the caller's order wants them (result_index); a vector's V kh kw columns are neighbours in both orders,
 // so a tile's stores stay inside the same few cache lines.
 #pragma once
@@ -37,14 +39,6 @@ namespace kfac {
 static __device__ uint4 g_zero_chunk = {0u, 0u, 0u, 0u};
 
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ int fast_div(int a, int d, float inv) {   // exact for 0 <= a < 2^24
-    int q = (int)((float)a * inv);
-    int rem = a - q * d;
-    if (rem < 0) --q;
-    else if (rem >= d) ++q;
-    return q;
-}
 
 #define KFAC_TR_READ(dst, addr, off) \
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off))
@@ -63,24 +57,37 @@ struct View {
     int chunked;     // internal column order: (channel vector, tap, channel in vector)
     int mapped;      // internal column index != result index
     int repack;      // the tensor is a repacked copy in the build's workspace
+    int run;         // columns per kernel tap (C), or, if `rows`, per kernel row
+    int rows;        // few channels: a repacked pixel has 4, and a kernel row's kw pixels in a row (an even number, the last one
+                     // of no interest if kw is odd) are one run of columns; the copy has the zero padding in it, so that every
+                     // run is whole.  The view's kw is 1, its pad 0.
+    int kw;          // the layer's kernel width
 };
 
 // False: the matrix-core kernels cannot take the build.
 static inline __host__ __device__ bool make_view(const Unfold& u, View* v) {
     if (u.d >= 32768) return false;                                          // byte offsets into the result fit 32 bits
     const int V = u.dtype == KFAC_F32 ? 4 : 8;
-    const int Cp = (u.C + V - 1) / V * V;
-    if ((long long)u.N * u.H * u.W * Cp > 0x7fffffffLL) return false;        // 32-bit element offsets
+    const bool rows = u.dtype != KFAC_F32 && u.C <= 4 && u.kw > 1 && u.stride % 2 == 0;    // (even: runs start at 16-byte addresses)
+    const int npx = (u.kw + 1) / 2 * 2;                                      // pixels of a run
+    const int Cp = rows ? 4 : (u.C + V - 1) / V * V;
     v->u = u;
     v->u.C = Cp;
     v->u.layout = KFAC_NHWC;
-    v->u.d = u.kh * u.kw * Cp;
+    v->u.H = rows ? (u.Ho - 1) * u.stride + u.kh : u.H;
+    v->u.W = rows ? ((u.Wo - 1) * u.stride + npx + 1) / 2 * 2 : u.W;
+    v->u.kw = rows ? 1 : u.kw;
+    v->u.pad = rows ? 0 : u.pad;
+    v->run = rows ? 4 * npx : Cp;
+    v->u.d = u.kh * (rows ? 1 : u.kw) * v->run;
     v->dout = u.d;
     v->cout = u.C;
+    v->kw = u.kw;
+    v->rows = rows;
     v->chunked = u.order == KFAC_ORDER_C_KH_KW && u.kh * u.kw > 1;
-    v->mapped = v->chunked || Cp != u.C;
-    v->repack = (u.layout == KFAC_NCHW && u.H * u.W > 1) || Cp != u.C;
-    return true;
+    v->mapped = v->chunked || Cp != u.C || rows;
+    v->repack = (u.layout == KFAC_NCHW && u.H * u.W > 1) || Cp != u.C || rows;
+    return (long long)u.N * v->u.H * v->u.W * Cp <= 0x7fffffffLL;            // 32-bit element offsets
 }
 
 __device__ __forceinline__ bool is_plain(const Unfold& u) { return u.kh == 1 && u.kw == 1 && u.stride == 1 && u.pad == 0; }
@@ -89,6 +96,11 @@ __device__ __forceinline__ bool is_plain(const Unfold& u) { return u.kh == 1 && 
 __device__ __forceinline__ int result_index(const View& v, int p) {
     if (p >= v.u.d) return -1;
     if (!v.mapped) return p;
+    if (v.rows) {
+        const int ki = p / v.run, kj = (p - ki * v.run) >> 2, c = p & 3;
+        if (kj >= v.kw || c >= v.cout) return -1;
+        return v.chunked ? (c * v.u.kh + ki) * v.kw + kj : (ki * v.kw + kj) * v.cout + c;
+    }
     const int kk = v.u.kh * v.u.kw;
     if (v.chunked) {
         const int V = v.u.dtype == KFAC_F32 ? 4 : 8;
@@ -113,14 +125,14 @@ __device__ __forceinline__ ColGroup decode_group(const View& v, int gcol0) {
     g.data = gcol0 < u.d;
     if (g.data) {
         int tap, c0;
-        if (v.chunked) {
+        if (v.chunked && !v.rows) {
             const int V = u.dtype == KFAC_F32 ? 4 : 8, kk = u.kh * u.kw;
             const int q = gcol0 / V;
             c0 = (q / kk) * V;
             tap = q % kk;
         } else {
-            tap = gcol0 / u.C;
-            c0 = gcol0 - tap * u.C;
+            tap = gcol0 / v.run;
+            c0 = gcol0 - tap * v.run;
         }
         g.ki = tap / u.kw;
         g.kj = tap - g.ki * u.kw;
