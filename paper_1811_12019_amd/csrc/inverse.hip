@@ -366,7 +366,9 @@ __device__ __forceinline__ void invert16_step(float (&E)[4], int i, int g, float
     const float u = vi * r, m = prow ? r : -u;             // row S becomes u r, the others lose u times it
 #pragma unroll
     for (int q = 0; q < 4; ++q) E[q] = fmaf(row_bcast<S>(E[q]) * r, m, prow ? 0.f : E[q]);
-    E[qs] = g == gs ? (prow ? -(r * r) : u * r) : E[qs];
+    float col = -m * r;                                    // -1 / p in row S, u r in the others
+    asm("" : "+v"(col));                                   // (a value, not an expression: the compiler would branch around it)
+    E[qs] = g == gs ? col : E[qs];
 }
 
 // One wavefront: Ps = inverse of the symmetric positive definite 16 x 16 block whose element (i, 4 g + q) lane
