@@ -1,21 +1,14 @@
-// fp32 "NT" tile product on the bf16 matrix cores: acc[128 x 128] += A[128 x K] . B[128 x K]^T, both operands
-// fp32, row-major, K contiguous.  Each fp32 operand value is split on the fly into NS bf16 pieces
-//     x = x0 + x1 (+ x2),   x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1)
-// (8 significant bits each, so 2 pieces carry 16 bits of x and 3 pieces all 24), and the product is the sum of
-// the bf16 x bf16 MFMAs (exact products, fp32 accumulate) of all piece pairs whose combined order is below NS:
-//     NS = 2:  a0 b0 + a0 b1 + a1 b0                            relative error of a product ~ 2^-16
-//     NS = 3:  a0 b0 + a0 b1 + a1 b0 + a0 b2 + a1 b1 + a2 b0    ~ 2^-23: on a par with fp32 multiply-add
-// v_mfma_f32_32x32x16_bf16 runs at 16 times the rate of v_mfma_f32_32x32x2_f32, so 3 (6) products per fp32
-// product still leave a factor 5.3 (2.7) over the fp32 matrix-core peak.
+// fp32 products on the 16-bit matrix cores, operands split into 16-bit pieces.
 //
-// (A variant with two fp16 pieces of scaled operands, split ahead of time by the producer, is at the end of this file.)
+// Three bf16 pieces (the sweep's panel product, below): each fp32 operand value is split on the fly,
+//     x = x0 + x1 + x2,   x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1)
+// (8 significant bits each, all 24 of x together), and the product is the sum of the bf16 x bf16 MFMAs (exact products, fp32
+// accumulate) of all piece pairs whose combined order is below 3:
+//     a0 b0 + a0 b1 + a1 b0 + a0 b2 + a1 b1 + a2 b0     relative error ~ 2^-23: on a par with fp32 multiply-add
+// v_mfma_f32_32x32x16_bf16 runs at 16 times the rate of v_mfma_f32_32x32x2_f32, so 6 products per fp32 product still leave a
+// factor 2.7 over the fp32 matrix-core peak.
 //
-// One workgroup = 4 wavefronts in a 2 x 2 arrangement, each owning a 64 x 64 quadrant as 2 x 2 MFMA blocks.  K
-// advances 16 at a time through a double-buffered LDS stage: the next slab is fetched into registers while the
-// current one is multiplied, then split and stored to the other buffer; one barrier per slab.
-// LDS layout per buffer: operand (A, B) x piece x 128 rows x 32 bytes (16 bf16 = the slab's K); the two 16-byte
-// halves of a row swap places from one group of 4 rows to the next and again from one group of 8 to the next, which
-// makes the 16-byte MFMA operand reads (served 16 consecutive rows at a time from 64 banks) bank-conflict free.
+// Two fp16 pieces of scaled operands, split ahead of time by their producer: the rest of the file.
 #pragma once
 
 #include "factor_mfma.h"
@@ -25,7 +18,6 @@ namespace kfac {
 
 constexpr int SPLIT_KS = 16;                           // K per LDS stage
 constexpr int SPLIT_PLANE = 128 * 32;                  // bytes of one operand piece per stage
-template <int NS> constexpr int split_lds_bytes() { return 2 * 2 * NS * SPLIT_PLANE; }   // 32 KB (NS=2), 48 KB (NS=3)
 
 typedef __bf16 v2bf_t __attribute__((ext_vector_type(2)));
 typedef float v2f_t __attribute__((ext_vector_type(2)));
@@ -51,122 +43,80 @@ __device__ __forceinline__ void split4(const v4f& x, uint2 (&piece)[NS]) {
     }
 }
 
-// lds: split_lds_bytes<NS>() bytes, 16-byte aligned.  acc is accumulated into (the caller zeroes it).
-// skip_upper_right: the (wm = 0, wn = 1) quadrant is not needed (diagonal tile of a symmetric result).
-// NEG_A: the product is subtracted (the A operand is negated before it is split).
-// NST > 0: both operands are complete, 16-byte aligned panels (all 128 rows present, K exactly NST * 16): loads are
-// unguarded, every wavefront multiplies, and the stage loop is unrolled completely.  With no branches left the
-// compiler counts the loads in flight exactly instead of draining them at every join, which is what makes the
-// two-stage look-ahead effective.
-// ROWS_ALIGN4 (with NST > 0): the panels' rows are only 4-byte aligned (odd leading dimension).
-template <int NS, bool NEG_A = false, int NST = 0, bool ROWS_ALIGN4 = false>
-__device__ __forceinline__ void tile_mma_nt_split(const gfloat* __restrict__ A, int lda, int arows,
-                                                  const gfloat* __restrict__ B, int ldb, int brows, int K,
-                                                  unsigned char* __restrict__ lds, TileAcc& acc,
-                                                  bool skip_upper_right = false) {
-    static_assert(NS == 2 || NS == 3, "two or three bf16 pieces");
-    constexpr int BUF = 2 * NS * SPLIT_PLANE;          // bytes per buffer
-    const int t = threadIdx.x;
-    const int lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+// acc[64 x 128] = A[64 x 128] . B[128 x 128]^T for a workgroup of 4 wavefronts, each owning 32 rows x 64 columns as two
+// MFMA blocks.  A: complete rows in global memory, leading dimension 128.  B passes through LDS: its values are fetched by
+// panel_fetch_b (any time before: the caller hides the latency), split a 16-wide slice at a time and stored to a
+// double-buffered stage of 3 pieces x 128 rows x 32 bytes; the two 16-byte halves of a row swap places from one group of 4
+// rows to the next and again from one group of 8 to the next, which makes the 16-byte MFMA operand reads (served 16
+// consecutive rows at a time from 64 banks) bank-conflict free.  A's 8 values per lane and slice are the lane's operand as they
+// lie in memory: split in registers, two slices ahead in flight.  lds: PANEL_B_LDS bytes, 16-byte aligned; one barrier a slice.
+constexpr int PANEL_B_LDS = 2 * 3 * SPLIT_PLANE;
+
+__device__ __forceinline__ void panel_fetch_b(const gfloat* __restrict__ B, v4f (&pb)[16]) {
+    const int lr = threadIdx.x >> 2, kq = threadIdx.x & 3;       // rows lr and lr + 64, floats 4 kq .. + 3 of a slice
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) pb[2 * s + p] = *(const KFAC_AS1 v4f*)(B + (lr + 64 * p) * 128 + s * SPLIT_KS + 4 * kq);
+}
+
+__device__ __forceinline__ void panel_product(const gfloat* __restrict__ A, const v4f (&pb)[16], unsigned char* __restrict__ lds,
+                                              v16f (&acc)[2]) {
+    constexpr int BUF = 3 * SPLIT_PLANE;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
     const int lm = lane & 31, h = lane >> 5;
-    const bool compute = !(skip_upper_right && wm == 0 && wn == 1);
-    // producer: rows lr and lr + 64, floats 4 kq .. 4 kq + 3 of the slab
     const int lr = t >> 2, kq = t & 3;
-    unsigned w_off[2];
+    unsigned w_off[2], b_off[2];
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
-        const int row = lr + 64 * p;
+        const int row = lr + 64 * p, rb = wn * 64 + p * 32 + lm;
         w_off[p] = (unsigned)(row * 32 + (((kq >> 1) ^ ((row >> 2) & 1) ^ ((row >> 3) & 1)) * 16) + (kq & 1) * 8);
+        b_off[p] = (unsigned)(rb * 32 + ((h ^ ((rb >> 2) & 1) ^ ((rb >> 3) & 1)) * 16));
     }
-    // consumer: byte offsets (inside one piece plane) of this lane's 16 bytes for row blocks 0, 1
-    unsigned a_off[2], b_off[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int ra = wm * 64 + q * 32 + lm, rb = wn * 64 + q * 32 + lm;
-        a_off[q] = (unsigned)(ra * 32 + ((h ^ ((ra >> 2) & 1) ^ ((ra >> 3) & 1)) * 16));
-        b_off[q] = (unsigned)(rb * 32 + ((h ^ ((rb >> 2) & 1) ^ ((rb >> 3) & 1)) * 16) + NS * SPLIT_PLANE);
-    }
-
-    // Two register sets: the slab two stages ahead is in flight while the current one is multiplied, so a fetch
-    // has two stage times to arrive (the operands of a sweep step were just written by another kernel and come
-    // from beyond the L2).
-    v4f ra[2][2], rb[2][2];
-    auto fetch = [&](int k0, v4f (&xa)[2], v4f (&xb)[2]) {
+    auto stash = [&](int s) {
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            const int row = lr + 64 * p;
-            if constexpr (NST > 0 && ROWS_ALIGN4) {
-                xa[p] = *(const KFAC_AS1 v4f_a4*)(A + (size_t)row * lda + k0 + 4 * kq);
-                xb[p] = *(const KFAC_AS1 v4f_a4*)(B + (size_t)row * ldb + k0 + 4 * kq);
-            } else if constexpr (NST > 0) {
-                xa[p] = *(const KFAC_AS1 v4f*)(A + (size_t)row * lda + k0 + 4 * kq);
-                xb[p] = *(const KFAC_AS1 v4f*)(B + (size_t)row * ldb + k0 + 4 * kq);
-            } else {
-                xa[p] = load4_guard(A + (size_t)row * lda, row < arows, k0 + 4 * kq, K);
-                xb[p] = load4_guard(B + (size_t)row * ldb, row < brows, k0 + 4 * kq, K);
-            }
+            uint2 piece[3];
+            split4<3>(pb[2 * s + p], piece);
+#pragma unroll
+            for (int e = 0; e < 3; ++e) *(uint2*)(lds + (s & 1) * BUF + e * SPLIT_PLANE + w_off[p]) = piece[e];
         }
     };
-    auto stash = [&](int buf, const v4f (&xa)[2], const v4f (&xb)[2]) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            uint2 pa[NS], pb[NS];
-            split4<NS>(NEG_A ? -xa[p] : xa[p], pa);     // negated here, not at the fetch: a use would force the wait early
-            split4<NS>(xb[p], pb);
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                *(uint2*)(lds + buf * BUF + s * SPLIT_PLANE + w_off[p]) = pa[s];
-                *(uint2*)(lds + buf * BUF + (NS + s) * SPLIT_PLANE + w_off[p]) = pb[s];
-            }
-        }
+    v4f xa[3][2];                                                // slices s, s + 1, s + 2
+    const gfloat* arow = A + (wm * 32 + lm) * 128 + 8 * h;
+    auto fetch = [&](int s, v4f (&x)[2]) {
+        x[0] = *(const KFAC_AS1 v4f*)(arow + s * SPLIT_KS);
+        x[1] = *(const KFAC_AS1 v4f*)(arow + s * SPLIT_KS + 4);
     };
-    auto mma = [&](int buf) {
-        if (NST == 0 && !compute) return;
-        uint4 a[2][NS], b[2][NS];
+    fetch(0, xa[0]);
+    fetch(1, xa[1]);
+    stash(0);
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
+    for (int n = 0; n < 2; ++n)
 #pragma unroll
-            for (int p = 0; p < NS; ++p) {
-                a[q][p] = *(const uint4*)(lds + buf * BUF + p * SPLIT_PLANE + a_off[q]);
-                b[q][p] = *(const uint4*)(lds + buf * BUF + p * SPLIT_PLANE + b_off[q]);
-            }
+        for (int r = 0; r < 16; ++r) acc[n][r] = 0.f;
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        if (s + 2 < 8) fetch(s + 2, xa[(s + 2) % 3]);
+        uint4 a[3], b[2][3];
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+            for (int e = 0; e < 3; ++e) b[n][e] = *(const uint4*)(lds + (s & 1) * BUF + e * SPLIT_PLANE + b_off[n]);
+        uint2 lo[3], hi[3];
+        split4<3>(xa[s % 3][0], lo);
+        split4<3>(xa[s % 3][1], hi);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) a[e] = make_uint4(lo[e].x, lo[e].y, hi[e].x, hi[e].y);
         // smallest terms first
 #pragma unroll
-        for (int order = NS - 1; order >= 0; --order)
+        for (int order = 2; order >= 0; --order)
 #pragma unroll
             for (int pa = 0; pa <= order; ++pa)
 #pragma unroll
-                for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                    for (int nb = 0; nb < 2; ++nb)
-                        acc.c[mb][nb] = mfma16<false>(a[mb][pa], b[nb][order - pa], acc.c[mb][nb]);
-    };
-
-    if constexpr (NST > 0) {
-        fetch(0, ra[0], rb[0]);
-        if (NST > 1) fetch(SPLIT_KS, ra[1], rb[1]);
-        stash(0, ra[0], rb[0]);
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < NST; ++s) {
-            if (s + 2 < NST) fetch((s + 2) * SPLIT_KS, ra[s & 1], rb[s & 1]);
-            mma(s & 1);
-            if (s + 1 < NST) stash((s + 1) & 1, ra[(s + 1) & 1], rb[(s + 1) & 1]);
-            __syncthreads();
-        }
-        return;
-    }
-    // general K: one slab of look-ahead (a second register set only costs occupancy here: inside a loop the
-    // compiler drains all loads at the back edge anyway)
-    const int nst = (K + SPLIT_KS - 1) / SPLIT_KS;
-    fetch(0, ra[0], rb[0]);
-    stash(0, ra[0], rb[0]);
-    __syncthreads();
-    for (int s = 0; s < nst; ++s) {
-        const int buf = s & 1;
-        if (s + 1 < nst) fetch((s + 1) * SPLIT_KS, ra[0], rb[0]);
-        mma(buf);
-        if (s + 1 < nst) stash(buf ^ 1, ra[0], rb[0]);
+                for (int n = 0; n < 2; ++n) acc[n] = mfma16<false>(a[pa], b[n][order - pa], acc[n]);
+        if (s + 1 < 8) stash(s + 1);
         __syncthreads();
     }
 }

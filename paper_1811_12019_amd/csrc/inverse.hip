@@ -264,14 +264,14 @@ struct WsView {
     size_t stride;
     size_t plane;   // bytes of one piece plane (d_pad x NB fp16)
     gfloat* P;      // NB x NB    : inverse of the pivot block
-    gfloat* SC;     // 2 NBUF x nblk: power-of-two scales of the 128-row slabs of T and U of every buffer (gemm_split.h)
+    gfloat* SC;     // 2 NBUF x 2 nblk: power-of-two scales of the half slabs (64 rows) of T and U of every buffer (gemm_split.h)
     int nblk;
     __device__ __forceinline__ gfloat* U(int q) const { return buf0 + q * stride; }
     __device__ __forceinline__ gfloat* T(int q) const { return buf0 + q * stride + plane / 2; }
     __device__ __forceinline__ KFAC_AS1 unsigned char* TH(int q) const { return (KFAC_AS1 unsigned char*)(buf0 + q * stride + plane); }
     __device__ __forceinline__ KFAC_AS1 unsigned char* UH(int q) const { return TH(q) + 2 * plane; }
-    __device__ __forceinline__ gfloat& scaleT(int q, int slab) const { return SC[(q * 2 + 0) * nblk + slab]; }
-    __device__ __forceinline__ gfloat& scaleU(int q, int slab) const { return SC[(q * 2 + 1) * nblk + slab]; }
+    __device__ __forceinline__ gfloat& scaleT(int q, int half_slab) const { return SC[(q * 2 + 0) * 2 * nblk + half_slab]; }
+    __device__ __forceinline__ gfloat& scaleU(int q, int half_slab) const { return SC[(q * 2 + 1) * 2 * nblk + half_slab]; }
 };
 
 static inline __host__ __device__ size_t panel_buffer_floats(int dim) { return (size_t)nblk_of(dim) * NB * NB * 4; }
@@ -735,145 +735,128 @@ __global__ __launch_bounds__(256) void inv_pivot_kernel(Batch b, int step, int f
 
 // T = U . P for every 128-row slab of block column k; U is copied aside for the update.  Slabs below the pivot
 // block read the column block itself; slabs above it read block row k transposed.
-// Full pivot block (every step but a matrix's last): the slab is first copied to U (through an LDS transpose for the
-// slabs above the pivot), all 64 KB in flight at once, and the product then runs on the bf16 matrix cores with both
-// operands split three ways, reading the copy.  Ragged pivot block: fp32 matrix cores, operands guarded.
-// The transpose and the way out of T pass through LDS 64 rows at a time, so that the workgroup needs no more LDS than
-// the product (48 KB): a panel workgroup then fits into the room one finished update (or factor) workgroup leaves on
-// a CU.  With a full 128-row stage (66 KB) it had to wait until two of them had finished on the same CU, and the
-// panel launches, links of the chain, lasted 47 us instead of 21 us while other streams kept the CUs full.
+// Full pivot block (every step but a matrix's last): a workgroup takes half a slab (64 rows): twice the CUs for a link of the
+// chain that leaves most of them idle, and half the time in every phase.  The half slab is first copied to U (through an LDS
+// transpose for the slabs above the pivot), and the product then runs on the bf16 matrix cores with both operands split
+// three ways (panel_product).  The loads of P go out with those of the slab, which hides their latency.
+// Ragged pivot block: one workgroup per slab, fp32 matrix cores, operands guarded.
+// At 37 KB of LDS a panel workgroup fits into the room one finished update (or factor) workgroup leaves on a CU; with a full
+// 128-row stage (66 KB) it had to wait until two of them had finished on the same CU.
+// Alone, 2049 wide: 16.2 us a launch with 128-row workgroups that split U in LDS, 11.5 us now.
+constexpr int PH = NB / 2;                 // rows of a workgroup
 constexpr int PANEL_TLD = NB + 1;          // LDS row stride of the transpose stage
 constexpr int PANEL_RLD = NB + 4;          // LDS row stride when the stage is read back four columns at a time
-constexpr int PANEL_LDS_FLOATS = split_lds_bytes<3>() / 4;
-static_assert(PANEL_LDS_FLOATS >= GEMM_LDS_FLOATS && PANEL_LDS_FLOATS >= (NB / 2) * PANEL_RLD, "one buffer serves all uses");
+constexpr int PANEL_LDS_FLOATS = GEMM_LDS_FLOATS;
+static_assert(PANEL_LDS_FLOATS * 4 >= PANEL_B_LDS && PANEL_LDS_FLOATS >= PH * PANEL_RLD, "one buffer serves all uses");
 
-__global__ __launch_bounds__(256) void inv_panel_kernel(ChainBatch b) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void inv_panel_kernel(ChainBatch b) {
     __shared__ __attribute__((aligned(16))) float lds[PANEL_LDS_FLOATS];
     __shared__ float red[4];
     __builtin_amdgcn_s_setprio(3);                       // a link of the chain: ahead of whatever shares its SIMDs
-    int m, slab;
-    locate(b, blockIdx.x, m, slab);
+    int m, wg;
+    locate(b, blockIdx.x, m, wg);
     const Item it = get_item(b, m);
     const int d = it.dim;
     const int step = b.step[m];
+    const int slab = wg >> 1, half = wg & 1;
     const int k0 = step * NB;
     const int nb = min(NB, d - k0);
     if (slab == step) return;                 // the pivot block's own rows are not needed
-    const int r0 = slab * NB;
-    const int rows = min(NB, d - r0);
     const WsView ws = ws_view(it.ws, d);
     const int q = step % NBUF;
-    gfloat* __restrict__ Uc = ws.U(q) + (size_t)r0 * NB;
-    gfloat* __restrict__ Tc = ws.T(q) + (size_t)r0 * NB;
     const int t = threadIdx.x;
-    TileAcc acc;
+    const int lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
     if (nb == NB) {
-        const int c4 = (t & 31) * 4, rr = t >> 5;            // 8 rows x 32 float4 per pass, 16 passes
-        v4f v[16];
+        const int r0 = slab * NB + half * PH;
+        const int rows = max(0, min(PH, d - r0));            // (rows past the end: zeros)
+        gfloat* __restrict__ Uc = ws.U(q) + (size_t)r0 * NB;
+        gfloat* __restrict__ Tc = ws.T(q) + (size_t)r0 * NB;
+        const int c4 = (t & 31) * 4, rr = t >> 5;            // 8 rows x 32 float4 per pass, 8 passes
+        const int tc4 = (t & 15) * 4, tk = t >> 4;           // transposed: 16 rows of W x 16 float4 per pass, 8 passes
+        v4f v[8], pb[16];
         if (slab > step) {
 #pragma unroll
-            for (int p = 0; p < 16; ++p) {
+            for (int p = 0; p < 8; ++p) {
                 const int row = rr + 8 * p;
                 v4f x = {0.f, 0.f, 0.f, 0.f};
                 if (row < rows) x = *(const KFAC_AS1 v4f*)&ws.W[(size_t)(r0 + row) * ws.ldw + k0 + c4];
                 v[p] = x;
             }
-#pragma unroll
-            for (int p = 0; p < 16; ++p) *(KFAC_AS1 v4f*)&Uc[(size_t)(rr + 8 * p) * NB + c4] = v[p];   // rows past the end: zero
         } else {
             // element (a, k) of the slab is W[k0 + k][r0 + a]; a slab above the pivot has all its 128 rows
 #pragma unroll
-            for (int p = 0; p < 16; ++p)
-                v[p] = *(const KFAC_AS1 v4f*)&ws.W[(size_t)(k0 + rr + 8 * p) * ws.ldw + r0 + c4];
+            for (int p = 0; p < 8; ++p) v[p] = *(const KFAC_AS1 v4f*)&ws.W[(size_t)(k0 + tk + 16 * p) * ws.ldw + r0 + tc4];
         }
-        float um = 0.f;                        // the slab's scale for the update's fp16 pieces
+        panel_fetch_b(ws.P, pb);
+        if (slab > step) {
 #pragma unroll
-        for (int p = 0; p < 16; ++p)
+            for (int p = 0; p < 8; ++p) *(KFAC_AS1 v4f*)&Uc[(size_t)(rr + 8 * p) * NB + c4] = v[p];
+        }
+        float um = 0.f;                        // the half slab's scale for the update's fp16 pieces
+#pragma unroll
+        for (int p = 0; p < 8; ++p)
 #pragma unroll
             for (int i = 0; i < 4; ++i) um = fmaxf(um, fabsf(v[p][i]));
         um = block_absmax(um, red);
         const float su = panel_scale(um);
-        if (t == 0) ws.scaleU(q, slab) = su;
-        // the copy (slabs above the pivot) and the slab's scaled fp16 pieces
+        if (t == 0) ws.scaleU(q, wg) = su;
+        // the copy (slabs above the pivot) and the half slab's scaled fp16 pieces
         KFAC_AS1 unsigned char* uh = ws.UH(q) + (size_t)slab * PRE_SLAB;
         if (slab > step) {
 #pragma unroll
-            for (int p = 0; p < 16; ++p) store_split4_h2(uh, uh + ws.plane, rr + 8 * p, c4, v[p] * su);
+            for (int p = 0; p < 8; ++p) store_split4_h2(uh, uh + ws.plane, half * PH + rr + 8 * p, c4, v[p] * su);
         } else {
-            // transposed through LDS, 64 rows of the slab at a time: the threads holding columns c4 .. c4 + 3 of that
-            // half write them, then every thread reads four consecutive elements of eight rows
-#pragma unroll 1
-            for (int half = 0; half < 2; ++half) {
-                if (half == 1) __syncthreads();
-                if ((c4 >> 6) == half) {
 #pragma unroll
-                    for (int p = 0; p < 16; ++p)
+            for (int p = 0; p < 8; ++p)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) lds[(c4 + i - 64 * half) * PANEL_TLD + rr + 8 * p] = v[p][i];
-                }
-                __syncthreads();
+                for (int i = 0; i < 4; ++i) lds[(tc4 + i) * PANEL_TLD + tk + 16 * p] = v[p][i];
+            __syncthreads();
 #pragma unroll
-                for (int p = 0; p < 8; ++p) {
-                    const int a = 64 * half + rr + 8 * p;
-                    const float* src = &lds[(rr + 8 * p) * PANEL_TLD + c4];
-                    const v4f x = {src[0], src[1], src[2], src[3]};
-                    *(KFAC_AS1 v4f*)&Uc[(size_t)a * NB + c4] = x;
-                    store_split4_h2(uh, uh + ws.plane, a, c4, x * su);
-                }
+            for (int p = 0; p < 8; ++p) {
+                const int a = rr + 8 * p;
+                const float* src = &lds[a * PANEL_TLD + c4];
+                const v4f x = {src[0], src[1], src[2], src[3]};
+                *(KFAC_AS1 v4f*)&Uc[(size_t)a * NB + c4] = x;
+                store_split4_h2(uh, uh + ws.plane, half * PH + a, c4, x * su);
             }
         }
         __threadfence_block();
         __syncthreads();                       // the copy is visible to the whole workgroup; the LDS stage is free
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc.c[mb][nbk][r] = 0.f;
-        tile_mma_nt_split<3, false, NB / SPLIT_KS>(Uc, NB, NB, ws.P, NB, NB, NB, (unsigned char*)lds, acc);
-    } else if (slab > step) {
-        tile_mma_nt<false>(ws.W + (size_t)r0 * ws.ldw + k0, ws.ldw, rows, ws.P, NB, nb, nb, lds, acc, Uc, NB);
-    } else {
-        tile_mma_nt<true>(ws.W + (size_t)k0 * ws.ldw + r0, ws.ldw, rows, ws.P, NB, nb, nb, lds, acc, Uc, NB);
-    }
-    const int lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
-    if (nb == NB) {
+        v16f acc[2];
+        panel_product(Uc, pb, (unsigned char*)lds, acc);
         // T leaves through LDS, row-wise: the fp32 panel in 16-byte stores and its scaled, negated fp16 pieces
         float tm = 0.f;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int nbk = 0; nbk < 2; ++nbk)
 #pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) tm = fmaxf(tm, fabsf(acc.c[mb][nbk][r]));
+            for (int r = 0; r < 16; ++r) tm = fmaxf(tm, fabsf(acc[nbk][r]));
         tm = block_absmax(tm, red);                       // (its barriers also separate the product's LDS use from this one)
         const float st = panel_scale(tm);
-        if (t == 0) ws.scaleT(q, slab) = st;
-        const int c4 = (t & 31) * 4, rr = t >> 5;
+        if (t == 0) ws.scaleT(q, wg) = st;
         KFAC_AS1 unsigned char* th = ws.TH(q) + (size_t)slab * PRE_SLAB;
-#pragma unroll 1
-        for (int half = 0; half < 2; ++half) {
-            if (half == 1) __syncthreads();
-            if (wm == half) {
 #pragma unroll
-                for (int mb = 0; mb < 2; ++mb)
+        for (int nbk = 0; nbk < 2; ++nbk)
 #pragma unroll
-                    for (int nbk = 0; nbk < 2; ++nbk)
+            for (int r = 0; r < 16; ++r)
+                lds[(wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * PANEL_RLD + wn * 64 + nbk * 32 + (lane & 31)] = acc[nbk][r];
+        __syncthreads();
 #pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            lds[(acc_row(wm, mb, r, lane) - 64 * half) * PANEL_RLD + acc_col(wn, nbk, lane)] = acc.c[mb][nbk][r];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int row = 64 * half + rr + 8 * p;
-                const v4f x = *(const v4f*)&lds[(rr + 8 * p) * PANEL_RLD + c4];
-                if (row < rows) *(KFAC_AS1 v4f*)&Tc[(size_t)row * NB + c4] = x;
-                store_split4_h2(th, th + ws.plane, row, c4, x * -st);
-            }
+        for (int p = 0; p < 8; ++p) {
+            const int row = rr + 8 * p;
+            const v4f x = *(const v4f*)&lds[row * PANEL_RLD + c4];
+            if (row < rows) *(KFAC_AS1 v4f*)&Tc[(size_t)row * NB + c4] = x;
+            store_split4_h2(th, th + ws.plane, half * PH + row, c4, x * -st);
         }
         return;
     }
+    if (half == 1) return;
+    const int r0 = slab * NB;
+    const int rows = min(NB, d - r0);
+    gfloat* __restrict__ Uc = ws.U(q) + (size_t)r0 * NB;
+    gfloat* __restrict__ Tc = ws.T(q) + (size_t)r0 * NB;
+    TileAcc acc;
+    if (slab > step) tile_mma_nt<false>(ws.W + (size_t)r0 * ws.ldw + k0, ws.ldw, rows, ws.P, NB, nb, nb, lds, acc, Uc, NB);
+    else tile_mma_nt<true>(ws.W + (size_t)k0 * ws.ldw + r0, ws.ldw, rows, ws.P, NB, nb, nb, lds, acc, Uc, NB);
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
@@ -884,11 +867,9 @@ __global__ __launch_bounds__(256) void inv_panel_kernel(ChainBatch b) {
                 if (row < rows) Tc[(size_t)row * NB + col] = col < nb ? acc.c[mb][nbk][r] : 0.f;
             }
     // the update streams whole 16-float slabs of T and U: keep the columns beyond a ragged block at zero
-    if (nb < NB) {
-        for (int e = t; e < rows * NB; e += 256) {
-            const int row = e >> 7, col = e & (NB - 1);
-            if (col >= nb) Uc[(size_t)row * NB + col] = 0.f;
-        }
+    for (int e = t; e < rows * NB; e += 256) {
+        const int row = e >> 7, col = e & (NB - 1);
+        if (col >= nb) Uc[(size_t)row * NB + col] = 0.f;
     }
 }
 
@@ -1110,6 +1091,8 @@ typedef SplitRun<MAXRUN> PanelRun;
 // The products of tile (I, J) with the panels of the n consecutive steps first_step .. first_step + n - 1 (buffer =
 // step mod NBUF).
 __device__ __forceinline__ PanelRun panel_run(const WsView& ws, int first_step, int n, int I, int J) {
+    // (a wavefront's quadrant is one half slab by one half slab: one scale)
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1;
     PanelRun r;
     r.a_hi = ws.TH(0) + (size_t)I * PRE_SLAB;
     r.b_hi = ws.UH(0) + (size_t)J * PRE_SLAB;
@@ -1121,7 +1104,7 @@ __device__ __forceinline__ PanelRun panel_run(const WsView& ws, int first_step, 
 #pragma unroll
     for (int q = 0; q < MAXRUN; ++q) {
         const int b = (first_step + q) % NBUF;
-        r.scale[q] = ws.scaleT(b, I) * ws.scaleU(b, J);
+        r.scale[q] = ws.scaleT(b, 2 * I + wm) * ws.scaleU(b, 2 * J + wn);
     }
     return r;
 }
@@ -1542,7 +1525,7 @@ static int run_group(const kfac_inverse_item* h, int count, hipStream_t stream) 
             const bool run = l < span && (int)(((long long)(l + 1) * n) / span) > (int)(((long long)l * n) / span);
             c.step[i] = run ? done[i] : -1;
         }
-        for (int i = 0; i < n_multi; ++i) c.prefix[i + 1] = c.prefix[i] + (c.step[i] >= 0 ? nblk_of(h[i].dim) : 0);
+        for (int i = 0; i < n_multi; ++i) c.prefix[i + 1] = c.prefix[i] + (c.step[i] >= 0 ? 2 * nblk_of(h[i].dim) : 0);
         KFAC_LAUNCH(inv_panel_kernel, dim3(c.prefix[n_multi]), dim3(256), stream, c);
         for (int i = 0; i < n_multi; ++i)
             c.prefix[i + 1] = c.prefix[i] + (c.step[i] >= 0 ? update_tiles(h[i].dim, c.step[i]) : 0);
@@ -1555,7 +1538,7 @@ static int run_group(const kfac_inverse_item* h, int count, hipStream_t stream) 
 static size_t ws_bytes_of(int dim) {
     if (nblk_of(dim) == 1) return 256;
     const size_t d_pad = (size_t)nblk_of(dim) * NB;
-    return align_up((d_pad * ldw_of(dim) + NBUF * panel_buffer_floats(dim) + (size_t)NB * NB + 2 * NBUF * (size_t)nblk_of(dim)) * sizeof(float), 256);
+    return align_up((d_pad * ldw_of(dim) + NBUF * panel_buffer_floats(dim) + (size_t)NB * NB + 4 * NBUF * (size_t)nblk_of(dim)) * sizeof(float), 256);
 }
 
 static bool item_ok(const kfac_inverse_item& it) {
