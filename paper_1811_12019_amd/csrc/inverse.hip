@@ -436,8 +436,8 @@ __device__ __forceinline__ void pivot_border(v16f (&acc)[2][2], int nb) {
 // T16 = U16 . P16 for the 32 rows of this wavefront (v_mfma_f32_16x16x4_f32: lane l supplies A[l % 16][l / 16] and
 // B[l / 16][l % 16] and receives C[4 (l / 16) + i][l % 16], i < 4); the rows of sub-block jb itself become -P16.
 __device__ __forceinline__ void sweep_panel(const float* __restrict__ Us, const float* __restrict__ Ps, float* __restrict__ Ts,
-                                            int wave, int jb) {
-    const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+                                            int lane, int wave, int jb) {
+    const int l16 = lane & 15, lq = lane >> 4;
     float a[2][4], b[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
@@ -467,8 +467,8 @@ __device__ __forceinline__ void sweep_panel(const float* __restrict__ Us, const 
 __device__ __forceinline__ void sweep_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // U16 of sub-block jb: D's columns 16 jb .. + 15, rows above the 32 x 32 diagonal block from D's rows (transposed).
-__device__ __forceinline__ void sweep_publish(const v16f (&acc)[2][2], int wm, int wn, int jb, float* __restrict__ Us) {
-    const int lane = threadIdx.x & 63, lm = lane & 31, h = lane >> 5;
+__device__ __forceinline__ void sweep_publish(const v16f (&acc)[2][2], int lane, int wm, int wn, int jb, float* __restrict__ Us) {
+    const int lm = lane & 31, h = lane >> 5;
     const int ow = jb >> 2, ob = (jb >> 1) & 1, oh = jb & 1;   // wavefront row / column, block inside it, half of the block
     if (wn == ow && wm >= ow && (lm >> 4) == oh) {
 #pragma unroll
@@ -492,8 +492,8 @@ __device__ __forceinline__ void sweep_publish(const v16f (&acc)[2][2], int wm, i
 }
 
 // Diagonal sub-block jb, as v_mfma_f32_16x16x4_f32 would leave it: float 4 lane + i is row 4 (lane / 16) + i, column lane % 16.
-__device__ __forceinline__ void sweep_publish_diagonal(const v16f (&acc)[2][2], int wm, int wn, int jb, float* __restrict__ DG) {
-    const int lane = threadIdx.x & 63, lm = lane & 31, h = lane >> 5;
+__device__ __forceinline__ void sweep_publish_diagonal(const v16f (&acc)[2][2], int lane, int wm, int wn, int jb, float* __restrict__ DG) {
+    const int lm = lane & 31, h = lane >> 5;
     const int ob = (jb >> 1) & 1, oh = jb & 1;
     if (wm == (jb >> 2) && wn == wm && (lm >> 4) == oh) {
 #pragma unroll
@@ -512,11 +512,10 @@ __device__ __forceinline__ int pivot_sweep(v16f (&acc)[2][2], int nb, float* __r
     float* __restrict__ Ts = lds + PIV_TS;
     float* __restrict__ DG = lds + PIV_DG;
     int* bad = (int*)(lds + PIV_BAD);
-    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1;
-    const int lm = lane & 31, h = lane >> 5;
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1;
     const int nsb = (nb + PSB - 1) / PSB;
     if (wave == 1) {
-        const int l16 = lane & 15, lq = lane >> 4;
+        const int lane = t & 63, l16 = lane & 15, lq = lane >> 4;
         sweep_barrier();                                       // the first U16 and the diagonal sub-blocks are there
         int first_bad = 0;
         {
@@ -528,7 +527,7 @@ __device__ __forceinline__ int pivot_sweep(v16f (&acc)[2][2], int nb, float* __r
 #pragma unroll 1
         for (int jb = 0; jb < nsb; ++jb) {
             const float* Us = lds + PIV_US + (jb & 1) * (NB * PLD);
-            sweep_panel(Us, lds + PIV_PS + (jb & 1) * (PSB * PLD), Ts, 1, jb);
+            sweep_panel(Us, lds + PIV_PS + (jb & 1) * (PSB * PLD), Ts, lane, 1, jb);
             sweep_barrier();
             const int n = jb + 1;
             if (n < nsb) {                                     // diagonal sub-block n -= T16 . U16^T, and its inverse
@@ -550,16 +549,21 @@ __device__ __forceinline__ int pivot_sweep(v16f (&acc)[2][2], int nb, float* __r
             sweep_barrier();
         }
     } else {
-        sweep_publish(acc, wm, wn, 0, lds + PIV_US);
-        sweep_publish_diagonal(acc, wm, wn, 0, DG);
-        sweep_publish_diagonal(acc, wm, wn, 1, DG + PSB * PSB);
+        int lane = t & 63;
+        sweep_publish(acc, lane, wm, wn, 0, lds + PIV_US);
+        sweep_publish_diagonal(acc, lane, wm, wn, 0, DG);
+        sweep_publish_diagonal(acc, lane, wm, wn, 1, DG + PSB * PSB);
         sweep_barrier();
         sweep_barrier();                                       // wavefront 1 has inverted the first diagonal sub-block
 #pragma unroll
         for (int jb = 0; jb < NB / PSB; ++jb) {
             if (jb >= nsb) break;                              // uniform
+            // Addresses are worked out anew for each sub-block: kept over the unrolled loop they would not fit beside D, and
+            // every phase would begin by waiting for one from scratch memory.
+            asm volatile("" : "+v"(lane));
+            const int lm = lane & 31, h = lane >> 5;
             const float* Us = lds + PIV_US + (jb & 1) * (NB * PLD);
-            sweep_panel(Us, lds + PIV_PS + (jb & 1) * (PSB * PLD), Ts, wave, jb);
+            sweep_panel(Us, lds + PIV_PS + (jb & 1) * (PSB * PLD), Ts, lane, wave, jb);
             sweep_barrier();
             // D -= T16 . U16^T  (lane (lm, h) takes k = 8s + 4h .. +3 of both operands), then the fix-ups
 #pragma unroll
@@ -605,8 +609,8 @@ __device__ __forceinline__ int pivot_sweep(v16f (&acc)[2][2], int nb, float* __r
                         }
                     }
             }
-            if (jb + 1 < NB / PSB) sweep_publish(acc, wm, wn, jb + 1, lds + PIV_US + ((jb + 1) & 1) * (NB * PLD));
-            if (jb + 2 < NB / PSB) sweep_publish_diagonal(acc, wm, wn, jb + 2, DG + (jb & 1) * (PSB * PSB));
+            if (jb + 1 < NB / PSB) sweep_publish(acc, lane, wm, wn, jb + 1, lds + PIV_US + ((jb + 1) & 1) * (NB * PLD));
+            if (jb + 2 < NB / PSB) sweep_publish_diagonal(acc, lane, wm, wn, jb + 2, DG + (jb & 1) * (PSB * PSB));
             sweep_barrier();
         }
     }
