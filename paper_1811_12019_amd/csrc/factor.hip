@@ -263,38 +263,76 @@ static FactorPlan plan_generic(const Unfold& u) {
     return p;
 }
 
-// Tile width and row split of a matrix-core build.  `many`: it shares its launch with many others.
-// Width: 256 halves the operand traffic per product against 128; a matrix of up to 128 (64) columns is one tile of that
-// width.  A build launched alone that cannot give every CU a 256-wide tile of at least 1024 rows takes 128-wide ones (4609 columns
-// of 1568 rows: 171 workgroups of about 90 us, or 666 of three to a CU: 75 us).
-// Split: alone, about two workgroups per CU (one of the 8-wavefront 256-wide ones); among many builds that fill the chip
-// together, only as many as keep a workgroup's share of rows bounded, since every split adds a tile of partial sums to HBM.
-// fp32 rows take eight times as long as 16-bit ones, so their shares are smaller.
-constexpr int ROWS_PER_WG_MANY = 6400, ROWS_PER_WG_MANY_F32 = 1600;
+// Tile width and row split of a matrix-core build.  `share`: how the builds of a call are cut (share_of): the rows of a
+// workgroup, plus SHARE_WIDE if matrices of more than 128 columns get 256-wide tiles.  A matrix of up to 128 (64) columns is
+// one tile of that width.
+constexpr int SHARE_WIDE = 1 << 20;
+constexpr int ROWS_PER_WG_MAX = 6400, ROWS_PER_WG_MAX_F32 = 1600;
 constexpr int ROWS_PER_WG_MIN = 512, ROWS_PER_WG_MIN_F32 = 64;
 
-static inline __host__ __device__ FactorPlan plan_tiles(const View& v, bool many) {
+// splits that keep a build's partial sums below 34 MB (67 MB), unless a workgroup's rows would pass the maximum
+static inline __host__ __device__ int most_splits(int R, int tw, int ntiles, bool f32) {
+    const int cap = (tw == 256 ? 256 : 512) / ntiles, need = ceil_div(R, f32 ? ROWS_PER_WG_MAX_F32 : ROWS_PER_WG_MAX);
+    const int most = R / (f32 ? ROWS_PER_WG_MIN_F32 : ROWS_PER_WG_MIN);
+    const int ns = cap > need ? cap : need;
+    return ns > most ? (most > 1 ? most : 1) : (ns > 1 ? ns : 1);
+}
+
+static inline __host__ __device__ FactorPlan plan_tiles(const View& v, int share) {
     FactorPlan p;
     const int D = v.u.d, R = v.u.R;
     const bool f32 = v.u.dtype == KFAC_F32;
-    const int least = f32 ? ROWS_PER_WG_MIN_F32 : ROWS_PER_WG_MIN;
-    const int max_split = R / least > 1 ? R / least : 1;
-    if (D <= 64) p.tw = 64;
-    else if (D <= 128 || f32) p.tw = 128;
-    else {
-        const int n = ceil_div(D, 256), splits = R / 1024 > 1 ? R / 1024 : 1;
-        p.tw = many || (long long)n * (n + 1) / 2 * splits >= 256 ? 256 : 128;
-    }
+    p.tw = D <= 64 ? 64 : D <= 128 || f32 || !(share & SHARE_WIDE) ? 128 : 256;
     p.tiles_dim = ceil_div(D, p.tw);
     p.ntiles = p.tiles_dim * (p.tiles_dim + 1) / 2;
-    int ns = many ? ceil_div(R, f32 ? ROWS_PER_WG_MANY_F32 : ROWS_PER_WG_MANY) : (p.tw == 256 ? 256 : 512) / p.ntiles;
-    if (ns > max_split) ns = max_split;
-    if (ns < 1) ns = 1;
+    const int most = most_splits(R, p.tw, p.ntiles, f32);
+    int ns = ceil_div(R, share & (SHARE_WIDE - 1));
+    if (ns > most) ns = most;
     if (ns >= 8) ns = ns / 8 * 8;                          // multiples of 8 keep a row range on one XCD
     p.rows_per_split = ceil_div(ceil_div(R, ns), 64) * 64;
     p.nsplit = ceil_div(R, p.rows_per_split);
     p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * ((size_t)p.ntiles * p.tw * p.tw + (size_t)p.tiles_dim * p.tw) * sizeof(float) : 0;
     return p;
+}
+
+// The work of a call's builds of one element size, in rows of 128 x 128 tiles, cut into 128- and into 256-wide tiles.
+struct TileWork {
+    double narrow, wide;
+};
+static void add_work(TileWork& w, const View& v) {
+    const double n = ceil_div(v.u.d, 128), m = ceil_div(v.u.d, 256);
+    w.narrow += 0.5 * n * (n + 1) * v.u.R;
+    w.wide += (v.u.d <= 128 ? 1.0 : 2.0 * m * (m + 1)) * v.u.R;
+}
+
+// How they are cut.  The rows of a workgroup: half of what each of the 768 workgroups that run at a time would get of all
+// the work, within limits.  More leaves the chip waiting for the last ones (18,816 rows of the first stage's layers at 3200
+// to a workgroup 119 us, at 6400 181 us), less adds partial sums, each as much traffic as a finished tile, for nothing (the third
+// stage's 18 layers at 1568 rows: 151 us unsplit, 334 us in two).  When there is little work the launch of the second pass
+// weighs too.
+// Width: a 256-wide tile halves the operand traffic per product, but a workgroup fills a CU, its epilogue overlaps with
+// nothing and a matrix is padded to multiples of 256.  It is the better one only for a lot of work with little padding (third
+// stage at 25,088 rows: 1385 us against 1600 us), or for so much that padding and the launch's end do not show (all of the
+// network at 128 images: 5.1 against 5.4 ms; at 64 both 2.55 ms, at 32 1480 us against 1350 us).
+static int share_of(const TileWork& w, bool f32) {
+    const double per_slot = w.narrow / 768;
+    const double least = f32 ? (per_slot < 100 ? 128 : 256) : (per_slot < 512 ? 1024 : 1600);
+    const double rows = std::min(std::max(0.52 * per_slot, least), (double)(f32 ? ROWS_PER_WG_MAX_F32 : ROWS_PER_WG_MAX));
+    const bool wide = per_slot >= (w.wide <= 1.15 * w.narrow ? 24000 : 100000);
+    return (int)rows + (wide && !f32 ? SHARE_WIDE : 0);
+}
+
+// An upper bound of plan_tiles' workspace over all shares.
+static size_t tiles_ws_bytes(const View& v) {
+    const int D = v.u.d, R = v.u.R;
+    const bool f32 = v.u.dtype == KFAC_F32;
+    size_t need = 0;
+    for (int tw = D <= 64 ? 64 : 128; tw <= (D <= 128 || f32 ? 128 : 256) && !(D <= 64 && tw > 64); tw *= 2) {
+        const int td = ceil_div(D, tw), nt = td * (td + 1) / 2;
+        const int ns = most_splits(R, tw, nt, f32);
+        if (ns > 1) need = std::max(need, (size_t)ns * ((size_t)nt * tw * tw + (size_t)td * tw) * sizeof(float));
+    }
+    return need;
 }
 
 // The workspace of a matrix-core build: the repacked tensor, if there is one, then the partial sums.
@@ -327,7 +365,7 @@ struct FBatch {
     const kfac_factor_item* table;   // device table, or nullptr -> `single`
     kfac_factor_item single;
     int count;
-    int many;                        // plan_tiles' argument for every build of this launch
+    int share;                       // plan_tiles' argument for every build of this launch
     int index[FMAXB];                // table index of the i-th build of this launch
     int prefix[FMAXB + 1];           // workgroup prefix sums
 };
@@ -359,7 +397,7 @@ void factor_tile_kernel(FBatch b) {
     Unfold u;
     View v;
     fbatch_item(b, m, it, u, v);
-    const FactorPlan p = plan_tiles(v, b.many);
+    const FactorPlan p = plan_tiles(v, b.share);
     const float scale = it.scale == 0.f ? 1.0f / (float)u.R : it.scale;
     const KFAC_AS1 unsigned char* x = (const KFAC_AS1 unsigned char*)(v.repack ? it.ws : it.x);
     factor_tile<TW, KIND>(v, x, scale, out_spec(it), partial_of(v, p, it.ws), p.rows_per_split, p.tiles_dim, p.ntiles, p.nsplit,
@@ -398,7 +436,7 @@ __global__ __launch_bounds__(256 * GROUPS) void factor_tile_reduce_kernel(FBatch
     Unfold u;
     View v;
     fbatch_item(b, m, it, u, v);
-    const FactorPlan pl = plan_tiles(v, b.many);
+    const FactorPlan pl = plan_tiles(v, b.share);
     const float scale = it.scale == 0.f ? 1.0f / (float)u.R : it.scale;
     const OutSpec os = out_spec(it);
     const Partial part = partial_of(v, pl, it.ws);
@@ -502,10 +540,7 @@ static size_t item_ws_bytes(const Unfold& u) {
     size_t need = plan_generic(u).ws_bytes;                    // any kernel may serve the build
     View v;
     if (make_view(u, &v)) {
-        for (int many = 0; many < 2; ++many) {
-            const size_t n = repack_bytes(v) + plan_tiles(v, many).ws_bytes;
-            if (n > need) need = n;
-        }
+        need = std::max(need, repack_bytes(v) + tiles_ws_bytes(v));
     }
     return align_up(need, 256);
 }
@@ -561,10 +596,10 @@ static Route route_of(const Unfold& u, const void* x, bool many, View* v) {
     return v->repack && !many && (long long)u.R * u.d * u.d <= GENERIC_MACS ? ROUTE_GENERIC : ROUTE_TILE;
 }
 
-static void fbatch_clear(FBatch& b, const kfac_factor_item* dev, int many) {
+static void fbatch_clear(FBatch& b, const kfac_factor_item* dev, int share) {
     b.table = dev;
     b.count = 0;
-    b.many = many;
+    b.share = share;
     b.prefix[0] = 0;
 }
 static void fbatch_add(FBatch& b, const kfac_factor_item* host, int i, int wgs) {
@@ -585,14 +620,22 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
         if (rc != KFAC_OK) return rc;
         n_tile += route_of(u, host[i].x, true, &v) == ROUTE_TILE;
     }
-    const int many = n_tile >= 16;
+    const bool many = n_tile >= 16;
+    TileWork work16 = {0, 0}, work32 = {0, 0};
+    for (int i = 0; i < count; ++i) {
+        Unfold u;
+        View v;
+        item_unfold(host[i], &u);
+        if (route_of(u, host[i].x, many, &v) == ROUTE_TILE) add_work(u.dtype == KFAC_F32 ? work32 : work16, v);
+    }
+    const int share16 = share_of(work16, false), share32 = share_of(work32, true);
     FBatch b, r, rmany;                                // rmany: builds of many splits (factor_tile_reduce_kernel<4>)
     auto repack = [&]() -> int {
         if (b.count) KFAC_LAUNCH(factor_repack_kernel, dim3(b.prefix[b.count]), dim3(256), stream, b);
-        fbatch_clear(b, dev, many);
+        fbatch_clear(b, dev, 0);
         return KFAC_OK;
     };
-    fbatch_clear(b, dev, many);
+    fbatch_clear(b, dev, 0);
     for (int i = 0; i < count; ++i) {
         Unfold u;
         View v;
@@ -611,10 +654,11 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
     static const int VAR_DTYPE[8] = {KFAC_BF16, KFAC_F16, KFAC_BF16, KFAC_F16, KFAC_BF16, KFAC_F16, KFAC_F32, KFAC_F32};
     for (int var = 0; var < 8; ++var) {
         int next = 0;
+        const int share = VAR_DTYPE[var] == KFAC_F32 ? share32 : share16;
         while (next < count) {
-            fbatch_clear(b, dev, many);
-            fbatch_clear(r, dev, many);
-            fbatch_clear(rmany, dev, many);
+            fbatch_clear(b, dev, share);
+            fbatch_clear(r, dev, share);
+            fbatch_clear(rmany, dev, share);
             struct Pick { int item, rows, wgs, reduce, nsplit; } pick[FMAXB];
             int n = 0;
             for (; next < count && n < FMAXB; ++next) {
@@ -622,7 +666,7 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
                 View v;
                 item_unfold(host[next], &u);
                 if (u.dtype != VAR_DTYPE[var] || route_of(u, host[next].x, many, &v) != ROUTE_TILE) continue;
-                const FactorPlan p = plan_tiles(v, many);
+                const FactorPlan p = plan_tiles(v, share);
                 if (p.tw != VAR_TW[var]) continue;
                 pick[n++] = {next, p.rows_per_split, (int)align_up(p.ntiles * p.nsplit, 8),   // (a multiple of 8: see factor_tile)
                              p.nsplit > 1 ? reduce_wgs(v, p) : 0, p.nsplit};

@@ -14,8 +14,9 @@
 // 16-byte block of zeros, so the slab in LDS is always complete and the inner loop has no special cases.
 //
 // What bounds it and how it is cut.  A TW x TW tile moves 2 TW elements per row through the L1 (64 bytes per cycle and
-// CU) for TW^2 multiply-adds, so with 128-wide tiles the copies alone take as many cycles as the matrix cores: wide
-// matrices get 256-wide tiles (8 wavefronts of 128 x 64, a ring of four 32-row slabs), which halves that.  Matrices of
+// CU) for TW^2 multiply-adds, so with 128-wide tiles the copies alone take as many cycles as the matrix cores: where there
+// is enough work (share_of), wide matrices get 256-wide tiles (8 wavefronts of 128 x 64, a ring of four 32-row slabs), which
+// halves that.  Matrices of
 // up to 128 (64) columns get one tile of that width.
 //
 // The bias column is not part of the tiled matrix (2048 + 1 columns would cost a ninth row of 256-wide tiles for one
