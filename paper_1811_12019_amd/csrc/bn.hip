@@ -2,7 +2,7 @@
 // shift_1..C), the gradient of sample n is
 //     g_n[c] = sum_s gout[n,s,c] * xhat[n,s,c],     g_n[C + c] = sum_s gout[n,s,c]        (s = spatial position)
 // and F = (1/N) sum_n g_n g_n^T (2C x 2C), or its diagonal.  This file builds the per-sample gradients from NHWC
-// tensors, for all BN layers of a network in one launch per 16-bit dtype plus one for the sums over chunks (HBM bound:
+// tensors, for all BN layers of a network in one launch per dtype plus one for the sums over chunks (HBM bound:
 // both tensors are read once), and applies the diagonal form; the full form is the generic factor build + damped
 // inverse + product on the (N x 2C) gradient matrix.
 #include <algorithm>
@@ -12,18 +12,22 @@
 namespace kfac {
 
 constexpr int BN_MAX = 64;            // layers per launch (argument block under 4 KB)
-constexpr int BN_UNIT = 32768;        // elements of each tensor per workgroup of the 16-bit kernel
-constexpr int BN_CVW = 64;            // 16-byte vectors (8 channels each) side by side in a workgroup, at most
+constexpr int BN_UNIT = 65536;        // bytes of each tensor per workgroup of the vector kernel
+constexpr int BN_CVW = 64;            // 16-byte vectors side by side in a workgroup, at most
 constexpr int BN_SP_GENERIC = 512;    // positions per workgroup of the general kernel
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
-// How one layer is cut into workgroups.  16-bit layers: a workgroup owns `cvw` vectors of `sp` consecutive positions of
-// one sample; its 256 threads are cvw vectors x (256 / cvw) position lanes.  General layers: all channels of `sp` positions.
+// channels of a 16-byte vector
+static inline __host__ __device__ int bn_vec(int dtype) { return dtype == KFAC_F32 ? 4 : 8; }
+
+// How one layer is cut into workgroups.  Layers whose channels are whole 16-byte vectors: a workgroup owns `cvw` vectors of
+// `sp` consecutive positions of one sample; its 256 threads are cvw vectors x (256 / cvw) position lanes.  General layers: all
+// channels of `sp` positions.
 struct BnPlan {
     int cvw, ncb, sp, nchunk;
 };
 
-static BnPlan bn_plan(int C, int HW, bool vec) {
+static BnPlan bn_plan(int C, int HW, int dtype, bool vec) {
     BnPlan p;
     if (!vec) {
         p.cvw = 0; p.ncb = 1;
@@ -31,11 +35,11 @@ static BnPlan bn_plan(int C, int HW, bool vec) {
         p.sp = BN_SP_GENERIC;
         return p;
     }
-    const int cv = C >> 3;
+    const int cv = C / bn_vec(dtype);
     p.cvw = cv < BN_CVW ? cv : BN_CVW;
     p.ncb = (cv + p.cvw - 1) / p.cvw;
     const int lanes = 256 / p.cvw;
-    int sp = BN_UNIT / (p.cvw * 8);
+    int sp = BN_UNIT / (p.cvw * 16);
     if (sp < 4 * lanes) sp = 4 * lanes;
     p.nchunk = (HW + sp - 1) / sp;
     p.sp = (HW + p.nchunk - 1) / p.nchunk;            // even chunks, no short tail
@@ -59,14 +63,16 @@ struct BnReduceBatch {
     float* g[BN_MAX];
 };
 
-// 16-bit NHWC, C % 8 == 0.  Both tensors are read once, 16 bytes per thread and load, eight loads in flight.
-template <bool F16>
+// NHWC, channels whole vectors.  Both tensors are read once, 16 bytes per thread and load, eight loads in flight.
+// (fp32 went through the general kernel before, one 4-byte load after the other: 53 layers at batch 2 19 ms, now @F32@.)
+template <int DTYPE>
 __global__ __launch_bounds__(256) void bn_partial_kernel(BnBatch b) {
-    __shared__ float red[256 * 16];                      // [position lane][half][vector][8]
+    constexpr int V = DTYPE == KFAC_F32 ? 4 : 8;
+    __shared__ float red[256 * 2 * V];                   // [position lane][half][vector][V]
     const int t = threadIdx.x;
     const int m = __syncthreads_count(t < b.count - 1 && b.prefix[t + 1] <= blockIdx.x);
     const int C = b.C[m], HW = b.HW[m], sp = b.sp[m], nchunk = b.nchunk[m];
-    const int cv = C >> 3;
+    const int cv = C / V;
     const int cvw = cv < BN_CVW ? cv : BN_CVW;
     const int ncb = (cv + cvw - 1) / cvw;
     const int lanes = 256 / cvw;
@@ -79,7 +85,7 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(BnBatch b) {
     const int vec0 = t % cvw, pl = t / cvw;
     const int vec = cb * cvw + vec0;
     const int s0 = chunk * sp, s1 = min(HW, s0 + sp);
-    float ds[8] = {}, db[8] = {};
+    float ds[V] = {}, db[V] = {};
     if (pl < lanes && vec < cv) {
         const size_t row0 = (size_t)n * HW;
         for (int s = s0 + pl; s < s1; s += 4 * lanes) {
@@ -98,26 +104,32 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(BnBatch b) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const unsigned xw = xv[u][k], gw = gv[u][k];
+                    if constexpr (DTYPE == KFAC_F32) {
+                        const float g = __uint_as_float(gw);
+                        ds[k] = fmaf(g, __uint_as_float(xw), ds[k]);
+                        db[k] += g;
+                        continue;
+                    }
                     float x0, x1, g0, g1;
-                    if constexpr (F16) {
+                    if constexpr (DTYPE == KFAC_F16) {
                         x0 = half_bits_to_float((uint16_t)(xw & 0xffff)); x1 = half_bits_to_float((uint16_t)(xw >> 16));
                         g0 = half_bits_to_float((uint16_t)(gw & 0xffff)); g1 = half_bits_to_float((uint16_t)(gw >> 16));
                     } else {
                         x0 = __uint_as_float(xw << 16); x1 = __uint_as_float(xw & 0xffff0000u);
                         g0 = __uint_as_float(gw << 16); g1 = __uint_as_float(gw & 0xffff0000u);
                     }
-                    ds[2 * k] = fmaf(g0, x0, ds[2 * k]);         db[2 * k] += g0;
-                    ds[2 * k + 1] = fmaf(g1, x1, ds[2 * k + 1]); db[2 * k + 1] += g1;
+                    ds[2 * k % V] = fmaf(g0, x0, ds[2 * k % V]);             db[2 * k % V] += g0;
+                    ds[(2 * k + 1) % V] = fmaf(g1, x1, ds[(2 * k + 1) % V]); db[(2 * k + 1) % V] += g1;
                 }
         }
     }
     // sum over the position lanes in a fixed order; every thread takes part
-    const int w8 = cvw * 8;                              // channels of this workgroup
+    const int w8 = cvw * V;                              // channels of this workgroup
     if (pl < lanes) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            red[pl * 2 * w8 + vec0 * 8 + e] = ds[e];
-            red[pl * 2 * w8 + w8 + vec0 * 8 + e] = db[e];
+        for (int e = 0; e < V; ++e) {
+            red[pl * 2 * w8 + vec0 * V + e] = ds[e];
+            red[pl * 2 * w8 + w8 + vec0 * V + e] = db[e];
         }
     }
     __syncthreads();
@@ -209,14 +221,14 @@ static bool bn_item_ok(const kfac_bn_item& it) {
 }
 
 static bool bn_item_vec(const kfac_bn_item& it) {
-    return it.dtype != KFAC_F32 && (it.C & 7) == 0 && (((uintptr_t)it.xhat | (uintptr_t)it.gout) & 15) == 0;
+    return it.C % bn_vec(it.dtype) == 0 && (((uintptr_t)it.xhat | (uintptr_t)it.gout) & 15) == 0;
 }
 
 // bytes of partial sums one layer needs (none when a single chunk covers all positions).  The 16-byte alignment of the
 // tensors is not known when only the shape is: both cuttings are covered.
 static size_t bn_item_ws(int N, int C, int HW, int dtype) {
-    int nchunk = bn_plan(C, HW, false).nchunk;
-    if (dtype != KFAC_F32 && (C & 7) == 0) nchunk = std::max(nchunk, bn_plan(C, HW, true).nchunk);
+    int nchunk = bn_plan(C, HW, dtype, false).nchunk;
+    if (C % bn_vec(dtype) == 0) nchunk = std::max(nchunk, bn_plan(C, HW, dtype, true).nchunk);
     return nchunk > 1 ? align_up((size_t)N * nchunk * 2 * C * sizeof(float), 256) : 0;
 }
 
@@ -242,14 +254,14 @@ extern "C" int kfac_bn_sample_grads_batched(const kfac_bn_item* items_host, int3
     char* wsp = (char*)ws;
     for (int first = 0; first < count; first += BN_MAX) {
         const int cnt = count - first < BN_MAX ? count - first : BN_MAX;
-        BnBatch b16, f16;                                 // bf16 and fp16 layers of this group
+        BnBatch lists[3];                                 // the fp32, bf16 and fp16 layers of this group
         BnReduceBatch rb;
-        b16.count = f16.count = rb.count = 0;
-        unsigned n16 = 0, nf16 = 0, nred = 0;
+        unsigned wgs[3] = {0, 0, 0}, nred = 0;
+        lists[KFAC_F32].count = lists[KFAC_BF16].count = lists[KFAC_F16].count = rb.count = 0;
         for (int i = 0; i < cnt; ++i) {
             const kfac_bn_item& it = items_host[first + i];
             const bool vec = bn_item_vec(it);
-            const BnPlan p = bn_plan(it.C, it.HW, vec);
+            const BnPlan p = bn_plan(it.C, it.HW, it.dtype, vec);
             float* dst = it.g;
             if (p.nchunk > 1) {
                 dst = (float*)wsp;
@@ -260,8 +272,8 @@ extern "C" int kfac_bn_sample_grads_batched(const kfac_bn_item* items_host, int3
             }
             wsp += bn_item_ws(it.N, it.C, it.HW, it.dtype);
             if (vec) {
-                BnBatch& b = it.dtype == KFAC_F16 ? f16 : b16;
-                unsigned& units = it.dtype == KFAC_F16 ? nf16 : n16;
+                BnBatch& b = lists[it.dtype];
+                unsigned& units = wgs[it.dtype];
                 const int k = b.count++;
                 b.prefix[k] = units;
                 b.C[k] = it.C; b.HW[k] = it.HW; b.sp[k] = p.sp; b.nchunk[k] = p.nchunk;
@@ -272,13 +284,13 @@ extern "C" int kfac_bn_sample_grads_batched(const kfac_bn_item* items_host, int3
                             (int)it.dtype, (int)it.C, (int)it.HW, p.nchunk, dst);
             }
         }
-        if (b16.count) {
-            b16.prefix[b16.count] = n16;
-            KFAC_LAUNCH(bn_partial_kernel<false>, dim3(n16), dim3(256), (hipStream_t)stream, b16);
-        }
-        if (f16.count) {
-            f16.prefix[f16.count] = nf16;
-            KFAC_LAUNCH(bn_partial_kernel<true>, dim3(nf16), dim3(256), (hipStream_t)stream, f16);
+        for (int dt = 0; dt < 3; ++dt) {
+            BnBatch& b = lists[dt];
+            if (b.count == 0) continue;
+            b.prefix[b.count] = wgs[dt];
+            if (dt == KFAC_F32) KFAC_LAUNCH(bn_partial_kernel<KFAC_F32>, dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b);
+            else if (dt == KFAC_BF16) KFAC_LAUNCH(bn_partial_kernel<KFAC_BF16>, dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b);
+            else KFAC_LAUNCH(bn_partial_kernel<KFAC_F16>, dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b);
         }
         if (rb.count) {
             rb.prefix[rb.count] = nred;
