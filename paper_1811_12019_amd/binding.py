@@ -206,7 +206,10 @@ def _check(status: int, where: str) -> None:
 
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # (the current stream's handle without a Stream object around it: 0.2 us instead of 2.8 us on every call)
+        if not torch.cuda.is_initialized():
+            return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
