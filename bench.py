@@ -53,7 +53,7 @@ def kernel_work(net: kstep.KfacNetworkStep):
                                   for d in dims)),
         # latency-bound helpers of the sweep (one workgroup per matrix / per 128-row slab): first-block inverses of nb^3
         # flops (fp32 matrix cores), panel products of 2 d nb^2 (bf16 matrix cores, operands split three ways)
-        "inv_pivot_kernel": ("mfma", PEAK["mfma_f32"], "TFLOP/s", sum(kstep.inverse_first_pivot_flops(d) for d in dims)),
+        "inv_begin_kernel": ("mfma", PEAK["mfma_f32"], "TFLOP/s", sum(kstep.inverse_first_pivot_flops(d) for d in dims)),
         "inv_panel_kernel": ("mfma", PEAK["mfma_bf16x3"], "TFLOP/s", sum(kstep.inverse_panel_flops(d) for d in dims)),
         "gemm_nt_kernel": ("mfma", PEAK["mfma_f16x2"], "TFLOP/s", sum(kstep.precondition_flops(s.d_G, s.d_A) for s in shapes)),
         # the operands' piece planes: every element read (4 B) and written (2 x 2 B): the gradient by the preconditioning

@@ -16,7 +16,7 @@
 // 4609-wide factor, so the launches are arranged to keep the chain short and the bulk of the flops off it:
 //   * the update launch of step k gives the tile that is pivot block k + 1 to a workgroup of its own, which updates
 //     it, keeps it in registers and inverts it at once: a step is two launches (panel, update), and the pivot runs
-//     beside the tile updates (inv_pivot_kernel only serves a matrix's first block and single-block matrices);
+//     beside the tile updates (inv_begin_kernel only serves a matrix's first block and single-block matrices);
 //   * steps are taken in groups of GM; inside a group only the next panel's block column / row and the diagonal
 //     tiles of the blocks still to come are brought up to date, every other tile receives a whole group as one
 //     rank-(GM * 128) update during the next group's launches (see Plan below);
@@ -48,7 +48,6 @@ struct Batch {
     int count;                        // matrices in this launch
     int prefix[MAXB + 1];             // workgroup prefix sums over them
     int dim[MAXB];
-    int step[MAXB];                   // the elimination step this launch takes for the matrix, or -1: none
     float damping[MAXB];
     const float* damping_dev[MAXB];   // NULL, or where the damping is to be read from instead
     const float* S[MAXB];
@@ -288,37 +287,6 @@ __device__ inline WsView ws_view(gfloat* ws, int dim) {
     v.P = v.buf0 + NBUF * v.stride;
     v.SC = v.P + (size_t)NB * NB;
     return v;
-}
-
-// W(lower) = S(lower) + lambda I; info = 0.  Tiles on the diagonal get both triangles (of S's lower one): the pivot code
-// works on whole 32 x 32 diagonal blocks, which the updates keep whole.
-__global__ __launch_bounds__(256) void inv_init_kernel(Batch b) {
-    int m, tile;
-    locate(b, blockIdx.x, m, tile);
-    const Item it = get_item(b, m);
-    const int d = it.dim;
-    int I, J;
-    tri_decode(tile, I, J);
-    if (tile == 0 && threadIdx.x == 0 && it.info) *it.info = 0;
-    const WsView ws = ws_view(it.ws, d);
-    const gfloat* __restrict__ S = it.S;
-    const float lam = it.damping;
-    const int c = threadIdx.x & 127, rh = threadIdx.x >> 7;
-    const int col = J * NB + c;
-#pragma unroll 1
-    for (int r8 = 0; r8 < NB; r8 += 16) {
-        float v[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {                    // loads only: arithmetic on a guarded load would make the
-            const int row = I * NB + r8 + 2 * i + rh;    // compiler wait for each load in turn
-            v[i] = (row < d && col < d && (I == J || col <= row)) ? S[(size_t)max(row, col) * d + min(row, col)] : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int row = I * NB + r8 + 2 * i + rh;
-            if (row < d && col < ws.ldw) ws.W[(size_t)row * ws.ldw + col] = v[i] + (row == col ? lam : 0.f);
-        }
-    }
 }
 
 // ---- pivot block -----------------------------------------------------------------------------------------------
@@ -682,60 +650,94 @@ __device__ __forceinline__ void pivot_write(const v16f (&acc)[2][2], float* __re
     }
 }
 
-// Pivot block `step` of every matrix of the batch, read from the working copy.
-// from_S: single-block matrices: read S + lambda I and write the caller's output directly.
-__global__ __launch_bounds__(256) void inv_pivot_kernel(Batch b, int step, int from_S) {
-    __shared__ __attribute__((aligned(16))) float lds[PIV_LDS_FLOATS];
-    __builtin_amdgcn_s_setprio(3);
-    const int m = blockIdx.x;
-    const Item it = get_item(b, m);
-    const int d = it.dim;
-    const int k0 = step * NB;
-    const int nb = min(NB, d - k0);
-    const bool last = k0 + NB >= d;
+// The first pivot block of a matrix, S + lambda I; the only one of a single-block matrix, whose output this writes.
+__device__ __forceinline__ void begin_pivot(const Item& it, float* __restrict__ lds) {
+    const int d = it.dim, nb = min(NB, d);
+    const bool single = d <= NB;
     const int t = threadIdx.x;
     const WsView ws = ws_view(it.ws, d);
-
-    // ---- load: lower triangle, row-wise.  All loads are issued before the first LDS store so that the block costs
-    //      one memory round trip, not one per row group ----
-    {
-        const int c4 = (t & 31) * 4, r0 = t >> 5;        // 8 rows x 32 float4 per pass, 16 passes
-        const bool vec_ok = !from_S;                     // the padded working copy is 16-byte aligned, S need not be
-        v4f v[16];
+    // lower triangle, row-wise.  All loads are issued before the first LDS store so that the block costs one memory round
+    // trip, not one per row group
+    const int c4 = (t & 31) * 4, r0 = t >> 5;            // 8 rows x 32 float4 per pass, 16 passes
+    v4f v[16];
+    if (nb == NB) {
+#pragma unroll
+        for (int p = 0; p < 16; ++p) v[p] = *(const KFAC_AS1 v4f_a4*)(it.S + (size_t)(r0 + 8 * p) * d + c4);
+    } else {
 #pragma unroll
         for (int p = 0; p < 16; ++p) {
             const int row = r0 + 8 * p;
-            v4f x = {0.f, 0.f, 0.f, 0.f};
+            v[p] = v4f{0.f, 0.f, 0.f, 0.f};
             if (row < nb && c4 <= row) {
-                if (vec_ok) {
-                    x = *(const KFAC_AS1 v4f*)&ws.W[(size_t)(k0 + row) * ws.ldw + k0 + c4];
-                } else {
-                    const gfloat* src = it.S + (size_t)(k0 + row) * d + k0 + c4;
+                const gfloat* src = it.S + (size_t)row * d + c4;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (c4 + i <= row) x[i] = src[i];            // (the damping is added at the LDS store below)
-                }
+                for (int i = 0; i < 4; ++i)
+                    if (c4 + i <= row) v[p][i] = src[i];
             }
-            v[p] = x;
         }
+    }
 #pragma unroll
-        for (int p = 0; p < 16; ++p) {
-            const int row = r0 + 8 * p;
+    for (int p = 0; p < 16; ++p) {
+        const int row = r0 + 8 * p;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (row < nb && c4 + i <= row) lds[tri_at(row, c4 + i)] = v[p][i] + ((from_S && c4 + i == row) ? it.damping : 0.f);
-        }
+        for (int i = 0; i < 4; ++i)
+            if (row < nb && c4 + i <= row) lds[tri_at(row, c4 + i)] = v[p][i] + (c4 + i == row ? it.damping : 0.f);
     }
     __syncthreads();
     v16f acc[2][2];
     pivot_fill(acc, lds, nb);
     const int f = pivot_sweep(acc, nb, lds);
-    if (t == 0 && it.info) {
-        if (from_S) *it.info = f;                                       // single-block matrix: this is its only kernel
-        else if (f != 0) atomicCAS((int*)it.info, 0, k0 + f);           // keep the first failing minor
-    }
-    pivot_write(acc, lds, it, ws, k0, nb, last, from_S != 0);
+    if (t == 0 && it.info) *it.info = f;                 // (later pivots: upd_next_pivot)
+    pivot_write(acc, lds, it, ws, 0, nb, single, single);
 }
+
+// A quarter (32 rows) of tile (I, J) of the working copy: W(lower) = S(lower) + lambda I.  Tiles on the diagonal get both
+// triangles (of S's lower one): the pivot code works on whole 32 x 32 diagonal blocks, which the updates keep whole.
+__device__ __forceinline__ void begin_tile(const Item& it, int I, int J, int quarter) {
+    const int d = it.dim;
+    const WsView ws = ws_view(it.ws, d);
+    const gfloat* __restrict__ S = it.S;
+    const int c = threadIdx.x & 127, rh = threadIdx.x >> 7;
+    const int col = J * NB + c, row0 = I * NB + quarter * 32 + rh;
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {                       // loads only: arithmetic on a guarded load would make the
+        const int row = row0 + 2 * i;                    // compiler wait for each load in turn
+        v[i] = (row < d && col < d && (I == J || col <= row)) ? S[(size_t)max(row, col) * d + min(row, col)] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int row = row0 + 2 * i;
+        if (row < d && col < ws.ldw) ws.W[(size_t)row * ws.ldw + col] = v[i] + (row == col ? it.damping : 0.f);
+    }
+}
+
+__device__ __forceinline__ void begin_tile_of(const Batch& b, int wg) {
+    int m, local;
+    locate(b, wg, m, local);
+    int I, J;
+    tri_decode(1 + (local >> 2), I, J);
+    begin_tile(get_item(b, m), I, J, local & 3);
+}
+
+// Start of every matrix of the batch: its first pivot block and, in the workgroups after the pivots', the damped working copy
+// (of matrices with more than one block; the tile of the pivot block is the pivot's to write).  The copies are done before
+// the pivots are; in a launch before the pivots' they took 15 us of every inversion's chain.
+__global__ __launch_bounds__(256) void inv_begin_kernel(Batch b) {
+    __shared__ __attribute__((aligned(16))) float lds[PIV_LDS_FLOATS];
+    if ((int)blockIdx.x < b.count) {
+        __builtin_amdgcn_s_setprio(3);
+        begin_pivot(get_item(b, blockIdx.x), lds);
+        return;
+    }
+    begin_tile_of(b, blockIdx.x - b.count);
+}
+
+// The working copies alone, for batches whose copies do not fit the chip beside the pivots: these workgroups need a tenth of
+// the pivot's registers and no LDS, and find room between those of other streams (a network's step at batch 32, whose
+// factor builds run beside: 5.87 ms, with the copies in the pivots' launch 6.07 ms).
+__global__ __launch_bounds__(256) void inv_init_kernel(Batch b) { begin_tile_of(b, blockIdx.x); }
+constexpr int BEGIN_TOGETHER = 768;      // quarter tiles: three workgroups to a CU
 
 // T = U . P for every 128-row slab of block column k; U is copied aside for the update.  Slabs below the pivot
 // block read the column block itself; slabs above it read block row k transposed.
@@ -1492,24 +1494,16 @@ static int run_group(const kfac_inverse_item* h, int count, hipStream_t stream) 
     int n_multi = 0;
     while (n_multi < count && nblk_of(h[n_multi].dim) > 1) ++n_multi;
 
-    // single-block matrices: damp, invert and write in one kernel, straight from S
-    for (int first = n_multi; first < count; first += MAXB) {
-        fill_batch(b, h + first, min(MAXB, count - first));
-        KFAC_LAUNCH(inv_pivot_kernel, dim3(b.count), dim3(256), stream, b, 0, 1);
-    }
-    if (n_multi == 0) return KFAC_OK;
-    // damped working copies, then the first pivot blocks (later ones: by the update launches)
-    for (int first = 0; first < n_multi; first += MAXB) {
-        const int n = min(MAXB, n_multi - first);
+    for (int first = 0; first < count; first += MAXB) {
+        const int n = min(MAXB, count - first);
         fill_batch(b, h + first, n);
         b.prefix[0] = 0;
-        for (int i = 0; i < n; ++i) b.prefix[i + 1] = b.prefix[i] + tri_tiles(h[first + i].dim);
-        KFAC_LAUNCH(inv_init_kernel, dim3(b.prefix[n]), dim3(256), stream, b);
+        for (int i = 0; i < n; ++i) b.prefix[i + 1] = b.prefix[i] + 4 * (tri_tiles(h[first + i].dim) - 1);
+        const bool together = b.prefix[n] <= BEGIN_TOGETHER;
+        if (!together) KFAC_LAUNCH(inv_init_kernel, dim3(b.prefix[n]), dim3(256), stream, b);
+        KFAC_LAUNCH(inv_begin_kernel, dim3(n + (together ? b.prefix[n] : 0)), dim3(256), stream, b);
     }
-    for (int first = 0; first < n_multi; first += MAXB) {
-        fill_batch(b, h + first, min(MAXB, n_multi - first));
-        KFAC_LAUNCH(inv_pivot_kernel, dim3(b.count), dim3(256), stream, b, 0, 0);
-    }
+    if (n_multi == 0) return KFAC_OK;
     // One panel and one update launch per step of the matrix with the most blocks.  A matrix with fewer blocks takes
     // its steps at evenly spread launches rather than in the first ones: the tile updates of the whole batch are then
     // spread over all launches, each of which lasts at least as long as a pivot workgroup anyway.
