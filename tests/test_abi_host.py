@@ -155,6 +155,17 @@ def test_bad_arguments_are_rejected_on_the_host():
     assert lib.kfac_precondition(fake, fake, fake, 4, 5, fake, ctypes.c_void_p(0x9000), 1 << 20, None) == kb.KFAC_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("C,HW", [(8, 4097), (64, 552), (64, 12544), (256, 3136), (264, 513), (512, 784), (2048, 49)])
+def test_bn_scratch_does_not_depend_on_the_dtype(C, HW):
+    """An fp32 layer whose channels are whole vectors in every dtype needs no more scratch than a 16-bit one, so that the
+    single-layer size, which is asked for by shape alone, is the 16-bit one."""
+    lib = kb.load_library()
+    size = {dt: lib.kfac_bn_sample_grads_batched_workspace_bytes((kb.kfac_bn_item * 1)(kb.kfac_bn_item(0x1000, 0x1000, 0x1000, 3, C, HW, dt)), 1)
+            for dt in (kb.KFAC_F32, kb.KFAC_BF16, kb.KFAC_F16)}
+    assert size[kb.KFAC_F32] <= size[kb.KFAC_BF16] == size[kb.KFAC_F16]
+    assert lib.kfac_bn_sample_grads_workspace_bytes(3, C, HW) == size[kb.KFAC_BF16]
+
+
 def test_product_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_1811_12019_amd")
     for dirpath, _, files in os.walk(pkg):
