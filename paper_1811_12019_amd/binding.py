@@ -205,12 +205,14 @@ def _check(status: int, where: str) -> None:
 
 
 def _stream(stream) -> int:
-    if stream is None:
-        # (the current stream's handle without a Stream object around it: 0.2 us instead of 2.8 us on every call)
-        if not torch.cuda.is_initialized():
-            return torch.cuda.current_stream().cuda_stream
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+    if stream is not None:
+        return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+    # The current stream's handle without a Stream object around it (0.2 us instead of 2.8 us on every call), where this torch
+    # has the two functions for that: they are not part of its public interface.
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(device())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:

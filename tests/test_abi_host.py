@@ -166,6 +166,22 @@ def test_bn_scratch_does_not_depend_on_the_dtype(C, HW):
     assert lib.kfac_bn_sample_grads_workspace_bytes(3, C, HW) == size[kb.KFAC_BF16]
 
 
+@pytest.mark.parametrize("missing", [(), ("_cuda_getDevice",), ("_cuda_getCurrentRawStream",), ("_cuda_getDevice", "_cuda_getCurrentRawStream")])
+def test_current_stream_with_and_without_torchs_private_functions(monkeypatch, missing):
+    import types
+    import torch
+    private = types.SimpleNamespace(_cuda_getDevice=lambda: 3, _cuda_getCurrentRawStream=lambda device: 1000 + device)
+    for name in missing:
+        delattr(private, name)
+    monkeypatch.setattr(torch, "_C", private)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert kb._stream(None) == (77 if missing else 1003)
+    assert kb._stream(5) == 5 and kb._stream(types.SimpleNamespace(cuda_stream=6)) == 6
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)          # (current_stream() initialises)
+    assert kb._stream(None) == 77
+
+
 def test_product_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_1811_12019_amd")
     for dirpath, _, files in os.walk(pkg):
