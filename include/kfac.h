@@ -92,8 +92,11 @@ int kfac_factor_G(const kfac_layer_desc* desc, const void* gout, float scale, fl
 /* Many factor builds at once (all layers of a network): builds that the matrix-core kernel can serve share a
  * launch, so that the many small ones fill the machine together.  items_host[i] / items_dev[i] describe the same
  * build (device copy uploaded once by the caller); each item's `ws` needs kfac_factor_workspace_bytes(op, &desc)
- * bytes of its own.  Results are identical to the single calls.  An item may instead fold its result into a running
- * average (`running`) or deliver it as a packed upper triangle (`packed`); see the fields. */
+ * bytes of its own.  Deterministic: the same call gives the same bits.  While fewer than 16 of the call's builds are ones the
+ * matrix cores can take, the results are those of the single calls, bit for bit; in larger calls the rows of a build are
+ * cut by the work of the whole call, and its fp32 sums may differ from the single call's in their last bits.  An item may
+ * instead fold its result into a running average (`running`) or deliver it as a packed upper triangle (`packed`); see the
+ * fields. */
 typedef struct kfac_factor_item {
     kfac_layer_desc desc;
     const void* x;       /* act (op = KFAC_OP_FACTOR_A) or gout (op = KFAC_OP_FACTOR_G), device */

@@ -305,11 +305,11 @@ static void add_work(TileWork& w, const View& v) {
     w.wide += (v.u.d <= 128 ? 1.0 : 2.0 * m * (m + 1)) * v.u.R;
 }
 
-// How they are cut.  The rows of a workgroup: half of what each of the 768 workgroups that run at a time would get of all
-// the work, within limits.  More leaves the chip waiting for the last ones (18,816 rows of the first stage's layers at 3200
-// to a workgroup 119 us, at 6400 181 us), less adds partial sums, each as much traffic as a finished tile, for nothing (the third
-// stage's 18 layers at 1568 rows: 151 us unsplit, 334 us in two).  When there is little work the launch of the second pass
-// weighs too.
+// How they are cut (in a call of few builds each by its own work: run_factor_items).  The rows of a workgroup: half of what
+// each of the 768 workgroups that run at a time would get of all the work, within limits.  More leaves the chip waiting for the
+// last ones (18,816 rows of the first stage's layers at 3200 to a workgroup 119 us, at 6400 181 us), less adds partial sums, each
+// as much traffic as a finished tile, for nothing (the third stage's 18 layers at 1568 rows: 151 us unsplit, 334 us in two).  When
+// there is little work the launch of the second pass weighs too.
 // Width: a 256-wide tile halves the operand traffic per product, but a workgroup fills a CU, its epilogue overlaps with
 // nothing and a matrix is padded to multiples of 256.  It is the better one only for a lot of work with little padding (third
 // stage at 25,088 rows: 1385 us against 1600 us), or for so much that padding and the launch's end do not show (all of the
@@ -365,8 +365,8 @@ struct FBatch {
     const kfac_factor_item* table;   // device table, or nullptr -> `single`
     kfac_factor_item single;
     int count;
-    int share;                       // plan_tiles' argument for every build of this launch
     int index[FMAXB];                // table index of the i-th build of this launch
+    int share[FMAXB];                // plan_tiles' argument for it
     int prefix[FMAXB + 1];           // workgroup prefix sums
 };
 
@@ -397,7 +397,7 @@ void factor_tile_kernel(FBatch b) {
     Unfold u;
     View v;
     fbatch_item(b, m, it, u, v);
-    const FactorPlan p = plan_tiles(v, b.share);
+    const FactorPlan p = plan_tiles(v, b.share[m]);
     const float scale = it.scale == 0.f ? 1.0f / (float)u.R : it.scale;
     const KFAC_AS1 unsigned char* x = (const KFAC_AS1 unsigned char*)(v.repack ? it.ws : it.x);
     factor_tile<TW, KIND>(v, x, scale, out_spec(it), partial_of(v, p, it.ws), p.rows_per_split, p.tiles_dim, p.ntiles, p.nsplit,
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(256 * GROUPS) void factor_tile_reduce_kernel(FBatch
     Unfold u;
     View v;
     fbatch_item(b, m, it, u, v);
-    const FactorPlan pl = plan_tiles(v, b.share);
+    const FactorPlan pl = plan_tiles(v, b.share[m]);
     const float scale = it.scale == 0.f ? 1.0f / (float)u.R : it.scale;
     const OutSpec os = out_spec(it);
     const Partial part = partial_of(v, pl, it.ws);
@@ -596,14 +596,14 @@ static Route route_of(const Unfold& u, const void* x, bool many, View* v) {
     return v->repack && !many && (long long)u.R * u.d * u.d <= GENERIC_MACS ? ROUTE_GENERIC : ROUTE_TILE;
 }
 
-static void fbatch_clear(FBatch& b, const kfac_factor_item* dev, int share) {
+static void fbatch_clear(FBatch& b, const kfac_factor_item* dev) {
     b.table = dev;
     b.count = 0;
-    b.share = share;
     b.prefix[0] = 0;
 }
-static void fbatch_add(FBatch& b, const kfac_factor_item* host, int i, int wgs) {
+static void fbatch_add(FBatch& b, const kfac_factor_item* host, int i, int share, int wgs) {
     b.index[b.count] = i;
+    b.share[b.count] = share;
     b.prefix[b.count + 1] = b.prefix[b.count] + wgs;
     if (!b.table) b.single = host[i];
     ++b.count;
@@ -629,19 +629,30 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
         if (route_of(u, host[i].x, many, &v) == ROUTE_TILE) add_work(u.dtype == KFAC_F32 ? work32 : work16, v);
     }
     const int share16 = share_of(work16, false), share32 = share_of(work32, true);
+    // Few builds: each is cut as it would be in a call of its own, so that its result is the same to the last bit (kfac.h).  By
+    // the work of the whole call, one to seven layers of ResNet-50 at batch 2 to 32 take between 26 % less time (five layers of the
+    // third stage at batch 8: 52 instead of 70 us) and 11 % more (four layers around the second stage's start at batch 8: 70 instead
+    // of 63 us).
+    auto share_for = [&](const View& v) -> int {
+        const bool f32 = v.u.dtype == KFAC_F32;
+        if (many) return f32 ? share32 : share16;
+        TileWork own = {0, 0};
+        add_work(own, v);
+        return share_of(own, f32);
+    };
     FBatch b, r, rmany;                                // rmany: builds of many splits (factor_tile_reduce_kernel<4>)
     auto repack = [&]() -> int {
         if (b.count) KFAC_LAUNCH(factor_repack_kernel, dim3(b.prefix[b.count]), dim3(256), stream, b);
-        fbatch_clear(b, dev, 0);
+        fbatch_clear(b, dev);
         return KFAC_OK;
     };
-    fbatch_clear(b, dev, 0);
+    fbatch_clear(b, dev);
     for (int i = 0; i < count; ++i) {
         Unfold u;
         View v;
         item_unfold(host[i], &u);
         if (route_of(u, host[i].x, many, &v) != ROUTE_TILE || !v.repack) continue;
-        fbatch_add(b, host, i, repack_wgs(u, v));
+        fbatch_add(b, host, i, 0, repack_wgs(u, v));
         if (b.count == FMAXB) {
             int rc = repack();
             if (rc != KFAC_OK) return rc;
@@ -654,29 +665,29 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
     static const int VAR_DTYPE[8] = {KFAC_BF16, KFAC_F16, KFAC_BF16, KFAC_F16, KFAC_BF16, KFAC_F16, KFAC_F32, KFAC_F32};
     for (int var = 0; var < 8; ++var) {
         int next = 0;
-        const int share = VAR_DTYPE[var] == KFAC_F32 ? share32 : share16;
         while (next < count) {
-            fbatch_clear(b, dev, share);
-            fbatch_clear(r, dev, share);
-            fbatch_clear(rmany, dev, share);
-            struct Pick { int item, rows, wgs, reduce, nsplit; } pick[FMAXB];
+            fbatch_clear(b, dev);
+            fbatch_clear(r, dev);
+            fbatch_clear(rmany, dev);
+            struct Pick { int item, share, rows, wgs, reduce, nsplit; } pick[FMAXB];
             int n = 0;
             for (; next < count && n < FMAXB; ++next) {
                 Unfold u;
                 View v;
                 item_unfold(host[next], &u);
                 if (u.dtype != VAR_DTYPE[var] || route_of(u, host[next].x, many, &v) != ROUTE_TILE) continue;
+                const int share = share_for(v);
                 const FactorPlan p = plan_tiles(v, share);
                 if (p.tw != VAR_TW[var]) continue;
-                pick[n++] = {next, p.rows_per_split, (int)align_up(p.ntiles * p.nsplit, 8),   // (a multiple of 8: see factor_tile)
+                pick[n++] = {next, share, p.rows_per_split, (int)align_up(p.ntiles * p.nsplit, 8),   // (a multiple of 8: see factor_tile)
                              p.nsplit > 1 ? reduce_wgs(v, p) : 0, p.nsplit};
             }
             if (n == 0) continue;
             // the longest workgroups first: the short ones fill the end of the launch
             std::stable_sort(pick, pick + n, [](const Pick& a, const Pick& c) { return a.rows > c.rows; });
             for (int i = 0; i < n; ++i) {
-                fbatch_add(b, host, pick[i].item, pick[i].wgs);
-                if (pick[i].reduce) fbatch_add(pick[i].nsplit >= 32 ? rmany : r, host, pick[i].item, pick[i].reduce);
+                fbatch_add(b, host, pick[i].item, pick[i].share, pick[i].wgs);
+                if (pick[i].reduce) fbatch_add(pick[i].nsplit >= 32 ? rmany : r, host, pick[i].item, pick[i].share, pick[i].reduce);
             }
             switch (var) {
                 case 0: rc = launch_tiles<64, 0>(b, stream); break;

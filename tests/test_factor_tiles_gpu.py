@@ -75,3 +75,25 @@ def test_factor_outputs(many, layout, dtype, order):
         np.testing.assert_array_equal(got, got.T)
         np.testing.assert_array_equal(p.cpu().numpy(), ko.pack_upper(got).astype(np.float32))
         np.testing.assert_array_equal(r.cpu().numpy(), want_r.cpu().numpy())
+
+
+@pytest.mark.parametrize("layout,dtype,order", [(NHWC, kb.KFAC_BF16, KKC), (NCHW, kb.KFAC_F16, CKK), (NHWC, kb.KFAC_F32, KKC)])
+def test_few_builds_equal_single_calls(layout, dtype, order):
+    """14 matrix-core builds in one call, each with enough rows to be split and together enough work that a cut by the whole
+    call would split them differently (9,248 rows: 6 ranges instead of 8; fp32: 36 and more): each equals its single call bit
+    for bit."""
+    shapes = [synth.LayerShape("s3x3", 8, 48, 34, 34, 72, 3, 3, 1, 1), synth.LayerShape("s1x1", 8, 264, 34, 34, 136, 1, 1, 1, 0)]
+    builds = []
+    for i in range(7):
+        s = shapes[i % 2]
+        act, gout = _NP_ROUND[dtype](synth.make_act(s, 30 + i)), _NP_ROUND[dtype](synth.make_gout(s, 30 + i))
+        desc = kb.make_desc(s, layout, dtype, order)
+        builds.append((kb.KFAC_OP_FACTOR_A, desc, kb.to_device_tensor(act, layout, dtype, DEV), s.d_A))
+        builds.append((kb.KFAC_OP_FACTOR_G, desc, kb.to_device_tensor(gout, layout, dtype, DEV), s.d_G))
+    outs = [torch.full((d, d), float("nan"), device=DEV) for _, _, _, d in builds]
+    kb.kfac_factor_batched(kb.FactorBatch([(op, desc, x, o, 0.0) for (op, desc, x, _), o in zip(builds, outs)], device=DEV))
+    for (op, desc, x, d), got in zip(builds, outs):
+        alone = torch.full((d, d), float("nan"), device=DEV)
+        ws = kb.alloc_workspace(kb.kfac_factor_workspace_bytes(op, desc), DEV)
+        (kb.kfac_factor_A if op == kb.KFAC_OP_FACTOR_A else kb.kfac_factor_G)(desc, x, 0.0, alone, ws)
+        np.testing.assert_array_equal(got.cpu().numpy(), alone.cpu().numpy())
