@@ -75,7 +75,9 @@ enum { KFAC_OP_FACTOR_A = 0, KFAC_OP_FACTOR_G = 1 };
 
 const char* kfac_status_string(int status);
 
-/* Workspace a factor build needs (split-K partial tiles), op = KFAC_OP_FACTOR_A / _G.  0 on a bad descriptor. */
+/* Workspace a factor build needs, op = KFAC_OP_FACTOR_A / _G: partial sums of its row ranges, as many as any call it may be
+ * part of makes, and a channels-last copy of the tensor if it is NCHW or its channels are not whole 16-byte vectors (padded to
+ * such, so up to 8 / C times the tensor).  Enough for every alignment of the tensor.  0 on a bad descriptor. */
 size_t kfac_factor_workspace_bytes(int op, const kfac_layer_desc* desc);
 
 /* Stage 1.  A[d_A x d_A] = scale * sum_r abar_r abar_r^T over the R unfolded input patches abar_r of `act`

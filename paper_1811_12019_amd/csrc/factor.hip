@@ -269,14 +269,18 @@ static FactorPlan plan_generic(const Unfold& u) {
 constexpr int SHARE_WIDE = 1 << 20;
 constexpr int ROWS_PER_WG_MAX = 6400, ROWS_PER_WG_MAX_F32 = 1600;
 constexpr int ROWS_PER_WG_MIN = 512, ROWS_PER_WG_MIN_F32 = 64;
+constexpr int SHARE_LEAST = 1024, SHARE_LEAST_F32 = 128;           // the fewest rows share_of gives a workgroup
 
-// splits that keep a build's partial sums below 34 MB (67 MB), unless a workgroup's rows would pass the maximum
+// splits that keep a build's partial sums below 34 MB (256-wide tiles: 67 MB), unless a workgroup's rows would pass the maximum
 static inline __host__ __device__ int most_splits(int R, int tw, int ntiles, bool f32) {
     const int cap = (tw == 256 ? 256 : 512) / ntiles, need = ceil_div(R, f32 ? ROWS_PER_WG_MAX_F32 : ROWS_PER_WG_MAX);
     const int most = R / (f32 ? ROWS_PER_WG_MIN_F32 : ROWS_PER_WG_MIN);
     const int ns = cap > need ? cap : need;
     return ns > most ? (most > 1 ? most : 1) : (ns > 1 ? ns : 1);
 }
+
+// multiples of 8 keep a row range on one XCD
+static inline __host__ __device__ int xcd_splits(int ns) { return ns >= 8 ? ns / 8 * 8 : ns; }
 
 static inline __host__ __device__ FactorPlan plan_tiles(const View& v, int share) {
     FactorPlan p;
@@ -288,7 +292,7 @@ static inline __host__ __device__ FactorPlan plan_tiles(const View& v, int share
     const int most = most_splits(R, p.tw, p.ntiles, f32);
     int ns = ceil_div(R, share & (SHARE_WIDE - 1));
     if (ns > most) ns = most;
-    if (ns >= 8) ns = ns / 8 * 8;                          // multiples of 8 keep a row range on one XCD
+    ns = xcd_splits(ns);
     p.rows_per_split = ceil_div(ceil_div(R, ns), 64) * 64;
     p.nsplit = ceil_div(R, p.rows_per_split);
     p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * ((size_t)p.ntiles * p.tw * p.tw + (size_t)p.tiles_dim * p.tw) * sizeof(float) : 0;
@@ -314,22 +318,27 @@ static void add_work(TileWork& w, const View& v) {
 // nothing and a matrix is padded to multiples of 256.  It is the better one only for a lot of work with little padding (third
 // stage at 25,088 rows: 1385 us against 1600 us), or for so much that padding and the launch's end do not show (all of the
 // network at 128 images: 5.1 against 5.4 ms; at 64 both 2.55 ms, at 32 1480 us against 1350 us).
+constexpr double WIDE_PER_SLOT = 24000;
 static int share_of(const TileWork& w, bool f32) {
     const double per_slot = w.narrow / 768;
-    const double least = f32 ? (per_slot < 100 ? 128 : 256) : (per_slot < 512 ? 1024 : 1600);
+    const double least = f32 ? (per_slot < 100 ? SHARE_LEAST_F32 : 256) : (per_slot < 512 ? SHARE_LEAST : 1600);
     const double rows = std::min(std::max(0.52 * per_slot, least), (double)(f32 ? ROWS_PER_WG_MAX_F32 : ROWS_PER_WG_MAX));
-    const bool wide = per_slot >= (w.wide <= 1.15 * w.narrow ? 24000 : 100000);
+    static_assert(0.52 * WIDE_PER_SLOT >= ROWS_PER_WG_MAX, "256-wide tiles always come with the most rows (tiles_ws_bytes)");
+    const bool wide = per_slot >= (w.wide <= 1.15 * w.narrow ? WIDE_PER_SLOT : 100000);
     return (int)rows + (wide && !f32 ? SHARE_WIDE : 0);
 }
 
-// An upper bound of plan_tiles' workspace over all shares.
+// An upper bound of plan_tiles' workspace over all shares that share_of gives: the partial sums of as many splits as the fewest
+// rows to a workgroup make.  (The factors of ResNet-50 from channels-last bf16 tensors: 2.9 GB
+// at batch 32, 3.9 GB at batch 128; most_splits alone would ask for 3.5 and 5.2 GB.)
 static size_t tiles_ws_bytes(const View& v) {
     const int D = v.u.d, R = v.u.R;
     const bool f32 = v.u.dtype == KFAC_F32;
     size_t need = 0;
     for (int tw = D <= 64 ? 64 : 128; tw <= (D <= 128 || f32 ? 128 : 256) && !(D <= 64 && tw > 64); tw *= 2) {
         const int td = ceil_div(D, tw), nt = td * (td + 1) / 2;
-        const int ns = most_splits(R, tw, nt, f32);
+        const int least = f32 ? SHARE_LEAST_F32 : tw == 256 ? ROWS_PER_WG_MAX : SHARE_LEAST;
+        const int ns = xcd_splits(std::min(most_splits(R, tw, nt, f32), ceil_div(R, least)));
         if (ns > 1) need = std::max(need, (size_t)ns * ((size_t)nt * tw * tw + (size_t)td * tw) * sizeof(float));
     }
     return need;

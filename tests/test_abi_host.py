@@ -155,6 +155,17 @@ def test_bad_arguments_are_rejected_on_the_host():
     assert lib.kfac_precondition(fake, fake, fake, 4, 5, fake, ctypes.c_void_p(0x9000), 1 << 20, None) == kb.KFAC_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("batch,layout,dtype,most", [(32, kb.KFAC_NHWC, kb.KFAC_BF16, 3.0e9), (128, kb.KFAC_NHWC, kb.KFAC_BF16, 4.0e9),
+                                                     (32, kb.KFAC_NCHW, kb.KFAC_BF16, 3.5e9)])
+def test_factor_scratch_of_a_whole_network(batch, layout, dtype, most):
+    """Every build's scratch covers the partial sums of the most row ranges its rows can be cut into, and no more."""
+    total = 0
+    for s in synth.resnet50_layers(batch):
+        desc = kb.make_desc(s, layout, dtype, kb.KFAC_ORDER_KH_KW_C)
+        total += sum(kb.kfac_factor_workspace_bytes(op, desc) for op in (kb.KFAC_OP_FACTOR_A, kb.KFAC_OP_FACTOR_G))
+    assert 1.0e9 < total < most
+
+
 @pytest.mark.parametrize("C,HW", [(8, 4097), (64, 552), (64, 12544), (256, 3136), (264, 513), (512, 784), (2048, 49)])
 def test_bn_scratch_does_not_depend_on_the_dtype(C, HW):
     """An fp32 layer whose channels are whole vectors in every dtype needs no more scratch than a 16-bit one, so that the
