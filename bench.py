@@ -30,7 +30,7 @@ from paper_1811_12019_amd import binding as kb        # noqa: E402
 from paper_1811_12019_amd import step as kstep        # noqa: E402
 from paper_1811_12019_amd import synth                # noqa: E402
 
-PEAK = {"mfma_bf16": 2500.0, "mfma_f32": 157.3, "alu_f32": 157.3, "hbm": 8000.0}   # TFLOP/s, TFLOP/s, TFLOP/s, GB/s
+PEAK = {"mfma_bf16": 2500.0, "mfma_f32": 157.3, "hbm": 8000.0}   # TFLOP/s, TFLOP/s, GB/s
 # fp32 products computed as sums of 16-bit MFMAs over split operands: 6 MFMAs per fp32 product with both operands
 # split into three bf16 pieces (the sweep's panel product), 3 with both split into two fp16 pieces of scaled operands
 # (the sweep's rank-128 updates, both preconditioning products); fp16 and bf16 MFMA peaks are equal
@@ -38,13 +38,19 @@ PEAK["mfma_bf16x3"] = round(PEAK["mfma_bf16"] / 6, 1)
 PEAK["mfma_f16x2"] = round(PEAK["mfma_bf16"] / 3, 1)
 
 
-def kernel_work(net: kstep.KfacNetworkStep):
-    """Algorithmic work of each kernel over ONE step of the whole network: (bound, peak, unit, amount)."""
+def kernel_work(net: kstep.KfacNetworkStep, kernels):
+    """Algorithmic work of each kernel over ONE step of the whole network: (bound, peak, unit, amount).  kernels: the names of
+    those that ran (which width of tiles the wide factors were built with is the library's choice)."""
     shapes = [l.shape for l in net.layers]
     dims = [d for s in shapes for d in (s.d_A, s.d_G)]
 
-    fac_tile = (sum(kstep.factor_flops(s.R, s.d_A) for s in shapes if s.C_in % 8 == 0) +
-                sum(kstep.factor_flops(s.R, s.d_G) for s in shapes))
+    # every factor is built by the tile kernel: up to 64 columns (without the bias) by the 64-wide one, up to 128 by the 128-wide
+    # one, wider ones all by the 128- or all by the 256-wide one
+    wide = 256 if "factor_tile_kernel<256, 16-bit>" in kernels else 128
+    fac_tile = {64: 0.0, 128: 0.0, 256: 0.0}
+    for s in shapes:
+        for d, columns in ((s.d_A, s.d_A - s.has_bias), (s.d_G, s.d_G)):
+            fac_tile[64 if columns <= 64 else 128 if columns <= 128 else wide] += kstep.factor_flops(s.R, d)
     w = {
         # all steps of all matrices in one kernel; a matrix's last step (short product, dense mirrored output) is a
         # small part of it; it also inverts the next step's pivot block (fp32 matrix cores) beside the update
@@ -60,13 +66,12 @@ def kernel_work(net: kstep.KfacNetworkStep):
         # call, the inverses by the inversion call (kfac_inverse_item.planes)
         "pre_split_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(8.0 * s.d_G * s.d_A for s in shapes)),
         "inv_planes_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(8.0 * d * d for d in dims)),
-        "factor_generic_kernel": ("alu", PEAK["alu_f32"], "TFLOP/s",
-                                  sum(kstep.factor_flops(s.R, s.d_A) for s in shapes if s.C_in % 8 != 0)),
-        "factor_tile_kernel<16-bit>": ("mfma", PEAK["mfma_bf16"], "TFLOP/s", fac_tile),
         "kfac::ema_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(12.0 * d * d for d in dims)),
         "kfac::ema_batched_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(12.0 * d * d for d in dims)),
         "inv_init_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(4.0 * d * (d + 1) for d in dims if d > kstep.INVERSE_BLOCK)),
     }
+    for width, flops in fac_tile.items():
+        w[f"factor_tile_kernel<{width}, 16-bit>"] = ("mfma", PEAK["mfma_bf16"], "TFLOP/s", flops)
     return w
 
 
@@ -342,7 +347,7 @@ def main():
         torch.cuda.synchronize()
         del src, dst
 
-    work = kernel_work(net)
+    work = kernel_work(net, report)
     per_kernel = {}
     for name, (tot_ms, n) in report.items():
         base = name if name in work else name.split("<")[0]

@@ -573,7 +573,10 @@ static int launch_tiles(const FBatch& b, hipStream_t stream) {
         (void)hipFuncSetAttribute((const void*)factor_tile_kernel<TW, KIND>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     });
     void* tok = nullptr;
-    if (timing_enabled()) timing_begin(KIND == 2 ? "factor_tile_kernel<f32>" : "factor_tile_kernel<16-bit>", stream, &tok);
+    static const char* const name = KIND == 2 ? (TW == 64 ? "factor_tile_kernel<64, f32>" : "factor_tile_kernel<128, f32>")
+                                  : TW == 64 ? "factor_tile_kernel<64, 16-bit>"
+                                  : TW == 128 ? "factor_tile_kernel<128, 16-bit>" : "factor_tile_kernel<256, 16-bit>";
+    if (timing_enabled()) timing_begin(name, stream, &tok);
     hipLaunchKernelGGL((factor_tile_kernel<TW, KIND>), dim3(b.prefix[b.count]), dim3(tile_threads<TW, KIND == 2 ? 4 : 2>()), LDS, stream, b);
     if (tok) timing_end(stream, tok);
     if (hipGetLastError() != hipSuccess) return KFAC_ERR_HIP;

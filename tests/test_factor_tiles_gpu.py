@@ -1,5 +1,6 @@
 """Matrix-core factor builder at the sizes where it can go wrong: tile widths 64 / 128 / 256 and one column either side,
-padded channels, both column orders and layouts, every dtype, split and unsplit rows, every kind of output."""
+padded channels, both column orders and layouts, every dtype, split and unsplit rows, every kind of output.  256-wide tiles are
+only taken in calls of much work (test_wide_tiles); the other tests run 64- and 128-wide ones."""
 import numpy as np
 import pytest
 import torch
@@ -24,7 +25,7 @@ EDGE_SHAPES = [
     synth.LayerShape("k3c57s2", 4, 57, 23, 21, 40, 3, 3, 2, 1),            # 64 padded channels, stride 2: 576 columns
     synth.LayerShape("k5c12", 2, 12, 14, 15, 9, 5, 5, 1, 2, has_bias=False),
     synth.LayerShape("fc1", 1, 520, 1, 1, 10, 1, 1, 1, 0),                 # one row
-    synth.LayerShape("k3long", 8, 72, 41, 40, 33, 3, 3, 1, 1),             # 13,120 rows x 648 columns: 256-wide tiles, split
+    synth.LayerShape("k3long", 8, 72, 41, 40, 33, 3, 3, 1, 1),             # 13,120 rows x 648 columns: split
 ]
 
 
@@ -38,7 +39,7 @@ def test_factor_tile_edges(shape, layout, dtype, order):
 
 @pytest.mark.parametrize("layout,dtype,order", [(NCHW, kb.KFAC_BF16, CKK), (NHWC, kb.KFAC_BF16, KKC), (NCHW, kb.KFAC_F32, CKK)])
 def test_narrow_layer_in_any_layout(layout, dtype, order):
-    """conv1-like: 3 channels, 4,900 rows (16-bit: gathered element by element; fp32: repacked)."""
+    """conv1-like: 3 channels, 4,900 rows (16-bit: repacked to runs of pixels; fp32: to four channels)."""
     check_factor_pair(synth.LayerShape("g", 4, 3, 70, 70, 16, 7, 7, 2, 3, relu_input=False), layout, dtype, order, seed=3)
 
 
@@ -46,7 +47,7 @@ def test_narrow_layer_in_any_layout(layout, dtype, order):
 @pytest.mark.parametrize("layout,dtype,order", [(NHWC, kb.KFAC_BF16, KKC), (NCHW, kb.KFAC_BF16, CKK), (NCHW, kb.KFAC_F32, CKK)])
 def test_factor_outputs(many, layout, dtype, order):
     """Running average and packed triangle against the plain build, bit for bit, and the plain build against the oracle;
-    alone (fine row splits) and among enough builds for the coarse splits and the 256-wide tiles."""
+    ten builds, each cut as if alone, and 24, cut by their work together."""
     shapes = [EDGE_SHAPES[i] for i in (1, 3, 5, 6, 9)] + [synth.LayerShape("k1long", 6, 48, 50, 50, 304, 1, 1, 1, 0)]
     builds, refs = [], []
     for s in shapes:
@@ -97,3 +98,75 @@ def test_few_builds_equal_single_calls(layout, dtype, order):
         ws = kb.alloc_workspace(kb.kfac_factor_workspace_bytes(op, desc), DEV)
         (kb.kfac_factor_A if op == kb.KFAC_OP_FACTOR_A else kb.kfac_factor_G)(desc, x, 0.0, alone, ws)
         np.testing.assert_array_equal(got.cpu().numpy(), alone.cpu().numpy())
+
+
+# 256-wide tiles: one column either side of one and two tiles, padded and mapped columns, one row, rows split into 2, 8 and 32
+# ranges.
+WIDE_SHAPES = [
+    synth.LayerShape("w129", 2, 129, 9, 11, 255, 1, 1, 1, 0),              # 198 rows
+    synth.LayerShape("w256", 1, 256, 5, 5, 257, 1, 1, 1, 0),               # 25 rows: less than a slab
+    synth.LayerShape("w511", 3, 511, 7, 7, 512, 1, 1, 1, 0),
+    synth.LayerShape("w513", 2, 513, 6, 5, 264, 1, 1, 1, 0),
+    synth.LayerShape("onerow", 1, 768, 1, 1, 300, 1, 1, 1, 0),
+    synth.LayerShape("k3c32s2", 4, 32, 23, 21, 136, 3, 3, 2, 1),           # 288 columns
+    synth.LayerShape("k3c57", 4, 57, 19, 18, 200, 3, 3, 1, 1),             # 64 padded channels: 576 columns
+    synth.LayerShape("k3nobias", 2, 40, 14, 15, 520, 3, 3, 1, 1, has_bias=False),
+    synth.LayerShape("split2", 6401, 264, 1, 1, 136, 1, 1, 1, 0),          # 6,401 rows: ranges of 3,264 and 3,137
+    synth.LayerShape("split8", 8, 72, 81, 80, 136, 3, 3, 1, 1),            # 51,840 rows x 648 columns
+    synth.LayerShape("split32", 16, 8, 114, 113, 136, 1, 1, 1, 0),         # 206,112 rows
+]
+
+
+@pytest.mark.parametrize("layout,dtype,order", [
+    (NHWC, kb.KFAC_BF16, KKC), (NHWC, kb.KFAC_F16, CKK), (NCHW, kb.KFAC_BF16, CKK), (NCHW, kb.KFAC_F16, KKC)])
+def test_wide_tiles(layout, dtype, order):
+    """256-wide tiles, which the library takes for calls of 24,000 and more rows of 128 x 128 tiles to a workgroup slot with little
+    padding: 16 builds of 8,704 rows x 2,048 columns beside the shapes above make such a call.  Plain results against the oracle;
+    running average and packed triangle against the plain ones, bit for bit; nothing is written beyond the scratch that
+    kfac_factor_workspace_bytes asks for."""
+    def anchor_build():
+        s = synth.LayerShape("anchor", 8704, 2048, 1, 1, 8, 1, 1, 1, 0)
+        act = _NP_ROUND[dtype](synth.make_act(s, 1))
+        return s, act, (kb.KFAC_OP_FACTOR_A, kb.make_desc(s, layout, dtype, order), kb.to_device_tensor(act, layout, dtype, DEV), s.d_A)
+    anchor, anchor_act, build = anchor_build()
+    builds, refs = [build] * 16, [None] * 16                               # (one of them is checked: refs[0])
+    refs[0] = ko.factor_A(anchor_act, 1, 1, 1, 0, True, order)
+    for i, s in enumerate(WIDE_SHAPES):
+        act, gout = _NP_ROUND[dtype](synth.make_act(s, 40 + i)), _NP_ROUND[dtype](synth.make_gout(s, 40 + i))
+        desc = kb.make_desc(s, layout, dtype, order)
+        if s.d_A > 129:                                                    # (more than 128 data columns)
+            builds.append((kb.KFAC_OP_FACTOR_A, desc, kb.to_device_tensor(act, layout, dtype, DEV), s.d_A))
+            refs.append(ko.factor_A(act, s.kh, s.kw, s.stride, s.pad, s.has_bias, order))
+        builds.append((kb.KFAC_OP_FACTOR_G, desc, kb.to_device_tensor(gout, layout, dtype, DEV), s.d_G))
+        refs.append(ko.factor_G(gout))
+    guard, mark = 4096, 0xA5
+    need = [kb.kfac_factor_workspace_bytes(op, desc) for op, desc, _, _ in builds]
+    ws = [torch.full((n + guard,), mark, dtype=torch.uint8, device=DEV) for n in need]
+    full = [torch.full((d, d), float("nan"), device=DEV) for _, _, _, d in builds]
+    packed = [torch.full((kb.packed_elems(d),), float("nan"), device=DEV) for _, _, _, d in builds]
+    run = [torch.eye(d, device=DEV) * 2.0 + 0.25 for _, _, _, d in builds]
+    plain = [r.clone() for r in run]
+    items = lambda outs: [(op, desc, x, o, 0.0) for (op, desc, x, _), o in zip(builds, outs)]
+    kb.kfac_kernel_timing_enable(True)
+    try:
+        kb.kfac_factor_batched(kb.FactorBatch(items(full), device=DEV, ws=ws))
+        kb.kfac_factor_batched(kb.FactorBatch(items(packed), device=DEV, packed=True, ws=ws))
+        kb.kfac_factor_batched(kb.FactorBatch(items(full), device=DEV, running=run, decay=0.9, ws=ws))
+        kernels = kb.kfac_kernel_timing_report()
+    finally:
+        kb.kfac_kernel_timing_enable(False)
+    tiles = {k: n for k, (_, n) in kernels.items() if k.startswith("factor_tile_kernel<")}
+    assert tiles == {"factor_tile_kernel<256, 16-bit>": 3}, kernels        # every build, in all three calls
+    assert kernels["factor_tile_reduce_kernel<1>"][1] == kernels["factor_tile_reduce_kernel<4>"][1] == 3
+    kb.kfac_ema_batched(kb.EmaBatch(plain, full), 0.9)
+    torch.cuda.synchronize()
+    for n, w in zip(need, ws):
+        assert bool((w[n:] == mark).all())
+    for i, (ref, f, p, r, want_r) in enumerate(zip(refs, full, packed, run, plain)):
+        got = f.cpu().numpy()
+        want = ref if ref is not None else full[0].cpu().numpy().astype(np.float64)
+        assert np.isfinite(got).all(), i
+        assert rel_fro(got, want) < FACTOR_TOL and rel_max(got, want) < FACTOR_TOL, (i, rel_fro(got, want), rel_max(got, want))
+        np.testing.assert_array_equal(got, got.T)
+        np.testing.assert_array_equal(p.cpu().numpy(), ko.pack_upper(got).astype(np.float32))
+        np.testing.assert_array_equal(r.cpu().numpy(), want_r.cpu().numpy())
