@@ -27,16 +27,6 @@
         if (hipGetLastError() != hipSuccess) return KFAC_ERR_HIP;                  \
     } while (0)
 
-// Same, with `lds` bytes of dynamic LDS.
-#define KFAC_LAUNCH_LDS(kernel, grid, block, lds, stream, ...)                     \
-    do {                                                                           \
-        void* tok__ = nullptr;                                                     \
-        if (kfac::timing_enabled()) kfac::timing_begin(#kernel, stream, &tok__);   \
-        hipLaunchKernelGGL(kernel, grid, block, lds, stream, __VA_ARGS__);         \
-        if (tok__) kfac::timing_end(stream, tok__);                                \
-        if (hipGetLastError() != hipSuccess) return KFAC_ERR_HIP;                  \
-    } while (0)
-
 namespace kfac {
 
 // Opt-in per-kernel event timing (runtime.hip).
@@ -44,12 +34,9 @@ bool timing_enabled();
 void timing_begin(const char* name, hipStream_t stream, void** token);
 void timing_end(hipStream_t stream, void* token);
 
-constexpr int WAVE = 64;
-
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef short v8s __attribute__((ext_vector_type(8)));
 
 // Four floats that are only guaranteed dword alignment (rows of an odd-sized matrix).
 typedef v4f v4f_a4 __attribute__((aligned(4)));

@@ -12,7 +12,6 @@
 // All enumerate only the lower-triangular tiles of the symmetric output and mirror them, and all can split the R unfolded
 // rows over several workgroups (deterministic two-pass reduction through the caller's workspace, no float atomics).
 #include <algorithm>
-#include <cstdlib>
 #include <mutex>
 
 #include "common.h"
