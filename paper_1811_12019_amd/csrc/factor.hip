@@ -12,7 +12,6 @@
 // All enumerate only the lower-triangular tiles of the symmetric output and mirror them, and all can split the R unfolded
 // rows over several workgroups (deterministic two-pass reduction through the caller's workspace, no float atomics).
 #include <algorithm>
-#include <mutex>
 
 #include "common.h"
 #include "factor_tile.h"
@@ -567,10 +566,12 @@ static int check_item(const kfac_factor_item& it, Unfold* u) {
 template <int TW, int KIND>
 static int launch_tiles(const FBatch& b, hipStream_t stream) {
     constexpr int LDS = tile_lds_bytes<TW, KIND == 2 ? 4 : 2>();
-    static std::once_flag attr_once;                 // (one per kernel variant; safe from any number of host threads)
-    std::call_once(attr_once, [] {
-        (void)hipFuncSetAttribute((const void*)factor_tile_kernel<TW, KIND>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-    });
+    // More than 64 KB of LDS have to be asked for, on every device anew: the 256-wide kernels' launches do, each for the device it
+    // goes to (nothing to remember between calls; their work is milliseconds).
+    if constexpr (LDS > 64 * 1024) {
+        if (hipFuncSetAttribute((const void*)factor_tile_kernel<TW, KIND>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS) != hipSuccess)
+            return KFAC_ERR_HIP;
+    }
     void* tok = nullptr;
     static const char* const name = KIND == 2 ? (TW == 64 ? "factor_tile_kernel<64, f32>" : "factor_tile_kernel<128, f32>")
                                   : TW == 64 ? "factor_tile_kernel<64, 16-bit>"

@@ -170,3 +170,29 @@ def test_wide_tiles(layout, dtype, order):
         np.testing.assert_array_equal(got, got.T)
         np.testing.assert_array_equal(p.cpu().numpy(), ko.pack_upper(got).astype(np.float32))
         np.testing.assert_array_equal(r.cpu().numpy(), want_r.cpu().numpy())
+
+
+def test_wide_tiles_in_a_captured_graph():
+    """A call of 256-wide tiles with split rows, captured and replayed: every replay equals the eager call."""
+    s = synth.LayerShape("anchor", 8704, 2048, 1, 1, 8, 1, 1, 1, 0)
+    desc = kb.make_desc(s, NHWC, kb.KFAC_BF16, KKC)
+    x = torch.randn((s.N, s.C_in), device=DEV).to(torch.bfloat16)
+    outs = [torch.full((s.d_A, s.d_A), float("nan"), device=DEV) for _ in range(16)]
+    batch = kb.FactorBatch([(kb.KFAC_OP_FACTOR_A, desc, x, o, 0.0) for o in outs], device=DEV)
+    kb.kfac_kernel_timing_enable(True)
+    try:
+        kb.kfac_factor_batched(batch)
+        assert "factor_tile_kernel<256, 16-bit>" in kb.kfac_kernel_timing_report()
+    finally:
+        kb.kfac_kernel_timing_enable(False)
+    want = [o.clone() for o in outs]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        kb.kfac_factor_batched(batch)
+    for _ in range(3):
+        for o in outs:
+            o.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for o, w in zip(outs, want):
+            assert torch.equal(o, w)
