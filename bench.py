@@ -15,8 +15,10 @@ One GPU only: the per-GPU share of the paper's data-parallel step is what is mea
 from __future__ import annotations
 
 import argparse
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -88,15 +90,28 @@ def factor_shape_roofline_ms(layers):
     return total * 1e3
 
 
+def kernel_code_digest() -> str:
+    """16 hex digits that name the kernels' code: the library's sources without comments and white space."""
+    csrc = os.path.join(ROOT, "paper_1811_12019_amd", "csrc")
+    h = hashlib.sha256()
+    for name in sorted(os.listdir(csrc)):
+        if name.endswith((".h", ".hip")):
+            text = re.sub(r"/\*.*?\*/|//[^\n]*", "", open(os.path.join(csrc, name)).read(), flags=re.S)
+            h.update((name + "".join(text.split())).encode())
+    return h.hexdigest()[:16]
+
+
 def measured_traffic(kernel: str, batch: int):
     """HBM bytes per launch of `kernel` as rocprofv3's FETCH_SIZE + WRITE_SIZE counters measured them on this
     workload (scaled by a copy kernel of known size); the figure is kept with the profile summaries.  None when no
-    summary covers this kernel and batch size."""
-    import re
+    summary covers this kernel and batch size, or when it was counted on other code than this (the summary says which)."""
     path = os.path.join(ROOT, "profiles", "hbm_traffic_resnet50_b32_step.md")
     if batch != 32 or not os.path.exists(path):
         return None
-    for line in open(path):
+    text = open(path).read()
+    if f"Kernel code {kernel_code_digest()}" not in text:
+        return None
+    for line in text.splitlines():
         m = re.match(r"\|\s*`?([^|`]+?)`?\s*\|.*\|\s*([0-9.]+)\s*\|\s*$", line)
         if m and m.group(1).strip() == kernel:
             return {"bytes_per_launch": float(m.group(2)), "source": "profiles/hbm_traffic_resnet50_b32_step.md"}

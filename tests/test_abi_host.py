@@ -193,6 +193,25 @@ def test_current_stream_with_and_without_torchs_private_functions(monkeypatch, m
     assert kb._stream(None) == 77
 
 
+def test_profiled_traffic_is_used_only_for_the_code_it_was_counted_on(monkeypatch):
+    """bench.py's roofline takes a kernel's HBM bytes from the profile summary, which names the code it was counted on; the
+    summaries name no kernel that the sources do not have."""
+    import bench
+    assert re.fullmatch("[0-9a-f]{16}", bench.kernel_code_digest())
+    text = open(os.path.join(ROOT, "profiles", "hbm_traffic_resnet50_b32_step.md")).read()
+    counted = re.search("Kernel code ([0-9a-f]{16})", text).group(1)
+    monkeypatch.setattr(bench, "kernel_code_digest", lambda: counted)
+    assert bench.measured_traffic("inv_update_kernel", 32)["bytes_per_launch"] > 0
+    assert bench.measured_traffic("inv_update_kernel", 128) is None and bench.measured_traffic("no_such_kernel", 32) is None
+    monkeypatch.setattr(bench, "kernel_code_digest", lambda: "0" * 16)
+    assert bench.measured_traffic("inv_update_kernel", 32) is None
+    csrc = os.path.join(ROOT, "paper_1811_12019_amd", "csrc")
+    sources = "".join(open(os.path.join(csrc, f)).read() for f in os.listdir(csrc))
+    for name in os.listdir(os.path.join(ROOT, "profiles")):
+        for kernel in re.findall(r"^\| `(\w+_kernel)\b", open(os.path.join(ROOT, "profiles", name)).read(), flags=re.M):
+            assert re.search(rf"\b{kernel}\(", sources), (name, kernel)
+
+
 def test_product_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_1811_12019_amd")
     for dirpath, _, files in os.walk(pkg):
