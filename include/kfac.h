@@ -207,7 +207,8 @@ size_t kfac_bn_sample_grads_workspace_bytes(int32_t N, int32_t C, int32_t HW);  
 int kfac_bn_sample_grads(const void* xhat, const void* gout, int32_t N, int32_t C, int32_t HW, int32_t dtype, float* g,
                          void* ws, size_t ws_bytes, void* stream);
 
-/* The same for many layers at once (all BN layers of a network in two or three launches).  items_host: host array,
+/* The same for many layers at once (one launch per dtype for 64 of them, and one for the sums over chunks; layers whose channels
+ * are not whole 16-byte vectors, or whose tensors are not 16-byte aligned, take one each).  items_host: host array,
  * read during the call only; the tensors it names are device memory.  Layers may differ in every field. */
 typedef struct {
     const void* xhat;

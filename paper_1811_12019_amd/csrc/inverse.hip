@@ -23,7 +23,7 @@
 //   * every matrix of a batch carries its own step number, so that matrices with fewer blocks spread their steps
 //     over the launches of the largest one.
 // Products: the panel on the bf16 matrix cores with operands split three ways; the updates on the fp16 matrix cores
-// from operands that the panel launch has already scaled per 128-row slab and split two ways, stored as planes that
+// from operands that the panel launch has already scaled per half slab (64 rows) and split two ways, stored as planes that
 // go to LDS by DMA (gemm_split.h); both to fp32 accuracy.
 //
 // Storage.  The sweep works on a copy W of the matrix in the caller's workspace whose rows are padded to a
@@ -132,11 +132,9 @@ __device__ __forceinline__ float inverse_plane_scale(float damping) {
     return damping > 0.f ? ldexpf(1.0f, 8 + ilogbf(damping)) : 1.0f;
 }
 // Steps are taken in groups of up to GM consecutive blocks, none of them the matrix's last.  Inside a group only the
-// tiles that the group's remaining pivots and panels need are kept up to date step by step (block rows / columns of
-// the blocks still to come, all of them short lists: "narrow" launches); every other tile receives the group's
-// rank-128 updates together, in one pass over the matrix, in the launch of the group's last step ("wide"), which
-// cuts the traffic of the working copy by the group size.  The arithmetic per tile is the same sequence of fp32
-// operations as step-by-step updating.
+// tiles that the group's remaining pivots and panels need are brought up to date; every other tile receives the group's
+// rank-128 updates together, in one visit during the next group's launches (plan_of), which cuts the traffic of the working copy
+// by the group size.  The arithmetic per tile is the same sequence of fp32 operations as step-by-step updating.
 constexpr int GM = 4;
 struct Group {
     int g0;      // first step of the group that `step` belongs to
@@ -1086,7 +1084,7 @@ struct OldSrc {
 // Regular tile of a step that is not the matrix's last one: new = old - A0 B0^T - A1 B1^T - ... (one product per pending
 // step, in step order) goes back into the working copy.  Only a matrix's last block can be ragged and the step that eliminates it is its last, so here the pivot
 // blocks are full (K = 128 per product).  The products run on the fp16 matrix cores with both operands scaled per
-// slab and split two ways (gemm_split.h): the accumulators start as the tile's old values (fetched straight into MFMA register layout:
+// half slab and split two ways (gemm_split.h): the accumulators start as the tile's old values (fetched straight into MFMA register layout:
 // register r of a 32 x 32 block is 32 consecutive floats of one row per half-wave), the negated products are added,
 // and the result is stored from the registers: nothing is staged in LDS.
 // STORE = false: the new values stay in acc (valid where the tile has rows and columns;
@@ -1257,7 +1255,7 @@ __device__ __forceinline__ void upd_panel(const UpdCtx& c, bool column, float* _
 }
 
 // Tile (I, J) of a step that is not the matrix's last: brings it up to date through step kq = g.g0 + g.j of group g.
-// single: the tile has been kept up to date step by step (a narrow launch): it sees step kq only, and its old value
+// single: the tile has been kept up to date step by step (a diagonal tile inside a group): it sees step kq only, and its old value
 // is in the working copy.  Otherwise it sees all of the group's steps up to kq that it has not seen yet: all of them
 // for a tile with no index inside the group.  A tile with an index inside the group was kept up to date until its
 // later such index c was eliminated (when it became part of panel c: T_I for a tile of block column c, T_J transposed

@@ -116,11 +116,12 @@ def test_factors_resnet_layers_full_size(name):
 
 
 GATHER_SHAPES = [
-    # narrow layers (channels not a multiple of 8) with thousands of rows: the gather-based matrix-core kernel
-    synth.LayerShape("g7x7s2", 4, 3, 70, 70, 16, 7, 7, 2, 3, relu_input=False),      # 4,900 rows, 148 columns
-    synth.LayerShape("g3x3c5", 3, 5, 48, 50, 8, 3, 3, 1, 1),                         # 7,200 rows, 46 columns
-    synth.LayerShape("g1x1c17", 2, 17, 50, 47, 8, 1, 1, 1, 0),                       # 4,700 rows, 18 columns
-    synth.LayerShape("g5x5nobias", 2, 6, 52, 52, 8, 5, 5, 1, 2, has_bias=False),     # 5,408 rows, 150 columns
+    # narrow layers (channels not a multiple of 8) with thousands of rows: repacked and built on the matrix cores, or, where that
+    # is too little work for two more launches, by the generic kernel
+    synth.LayerShape("g7x7s2", 4, 3, 70, 70, 16, 7, 7, 2, 3, relu_input=False),      # 4,900 rows, 148 columns: runs of pixels
+    synth.LayerShape("g3x3c5", 3, 5, 48, 50, 8, 3, 3, 1, 1),                         # 7,200 rows, 46 columns: generic
+    synth.LayerShape("g1x1c17", 2, 17, 50, 47, 8, 1, 1, 1, 0),                       # 4,700 rows, 18 columns: generic
+    synth.LayerShape("g5x5nobias", 2, 6, 52, 52, 8, 5, 5, 1, 2, has_bias=False),     # 5,408 rows, 150 columns: padded channels
 ]
 
 
@@ -131,7 +132,7 @@ def test_factors_narrow_layers(shape, dtype):
 
 
 def test_factor_image_too_wide_for_the_packed_patch_origin():
-    """An image wider than the matrix-core kernel's 16-bit patch coordinates allow is served by another kernel."""
+    """A patch's origin does not fit 14 bits: an image of 17,000 pixels to a row."""
     shp = synth.LayerShape("wide", 1, 8, 3, 17000, 8, 3, 3, 1, 1)
     check_factor_pair(shp, kb.KFAC_NHWC, kb.KFAC_BF16, kb.KFAC_ORDER_KH_KW_C)
 
@@ -236,7 +237,7 @@ def _fused_and_packed_case(shapes, dtype=None):
 FUSED_SHAPES = [
     synth.LayerShape("f.3x3", 3, 40, 9, 9, 70, 3, 3, 1, 1),                 # several tiles, ragged edges, one row split
     synth.LayerShape("f.1x1long", 4, 64, 40, 40, 136, 1, 1, 1, 0),          # 6,400 rows: split over workgroups, reduced
-    synth.LayerShape("f.conv1", 2, 3, 70, 70, 16, 7, 7, 2, 3, relu_input=False),   # 3 channels: the narrow-layer kernel
+    synth.LayerShape("f.conv1", 2, 3, 70, 70, 16, 7, 7, 2, 3, relu_input=False),   # 3 channels: runs of pixels, split
     synth.LayerShape("f.wide", 2, 160, 5, 5, 300, 3, 3, 1, 1),              # d_A = 1441: many whole tiles
 ]
 
@@ -809,7 +810,7 @@ def test_layer_step_config0_end_to_end():
 # whole-network step (the object bench.py times), with a stale-inverse schedule
 # ----------------------------------------------------------------------------------------------
 NET_LAYERS = [
-    synth.LayerShape("n.conv1", 4, 3, 70, 70, 16, 7, 7, 2, 3, relu_input=False),    # narrow-layer kernel, 4,900 rows
+    synth.LayerShape("n.conv1", 4, 3, 70, 70, 16, 7, 7, 2, 3, relu_input=False),    # runs of pixels, 4,900 rows
     synth.LayerShape("n.3x3", 4, 16, 14, 14, 24, 3, 3, 1, 1),
     synth.LayerShape("n.1x1", 4, 24, 14, 14, 40, 1, 1, 1, 0),
     synth.LayerShape("n.3x3s2", 4, 40, 14, 14, 48, 3, 3, 2, 1),                     # d_A = 361: three 128-blocks
