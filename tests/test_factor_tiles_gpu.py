@@ -196,3 +196,63 @@ def test_wide_tiles_in_a_captured_graph():
         torch.cuda.synchronize()
         for o, w in zip(outs, want):
             assert torch.equal(o, w)
+
+
+# up to four channels and an even stride (16-bit): a kernel row's pixels as one run of columns.  Even and odd kernel widths, one row,
+# strides 2 and 4, pixels that no patch reaches, padding wider than the image's remainder.
+RUN_SHAPES = [synth.LayerShape(f"c{C}k{kh}x{kw}s{stride}p{pad}", 3, C, 19 + C, 23 - C, 9 + C, kh, kw, stride, pad, has_bias=bias)
+              for C, kh, kw, stride, pad, bias in [
+                  (1, 1, 2, 2, 0, True), (1, 3, 3, 2, 1, False), (2, 5, 2, 4, 2, True), (2, 2, 4, 2, 0, True), (3, 7, 7, 2, 3, True),
+                  (3, 3, 5, 4, 4, False), (4, 3, 3, 2, 1, True), (4, 1, 7, 2, 3, True), (4, 11, 11, 4, 5, True)]]
+
+
+@pytest.mark.parametrize("layout,dtype,order", [
+    (NHWC, kb.KFAC_BF16, KKC), (NHWC, kb.KFAC_F16, CKK), (NCHW, kb.KFAC_BF16, CKK), (NCHW, kb.KFAC_F16, KKC)])
+def test_runs_of_pixels(layout, dtype, order):
+    """Few-channel convolutions in a call of 18 builds (so that none is left to the generic kernel): against the oracle, and running
+    average and packed triangle against the plain result, bit for bit."""
+    builds, refs = [], []
+    for i, s in enumerate(RUN_SHAPES):
+        act, gout = _NP_ROUND[dtype](synth.make_act(s, 60 + i)), _NP_ROUND[dtype](synth.make_gout(s, 60 + i))
+        desc = kb.make_desc(s, layout, dtype, order)
+        builds.append((kb.KFAC_OP_FACTOR_A, desc, kb.to_device_tensor(act, layout, dtype, DEV), s.d_A))
+        builds.append((kb.KFAC_OP_FACTOR_G, desc, kb.to_device_tensor(gout, layout, dtype, DEV), s.d_G))
+        refs += [ko.factor_A(act, s.kh, s.kw, s.stride, s.pad, s.has_bias, order), ko.factor_G(gout)]
+    full = [torch.full((d, d), float("nan"), device=DEV) for _, _, _, d in builds]
+    packed = [torch.full((kb.packed_elems(d),), float("nan"), device=DEV) for _, _, _, d in builds]
+    run = [torch.eye(d, device=DEV) * 2.0 + 0.25 for _, _, _, d in builds]
+    plain = [r.clone() for r in run]
+    items = lambda outs: [(op, desc, x, o, 0.0) for (op, desc, x, _), o in zip(builds, outs)]
+    kb.kfac_kernel_timing_enable(True)
+    try:
+        kb.kfac_factor_batched(kb.FactorBatch(items(full), device=DEV))
+        kb.kfac_factor_batched(kb.FactorBatch(items(packed), device=DEV, packed=True))
+        kb.kfac_factor_batched(kb.FactorBatch(items(full), device=DEV, running=run, decay=0.9))
+        kernels = kb.kfac_kernel_timing_report()
+    finally:
+        kb.kfac_kernel_timing_enable(False)
+    assert "factor_repack_kernel" in kernels and "factor_generic_kernel" not in kernels, kernels
+    kb.kfac_ema_batched(kb.EmaBatch(plain, full), 0.9)
+    for ref, f, p, r, want_r in zip(refs, full, packed, run, plain):
+        got = f.cpu().numpy()
+        assert np.isfinite(got).all() and rel_fro(got, ref) < FACTOR_TOL and rel_max(got, ref) < FACTOR_TOL
+        np.testing.assert_array_equal(got, got.T)
+        np.testing.assert_array_equal(p.cpu().numpy(), ko.pack_upper(got).astype(np.float32))
+        np.testing.assert_array_equal(r.cpu().numpy(), want_r.cpu().numpy())
+
+
+@pytest.mark.parametrize("layout,dtype", [(NHWC, kb.KFAC_BF16), (NCHW, kb.KFAC_F16), (NHWC, kb.KFAC_F32), (NCHW, kb.KFAC_F32)])
+def test_tensor_off_the_vector_alignment(layout, dtype):
+    """A tensor one element off the 16-byte grid (a slice of a larger buffer): repacked (NCHW) or read by the generic kernel (NHWC)."""
+    s = synth.LayerShape("off", 3, 64, 17, 18, 72, 3, 3, 1, 1)
+    act = _NP_ROUND[dtype](synth.make_act(s, 5))
+    desc = kb.make_desc(s, layout, dtype, CKK)
+    aligned = kb.to_device_tensor(act, layout, dtype, DEV)
+    off = torch.empty(aligned.numel() + 8, dtype=aligned.dtype, device=DEV)[1:1 + aligned.numel()].view(aligned.shape)
+    off.copy_(aligned)
+    assert off.data_ptr() % 16 != 0
+    A = torch.full((s.d_A, s.d_A), float("nan"), device=DEV)
+    kb.kfac_factor_A(desc, off, 0.0, A, kb.alloc_workspace(kb.kfac_factor_workspace_bytes(kb.KFAC_OP_FACTOR_A, desc), DEV))
+    got, ref = A.cpu().numpy(), ko.factor_A(act, 3, 3, 1, 1, True, CKK)
+    assert rel_fro(got, ref) < FACTOR_TOL and rel_max(got, ref) < FACTOR_TOL
+    np.testing.assert_array_equal(got, got.T)

@@ -453,6 +453,10 @@ def _bn_inputs(N, C, H, W, dtype, seed):
     (2, 2056, 3, 3, kb.KFAC_BF16),        # more than 256 vectors per position, ragged
     (3, 5, 6, 7, kb.KFAC_BF16),           # channels not a multiple of 8: general kernel
     (2, 16, 5, 5, kb.KFAC_F32),
+    (3, 4, 91, 90, kb.KFAC_F32),          # one vector a position, one chunk
+    (2, 12, 61, 60, kb.KFAC_F32),         # three vectors, two chunks
+    (2, 260, 13, 13, kb.KFAC_F32),        # 65 vectors: a second, nearly empty block of channels; two chunks
+    (2, 6, 25, 25, kb.KFAC_F32),          # channels not a multiple of 4: general kernel, two chunks
 ])
 def test_bn_sample_grads(N, C, H, W, dtype):
     xhat, gout, xt, gt = _bn_inputs(N, C, H, W, dtype, 51)
