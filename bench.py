@@ -252,7 +252,7 @@ def peaks():
 
 
 def run_cfg4(args):
-    """configs[4]: batch 128, factors rebuilt and gradients preconditioned every step, inverses refreshed every 10th."""
+    """The stale-inverse schedule: batch 128, factors rebuilt and gradients preconditioned every step, inverses refreshed every 10th."""
     layers = synth.resnet50_layers(128)
     net = kstep.KfacNetworkStep(layers, dtype=kb.KFAC_BF16, order=kb.KFAC_ORDER_KH_KW_C, decay=0.95, gamma=1e-4, seed=0)
     for _ in range(max(1, args.warmup)):
