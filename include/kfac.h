@@ -82,7 +82,8 @@ size_t kfac_factor_workspace_bytes(int op, const kfac_layer_desc* desc);
 
 /* Stage 1.  A[d_A x d_A] = scale * sum_r abar_r abar_r^T over the R unfolded input patches abar_r of `act`
  * (zero padding outside the image, a trailing 1 if has_bias); scale = 0 selects 1/R, the mini-batch
- * mean of Sec. 3.1.  `act` holds N*C_in*H*W elements of desc->dtype in desc->layout.  Accumulation is fp32. */
+ * mean of Sec. 3.1.  `act` holds N*C_in*H*W elements of desc->dtype in desc->layout.  Accumulation is fp32.  A non-finite input
+ * makes its entries non-finite; whether 0 (padding) times infinity is formed is not specified. */
 int kfac_factor_A(const kfac_layer_desc* desc, const void* act, float scale, float* A,
                   void* ws, size_t ws_bytes, void* stream);
 

@@ -14,8 +14,7 @@
 #include <algorithm>
 
 #include "common.h"
-#include "factor_tile.h"
-#include "factor_repack.h"
+#include "factor_batch.h"
 
 namespace kfac {
 
@@ -238,15 +237,6 @@ __global__ __launch_bounds__(256) void factor_reduce_kernel(const float* __restr
     factor_reduce_block<T>(as_global(partial), nsplit, gridDim.x, blockIdx.x, blockIdx.y, d, scale, os, tr);
 }
 
-struct FactorPlan {
-    int tw;          // tile width (matrix-core builds)
-    int tiles_dim;   // tiles per dimension
-    int ntiles;      // lower-triangular tiles
-    int nsplit;
-    int rows_per_split;
-    size_t ws_bytes;
-};
-
 static FactorPlan plan_generic(const Unfold& u) {
     FactorPlan p;
     p.tiles_dim = ceil_div(u.d, GT);
@@ -261,47 +251,17 @@ static FactorPlan plan_generic(const Unfold& u) {
     return p;
 }
 
-// Tile width and row split of a matrix-core build.  `share`: how the builds of a call are cut (share_of): the rows of a
-// workgroup, plus SHARE_WIDE if matrices of more than 128 columns get 256-wide tiles.  A matrix of up to 128 (64) columns is
-// one tile of that width.
-constexpr int SHARE_WIDE = 1 << 20;
-constexpr int ROWS_PER_WG_MAX = 6400, ROWS_PER_WG_MAX_F32 = 1600;
-constexpr int ROWS_PER_WG_MIN = 512, ROWS_PER_WG_MIN_F32 = 64;
-constexpr int SHARE_LEAST = 1024, SHARE_LEAST_F32 = 128;           // the fewest rows share_of gives a workgroup
-
-// splits that keep a build's partial sums below 34 MB (256-wide tiles: 67 MB), unless a workgroup's rows would pass the maximum
-static inline __host__ __device__ int most_splits(int R, int tw, int ntiles, bool f32) {
-    const int cap = (tw == 256 ? 256 : 512) / ntiles, need = ceil_div(R, f32 ? ROWS_PER_WG_MAX_F32 : ROWS_PER_WG_MAX);
-    const int most = R / (f32 ? ROWS_PER_WG_MIN_F32 : ROWS_PER_WG_MIN);
-    const int ns = cap > need ? cap : need;
-    return ns > most ? (most > 1 ? most : 1) : (ns > 1 ? ns : 1);
-}
-
-// multiples of 8 keep a row range on one XCD
-static inline __host__ __device__ int xcd_splits(int ns) { return ns >= 8 ? ns / 8 * 8 : ns; }
-
-static inline __host__ __device__ FactorPlan plan_tiles(const View& v, int share) {
-    FactorPlan p;
-    const int D = v.u.d, R = v.u.R;
-    const bool f32 = v.u.dtype == KFAC_F32;
-    p.tw = D <= 64 ? 64 : D <= 128 || f32 || !(share & SHARE_WIDE) ? 128 : 256;
-    p.tiles_dim = ceil_div(D, p.tw);
-    p.ntiles = p.tiles_dim * (p.tiles_dim + 1) / 2;
-    const int most = most_splits(R, p.tw, p.ntiles, f32);
-    int ns = ceil_div(R, share & (SHARE_WIDE - 1));
-    if (ns > most) ns = most;
-    ns = xcd_splits(ns);
-    p.rows_per_split = ceil_div(ceil_div(R, ns), 64) * 64;
-    p.nsplit = ceil_div(R, p.rows_per_split);
-    p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * ((size_t)p.ntiles * p.tw * p.tw + (size_t)p.tiles_dim * p.tw) * sizeof(float) : 0;
-    return p;
-}
-
 // The work of a call's builds of one element size, in rows of 128 x 128 tiles, cut into 128- and into 256-wide tiles.
 struct TileWork {
     double narrow, wide;
 };
 static void add_work(TileWork& w, const View& v) {
+    if (v.shared) {
+        const double n = ceil_div(v.u.C, 128), m = ceil_div(v.u.C, 256);
+        w.narrow += (v.u.C <= 64 ? 13 * 0.5 : 0.5 * n * (n + 1) + 12 * n * n) * v.u.R;
+        w.wide += (v.u.C <= 64 ? 13 * 0.5 : v.u.C <= 128 ? 13 : 2.0 * m * (m + 1) + 48 * m * m) * v.u.R;
+        return;
+    }
     const double n = ceil_div(v.u.d, 128), m = ceil_div(v.u.d, 256);
     w.narrow += 0.5 * n * (n + 1) * v.u.R;
     w.wide += (v.u.d <= 128 ? 1.0 : 2.0 * m * (m + 1)) * v.u.R;
@@ -332,6 +292,8 @@ static int share_of(const TileWork& w, bool f32) {
 static size_t tiles_ws_bytes(const View& v) {
     const int D = v.u.d, R = v.u.R;
     const bool f32 = v.u.dtype == KFAC_F32;
+    if (v.shared)
+        return std::max(plan_shared(v, f32 ? SHARE_LEAST_F32 : SHARE_LEAST).ws_bytes, f32 ? 0 : plan_shared(v, ROWS_PER_WG_MAX + SHARE_WIDE).ws_bytes);
     size_t need = 0;
     for (int tw = D <= 64 ? 64 : 128; tw <= (D <= 128 || f32 ? 128 : 256) && !(D <= 64 && tw > 64); tw *= 2) {
         const int td = ceil_div(D, tw), nt = td * (td + 1) / 2;
@@ -342,55 +304,9 @@ static size_t tiles_ws_bytes(const View& v) {
     return need;
 }
 
-// The workspace of a matrix-core build: the repacked tensor, if there is one, then the partial sums.
-static inline __host__ __device__ Partial partial_of(const View& v, const FactorPlan& p, void* ws) {
-    Partial q;
-    q.tiles = (gfloat*)(ws ? (unsigned char*)ws + repack_bytes(v) : nullptr);
-    q.sums = q.tiles + (size_t)p.nsplit * p.ntiles * p.tw * p.tw;
-    return q;
-}
-
 // Whether the matrix-core kernels take a build whose tensor lies at x.
 static bool tile_eligible(const Unfold& u, const void* x, View* v) {
     return make_view(u, v) && ((uintptr_t)x & (v->repack ? (u.dtype == KFAC_F32 ? 3 : 1) : 15)) == 0;
-}
-
-// Where an item's result goes.
-static __host__ __device__ __forceinline__ OutSpec out_spec(const kfac_factor_item& it) {
-    OutSpec o;
-    o.decay = it.decay;
-    o.one_minus = 1.0f - it.decay;
-    if (it.running) { o.dst = (gfloat*)it.running; o.mode = OUT_EMA; }
-    else { o.dst = (gfloat*)it.out; o.mode = it.packed ? OUT_PACKED : OUT_PLAIN; }
-    return o;
-}
-
-// ---- batched launches: many factor builds in one grid -------------------------------------------------------------
-constexpr int FMAXB = 120;
-
-struct FBatch {
-    const kfac_factor_item* table;   // device table, or nullptr -> `single`
-    kfac_factor_item single;
-    int count;
-    int index[FMAXB];                // table index of the i-th build of this launch
-    int share[FMAXB];                // plan_tiles' argument for it
-    int prefix[FMAXB + 1];           // workgroup prefix sums
-};
-
-__device__ __forceinline__ int fbatch_locate(const FBatch& b, int wg, int& local) {
-    int lo = 0, hi = b.count;
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (b.prefix[mid] <= wg) lo = mid; else hi = mid;
-    }
-    local = wg - b.prefix[lo];
-    return lo;
-}
-
-__device__ __forceinline__ void fbatch_item(const FBatch& b, int m, kfac_factor_item& it, Unfold& u, View& v) {
-    it = b.table ? b.table[b.index[m]] : b.single;
-    if (it.op == KFAC_OP_FACTOR_A) make_unfold_A(&it.desc, &u); else make_unfold_G(&it.desc, &u);
-    make_view(u, &v);
 }
 
 // (128 and 64 wide: three workgroups of four wavefronts per CU; 256 wide: one of eight)
@@ -404,9 +320,13 @@ void factor_tile_kernel(FBatch b) {
     Unfold u;
     View v;
     fbatch_item(b, m, it, u, v);
+    const KFAC_AS1 unsigned char* x = (const KFAC_AS1 unsigned char*)(v.repack ? it.ws : it.x);
+    if (v.shared) {
+        shared_tile<TW, KIND>(v, x, plan_shared(v, b.share[m]), shared_ws(v, it.ws), local, smem);
+        return;
+    }
     const FactorPlan p = plan_tiles(v, b.share[m]);
     const float scale = it.scale == 0.f ? 1.0f / (float)u.R : it.scale;
-    const KFAC_AS1 unsigned char* x = (const KFAC_AS1 unsigned char*)(v.repack ? it.ws : it.x);
     factor_tile<TW, KIND>(v, x, scale, out_spec(it), partial_of(v, p, it.ws), p.rows_per_split, p.tiles_dim, p.ntiles, p.nsplit,
                           local, smem);
 }
@@ -422,119 +342,6 @@ __global__ __launch_bounds__(256) void factor_repack_kernel(FBatch b) {
     if (v.rows) repack_rows(u, v, (const KFAC_AS1 unsigned short*)it.x, (KFAC_AS1 unsigned*)it.ws, local);
     else if (u.dtype == KFAC_F32) repack_tile<float>(u, v, (const gfloat*)it.x, (KFAC_AS1 unsigned*)it.ws, local, smem);
     else repack_tile<unsigned short>(u, v, (const KFAC_AS1 unsigned short*)it.x, (KFAC_AS1 unsigned*)it.ws, local, smem);
-}
-
-// Second pass of split matrix-core builds: the per-split partial tiles summed in a fixed order, scaled, written with
-// their mirror (one workgroup per 32 x 32 sub-block: partial reads are 128-byte runs, the mirror goes through an LDS
-// transpose), and the bias row from the column sums (one workgroup per 256 columns).
-static inline __host__ __device__ int reduce_wgs(const View& v, const FactorPlan& p) {
-    return p.ntiles * (p.tw / 32) * (p.tw / 32) + (v.u.has_bias ? ceil_div(v.u.d, 256) : 0);
-}
-
-// GROUPS: groups of 256 threads that share out the splits (narrow matrices of many rows: few sub-blocks, hundreds of splits).
-template <int GROUPS>
-__global__ __launch_bounds__(256 * GROUPS) void factor_tile_reduce_kernel(FBatch b) {
-    __shared__ float tr[32][33];
-    __shared__ v4f gsum[GROUPS > 1 ? (GROUPS - 1) * 256 : 1];
-    const int t = threadIdx.x & 255, grp = threadIdx.x >> 8;
-    int local;
-    const int m = fbatch_locate(b, blockIdx.x, local);
-    kfac_factor_item it;
-    Unfold u;
-    View v;
-    fbatch_item(b, m, it, u, v);
-    const FactorPlan pl = plan_tiles(v, b.share[m]);
-    const float scale = it.scale == 0.f ? 1.0f / (float)u.R : it.scale;
-    const OutSpec os = out_spec(it);
-    const Partial part = partial_of(v, pl, it.ws);
-    const int D = v.u.d, d = v.dout, T = pl.tw, SB = T / 32, subs = SB * SB;
-    if (local >= pl.ntiles * subs) {
-        const int wg = local - pl.ntiles * subs, c = wg * 256 + t;
-        if (grp > 0) return;
-        if (c == 0) emit_sym(os, d, d - 1, d - 1, (float)u.R * scale, false);
-        const int co = result_index(v, c);
-        if (co < 0) return;
-        const size_t stride = (size_t)pl.tiles_dim * T;
-        float s = 0.f;
-#pragma unroll 8
-        for (int sp = 0; sp < pl.nsplit; ++sp) s += part.sums[sp * stride + c];
-        emit_sym(os, d, d - 1, co, s * scale, true);
-        return;
-    }
-    const int tile = local / subs, sub = local - tile * subs;
-    int I, J;
-    tri_decode_blocked<4>(pl.tiles_dim, tile, I, J);                 // (the tile kernel's order)
-    const int si = sub / SB, sj = sub - si * SB;
-    const int row0 = I * T + si * 32, col0 = J * T + sj * 32;
-    if (row0 < col0 || row0 >= D || col0 >= D) return;               // above the diagonal, or outside the matrix
-    const bool dg = row0 == col0;
-    const gfloat* src = part.tiles + (size_t)tile * (T * T) + (si * SB + sj) * 1024 + t * 4;
-    const size_t stride = (size_t)pl.ntiles * (T * T);
-    v4f s = {0.f, 0.f, 0.f, 0.f};
-    int sp = grp;
-    for (; sp + 7 * GROUPS < pl.nsplit; sp += 8 * GROUPS) {
-        v4f p[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) p[k] = *(const KFAC_AS1 v4f*)(src + (size_t)(sp + k * GROUPS) * stride);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) s += p[k];
-    }
-    for (; sp < pl.nsplit; sp += GROUPS) s += *(const KFAC_AS1 v4f*)(src + (size_t)sp * stride);
-    if constexpr (GROUPS > 1) {                                      // the groups' sums, in a fixed order
-        if (grp > 0) gsum[(grp - 1) * 256 + t] = s;
-        __syncthreads();
-        if (grp > 0) return;
-#pragma unroll
-        for (int k = 0; k < GROUPS - 1; ++k) s += gsum[k * 256 + t];
-    }
-    // from the registers' order (Partial) to four columns of one row per thread
-    {
-        const int q = t >> 6, lane = t & 63;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) tr[8 * q + 4 * (lane >> 5) + i][lane & 31] = s[i];
-    }
-    __syncthreads();
-    const int lr = t >> 3, lc = (t & 7) * 4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) s[i] = tr[lr][lc + i];
-    __syncthreads();
-    s *= scale;
-    gfloat* __restrict__ out = os.dst;
-    {
-        const int row = row0 + lr, ro = result_index(v, row);
-        int co[4];
-        bool ok[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            co[q] = result_index(v, col0 + lc + q);
-            ok[q] = ro >= 0 && co[q] >= 0 && !(dg && row < col0 + lc + q);
-        }
-        if (os.mode == OUT_EMA) {
-            float old[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) old[q] = ok[q] ? out[(size_t)ro * d + co[q]] : 0.f;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) s[q] = fmaf(os.decay, old[q], os.one_minus * s[q]);
-        }
-        if (os.mode != OUT_PACKED) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (ok[q]) out[(size_t)ro * d + co[q]] = s[q];
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) tr[lr][lc + q] = s[q];
-    __syncthreads();
-    // transposed: thread (lr, lc .. lc + 3) holds column col0 + lr of rows row0 + lc ..
-    const bool packed = os.mode == OUT_PACKED;
-    const int col = col0 + lr, co = result_index(v, col);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int row = row0 + lc + q, ro = result_index(v, row);
-        if (ro < 0 || co < 0 || (dg && (packed ? row < col : row <= col))) continue;
-        if (packed) out[packed_row_base(min(ro, co), d) + max(ro, co)] = tr[lc + q][lr];
-        else out[(size_t)co * d + ro] = tr[lc + q][lr];
-    }
 }
 
 static bool item_unfold(const kfac_factor_item& it, Unfold* u) {
@@ -652,7 +459,13 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
         add_work(own, v);
         return share_of(own, f32);
     };
-    FBatch b, r, rmany;                                // rmany: builds of many splits (factor_tile_reduce_kernel<4>)
+    FBatch b, fin[FINISH_LISTS];                       // fin: second passes, after all tiles
+    auto finish = [&](int k) -> int {
+        const int rc = launch_factor_finish(fin[k], k, stream);
+        fbatch_clear(fin[k], dev);
+        return rc;
+    };
+    for (int k = 0; k < FINISH_LISTS; ++k) fbatch_clear(fin[k], dev);
     auto repack = [&]() -> int {
         if (b.count) KFAC_LAUNCH(factor_repack_kernel, dim3(b.prefix[b.count]), dim3(256), stream, b);
         fbatch_clear(b, dev);
@@ -679,9 +492,7 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
         int next = 0;
         while (next < count) {
             fbatch_clear(b, dev);
-            fbatch_clear(r, dev);
-            fbatch_clear(rmany, dev);
-            struct Pick { int item, share, rows, wgs, reduce, nsplit; } pick[FMAXB];
+            struct Pick { int item, share, rows, wgs, finish, list; } pick[FMAXB];
             int n = 0;
             for (; next < count && n < FMAXB; ++next) {
                 Unfold u;
@@ -689,18 +500,21 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
                 item_unfold(host[next], &u);
                 if (u.dtype != VAR_DTYPE[var] || route_of(u, host[next].x, many, &v) != ROUTE_TILE) continue;
                 const int share = share_for(v);
+                if (v.shared) {
+                    const SharedPlan p = plan_shared(v, share);
+                    if (p.tw == VAR_TW[var]) pick[n++] = {next, share, p.rows, shared_workgroups(p), shared_assemble_wgs(v),
+                                                           v.chunked ? FINISH_CHANNELS : FINISH_FEW};
+                    continue;
+                }
                 const FactorPlan p = plan_tiles(v, share);
                 if (p.tw != VAR_TW[var]) continue;
                 pick[n++] = {next, share, p.rows_per_split, (int)align_up(p.ntiles * p.nsplit, 8),   // (a multiple of 8: see factor_tile)
-                             p.nsplit > 1 ? reduce_wgs(v, p) : 0, p.nsplit};
+                             p.nsplit > 1 ? reduce_wgs(v, p) : 0, p.nsplit >= MANY_SPLITS ? FINISH_MANY : FINISH_FEW};
             }
             if (n == 0) continue;
             // the longest workgroups first: the short ones fill the end of the launch
             std::stable_sort(pick, pick + n, [](const Pick& a, const Pick& c) { return a.rows > c.rows; });
-            for (int i = 0; i < n; ++i) {
-                fbatch_add(b, host, pick[i].item, pick[i].share, pick[i].wgs);
-                if (pick[i].reduce) fbatch_add(pick[i].nsplit >= 32 ? rmany : r, host, pick[i].item, pick[i].share, pick[i].reduce);
-            }
+            for (int i = 0; i < n; ++i) fbatch_add(b, host, pick[i].item, pick[i].share, pick[i].wgs);
             switch (var) {
                 case 0: rc = launch_tiles<64, 0>(b, stream); break;
                 case 1: rc = launch_tiles<64, 1>(b, stream); break;
@@ -712,14 +526,16 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
                 default: rc = launch_tiles<128, 2>(b, stream); break;
             }
             if (rc != KFAC_OK) return rc;
-            if (rmany.count > 0) {
-                KFAC_LAUNCH(factor_tile_reduce_kernel<4>, dim3(rmany.prefix[rmany.count]), dim3(1024), stream, rmany);
-            }
-            if (r.count > 0) {
-                KFAC_LAUNCH(factor_tile_reduce_kernel<1>, dim3(r.prefix[r.count]), dim3(256), stream, r);
+            for (int i = 0; i < n; ++i) {
+                if (!pick[i].finish) continue;
+                FBatch& f = fin[pick[i].list];
+                fbatch_add(f, host, pick[i].item, pick[i].share, pick[i].finish);
+                if (f.count == FMAXB && (rc = finish(pick[i].list)) != KFAC_OK) return rc;
             }
         }
     }
+    for (int k = 0; k < FINISH_LISTS; ++k)
+        if ((rc = finish(k)) != KFAC_OK) return rc;
     for (int i = 0; i < count; ++i) {
         Unfold u;
         View v;

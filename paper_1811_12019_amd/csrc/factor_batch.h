@@ -1,0 +1,147 @@
+// What the factor builders' launches share (factor.hip, factor_finish.hip): how a build is cut into tiles and row ranges, where its
+// partial sums lie, and the argument block of a launch that serves many builds.
+#pragma once
+
+#include "factor_tile.h"
+#include "factor_repack.h"
+#include "factor_shared.h"
+
+namespace kfac {
+
+struct FactorPlan {
+    int tw;          // tile width (matrix-core builds)
+    int tiles_dim;   // tiles per dimension
+    int ntiles;      // lower-triangular tiles
+    int nsplit;
+    int rows_per_split;
+    size_t ws_bytes;
+};
+
+// Tile width and row split of a matrix-core build.  `share`: how the builds of a call are cut (share_of): the rows of a
+// workgroup, plus SHARE_WIDE if matrices of more than 128 columns get 256-wide tiles.  A matrix of up to 128 (64) columns is
+// one tile of that width.
+constexpr int SHARE_WIDE = 1 << 20;
+constexpr int ROWS_PER_WG_MAX = 6400, ROWS_PER_WG_MAX_F32 = 1600;
+constexpr int ROWS_PER_WG_MIN = 512, ROWS_PER_WG_MIN_F32 = 64;
+constexpr int SHARE_LEAST = 1024, SHARE_LEAST_F32 = 128;           // the fewest rows share_of gives a workgroup
+
+// splits that keep a build's partial sums below 34 MB (256-wide tiles: 67 MB), unless a workgroup's rows would pass the maximum
+static inline __host__ __device__ int most_splits(int R, int tw, int ntiles, bool f32) {
+    const int cap = (tw == 256 ? 256 : 512) / ntiles, need = ceil_div(R, f32 ? ROWS_PER_WG_MAX_F32 : ROWS_PER_WG_MAX);
+    const int most = R / (f32 ? ROWS_PER_WG_MIN_F32 : ROWS_PER_WG_MIN);
+    const int ns = cap > need ? cap : need;
+    return ns > most ? (most > 1 ? most : 1) : (ns > 1 ? ns : 1);
+}
+
+// multiples of 8 keep a row range on one XCD
+static inline __host__ __device__ int xcd_splits(int ns) { return ns >= 8 ? ns / 8 * 8 : ns; }
+
+// The same for a layer whose tap pairs share their sums.
+static inline __host__ __device__ SharedPlan plan_shared(const View& v, int share) {
+    SharedPlan p;
+    const Unfold& u = v.u;
+    const bool f32 = u.dtype == KFAC_F32;
+    p.tw = u.C <= 64 ? 64 : u.C <= 128 || f32 || !(share & SHARE_WIDE) ? 128 : 256;
+    p.T = ceil_div(u.C, p.tw);
+    p.ntl = p.T * (p.T + 1) / 2;
+    p.nf = p.T * p.T;
+    p.per[0] = p.ntl + 12 * p.nf;
+    p.per[1] = p.per[2] = 2 * p.ntl + 4 * p.nf;
+    p.per[3] = 4 * p.ntl;
+    const int share_rows = share & (SHARE_WIDE - 1);
+    const int rows = u.N * (u.H - 1) * (u.W - 1);
+    const int most = most_splits(rows, p.tw, p.per[0], f32);
+    int ns = ceil_div(rows, share_rows);
+    if (ns > most) ns = most;
+    p.ns[0] = xcd_splits(ns);
+    const int ends[3] = {u.N * (u.W - 1), u.N * (u.H - 1), u.N};
+    p.first[0] = 0;
+    p.first[1] = p.ns[0] * p.per[0];
+#pragma unroll
+    for (int c = 1; c < 4; ++c) {
+        const int n = ceil_div(ends[c - 1], share_rows);
+        p.ns[c] = n < p.ns[0] ? n : p.ns[0];
+        p.first[c + 1] = p.first[c] + p.ns[c] * p.per[c];
+    }
+    p.rows = ceil_div(rows, p.ns[0]);
+    p.ws_bytes = ((size_t)p.first[4] * p.tw * p.tw + (size_t)9 * p.ns[0] * p.T * p.tw) * sizeof(float);
+    return p;
+}
+
+static inline __host__ __device__ FactorPlan plan_tiles(const View& v, int share) {
+    FactorPlan p;
+    const int D = v.u.d, R = v.u.R;
+    const bool f32 = v.u.dtype == KFAC_F32;
+    p.tw = D <= 64 ? 64 : D <= 128 || f32 || !(share & SHARE_WIDE) ? 128 : 256;
+    p.tiles_dim = ceil_div(D, p.tw);
+    p.ntiles = p.tiles_dim * (p.tiles_dim + 1) / 2;
+    const int most = most_splits(R, p.tw, p.ntiles, f32);
+    int ns = ceil_div(R, share & (SHARE_WIDE - 1));
+    if (ns > most) ns = most;
+    ns = xcd_splits(ns);
+    p.rows_per_split = ceil_div(ceil_div(R, ns), 64) * 64;
+    p.nsplit = ceil_div(R, p.rows_per_split);
+    p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * ((size_t)p.ntiles * p.tw * p.tw + (size_t)p.tiles_dim * p.tw) * sizeof(float) : 0;
+    return p;
+}
+
+// The workspace of a matrix-core build: the repacked tensor, if there is one, then the partial sums.
+static inline __host__ __device__ Partial partial_of(const View& v, const FactorPlan& p, void* ws) {
+    Partial q;
+    q.tiles = (gfloat*)(ws ? (unsigned char*)ws + repack_bytes(v) : nullptr);
+    q.sums = q.tiles + (size_t)p.nsplit * p.ntiles * p.tw * p.tw;
+    return q;
+}
+
+static inline __device__ gfloat* shared_ws(const View& v, void* ws) { return (gfloat*)((unsigned char*)ws + repack_bytes(v)); }
+
+// Where an item's result goes.
+static __host__ __device__ __forceinline__ OutSpec out_spec(const kfac_factor_item& it) {
+    OutSpec o;
+    o.decay = it.decay;
+    o.one_minus = 1.0f - it.decay;
+    if (it.running) { o.dst = (gfloat*)it.running; o.mode = OUT_EMA; }
+    else { o.dst = (gfloat*)it.out; o.mode = it.packed ? OUT_PACKED : OUT_PLAIN; }
+    return o;
+}
+
+// ---- batched launches: many factor builds in one grid -------------------------------------------------------------
+constexpr int FMAXB = 120;
+
+struct FBatch {
+    const kfac_factor_item* table;   // device table, or nullptr -> `single`
+    kfac_factor_item single;
+    int count;
+    int index[FMAXB];                // table index of the i-th build of this launch
+    int share[FMAXB];                // plan_tiles' argument for it
+    int prefix[FMAXB + 1];           // workgroup prefix sums
+};
+
+__device__ __forceinline__ int fbatch_locate(const FBatch& b, int wg, int& local) {
+    int lo = 0, hi = b.count;
+    while (hi - lo > 1) {
+        int mid = (lo + hi) >> 1;
+        if (b.prefix[mid] <= wg) lo = mid; else hi = mid;
+    }
+    local = wg - b.prefix[lo];
+    return lo;
+}
+
+__device__ __forceinline__ void fbatch_item(const FBatch& b, int m, kfac_factor_item& it, Unfold& u, View& v) {
+    it = b.table ? b.table[b.index[m]] : b.single;
+    if (it.op == KFAC_OP_FACTOR_A) make_unfold_A(&it.desc, &u); else make_unfold_G(&it.desc, &u);
+    make_view(u, &v);
+}
+
+// Second passes of the builds of `b` (factor_finish.hip): builds of few row ranges or shared sums, of many ranges, of shared sums in
+// (channel, tap) order.
+enum { FINISH_FEW, FINISH_MANY, FINISH_CHANNELS, FINISH_LISTS };
+int launch_factor_finish(const FBatch& b, int list, hipStream_t stream);
+
+// Workgroups of the second pass of split rows.
+constexpr int MANY_SPLITS = 32;
+static inline __host__ __device__ int reduce_wgs(const View& v, const FactorPlan& p) {
+    return p.ntiles * (p.tw / 32) * (p.tw / 32) * (p.nsplit >= MANY_SPLITS ? 4 : 1) + (v.u.has_bias ? ceil_div(v.u.d, 256) : 0);
+}
+
+}  // namespace kfac

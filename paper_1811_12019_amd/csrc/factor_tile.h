@@ -55,6 +55,8 @@ __device__ __forceinline__ v16f mfma16_halves(v2u a0, v2u a1, v2u b0, v2u b1, v1
     return mfma16<F16>(a, b, c);
 }
 
+constexpr int SHARED_ROWS_MIN = 1024, SHARED_INPUT_MIN = 1 << 17;
+
 // A build as the matrix-core kernels see it.
 struct View {
     Unfold u;        // the tensor they read: channels last, C a multiple of the 16-byte vector; d = data columns (no bias)
@@ -68,7 +70,22 @@ struct View {
                      // of no interest if kw is odd) are one run of columns; the copy has the zero padding in it, so that every
                      // run is whole.  The view's kw is 1, its pad 0.
     int kw;          // the layer's kernel width
+    int shared;      // tap pairs at the same offset share their sums (factor_shared.h)
 };
+
+// Whether a 3 x 3 layer of stride 1 and padding 1 is built from the sums that its tap pairs share (factor_shared.h): 13 C x C
+// blocks (offset (0, 0): its lower half) instead of the lower half of a 9 C x 9 C matrix, in whole tiles.  A 64-wide tile
+// moves twice as many bytes per product as a 128-wide one.  At most half as many: the strips and the second launch cost something
+// too.  Little work is left to the dense form, whose tiles then need no second launch: at 1,568 rows 128 channels take 29 us against
+// 31, 16 such builds in a call 80 against 75; 64 channels at 6,272 rows 24 against 30.
+static inline __host__ __device__ bool taps_shared(const Unfold& u) {
+    if (u.kh != 3 || u.kw != 3 || u.stride != 1 || u.pad != 1 || u.H < 4 || u.W < 4 || u.R < SHARED_ROWS_MIN ||
+        (long long)u.R * u.C < SHARED_INPUT_MIN)
+        return false;
+    const long long n = ceil_div(u.d, 128), m = u.C <= 64 ? 1 : ceil_div(u.C, 128);
+    const long long dense = n * (n + 1) / 2 * 4, parts = u.C <= 64 ? 13 * 2 : 4 * (m * (m + 1) / 2 + 12 * m * m);
+    return 2 * parts <= dense;
+}
 
 // False: the matrix-core kernels cannot take the build.
 static inline __host__ __device__ bool make_view(const Unfold& u, View* v) {
@@ -92,6 +109,7 @@ static inline __host__ __device__ bool make_view(const Unfold& u, View* v) {
     v->rows = rows;
     v->chunked = u.order == KFAC_ORDER_C_KH_KW && u.kh * u.kw > 1;
     v->mapped = v->chunked || Cp != u.C || rows;
+    v->shared = !rows && taps_shared(v->u);
     v->repack = (u.layout == KFAC_NCHW && u.H * u.W > 1) || Cp != u.C || rows;
     return (long long)u.N * v->u.H * v->u.W * Cp <= 0x7fffffffLL;            // 32-bit element offsets
 }
@@ -174,16 +192,25 @@ template <int N> struct StaticInt { static constexpr int value = N; };
 
 // What a tile's workgroup works on.
 struct TileJob {
-    int I, J, tile, split;
+    int I, J;
     int r_begin, r_end;
-    int tiles_dim, ntiles, nsplit;
     float scale;
+    bool split;              // partial sums: the tile goes to tile_dst, the column sums of a diagonal one to sums_dst
+    gfloat *tile_dst, *sums_dst;
+    int first_pixel, partner;  // FEED_WINDOW: the rectangle's first pixel, and how many pixels behind a row's pixel the one of the
+                               // tile's columns lies
 };
 
+// Where the rows come from.  PATCHES: unfolded patches of any geometry.  PIXELS: a row is a pixel, all of the tensor in order.
+// WINDOW: a row is a pair of pixels at a fixed offset, the first for the tile's rows, the second for its columns; the first ones
+// are an Ho x Wo rectangle of each image (factor_shared.h).
+enum { FEED_PATCHES, FEED_PIXELS, FEED_WINDOW };
+
 // One tile.  KIND 0: bf16, 1: fp16, 2: fp32.
-template <int TW, int KIND, bool PLAIN, bool DIAG>
+template <int TW, int KIND, int FEED, bool DIAG>
 __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 unsigned char* x, const TileJob& job,
-                                                const OutSpec& os, const Partial& part, unsigned char* smem) {
+                                                const OutSpec& os, unsigned char* smem) {
+    constexpr bool PLAIN = FEED == FEED_PIXELS, WINDOW = FEED == FEED_WINDOW;
     constexpr int ES = KIND == 2 ? 4 : 2, V = 16 / ES;
     typedef TileShape<TW, ES> S;
     constexpr int NW = S::WM * S::WN, DK = S::DK;
@@ -221,7 +248,15 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
         row0 = 4 * (L / (TW / 2)) + ((s & 7) >> 1);
         q = 2 * (s >> 3) + (s & 1);
     }
-    const ColGroup g = decode_group(v, (pan == 0 ? I : J) * TW + q * V);
+    ColGroup g;
+    if constexpr (WINDOW) {
+        g.ki = g.kj = 0;
+        g.off = (pan == 0 ? I : J) * TW + q * V;
+        g.data = g.off < D;
+        g.off += pan == 0 ? job.first_pixel * u.C : (job.first_pixel + job.partner) * u.C;
+    } else {
+        g = decode_group(v, (pan == 0 ? I : J) * TW + q * V);
+    }
     lds_byte* lds0 = (lds_byte*)smem + pan * PANEL + b0 * 1024;
     const unsigned long long zero_addr = (unsigned long long)(const KFAC_AS1 unsigned char*)&g_zero_chunk;
 
@@ -258,7 +293,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             bool ok = rows_left > j * ROWSTEP;
-            if constexpr (!PLAIN) ok = ok & ((unsigned)ty[j] < (unsigned)u.H) & ((unsigned)tx[j] < (unsigned)u.W);
+            if constexpr (FEED == FEED_PATCHES) ok = ok & ((unsigned)ty[j] < (unsigned)u.H) & ((unsigned)tx[j] < (unsigned)u.W);
             src[j] = ok ? at[j] : zero_addr;
             at[j] += (unsigned long long)step_bytes;
             if constexpr (!PLAIN) {
@@ -360,7 +395,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     const int d = v.dout;
     gfloat* __restrict__ out = os.dst;
     const bool packed = os.mode == OUT_PACKED, ema = os.mode == OUT_EMA;
-    const bool split = job.nsplit > 1;
+    const bool split = WINDOW || job.split;
     // result row of each of the tile's rows and columns (-1: none), and the same times the result's width
     int* rmap = (int*)(smem + tile_ring_bytes<TW, ES>());
     int* cmap = rmap + TW;
@@ -409,7 +444,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
         });
         if (h == 0) {                                           // (all rows of the products are the sums)
             if (split) {
-                gfloat* dst = part.sums + (size_t)job.split * (job.tiles_dim * TW) + J * TW + c0;
+                gfloat* dst = job.sums_dst + J * TW + c0;
 #pragma unroll
                 for (int i = 0; i < BB; ++i) dst[i * 32 + lm] = acc[i][0];
             } else {
@@ -465,7 +500,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     // Stores leave a CU at four lanes per cycle, whatever a lane stores: 16-byte stores wherever four neighbours are there
     // (4-byte ones took 30 us of a tile's life).
     if (split) {                                                   // partial sums: in register order, see Partial
-        gfloat* dst = part.tiles + ((size_t)job.split * job.ntiles + job.tile) * (TW * TW) + (size_t)lane * 4;
+        gfloat* dst = job.tile_dst + (size_t)lane * 4;
 #pragma unroll
         for (int p = 0; p < S::MB; ++p)
 #pragma unroll
@@ -605,28 +640,30 @@ __device__ __forceinline__ void factor_tile(const View& v, const KFAC_AS1 unsign
     // x-th contiguous eighth of the build's work list (row ranges in order, tiles in blocked order inside a range): the
     // tiles of a row range, which all read the same rows, share one L2 instead of fetching them eight times.
     TileJob job;
+    int tile, sp;
     {
         const int work = ntiles * nsplit;
         const int per_xcd = (work + 7) >> 3;
         const int unit = (wg & 7) * per_xcd + (wg >> 3);
         if ((wg >> 3) >= per_xcd || unit >= work) return;          // padding workgroup (uniform, before any barrier)
-        job.split = unit / ntiles;
-        job.tile = unit - job.split * ntiles;
+        sp = unit / ntiles;
+        tile = unit - sp * ntiles;
     }
-    tri_decode_blocked<4>(tiles_dim, job.tile, job.I, job.J);      // (tiles that share row panels run together: see the function)
-    job.r_begin = job.split * rows_per_split;
+    tri_decode_blocked<4>(tiles_dim, tile, job.I, job.J);          // (tiles that share row panels run together: see the function)
+    job.r_begin = sp * rows_per_split;
     job.r_end = min(v.u.R, job.r_begin + rows_per_split);
-    job.tiles_dim = tiles_dim;
-    job.ntiles = ntiles;
-    job.nsplit = nsplit;
+    job.split = nsplit > 1;
+    job.tile_dst = part.tiles + ((size_t)sp * ntiles + tile) * (TW * TW);
+    job.sums_dst = part.sums + (size_t)sp * (tiles_dim * TW);
     job.scale = scale;
+    job.first_pixel = job.partner = 0;
     const bool plain = is_plain(v.u);
     if (job.I == job.J) {
-        if (plain) factor_tile_run<TW, KIND, true, true>(v, x, job, os, part, smem);
-        else factor_tile_run<TW, KIND, false, true>(v, x, job, os, part, smem);
+        if (plain) factor_tile_run<TW, KIND, FEED_PIXELS, true>(v, x, job, os, smem);
+        else factor_tile_run<TW, KIND, FEED_PATCHES, true>(v, x, job, os, smem);
     } else if constexpr (TW > 64) {                                // (64-wide matrices are one tile)
-        if (plain) factor_tile_run<TW, KIND, true, false>(v, x, job, os, part, smem);
-        else factor_tile_run<TW, KIND, false, false>(v, x, job, os, part, smem);
+        if (plain) factor_tile_run<TW, KIND, FEED_PIXELS, false>(v, x, job, os, smem);
+        else factor_tile_run<TW, KIND, FEED_PATCHES, false>(v, x, job, os, smem);
     }
 }
 
