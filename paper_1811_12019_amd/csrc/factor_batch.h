@@ -50,9 +50,10 @@ static inline __host__ __device__ SharedPlan plan_shared(const View& v, int shar
     p.per[3] = 4 * p.ntl;
     const int share_rows = share & (SHARE_WIDE - 1);
     const int rows = u.N * (u.H - 1) * (u.W - 1);
-    const int most = most_splits(rows, p.tw, p.per[0], f32);
+    const int cap = most_splits(rows, p.tw, p.per[0], f32), least = rows / (f32 ? SHARE_LEAST_F32 : SHARE_LEAST);
     int ns = ceil_div(rows, share_rows);
-    if (ns > most) ns = most;
+    if (ns > cap) ns = cap;
+    if (ns > least) ns = least > 1 ? least : 1;        // (a set of partial sums for less than SHARE_LEAST rows is not worth its traffic)
     p.ns[0] = xcd_splits(ns);
     const int ends[3] = {u.N * (u.W - 1), u.N * (u.H - 1), u.N};
     p.first[0] = 0;
