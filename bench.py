@@ -34,9 +34,8 @@ from paper_1811_12019_amd import synth                # noqa: E402
 
 PEAK = {"mfma_bf16": 2500.0, "mfma_f32": 157.3, "hbm": 8000.0}   # TFLOP/s, TFLOP/s, GB/s
 # fp32 products computed as sums of 16-bit MFMAs over split operands: 6 MFMAs per fp32 product with both operands
-# split into three bf16 pieces (the sweep's panel product), 3 with both split into two fp16 pieces of scaled operands
+# split into three bf16 pieces (the sweep's panel products), 3 with both split into two fp16 pieces of scaled operands
 # (the sweep's rank-128 updates, both preconditioning products); fp16 and bf16 MFMA peaks are equal
-PEAK["mfma_bf16x3"] = round(PEAK["mfma_bf16"] / 6, 1)
 PEAK["mfma_f16x2"] = round(PEAK["mfma_bf16"] / 3, 1)
 
 
@@ -47,22 +46,24 @@ def kernel_work(net: kstep.KfacNetworkStep, kernels):
     dims = [d for s in shapes for d in (s.d_A, s.d_G)]
 
     # every factor is built by the tile kernel: up to 64 columns (without the bias) by the 64-wide one, up to 128 by the 128-wide
-    # one, wider ones all by the 128- or all by the 256-wide one
+    # one, wider ones all by the 128- or all by the 256-wide one; 3 x 3 layers of stride 1 from the C x C sums that their tap pairs
+    # share (12.5 of them, with the symmetric one's half)
     wide = 256 if "factor_tile_kernel<256, 16-bit>" in kernels else 128
     fac_tile = {64: 0.0, 128: 0.0, 256: 0.0}
     for s in shapes:
         for d, columns in ((s.d_A, s.d_A - s.has_bias), (s.d_G, s.d_G)):
-            fac_tile[64 if columns <= 64 else 128 if columns <= 128 else wide] += kstep.factor_flops(s.R, d)
+            flops = kstep.factor_flops(s.R, d)
+            if d == s.d_A and (s.kh, s.kw, s.stride, s.pad) == (3, 3, 1, 1) and s.C_in % 64 == 0:
+                columns, flops = s.C_in, 25.0 * s.R * s.C_in * s.C_in
+            fac_tile[64 if columns <= 64 else 128 if columns <= 128 else wide] += flops
     w = {
-        # all steps of all matrices in one kernel; a matrix's last step (short product, dense mirrored output) is a
-        # small part of it; it also inverts the next step's pivot block (fp32 matrix cores) beside the update
+        # all steps of all matrices in one kernel: rank-128 updates (fp16 pieces), panel products (2 d nb^2 a step, bf16 pieces) and
+        # the later pivot blocks' inversions (fp32)
         "inv_update_kernel": ("mfma", PEAK["mfma_f16x2"], "TFLOP/s",
-                              sum(kstep.inverse_update_flops(d) + kstep.inverse_pivot_flops(d) - kstep.inverse_first_pivot_flops(d)
-                                  for d in dims)),
-        # latency-bound helpers of the sweep (one workgroup per matrix / per 128-row slab): first-block inverses of nb^3
-        # flops (fp32 matrix cores), panel products of 2 d nb^2 (bf16 matrix cores, operands split three ways)
+                              sum(kstep.inverse_update_flops(d) + kstep.inverse_panel_flops(d) + kstep.inverse_pivot_flops(d)
+                                  - kstep.inverse_first_pivot_flops(d) for d in dims)),
+        # one workgroup per matrix: first-block inverses of nb^3 flops
         "inv_begin_kernel": ("mfma", PEAK["mfma_f32"], "TFLOP/s", sum(kstep.inverse_first_pivot_flops(d) for d in dims)),
-        "inv_panel_kernel": ("mfma", PEAK["mfma_bf16x3"], "TFLOP/s", sum(kstep.inverse_panel_flops(d) for d in dims)),
         "gemm_nt_kernel": ("mfma", PEAK["mfma_f16x2"], "TFLOP/s", sum(kstep.precondition_flops(s.d_G, s.d_A) for s in shapes)),
         # the operands' piece planes: every element read (4 B) and written (2 x 2 B): the gradient by the preconditioning
         # call, the inverses by the inversion call (kfac_inverse_item.planes)

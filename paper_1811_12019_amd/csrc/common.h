@@ -88,7 +88,7 @@ __device__ __forceinline__ void emit_sym(const OutSpec& o, int d, int row, int c
 }
 
 // lower-triangular tile index -> (I, J), I >= J, tiles numbered row by row
-__device__ __forceinline__ void tri_decode(int t, int& I, int& J) {
+__host__ __device__ __forceinline__ void tri_decode(int t, int& I, int& J) {
     int i = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
     while ((i + 1) * (i + 2) / 2 <= t) ++i;
     while (i * (i + 1) / 2 > t) --i;
@@ -101,7 +101,7 @@ __device__ __forceinline__ void tri_decode(int t, int& I, int& J) {
 // inside one), so that a contiguous range of the list, which is what one XCD (one L2) gets, reads about as many
 // different row panels as column panels instead of one or two of the former and all of the latter.
 template <int SB = 8>
-__device__ __forceinline__ void tri_decode_blocked(int n, int t, int& I, int& J) {
+__host__ __device__ __forceinline__ void tri_decode_blocked(int n, int t, int& I, int& J) {
     int r0 = 0;
     for (;;) {                                           // super-row with rows r0 .. r0 + h - 1
         const int h = min(SB, n - r0);

@@ -42,14 +42,9 @@ __device__ __forceinline__ v4f load4_guard(const gfloat* p, bool row_ok, int k, 
 }
 
 // A: first row of the tile's A operand, lda floats between rows, arows (<=128) valid rows; same for B.
-// A_TRANS: the A operand is stored transposed in memory, element (m, k) at A[k * lda + m] (used for the part of
-//          a symmetric matrix's block column that only exists, transposed, in the lower triangle).
-// The A slabs are also written to copyA[row * ldcopy + k] as they stream through.
-template <bool A_TRANS>
 __device__ __forceinline__ void tile_mma_nt(const gfloat* __restrict__ A, int lda, int arows,
                                             const gfloat* __restrict__ B, int ldb, int brows, int K,
-                                            float* __restrict__ lds, TileAcc& acc,
-                                            gfloat* __restrict__ copyA, int ldcopy) {
+                                            float* __restrict__ lds, TileAcc& acc) {
     constexpr int QK = TK / 4;                        // float4 per row of a slab
     constexpr int RP = 256 / QK;                      // rows per pass
     constexpr int NP = TM / RP;                       // passes per operand
@@ -59,7 +54,6 @@ __device__ __forceinline__ void tile_mma_nt(const gfloat* __restrict__ A, int ld
     const int lane = t & 63, wave = t >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int lr = t / QK, kq = (t % QK) * 4;         // RP rows x QK float4 per pass
-    const int tm = (t & 31) * 4, tk = t >> 5;         // transposed A: 8 k x 32 float4 (along m) per pass
     const int lm = lane & 31, h = lane >> 5;
 
 #pragma unroll
@@ -74,12 +68,7 @@ __device__ __forceinline__ void tile_mma_nt(const gfloat* __restrict__ A, int ld
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const int row = lr + RP * p;
-            if constexpr (A_TRANS) {
-                const int k = k0 + tk + 8 * p;      // NP passes of 8 k each cover the slab (TK = 8 * NP)
-                ra[p] = load4_guard(A + (size_t)k * lda, k < K, tm, arows);
-            } else {
-                ra[p] = load4_guard(A + (size_t)row * lda, row < arows, k0 + kq, K);
-            }
+            ra[p] = load4_guard(A + (size_t)row * lda, row < arows, k0 + kq, K);
             rb[p] = load4_guard(B + (size_t)row * ldb, row < brows, k0 + kq, K);
         }
     };
@@ -87,26 +76,10 @@ __device__ __forceinline__ void tile_mma_nt(const gfloat* __restrict__ A, int ld
     for (int k0 = 0; k0 < K; k0 += TK) {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            const int row = lr + RP * p;
-            if constexpr (A_TRANS) {
-                const int kk = tk + 8 * p;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) As[(tm + i) * TLD + kk] = ra[p][i];
-            } else {
-                *(v4f*)&As[row * TLD + kq] = ra[p];
-                if (row < arows && k0 + kq < K) *(KFAC_AS1 v4f*)&copyA[(size_t)row * ldcopy + k0 + kq] = ra[p];
-            }
-            *(v4f*)&Bs[row * TLD + kq] = rb[p];
+            *(v4f*)&As[(lr + RP * p) * TLD + kq] = ra[p];
+            *(v4f*)&Bs[(lr + RP * p) * TLD + kq] = rb[p];
         }
         __syncthreads();
-        if constexpr (A_TRANS) {
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const int row = lr + RP * p;
-                if (row < arows && k0 + kq < K)
-                    *(KFAC_AS1 v4f*)&copyA[(size_t)row * ldcopy + k0 + kq] = *(const v4f*)&As[row * TLD + kq];
-            }
-        }
         if (k0 + TK < K) fetch(k0 + TK);
 #pragma unroll
         for (int s = 0; s < TK / 8; ++s) {

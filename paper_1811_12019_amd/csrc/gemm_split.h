@@ -52,36 +52,42 @@ __device__ __forceinline__ void split4(const v4f& x, uint2 (&piece)[NS]) {
 // lie in memory: split in registers, two slices ahead in flight.  lds: PANEL_B_LDS bytes, 16-byte aligned; one barrier a slice.
 constexpr int PANEL_B_LDS = 2 * 3 * SPLIT_PLANE;
 
-__device__ __forceinline__ void panel_fetch_b(const gfloat* __restrict__ B, v4f (&pb)[16]) {
-    const int lr = threadIdx.x >> 2, kq = threadIdx.x & 3;       // rows lr and lr + 64, floats 4 kq .. + 3 of a slice
+// B's rows lr and lr + 64 (lr = t / 4), floats 4 kq .. + 3 (kq = t % 4) of slice s: fetched, and stored as pieces to stage s % 2.
+__device__ __forceinline__ void panel_fetch_slice(const gfloat* __restrict__ B, int s, v4f (&x)[2]) {
+    const int lr = threadIdx.x >> 2, kq = threadIdx.x & 3;
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
-#pragma unroll
-        for (int p = 0; p < 2; ++p) pb[2 * s + p] = *(const KFAC_AS1 v4f*)(B + (lr + 64 * p) * 128 + s * SPLIT_KS + 4 * kq);
+    for (int p = 0; p < 2; ++p) x[p] = *(const KFAC_AS1 v4f*)(B + (lr + 64 * p) * 128 + s * SPLIT_KS + 4 * kq);
 }
 
-__device__ __forceinline__ void panel_product(const gfloat* __restrict__ A, const v4f (&pb)[16], unsigned char* __restrict__ lds,
+__device__ __forceinline__ void panel_stash(unsigned char* __restrict__ lds, int s, const v4f (&x)[2]) {
+    const int lr = threadIdx.x >> 2, kq = threadIdx.x & 3;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int row = lr + 64 * p;
+        const unsigned off = (unsigned)(row * 32 + (((kq >> 1) ^ ((row >> 2) & 1) ^ ((row >> 3) & 1)) * 16) + (kq & 1) * 8);
+        uint2 piece[3];
+        split4<3>(x[p], piece);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) *(uint2*)(lds + (s & 1) * (3 * SPLIT_PLANE) + e * SPLIT_PLANE + off) = piece[e];
+    }
+}
+
+__device__ __forceinline__ void panel_fetch_b(const gfloat* __restrict__ B, v4f (&pb)[8][2]) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) panel_fetch_slice(B, s, pb[s]);
+}
+
+__device__ __forceinline__ void panel_product(const gfloat* __restrict__ A, const v4f (&pb)[8][2], unsigned char* __restrict__ lds,
                                               v16f (&acc)[2]) {
     constexpr int BUF = 3 * SPLIT_PLANE;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
     const int lm = lane & 31, h = lane >> 5;
-    const int lr = t >> 2, kq = t & 3;
-    unsigned w_off[2], b_off[2];
+    unsigned b_off[2];
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
-        const int row = lr + 64 * p, rb = wn * 64 + p * 32 + lm;
-        w_off[p] = (unsigned)(row * 32 + (((kq >> 1) ^ ((row >> 2) & 1) ^ ((row >> 3) & 1)) * 16) + (kq & 1) * 8);
+        const int rb = wn * 64 + p * 32 + lm;
         b_off[p] = (unsigned)(rb * 32 + ((h ^ ((rb >> 2) & 1) ^ ((rb >> 3) & 1)) * 16));
     }
-    auto stash = [&](int s) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            uint2 piece[3];
-            split4<3>(pb[2 * s + p], piece);
-#pragma unroll
-            for (int e = 0; e < 3; ++e) *(uint2*)(lds + (s & 1) * BUF + e * SPLIT_PLANE + w_off[p]) = piece[e];
-        }
-    };
     v4f xa[3][2];                                                // slices s, s + 1, s + 2
     const gfloat* arow = A + (wm * 32 + lm) * 128 + 8 * h;
     auto fetch = [&](int s, v4f (&x)[2]) {
@@ -90,7 +96,7 @@ __device__ __forceinline__ void panel_product(const gfloat* __restrict__ A, cons
     };
     fetch(0, xa[0]);
     fetch(1, xa[1]);
-    stash(0);
+    panel_stash(lds, 0, pb[0]);
 #pragma unroll
     for (int n = 0; n < 2; ++n)
 #pragma unroll
@@ -116,7 +122,7 @@ __device__ __forceinline__ void panel_product(const gfloat* __restrict__ A, cons
             for (int pa = 0; pa <= order; ++pa)
 #pragma unroll
                 for (int n = 0; n < 2; ++n) acc[n] = mfma16<false>(a[pa], b[n][order - pa], acc[n]);
-        if (s + 1 < 8) stash(s + 1);
+        if (s + 1 < 8) panel_stash(lds, s + 1, pb[s + 1]);
         __syncthreads();
     }
 }
@@ -301,6 +307,89 @@ __device__ __forceinline__ float tile_mma_presplit(const SplitRun<MAXN>& p, unsi
                         __builtin_memcpy(&bv, &b[nb][term == 1 ? 1 : 0], 16);
                         acc.c[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv, acc.c[mb][nb], 0, 0, 0);
                     }
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");            // ring idle: the LDS may be reused
+    return back;
+}
+
+// The same for half a slab of A: acc[64 x 128] (+)= sum over the products of A_q B_q^T, a_hi pointing at the half slab's rows.
+// Wavefront (wm, wn) holds rows 32 wm .. + 31 of columns 64 wn .. + 63 as two MFMA blocks; scale[q] is that of the wavefront's
+// columns.  A slice is 12 KB (three 1 KB copies a wavefront) in a ring of HALF_NS stages.
+constexpr int HALF_MAXN = 5;
+constexpr int HALF_STAGE = 3 * PRE_BLOCK;              // A high, A low (half a block each), B high, B low
+constexpr int HALF_NS = 4;
+typedef SplitRun<HALF_MAXN> HalfRun;
+
+__device__ __forceinline__ float half_mma_presplit(const HalfRun& p, unsigned char* __restrict__ lds, v16f (&acc)[2]) {
+    typedef __attribute__((address_space(3))) unsigned char lds_byte;
+    constexpr int NSL = 128 / SPLIT_KS;                // slices per product
+    const int t = threadIdx.x;
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1;
+    const int lm = lane & 31, h = lane >> 5;
+    lds_byte* l0 = (lds_byte*)lds;
+    const unsigned a_addr = (unsigned)split_plane_offset(wm * 32 + lm, h);
+    unsigned b_addr[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) b_addr[q] = (unsigned)(PRE_BLOCK + split_plane_offset(wn * 64 + q * 32 + lm, h));
+    // kilobytes 3 wave .. + 2 of a stage: 0, 1 A high, 2, 3 A low, 4 .. 7 B high, 8 .. 11 B low
+    const KFAC_AS1 unsigned char* src[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int kb = 3 * wave + j;
+        src[j] = (kb < 4 ? p.a_hi + (kb >> 1) * p.plane + (kb & 1) * 1024 : p.b_hi + (kb >= 8 ? p.plane : 0) + (kb & 3) * 1024) + lane * 16;
+    }
+    const int nst = p.n * NSL;
+    auto issue = [&](int s, int buf) {
+        const int sc = s < nst ? s : nst - 1;          // past the end: re-read the last slice (never consumed)
+        const int q = sc / NSL, ks = sc - q * NSL;
+        const int bq = p.first + q;                    // (first < nbuf, q < nbuf)
+        const size_t off = (size_t)(bq >= p.nbuf ? bq - p.nbuf : bq) * p.stride + ks * PRE_BLOCK;
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[j] + off),
+                                             (__attribute__((address_space(3))) void*)(l0 + buf * HALF_STAGE + (3 * wave + j) * 1024),
+                                             16, 0, 0);
+    };
+    float back = 1.0f;
+#pragma unroll
+    for (int s = 0; s < HALF_NS - 1; ++s) issue(s, s);
+    for (int it = 0; it < nst; it += HALF_NS) {
+#pragma unroll
+        for (int bi = 0; bi < HALF_NS; ++bi) {
+            const int s = it + bi;                                          // (nst is a multiple of HALF_NS)
+            static_assert(HALF_NS == 4 && NSL % HALF_NS == 0, "the wait below counts (HALF_NS - 2) * 3 younger copies");
+            asm volatile("s_waitcnt vmcnt(6)\n\ts_barrier" ::: "memory");   // slice s landed (everybody's part)
+            issue(s + HALF_NS - 1, (bi + HALF_NS - 1) % HALF_NS);            // refill the slot slice s - 1 vacated
+            if (s % NSL == 0) {                                              // uniform: a new product begins
+                float sq = p.scale[0];
+#pragma unroll
+                for (int q = 1; q < HALF_MAXN; ++q) sq = s / NSL == q ? p.scale[q] : sq;
+                const float f = sq * back;
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) acc[nb] *= f;
+                back = 1.0f / sq;
+            }
+            v4f a[2], b[2][2];                                               // (16 bytes = 8 fp16 each)
+            asm volatile("ds_read_b128 %0, %1" : "=v"(a[0]) : "v"(a_addr + bi * HALF_STAGE));
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(a[1]) : "v"(a_addr + bi * HALF_STAGE), "n"(PRE_BLOCK / 2));
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int pc = 0; pc < 2; ++pc)
+                    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(b[q][pc]) : "v"(b_addr[q] + bi * HALF_STAGE), "n"(pc * PRE_BLOCK));
+            asm volatile("s_waitcnt lgkmcnt(0)"
+                         : "+v"(a[0]), "+v"(a[1]), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]));
+            // smallest terms first
+#pragma unroll
+            for (int term = 0; term < 3; ++term)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) {
+                    v8h av, bv;
+                    __builtin_memcpy(&av, &a[term == 0 ? 1 : 0], 16);
+                    __builtin_memcpy(&bv, &b[nb][term == 1 ? 1 : 0], 16);
+                    acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv, acc[nb], 0, 0, 0);
+                }
         }
     }
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");            // ring idle: the LDS may be reused

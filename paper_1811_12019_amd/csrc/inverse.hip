@@ -12,16 +12,20 @@
 // advances together: one launch per stage per step for the whole batch (the workgroup -> (matrix, tile) map is a
 // prefix table passed in the kernel arguments).
 //
-// Launch structure.  Pivot -> panel -> update -> next pivot is a chain of dependent launches, 37 links long for a
-// 4609-wide factor, so the launches are arranged to keep the chain short and the bulk of the flops off it:
-//   * the update launch of step k gives the tile that is pivot block k + 1 to a workgroup of its own, which updates
-//     it, keeps it in registers and inverts it at once: a step is two launches (panel, update), and the pivot runs
-//     beside the tile updates (inv_begin_kernel only serves a matrix's first block and single-block matrices);
-//   * steps are taken in groups of GM; inside a group only the next panel's block column / row and the diagonal
-//     tiles of the blocks still to come are brought up to date, every other tile receives a whole group as one
-//     rank-(GM * 128) update during the next group's launches (see Plan below);
-//   * every matrix of a batch carries its own step number, so that matrices with fewer blocks spread their steps
-//     over the launches of the largest one.
+// Launch structure.  The elimination is a chain, 37 steps long for a 4609-wide factor, most of whose steps leave the chip nearly
+// idle, so a step is one launch and the bulk of the flops is moved off the chain.  The launch of step k starts from P_k and from
+// panel k (block column k, assembled: U_k), both left by the launch before, and has workgroups of three kinds:
+//   * the look-ahead pivot: the rank-128 update of the diagonal tile that is pivot block k + 1, with a T_(k+1) = U_(k+1) P_k of its
+//     own, kept in registers, and its inversion: P_(k+1);
+//   * slabs, half a slab (64 rows) each: T_I = U_I P_k and, from it, the next panel, U_I(k+1) = W_I(k+1) - ... - T_I U_(k+1)^T
+//     (U_(k+1) is part of panel k: nothing in the launch waits for another workgroup of it);
+//   * tiles of the rest of the matrix, which receive the updates of finished steps in one visit for a group of GM steps (Plan).
+// Every matrix of a batch carries its own stage, so that matrices with fewer blocks spread their launches over those of the
+// largest one.  The last step takes two launches: its panel beside the tiles that still owe updates, then the output.
+// Bound: one matrix alone by the look-ahead pivot's workgroup (its update 11.8 us, the sweep 15.3, write-out 1.9, from launch to
+// launch 2.5; half slabs are done after 13 to 25): 31.5 us a step, 40 when panel and tiles were launches of their own.  One matrix
+// alone, us: 145 columns 81 -> 64, 1000 328 -> 281, 2049 632 -> 565, 4609 1501 -> 1370; ten ragged ones (10 to 1153 columns) with
+// their preconditioning 557 -> 453.  Batches of wide matrices are bound by their tile visits.
 // Products: the panel on the bf16 matrix cores with operands split three ways; the updates on the fp16 matrix cores
 // from operands that the panel launch has already scaled per half slab (64 rows) and split two ways, stored as planes that
 // go to LDS by DMA (gemm_split.h); both to fp32 accuracy.
@@ -29,7 +33,7 @@
 // Storage.  The sweep works on a copy W of the matrix in the caller's workspace whose rows are padded to a
 // multiple of 32 floats, so that every 128-wide tile row is a run of whole 128-byte lines, and it keeps only the
 // lower triangle (tiles on or below the diagonal) up to date: the part of block column k that lies above the
-// pivot block is read, transposed, from block row k.  Only the last step writes the caller's dense output, both
+// pivot block is read, transposed, from block row k.  Only the last launch writes the caller's dense output, both
 // triangles, exactly symmetric (the upper one is a copy of the lower one).
 #include "gemm_split.h"
 
@@ -41,6 +45,8 @@ constexpr int CMAXB = 112;       // matrices per launch of the sweep's per-step 
 constexpr int UPD_WAVES = 3;     // wavefronts per SIMD the update kernel is compiled for (register budget)
 constexpr int SLD = 132;         // epilogue staging stride (floats) for row-wise float4 access
 constexpr int SLD_T = 129;       // epilogue staging stride when the stage is also read column-wise
+constexpr int PH = NB / 2;       // rows of a half slab
+constexpr int UPD_LDS_BYTES = 48 * 1024;   // of a workgroup of the sweep's launches: three of them on a CU
 
 // Everything a launch needs to know about its matrices travels in the kernel arguments (scalar loads, no dependent
 // memory round trip at the start of every workgroup).
@@ -64,7 +70,7 @@ struct ChainBatch {
     int count;
     int prefix[CMAXB + 1];
     int dim[CMAXB];
-    int step[CMAXB];                  // the elimination step this launch takes for the matrix, or -1: none
+    int stage[CMAXB];                 // the stage this launch takes for the matrix (plan_of), or -1: none
     float* Minv[CMAXB];
     void* ws[CMAXB];
     int32_t* info[CMAXB];
@@ -131,123 +137,115 @@ static inline __host__ __device__ size_t inverse_planes_bytes(int dim) {
 __device__ __forceinline__ float inverse_plane_scale(float damping) {
     return damping > 0.f ? ldexpf(1.0f, 8 + ilogbf(damping)) : 1.0f;
 }
-// Steps are taken in groups of up to GM consecutive blocks, none of them the matrix's last.  Inside a group only the
-// tiles that the group's remaining pivots and panels need are brought up to date; every other tile receives the group's
-// rank-128 updates together, in one visit during the next group's launches (plan_of), which cuts the traffic of the working copy
-// by the group size.  The arithmetic per tile is the same sequence of fp32 operations as step-by-step updating.
+// Steps are taken in groups of up to GM consecutive blocks, none of them the matrix's last.  Inside a group only what the chain
+// needs is brought up to date; every other tile receives the group's rank-128 updates together, in one visit during the next
+// group's launches, which cuts the traffic of the working copy by the group size.  The arithmetic per tile is the same sequence
+// of fp32 operations as step-by-step updating.
 constexpr int GM = 4;
 struct Group {
-    int g0;      // first step of the group that `step` belongs to
-    int m;       // its size (1 .. GM); 0: `step` is the matrix's last step, which is never part of a group
-    int j;       // step - g0
+    int g0;      // first step of a run of steps
+    int m;       // its size (1 .. GM)
+    int j;       // the last of them that a tile is to see, minus g0
 };
-static inline __host__ __device__ Group group_of(int dim, int step) {
-    const int n = nblk_of(dim);
-    Group g;
-    g.g0 = step / GM * GM;
-    g.j = step - g.g0;
-    g.m = min(GM, n - 1 - g.g0);
-    if (g.m < 0 || g.j >= g.m) g.m = 0;
-    return g;
-}
-// Tiles of the update launch of `step` = k, per matrix: "chain" tiles, which the next step needs at once, and "lag"
-// tiles.
-//   * Chain launch (every step but the two kinds below).  Inside a group, and from one group to the next, a tile is
-//     brought up to date only when the next step needs it:
-//       - the tiles of block column / row k + 1 (all of them but the diagonal one, which the look-ahead pivot workgroup
-//         takes): each sees, in one visit, every step it still owes, up to k -- at most the whole group before its own
-//         and its own group's steps so far (chain_tile);
-//       - the diagonal tiles of the blocks still to come in the group and of the first block after it, which are
-//         kept up to date step by step so that a look-ahead pivot never owes more than one product; in a group's last
-//         step these are the diagonal tiles of the next group's blocks and of the first block after those, which see
-//         the whole group.
-//     In a group's last step the off-diagonal tiles of the next group's other block columns / rows also see the whole
-//     group ("early" tiles: not needed by the next step, but their chain visits then owe only their own group's steps).
-//     Every other tile owes the group's steps: the rest of the matrix is dealt, as lag tiles, to the next group's
-//     chain launches (all but its last), where it runs beside the pivot workgroups that set those launches' duration.
-//   * Whole: the last step of a group that is not followed by a group of two or more steps; all tiles of the triangle
-//     are brought up to date.
-//   * Last: the matrix's last step, which writes the output.
-// The panels of two consecutive groups coexist in the NBUF buffers, so lag tiles read the previous group's.
+// What the launch of a stage does for a matrix of n blocks (n >= 2).  Stage k <= n - 2 is step k, of the group [g0, g0 + GM):
+//   * `slabs` half slabs (of pivot block k + 1's own only T).  Tile (I, k + 1) owes, in one visit, all steps from chain_from(k + 1) on.
+//     The slabs of block k + 2 also bring their diagonal tile, which is kept up to date through step k - 2, up to step k.
+//   * Diagonal tiles of the blocks the next pivots need are kept up to date one step behind, so that a look-ahead pivot never owes
+//     more than one product: in a group's first launch blocks g0 + 3 .. g0 + 6 receive the whole group before, in the others
+//     blocks k + 3 .. g0 + 6 step k - 1.
+//   * The bulk: every other tile without an index inside the group receives the whole group before, in the group's launches but its
+//     fourth (whose panel k + 1 takes the buffer of the first step of the group before).  The tiles of blocks g0 + 2 and g0 + 3
+//     come first, in the group's first launch ("early" tiles): the panels k + 1 of the group's second and third launch read them.
+//     (Block g0 + 1, whose panel the first launch forms, owes the group before and step g0: chain_from.)
+// Stage n - 1: the panel of the last step, beside the tiles of all other blocks, which receive what the last group owes them.
+// Stage n: the output.
 struct Plan {
-    Group g;
-    int kind;            // PLAN_CHAIN, PLAN_WHOLE, PLAN_LAST
-    int d_begin, d_end;  // chain: diagonal tiles of blocks d_begin .. d_end - 1
-    int chain;           // number of chain tiles
-    int lag;             // number of lag tiles in this launch
-    int lag_off;         // index of the first one in the lag list
-    int early;           // number of early tiles (a group's last step; no lag tiles then): see plan_of
-    int next_m;          // size of the next group (early tiles)
+    int kind;            // PLAN_STEP, PLAN_PANEL, PLAN_OUT
+    Group g;             // the run of steps that diagonal, early and lag tiles (PLAN_PANEL: all tiles) see
+    int slabs;           // workgroups of half slabs
+    int d_begin, diag;   // diagonal tiles, from block d_begin on
+    bool single;         // they see only the run's last step
+    int g0, w;           // the group's first block and how many blocks it takes out of the bulk
+    int early;           // number of early tiles of the group; early and lag tiles are one list, of which this launch takes
+    int off, bulk;       // `bulk` tiles from `off` on
+    int tiles;           // PLAN_PANEL, PLAN_OUT: tiles of the triangle
 };
-constexpr int PLAN_CHAIN = 0, PLAN_WHOLE = 2, PLAN_LAST = 3;
+constexpr int PLAN_STEP = 0, PLAN_PANEL = 1, PLAN_OUT = 2;
 
-static inline __host__ __device__ Plan plan_of(int dim, int step) {
+static inline __host__ __device__ Plan plan_of(int dim, int stage) {
     const int n = nblk_of(dim);
     Plan p;
-    p.g = group_of(dim, step);
-    p.lag = p.lag_off = 0;
-    p.early = p.next_m = 0;
-    p.d_begin = p.d_end = 0;
-    if (p.g.m == 0) { p.kind = PLAN_LAST; p.chain = n * (n + 1) / 2; return p; }
-    const int E = p.g.g0 + p.g.m;
-    if (p.g.j < p.g.m - 1) {
-        p.kind = PLAN_CHAIN;
-        p.d_begin = step + 2; p.d_end = E + 1;
-        p.chain = n - 1 + p.d_end - p.d_begin;
-        if (p.g.g0 > 0) {                                   // the previous group left its update of the bulk to this one
-            const int nc = n - p.g.m;                       // (the tiles with no index inside this group)
-            const int total = nc * (nc + 1) / 2, per = (total + p.g.m - 2) / (p.g.m - 1);
-            p.lag_off = p.g.j * per;
-            p.lag = max(0, min(per, total - p.lag_off));
-        }
+    p.slabs = p.d_begin = p.diag = p.g0 = p.w = p.early = p.off = p.bulk = p.tiles = 0;
+    p.single = false;
+    p.g.g0 = 0; p.g.m = 0; p.g.j = 0;
+    if (stage == n) {
+        p.kind = PLAN_OUT;
+        p.tiles = n * (n + 1) / 2;
         return p;
     }
-    const Group next = group_of(dim, E);
-    if (next.m >= 2) {
-        p.kind = PLAN_CHAIN;
-        p.d_begin = E + 1; p.d_end = E + next.m + 1;
-        p.chain = n - 1 + p.d_end - p.d_begin;
-        // Early tiles: the off-diagonal tiles of the next group's other block columns / rows c = E + 1 .. E + next.m - 1
-        // (row part J < E, column part I > c) receive this group's steps now, beside the chain tiles and off the chain,
-        // so that their own chain visits inside the next group owe only that group's steps (1 .. 3 products instead of
-        // 5 .. 7 on the chain's critical path).
-        p.next_m = next.m;
-        for (int c = E + 1; c < E + next.m; ++c) p.early += E + n - 1 - c;
+    p.slabs = stage == n - 1 ? 2 * (n - 1) : 2 * n;
+    if (stage == n - 1) {
+        p.kind = PLAN_PANEL;
+        p.g.g0 = (n - 2) / GM * GM;
+        p.g.m = n - 1 - p.g.g0;
+        p.g.j = p.g.m - 1;
+        p.tiles = n * (n - 1) / 2;
+        return p;
+    }
+    p.kind = PLAN_STEP;
+    const int k = stage, g0 = k / GM * GM, j = k - g0, m = min(GM, n - 1 - g0);
+    p.g0 = g0;
+    p.w = min(GM, n - g0);
+    if (j > 0) {
+        p.g.g0 = g0;
+        p.g.m = m;
+        p.g.j = j - 1;
+        p.single = true;
+        p.d_begin = k + 3;
     } else {
-        p.kind = PLAN_WHOLE;
-        p.chain = n * (n + 1) / 2;
+        p.g.g0 = g0 - GM;
+        p.g.m = GM;
+        p.g.j = GM - 1;
+        p.d_begin = g0 + 3;
+    }
+    if (k > 0) p.diag = max(0, min(g0 + 6, n - 1) - p.d_begin + 1);
+    if (g0 > 0) {
+        const int others = n - p.w, columns = max(0, p.w - 2);
+        p.early = columns * others + (columns == 2);
+        const int total = p.early + others * (others + 1) / 2, launches = min(m, GM - 1);
+        const int first = launches == 1 ? total : max(p.early, (total + launches - 1) / launches);
+        if (j == 0) {
+            p.bulk = first;
+        } else if (j < launches) {
+            const int per = (total - first + launches - 2) / (launches - 1);
+            p.off = first + (j - 1) * per;
+            p.bulk = max(0, min(per, total - p.off));
+        }
     }
     return p;
 }
-static inline __host__ __device__ int update_tiles(int dim, int step) {
-    const Plan p = plan_of(dim, step);
-    return p.chain + p.lag + p.early;
+static inline __host__ __device__ int plan_workgroups(const Plan& p) { return p.slabs + p.diag + p.bulk + p.tiles; }
+// The first step that the tiles of block column / row c owe when panel c is formed (by the launch of step c - 1): the working copy
+// holds them through the step before it.
+static inline __host__ __device__ int chain_from(int c) {
+    const int r = c % GM;
+    return max(0, r == 0 ? c - GM : r == 1 ? c - 1 - GM : c - r);
 }
-// Tile index of a chain list -> (I, J): block row c = step + 1 left of the diagonal, block column c below it, then
-// the diagonal tiles d_begin ..
-__device__ __forceinline__ void chain_decode(int n, int c, int d_begin, int t, int& I, int& J) {
-    if (t < c) { I = c; J = t; }
-    else if (t < n - 1) { I = t + 1; J = c; }
-    else { I = J = d_begin + (t - (n - 1)); }
-}
-// index in the early list of a launch (E: first block of the next group, nm its size) -> (I, J)
-__device__ __forceinline__ void early_decode(int n, int E, int nm, int t, int& I, int& J) {
-    for (int c = E + 1; c < E + nm; ++c) {
-        const int cnt = E + n - 1 - c;
-        if (t < cnt) {
-            if (t < E) { I = c; J = t; }
-            else { I = c + 1 + (t - E); J = c; }
-            return;
-        }
-        t -= cnt;
+// index in the list of early and lag tiles -> (I, J): tiles of blocks g0 + 2 and g0 + 3, then the triangle over the blocks outside
+// the group
+__host__ __device__ __forceinline__ void bulk_decode(int n, int g0, int w, int early, int t, int& I, int& J) {
+    const int others = n - w;
+    if (t >= early) {
+        tri_decode_blocked(others, t - early, I, J);
+        if (I >= g0) I += w;
+        if (J >= g0) J += w;
+        return;
     }
-    I = J = 0;                                           // (not reached)
-}
-// index in the lag list of a group [E, E + m) -> (I, J): the lower triangle over the blocks outside the group
-__device__ __forceinline__ void lag_decode(int n, int E, int m, int t, int& I, int& J) {
-    tri_decode_blocked(n - m, t, I, J);
-    if (I >= E) I += m;
-    if (J >= E) J += m;
+    const int ci = t / others;
+    if (ci >= w - 2) { I = g0 + 3; J = g0 + 2; return; }     // (the one tile of both)
+    const int c = g0 + 2 + ci, o = t - ci * others, x = o < g0 ? o : o + w;
+    I = max(c, x);
+    J = min(c, x);
 }
 
 // Panels of one step, kept in buffer (step % NBUF): the fp32 copy U of block column k as it was before the step (all
@@ -260,9 +258,10 @@ struct WsView {
     gfloat* buf0;   // NBUF panel buffers, `stride` floats each: U | T | -T high | -T low | U high | U low
     size_t stride;
     size_t plane;   // bytes of one piece plane (d_pad x NB fp16)
-    gfloat* P;      // NB x NB    : inverse of the pivot block
+    gfloat* P0;     // 2 x NB x NB : inverses of the pivot blocks of even and of odd steps
     gfloat* SC;     // 2 NBUF x 2 nblk: power-of-two scales of the half slabs (64 rows) of T and U of every buffer (gemm_split.h)
     int nblk;
+    __device__ __forceinline__ gfloat* P(int step) const { return P0 + (step & 1) * (NB * NB); }
     __device__ __forceinline__ gfloat* U(int q) const { return buf0 + q * stride; }
     __device__ __forceinline__ gfloat* T(int q) const { return buf0 + q * stride + plane / 2; }
     __device__ __forceinline__ KFAC_AS1 unsigned char* TH(int q) const { return (KFAC_AS1 unsigned char*)(buf0 + q * stride + plane); }
@@ -282,8 +281,8 @@ __device__ inline WsView ws_view(gfloat* ws, int dim) {
     v.buf0 = v.W + d_pad * v.ldw;
     v.stride = panel_buffer_floats(dim);                 // 2 fp32 panels + 4 fp16 planes = 4 d_pad NB floats
     v.plane = d_pad * NB * 2;
-    v.P = v.buf0 + NBUF * v.stride;
-    v.SC = v.P + (size_t)NB * NB;
+    v.P0 = v.buf0 + NBUF * v.stride;
+    v.SC = v.P0 + (size_t)2 * NB * NB;
     return v;
 }
 
@@ -292,14 +291,14 @@ __device__ inline WsView ws_view(gfloat* ws, int dim) {
 // block D lives in registers in MFMA accumulator layout (wavefronts 0, 2, 3: the 64 x 64 quadrants on and below the
 // diagonal, as whole 32 x 32 blocks); wavefront 1, whose quadrant lies above the diagonal, looks ahead: it inverts the next
 // 16 x 16 diagonal sub-block while the others update D.  Per sub-block j:
-//   1. T16 = U16 . P16 (all wavefronts; U16 = D's columns j, in LDS; the rows of the sub-block itself become -P16);
-//   2. wavefronts 0, 2, 3: D -= T16 . U16^T on the matrix cores, columns / rows j of D become T16, and the owners copy
-//      columns / rows j + 1 and diagonal sub-block j + 2 to LDS for the next round;
-//      wavefront 1: takes sub-block j + 1, which the round before left in LDS, through this round's update and inverts it.
+//   * wavefronts 0, 2, 3: T16 = U16 . P16 (U16 = D's columns j, in LDS; the rows of the sub-block itself become -P16); then
+//     D -= T16 . U16^T on the matrix cores, columns / rows j of D become T16, and the owners copy
+//     columns / rows j + 1 and diagonal sub-block j + 2 to LDS for the next round;
+//   * wavefront 1: takes sub-block j + 1, which the round before left in LDS, through this round's update, with a T16 of its own,
+//     and inverts it.
 // Padding with the identity makes ragged blocks (fewer than 128 rows) need no special cases.
-// One workgroup, bound by its chain of dependent steps.  Look-ahead, the row-broadcast elimination (invert16_wave) and
-// keeping the lower triangle alone took an update launch that a full block's sweep paces from 36.3 to 27.5 us (2049 wide,
-// one matrix alone).
+// One workgroup, bound by its chain of dependent steps: 1.75 us a sub-block, of which wavefront 2, with four 32 x 32 blocks to
+// update, takes 1.2 for them (v_mfma_f32_32x32x2_f32), and wavefront 1 takes 1.4 in all.
 constexpr int PSB = 16;          // sub-block
 constexpr int PLD = 20;          // LDS row stride of the 16-wide panels (float4 aligned)
 
@@ -338,15 +337,18 @@ __device__ __forceinline__ void invert16_step(float (&E)[4], int i, int g, float
 }
 
 // One wavefront: Ps = inverse of the symmetric positive definite 16 x 16 block whose element (i, 4 g + q) lane
-// (i = lane % 16, g = lane / 16) holds in E[q], lower triangle taken as the truth.  Returns the 1-based index of the first
-// non-positive pivot, or 0.  A step is about 30 instructions, none of them through LDS.
-__device__ __forceinline__ int invert16_wave(float (&E)[4], float* __restrict__ Ps) {
+// (i = lane % 16, g = lane / 16) holds in E[q], lower triangle taken as the truth; E becomes minus the inverse.  Returns the 1-based
+// index of the first non-positive pivot, or 0.  A step is about 30 instructions, none of them through LDS.  midway(): called
+// after a few steps.
+template <class F>
+__device__ __forceinline__ int invert16_wave(float (&E)[4], float* __restrict__ Ps, F&& midway) {
     const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
     float piv[16];
     *(v4f*)&Ps[i * PLD + 4 * g] = v4f{E[0], E[1], E[2], E[3]};
 #pragma unroll
     for (int q = 0; q < 4; ++q) E[q] = Ps[max(i, 4 * g + q) * PLD + min(i, 4 * g + q)];
     invert16_step<0>(E, i, g, piv);  invert16_step<1>(E, i, g, piv);  invert16_step<2>(E, i, g, piv);  invert16_step<3>(E, i, g, piv);
+    midway();
     invert16_step<4>(E, i, g, piv);  invert16_step<5>(E, i, g, piv);  invert16_step<6>(E, i, g, piv);  invert16_step<7>(E, i, g, piv);
     invert16_step<8>(E, i, g, piv);  invert16_step<9>(E, i, g, piv);  invert16_step<10>(E, i, g, piv); invert16_step<11>(E, i, g, piv);
     invert16_step<12>(E, i, g, piv); invert16_step<13>(E, i, g, piv); invert16_step<14>(E, i, g, piv); invert16_step<15>(E, i, g, piv);
@@ -368,23 +370,6 @@ static_assert(TRI_FLOATS <= PIV_LDS_FLOATS, "one buffer serves both uses");
 __device__ __forceinline__ int tri_at(int r, int c) { return ((r * (r + 1)) >> 1) + c; }          // r >= c
 __device__ __forceinline__ int tri_sym(int r, int c) { return r >= c ? tri_at(r, c) : tri_at(c, r); }
 
-// D (accumulator layout, all four quadrants) <- the symmetric block whose lower triangle is in tri, bordered by the
-// identity beyond nb.  Ends with a barrier: tri may be overwritten afterwards.
-__device__ __forceinline__ void pivot_fill(v16f (&acc)[2][2], const float* __restrict__ tri, int nb) {
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = acc_row(wm, mb, r, lane), col = acc_col(wn, nbk, lane);
-                if (!(row < nb && col < nb)) acc[mb][nbk][r] = row == col ? 1.f : 0.f;
-                else acc[mb][nbk][r] = tri[tri_sym(row, col)];
-            }
-    __syncthreads();
-}
-
 // identity beyond nb
 __device__ __forceinline__ void pivot_border(v16f (&acc)[2][2], int nb) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
@@ -399,34 +384,26 @@ __device__ __forceinline__ void pivot_border(v16f (&acc)[2][2], int nb) {
             }
 }
 
-// T16 = U16 . P16 for the 32 rows of this wavefront (v_mfma_f32_16x16x4_f32: lane l supplies A[l % 16][l / 16] and
-// B[l / 16][l % 16] and receives C[4 (l / 16) + i][l % 16], i < 4); the rows of sub-block jb itself become -P16.
+// T16 = U16 . P16 for row blocks rb0 .. rb0 + N - 1 (below 8): formed as its transpose P16 . U16^T with v_mfma_f32_16x16x4_f32 (lane l
+// supplies A[l % 16][l / 16] and B[l / 16][l % 16] and receives C[4 (l / 16) + i][l % 16], i < 4), the contraction index in the order
+// 4 (l / 16) + kk, so that operands and result are four neighbours of one row; the rows of sub-block jb itself become -P16.
+template <int N>
 __device__ __forceinline__ void sweep_panel(const float* __restrict__ Us, const float* __restrict__ Ps, float* __restrict__ Ts,
-                                            int lane, int wave, int jb) {
+                                            int lane, int rb0, int jb) {
     const int l16 = lane & 15, lq = lane >> 4;
-    float a[2][4], b[4];
+    const v4f p = *(const v4f*)&Ps[l16 * PLD + 4 * lq];
+    v4f u[N], c[N];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        b[kk] = Ps[(4 * kk + lq) * PLD + l16];
-#pragma unroll
-        for (int rbi = 0; rbi < 2; ++rbi) a[rbi][kk] = Us[((2 * wave + rbi) * PSB + l16) * PLD + 4 * kk + lq];
+    for (int e = 0; e < N; ++e) {
+        u[e] = *(const v4f*)&Us[((rb0 + e) * PSB + l16) * PLD + 4 * lq];
+        c[e] = v4f{0.f, 0.f, 0.f, 0.f};
     }
-    v4f c4[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-        for (int rbi = 0; rbi < 2; ++rbi) c4[rbi] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rbi][kk], b[kk], c4[rbi], 0, 0, 0);
+        for (int e = 0; e < N; ++e) c[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[kk], u[e][kk], c[e], 0, 0, 0);
 #pragma unroll
-    for (int rbi = 0; rbi < 2; ++rbi) {
-        const int rb = 2 * wave + rbi;
-        if (rb == jb) {                                        // (uniform)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) Ts[(rb * PSB + 4 * lq + i) * PLD + l16] = -Ps[(4 * lq + i) * PLD + l16];
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) Ts[(rb * PSB + 4 * lq + i) * PLD + l16] = c4[rbi][i];
-        }
-    }
+    for (int e = 0; e < N; ++e) *(v4f*)&Ts[((rb0 + e) * PSB + l16) * PLD + 4 * lq] = rb0 + e == jb ? -p : c[e];
 }
 
 // Between the phases of the sweep: everybody's LDS accesses are done.
@@ -483,33 +460,32 @@ __device__ __forceinline__ int pivot_sweep(v16f (&acc)[2][2], int nb, float* __r
     if (wave == 1) {
         const int lane = t & 63, l16 = lane & 15, lq = lane >> 4;
         sweep_barrier();                                       // the first U16 and the diagonal sub-blocks are there
-        int first_bad = 0;
+        float E[4];
         {
             const v4f c4 = *(const v4f*)&DG[lane * 4];
-            float E[4] = {c4[0], c4[1], c4[2], c4[3]};
-            first_bad = invert16_wave(E, lds + PIV_PS);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) E[i] = c4[i];
         }
+        int first_bad = invert16_wave(E, lds + PIV_PS, [] {});
         sweep_barrier();
 #pragma unroll 1
         for (int jb = 0; jb < nsb; ++jb) {
-            const float* Us = lds + PIV_US + (jb & 1) * (NB * PLD);
-            sweep_panel(Us, lds + PIV_PS + (jb & 1) * (PSB * PLD), Ts, lane, 1, jb);
-            sweep_barrier();
             const int n = jb + 1;
             if (n < nsb) {                                     // diagonal sub-block n -= T16 . U16^T, and its inverse
-                v4f c4 = *(const v4f*)&DG[(n & 1) * (PSB * PSB) + lane * 4];
-                float a[4], b[4];
+                // (E: minus the inverse of sub-block jb; T16 as in sweep_panel, for these 16 rows, stays in registers)
+                const v4f u = *(const v4f*)&lds[PIV_US + (jb & 1) * (NB * PLD) + (n * PSB + l16) * PLD + 4 * lq];
+                v4f c4 = *(const v4f*)&DG[(n & 1) * (PSB * PSB) + lane * 4], tt = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    a[i] = -Ts[(n * PSB + l16) * PLD + 4 * i + lq];
-                    b[i] = Us[(n * PSB + l16) * PLD + 4 * i + lq];
-                }
+                for (int kk = 0; kk < 4; ++kk) tt = __builtin_amdgcn_mfma_f32_16x16x4f32(E[kk], u[kk], tt, 0, 0, 0);
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) c4 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], b[kk], c4, 0, 0, 0);
+                for (int kk = 0; kk < 4; ++kk) c4 = __builtin_amdgcn_mfma_f32_16x16x4f32(tt[kk], u[kk], c4, 0, 0, 0);
                 // the accumulator layout holds (row 4 lq + i, column l16): by symmetry element (l16, 4 lq + i)
-                float E[4] = {c4[0], c4[1], c4[2], c4[3]};
-                const int f = invert16_wave(E, lds + PIV_PS + (n & 1) * (PSB * PLD));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) E[i] = c4[i];
+                const int f = invert16_wave(E, lds + PIV_PS + (n & 1) * (PSB * PLD), [] { sweep_barrier(); });
                 first_bad = f != 0 && first_bad == 0 ? n * PSB + f : first_bad;
+            } else {
+                sweep_barrier();
             }
             if (jb + 1 == nsb && lane == 0) *bad = first_bad;
             sweep_barrier();
@@ -529,7 +505,10 @@ __device__ __forceinline__ int pivot_sweep(v16f (&acc)[2][2], int nb, float* __r
             asm volatile("" : "+v"(lane));
             const int lm = lane & 31, h = lane >> 5;
             const float* Us = lds + PIV_US + (jb & 1) * (NB * PLD);
-            sweep_panel(Us, lds + PIV_PS + (jb & 1) * (PSB * PLD), Ts, lane, wave, jb);
+            const float* Ps = lds + PIV_PS + (jb & 1) * (PSB * PLD);
+            if (wave == 0) sweep_panel<3>(Us, Ps, Ts, lane, 0, jb);
+            else if (wave == 2) sweep_panel<2>(Us, Ps, Ts, lane, 3, jb);     // (has a block more in the update)
+            else sweep_panel<3>(Us, Ps, Ts, lane, 5, jb);
             sweep_barrier();
             // D -= T16 . U16^T  (lane (lm, h) takes k = 8s + 4h .. +3 of both operands), then the fix-ups
 #pragma unroll
@@ -592,6 +571,7 @@ __device__ __forceinline__ void pivot_write(const v16f (&acc)[2][2], float* __re
                                             const WsView& ws, int k0, int nb, bool last, bool from_S) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
     const int d = it.dim;
+    gfloat* P = ws.P(k0 / NB);
     if (!last && !from_S && nb == NB) {
         // A full block inside the sweep (the look-ahead pivot's usual case) goes out as it lies in the registers: a half-wave's
         // 32 lanes hold 32 consecutive floats of a row, and four registers four consecutive floats of the mirror image's.
@@ -606,13 +586,13 @@ __device__ __forceinline__ void pivot_write(const v16f (&acc)[2][2], float* __re
                     const int row = acc_row(wm, mb, r, lane), col = acc_col(wn, nbk, lane);
                     const float x = acc[mb][nbk][r];
                     ws.W[(size_t)(k0 + row) * ws.ldw + k0 + col] = x;
-                    ws.P[row * NB + col] = -x;
+                    P[row * NB + col] = -x;
                 }
                 if (wm == wn && nbk == mb) continue;           // a block on the diagonal is its own mirror image
 #pragma unroll
                 for (int r = 0; r < 16; r += 4) {
                     const v4f x = {-acc[mb][nbk][r], -acc[mb][nbk][r + 1], -acc[mb][nbk][r + 2], -acc[mb][nbk][r + 3]};
-                    *(KFAC_AS1 v4f*)&ws.P[acc_col(wn, nbk, lane) * NB + acc_row(wm, mb, r, lane)] = x;
+                    *(KFAC_AS1 v4f*)&P[acc_col(wn, nbk, lane) * NB + acc_row(wm, mb, r, lane)] = x;
                 }
             }
         return;
@@ -644,7 +624,7 @@ __device__ __forceinline__ void pivot_write(const v16f (&acc)[2][2], float* __re
         } else {
             *(KFAC_AS1 v4f*)&ws.W[(size_t)(k0 + row) * ws.ldw + k0 + c4] = x;      // a block that is not last is full
         }
-        if (!from_S) *(KFAC_AS1 v4f*)&ws.P[row * NB + c4] = -x;    // (columns beyond a ragged block are never read)
+        if (!from_S) *(KFAC_AS1 v4f*)&P[row * NB + c4] = -x;    // (columns beyond a ragged block are never read)
     }
 }
 
@@ -654,36 +634,27 @@ __device__ __forceinline__ void begin_pivot(const Item& it, float* __restrict__ 
     const bool single = d <= NB;
     const int t = threadIdx.x;
     const WsView ws = ws_view(it.ws, d);
-    // lower triangle, row-wise.  All loads are issued before the first LDS store so that the block costs one memory round
-    // trip, not one per row group
-    const int c4 = (t & 31) * 4, r0 = t >> 5;            // 8 rows x 32 float4 per pass, 16 passes
-    v4f v[16];
-    if (nb == NB) {
-#pragma unroll
-        for (int p = 0; p < 16; ++p) v[p] = *(const KFAC_AS1 v4f_a4*)(it.S + (size_t)(r0 + 8 * p) * d + c4);
-    } else {
-#pragma unroll
-        for (int p = 0; p < 16; ++p) {
-            const int row = r0 + 8 * p;
-            v[p] = v4f{0.f, 0.f, 0.f, 0.f};
-            if (row < nb && c4 <= row) {
-                const gfloat* src = it.S + (size_t)row * d + c4;
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (c4 + i <= row) v[p][i] = src[i];
-            }
-        }
-    }
-#pragma unroll
-    for (int p = 0; p < 16; ++p) {
-        const int row = r0 + 8 * p;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (row < nb && c4 + i <= row) lds[tri_at(row, c4 + i)] = v[p][i] + (c4 + i == row ? it.damping : 0.f);
-    }
-    __syncthreads();
+    // straight into the accumulators, of the lower triangle (wavefront 1's quadrant lies above it); indices clamped, not guarded, so
+    // that all loads go out together
     v16f acc[2][2];
-    pivot_fill(acc, lds, nb);
+    const int lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+    if (wave != 1) {
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int nbk = 0; nbk < 2; ++nbk)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = min(acc_row(wm, mb, r, lane), nb - 1), col = min(acc_col(wn, nbk, lane), nb - 1);
+                    acc[mb][nbk][r] = it.S[(size_t)max(row, col) * d + min(row, col)];
+                }
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (wm == wn && acc_row(wm, mb, r, lane) == acc_col(wn, mb, lane)) acc[mb][mb][r] += it.damping;
+    }
+    if (nb < NB) pivot_border(acc, nb);
     const int f = pivot_sweep(acc, nb, lds);
     if (t == 0 && it.info) *it.info = f;                 // (later pivots: upd_next_pivot)
     pivot_write(acc, lds, it, ws, 0, nb, single, single);
@@ -710,12 +681,57 @@ __device__ __forceinline__ void begin_tile(const Item& it, int I, int J, int qua
     }
 }
 
-__device__ __forceinline__ void begin_tile_of(const Batch& b, int wg) {
+// Half a slab (64 rows) of panel `step`: the scale and the fp16 pieces of U that the tile products read, and U itself.  v[p]: columns
+// c4 .. c4 + 3 of row rr + 8 p, c4 = 4 (t % 32), rr = t / 32.
+__device__ __forceinline__ void put_panel(const WsView& ws, int step, int slab, int half, const v4f (&v)[8], float* __restrict__ red) {
+    const int t = threadIdx.x, c4 = (t & 31) * 4, rr = t >> 5, q = step % NBUF;
+    gfloat* __restrict__ Uc = ws.U(q) + (size_t)(slab * NB + half * PH) * NB;
+    float um = 0.f;
+#pragma unroll
+    for (int p = 0; p < 8; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) um = fmaxf(um, fabsf(v[p][i]));
+    um = block_absmax(um, red);
+    const float su = panel_scale(um);
+    if (t == 0) ws.scaleU(q, 2 * slab + half) = su;
+    KFAC_AS1 unsigned char* uh = ws.UH(q) + (size_t)slab * PRE_SLAB;
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+        *(KFAC_AS1 v4f*)&Uc[(size_t)(rr + 8 * p) * NB + c4] = v[p];
+        store_split4_h2(uh, uh + ws.plane, half * PH + rr + 8 * p, c4, v[p] * su);
+    }
+}
+
+// Panel 0, straight from the factor.
+__device__ __forceinline__ void begin_panel(const Item& it, int slab, int half, float* __restrict__ red) {
+    const int d = it.dim, t = threadIdx.x, c4 = (t & 31) * 4, r0 = slab * NB + half * PH + (t >> 5);
+    v4f v[8];
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {                        // (rows clamped, not guarded: all loads go out together)
+        const int row = r0 + 8 * p;
+        v[p] = *(const KFAC_AS1 v4f_a4*)(it.S + (size_t)min(row, d - 1) * d + c4);
+    }
+#pragma unroll
+    for (int p = 0; p < 8; ++p)
+        if (r0 + 8 * p >= d) v[p] = v4f{0.f, 0.f, 0.f, 0.f};
+    put_panel(ws_view(it.ws, d), 0, slab, half, v, red);
+}
+
+// The working copy's workgroups of a matrix of n blocks: the half slabs of panel 0, then the quarter tiles of the rest.
+static inline __host__ __device__ int begin_workgroups(int n) { return 2 * (n - 1) + 4 * (n * (n - 1) / 2); }
+__device__ __forceinline__ void begin_tile_of(const Batch& b, int wg, float* __restrict__ red) {
     int m, local;
     locate(b, wg, m, local);
+    const Item it = get_item(b, m);
+    const int panel = 2 * (nblk_of(it.dim) - 1);
+    if (local < panel) {
+        begin_panel(it, 1 + (local >> 1), local & 1, red);
+        return;
+    }
+    local -= panel;
     int I, J;
-    tri_decode(1 + (local >> 2), I, J);
-    begin_tile(get_item(b, m), I, J, local & 3);
+    tri_decode(local >> 2, I, J);
+    begin_tile(it, I + 1, J + 1, local & 3);
 }
 
 // Start of every matrix of the batch: its first pivot block and, in the workgroups after the pivots', the damped working copy
@@ -728,154 +744,17 @@ __global__ __launch_bounds__(256) void inv_begin_kernel(Batch b) {
         begin_pivot(get_item(b, blockIdx.x), lds);
         return;
     }
-    begin_tile_of(b, blockIdx.x - b.count);
+    begin_tile_of(b, blockIdx.x - b.count, lds);
 }
 
 // The working copies alone, for batches whose copies do not fit the chip beside the pivots: these workgroups need a tenth of
 // the pivot's registers and no LDS, and find room between those of other streams (a network's step at batch 32, whose
 // factor builds run beside: 5.87 ms, with the copies in the pivots' launch 6.07 ms).
-__global__ __launch_bounds__(256) void inv_init_kernel(Batch b) { begin_tile_of(b, blockIdx.x); }
-constexpr int BEGIN_TOGETHER = 768;      // quarter tiles: three workgroups to a CU
-
-// T = U . P for every 128-row slab of block column k; U is copied aside for the update.  Slabs below the pivot
-// block read the column block itself; slabs above it read block row k transposed.
-// Full pivot block (every step but a matrix's last): a workgroup takes half a slab (64 rows): twice the CUs for a link of the
-// chain that leaves most of them idle, and half the time in every phase.  The half slab is first copied to U (through an LDS
-// transpose for the slabs above the pivot), and the product then runs on the bf16 matrix cores with both operands split
-// three ways (panel_product).  The loads of P go out with those of the slab, which hides their latency.
-// Ragged pivot block: one workgroup per slab, fp32 matrix cores, operands guarded.
-// At 37 KB of LDS a panel workgroup fits into the room one finished update (or factor) workgroup leaves on a CU; with a full
-// 128-row stage (66 KB) it had to wait until two of them had finished on the same CU.
-// Alone, 2049 wide: 16.2 us a launch with 128-row workgroups that split U in LDS, 11.5 us now.
-constexpr int PH = NB / 2;                 // rows of a workgroup
-constexpr int PANEL_TLD = NB + 1;          // LDS row stride of the transpose stage
-constexpr int PANEL_RLD = NB + 4;          // LDS row stride when the stage is read back four columns at a time
-constexpr int PANEL_LDS_FLOATS = GEMM_LDS_FLOATS;
-static_assert(PANEL_LDS_FLOATS * 4 >= PANEL_B_LDS && PANEL_LDS_FLOATS >= PH * PANEL_RLD, "one buffer serves all uses");
-
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void inv_panel_kernel(ChainBatch b) {
-    __shared__ __attribute__((aligned(16))) float lds[PANEL_LDS_FLOATS];
+__global__ __launch_bounds__(256) void inv_init_kernel(Batch b) {
     __shared__ float red[4];
-    __builtin_amdgcn_s_setprio(3);                       // a link of the chain: ahead of whatever shares its SIMDs
-    int m, wg;
-    locate(b, blockIdx.x, m, wg);
-    const Item it = get_item(b, m);
-    const int d = it.dim;
-    const int step = b.step[m];
-    const int slab = wg >> 1, half = wg & 1;
-    const int k0 = step * NB;
-    const int nb = min(NB, d - k0);
-    if (slab == step) return;                 // the pivot block's own rows are not needed
-    const WsView ws = ws_view(it.ws, d);
-    const int q = step % NBUF;
-    const int t = threadIdx.x;
-    const int lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
-    if (nb == NB) {
-        const int r0 = slab * NB + half * PH;
-        const int rows = max(0, min(PH, d - r0));            // (rows past the end: zeros)
-        gfloat* __restrict__ Uc = ws.U(q) + (size_t)r0 * NB;
-        gfloat* __restrict__ Tc = ws.T(q) + (size_t)r0 * NB;
-        const int c4 = (t & 31) * 4, rr = t >> 5;            // 8 rows x 32 float4 per pass, 8 passes
-        const int tc4 = (t & 15) * 4, tk = t >> 4;           // transposed: 16 rows of W x 16 float4 per pass, 8 passes
-        v4f v[8], pb[16];
-        if (slab > step) {
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int row = rr + 8 * p;
-                v4f x = {0.f, 0.f, 0.f, 0.f};
-                if (row < rows) x = *(const KFAC_AS1 v4f*)&ws.W[(size_t)(r0 + row) * ws.ldw + k0 + c4];
-                v[p] = x;
-            }
-        } else {
-            // element (a, k) of the slab is W[k0 + k][r0 + a]; a slab above the pivot has all its 128 rows
-#pragma unroll
-            for (int p = 0; p < 8; ++p) v[p] = *(const KFAC_AS1 v4f*)&ws.W[(size_t)(k0 + tk + 16 * p) * ws.ldw + r0 + tc4];
-        }
-        panel_fetch_b(ws.P, pb);
-        if (slab > step) {
-#pragma unroll
-            for (int p = 0; p < 8; ++p) *(KFAC_AS1 v4f*)&Uc[(size_t)(rr + 8 * p) * NB + c4] = v[p];
-        }
-        float um = 0.f;                        // the half slab's scale for the update's fp16 pieces
-#pragma unroll
-        for (int p = 0; p < 8; ++p)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) um = fmaxf(um, fabsf(v[p][i]));
-        um = block_absmax(um, red);
-        const float su = panel_scale(um);
-        if (t == 0) ws.scaleU(q, wg) = su;
-        // the copy (slabs above the pivot) and the half slab's scaled fp16 pieces
-        KFAC_AS1 unsigned char* uh = ws.UH(q) + (size_t)slab * PRE_SLAB;
-        if (slab > step) {
-#pragma unroll
-            for (int p = 0; p < 8; ++p) store_split4_h2(uh, uh + ws.plane, half * PH + rr + 8 * p, c4, v[p] * su);
-        } else {
-#pragma unroll
-            for (int p = 0; p < 8; ++p)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) lds[(tc4 + i) * PANEL_TLD + tk + 16 * p] = v[p][i];
-            __syncthreads();
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int a = rr + 8 * p;
-                const float* src = &lds[a * PANEL_TLD + c4];
-                const v4f x = {src[0], src[1], src[2], src[3]};
-                *(KFAC_AS1 v4f*)&Uc[(size_t)a * NB + c4] = x;
-                store_split4_h2(uh, uh + ws.plane, half * PH + a, c4, x * su);
-            }
-        }
-        __threadfence_block();
-        __syncthreads();                       // the copy is visible to the whole workgroup; the LDS stage is free
-        v16f acc[2];
-        panel_product(Uc, pb, (unsigned char*)lds, acc);
-        // T leaves through LDS, row-wise: the fp32 panel in 16-byte stores and its scaled, negated fp16 pieces
-        float tm = 0.f;
-#pragma unroll
-        for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) tm = fmaxf(tm, fabsf(acc[nbk][r]));
-        tm = block_absmax(tm, red);                       // (its barriers also separate the product's LDS use from this one)
-        const float st = panel_scale(tm);
-        if (t == 0) ws.scaleT(q, wg) = st;
-        KFAC_AS1 unsigned char* th = ws.TH(q) + (size_t)slab * PRE_SLAB;
-#pragma unroll
-        for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                lds[(wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * PANEL_RLD + wn * 64 + nbk * 32 + (lane & 31)] = acc[nbk][r];
-        __syncthreads();
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int row = rr + 8 * p;
-            const v4f x = *(const v4f*)&lds[row * PANEL_RLD + c4];
-            if (row < rows) *(KFAC_AS1 v4f*)&Tc[(size_t)row * NB + c4] = x;
-            store_split4_h2(th, th + ws.plane, half * PH + row, c4, x * -st);
-        }
-        return;
-    }
-    if (half == 1) return;
-    const int r0 = slab * NB;
-    const int rows = min(NB, d - r0);
-    gfloat* __restrict__ Uc = ws.U(q) + (size_t)r0 * NB;
-    gfloat* __restrict__ Tc = ws.T(q) + (size_t)r0 * NB;
-    TileAcc acc;
-    if (slab > step) tile_mma_nt<false>(ws.W + (size_t)r0 * ws.ldw + k0, ws.ldw, rows, ws.P, NB, nb, nb, lds, acc, Uc, NB);
-    else tile_mma_nt<true>(ws.W + (size_t)k0 * ws.ldw + r0, ws.ldw, rows, ws.P, NB, nb, nb, lds, acc, Uc, NB);
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                int row = acc_row(wm, mb, r, lane), col = acc_col(wn, nbk, lane);
-                if (row < rows) Tc[(size_t)row * NB + col] = col < nb ? acc.c[mb][nbk][r] : 0.f;
-            }
-    // the update streams whole 16-float slabs of T and U: keep the columns beyond a ragged block at zero
-    for (int e = t; e < rows * NB; e += 256) {
-        const int row = e >> 7, col = e & (NB - 1);
-        if (col >= nb) Uc[(size_t)row * NB + col] = 0.f;
-    }
+    begin_tile_of(b, blockIdx.x, red);
 }
+constexpr int BEGIN_TOGETHER = 768;      // three workgroups to a CU
 
 // One tile (I >= J) of one elimination step.  Tile kinds:
 //   regular      new = old - T_I U_J^T
@@ -891,11 +770,22 @@ struct UpdCtx {
     bool diag;
 };
 
+// Elements from .. n - 1 of four neighbours, any alignment of floats.
+__device__ __forceinline__ void put4(gfloat* dst, const v4f& x, int from, int n) {
+    if (from <= 0 && n >= 4) {
+        *(KFAC_AS1 v4f_a4*)dst = x;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i >= from && i < n) dst[i] = x[i];
+    }
+}
+
 // stage (64 x sld floats) holds rows h0..h0+63 of the tile's new values (or of the product, for regular tiles
 // when COMBINE: new = old - stage, old prefetched in oldv).
 template <bool LAST, bool COMBINE>
 __device__ __forceinline__ void upd_flush(const UpdCtx& c, float* __restrict__ stage, int h0, const v4f (&oldv)[8]) {
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int t = threadIdx.x;
     const int pr = t >> 5, pc = (t & 31) * 4;
     constexpr int sld = LAST ? SLD_T : SLD;
     if constexpr (!LAST) {
@@ -909,34 +799,26 @@ __device__ __forceinline__ void upd_flush(const UpdCtx& c, float* __restrict__ s
             }
         }
     } else {
-        // final values (sign flipped) back into the stage, then out: rows of the tile and rows of its mirror
+        // final values (sign flipped) out along the tile's rows and back into the stage, then out along its mirror image's
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
-            const int rl = pr + 8 * p;
+            const int rl = pr + 8 * p, row = h0 + rl;
+            v4f x;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float x = stage[rl * sld + pc + i];
-                stage[rl * sld + pc + i] = COMBINE ? x - oldv[p][i] : -x;
+                const float s = stage[rl * sld + pc + i];
+                x[i] = COMBINE ? s - oldv[p][i] : -s;
+                stage[rl * sld + pc + i] = x[i];
             }
+            if (row < c.irows) put4(c.out + (size_t)(c.i0 + row) * c.d + c.j0 + pc, x, 0, min(c.jrows - pc, c.diag ? row - pc + 1 : 4));
         }
         __syncthreads();
-        // direct: wavefront w writes tile rows h0 + 16w .. +15, two 64-float runs per row
-        for (int rr = 0; rr < 16; ++rr) {
-            const int rl = wave * 16 + rr, row = h0 + rl;
-            if (row >= c.irows) break;
+        const int mr = (t & 15) * 4, mc = t >> 4;         // four tile rows (neighbours in the mirror image), 16 columns a pass
 #pragma unroll
-            for (int cc = 0; cc < 2; ++cc) {
-                const int col = cc * 64 + lane;
-                if (col < c.jrows && !(c.diag && col > row))
-                    c.out[(size_t)(c.i0 + row) * c.d + c.j0 + col] = stage[rl * sld + col];
-            }
-        }
-        // mirror: wavefront w writes output rows j0 + 32w .. +31, one 64-float run (tile rows h0..h0+63) each
-        for (int cc = 0; cc < 32; ++cc) {
-            const int col = wave * 32 + cc, row = h0 + lane;
-            if (col >= c.jrows) break;
-            if (row < c.irows && !(c.diag && col >= row))
-                c.out[(size_t)(c.j0 + col) * c.d + c.i0 + row] = stage[lane * sld + col];
+        for (int p = 0; p < 8; ++p) {
+            const int col = mc + 16 * p, row = h0 + mr;
+            const v4f x = {stage[mr * sld + col], stage[(mr + 1) * sld + col], stage[(mr + 2) * sld + col], stage[(mr + 3) * sld + col]};
+            if (col < c.jrows) put4(c.out + (size_t)(c.j0 + col) * c.d + c.i0 + row, x, c.diag ? col - row + 1 : 0, c.irows - row);
         }
     }
 }
@@ -950,8 +832,8 @@ constexpr int UK = 16;                    // K-slab
 constexpr int UNS = 3;                    // ring stages
 constexpr int UPANEL = 8 * 1024;          // bytes per operand panel per stage
 constexpr int USTAGE = 2 * UPANEL;
-static_assert(UNS * USTAGE <= GEMM_LDS_FLOATS * 4 + 12288, "ring must fit the kernel's LDS");
-static_assert(UNS * USTAGE >= PRE_NS * PRE_STAGE, "the tile products' ring shares the kernel's LDS");
+static_assert(UNS * USTAGE <= UPD_LDS_BYTES && PRE_NS * PRE_STAGE <= UPD_LDS_BYTES && HALF_NS * HALF_STAGE <= UPD_LDS_BYTES &&
+              GEMM_LDS_FLOATS * 4 <= UPD_LDS_BYTES && PIV_LDS_FLOATS * 4 <= UPD_LDS_BYTES, "all uses share the kernel's LDS");
 
 #define KFAC_LDS_READ128(dst, addr, off) \
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off))
@@ -1087,8 +969,7 @@ struct OldSrc {
 // half slab and split two ways (gemm_split.h): the accumulators start as the tile's old values (fetched straight into MFMA register layout:
 // register r of a 32 x 32 block is 32 consecutive floats of one row per half-wave), the negated products are added,
 // and the result is stored from the registers: nothing is staged in LDS.
-// STORE = false: the new values stay in acc (valid where the tile has rows and columns;
-// the quadrant above the diagonal of a diagonal tile is not computed) and nothing is written.
+// The quadrant above the diagonal of a diagonal tile is not computed.
 constexpr int MAXRUN = GM;               // a tile owes at most one whole group (the group before, or its own so far)
 typedef SplitRun<MAXRUN> PanelRun;
 
@@ -1113,9 +994,9 @@ __device__ __forceinline__ PanelRun panel_run(const WsView& ws, int first_step, 
     return r;
 }
 
-template <bool STORE = true>
 __device__ __forceinline__ void upd_regular_mid_split(const UpdCtx& c, const OldSrc& o, const PanelRun& pl,
-                                                      unsigned char* __restrict__ lds, TileAcc& acc) {
+                                                      unsigned char* __restrict__ lds) {
+    TileAcc acc;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
     const int lm = lane & 31, h = lane >> 5;
     const bool dead = c.diag && wm == 0 && wn == 1;      // strictly above the diagonal, never used
@@ -1156,54 +1037,426 @@ __device__ __forceinline__ void upd_regular_mid_split(const UpdCtx& c, const Old
     for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
         for (int nbk = 0; nbk < 2; ++nbk) acc.c[mb][nbk] *= back;
-    if constexpr (STORE) {
-        if (whole) {
+    if (whole) {
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int nbk = 0; nbk < 2; ++nbk)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    wq[nbk][(size_t)(mb * 32 + (r >> 2) * 8 + (r & 3)) * c.ldw] = acc.c[mb][nbk][r];
+    } else {
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int nbk = 0; nbk < 2; ++nbk)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int dr = mb * 32 + (r >> 2) * 8 + (r & 3);
+                    if (colok[nbk] && dr < rows_left) wq[nbk][(size_t)dr * c.ldw] = acc.c[mb][nbk][r];
+                }
+    }
+}
+
+// T = U . P for half a slab (64 rows): the fp32 panel and the scaled, negated fp16 pieces that the tile products read, with their
+// scale (returned).  Half slabs: twice the workgroups for a link of the chain that leaves most CUs idle, and half the time in every
+// phase.  The product runs on the bf16 matrix cores with both operands split three ways (panel_product).  pb: P's values
+// (panel_fetch_b).  Ends with the LDS free and T's stores on their way.
+constexpr int PANEL_RLD = NB + 4;          // LDS row stride of the stage, read back four columns at a time
+static_assert(UPD_LDS_BYTES >= PANEL_B_LDS && UPD_LDS_BYTES >= PH * PANEL_RLD * 4, "one buffer serves all uses");
+
+// (accumulators of a 64 x 128 half slab: wavefront (wm, wn) holds rows 32 wm .. of columns 64 wn .., as two MFMA blocks)
+__device__ __forceinline__ int half_row(int wm, int r, int lane) { return wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3); }
+
+__device__ __forceinline__ void half_stage(const v16f (&acc)[2], float* __restrict__ lds) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+#pragma unroll
+    for (int nbk = 0; nbk < 2; ++nbk)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) lds[half_row(wm, r, lane) * PANEL_RLD + acc_col(wn, nbk, lane)] = acc[nbk][r];
+}
+
+__device__ __forceinline__ float slab_T(const WsView& ws, int d, int step, int slab, int half, const v4f (&pb)[8][2], float* __restrict__ lds,
+                                        float* __restrict__ red) {
+    const int t = threadIdx.x, q = step % NBUF, r0 = slab * NB + half * PH;
+    const int c4 = (t & 31) * 4, rr = t >> 5;
+    v16f acc[2];
+    panel_product(ws.U(q) + (size_t)r0 * NB, pb, (unsigned char*)lds, acc);
+    float tm = 0.f;
+#pragma unroll
+    for (int nbk = 0; nbk < 2; ++nbk)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) tm = fmaxf(tm, fabsf(acc[nbk][r]));
+    tm = block_absmax(tm, red);                          // (its barriers also separate the product's LDS use from this one)
+    const float st = panel_scale(tm);
+    if (t == 0) ws.scaleT(q, 2 * slab + half) = st;
+    half_stage(acc, lds);
+    __syncthreads();
+    gfloat* __restrict__ Tc = ws.T(q) + (size_t)r0 * NB;
+    KFAC_AS1 unsigned char* th = ws.TH(q) + (size_t)slab * PRE_SLAB;
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+        const int row = rr + 8 * p;
+        const v4f x = *(const v4f*)&lds[row * PANEL_RLD + c4];
+        if (r0 + row < d) *(KFAC_AS1 v4f*)&Tc[(size_t)row * NB + c4] = x;
+        store_split4_h2(th, th + ws.plane, half * PH + row, c4, x * -st);
+    }
+    __threadfence_block();
+    __syncthreads();                                     // T is visible to the workgroup; the stage is free
+    return st;
+}
+
+// The operands of half slab (I, half) times slab J for the n consecutive steps first .. first + n - 1, the last of them `step`, whose
+// T this workgroup has just formed (st: its scale).
+__device__ __forceinline__ HalfRun half_run(const WsView& ws, int first, int step, int I, int half, int J, float st) {
+    const int wn = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) & 1;
+    HalfRun r;
+    r.a_hi = ws.TH(0) + (size_t)I * PRE_SLAB + half * (PRE_BLOCK / 2);
+    r.b_hi = ws.UH(0) + (size_t)J * PRE_SLAB;
+    r.plane = ws.plane;
+    r.stride = ws.stride * sizeof(float);
+    r.first = first % NBUF;
+    r.nbuf = NBUF;
+    r.n = step - first + 1;
+#pragma unroll
+    for (int q = 0; q < HALF_MAXN; ++q) {
+        const int b = (first + q) % NBUF;
+        r.scale[q] = first + q < step ? ws.scaleT(b, 2 * I + half) * ws.scaleU(b, 2 * J + wn) : st * ws.scaleU(b, 2 * J + wn);
+    }
+    return r;
+}
+
+// One half slab of step k: T, then the half slab of panel k + 1 (and, for the block after that, half of its diagonal tile).
+__device__ __forceinline__ void step_slab(const Item& it, int k, int I, int half, float* __restrict__ lds, float* __restrict__ red) {
+    const int d = it.dim, c1 = k + 1;
+    const WsView ws = ws_view(it.ws, d);
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+    const int lm = lane & 31, h = lane >> 5;
+    v4f pb[8][2];
+    v16f acc[2];
+    if (I == k) {
+        // block row k + 1 left of the diagonal, in block column k: T_(k+1) transposed = P U_(k+1)^T
+        panel_fetch_b(ws.U(k % NBUF) + (size_t)c1 * NB * NB, pb);
+        panel_product(ws.P(k) + half * PH * NB, pb, (unsigned char*)lds, acc);
+        __syncthreads();
+    } else {
+        panel_fetch_b(ws.P(k), pb);
+        const float st = slab_T(ws, d, k, I, half, pb, lds, red);
+        if (I == c1) return;                             // (the tile itself is the look-ahead pivot's)
+        // Old values of tile (I, k + 1) in the accumulators' order.  Left of the diagonal the tile is stored as (k + 1, I); a block
+        // that was eliminated since the working copy was last up to date left it in that step's T.
+        int first = chain_from(c1);
+        const int row0 = half * PH + wm * 32 + 4 * h;    // this lane's first row, inside the slab
+        if (I > c1) {
+            const gfloat* src = ws.W + (size_t)(I * NB + row0) * ws.ldw + c1 * NB + wn * 64 + lm;
+            const int left = d - I * NB - row0;
+#pragma unroll
+            for (int nbk = 0; nbk < 2; ++nbk) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {           // (rows clamped, not guarded: all loads go out together)
+                    const int dr = (r >> 2) * 8 + (r & 3);
+                    acc[nbk][r] = src[(ptrdiff_t)min(dr, left - 1) * ws.ldw + nbk * 32];
+                }
+            }
+            if (left < 32) {
 #pragma unroll
                 for (int nbk = 0; nbk < 2; ++nbk)
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
-                        wq[nbk][(size_t)(mb * 32 + (r >> 2) * 8 + (r & 3)) * c.ldw] = acc.c[mb][nbk][r];
+                        if ((r >> 2) * 8 + (r & 3) >= left) acc[nbk][r] = 0.f;
+            }
         } else {
+            const bool in_T = I >= first;                // (first <= I < k)
+            if (in_T) first = I + 1;
+            const gfloat* base = in_T ? ws.T(I % NBUF) + (size_t)c1 * NB * NB : ws.W + (size_t)c1 * NB * ws.ldw + I * NB;
+            const size_t ld = in_T ? NB : ws.ldw;
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
+            for (int nbk = 0; nbk < 2; ++nbk) {
+                const int col = wn * 64 + nbk * 32 + lm;
+                const gfloat* src = base + (size_t)min(col, d - 1 - c1 * NB) * ld + row0;
 #pragma unroll
-                for (int nbk = 0; nbk < 2; ++nbk)
+                for (int r = 0; r < 16; r += 4) {
+                    const v4f x = *(const KFAC_AS1 v4f*)(src + 2 * r);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int dr = mb * 32 + (r >> 2) * 8 + (r & 3);
-                        if (colok[nbk] && dr < rows_left) wq[nbk][(size_t)dr * c.ldw] = acc.c[mb][nbk][r];
-                    }
+                    for (int i = 0; i < 4; ++i) acc[nbk][r + i] = x[i];
+                }
+                if (c1 * NB + col >= d) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[nbk][r] = 0.f;
+                }
+            }
+        }
+        const float back = half_mma_presplit(half_run(ws, first, k, I, half, c1, st), (unsigned char*)lds, acc);
+#pragma unroll
+        for (int nbk = 0; nbk < 2; ++nbk) acc[nbk] *= back;
+        if (I == k + 2) {
+            half_stage(acc, lds);
+            __syncthreads();
+            v4f v[8];
+#pragma unroll
+            for (int p = 0; p < 8; ++p) v[p] = *(const v4f*)&lds[((t >> 5) + 8 * p) * PANEL_RLD + (t & 31) * 4];
+            put_panel(ws, c1, I, half, v, red);
+            // the diagonal tile of block k + 2: steps k - 1 and k
+            gfloat* dst = ws.W + (size_t)(I * NB + row0) * ws.ldw + I * NB + wn * 64 + lm;
+            const int left = d - I * NB - row0;
+            const bool col_ok[2] = {I * NB + wn * 64 < ws.ldw, I * NB + wn * 64 + 32 < ws.ldw};
+#pragma unroll
+            for (int nbk = 0; nbk < 2; ++nbk)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int dr = (r >> 2) * 8 + (r & 3);
+                    acc[nbk][r] = dr < left && col_ok[nbk] ? dst[(size_t)dr * ws.ldw + nbk * 32] : 0.f;
+                }
+            const float back2 = half_mma_presplit(half_run(ws, max(0, k - 1), k, I, half, I, st), (unsigned char*)lds, acc);
+#pragma unroll
+            for (int nbk = 0; nbk < 2; ++nbk)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int dr = (r >> 2) * 8 + (r & 3);
+                    if (dr < left && col_ok[nbk]) dst[(size_t)dr * ws.ldw + nbk * 32] = acc[nbk][r] * back2;
+                }
+            return;
         }
     }
+    half_stage(acc, lds);
+    __syncthreads();
+    v4f v[8];
+#pragma unroll
+    for (int p = 0; p < 8; ++p) v[p] = *(const v4f*)&lds[((t >> 5) + 8 * p) * PANEL_RLD + (t & 31) * 4];
+    put_panel(ws, c1, I, half, v, red);
 }
 
-// Look-ahead: the diagonal tile that is the next step's pivot block is updated by a workgroup of its own, which
-// keeps the new values in registers and inverts the block at once (the pivot sweep is the longest link of the chain
-// pivot -> panel -> update; here it runs beside the update of all other tiles instead of after it).
-__device__ __forceinline__ void upd_next_pivot(const Item& it, int step, float* __restrict__ lds) {
-    const int d = it.dim, kn = step + 1;
+// One half slab of the last step's panel.  Ragged pivot block: fp32 matrix cores, a workgroup per slab.
+__device__ __forceinline__ void last_slab(const Item& it, int k, int I, int half, float* __restrict__ lds, float* __restrict__ red) {
+    const int d = it.dim, nb = d - k * NB, q = k % NBUF;
     const WsView ws = ws_view(it.ws, d);
-    const int k0 = kn * NB, nb = min(NB, d - k0);
-    UpdCtx c;
-    const int cur = step % NBUF;                         // (the block is kept up to date through the step before)
-    c.W = ws.W; c.ldw = ws.ldw; c.T = ws.T(cur); c.out = it.Minv;
-    c.d = d;
-    c.i0 = c.j0 = k0;
-    c.irows = c.jrows = nb;
-    c.nb = NB;
-    c.diag = true;
+    if (nb == NB) {
+        v4f pb[8][2];
+        panel_fetch_b(ws.P(k), pb);
+        slab_T(ws, d, k, I, half, pb, lds, red);
+        return;
+    }
+    if (half == 1) return;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+    gfloat* __restrict__ Tc = ws.T(q) + (size_t)I * NB * NB;
     TileAcc acc;
-    const OldSrc o = {ws.W + (size_t)k0 * ws.ldw + k0, ws.ldw, 1};
-    const PanelRun pl = panel_run(ws, step, 1, kn, kn);
-    upd_regular_mid_split<false>(c, o, pl, (unsigned char*)lds, acc);
-    __syncthreads();                                     // the product's LDS stages are free
-    const int t = threadIdx.x;
-    if (nb < NB) pivot_border(acc.c, nb);                // (uniform)
-    const int f = pivot_sweep(acc.c, nb, lds);
-    if (t == 0 && it.info && f != 0) atomicCAS((int*)it.info, 0, k0 + f);
-    pivot_write(acc.c, lds, it, ws, k0, nb, k0 + NB >= d, false);
+    tile_mma_nt(ws.U(q) + (size_t)I * NB * NB, NB, NB, ws.P(k), NB, nb, nb, lds, acc);
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int nbk = 0; nbk < 2; ++nbk)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {                // (the output's products stream whole 16-float slices of T: zeros beyond nb)
+                const int row = acc_row(wm, mb, r, lane), col = acc_col(wn, nbk, lane);
+                Tc[(size_t)row * NB + col] = col < nb ? acc.c[mb][nbk][r] : 0.f;
+            }
+}
+
+// Look-ahead: the diagonal tile that is the next step's pivot block is updated by a workgroup of its own, which keeps the new
+// values in registers and inverts the block at once.  It is the launch's longest workgroup, so the update is formed from what the
+// launch starts with, without waiting for the slab's T to be written: T^T = P U^T, every wavefront for 32 rows of T, leaves the
+// matrix cores in registers that serve, scaled and split into fp16 pieces, as the operand of T U^T (the contraction index in the
+// order the accumulators hold it; U's pieces are read in the same order).  U's pieces come by LDS copies that start before the
+// first product, and, as far as the LDS does not hold them yet, through registers that the first product no longer needs.  D: acc (blocks on and below the diagonal), from W's tile.
+// Taken from the slab's T as the other workgroups write it, two half slabs one after the other: 19 us until the sweep begins, and 26
+// with a tile's workgroup on the same CU.
+constexpr int PUP_RING = PANEL_B_LDS;                    // LDS: P's pieces (panel_stash), then three slices of U's; later six
+static_assert(PUP_RING + 3 * 2 * PRE_BLOCK <= UPD_LDS_BYTES && 10 * 4096 <= UPD_LDS_BYTES, "the kernel's LDS");
+
+__device__ __forceinline__ void pivot_update(const WsView& ws, int step, int nb, unsigned char* __restrict__ lds, v16f (&acc)[2][2]) {
+    typedef __attribute__((address_space(3))) unsigned char lds_byte;
+    const int kn = step + 1, q = step % NBUF;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), lm = lane & 31, h = lane >> 5;
+    lds_byte* l0 = (lds_byte*)lds;
+    const gfloat* P = ws.P(step);
+    const KFAC_AS1 unsigned char* uh = ws.UH(q) + (size_t)kn * PRE_SLAB + lane * 16;
+    auto copy_slice = [&](int s, int at) {               // both planes of slice s to LDS offset `at`: 8 KB, two copies a wavefront
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int kb = 2 * wave + j;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(uh + (kb >= 4 ? ws.plane : 0) + s * PRE_BLOCK + (kb & 3) * 1024),
+                                             (__attribute__((address_space(3))) void*)(l0 + at + kb * 1024), 16, 0, 0);
+        }
+    };
+    const KFAC_AS1 unsigned char* ur = ws.UH(q) + (size_t)kn * PRE_SLAB + (wave >> 1) * ws.plane + (wave & 1) * 2048 + lane * 16;
+    auto fetch_slice = [&](int s, v4f (&x)[2]) {         // the same by way of registers
+#pragma unroll
+        for (int j = 0; j < 2; ++j) x[j] = *(const KFAC_AS1 v4f*)(ur + s * PRE_BLOCK + j * 1024);
+    };
+    auto put_slice = [&](int at, const v4f (&x)[2]) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) *(v4f*)(lds + at + (2 * wave + j) * 1024 + lane * 16) = x[j];
+    };
+    // ---- T^T = P U^T: block kb holds rows (of P, the contraction index of the second product) 32 kb .., columns = rows 32 wave .. of T
+    constexpr int AHEAD = 4;                             // slices of P in flight
+    v4f pb[AHEAD][2], xa[3][2];
+    panel_fetch_slice(P, 0, pb[0]);
+    const gfloat* urow = ws.U(q) + ((size_t)kn * NB + wave * 32 + lm) * NB + 8 * h;
+    auto fetch_u = [&](int s, v4f (&x)[2]) {
+        x[0] = *(const KFAC_AS1 v4f*)(urow + s * SPLIT_KS);
+        x[1] = *(const KFAC_AS1 v4f*)(urow + s * SPLIT_KS + 4);
+    };
+    fetch_u(0, xa[0]);
+#pragma unroll
+    for (int s = 1; s < AHEAD; ++s) panel_fetch_slice(P, s, pb[s]);
+    fetch_u(1, xa[1]);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) copy_slice(s, PUP_RING + s * 2 * PRE_BLOCK);
+    // the tile's old values, into this XCD's L2: two of its 512 cache lines a thread
+    const gfloat* wtile = ws.W + (size_t)kn * NB * ws.ldw + kn * NB;
+    float touch[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int row = min(t >> 1, nb - 1), col = ((t & 1) * 2 + i) * 32;
+        touch[i] = wtile[(size_t)row * ws.ldw + (col < nb ? col : 0)];
+    }
+    unsigned a_off[4];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) a_off[kb] = (unsigned)split_plane_offset(kb * 32 + lm, h);
+    v16f tt[4];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) tt[kb][r] = 0.f;
+    panel_stash(lds, 0, pb[0]);
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        if (s + AHEAD < 8) panel_fetch_slice(P, s + AHEAD, pb[s % AHEAD]);
+        if (s + 2 < 8) fetch_u(s + 2, xa[(s + 2) % 3]);
+        uint2 lo[3], hi[3];
+        uint4 u[3];
+        split4<3>(xa[s % 3][0], lo);
+        split4<3>(xa[s % 3][1], hi);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) u[e] = make_uint4(lo[e].x, lo[e].y, hi[e].x, hi[e].y);
+        uint4 p[2][3];                                   // (the next block's pieces are on their way beside a block's products)
+        auto read_p = [&](int kb) {
+#pragma unroll
+            for (int e = 0; e < 3; ++e) p[kb & 1][e] = *(const uint4*)(lds + (s & 1) * (3 * SPLIT_PLANE) + e * SPLIT_PLANE + a_off[kb]);
+        };
+        read_p(0);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            if (kb + 1 < 4) read_p(kb + 1);
+            // smallest terms first
+#pragma unroll
+            for (int order = 2; order >= 0; --order)
+#pragma unroll
+                for (int pa = 0; pa <= order; ++pa) tt[kb] = mfma16<false>(p[kb & 1][pa], u[order - pa], tt[kb]);
+        }
+        if (s + 1 < 8) panel_stash(lds, s + 1, pb[(s + 1) % AHEAD]);
+        if (s >= 3 && s < 7) fetch_slice(s, pb[(s + 1) % AHEAD]);        // (free from here on)
+        __syncthreads();
+    }
+    fetch_slice(7, xa[0]);
+    asm volatile("" :: "v"(touch[0]), "v"(touch[1]));
+    // ---- T U^T: row block `wave`, column blocks 0 .. wave
+    // (U's first three slices landed before the last of P's: this wavefront's loads return in order; P's pieces are done with)
+#pragma unroll
+    for (int s = 3; s < 6; ++s) put_slice((s - 3) * 2 * PRE_BLOCK, pb[(s + 1) % AHEAD]);
+    float tm = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) tm = fmaxf(tm, fabsf(tt[kb][r]));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) tm = fmaxf(tm, __shfl_xor(tm, off, 64));
+    const float st = panel_scale(tm);
+    v16f dd[4];
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dd[cb][r] = 0.f;
+    auto slice = [&](int s, int at) {
+        uint2 p0[2], p1[2];
+        const v4f x0 = {tt[s >> 1][8 * (s & 1)] * st, tt[s >> 1][8 * (s & 1) + 1] * st, tt[s >> 1][8 * (s & 1) + 2] * st, tt[s >> 1][8 * (s & 1) + 3] * st};
+        const v4f x1 = {tt[s >> 1][8 * (s & 1) + 4] * st, tt[s >> 1][8 * (s & 1) + 5] * st, tt[s >> 1][8 * (s & 1) + 6] * st, tt[s >> 1][8 * (s & 1) + 7] * st};
+        split4_h2(x0, p0);
+        split4_h2(x1, p1);
+        const uint4 a[2] = {make_uint4(p0[0].x, p0[0].y, p1[0].x, p1[0].y), make_uint4(p0[1].x, p0[1].y, p1[1].x, p1[1].y)};
+        uint4 b[2][2];
+        auto read_b = [&](int cb) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const unsigned char* src = lds + at + e * PRE_BLOCK + 8 * h;
+                const uint2 x = *(const uint2*)(src + split_plane_offset(cb * 32 + lm, 0)), y = *(const uint2*)(src + split_plane_offset(cb * 32 + lm, 1));
+                b[cb & 1][e] = make_uint4(x.x, x.y, y.x, y.y);
+            }
+        };
+        read_b(0);
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            if (cb > wave) continue;                     // (uniform)
+            if (cb + 1 < 4) read_b(cb + 1);
+            dd[cb] = mfma16<true>(a[1], b[cb & 1][0], dd[cb]);
+            dd[cb] = mfma16<true>(a[0], b[cb & 1][1], dd[cb]);
+            dd[cb] = mfma16<true>(a[0], b[cb & 1][0], dd[cb]);
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < 3; ++s) slice(s, PUP_RING + s * 2 * PRE_BLOCK);
+    __syncthreads();                                     // slices 3 .. 5 are there, 0 .. 2 are done with
+    put_slice(PUP_RING, pb[(6 + 1) % AHEAD]);
+    put_slice(PUP_RING + 2 * PRE_BLOCK, xa[0]);
+#pragma unroll
+    for (int s = 3; s < 6; ++s) slice(s, (s - 3) * 2 * PRE_BLOCK);
+    __syncthreads();
+#pragma unroll
+    for (int s = 6; s < 8; ++s) slice(s, PUP_RING + (s - 6) * 2 * PRE_BLOCK);
+    const int wm = wave >> 1, wn = wave & 1;
+    if (wave != 1) {
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int nbk = 0; nbk < 2; ++nbk)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {            // (clamped, not guarded: all loads go out together)
+                    const int row = min(acc_row(wm, mb, r, lane), nb - 1), col = min(acc_col(wn, nbk, lane), nb - 1);
+                    acc[mb][nbk][r] = wtile[(size_t)row * ws.ldw + col];
+                }
+    }
+    // ---- to the wavefronts that hold the quadrants, block by block in register order
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");          // U's pieces are done with
+    float* blocks = (float*)lds;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) {
+        if (cb > wave) continue;
+        const float back = 1.0f / (st * ws.scaleU(q, 2 * kn + (cb >> 1)));
+#pragma unroll
+        for (int r = 0; r < 16; r += 4) {
+            const v4f x = {dd[cb][r] * back, dd[cb][r + 1] * back, dd[cb][r + 2] * back, dd[cb][r + 3] * back};
+            *(v4f*)&blocks[(wave * (wave + 1) / 2 + cb) * 1024 + r * 64 + lane * 4] = x;
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (wave != 1) {
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int nbk = 0; nbk < 2; ++nbk) {
+                const int rb = 2 * wm + mb, cb = 2 * wn + nbk;
+                if (cb > rb) continue;
+#pragma unroll
+                for (int r = 0; r < 16; r += 4) {
+                    const v4f x = *(const v4f*)&blocks[(rb * (rb + 1) / 2 + cb) * 1024 + r * 64 + lane * 4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[mb][nbk][r + i] -= x[i];
+                }
+            }
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ void step_pivot(const Item& it, int step, float* __restrict__ lds) {
+    const int d = it.dim, k0 = (step + 1) * NB, nb = min(NB, d - k0);
+    const WsView ws = ws_view(it.ws, d);
+    v16f acc[2][2];
+    pivot_update(ws, step, nb, (unsigned char*)lds, acc);
+    if (nb < NB) pivot_border(acc, nb);                  // (uniform)
+    const int f = pivot_sweep(acc, nb, lds);
+    if (threadIdx.x == 0 && it.info && f != 0) atomicCAS((int*)it.info, 0, k0 + f);
+    pivot_write(acc, lds, it, ws, k0, nb, k0 + NB >= d, false);
 }
 
 // column tile (from_rows = true): new[a][c] = T[(i0 + a)][c];  row tile: new[a][c] = T[(j0 + c)][a]
@@ -1289,52 +1542,34 @@ __device__ __forceinline__ void group_tile(const Item& it, const WsView& ws, int
             o = OldSrc{ws.T(gbuf + J - g.g0) + (size_t)c.i0 * NB, NB, 1};
         }
     }
-    TileAcc acc;
-    const PanelRun run = panel_run(ws, g.g0 + first, g.j - first + 1, I, J);
-    upd_regular_mid_split(c, o, run, (unsigned char*)lds, acc);
+    upd_regular_mid_split(c, o, panel_run(ws, g.g0 + first, g.j - first + 1, I, J), (unsigned char*)lds);
 }
 
-// Tile of block column / row c = k + 1 (not the diagonal one) in the chain launch of step k: brought up to date
-// through step k, whatever it owes.  With `other` its second index:
-//   other == k              it becomes part of panel k: T_I of this step (block column k)
-//   lo <= other < k         block column `other` was eliminated at a step inside the window the tile can owe: the tile
-//                           then became T_I of that step (not written to the working copy), and owes the steps after it
-//   otherwise               its value in the working copy is up to date through step lo - 1 and it owes lo .. k.  For the
-//                           first block of a group, lo is the first step of the group before (whose bulk update ran
-//                           while that group was under way and skipped the tiles with an index inside it); for the other
-//                           blocks of a group it is the group's own first step (the last launch of the group before
-//                           brought their tiles up to date: the early tiles of plan_of).
-__device__ __forceinline__ void chain_tile(const Item& it, const WsView& ws, int I, int J, int k, float* __restrict__ lds) {
-    const int c1 = k + 1;
-    UpdCtx c;
-    c.W = ws.W; c.ldw = ws.ldw; c.T = ws.T(k % NBUF); c.out = it.Minv;
-    c.d = it.dim;
-    c.i0 = I * NB; c.j0 = J * NB;
-    c.irows = min(NB, c.d - c.i0); c.jrows = min(NB, c.d - c.j0);
-    c.nb = NB;
-    c.diag = false;
-    if (J == k) {                                        // (I == c1: the tile below the pivot block)
-        upd_panel<false>(c, true, lds);
-        return;
+// How the work list is dealt to the XCDs: equal shares, but where few matrices' look-ahead pivots run on few XCDs and the others can
+// take the rest, the pivots' hosts get no more than they have compute units left (a tile's workgroup beside the pivot's lengthens
+// the chain by 5 us a step).
+constexpr int XCD_CUS = 32;
+struct XcdShare {
+    int hosts, host, other;      // XCDs 0 .. hosts - 1 get `host` workgroups each, the others `other`
+};
+static inline __host__ __device__ XcdShare xcd_share(int count, int total) {
+    XcdShare s;
+    s.hosts = 0;
+    s.host = s.other = (total + 7) >> 3;
+    if (count <= 4 && s.other >= XCD_CUS && s.other <= XCD_CUS * 3 / 2) {
+        s.hosts = count;
+        s.host = XCD_CUS - 1;
+        s.other = (total - count * s.host + 7 - count) / (8 - count);
     }
-    const int lo = c1 % GM == 0 ? max(0, c1 - GM) : c1 / GM * GM;
-    OldSrc o = {ws.W + (size_t)c.i0 * ws.ldw + c.j0, ws.ldw, 1};
-    int first = lo;
-    if (I == c1 && J >= lo) {                            // (J < k here)
-        first = J + 1;
-        o = OldSrc{ws.T(J % NBUF) + (size_t)c.i0 * NB, NB, 1};
-    }
-    TileAcc acc;
-    const PanelRun run = panel_run(ws, first, k - first + 1, I, J);
-    upd_regular_mid_split(c, o, run, (unsigned char*)lds, acc);
+    return s;
 }
 
-// One launch per step for all matrices of the batch that still have a block `step`; a matrix whose last block this
-// is takes the output-writing paths (LAST), the others update their working copies.
+// One launch of the sweep: each matrix of the batch takes its stage.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UPD_WAVES, 8))) void inv_update_kernel(ChainBatch b) {
-    __shared__ __attribute__((aligned(1024))) float lds[UNS * USTAGE / 4];
+    __shared__ __attribute__((aligned(1024))) float lds[UPD_LDS_BYTES / 4];
+    __shared__ float red[4];
     // Workgroups go to the 8 XCDs round-robin (id % 8) and each XCD has an L2 of its own.  XCD x therefore takes the
-    // x-th contiguous eighth of the tile list (matrix by matrix, row-major over the lower triangle): tiles that
+    // x-th contiguous eighth of the work list (matrix by matrix: slabs, then tiles): tiles that
     // share a T panel (same block row) and mostly the same U panels run on the same L2 instead of all eight.
     // The first workgroups (one per matrix, padded to a multiple of 8 so that the others keep their XCD) take the
     // next step's pivot block; they are dispatched first and run the longest.
@@ -1343,53 +1578,56 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UPD_WAVES, 
         if ((int)blockIdx.x >= b.count) return;
         __builtin_amdgcn_s_setprio(3);                   // the chain's longest link: ahead of whatever shares its SIMDs
         const Item it = get_item(b, blockIdx.x);
-        const int step = b.step[blockIdx.x];
-        if (step >= 0 && nblk_of(it.dim) > step + 1) upd_next_pivot(it, step, lds);
+        const int stage = b.stage[blockIdx.x];
+        if (stage >= 0 && stage < nblk_of(it.dim) - 1) step_pivot(it, stage, lds);
         return;
     }
     const unsigned bx = blockIdx.x - npiv;
-    const int total = b.prefix[b.count];
-    const int per_xcd = (total + 7) >> 3;
-    const int lin = (int)(bx & 7) * per_xcd + (int)(bx >> 3);
-    if ((int)(bx >> 3) >= per_xcd || lin >= total) return;
+    const int x = bx & 7, in = bx >> 3, total = b.prefix[b.count];
+    const XcdShare sh = xcd_share(b.count, total);
+    const int lin = (x < sh.hosts ? x * sh.host : sh.hosts * sh.host + (x - sh.hosts) * sh.other) + in;
+    if (in >= (x < sh.hosts ? sh.host : sh.other) || lin >= total) return;
     int m, tile;
     locate(b, lin, m, tile);
     const Item it = get_item(b, m);
-    const int nblk = nblk_of(it.dim);
-    const int step = b.step[m];
-    const Plan pl = plan_of(it.dim, step);
+    const int n = nblk_of(it.dim);
+    const int stage = b.stage[m];
+    const Plan pl = plan_of(it.dim, stage);
+    if (tile < pl.slabs) {
+        __builtin_amdgcn_s_setprio(2);                   // the next launch waits for these; the tiles do not hurry
+        const int slab = tile >> 1, half = tile & 1;
+        if (pl.kind == PLAN_STEP) step_slab(it, stage, slab, half, lds, red);
+        else last_slab(it, stage, slab, half, lds, red);
+        return;
+    }
+    tile -= pl.slabs;
     const WsView ws = ws_view(it.ws, it.dim);
     int I, J;
-    if (tile >= pl.chain && pl.early > 0) {
-        // early tile: this group's steps, all of them (the launch is the group's last)
-        early_decode(nblk, pl.g.g0 + pl.g.m, pl.next_m, tile - pl.chain, I, J);
-        group_tile(it, ws, I, J, pl.g, false, lds);
+    if (pl.kind == PLAN_STEP) {
+        bool single = false;
+        if (tile < pl.diag) {
+            I = J = pl.d_begin + tile;
+            single = pl.single;
+        } else {
+            bulk_decode(n, pl.g0, pl.w, pl.early, pl.off + tile - pl.diag, I, J);
+            // -P of the group's last step; the diagonal tiles above
+            if (I == J && (I == pl.g0 - 1 || (I > pl.g0 && I <= pl.g0 + 6))) return;
+        }
+        Group g = pl.g;
+        if (!single) {                                   // (the bulk sees the whole group before, whatever the diagonal tiles see)
+            g.g0 = pl.g0 - GM;
+            g.j = GM - 1;
+        }
+        group_tile(it, ws, I, J, g, single, lds);
         return;
     }
-    if (tile >= pl.chain) {
-        // lag tile: the whole update of the previous group (steps g0 - GM .. g0 - 1, all GM of them)
-        lag_decode(nblk, pl.g.g0, pl.g.m, pl.lag_off + tile - pl.chain, I, J);
-        const int E = pl.g.g0 + pl.g.m;
-        if (I == J && (I == pl.g.g0 - 1 || I == E)) return;   // -P of the group's last step; a chain tile of this group
-        Group pg;
-        pg.g0 = pl.g.g0 - GM; pg.m = GM; pg.j = GM - 1;
-        group_tile(it, ws, I, J, pg, false, lds);
+    tri_decode_blocked(pl.kind == PLAN_PANEL ? n - 1 : n, tile, I, J);
+    if (pl.kind == PLAN_PANEL) {
+        if (I != J || I != n - 2) group_tile(it, ws, I, J, pl.g, false, lds);    // (that one is -P of its step)
         return;
     }
-    if (pl.kind == PLAN_CHAIN) {
-        __builtin_amdgcn_s_setprio(2);                   // the next panel waits for these; lag tiles do not hurry
-        chain_decode(nblk, step + 1, pl.d_begin, tile, I, J);
-        if (I != J) chain_tile(it, ws, I, J, step, lds);
-        else group_tile(it, ws, I, J, pl.g, pl.g.j < pl.g.m - 1, lds);   // kept up to date step by step inside a group
-        return;
-    }
-    tri_decode_blocked(nblk, tile, I, J);
-    if (I == J && (I == step || I == step + 1)) return;  // this step's pivot block and the next one's are written elsewhere
-    if (pl.kind == PLAN_WHOLE) {
-        group_tile(it, ws, I, J, pl.g, false, lds);
-        return;
-    }
-    const int cur = step % NBUF;
+    const int step = n - 1, cur = step % NBUF;
+    if (I == J && I == step) return;                     // the pivot code wrote it
     UpdCtx c;
     c.W = ws.W; c.ldw = ws.ldw; c.T = ws.T(cur); c.out = it.Minv;
     c.d = it.dim;
@@ -1397,7 +1635,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UPD_WAVES, 
     c.irows = min(NB, c.d - c.i0); c.jrows = min(NB, c.d - c.j0);
     c.nb = min(NB, c.d - step * NB);
     c.diag = I == J;
-    if (J == step || I == step) upd_panel<true>(c, J == step, lds);
+    if (I == step) upd_panel<true>(c, false, lds);
     else upd_regular<true>(c, ws.U(cur), lds);
 }
 
@@ -1466,8 +1704,6 @@ static int write_planes(const kfac_inverse_item* h, int count, hipStream_t strea
     return KFAC_OK;
 }
 
-static inline int tri_tiles(int dim) { int n = nblk_of(dim); return n * (n + 1) / 2; }
-
 static void fill_batch(Batch& b, const kfac_inverse_item* items, int count) {
     b.count = count;
     for (int i = 0; i < count; ++i) {
@@ -1482,12 +1718,8 @@ static void fill_batch(Batch& b, const kfac_inverse_item* items, int count) {
 }
 
 // items must be sorted by non-increasing dim (checked by the caller of this function).
-static inline int xcd_grid(int tiles) { return 8 * ((tiles + 7) / 8); }   // eight equal shares, the last one padded
-
 static int run_group(const kfac_inverse_item* h, int count, hipStream_t stream) {
     Batch b;
-    const int max_steps = nblk_of(h[0].dim);
-
     // matrices needing the blocked path (more than one block) come first in the sorted order
     int n_multi = 0;
     while (n_multi < count && nblk_of(h[n_multi].dim) > 1) ++n_multi;
@@ -1496,14 +1728,14 @@ static int run_group(const kfac_inverse_item* h, int count, hipStream_t stream) 
         const int n = min(MAXB, count - first);
         fill_batch(b, h + first, n);
         b.prefix[0] = 0;
-        for (int i = 0; i < n; ++i) b.prefix[i + 1] = b.prefix[i] + 4 * (tri_tiles(h[first + i].dim) - 1);
+        for (int i = 0; i < n; ++i) b.prefix[i + 1] = b.prefix[i] + begin_workgroups(nblk_of(h[first + i].dim));
         const bool together = b.prefix[n] <= BEGIN_TOGETHER;
         if (!together) KFAC_LAUNCH(inv_init_kernel, dim3(b.prefix[n]), dim3(256), stream, b);
         KFAC_LAUNCH(inv_begin_kernel, dim3(n + (together ? b.prefix[n] : 0)), dim3(256), stream, b);
     }
     if (n_multi == 0) return KFAC_OK;
-    // One panel and one update launch per step of the matrix with the most blocks.  A matrix with fewer blocks takes
-    // its steps at evenly spread launches rather than in the first ones: the tile updates of the whole batch are then
+    // One launch per stage of the matrix with the most blocks.  A matrix with fewer blocks takes
+    // its stages at evenly spread launches rather than in the first ones: the tile updates of the whole batch are then
     // spread over all launches, each of which lasts at least as long as a pivot workgroup anyway.
     ChainBatch c;
     c.count = n_multi;
@@ -1511,22 +1743,21 @@ static int run_group(const kfac_inverse_item* h, int count, hipStream_t stream) 
     for (int i = 0; i < n_multi; ++i) {
         c.dim[i] = h[i].dim; c.Minv[i] = h[i].Minv; c.ws[i] = h[i].ws; c.info[i] = h[i].info;
     }
-    int done[CMAXB] = {};                               // steps taken so far
-    for (int l = 0; l < max_steps; ++l) {
+    int done[CMAXB] = {};                               // stages taken so far
+    const int launches = nblk_of(h[0].dim) + 1;
+    for (int l = 0; l < launches; ++l) {
         for (int i = 0; i < n_multi; ++i) {
-            // (a matrix's last two steps touch all of its tiles, the last one on a slow path: matrices with fewer blocks
+            // (a matrix's last two stages touch all of its tiles, the last one on a slow path: matrices with fewer blocks
             // than the largest finish at different launches, none with the largest ones)
-            const int n = nblk_of(h[i].dim);
-            const int span = n == max_steps ? n : max(n, max_steps - 2 - 2 * (i % 6));
+            const int n = nblk_of(h[i].dim) + 1;
+            const int span = n == launches ? n : max(n, launches - 2 - 2 * (i % 6));
             const bool run = l < span && (int)(((long long)(l + 1) * n) / span) > (int)(((long long)l * n) / span);
-            c.step[i] = run ? done[i] : -1;
+            c.stage[i] = run ? done[i] : -1;
+            c.prefix[i + 1] = c.prefix[i] + (run ? plan_workgroups(plan_of(h[i].dim, done[i])) : 0);
+            done[i] += run;
         }
-        for (int i = 0; i < n_multi; ++i) c.prefix[i + 1] = c.prefix[i] + (c.step[i] >= 0 ? 2 * nblk_of(h[i].dim) : 0);
-        KFAC_LAUNCH(inv_panel_kernel, dim3(c.prefix[n_multi]), dim3(256), stream, c);
-        for (int i = 0; i < n_multi; ++i)
-            c.prefix[i + 1] = c.prefix[i] + (c.step[i] >= 0 ? update_tiles(h[i].dim, c.step[i]) : 0);
-        KFAC_LAUNCH(inv_update_kernel, dim3(xcd_grid(n_multi) + xcd_grid(c.prefix[n_multi])), dim3(256), stream, c);
-        for (int i = 0; i < n_multi; ++i) done[i] += c.step[i] >= 0;
+        const XcdShare sh = xcd_share(n_multi, c.prefix[n_multi]);
+        KFAC_LAUNCH(inv_update_kernel, dim3(((n_multi + 7) & ~7) + 8 * max(sh.host, sh.other)), dim3(256), stream, c);
     }
     return KFAC_OK;
 }
@@ -1534,7 +1765,7 @@ static int run_group(const kfac_inverse_item* h, int count, hipStream_t stream) 
 static size_t ws_bytes_of(int dim) {
     if (nblk_of(dim) == 1) return 256;
     const size_t d_pad = (size_t)nblk_of(dim) * NB;
-    return align_up((d_pad * ldw_of(dim) + NBUF * panel_buffer_floats(dim) + (size_t)NB * NB + 4 * NBUF * (size_t)nblk_of(dim)) * sizeof(float), 256);
+    return align_up((d_pad * ldw_of(dim) + NBUF * panel_buffer_floats(dim) + (size_t)2 * NB * NB + 4 * NBUF * (size_t)nblk_of(dim)) * sizeof(float), 256);
 }
 
 static bool item_ok(const kfac_inverse_item& it) {
