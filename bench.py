@@ -65,10 +65,10 @@ def kernel_work(net: kstep.KfacNetworkStep, kernels):
         # one workgroup per matrix: first-block inverses of nb^3 flops
         "inv_begin_kernel": ("mfma", PEAK["mfma_f32"], "TFLOP/s", sum(kstep.inverse_first_pivot_flops(d) for d in dims)),
         "gemm_nt_kernel": ("mfma", PEAK["mfma_f16x2"], "TFLOP/s", sum(kstep.precondition_flops(s.d_G, s.d_A) for s in shapes)),
-        # the operands' piece planes: every element read (4 B) and written (2 x 2 B): the gradient by the preconditioning
-        # call, the inverses by the inversion call (kfac_inverse_item.planes)
+        # the gradient's piece planes: every element read (4 B) and written (2 x 2 B)
         "pre_split_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(8.0 * s.d_G * s.d_A for s in shapes)),
-        "inv_planes_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(8.0 * d * d for d in dims)),
+        # lower triangles read, inverses written as squares and as piece planes
+        "inv_out_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(10.0 * d * d for d in dims)),
         "kfac::ema_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(12.0 * d * d for d in dims)),
         "kfac::ema_batched_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(12.0 * d * d for d in dims)),
         "inv_init_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(4.0 * d * (d + 1) for d in dims if d > kstep.INVERSE_BLOCK)),

@@ -21,7 +21,7 @@
 //     (U_(k+1) is part of panel k: nothing in the launch waits for another workgroup of it);
 //   * tiles of the rest of the matrix, which receive the updates of finished steps in one visit for a group of GM steps (Plan).
 // Every matrix of a batch carries its own stage, so that matrices with fewer blocks spread their launches over those of the
-// largest one.  The last step takes two launches: its panel beside the tiles that still owe updates, then the output.
+// largest one.  The last step's panel is a launch, and one launch for the whole batch writes the outputs (inv_out_kernel).
 // Bound: one matrix alone by the look-ahead pivot's workgroup (its update 11.8 us, the sweep 15.3, write-out 1.9, from launch to
 // launch 2.5; half slabs are done after 13 to 25): 31.5 us a step, 40 when panel and tiles were launches of their own.  One matrix
 // alone, us: 145 columns 81 -> 64, 1000 328 -> 281, 2049 632 -> 565, 4609 1501 -> 1370; ten ragged ones (10 to 1153 columns) with
@@ -43,8 +43,8 @@ constexpr int NB = 128;          // elimination block = tile edge
 constexpr int MAXB = 64;         // matrices per launch of the kernels that read S (bounded by the 4 KB of kernel arguments)
 constexpr int CMAXB = 112;       // matrices per launch of the sweep's per-step kernels, whose argument block is leaner
 constexpr int UPD_WAVES = 3;     // wavefronts per SIMD the update kernel is compiled for (register budget)
-constexpr int SLD = 132;         // epilogue staging stride (floats) for row-wise float4 access
-constexpr int SLD_T = 129;       // epilogue staging stride when the stage is also read column-wise
+constexpr int SLD = 132;         // staging stride (floats) for row-wise float4 access
+constexpr int SLD_T = 129;       // staging stride when the stage is also read column-wise
 constexpr int PH = NB / 2;       // rows of a half slab
 constexpr int UPD_LDS_BYTES = 48 * 1024;   // of a workgroup of the sweep's launches: three of them on a CU
 
@@ -157,42 +157,33 @@ struct Group {
 //     fourth (whose panel k + 1 takes the buffer of the first step of the group before).  The tiles of blocks g0 + 2 and g0 + 3
 //     come first, in the group's first launch ("early" tiles): the panels k + 1 of the group's second and third launch read them.
 //     (Block g0 + 1, whose panel the first launch forms, owes the group before and step g0: chain_from.)
-// Stage n - 1: the panel of the last step, beside the tiles of all other blocks, which receive what the last group owes them.
-// Stage n: the output.
+// Stage n - 1: the panel of the last step, beside the tiles of all other blocks, which receive what the last group owes them, unless
+// the output launch, which follows, is to do that (OUT_OWED).
 struct Plan {
-    int kind;            // PLAN_STEP, PLAN_PANEL, PLAN_OUT
-    Group g;             // the run of steps that diagonal, early and lag tiles (PLAN_PANEL: all tiles) see
+    Group g;             // the run of steps that the tiles see
     int slabs;           // workgroups of half slabs
     int d_begin, diag;   // diagonal tiles, from block d_begin on
     bool single;         // they see only the run's last step
     int g0, w;           // the group's first block and how many blocks it takes out of the bulk
     int early;           // number of early tiles of the group; early and lag tiles are one list, of which this launch takes
     int off, bulk;       // `bulk` tiles from `off` on
-    int tiles;           // PLAN_PANEL, PLAN_OUT: tiles of the triangle
+    int tiles;           // stage n - 1: all tiles but the last block's (left out where the output launch takes their updates)
 };
-constexpr int PLAN_STEP = 0, PLAN_PANEL = 1, PLAN_OUT = 2;
 
 static inline __host__ __device__ Plan plan_of(int dim, int stage) {
     const int n = nblk_of(dim);
     Plan p;
-    p.slabs = p.d_begin = p.diag = p.g0 = p.w = p.early = p.off = p.bulk = p.tiles = 0;
+    p.d_begin = p.diag = p.g0 = p.w = p.early = p.off = p.bulk = p.tiles = 0;
     p.single = false;
-    p.g.g0 = 0; p.g.m = 0; p.g.j = 0;
-    if (stage == n) {
-        p.kind = PLAN_OUT;
-        p.tiles = n * (n + 1) / 2;
-        return p;
-    }
-    p.slabs = stage == n - 1 ? 2 * (n - 1) : 2 * n;
     if (stage == n - 1) {
-        p.kind = PLAN_PANEL;
+        p.slabs = 2 * (n - 1);
+        p.tiles = n * (n - 1) / 2;
         p.g.g0 = (n - 2) / GM * GM;
         p.g.m = n - 1 - p.g.g0;
         p.g.j = p.g.m - 1;
-        p.tiles = n * (n - 1) / 2;
         return p;
     }
-    p.kind = PLAN_STEP;
+    p.slabs = 2 * n;
     const int k = stage, g0 = k / GM * GM, j = k - g0, m = min(GM, n - 1 - g0);
     p.g0 = g0;
     p.w = min(GM, n - g0);
@@ -224,7 +215,7 @@ static inline __host__ __device__ Plan plan_of(int dim, int stage) {
     }
     return p;
 }
-static inline __host__ __device__ int plan_workgroups(const Plan& p) { return p.slabs + p.diag + p.bulk + p.tiles; }
+static inline int plan_workgroups(const Plan& p, bool out_owed) { return p.slabs + p.diag + p.bulk + (out_owed ? 0 : p.tiles); }
 // The first step that the tiles of block column / row c owe when panel c is formed (by the launch of step c - 1): the working copy
 // holds them through the step before it.
 static inline __host__ __device__ int chain_from(int c) {
@@ -760,70 +751,67 @@ constexpr int BEGIN_TOGETHER = 768;      // three workgroups to a CU
 //   regular      new = old - T_I U_J^T
 //   column       J == k, I > k:  new[a][c] = T[I*128 + a][c]          (block column k below the pivot)
 //   row          I == k, J < k:  new[a][c] = T[J*128 + c][a]          (block row k left of the pivot)
-// LAST = false: the tile goes back into the padded working copy (whole 512-byte rows).
-// LAST = true (the matrix's final step): the tile, negated, goes to the caller's output, and so does its mirror image.
-// Column / row tiles and all tiles of a final step pass through an LDS stage, 64 tile rows at a time, so that global
-// accesses are row-wise; regular tiles of the other steps go from and to registers (upd_regular_mid_split).
+// Regular tiles go from and to registers (upd_regular_mid_split); column and row tiles pass through an LDS stage, 64 tile rows at a
+// time, so that global accesses are row-wise.
 struct UpdCtx {
-    gfloat* W; int ldw; const gfloat* T; gfloat* out;
+    gfloat* W; int ldw; const gfloat* T;
     int d, i0, j0, irows, jrows, nb;
     bool diag;
 };
 
-// Elements from .. n - 1 of four neighbours, any alignment of floats.
-__device__ __forceinline__ void put4(gfloat* dst, const v4f& x, int from, int n) {
-    if (from <= 0 && n >= 4) {
-        *(KFAC_AS1 v4f_a4*)dst = x;
-    } else {
+// stage[rl][c] (64 x sld floats) <- rows h0 .. h0 + 63 of a column or row tile.
+__device__ __forceinline__ void panel_stage(const UpdCtx& c, bool column, int h0, int sld, float* __restrict__ stage) {
+    const int t = threadIdx.x, pr = t >> 5, pc = (t & 31) * 4;
+    // all eight loads go out before the first value is used (a use inside the guarded block would make the
+    // compiler wait for every load in turn)
+    v4f x[8];
+    if (column) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (i >= from && i < n) dst[i] = x[i];
+        for (int p = 0; p < 8; ++p) {
+            const int row = h0 + pr + 8 * p;
+            x[p] = v4f{0.f, 0.f, 0.f, 0.f};
+            if (row < c.irows) x[p] = *(const KFAC_AS1 v4f*)&c.T[(size_t)(c.i0 + row) * NB + pc];
+        }
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            const int rl = pr + 8 * p;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) stage[rl * sld + pc + i] = pc + i < c.nb ? x[p][i] : 0.f;
+        }
+    } else {
+        const int ta = (t & 15) * 4, tc = t >> 4;         // 16 float4 along a (64 a's), 16 c's per pass
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            const int cc = tc + 16 * p;
+            x[p] = v4f{0.f, 0.f, 0.f, 0.f};
+            if (cc < c.jrows) x[p] = *(const KFAC_AS1 v4f*)&c.T[(size_t)(c.j0 + cc) * NB + h0 + ta];
+        }
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            const int cc = tc + 16 * p;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) stage[(ta + i) * sld + cc] = h0 + ta + i < c.nb ? x[p][i] : 0.f;
+        }
     }
 }
 
-// stage (64 x sld floats) holds rows h0..h0+63 of the tile's new values (or of the product, for regular tiles
-// when COMBINE: new = old - stage, old prefetched in oldv).
-template <bool LAST, bool COMBINE>
-__device__ __forceinline__ void upd_flush(const UpdCtx& c, float* __restrict__ stage, int h0, const v4f (&oldv)[8]) {
-    const int t = threadIdx.x;
-    const int pr = t >> 5, pc = (t & 31) * 4;
-    constexpr int sld = LAST ? SLD_T : SLD;
-    if constexpr (!LAST) {
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int rl = pr + 8 * p, row = h0 + rl;
-            if (row < c.irows && c.j0 + pc < c.ldw) {
-                v4f s = *(const v4f*)&stage[rl * sld + pc];
-                if constexpr (COMBINE) s = oldv[p] - s;
-                *(KFAC_AS1 v4f*)&c.W[(size_t)(c.i0 + row) * c.ldw + c.j0 + pc] = s;
-            }
-        }
-    } else {
-        // final values (sign flipped) out along the tile's rows and back into the stage, then out along its mirror image's
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int rl = pr + 8 * p, row = h0 + rl;
-            v4f x;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float s = stage[rl * sld + pc + i];
-                x[i] = COMBINE ? s - oldv[p][i] : -s;
-                stage[rl * sld + pc + i] = x[i];
-            }
-            if (row < c.irows) put4(c.out + (size_t)(c.i0 + row) * c.d + c.j0 + pc, x, 0, min(c.jrows - pc, c.diag ? row - pc + 1 : 4));
-        }
+__device__ __forceinline__ void upd_panel(const UpdCtx& c, bool column, float* __restrict__ lds) {
+    const int t = threadIdx.x, pr = t >> 5, pc = (t & 31) * 4;
+#pragma unroll 1
+    for (int h0 = 0; h0 < c.irows; h0 += 64) {
+        if (h0 > 0) __syncthreads();
+        panel_stage(c, column, h0, SLD, lds);
         __syncthreads();
-        const int mr = (t & 15) * 4, mc = t >> 4;         // four tile rows (neighbours in the mirror image), 16 columns a pass
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
-            const int col = mc + 16 * p, row = h0 + mr;
-            const v4f x = {stage[mr * sld + col], stage[(mr + 1) * sld + col], stage[(mr + 2) * sld + col], stage[(mr + 3) * sld + col]};
-            if (col < c.jrows) put4(c.out + (size_t)(c.j0 + col) * c.d + c.i0 + row, x, c.diag ? col - row + 1 : 0, c.irows - row);
+            const int rl = pr + 8 * p, row = h0 + rl;
+            if (row < c.irows && c.j0 + pc < c.ldw)
+                *(KFAC_AS1 v4f*)&c.W[(size_t)(c.i0 + row) * c.ldw + c.j0 + pc] = *(const v4f*)&lds[rl * SLD + pc];
         }
     }
 }
 
-// Regular tile: acc = T_I . U_J^T with both operand panels (128 rows x nb floats, row stride 128, zero beyond nb)
+// acc = T_I . U_J^T of a matrix's last step, fp32, with both operand panels (128 rows x nb floats, row stride 128, zero beyond nb)
 // streamed through a 3-stage LDS ring by global_load_lds_dwordx4 (lane i's 16 bytes land at block base + 16 i), so
 // no registers are spent on staging and one barrier per 16-wide K-slab suffices.  Inside a 1 KB block (16 rows x 4
 // chunks of 4 floats) chunk c of row r sits in slot 4 r + (c ^ ((r >> 1) & 3)): the MFMA operand reads (one float4
@@ -838,27 +826,12 @@ static_assert(UNS * USTAGE <= UPD_LDS_BYTES && PRE_NS * PRE_STAGE <= UPD_LDS_BYT
 #define KFAC_LDS_READ128(dst, addr, off) \
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off))
 
-template <bool LAST>
-__device__ __forceinline__ void upd_regular(const UpdCtx& c, const gfloat* __restrict__ U, float* __restrict__ lds) {
+__device__ __forceinline__ void product_f32(const UpdCtx& c, const gfloat* __restrict__ U, float* __restrict__ lds, TileAcc& acc) {
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
     const int lm = lane & 31, h = lane >> 5;
-    const int pr = t >> 5, pc = (t & 31) * 4;
-    constexpr int sld = LAST ? SLD_T : SLD;
     const bool dead = c.diag && wm == 0 && wn == 1;      // strictly above the diagonal, never used
     lds_byte* l0 = (lds_byte*)lds;
-
-    // LAST: old values are fetched row-wise (the epilogue transposes through LDS for the mirror image).
-    v4f oldv[8];
-    if constexpr (LAST) {
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int row = pr + 8 * p;
-            v4f o = {0.f, 0.f, 0.f, 0.f};
-            if (row < c.irows && c.j0 + pc < c.ldw) o = *(const KFAC_AS1 v4f*)&c.W[(size_t)(c.i0 + row) * c.ldw + c.j0 + pc];
-            oldv[p] = o;
-        }
-    }
 
     // ---- producer: wavefronts 0,1 stream T_I, wavefronts 2,3 stream U_J; four 1 KB blocks each per stage ----
     const int pan = wave >> 1;
@@ -888,7 +861,6 @@ __device__ __forceinline__ void upd_regular(const UpdCtx& c, const gfloat* __res
             b_addr[q][s2] = (unsigned)(UPANEL + (mb_ >> 4) * 1024 + (4 * (mb_ & 15) + (ch ^ (((mb_ & 15) >> 1) & 3))) * 16);
         }
 
-    TileAcc acc;
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
@@ -925,36 +897,7 @@ __device__ __forceinline__ void upd_regular(const UpdCtx& c, const gfloat* __res
             }
         }
     }
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");            // ring idle: LDS becomes the epilogue stage
-#pragma unroll 1
-    for (int half = 0; half < 2; ++half) {
-        const int h0 = half * 64;
-        if (h0 >= c.irows) break;                          // uniform
-        if (half == 1) {
-            __syncthreads();                               // everyone is done with the first half's stage
-            // old values of the second half, all fetched before anything more is stored
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int row = h0 + pr + 8 * p;
-                v4f o = {0.f, 0.f, 0.f, 0.f};
-                if (row < c.irows && c.j0 + pc < c.ldw) o = *(const KFAC_AS1 v4f*)&c.W[(size_t)(c.i0 + row) * c.ldw + c.j0 + pc];
-                oldv[p] = o;
-            }
-        }
-        if (wm == half) {
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int rl = mb * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-                        lds[rl * sld + acc_col(wn, nbk, lane)] = dead ? 0.f : acc.c[mb][nbk][r];
-                    }
-        }
-        __syncthreads();
-        upd_flush<LAST, true>(c, lds, h0, oldv);
-    }
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");            // ring idle: the LDS may be reused
 }
 
 // Where a tile's old values come from: element (a, c) of the tile is base[a * rs + c * cs].
@@ -1459,54 +1402,6 @@ __device__ __forceinline__ void step_pivot(const Item& it, int step, float* __re
     pivot_write(acc, lds, it, ws, k0, nb, k0 + NB >= d, false);
 }
 
-// column tile (from_rows = true): new[a][c] = T[(i0 + a)][c];  row tile: new[a][c] = T[(j0 + c)][a]
-template <bool LAST>
-__device__ __forceinline__ void upd_panel(const UpdCtx& c, bool column, float* __restrict__ lds) {
-    const int t = threadIdx.x;
-    const int pr = t >> 5, pc = (t & 31) * 4;
-    constexpr int sld = LAST ? SLD_T : SLD;
-    const v4f none[8] = {};
-#pragma unroll 1
-    for (int half = 0; half < 2; ++half) {
-        const int h0 = half * 64;
-        if (h0 >= c.irows) break;
-        if (half == 1) __syncthreads();
-        // all eight loads go out before the first value is used (a use inside the guarded block would make the
-        // compiler wait for every load in turn)
-        v4f x[8];
-        if (column) {
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int row = h0 + pr + 8 * p;
-                x[p] = v4f{0.f, 0.f, 0.f, 0.f};
-                if (row < c.irows) x[p] = *(const KFAC_AS1 v4f*)&c.T[(size_t)(c.i0 + row) * NB + pc];
-            }
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int rl = pr + 8 * p;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) lds[rl * sld + pc + i] = pc + i < c.nb ? x[p][i] : 0.f;
-            }
-        } else {
-            const int ta = (t & 15) * 4, tc = t >> 4;     // 16 float4 along a (64 a's), 16 c's per pass
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int cc = tc + 16 * p;
-                x[p] = v4f{0.f, 0.f, 0.f, 0.f};
-                if (cc < c.jrows) x[p] = *(const KFAC_AS1 v4f*)&c.T[(size_t)(c.j0 + cc) * NB + h0 + ta];
-            }
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int cc = tc + 16 * p;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) lds[(ta + i) * sld + cc] = h0 + ta + i < c.nb ? x[p][i] : 0.f;
-            }
-        }
-        __syncthreads();
-        upd_flush<LAST, false>(c, lds, h0, none);
-    }
-}
-
 // Tile (I, J) of a step that is not the matrix's last: brings it up to date through step kq = g.g0 + g.j of group g.
 // single: the tile has been kept up to date step by step (a diagonal tile inside a group): it sees step kq only, and its old value
 // is in the working copy.  Otherwise it sees all of the group's steps up to kq that it has not seen yet: all of them
@@ -1519,14 +1414,14 @@ __device__ __forceinline__ void group_tile(const Item& it, const WsView& ws, int
     const int kq = g.g0 + g.j;
     const int gbuf = g.g0 % NBUF;                        // buffer of the group's first step
     UpdCtx c;
-    c.W = ws.W; c.ldw = ws.ldw; c.T = ws.T(gbuf + g.j); c.out = it.Minv;
+    c.W = ws.W; c.ldw = ws.ldw; c.T = ws.T(gbuf + g.j);
     c.d = it.dim;
     c.i0 = I * NB; c.j0 = J * NB;
     c.irows = min(NB, c.d - c.i0); c.jrows = min(NB, c.d - c.j0);
     c.nb = NB;                                           // (only a matrix's last block can be ragged)
     c.diag = I == J;
     if (J == kq || I == kq) {                            // block column / row kq becomes the panel
-        upd_panel<false>(c, J == kq, lds);
+        upd_panel(c, J == kq, lds);
         return;
     }
     OldSrc o = {ws.W + (size_t)c.i0 * ws.ldw + c.j0, ws.ldw, 1};
@@ -1596,110 +1491,222 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UPD_WAVES, 
     if (tile < pl.slabs) {
         __builtin_amdgcn_s_setprio(2);                   // the next launch waits for these; the tiles do not hurry
         const int slab = tile >> 1, half = tile & 1;
-        if (pl.kind == PLAN_STEP) step_slab(it, stage, slab, half, lds, red);
+        if (stage < n - 1) step_slab(it, stage, slab, half, lds, red);
         else last_slab(it, stage, slab, half, lds, red);
         return;
     }
     tile -= pl.slabs;
-    const WsView ws = ws_view(it.ws, it.dim);
     int I, J;
-    if (pl.kind == PLAN_STEP) {
-        bool single = false;
-        if (tile < pl.diag) {
-            I = J = pl.d_begin + tile;
-            single = pl.single;
-        } else {
-            bulk_decode(n, pl.g0, pl.w, pl.early, pl.off + tile - pl.diag, I, J);
-            // -P of the group's last step; the diagonal tiles above
-            if (I == J && (I == pl.g0 - 1 || (I > pl.g0 && I <= pl.g0 + 6))) return;
-        }
-        Group g = pl.g;
-        if (!single) {                                   // (the bulk sees the whole group before, whatever the diagonal tiles see)
-            g.g0 = pl.g0 - GM;
-            g.j = GM - 1;
-        }
-        group_tile(it, ws, I, J, g, single, lds);
-        return;
+    bool single = false;
+    Group g = pl.g;
+    if (stage == n - 1) {
+        tri_decode_blocked(n - 1, tile, I, J);
+        if (I == J && I == n - 2) return;                // -P of the group's last step
+    } else if (tile < pl.diag) {
+        I = J = pl.d_begin + tile;
+        single = pl.single;
+    } else {
+        bulk_decode(n, pl.g0, pl.w, pl.early, pl.off + tile - pl.diag, I, J);
+        // -P of the group's last step; the diagonal tiles above
+        if (I == J && (I == pl.g0 - 1 || (I > pl.g0 && I <= pl.g0 + 6))) return;
+        g.g0 = pl.g0 - GM;                               // (the whole group before, whatever the diagonal tiles see)
+        g.j = GM - 1;
     }
-    tri_decode_blocked(pl.kind == PLAN_PANEL ? n - 1 : n, tile, I, J);
-    if (pl.kind == PLAN_PANEL) {
-        if (I != J || I != n - 2) group_tile(it, ws, I, J, pl.g, false, lds);    // (that one is -P of its step)
-        return;
-    }
-    const int step = n - 1, cur = step % NBUF;
-    if (I == J && I == step) return;                     // the pivot code wrote it
-    UpdCtx c;
-    c.W = ws.W; c.ldw = ws.ldw; c.T = ws.T(cur); c.out = it.Minv;
-    c.d = it.dim;
-    c.i0 = I * NB; c.j0 = J * NB;
-    c.irows = min(NB, c.d - c.i0); c.jrows = min(NB, c.d - c.j0);
-    c.nb = min(NB, c.d - step * NB);
-    c.diag = I == J;
-    if (I == step) upd_panel<true>(c, false, lds);
-    else upd_regular<true>(c, ws.U(cur), lds);
+    group_tile(it, ws_view(it.ws, it.dim), I, J, g, single, lds);
 }
 
-// The piece planes of finished inverses: one workgroup per 128 x 128 block, read from the caller's output after the
-// matrix's last step.  (Written by the last step's tiles themselves the planes cost the update kernel registers that
-// its hot paths miss, and more time than this pass over the output.)
-constexpr int PLMAXB = 100;
-struct PlanesBatch {
+// ---- output ----------------------------------------------------------------------------------------------------------
+// One launch for all matrices of a call: every lower tile receives the last step's update (fp32 products of its nb columns), in large
+// batches after the last group's (one trip through memory less; small ones, where a launch is as long as its longest workgroup, have
+// these in the launch before: ten ragged matrices of 200 tiles 451 us, 474 with them here; the long inversions of ResNet-50 and what
+// runs beside them 5.33 ms without, 5.23 with), and its negative goes to the caller's output, with its mirror image, and, if asked for, to the piece planes.  (With
+// these in launches of the sweep and the planes in a pass over the finished inverses, every tile went through memory twice more.)
+// Bound: HBM.
+constexpr int OMAXB = 90;
+constexpr int OUT_OWED = 512;        // lower tiles of a batch from which on the output launch takes the last group's updates too
+struct OutBatch {
     int count;
-    int prefix[PLMAXB + 1];           // block prefix sums
-    int dim[PLMAXB];
-    float damping[PLMAXB];
-    const float* damping_dev[PLMAXB];
-    const float* Minv[PLMAXB];
-    void* planes[PLMAXB];
+    int owed;                         // the last group's updates are this launch's
+    int prefix[OMAXB + 1];
+    int dim[OMAXB];
+    float damping[OMAXB];
+    const float* damping_dev[OMAXB];
+    float* Minv[OMAXB];
+    void* ws[OMAXB];
+    void* planes[OMAXB];
 };
-static_assert(sizeof(PlanesBatch) <= 4096, "the batch travels in the kernel arguments");
+static_assert(sizeof(OutBatch) <= 4096, "the batch travels in the kernel arguments");
 
-__global__ __launch_bounds__(256) void inv_planes_kernel(PlanesBatch b) {
-    const int t = threadIdx.x;
-    const int m = __syncthreads_count(t < b.count - 1 && b.prefix[t + 1] <= (int)blockIdx.x);
-    const int blk = blockIdx.x - b.prefix[m];
-    const int d = b.dim[m], n = nblk_of(d);
-    const int s = blk / n, c = blk - s * n;
-    const int r0 = s * NB, k0 = c * NB;
-    const float lam = b.damping_dev[m] ? *as_global(b.damping_dev[m]) : b.damping[m];
-    const float sc = inverse_plane_scale(lam);
-    const gfloat* X = as_global(b.Minv[m]);
-    KFAC_AS1 unsigned char* planes = (KFAC_AS1 unsigned char*)as_global((float*)b.planes[m]);
-    const size_t plane = inverse_plane_bytes(d);
-    if (t == 0) ((gfloat*)(planes + 2 * plane))[blk] = sc;
-    const int c4 = (t & 31) * 4, rr = t >> 5;
-    v4f v[16];
-    if (r0 + NB <= d && k0 + NB <= d) {                 // all loads go out together (a guard per load would serialise them)
+struct OutPlanes {
+    KFAC_AS1 unsigned char* base;    // null: none
+    size_t plane;
+    float scale;
+};
+
+// Elements from .. n - 1 of four neighbours, any alignment of floats.
+__device__ __forceinline__ void put4(gfloat* dst, const v4f& x, int from, int n) {
+    if (from <= 0 && n >= 4) {
+        *(KFAC_AS1 v4f_a4*)dst = x;
+    } else {
 #pragma unroll
-        for (int p = 0; p < 16; ++p) v[p] = *(const KFAC_AS1 v4f_a4*)(X + (size_t)(r0 + rr + 8 * p) * d + k0 + c4);
+        for (int i = 0; i < 4; ++i)
+            if (i >= from && i < n) dst[i] = x[i];
+    }
+}
+
+// stage (64 x SLD_T floats) holds rows h0 .. h0 + 63 of a tile's new values (zeros where the matrix ends): their negatives go out along
+// the tile's rows, and along those of its mirror image.
+__device__ __forceinline__ void out_flush(const UpdCtx& c, gfloat* __restrict__ out, const OutPlanes& pl, int I, int J, int n,
+                                          float* __restrict__ stage, int h0) {
+    const int t = threadIdx.x, pr = t >> 5, pc = (t & 31) * 4;
+    const bool planes = pl.base && !c.diag;
+    KFAC_AS1 unsigned char* dst = pl.base + (size_t)(I * n + J) * PRE_SLAB;
+    KFAC_AS1 unsigned char* mir = pl.base + (size_t)(J * n + I) * PRE_SLAB;
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+        const int rl = pr + 8 * p, row = h0 + rl;
+        v4f x;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = -stage[rl * SLD_T + pc + i];
+        if (row < c.irows) put4(out + (size_t)(c.i0 + row) * c.d + c.j0 + pc, x, 0, min(c.jrows - pc, c.diag ? row - pc + 1 : 4));
+        if (planes) store_split4_h2(dst, dst + pl.plane, row, pc, x * pl.scale);
+    }
+    const int mr = (t & 15) * 4, mc = t >> 4;             // four tile rows (neighbours in the mirror image), 16 columns a pass
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+        const int col = mc + 16 * p, row = h0 + mr;
+        const v4f x = {-stage[mr * SLD_T + col], -stage[(mr + 1) * SLD_T + col], -stage[(mr + 2) * SLD_T + col], -stage[(mr + 3) * SLD_T + col]};
+        if (col < c.jrows) put4(out + (size_t)(c.j0 + col) * c.d + c.i0 + row, x, c.diag ? col - row + 1 : 0, c.irows - row);
+        if (planes) store_split4_h2(mir, mir + pl.plane, col, row, x * pl.scale);
+    }
+}
+
+// The planes of diagonal block I, from the output.
+__device__ __forceinline__ void out_diagonal_planes(const gfloat* __restrict__ out, const OutPlanes& pl, int d, int I, int n) {
+    const int t = threadIdx.x, c4 = (t & 31) * 4, rr = t >> 5, r0 = I * NB;
+    KFAC_AS1 unsigned char* dst = pl.base + (size_t)(I * n + I) * PRE_SLAB;
+    v4f v[16];
+    if (r0 + NB <= d) {                                   // all loads go out together (a guard per load would serialise them)
+#pragma unroll
+        for (int p = 0; p < 16; ++p) v[p] = *(const KFAC_AS1 v4f_a4*)(out + (size_t)(r0 + rr + 8 * p) * d + r0 + c4);
     } else {
 #pragma unroll
         for (int p = 0; p < 16; ++p) {
             const int row = r0 + rr + 8 * p;
-            v[p] = load4_guard(X + (size_t)(row < d ? row : 0) * d, row < d, k0 + c4, d);
+            v[p] = load4_guard(out + (size_t)(row < d ? row : 0) * d, row < d, r0 + c4, d);
         }
     }
-    KFAC_AS1 unsigned char* dst = planes + (size_t)blk * PRE_SLAB;
 #pragma unroll
-    for (int p = 0; p < 16; ++p) store_split4_h2(dst, dst + plane, rr + 8 * p, c4, v[p] * sc);
+    for (int p = 0; p < 16; ++p) store_split4_h2(dst, dst + pl.plane, rr + 8 * p, c4, v[p] * pl.scale);
 }
 
-// Planes for the matrices of a call that asked for them (after all their steps have been enqueued on `stream`).
-static int write_planes(const kfac_inverse_item* h, int count, hipStream_t stream) {
-    PlanesBatch b;
-    b.count = 0;
-    b.prefix[0] = 0;
-    for (int i = 0; i <= count; ++i) {
-        if (i < count && h[i].planes) {
-            const int k = b.count++;
-            b.dim[k] = h[i].dim; b.damping[k] = h[i].damping; b.damping_dev[k] = h[i].damping_dev;
-            b.Minv[k] = h[i].Minv; b.planes[k] = h[i].planes;
-            b.prefix[k + 1] = b.prefix[k] + nblk_of(h[i].dim) * nblk_of(h[i].dim);
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) void inv_out_kernel(OutBatch b) {
+    __shared__ __attribute__((aligned(1024))) float lds[UPD_LDS_BYTES / 4];
+    const int total = b.prefix[b.count], per_xcd = (total + 7) >> 3;             // (XCD x: the x-th contiguous eighth)
+    const int lin = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per_xcd || lin >= total) return;
+    int m, tile, I, J;
+    locate(b, lin, m, tile);
+    const int d = b.dim[m], n = nblk_of(d), step = n - 1, nb = d - step * NB;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+    gfloat* out = as_global(b.Minv[m]);
+    OutPlanes pl;
+    pl.base = (KFAC_AS1 unsigned char*)as_global((float*)b.planes[m]);
+    pl.plane = inverse_plane_bytes(d);
+    pl.scale = 1.f;
+    tri_decode_blocked(n, tile, I, J);
+    if (pl.base) {
+        pl.scale = inverse_plane_scale(b.damping_dev[m] ? *as_global(b.damping_dev[m]) : b.damping[m]);
+        gfloat* scales = (gfloat*)(pl.base + 2 * pl.plane);
+        if (t == 0) scales[I * n + J] = scales[J * n + I] = pl.scale;
+    }
+    if (J == step) {                                      // the last pivot block: the pivot code wrote it
+        if (pl.base) out_diagonal_planes(out, pl, d, I, n);
+        return;
+    }
+    const WsView ws = ws_view(as_global((float*)b.ws[m]), d);
+    UpdCtx c;
+    c.W = ws.W; c.ldw = ws.ldw; c.T = ws.T(step % NBUF);
+    c.d = d;
+    c.i0 = I * NB; c.j0 = J * NB;
+    c.irows = I == step ? nb : NB; c.jrows = NB;
+    c.nb = nb;
+    c.diag = I == J;
+    if (I == step) {                                      // block row of the last step: T, transposed
+#pragma unroll 1
+        for (int h0 = 0; h0 < NB; h0 += 64) {             // (rows beyond nb: zeros for the planes)
+            if (h0 > 0) __syncthreads();
+            panel_stage(c, false, h0, SLD_T, lds);
+            __syncthreads();
+            out_flush(c, out, pl, I, J, n, lds, h0);
         }
-        if (b.count == PLMAXB || (i == count && b.count > 0)) {
-            KFAC_LAUNCH(inv_planes_kernel, dim3(b.prefix[b.count]), dim3(256), stream, b);
-            b.count = 0;
+        return;
+    }
+    // The last group's steps, as in group_tile, then the last step.
+    const int lm = lane & 31, h = lane >> 5;
+    const bool dead = c.diag && wm == 0 && wn == 1;
+    int first = b.owed ? (step - 1) / GM * GM : step;
+    OldSrc o = {ws.W + (size_t)c.i0 * ws.ldw + c.j0, ws.ldw, 1};
+    if (I >= first) {
+        first = I + 1;
+        if (I != J) o = OldSrc{ws.T(I % NBUF) + (size_t)c.j0 * NB, 1, NB};
+    } else if (J >= first) {
+        first = J + 1;
+        o = OldSrc{ws.T(J % NBUF) + (size_t)c.i0 * NB, NB, 1};
+    }
+    TileAcc acc, last;
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int nbk = 0; nbk < 2; ++nbk) {
+            const gfloat* src = o.base + (wm * 64 + mb * 32 + 4 * h) * o.rs + (dead ? 0 : (wn * 64 + nbk * 32 + lm) * o.cs);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc.c[mb][nbk][r] = src[((r >> 2) * 8 + (r & 3)) * o.rs];
         }
+    if (first < step) {                                   // (uniform)
+        const float back = tile_mma_presplit(panel_run(ws, first, step - first, I, J), (unsigned char*)lds, acc);
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int nbk = 0; nbk < 2; ++nbk) acc.c[mb][nbk] *= back;
+    }
+    product_f32(c, ws.U(step % NBUF), lds, last);
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
+        if (half == 1) __syncthreads();
+        if (wm == half) {
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int nbk = 0; nbk < 2; ++nbk)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        lds[(mb * 32 + (r >> 2) * 8 + h * 4 + (r & 3)) * SLD_T + acc_col(wn, nbk, lane)] = acc.c[mb][nbk][r] - last.c[mb][nbk][r];
+        }
+        __syncthreads();
+        out_flush(c, out, pl, I, J, n, lds, half * 64);
+    }
+    if (c.diag && pl.base) {
+        __threadfence_block();
+        __syncthreads();                                  // the block is in the output, both triangles
+        out_diagonal_planes(out, pl, d, I, n);
+    }
+}
+
+static int write_outputs(const kfac_inverse_item* h, int count, bool owed, hipStream_t stream) {
+    OutBatch b;
+    b.owed = owed;
+    for (int first = 0; first < count; first += OMAXB) {
+        b.count = min(OMAXB, count - first);
+        b.prefix[0] = 0;
+        for (int i = 0; i < b.count; ++i) {
+            const kfac_inverse_item& it = h[first + i];
+            const int n = nblk_of(it.dim);
+            b.dim[i] = it.dim; b.damping[i] = it.damping; b.damping_dev[i] = it.damping_dev;
+            b.Minv[i] = it.Minv; b.ws[i] = it.ws; b.planes[i] = it.planes;
+            b.prefix[i + 1] = b.prefix[i] + (n > 1 || it.planes ? n * (n + 1) / 2 : 0);
+        }
+        if (b.prefix[b.count] > 0) KFAC_LAUNCH(inv_out_kernel, dim3(8 * ((b.prefix[b.count] + 7) / 8)), dim3(256), stream, b);
     }
     return KFAC_OK;
 }
@@ -1733,7 +1740,10 @@ static int run_group(const kfac_inverse_item* h, int count, hipStream_t stream) 
         if (!together) KFAC_LAUNCH(inv_init_kernel, dim3(b.prefix[n]), dim3(256), stream, b);
         KFAC_LAUNCH(inv_begin_kernel, dim3(n + (together ? b.prefix[n] : 0)), dim3(256), stream, b);
     }
-    if (n_multi == 0) return KFAC_OK;
+    if (n_multi == 0) return write_outputs(h, count, false, stream);
+    int tiles = 0;
+    for (int i = 0; i < n_multi; ++i) tiles += nblk_of(h[i].dim) * (nblk_of(h[i].dim) + 1) / 2;
+    const bool out_owed = tiles >= OUT_OWED;
     // One launch per stage of the matrix with the most blocks.  A matrix with fewer blocks takes
     // its stages at evenly spread launches rather than in the first ones: the tile updates of the whole batch are then
     // spread over all launches, each of which lasts at least as long as a pivot workgroup anyway.
@@ -1744,22 +1754,21 @@ static int run_group(const kfac_inverse_item* h, int count, hipStream_t stream) 
         c.dim[i] = h[i].dim; c.Minv[i] = h[i].Minv; c.ws[i] = h[i].ws; c.info[i] = h[i].info;
     }
     int done[CMAXB] = {};                               // stages taken so far
-    const int launches = nblk_of(h[0].dim) + 1;
+    const int launches = nblk_of(h[0].dim);
     for (int l = 0; l < launches; ++l) {
         for (int i = 0; i < n_multi; ++i) {
-            // (a matrix's last two stages touch all of its tiles, the last one on a slow path: matrices with fewer blocks
-            // than the largest finish at different launches, none with the largest ones)
-            const int n = nblk_of(h[i].dim) + 1;
-            const int span = n == launches ? n : max(n, launches - 2 - 2 * (i % 6));
-            const bool run = l < span && (int)(((long long)(l + 1) * n) / span) > (int)(((long long)l * n) / span);
+            // (a matrix's last stage touches all of its tiles: matrices with fewer blocks than the largest take it at different
+            // launches, none with the largest ones)
+            const int n = nblk_of(h[i].dim), span = n == launches ? n : max(n, launches - 1 - i % 6);
+            const bool run = l < span && (l + 1) * n / span > l * n / span;
             c.stage[i] = run ? done[i] : -1;
-            c.prefix[i + 1] = c.prefix[i] + (run ? plan_workgroups(plan_of(h[i].dim, done[i])) : 0);
+            c.prefix[i + 1] = c.prefix[i] + (run ? plan_workgroups(plan_of(h[i].dim, done[i]), out_owed) : 0);
             done[i] += run;
         }
         const XcdShare sh = xcd_share(n_multi, c.prefix[n_multi]);
         KFAC_LAUNCH(inv_update_kernel, dim3(((n_multi + 7) & ~7) + 8 * max(sh.host, sh.other)), dim3(256), stream, c);
     }
-    return KFAC_OK;
+    return write_outputs(h, count, out_owed, stream);
 }
 
 static size_t ws_bytes_of(int dim) {
@@ -1819,5 +1828,5 @@ extern "C" int kfac_damped_inverse_batched(const kfac_inverse_item* items_host, 
         int rc = run_group(sel, n, (hipStream_t)stream);
         if (rc != KFAC_OK) return rc;
     }
-    return write_planes(items_host, count, (hipStream_t)stream);
+    return KFAC_OK;
 }
