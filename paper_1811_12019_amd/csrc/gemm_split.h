@@ -225,28 +225,86 @@ struct SplitRun {
     int n;                                             // 1 .. MAXN products
 };
 
-// acc[128 x 128] (+)= sum over the products q of A_q B_q^T, A_q / B_q complete 128 x 128 slabs given as piece planes
-// (high x high + high x low + low x high on the fp16 matrix cores).  The products may be scaled differently: acc is
-// brought to product q's scale before it is added to (acc holds the caller's values, at scale 1, on entry), and the
-// returned factor brings it back to scale 1 (the caller multiplies).  lds: PRE_NS * PRE_STAGE bytes, 1 KB aligned.
-// All 256 threads must call; ends with the ring drained and a barrier.
-template <int MAXN>
-__device__ __forceinline__ float tile_mma_presplit(const SplitRun<MAXN>& p, unsigned char* __restrict__ lds, TileAcc& acc) {
-    typedef __attribute__((address_space(3))) unsigned char lds_byte;
+// The loop of the tile products: acc[128 x 128] (+)= sum over nst 16-wide slices.  issue(s, buf): this wavefront's four copies of
+// slice s into ring stage buf; begin(s): called before a product's first slice is multiplied.
+// A slice's operands are read from LDS while the slice before is multiplied, so the ring's three stages hold one slice that is being
+// read and two that are on their way (110 tile products a microsecond on the chip, 98 with each slice read before it is multiplied; four
+// to a visit of a tile in W included 86 against 83).  All 256 threads must call; ends with the ring drained and a barrier.
+template <class Issue, class Begin>
+__device__ __forceinline__ void tile_mma_loop(int nst, Issue&& issue, Begin&& begin, TileAcc& acc) {
     constexpr int NSL = 128 / SPLIT_KS;                // slices per product
-    const int t = threadIdx.x;
-    const int lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1;
     const int lm = lane & 31, h = lane >> 5;
-    lds_byte* l0 = (lds_byte*)lds;
     unsigned a_addr[2], b_addr[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         a_addr[q] = (unsigned)split_plane_offset(wm * 64 + q * 32 + lm, h);
         b_addr[q] = (unsigned)(2 * PRE_BLOCK + split_plane_offset(wn * 64 + q * 32 + lm, h));
     }
+    v4f a[2][2][2], b[2][2][2];                        // [set][block][piece] (16 bytes = 8 fp16 each)
+    auto read = [&](int set, int stage) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int pc = 0; pc < 2; ++pc) {
+                // (the stage's base goes into the address: an instruction offset holds 16 bits only)
+                asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(a[set][q][pc]) : "v"(a_addr[q] + stage * PRE_STAGE), "n"(pc * PRE_BLOCK));
+                asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(b[set][q][pc]) : "v"(b_addr[q] + stage * PRE_STAGE), "n"(pc * PRE_BLOCK));
+            }
+    };
+    static_assert(PRE_NS == 3, "the waits below count younger copies");
+#pragma unroll
+    for (int s = 0; s < PRE_NS; ++s) issue(s, s);
+    asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+    read(0, 0);
+    for (int it = 0; it < nst; it += 2 * PRE_NS) {
+#pragma unroll
+        for (int bi = 0; bi < 2 * PRE_NS; ++bi) {
+            const int s = it + bi;
+            if (s >= nst) break;                                            // uniform
+            // slice s is in registers, slice s + 1 landed (everybody's part): the place of slice s is free
+            const int set = bi & 1;
+            asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier"
+                         : "+v"(a[set][0][0]), "+v"(a[set][0][1]), "+v"(a[set][1][0]), "+v"(a[set][1][1]),
+                           "+v"(b[set][0][0]), "+v"(b[set][0][1]), "+v"(b[set][1][0]), "+v"(b[set][1][1]) :: "memory");
+            read(set ^ 1, (bi + 1) % PRE_NS);
+            issue(s + PRE_NS, bi % PRE_NS);
+            if (s % NSL == 0) begin(s);
+            // smallest terms first
+#pragma unroll
+            for (int term = 0; term < 3; ++term)
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb) {
+                        v8h av, bv;
+                        __builtin_memcpy(&av, &a[set][mb][term == 0 ? 1 : 0], 16);
+                        __builtin_memcpy(&bv, &b[set][nb][term == 1 ? 1 : 0], 16);
+                        acc.c[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv, acc.c[mb][nb], 0, 0, 0);
+                    }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // (the last read's registers are not free before that wait)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier"
+                 : "+v"(a[0][0][0]), "+v"(a[0][0][1]), "+v"(a[0][1][0]), "+v"(a[0][1][1]),
+                   "+v"(b[0][0][0]), "+v"(b[0][0][1]), "+v"(b[0][1][0]), "+v"(b[0][1][1]) :: "memory");
+}
+
+// acc[128 x 128] (+)= sum over the products q of A_q B_q^T, A_q / B_q complete 128 x 128 slabs given as piece planes
+// (high x high + high x low + low x high on the fp16 matrix cores).  The products may be scaled differently: acc is
+// brought to product q's scale before it is added to (acc holds the caller's values, at scale 1, on entry), and the
+// returned factor brings it back to scale 1 (the caller multiplies).  lds: PRE_NS * PRE_STAGE bytes, 1 KB aligned.
+template <int MAXN>
+__device__ __forceinline__ float tile_mma_presplit(const SplitRun<MAXN>& p, unsigned char* __restrict__ lds, TileAcc& acc) {
+    typedef __attribute__((address_space(3))) unsigned char lds_byte;
+    constexpr int NSL = 128 / SPLIT_KS;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    lds_byte* l0 = (lds_byte*)lds;
     const int nst = p.n * NSL;
     const unsigned lane_off = (unsigned)(wave * 1024 + lane * 16);   // this lane's 16 bytes inside every block
-    auto issue = [&](int s, int buf) {
+    float back = 1.0f;
+    tile_mma_loop(nst, [&](int s, int buf) {
         const int sc = s < nst ? s : nst - 1;          // past the end: re-read the last slice (never consumed)
         const int q = sc / NSL, ks = sc - q * NSL;
         const int bq = p.first + q;                    // (first < nbuf, q < nbuf)
@@ -259,146 +317,132 @@ __device__ __forceinline__ float tile_mma_presplit(const SplitRun<MAXN>& p, unsi
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[j] + ks * PRE_BLOCK + lane_off),
                                              (__attribute__((address_space(3))) void*)(l0 + buf * PRE_STAGE + j * PRE_BLOCK + wave * 1024),
                                              16, 0, 0);
-    };
-    float back = 1.0f;
+    }, [&](int s) {
+        float sq = p.scale[0];
 #pragma unroll
-    for (int s = 0; s < PRE_NS - 1; ++s) issue(s, s);
-    for (int it = 0; it < nst; it += PRE_NS) {
+        for (int q = 1; q < MAXN; ++q) sq = s / NSL == q ? p.scale[q] : sq;
+        const float f = sq * back;
 #pragma unroll
-        for (int bi = 0; bi < PRE_NS; ++bi) {
-            const int s = it + bi;
-            if (s >= nst) break;                                            // uniform
-            static_assert(PRE_NS == 3, "the wait below counts (PRE_NS - 2) * 4 younger copies");
-            asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");   // slice s landed (everybody's part)
-            issue(s + PRE_NS - 1, (bi + PRE_NS - 1) % PRE_NS);               // refill the slot slice s - 1 vacated
-            if (s % NSL == 0) {                                              // uniform: a new product begins
-                float sq = p.scale[0];
+        for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-                for (int q = 1; q < MAXN; ++q) sq = s / NSL == q ? p.scale[q] : sq;
-                const float f = sq * back;
-#pragma unroll
-                for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                    for (int nb = 0; nb < 2; ++nb) acc.c[mb][nb] *= f;
-                back = 1.0f / sq;
-            }
-            v4f a[2][2], b[2][2];                                            // (16 bytes = 8 fp16 each)
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int pc = 0; pc < 2; ++pc) {
-                    // (the stage's base goes into the address: an instruction offset holds 16 bits only)
-                    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(a[q][pc]) : "v"(a_addr[q] + bi * PRE_STAGE), "n"(pc * PRE_BLOCK));
-                    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(b[q][pc]) : "v"(b_addr[q] + bi * PRE_STAGE), "n"(pc * PRE_BLOCK));
-                }
-            asm volatile("s_waitcnt lgkmcnt(0)"
-                         : "+v"(a[0][0]), "+v"(a[0][1]), "+v"(a[1][0]), "+v"(a[1][1]),
-                           "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]));
-            // smallest terms first
-#pragma unroll
-            for (int term = 0; term < 3; ++term)
-#pragma unroll
-                for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                    for (int nb = 0; nb < 2; ++nb)
-                    {
-                        v8h av, bv;
-                        __builtin_memcpy(&av, &a[mb][term == 0 ? 1 : 0], 16);
-                        __builtin_memcpy(&bv, &b[nb][term == 1 ? 1 : 0], 16);
-                        acc.c[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv, acc.c[mb][nb], 0, 0, 0);
-                    }
-        }
-    }
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");            // ring idle: the LDS may be reused
+            for (int nb = 0; nb < 2; ++nb) acc.c[mb][nb] *= f;
+        back = 1.0f / sq;
+    }, acc);
     return back;
 }
 
-// The same for half a slab of A: acc[64 x 128] (+)= sum over the products of A_q B_q^T, a_hi pointing at the half slab's rows.
-// Wavefront (wm, wn) holds rows 32 wm .. + 31 of columns 64 wn .. + 63 as two MFMA blocks; scale[q] is that of the wavefront's
-// columns.  A slice is 12 KB (three 1 KB copies a wavefront) in a ring of HALF_NS stages.
-constexpr int HALF_MAXN = 5;
+// The same for half a slab of A: acc[64 x 128] (+)= sum over the products of A_q B_q^T, A's planes pointing at the half slab's rows.
+// Wavefront (wm, wn) holds rows 32 wm .. + 31 of columns 64 wn .. + 63 as two MFMA blocks.  A slice is 12 KB, three 1 KB copies a
+// wavefront (kilobytes 3 wave .. + 2 of a stage: 0, 1 A high, 2, 3 A low, 4 .. 7 B high, 8 .. 11 B low), in a ring of HALF_NS stages: one
+// being read, three on their way.
 constexpr int HALF_STAGE = 3 * PRE_BLOCK;              // A high, A low (half a block each), B high, B low
 constexpr int HALF_NS = 4;
-typedef SplitRun<HALF_MAXN> HalfRun;
 
-__device__ __forceinline__ float half_mma_presplit(const HalfRun& p, unsigned char* __restrict__ lds, v16f (&acc)[2]) {
+struct HalfCopies {
+    const KFAC_AS1 unsigned char* src[3];              // in slice 0 of product 0
+};
+__device__ __forceinline__ HalfCopies half_copies(const KFAC_AS1 unsigned char* a_hi, size_t a_plane, const KFAC_AS1 unsigned char* b_hi,
+                                                  size_t b_plane) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    HalfCopies c;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int kb = 3 * wave + j;
+        c.src[j] = (kb < 4 ? a_hi + (kb >> 1) * a_plane + (kb & 1) * 1024 : b_hi + (kb >= 8 ? b_plane : 0) + (kb & 3) * 1024) + lane * 16;
+    }
+    return c;
+}
+// The three copies of the slice that lies `off` bytes further in both operands' planes.
+__device__ __forceinline__ void half_issue(const HalfCopies& c, size_t off, unsigned char* __restrict__ lds, int buf) {
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
-    constexpr int NSL = 128 / SPLIT_KS;                // slices per product
-    const int t = threadIdx.x;
-    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1;
-    const int lm = lane & 31, h = lane >> 5;
-    lds_byte* l0 = (lds_byte*)lds;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(c.src[j] + off),
+                                         (__attribute__((address_space(3))) void*)((lds_byte*)lds + buf * HALF_STAGE + (3 * wave + j) * 1024),
+                                         16, 0, 0);
+}
+
+template <class Issue, class Begin>
+__device__ __forceinline__ void half_mma_loop(int nst, Issue&& issue, Begin&& begin, v16f (&acc)[2]) {
+    constexpr int NSL = 128 / SPLIT_KS;
+    static_assert(HALF_NS == 4 && NSL % HALF_NS == 0, "the waits below count younger copies; nst is a multiple of HALF_NS");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1, lm = lane & 31, h = lane >> 5;
     const unsigned a_addr = (unsigned)split_plane_offset(wm * 32 + lm, h);
     unsigned b_addr[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) b_addr[q] = (unsigned)(PRE_BLOCK + split_plane_offset(wn * 64 + q * 32 + lm, h));
-    // kilobytes 3 wave .. + 2 of a stage: 0, 1 A high, 2, 3 A low, 4 .. 7 B high, 8 .. 11 B low
-    const KFAC_AS1 unsigned char* src[3];
+    v4f a[2][2], b[2][2][2];                           // [set][piece], [set][block][piece] (16 bytes = 8 fp16 each)
+    auto read = [&](int set, int stage) {
+        asm volatile("ds_read_b128 %0, %1" : "=v"(a[set][0]) : "v"(a_addr + stage * HALF_STAGE));
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(a[set][1]) : "v"(a_addr + stage * HALF_STAGE), "n"(PRE_BLOCK / 2));
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        const int kb = 3 * wave + j;
-        src[j] = (kb < 4 ? p.a_hi + (kb >> 1) * p.plane + (kb & 1) * 1024 : p.b_hi + (kb >= 8 ? p.plane : 0) + (kb & 3) * 1024) + lane * 16;
-    }
-    const int nst = p.n * NSL;
-    auto issue = [&](int s, int buf) {
-        const int sc = s < nst ? s : nst - 1;          // past the end: re-read the last slice (never consumed)
-        const int q = sc / NSL, ks = sc - q * NSL;
-        const int bq = p.first + q;                    // (first < nbuf, q < nbuf)
-        const size_t off = (size_t)(bq >= p.nbuf ? bq - p.nbuf : bq) * p.stride + ks * PRE_BLOCK;
+        for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int j = 0; j < 3; ++j)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[j] + off),
-                                             (__attribute__((address_space(3))) void*)(l0 + buf * HALF_STAGE + (3 * wave + j) * 1024),
-                                             16, 0, 0);
+            for (int pc = 0; pc < 2; ++pc)
+                asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(b[set][q][pc]) : "v"(b_addr[q] + stage * HALF_STAGE), "n"(pc * PRE_BLOCK));
     };
-    float back = 1.0f;
 #pragma unroll
-    for (int s = 0; s < HALF_NS - 1; ++s) issue(s, s);
+    for (int s = 0; s < HALF_NS; ++s) issue(s, s);
+    asm volatile("s_waitcnt vmcnt(9)\n\ts_barrier" ::: "memory");
+    read(0, 0);
     for (int it = 0; it < nst; it += HALF_NS) {
 #pragma unroll
         for (int bi = 0; bi < HALF_NS; ++bi) {
-            const int s = it + bi;                                          // (nst is a multiple of HALF_NS)
-            static_assert(HALF_NS == 4 && NSL % HALF_NS == 0, "the wait below counts (HALF_NS - 2) * 3 younger copies");
-            asm volatile("s_waitcnt vmcnt(6)\n\ts_barrier" ::: "memory");   // slice s landed (everybody's part)
-            issue(s + HALF_NS - 1, (bi + HALF_NS - 1) % HALF_NS);            // refill the slot slice s - 1 vacated
-            if (s % NSL == 0) {                                              // uniform: a new product begins
-                float sq = p.scale[0];
-#pragma unroll
-                for (int q = 1; q < HALF_MAXN; ++q) sq = s / NSL == q ? p.scale[q] : sq;
-                const float f = sq * back;
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb) acc[nb] *= f;
-                back = 1.0f / sq;
-            }
-            v4f a[2], b[2][2];                                               // (16 bytes = 8 fp16 each)
-            asm volatile("ds_read_b128 %0, %1" : "=v"(a[0]) : "v"(a_addr + bi * HALF_STAGE));
-            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(a[1]) : "v"(a_addr + bi * HALF_STAGE), "n"(PRE_BLOCK / 2));
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int pc = 0; pc < 2; ++pc)
-                    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(b[q][pc]) : "v"(b_addr[q] + bi * HALF_STAGE), "n"(pc * PRE_BLOCK));
-            asm volatile("s_waitcnt lgkmcnt(0)"
-                         : "+v"(a[0]), "+v"(a[1]), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]));
+            const int s = it + bi, set = bi & 1;
+            // slice s is in registers, slice s + 1 landed (everybody's part): the place of slice s is free
+            asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier"
+                         : "+v"(a[set][0]), "+v"(a[set][1]), "+v"(b[set][0][0]), "+v"(b[set][0][1]), "+v"(b[set][1][0]), "+v"(b[set][1][1]) :: "memory");
+            read(set ^ 1, (bi + 1) % HALF_NS);
+            issue(s + HALF_NS, bi);
+            if (s % NSL == 0) begin(s);                                      // (uniform: a new product)
             // smallest terms first
 #pragma unroll
             for (int term = 0; term < 3; ++term)
 #pragma unroll
                 for (int nb = 0; nb < 2; ++nb) {
                     v8h av, bv;
-                    __builtin_memcpy(&av, &a[term == 0 ? 1 : 0], 16);
-                    __builtin_memcpy(&bv, &b[nb][term == 1 ? 1 : 0], 16);
+                    __builtin_memcpy(&av, &a[set][term == 0 ? 1 : 0], 16);
+                    __builtin_memcpy(&bv, &b[set][nb][term == 1 ? 1 : 0], 16);
                     acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv, acc[nb], 0, 0, 0);
                 }
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");            // ring idle: the LDS may be reused
+    // (the last read's registers are not free before that wait)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier"
+                 : "+v"(a[0][0]), "+v"(a[0][1]), "+v"(b[0][0][0]), "+v"(b[0][0][1]), "+v"(b[0][1][0]), "+v"(b[0][1][1]) :: "memory");
+}
+
+constexpr int HALF_MAXN = 5;
+typedef SplitRun<HALF_MAXN> HalfRun;                   // (scale[q]: that of the wavefront's columns)
+
+__device__ __forceinline__ float half_mma_presplit(const HalfRun& p, unsigned char* __restrict__ lds, v16f (&acc)[2]) {
+    constexpr int NSL = 128 / SPLIT_KS;
+    const HalfCopies c = half_copies(p.a_hi, p.plane, p.b_hi, p.plane);
+    const int nst = p.n * NSL;
+    float back = 1.0f;
+    half_mma_loop(nst, [&](int s, int buf) {
+        const int sc = s < nst ? s : nst - 1;          // past the end: re-read the last slice (never consumed)
+        const int q = sc / NSL, ks = sc - q * NSL;
+        const int bq = p.first + q;                    // (first < nbuf, q < nbuf)
+        const size_t off = (size_t)(bq >= p.nbuf ? bq - p.nbuf : bq) * p.stride + ks * PRE_BLOCK;
+        half_issue(c, off, lds, buf);
+    }, [&](int s) {
+        float sq = p.scale[0];
+#pragma unroll
+        for (int q = 1; q < HALF_MAXN; ++q) sq = s / NSL == q ? p.scale[q] : sq;
+        const float f = sq * back;
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) acc[nb] *= f;
+        back = 1.0f / sq;
+    }, acc);
     return back;
 }
 
 // A long contraction: product q reads the q-th consecutive 128 x 128 block of its operands' planes (the blocks of one
 // 128-row slab of a matrix stored block by block along the contraction index); scale_lds[q] (LDS, filled and made
-// visible by the caller) is the product of the two blocks' scales.
+// visible by the caller) is the product of the two blocks' scales, for the wavefront's columns.
 struct SplitSeq {
     const KFAC_AS1 unsigned char* a_hi;                // first block of the A slab's high plane
     const KFAC_AS1 unsigned char* b_hi;
@@ -412,8 +456,9 @@ struct SplitSeq {
     __device__ __forceinline__ float scale_of(int q) const { return scale_lds[q]; }
 };
 
-// The same product loop for a long contraction given as a SplitSeq (kept apart from the SplitRun form, whose register
-// allocation inside the sweep's update kernel is tight).
+// The same for a long contraction given as a SplitSeq, each slice read from LDS just before it is multiplied: beside the preconditioner's
+// other registers a second set of operands does not fit three wavefronts per SIMD (16 of them went to scratch memory: both products
+// of ResNet-50's layers 90 us slower).
 __device__ __forceinline__ float tile_mma_presplit_seq(const SplitSeq& p, unsigned char* __restrict__ lds, TileAcc& acc) {
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
     constexpr int NSL = 128 / SPLIT_KS;                // slices per product
@@ -489,6 +534,27 @@ __device__ __forceinline__ float tile_mma_presplit_seq(const SplitSeq& p, unsign
         }
     }
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");            // ring idle: the LDS may be reused
+    return back;
+}
+
+// The same for half a slab of A (a_hi pointing at the half slab's rows).
+__device__ __forceinline__ float half_mma_presplit_seq(const SplitSeq& p, unsigned char* __restrict__ lds, v16f (&acc)[2]) {
+    constexpr int NSL = 128 / SPLIT_KS;
+    const HalfCopies c = half_copies(p.a_hi, p.plane_a, p.b_hi, p.plane_b);
+    const int nst = p.n * NSL;
+    float back = 1.0f;
+    half_mma_loop(nst, [&](int s, int buf) {
+        const int sc = s < nst ? s : nst - 1;          // past the end: re-read the last slice (never consumed)
+        const int q = sc / NSL, ks = sc - q * NSL;
+        const size_t off = (size_t)q * PRE_SLAB + ks * PRE_BLOCK;
+        half_issue(c, off, lds, buf);
+    }, [&](int s) {
+        const float sq = p.scale_of(s / NSL);
+        const float f = sq * back;
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) acc[nb] *= f;
+        back = 1.0f / sq;
+    }, acc);
     return back;
 }
 

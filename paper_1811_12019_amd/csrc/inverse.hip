@@ -30,11 +30,12 @@
 // from operands that the panel launch has already scaled per half slab (64 rows) and split two ways, stored as planes that
 // go to LDS by DMA (gemm_split.h); both to fp32 accuracy.
 //
-// Storage.  The sweep works on a copy W of the matrix in the caller's workspace whose rows are padded to a
-// multiple of 32 floats, so that every 128-wide tile row is a run of whole 128-byte lines, and it keeps only the
-// lower triangle (tiles on or below the diagonal) up to date: the part of block column k that lies above the
-// pivot block is read, transposed, from block row k.  Only the last launch writes the caller's dense output, both
-// triangles, exactly symmetric (the upper one is a copy of the lower one).
+// Storage.  The sweep works on a copy W of the matrix in the caller's workspace that holds only the tiles on and below the diagonal,
+// each as the matrix cores leave it in their registers (WsView::tile): a tile is loaded and stored 16 bytes a lane, a quarter of the
+// memory instructions of a row-major copy.  (A CU stores four lanes a cycle, whatever a lane stores.)  Tiles at the matrix's edge
+// are padded with zeros, which all products leave zero.  The part of block column k above the pivot block is read, transposed, from
+// block row k.  Only the last launch writes the caller's dense output, both triangles, exactly symmetric (the upper one is a copy of
+// the lower one).
 #include "gemm_split.h"
 
 namespace kfac {
@@ -43,8 +44,7 @@ constexpr int NB = 128;          // elimination block = tile edge
 constexpr int MAXB = 64;         // matrices per launch of the kernels that read S (bounded by the 4 KB of kernel arguments)
 constexpr int CMAXB = 112;       // matrices per launch of the sweep's per-step kernels, whose argument block is leaner
 constexpr int UPD_WAVES = 3;     // wavefronts per SIMD the update kernel is compiled for (register budget)
-constexpr int SLD = 132;         // staging stride (floats) for row-wise float4 access
-constexpr int SLD_T = 129;       // staging stride when the stage is also read column-wise
+constexpr int SLD_T = 129;       // staging stride (floats) where the stage is also read column-wise
 constexpr int PH = NB / 2;       // rows of a half slab
 constexpr int UPD_LDS_BYTES = 48 * 1024;   // of a workgroup of the sweep's launches: three of them on a CU
 
@@ -121,7 +121,7 @@ __device__ __forceinline__ void locate(const B& b, int wg, int& m, int& local) {
 }
 
 static inline __host__ __device__ int nblk_of(int dim) { return (dim + NB - 1) / NB; }
-static inline __host__ __device__ int ldw_of(int dim) { return (dim + 31) / 32 * 32; }
+static inline __host__ __device__ size_t working_copy_floats(int dim) { return (size_t)nblk_of(dim) * (nblk_of(dim) + 1) / 2 * NB * NB; }
 
 // Optional second form of the result, for the products that consume the inverse (preconditioning): the matrix cut
 // into 128 x 128 blocks (zero padded), every element scaled by one power of two and split into two fp16 pieces, as two
@@ -244,14 +244,15 @@ __host__ __device__ __forceinline__ void bulk_decode(int n, int g0, int w, int e
 // U, each as a plane of high and a plane of low pieces in the layout of gemm_split.h), which the tile updates multiply.
 constexpr int NBUF = 2 * GM;
 struct WsView {
-    gfloat* W;      // dim x ldw : working copy, lower triangle maintained
-    int ldw;
+    gfloat* W;      // working copy: lower tiles row by row, 64 KB each: 4 x 4 blocks of 32 x 32, float 256 q + 4 lane + i of a block
+                    // being row 8 q + 4 (lane / 32) + i, column lane % 32
     gfloat* buf0;   // NBUF panel buffers, `stride` floats each: U | T | -T high | -T low | U high | U low
     size_t stride;
     size_t plane;   // bytes of one piece plane (d_pad x NB fp16)
     gfloat* P0;     // 2 x NB x NB : inverses of the pivot blocks of even and of odd steps
     gfloat* SC;     // 2 NBUF x 2 nblk: power-of-two scales of the half slabs (64 rows) of T and U of every buffer (gemm_split.h)
     int nblk;
+    __device__ __forceinline__ gfloat* tile(int I, int J) const { return W + (size_t)(I * (I + 1) / 2 + J) * (NB * NB); }
     __device__ __forceinline__ gfloat* P(int step) const { return P0 + (step & 1) * (NB * NB); }
     __device__ __forceinline__ gfloat* U(int q) const { return buf0 + q * stride; }
     __device__ __forceinline__ gfloat* T(int q) const { return buf0 + q * stride + plane / 2; }
@@ -266,15 +267,31 @@ static inline __host__ __device__ size_t panel_buffer_floats(int dim) { return (
 __device__ inline WsView ws_view(gfloat* ws, int dim) {
     const size_t d_pad = (size_t)nblk_of(dim) * NB;
     WsView v;
-    v.ldw = ldw_of(dim);
     v.nblk = nblk_of(dim);
     v.W = ws;
-    v.buf0 = v.W + d_pad * v.ldw;
+    v.buf0 = v.W + working_copy_floats(dim);
     v.stride = panel_buffer_floats(dim);                 // 2 fp32 panels + 4 fp16 planes = 4 d_pad NB floats
     v.plane = d_pad * NB * 2;
     v.P0 = v.buf0 + NBUF * v.stride;
     v.SC = v.P0 + (size_t)2 * NB * NB;
     return v;
+}
+
+// 32 x 32 block (rb, cb) of a tile of W, and a block from / to the accumulators.
+__device__ __forceinline__ gfloat* tile_block(gfloat* tile, int rb, int cb) { return tile + (rb * 4 + cb) * 1024; }
+__device__ __forceinline__ void load_block(const gfloat* blk, v16f& acc) {
+    const gfloat* src = blk + (threadIdx.x & 63) * 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const v4f x = *(const KFAC_AS1 v4f*)(src + q * 256);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[4 * q + i] = x[i];
+    }
+}
+__device__ __forceinline__ void store_block(gfloat* blk, const v16f& acc) {
+    gfloat* dst = blk + (threadIdx.x & 63) * 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *(KFAC_AS1 v4f*)(dst + q * 256) = v4f{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
 }
 
 // ---- pivot block -----------------------------------------------------------------------------------------------
@@ -563,7 +580,7 @@ __device__ __forceinline__ void pivot_write(const v16f (&acc)[2][2], float* __re
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
     const int d = it.dim;
     gfloat* P = ws.P(k0 / NB);
-    if (!last && !from_S && nb == NB) {
+    if (!last) {                                           // (then the block is full)
         // A full block inside the sweep (the look-ahead pivot's usual case) goes out as it lies in the registers: a half-wave's
         // 32 lanes hold 32 consecutive floats of a row, and four registers four consecutive floats of the mirror image's.
         if (wave == 1) return;
@@ -572,13 +589,9 @@ __device__ __forceinline__ void pivot_write(const v16f (&acc)[2][2], float* __re
 #pragma unroll
             for (int nbk = 0; nbk < 2; ++nbk) {
                 if (wm == wn && nbk > mb) continue;            // above the diagonal: not kept
+                store_block(tile_block(ws.tile(k0 / NB, k0 / NB), 2 * wm + mb, 2 * wn + nbk), acc[mb][nbk]);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = acc_row(wm, mb, r, lane), col = acc_col(wn, nbk, lane);
-                    const float x = acc[mb][nbk][r];
-                    ws.W[(size_t)(k0 + row) * ws.ldw + k0 + col] = x;
-                    P[row * NB + col] = -x;
-                }
+                for (int r = 0; r < 16; ++r) P[acc_row(wm, mb, r, lane) * NB + acc_col(wn, nbk, lane)] = -acc[mb][nbk][r];
                 if (wm == wn && nbk == mb) continue;           // a block on the diagonal is its own mirror image
 #pragma unroll
                 for (int r = 0; r < 16; r += 4) {
@@ -608,13 +621,9 @@ __device__ __forceinline__ void pivot_write(const v16f (&acc)[2][2], float* __re
         v4f x;
 #pragma unroll
         for (int i = 0; i < 4; ++i) x[i] = tri[tri_sym(row, min(c4 + i, nb - 1))];
-        if (last) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (c4 + i < nb) it.Minv[(size_t)(k0 + row) * d + k0 + c4 + i] = -x[i];
-        } else {
-            *(KFAC_AS1 v4f*)&ws.W[(size_t)(k0 + row) * ws.ldw + k0 + c4] = x;      // a block that is not last is full
-        }
+        for (int i = 0; i < 4; ++i)
+            if (c4 + i < nb) it.Minv[(size_t)(k0 + row) * d + k0 + c4 + i] = -x[i];
         if (!from_S) *(KFAC_AS1 v4f*)&P[row * NB + c4] = -x;    // (columns beyond a ragged block are never read)
     }
 }
@@ -655,21 +664,22 @@ __device__ __forceinline__ void begin_pivot(const Item& it, float* __restrict__ 
 // triangles (of S's lower one): the pivot code works on whole 32 x 32 diagonal blocks, which the updates keep whole.
 __device__ __forceinline__ void begin_tile(const Item& it, int I, int J, int quarter) {
     const int d = it.dim;
-    const WsView ws = ws_view(it.ws, d);
     const gfloat* __restrict__ S = it.S;
-    const int c = threadIdx.x & 127, rh = threadIdx.x >> 7;
-    const int col = J * NB + c, row0 = I * NB + quarter * 32 + rh;
-    float v[16];
+    const int lane = threadIdx.x & 63, cb = threadIdx.x >> 6;
+    const int c = cb * 32 + (lane & 31), r0 = quarter * 32 + 4 * (lane >> 5);    // inside the tile
+    const int col = J * NB + c;
+    v16f v;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {                       // loads only: arithmetic on a guarded load would make the
-        const int row = row0 + 2 * i;                    // compiler wait for each load in turn
-        v[i] = (row < d && col < d && (I == J || col <= row)) ? S[(size_t)max(row, col) * d + min(row, col)] : 0.f;
+    for (int r = 0; r < 16; ++r) {                       // loads only: arithmetic on a guarded load would make the
+        const int row = I * NB + r0 + (r >> 2) * 8 + (r & 3);            // compiler wait for each load in turn
+        v[r] = row < d && col < d ? S[(size_t)max(row, col) * d + min(row, col)] : 0.f;
     }
+    if (I == J) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int row = row0 + 2 * i;
-        if (row < d && col < ws.ldw) ws.W[(size_t)row * ws.ldw + col] = v[i] + (row == col ? it.damping : 0.f);
+        for (int r = 0; r < 16; ++r)
+            if (r0 + (r >> 2) * 8 + (r & 3) == c) v[r] += it.damping;
     }
+    store_block(tile_block(ws_view(it.ws, d).tile(I, J), quarter, cb), v);
 }
 
 // Half a slab (64 rows) of panel `step`: the scale and the fp16 pieces of U that the tile products read, and U itself.  v[p]: columns
@@ -747,71 +757,7 @@ __global__ __launch_bounds__(256) void inv_init_kernel(Batch b) {
 }
 constexpr int BEGIN_TOGETHER = 768;      // three workgroups to a CU
 
-// One tile (I >= J) of one elimination step.  Tile kinds:
-//   regular      new = old - T_I U_J^T
-//   column       J == k, I > k:  new[a][c] = T[I*128 + a][c]          (block column k below the pivot)
-//   row          I == k, J < k:  new[a][c] = T[J*128 + c][a]          (block row k left of the pivot)
-// Regular tiles go from and to registers (upd_regular_mid_split); column and row tiles pass through an LDS stage, 64 tile rows at a
-// time, so that global accesses are row-wise.
-struct UpdCtx {
-    gfloat* W; int ldw; const gfloat* T;
-    int d, i0, j0, irows, jrows, nb;
-    bool diag;
-};
-
-// stage[rl][c] (64 x sld floats) <- rows h0 .. h0 + 63 of a column or row tile.
-__device__ __forceinline__ void panel_stage(const UpdCtx& c, bool column, int h0, int sld, float* __restrict__ stage) {
-    const int t = threadIdx.x, pr = t >> 5, pc = (t & 31) * 4;
-    // all eight loads go out before the first value is used (a use inside the guarded block would make the
-    // compiler wait for every load in turn)
-    v4f x[8];
-    if (column) {
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int row = h0 + pr + 8 * p;
-            x[p] = v4f{0.f, 0.f, 0.f, 0.f};
-            if (row < c.irows) x[p] = *(const KFAC_AS1 v4f*)&c.T[(size_t)(c.i0 + row) * NB + pc];
-        }
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int rl = pr + 8 * p;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) stage[rl * sld + pc + i] = pc + i < c.nb ? x[p][i] : 0.f;
-        }
-    } else {
-        const int ta = (t & 15) * 4, tc = t >> 4;         // 16 float4 along a (64 a's), 16 c's per pass
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int cc = tc + 16 * p;
-            x[p] = v4f{0.f, 0.f, 0.f, 0.f};
-            if (cc < c.jrows) x[p] = *(const KFAC_AS1 v4f*)&c.T[(size_t)(c.j0 + cc) * NB + h0 + ta];
-        }
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int cc = tc + 16 * p;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) stage[(ta + i) * sld + cc] = h0 + ta + i < c.nb ? x[p][i] : 0.f;
-        }
-    }
-}
-
-__device__ __forceinline__ void upd_panel(const UpdCtx& c, bool column, float* __restrict__ lds) {
-    const int t = threadIdx.x, pr = t >> 5, pc = (t & 31) * 4;
-#pragma unroll 1
-    for (int h0 = 0; h0 < c.irows; h0 += 64) {
-        if (h0 > 0) __syncthreads();
-        panel_stage(c, column, h0, SLD, lds);
-        __syncthreads();
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int rl = pr + 8 * p, row = h0 + rl;
-            if (row < c.irows && c.j0 + pc < c.ldw)
-                *(KFAC_AS1 v4f*)&c.W[(size_t)(c.i0 + row) * c.ldw + c.j0 + pc] = *(const v4f*)&lds[rl * SLD + pc];
-        }
-    }
-}
-
-// acc = T_I . U_J^T of a matrix's last step, fp32, with both operand panels (128 rows x nb floats, row stride 128, zero beyond nb)
+// acc = T . U^T of a matrix's last step, fp32, with both operand slabs (128 rows x nb floats, row stride 128, zero beyond nb)
 // streamed through a 3-stage LDS ring by global_load_lds_dwordx4 (lane i's 16 bytes land at block base + 16 i), so
 // no registers are spent on staging and one barrier per 16-wide K-slab suffices.  Inside a 1 KB block (16 rows x 4
 // chunks of 4 floats) chunk c of row r sits in slot 4 r + (c ^ ((r >> 1) & 3)): the MFMA operand reads (one float4
@@ -826,18 +772,18 @@ static_assert(UNS * USTAGE <= UPD_LDS_BYTES && PRE_NS * PRE_STAGE <= UPD_LDS_BYT
 #define KFAC_LDS_READ128(dst, addr, off) \
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off))
 
-__device__ __forceinline__ void product_f32(const UpdCtx& c, const gfloat* __restrict__ U, float* __restrict__ lds, TileAcc& acc) {
+__device__ __forceinline__ void product_f32(const gfloat* __restrict__ T, const gfloat* __restrict__ U, int nb, bool dead, float* __restrict__ lds,
+                                            TileAcc& acc) {
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
     const int lm = lane & 31, h = lane >> 5;
-    const bool dead = c.diag && wm == 0 && wn == 1;      // strictly above the diagonal, never used
     lds_byte* l0 = (lds_byte*)lds;
 
     // ---- producer: wavefronts 0,1 stream T_I, wavefronts 2,3 stream U_J; four 1 KB blocks each per stage ----
     const int pan = wave >> 1;
     const int drow = lane >> 2, dchunk = (lane & 3) ^ ((lane >> 3) & 3);
-    const gfloat* src0 = (pan == 0 ? c.T + (size_t)c.i0 * NB : U + (size_t)c.j0 * NB) + (size_t)drow * NB + 4 * dchunk;
-    const int nst = (c.nb + UK - 1) / UK;
+    const gfloat* src0 = (pan == 0 ? T : U) + (size_t)drow * NB + 4 * dchunk;
+    const int nst = (nb + UK - 1) / UK;
     auto issue = [&](int s, int buf) {
         const int sc = s < nst ? s : nst - 1;              // past the end: re-read the last slab (never consumed)
 #pragma unroll
@@ -900,19 +846,45 @@ __device__ __forceinline__ void product_f32(const UpdCtx& c, const gfloat* __res
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");            // ring idle: the LDS may be reused
 }
 
-// Where a tile's old values come from: element (a, c) of the tile is base[a * rs + c * cs].
+// Where a tile's old values come from: the working copy, or the T panel of the step that eliminated one of its blocks, as it lies
+// (block column) or transposed (block row).
+enum { OLD_W, OLD_T, OLD_T_TURNED };
 struct OldSrc {
-    const gfloat* base;
-    int rs, cs;
+    int kind;
+    const gfloat* base;      // the tile, or the first of the slab's rows
 };
 
-// Regular tile of a step that is not the matrix's last one: new = old - A0 B0^T - A1 B1^T - ... (one product per pending
-// step, in step order) goes back into the working copy.  Only a matrix's last block can be ragged and the step that eliminates it is its last, so here the pivot
+// Old values of this wavefront's quadrant, in the accumulators' order.  `dead`: the quadrant above the diagonal of a diagonal tile.
+__device__ __forceinline__ void load_old(const OldSrc& o, bool dead, TileAcc& acc) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1;
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int nbk = 0; nbk < 2; ++nbk) {
+            if (dead) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc.c[mb][nbk][r] = 0.f;
+            } else if (o.kind == OLD_W) {                 // (uniform)
+                load_block(o.base + ((2 * wm + mb) * 4 + 2 * wn + nbk) * 1024, acc.c[mb][nbk]);
+            } else if (o.kind == OLD_T) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc.c[mb][nbk][r] = o.base[acc_row(wm, mb, r, lane) * NB + acc_col(wn, nbk, lane)];
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; r += 4) {
+                    const v4f x = *(const KFAC_AS1 v4f*)&o.base[acc_col(wn, nbk, lane) * NB + acc_row(wm, mb, r, lane)];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc.c[mb][nbk][r + i] = x[i];
+                }
+            }
+        }
+}
+
+// The products of a tile, of all steps but the matrix's last one: new = old - A0 B0^T - A1 B1^T - ... (one product per pending
+// step, in step order).  Only a matrix's last block can be ragged and the step that eliminates it is its last, so here the pivot
 // blocks are full (K = 128 per product).  The products run on the fp16 matrix cores with both operands scaled per
-// half slab and split two ways (gemm_split.h): the accumulators start as the tile's old values (fetched straight into MFMA register layout:
-// register r of a 32 x 32 block is 32 consecutive floats of one row per half-wave), the negated products are added,
+// half slab and split two ways (gemm_split.h): the accumulators start as the tile's old values, the negated products are added,
 // and the result is stored from the registers: nothing is staged in LDS.
-// The quadrant above the diagonal of a diagonal tile is not computed.
 constexpr int MAXRUN = GM;               // a tile owes at most one whole group (the group before, or its own so far)
 typedef SplitRun<MAXRUN> PanelRun;
 
@@ -937,70 +909,6 @@ __device__ __forceinline__ PanelRun panel_run(const WsView& ws, int first_step, 
     return r;
 }
 
-__device__ __forceinline__ void upd_regular_mid_split(const UpdCtx& c, const OldSrc& o, const PanelRun& pl,
-                                                      unsigned char* __restrict__ lds) {
-    TileAcc acc;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
-    const int lm = lane & 31, h = lane >> 5;
-    const bool dead = c.diag && wm == 0 && wn == 1;      // strictly above the diagonal, never used
-    gfloat* wtile = c.W + (size_t)c.i0 * c.ldw + c.j0;
-    const int rows_left = c.irows - wm * 64 - 4 * h;     // tile rows from the lane's first row on
-    bool colok[2];
-    gfloat* wq[2];
-    const gfloat* oq[2];
-#pragma unroll
-    for (int nbk = 0; nbk < 2; ++nbk) {
-        colok[nbk] = !dead && c.j0 + wn * 64 + nbk * 32 < c.ldw;
-        wq[nbk] = wtile + (size_t)(wm * 64 + 4 * h) * c.ldw + wn * 64 + nbk * 32 + lm;
-        oq[nbk] = o.base + (wm * 64 + 4 * h) * o.rs + (wn * 64 + nbk * 32 + lm) * o.cs;
-    }
-    // the products run on operands scaled by sa, sb (powers of two): the accumulators follow, exactly
-    // a tile with all its rows and columns, off the diagonal (nearly all of them): no guards, no branches
-    const bool whole = !c.diag && c.irows == NB && c.j0 + NB <= c.ldw;
-    if (whole) {
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc.c[mb][nbk][r] = oq[nbk][(mb * 32 + (r >> 2) * 8 + (r & 3)) * o.rs];
-    } else {
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int dr = mb * 32 + (r >> 2) * 8 + (r & 3);
-                    acc.c[mb][nbk][r] = (colok[nbk] && dr < rows_left) ? oq[nbk][dr * o.rs] : 0.f;
-                }
-    }
-    const float back = tile_mma_presplit(pl, lds, acc);  // (what brings acc back to the scale of the tile)
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nbk = 0; nbk < 2; ++nbk) acc.c[mb][nbk] *= back;
-    if (whole) {
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    wq[nbk][(size_t)(mb * 32 + (r >> 2) * 8 + (r & 3)) * c.ldw] = acc.c[mb][nbk][r];
-    } else {
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int dr = mb * 32 + (r >> 2) * 8 + (r & 3);
-                    if (colok[nbk] && dr < rows_left) wq[nbk][(size_t)dr * c.ldw] = acc.c[mb][nbk][r];
-                }
-    }
-}
-
 // T = U . P for half a slab (64 rows): the fp32 panel and the scaled, negated fp16 pieces that the tile products read, with their
 // scale (returned).  Half slabs: twice the workgroups for a link of the chain that leaves most CUs idle, and half the time in every
 // phase.  The product runs on the bf16 matrix cores with both operands split three ways (panel_product).  pb: P's values
@@ -1019,7 +927,7 @@ __device__ __forceinline__ void half_stage(const v16f (&acc)[2], float* __restri
         for (int r = 0; r < 16; ++r) lds[half_row(wm, r, lane) * PANEL_RLD + acc_col(wn, nbk, lane)] = acc[nbk][r];
 }
 
-__device__ __forceinline__ float slab_T(const WsView& ws, int d, int step, int slab, int half, const v4f (&pb)[8][2], float* __restrict__ lds,
+__device__ __forceinline__ float slab_T(const WsView& ws, int step, int slab, int half, const v4f (&pb)[8][2], float* __restrict__ lds,
                                         float* __restrict__ red) {
     const int t = threadIdx.x, q = step % NBUF, r0 = slab * NB + half * PH;
     const int c4 = (t & 31) * 4, rr = t >> 5;
@@ -1041,7 +949,7 @@ __device__ __forceinline__ float slab_T(const WsView& ws, int d, int step, int s
     for (int p = 0; p < 8; ++p) {
         const int row = rr + 8 * p;
         const v4f x = *(const v4f*)&lds[row * PANEL_RLD + c4];
-        if (r0 + row < d) *(KFAC_AS1 v4f*)&Tc[(size_t)row * NB + c4] = x;
+        *(KFAC_AS1 v4f*)&Tc[(size_t)row * NB + c4] = x;       // (zeros beyond the matrix, as in U)
         store_split4_h2(th, th + ws.plane, half * PH + row, c4, x * -st);
     }
     __threadfence_block();
@@ -1084,50 +992,32 @@ __device__ __forceinline__ void step_slab(const Item& it, int k, int I, int half
         __syncthreads();
     } else {
         panel_fetch_b(ws.P(k), pb);
-        const float st = slab_T(ws, d, k, I, half, pb, lds, red);
+        const float st = slab_T(ws, k, I, half, pb, lds, red);
         if (I == c1) return;                             // (the tile itself is the look-ahead pivot's)
         // Old values of tile (I, k + 1) in the accumulators' order.  Left of the diagonal the tile is stored as (k + 1, I); a block
         // that was eliminated since the working copy was last up to date left it in that step's T.
         int first = chain_from(c1);
-        const int row0 = half * PH + wm * 32 + 4 * h;    // this lane's first row, inside the slab
+        const int ab = 2 * half + wm;                    // this wavefront's block of the slab's rows
         if (I > c1) {
-            const gfloat* src = ws.W + (size_t)(I * NB + row0) * ws.ldw + c1 * NB + wn * 64 + lm;
-            const int left = d - I * NB - row0;
 #pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk) {
+            for (int nbk = 0; nbk < 2; ++nbk) load_block(tile_block(ws.tile(I, c1), ab, 2 * wn + nbk), acc[nbk]);
+        } else if (I >= first) {                         // (first <= I < k)
+            first = I + 1;
+            const gfloat* src = ws.T(I % NBUF) + (size_t)(c1 * NB + wn * 64 + lm) * NB + ab * 32 + 4 * h;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {           // (rows clamped, not guarded: all loads go out together)
-                    const int dr = (r >> 2) * 8 + (r & 3);
-                    acc[nbk][r] = src[(ptrdiff_t)min(dr, left - 1) * ws.ldw + nbk * 32];
-                }
-            }
-            if (left < 32) {
-#pragma unroll
-                for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if ((r >> 2) * 8 + (r & 3) >= left) acc[nbk][r] = 0.f;
-            }
-        } else {
-            const bool in_T = I >= first;                // (first <= I < k)
-            if (in_T) first = I + 1;
-            const gfloat* base = in_T ? ws.T(I % NBUF) + (size_t)c1 * NB * NB : ws.W + (size_t)c1 * NB * ws.ldw + I * NB;
-            const size_t ld = in_T ? NB : ws.ldw;
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk) {
-                const int col = wn * 64 + nbk * 32 + lm;
-                const gfloat* src = base + (size_t)min(col, d - 1 - c1 * NB) * ld + row0;
+            for (int nbk = 0; nbk < 2; ++nbk)
 #pragma unroll
                 for (int r = 0; r < 16; r += 4) {
-                    const v4f x = *(const KFAC_AS1 v4f*)(src + 2 * r);
+                    const v4f x = *(const KFAC_AS1 v4f*)(src + nbk * (32 * NB) + 2 * r);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) acc[nbk][r + i] = x[i];
                 }
-                if (c1 * NB + col >= d) {
+        } else {
+            const gfloat* tile = ws.tile(c1, I) + (lm >> 3) * 256 + ((lm >> 2) & 1) * 128 + (lm & 3) + 16 * h;
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[nbk][r] = 0.f;
-                }
-            }
+            for (int nbk = 0; nbk < 2; ++nbk)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[nbk][r] = tile[((2 * wn + nbk) * 4 + ab) * 1024 + (r >> 2) * 32 + (r & 3) * 4];
         }
         const float back = half_mma_presplit(half_run(ws, first, k, I, half, c1, st), (unsigned char*)lds, acc);
 #pragma unroll
@@ -1140,24 +1030,12 @@ __device__ __forceinline__ void step_slab(const Item& it, int k, int I, int half
             for (int p = 0; p < 8; ++p) v[p] = *(const v4f*)&lds[((t >> 5) + 8 * p) * PANEL_RLD + (t & 31) * 4];
             put_panel(ws, c1, I, half, v, red);
             // the diagonal tile of block k + 2: steps k - 1 and k
-            gfloat* dst = ws.W + (size_t)(I * NB + row0) * ws.ldw + I * NB + wn * 64 + lm;
-            const int left = d - I * NB - row0;
-            const bool col_ok[2] = {I * NB + wn * 64 < ws.ldw, I * NB + wn * 64 + 32 < ws.ldw};
+            gfloat* tile = ws.tile(I, I);
 #pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int dr = (r >> 2) * 8 + (r & 3);
-                    acc[nbk][r] = dr < left && col_ok[nbk] ? dst[(size_t)dr * ws.ldw + nbk * 32] : 0.f;
-                }
+            for (int nbk = 0; nbk < 2; ++nbk) load_block(tile_block(tile, ab, 2 * wn + nbk), acc[nbk]);
             const float back2 = half_mma_presplit(half_run(ws, max(0, k - 1), k, I, half, I, st), (unsigned char*)lds, acc);
 #pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int dr = (r >> 2) * 8 + (r & 3);
-                    if (dr < left && col_ok[nbk]) dst[(size_t)dr * ws.ldw + nbk * 32] = acc[nbk][r] * back2;
-                }
+            for (int nbk = 0; nbk < 2; ++nbk) store_block(tile_block(tile, ab, 2 * wn + nbk), acc[nbk] * back2);
             return;
         }
     }
@@ -1176,7 +1054,7 @@ __device__ __forceinline__ void last_slab(const Item& it, int k, int I, int half
     if (nb == NB) {
         v4f pb[8][2];
         panel_fetch_b(ws.P(k), pb);
-        slab_T(ws, d, k, I, half, pb, lds, red);
+        slab_T(ws, k, I, half, pb, lds, red);
         return;
     }
     if (half == 1) return;
@@ -1206,7 +1084,7 @@ __device__ __forceinline__ void last_slab(const Item& it, int k, int I, int half
 constexpr int PUP_RING = PANEL_B_LDS;                    // LDS: P's pieces (panel_stash), then three slices of U's; later six
 static_assert(PUP_RING + 3 * 2 * PRE_BLOCK <= UPD_LDS_BYTES && 10 * 4096 <= UPD_LDS_BYTES, "the kernel's LDS");
 
-__device__ __forceinline__ void pivot_update(const WsView& ws, int step, int nb, unsigned char* __restrict__ lds, v16f (&acc)[2][2]) {
+__device__ __forceinline__ void pivot_update(const WsView& ws, int step, unsigned char* __restrict__ lds, v16f (&acc)[2][2]) {
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
     const int kn = step + 1, q = step % NBUF;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), lm = lane & 31, h = lane >> 5;
@@ -1246,13 +1124,8 @@ __device__ __forceinline__ void pivot_update(const WsView& ws, int step, int nb,
 #pragma unroll
     for (int s = 0; s < 3; ++s) copy_slice(s, PUP_RING + s * 2 * PRE_BLOCK);
     // the tile's old values, into this XCD's L2: two of its 512 cache lines a thread
-    const gfloat* wtile = ws.W + (size_t)kn * NB * ws.ldw + kn * NB;
-    float touch[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int row = min(t >> 1, nb - 1), col = ((t & 1) * 2 + i) * 32;
-        touch[i] = wtile[(size_t)row * ws.ldw + (col < nb ? col : 0)];
-    }
+    gfloat* wtile = ws.tile(kn, kn);
+    const float touch[2] = {wtile[t * 64], wtile[t * 64 + 32]};
     unsigned a_off[4];
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) a_off[kb] = (unsigned)split_plane_offset(kb * 32 + lm, h);
@@ -1353,11 +1226,7 @@ __device__ __forceinline__ void pivot_update(const WsView& ws, int step, int nb,
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
             for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {            // (clamped, not guarded: all loads go out together)
-                    const int row = min(acc_row(wm, mb, r, lane), nb - 1), col = min(acc_col(wn, nbk, lane), nb - 1);
-                    acc[mb][nbk][r] = wtile[(size_t)row * ws.ldw + col];
-                }
+                if (2 * wn + nbk <= 2 * wm + mb) load_block(tile_block(wtile, 2 * wm + mb, 2 * wn + nbk), acc[mb][nbk]);
     }
     // ---- to the wavefronts that hold the quadrants, block by block in register order
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");          // U's pieces are done with
@@ -1395,49 +1264,52 @@ __device__ __forceinline__ void step_pivot(const Item& it, int step, float* __re
     const int d = it.dim, k0 = (step + 1) * NB, nb = min(NB, d - k0);
     const WsView ws = ws_view(it.ws, d);
     v16f acc[2][2];
-    pivot_update(ws, step, nb, (unsigned char*)lds, acc);
+    pivot_update(ws, step, (unsigned char*)lds, acc);
     if (nb < NB) pivot_border(acc, nb);                  // (uniform)
     const int f = pivot_sweep(acc, nb, lds);
     if (threadIdx.x == 0 && it.info && f != 0) atomicCAS((int*)it.info, 0, k0 + f);
     pivot_write(acc, lds, it, ws, k0, nb, k0 + NB >= d, false);
 }
 
-// Tile (I, J) of a step that is not the matrix's last: brings it up to date through step kq = g.g0 + g.j of group g.
-// single: the tile has been kept up to date step by step (a diagonal tile inside a group): it sees step kq only, and its old value
-// is in the working copy.  Otherwise it sees all of the group's steps up to kq that it has not seen yet: all of them
-// for a tile with no index inside the group.  A tile with an index inside the group was kept up to date until its
-// later such index c was eliminated (when it became part of panel c: T_I for a tile of block column c, T_J transposed
-// for a tile of block row c, neither written to the working copy then), and sees the steps after c; the diagonal tile
-// (c, c) is -P_c, which the pivot code did write.
-__device__ __forceinline__ void group_tile(const Item& it, const WsView& ws, int I, int J, const Group& g, bool single,
-                                           float* __restrict__ lds) {
-    const int kq = g.g0 + g.j;
-    const int gbuf = g.g0 % NBUF;                        // buffer of the group's first step
-    UpdCtx c;
-    c.W = ws.W; c.ldw = ws.ldw; c.T = ws.T(gbuf + g.j);
-    c.d = it.dim;
-    c.i0 = I * NB; c.j0 = J * NB;
-    c.irows = min(NB, c.d - c.i0); c.jrows = min(NB, c.d - c.j0);
-    c.nb = NB;                                           // (only a matrix's last block can be ragged)
-    c.diag = I == J;
-    if (J == kq || I == kq) {                            // block column / row kq becomes the panel
-        upd_panel(c, J == kq, lds);
-        return;
+// The first step that tile (I, J) owes of the steps lo .. hi, and where its old values are: the working copy, unless one of its blocks
+// is among lo .. hi.  Such a tile was kept up to date until its later such block c was eliminated (when it became part of panel c:
+// T_I for a tile of block column c, T_J transposed for one of block row c, neither written to the working copy then), and owes the
+// steps after c; the diagonal tile (c, c) is -P_c, which the pivot code did write.
+__device__ __forceinline__ int owed_from(const WsView& ws, int I, int J, int lo, int hi, OldSrc& o) {
+    if (I >= lo && I <= hi) {                            // I is the later block (I >= J)
+        if (I != J) o = OldSrc{OLD_T_TURNED, ws.T(I % NBUF) + (size_t)J * (NB * NB)};
+        return I + 1;
     }
-    OldSrc o = {ws.W + (size_t)c.i0 * ws.ldw + c.j0, ws.ldw, 1};
-    int first = g.j;                                     // steps first .. g.j of the group, in order
-    if (!single) {
-        const bool inI = I >= g.g0 && I < kq, inJ = J >= g.g0 && J < kq;
-        first = 0;
-        if (inI) {                                       // I is the later index (I >= J)
-            first = I - g.g0 + 1;
-            if (I != J) o = OldSrc{ws.T(gbuf + I - g.g0) + (size_t)c.j0 * NB, 1, NB};
-        } else if (inJ) {                                // I lies beyond the group
-            first = J - g.g0 + 1;
-            o = OldSrc{ws.T(gbuf + J - g.g0) + (size_t)c.i0 * NB, NB, 1};
-        }
+    if (J >= lo && J <= hi) {                            // I lies beyond
+        o = OldSrc{OLD_T, ws.T(J % NBUF) + (size_t)I * (NB * NB)};
+        return J + 1;
     }
-    upd_regular_mid_split(c, o, panel_run(ws, g.g0 + first, g.j - first + 1, I, J), (unsigned char*)lds);
+    return lo;
+}
+
+// Tile (I, J) of a step that is not the matrix's last: brings it up to date through step g.g0 + g.j.
+// single: the tile has been kept up to date step by step (a diagonal tile inside a group): it sees that step only, and its old value
+// is in the working copy.  Otherwise it sees all of the group's steps up to it that it has not seen yet.
+__device__ __forceinline__ void group_tile(const WsView& ws, int I, int J, const Group& g, bool single, float* __restrict__ lds) {
+    const int kq = g.g0 + g.j, wave = threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1;
+    const bool dead = I == J && wave == 1;
+    OldSrc o = {OLD_W, ws.tile(I, J)};
+    int first = kq;                                      // steps first .. kq, in order
+    if (!single) first = owed_from(ws, I, J, g.g0, kq, o);
+    TileAcc acc;
+    load_old(o, dead, acc);
+    if (first <= kq) {                                   // (uniform)
+        const float back = tile_mma_presplit(panel_run(ws, first, kq - first + 1, I, J), (unsigned char*)lds, acc);
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int nbk = 0; nbk < 2; ++nbk) acc.c[mb][nbk] *= back;
+    }
+    if (dead) return;
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int nbk = 0; nbk < 2; ++nbk) store_block(tile_block(ws.tile(I, J), 2 * wm + mb, 2 * wn + nbk), acc.c[mb][nbk]);
 }
 
 // How the work list is dealt to the XCDs: equal shares, but where few matrices' look-ahead pivots run on few XCDs and the others can
@@ -1512,7 +1384,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UPD_WAVES, 
         g.g0 = pl.g0 - GM;                               // (the whole group before, whatever the diagonal tiles see)
         g.j = GM - 1;
     }
-    group_tile(it, ws_view(it.ws, it.dim), I, J, g, single, lds);
+    group_tile(ws_view(it.ws, it.dim), I, J, g, single, lds);
 }
 
 // ---- output ----------------------------------------------------------------------------------------------------------
@@ -1556,10 +1428,10 @@ __device__ __forceinline__ void put4(gfloat* dst, const v4f& x, int from, int n)
 
 // stage (64 x SLD_T floats) holds rows h0 .. h0 + 63 of a tile's new values (zeros where the matrix ends): their negatives go out along
 // the tile's rows, and along those of its mirror image.
-__device__ __forceinline__ void out_flush(const UpdCtx& c, gfloat* __restrict__ out, const OutPlanes& pl, int I, int J, int n,
-                                          float* __restrict__ stage, int h0) {
-    const int t = threadIdx.x, pr = t >> 5, pc = (t & 31) * 4;
-    const bool planes = pl.base && !c.diag;
+__device__ __forceinline__ void out_flush(gfloat* __restrict__ out, const OutPlanes& pl, int d, int I, int J, int n, const float* __restrict__ stage,
+                                          int h0) {
+    const int t = threadIdx.x, pr = t >> 5, pc = (t & 31) * 4, i0 = I * NB, j0 = J * NB, irows = min(NB, d - i0);   // (all columns are there)
+    const bool diag = I == J, planes = pl.base && !diag;
     KFAC_AS1 unsigned char* dst = pl.base + (size_t)(I * n + J) * PRE_SLAB;
     KFAC_AS1 unsigned char* mir = pl.base + (size_t)(J * n + I) * PRE_SLAB;
 #pragma unroll
@@ -1568,7 +1440,7 @@ __device__ __forceinline__ void out_flush(const UpdCtx& c, gfloat* __restrict__ 
         v4f x;
 #pragma unroll
         for (int i = 0; i < 4; ++i) x[i] = -stage[rl * SLD_T + pc + i];
-        if (row < c.irows) put4(out + (size_t)(c.i0 + row) * c.d + c.j0 + pc, x, 0, min(c.jrows - pc, c.diag ? row - pc + 1 : 4));
+        if (row < irows) put4(out + (size_t)(i0 + row) * d + j0 + pc, x, 0, diag ? row - pc + 1 : 4);
         if (planes) store_split4_h2(dst, dst + pl.plane, row, pc, x * pl.scale);
     }
     const int mr = (t & 15) * 4, mc = t >> 4;             // four tile rows (neighbours in the mirror image), 16 columns a pass
@@ -1576,7 +1448,7 @@ __device__ __forceinline__ void out_flush(const UpdCtx& c, gfloat* __restrict__ 
     for (int p = 0; p < 8; ++p) {
         const int col = mc + 16 * p, row = h0 + mr;
         const v4f x = {-stage[mr * SLD_T + col], -stage[(mr + 1) * SLD_T + col], -stage[(mr + 2) * SLD_T + col], -stage[(mr + 3) * SLD_T + col]};
-        if (col < c.jrows) put4(out + (size_t)(c.j0 + col) * c.d + c.i0 + row, x, c.diag ? col - row + 1 : 0, c.irows - row);
+        put4(out + (size_t)(j0 + col) * d + i0 + row, x, diag ? col - row + 1 : 0, irows - row);
         if (planes) store_split4_h2(mir, mir + pl.plane, col, row, x * pl.scale);
     }
 }
@@ -1625,44 +1497,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
         return;
     }
     const WsView ws = ws_view(as_global((float*)b.ws[m]), d);
-    UpdCtx c;
-    c.W = ws.W; c.ldw = ws.ldw; c.T = ws.T(step % NBUF);
-    c.d = d;
-    c.i0 = I * NB; c.j0 = J * NB;
-    c.irows = I == step ? nb : NB; c.jrows = NB;
-    c.nb = nb;
-    c.diag = I == J;
+    const gfloat* T = ws.T(step % NBUF);
     if (I == step) {                                      // block row of the last step: T, transposed
 #pragma unroll 1
-        for (int h0 = 0; h0 < NB; h0 += 64) {             // (rows beyond nb: zeros for the planes)
+        for (int h0 = 0; h0 < NB; h0 += 64) {             // (rows beyond nb: zeros, for the planes)
             if (h0 > 0) __syncthreads();
-            panel_stage(c, false, h0, SLD_T, lds);
+            const int ta = (t & 15) * 4, tc = t >> 4;     // 16 float4 along the tile's rows, 16 columns a pass
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                const int cc = tc + 16 * p;
+                const v4f x = *(const KFAC_AS1 v4f*)&T[(size_t)(J * NB + cc) * NB + h0 + ta];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) lds[(ta + i) * SLD_T + cc] = h0 + ta + i < nb ? x[i] : 0.f;
+            }
             __syncthreads();
-            out_flush(c, out, pl, I, J, n, lds, h0);
+            out_flush(out, pl, d, I, J, n, lds, h0);
         }
         return;
     }
     // The last group's steps, as in group_tile, then the last step.
-    const int lm = lane & 31, h = lane >> 5;
-    const bool dead = c.diag && wm == 0 && wn == 1;
-    int first = b.owed ? (step - 1) / GM * GM : step;
-    OldSrc o = {ws.W + (size_t)c.i0 * ws.ldw + c.j0, ws.ldw, 1};
-    if (I >= first) {
-        first = I + 1;
-        if (I != J) o = OldSrc{ws.T(I % NBUF) + (size_t)c.j0 * NB, 1, NB};
-    } else if (J >= first) {
-        first = J + 1;
-        o = OldSrc{ws.T(J % NBUF) + (size_t)c.i0 * NB, NB, 1};
-    }
+    const int h = lane >> 5;
+    const bool dead = I == J && wave == 1;
+    OldSrc o = {OLD_W, ws.tile(I, J)};
+    const int first = b.owed ? owed_from(ws, I, J, (step - 1) / GM * GM, step - 1, o) : step;
     TileAcc acc, last;
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nbk = 0; nbk < 2; ++nbk) {
-            const gfloat* src = o.base + (wm * 64 + mb * 32 + 4 * h) * o.rs + (dead ? 0 : (wn * 64 + nbk * 32 + lm) * o.cs);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc.c[mb][nbk][r] = src[((r >> 2) * 8 + (r & 3)) * o.rs];
-        }
+    load_old(o, dead, acc);
     if (first < step) {                                   // (uniform)
         const float back = tile_mma_presplit(panel_run(ws, first, step - first, I, J), (unsigned char*)lds, acc);
 #pragma unroll
@@ -1670,7 +1529,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
 #pragma unroll
             for (int nbk = 0; nbk < 2; ++nbk) acc.c[mb][nbk] *= back;
     }
-    product_f32(c, ws.U(step % NBUF), lds, last);
+    product_f32(T + (size_t)I * (NB * NB), ws.U(step % NBUF) + (size_t)J * (NB * NB), nb, dead, lds, last);
 #pragma unroll 1
     for (int half = 0; half < 2; ++half) {
         if (half == 1) __syncthreads();
@@ -1684,9 +1543,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
                         lds[(mb * 32 + (r >> 2) * 8 + h * 4 + (r & 3)) * SLD_T + acc_col(wn, nbk, lane)] = acc.c[mb][nbk][r] - last.c[mb][nbk][r];
         }
         __syncthreads();
-        out_flush(c, out, pl, I, J, n, lds, half * 64);
+        out_flush(out, pl, d, I, J, n, lds, half * 64);
     }
-    if (c.diag && pl.base) {
+    if (I == J && pl.base) {
         __threadfence_block();
         __syncthreads();                                  // the block is in the output, both triangles
         out_diagonal_planes(out, pl, d, I, n);
@@ -1773,8 +1632,7 @@ static int run_group(const kfac_inverse_item* h, int count, hipStream_t stream) 
 
 static size_t ws_bytes_of(int dim) {
     if (nblk_of(dim) == 1) return 256;
-    const size_t d_pad = (size_t)nblk_of(dim) * NB;
-    return align_up((d_pad * ldw_of(dim) + NBUF * panel_buffer_floats(dim) + (size_t)2 * NB * NB + 4 * NBUF * (size_t)nblk_of(dim)) * sizeof(float), 256);
+    return align_up((working_copy_floats(dim) + NBUF * panel_buffer_floats(dim) + (size_t)2 * NB * NB + 4 * NBUF * (size_t)nblk_of(dim)) * sizeof(float), 256);
 }
 
 static bool item_ok(const kfac_inverse_item& it) {
