@@ -64,7 +64,7 @@ def kernel_work(net: kstep.KfacNetworkStep, kernels):
                                   - kstep.inverse_first_pivot_flops(d) for d in dims)),
         # one workgroup per matrix: first-block inverses of nb^3 flops
         "inv_begin_kernel": ("mfma", PEAK["mfma_f32"], "TFLOP/s", sum(kstep.inverse_first_pivot_flops(d) for d in dims)),
-        "gemm_nt_kernel": ("mfma", PEAK["mfma_f16x2"], "TFLOP/s", sum(kstep.precondition_flops(s.d_G, s.d_A) for s in shapes)),
+        "gemm_nt_kernel<false>": ("mfma", PEAK["mfma_f16x2"], "TFLOP/s", sum(kstep.precondition_flops(s.d_G, s.d_A) for s in shapes)),
         # the gradient's piece planes: every element read (4 B) and written (2 x 2 B)
         "pre_split_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(8.0 * s.d_G * s.d_A for s in shapes)),
         # lower triangles read, inverses written as squares and as piece planes

@@ -34,7 +34,7 @@ struct PBatch {
 
 // A matrix of r x k elements as planes: ceil(r / 128) slabs of ceil(k / 128) blocks of 128 x 128 (zero padded), block
 // (s, c) at ((s * chunks + c) * PRE_SLAB) bytes in the plane of high pieces and in the plane of low pieces that
-// follows it, then one float per block: its scale.  The four plane sets of a layer (Ainv, Ginv, gradW: dG x dA, Yt:
+// follows it, then one float per block: its scale (Yt: two, one for each 64 rows).  The four plane sets of a layer (Ainv, Ginv, gradW: dG x dA, Yt:
 // dA x dG) live one after the other in its scratch; the inverses' may instead be the ones the inversion wrote.
 struct PlaneSet {
     KFAC_AS1 unsigned char* hi;
@@ -60,7 +60,7 @@ static inline __host__ __device__ PlaneLayout plane_layout(int dG, int dA) {
     L.g_off = L.a_off + plane_set_bytes(L.a_plane, L.nA * L.nA);
     L.w_off = L.g_off + plane_set_bytes(L.g_plane, L.nG * L.nG);
     L.y_off = L.w_off + plane_set_bytes(L.w_plane, L.nG * L.nA);
-    L.bytes = L.y_off + plane_set_bytes(L.w_plane, L.nG * L.nA);
+    L.bytes = L.y_off + plane_set_bytes(L.w_plane, 2 * L.nG * L.nA);
     return L;
 }
 struct LayerPlanes { PlaneSet a, g, w, y; };
@@ -140,14 +140,24 @@ __global__ __launch_bounds__(256) void pre_split_kernel(PBatch b) {
 }
 
 // phase 1: Yt[dA x dG] = Ainv . gradW^T (written as planes)      phase 2: out[dG x dA] = Ginv . Yt^T
+// A workgroup makes a 128 x 128 tile, or (HALF) 64 x 128 of one.  Full tiles move 2 / 3 of the bytes per product; half tiles take half
+// as long, which is what counts while there are not enough tiles for the chip (HALF_TILES).
+constexpr int HALF_TILES = 256;          // launches of up to so many tiles (one to a CU) are made of half tiles
+
+template <bool HALF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void gemm_nt_kernel(PBatch b, int phase) {
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[PRE_NS * PRE_STAGE];
-    __shared__ float sc[256];
+    constexpr int LDS = PRE_NS * PRE_STAGE;
+    static_assert(HALF_NS * HALF_STAGE <= LDS, "both rings fit");
+    constexpr int MB = HALF ? 1 : 2;                     // 32 x 32 blocks down a wavefront's part
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS];
+    __shared__ float sc[2 * 256];
     __shared__ float red[4];
     int local;
     const kfac_precond_item it = locate_item(b, blockIdx.x, local);
     const PlaneLayout L = plane_layout(it.dG, it.dA);
     const LayerPlanes P = layer_planes(it, L);
+    const int half = HALF ? local & 1 : 0;
+    if (HALF) local >>= 1;
     // Workgroups go to the 8 XCDs round-robin, each with an L2 of its own.  Inside a block of 8 tile rows, the eight
     // XCDs take one tile row each and walk along it: the tiles that share an A slab (128 rows of the inverse, the
     // large operand when the contraction is long) run on one L2, side by side, instead of on all eight.
@@ -155,6 +165,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
     const int blk = local / (8 * tn), within = local - blk * 8 * tn;
     const int rb = min(8, tm - 8 * blk);
     const int ti = 8 * blk + within % rb, tj = within / rb;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1;
     SplitSeq run;
     const gfloat *sa, *sb;
     if (phase == 1) {
@@ -166,38 +177,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
         run.n = L.nG;
         run.a_hi = P.g.hi + (size_t)ti * L.nG * PRE_SLAB; run.plane_a = P.g.plane;
         run.b_hi = P.y.hi + (size_t)tj * L.nG * PRE_SLAB; run.plane_b = P.y.plane;
-        sa = P.g.scales() + ti * L.nG; sb = P.y.scales() + tj * L.nG;
+        sa = P.g.scales() + ti * L.nG; sb = P.y.scales() + 2 * tj * L.nG;
     }
-    run.scale_lds = sc;
-    const int t = threadIdx.x;
-    if (t < run.n) sc[t] = sa[t] * sb[t];                // (at most 256 blocks along a contraction: dimensions end at 32768)
-    TileAcc acc;
+    run.a_hi += half * (PRE_BLOCK / 2);
+    run.scale_lds = sc + wn * 256;                       // (Yt's scales: the wavefront's columns are 64 rows of it)
+    if (t < run.n) {                                     // (at most 256 blocks along a contraction: dimensions end at 32768)
+        sc[t] = sa[t] * sb[phase == 1 ? t : 2 * t];
+        sc[256 + t] = sa[t] * sb[phase == 1 ? t : 2 * t + 1];
+    }
+    v16f acc[MB][2];
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc.c[mb][nb][r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.f;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (the product counts its own copies in flight)
     __syncthreads();
-    const float back = tile_mma_presplit_seq(run, lds, acc);
+    float back;
+    if constexpr (HALF) back = half_mma_presplit_seq(run, lds, acc[0]);
+    else back = tile_mma_presplit_seq(run, lds, *(TileAcc*)&acc);
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) acc.c[mb][nb] *= back;
-    const int lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+        for (int nb = 0; nb < 2; ++nb) acc[mb][nb] *= back;
+    auto row_of = [&](int mb, int r) { return half * 64 + wm * (32 * MB) + mb * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3); };   // in the tile
     if (phase == 2) {
         gfloat* C = as_global(it.out);
         const int i0 = ti * TM, j0 = tj * TM;
         const int irows = min(TM, it.dG - i0), jrows = min(TM, it.dA - j0);
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    int row = acc_row(wm, mb, r, lane), col = acc_col(wn, nb, lane);
-                    if (row < irows && col < jrows) C[(size_t)(i0 + row) * it.dA + j0 + col] = acc.c[mb][nb][r];
+                    int row = row_of(mb, r), col = acc_col(wn, nb, lane);
+                    if (row < irows && col < jrows) C[(size_t)(i0 + row) * it.dA + j0 + col] = acc[mb][nb][r];
                 }
         return;
     }
@@ -205,37 +221,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
     // four consecutive values of a row (rows and columns beyond the matrix are exact zeros: their operands were).
     float m = 0.f;
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) m = fmaxf(m, fabsf(acc.c[mb][nb][r]));
+            for (int r = 0; r < 16; ++r) m = fmaxf(m, fabsf(acc[mb][nb][r]));
     const float sy = panel_scale(block_absmax(m, red));
     const int blkidx = ti * L.nG + tj;
-    if (t == 0) P.y.scales()[blkidx] = sy;
+    if (t < MB) P.y.scales()[2 * blkidx + half + t] = sy;
     KFAC_AS1 unsigned char* yh = P.y.hi + (size_t)blkidx * PRE_SLAB;
     constexpr int RLD = TM + 4;
     float* stage = (float*)lds;
-    static_assert(64 * RLD * 4 <= PRE_NS * PRE_STAGE, "half a tile fits the ring's memory");
+    static_assert(64 * RLD * 4 <= LDS, "half a tile fits the ring's memory");
     const int c4 = (t & 31) * 4, rr = t >> 5;
 #pragma unroll 1
-    for (int half = 0; half < 2; ++half) {
-        if (half == 1) __syncthreads();
-        if (wm == half) {
+    for (int part = 0; part < MB; ++part) {
+        if (part == 1) __syncthreads();
+        if (HALF || wm == part) {
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        stage[(acc_row(0, mb, r, lane)) * RLD + acc_col(wn, nb, lane)] = acc.c[mb][nb][r];
+                    for (int r = 0; r < 16; ++r) stage[(row_of(mb, r) & 63) * RLD + acc_col(wn, nb, lane)] = acc[mb][nb][r];
         }
         __syncthreads();
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
             const int row = rr + 8 * p;
             const v4f x = *(const v4f*)&stage[row * RLD + c4];
-            store_split4_h2(yh, yh + P.y.plane, half * 64 + row, c4, x * sy);
+            store_split4_h2(yh, yh + P.y.plane, (half + part) * 64 + row, c4, x * sy);
         }
     }
 }
@@ -271,7 +286,12 @@ static int run_group(const kfac_precond_item* host, const kfac_precond_item* dev
             const kfac_precond_item& it = host[first + b.order[i]];
             b.prefix[i + 1] = b.prefix[i] + (phase == 1 ? tiles_of(it.dA, it.dG) : tiles_of(it.dG, it.dA));
         }
-        KFAC_LAUNCH(gemm_nt_kernel, dim3(b.prefix[count]), dim3(256), stream, b, phase);
+        if (b.prefix[count] <= HALF_TILES) {
+            for (int i = 0; i <= count; ++i) b.prefix[i] *= 2;
+            KFAC_LAUNCH(gemm_nt_kernel<true>, dim3(b.prefix[count]), dim3(256), stream, b, phase);
+        } else {
+            KFAC_LAUNCH(gemm_nt_kernel<false>, dim3(b.prefix[count]), dim3(256), stream, b, phase);
+        }
     }
     return KFAC_OK;
 }
