@@ -37,6 +37,7 @@ static inline __host__ __device__ int most_splits(int R, int tw, int ntiles, boo
 static inline __host__ __device__ int xcd_splits(int ns) { return ns >= 8 ? ns / 8 * 8 : ns; }
 
 // The same for a layer whose tap pairs share their sums.
+constexpr int SHARED_ROWS_LEAST = 400, SHARED_ROWS_LEAST_F32 = 80;
 static inline __host__ __device__ SharedPlan plan_shared(const View& v, int share) {
     SharedPlan p;
     const Unfold& u = v.u;
@@ -48,12 +49,16 @@ static inline __host__ __device__ SharedPlan plan_shared(const View& v, int shar
     p.per[0] = p.ntl + 12 * p.nf;
     p.per[1] = p.per[2] = 2 * p.ntl + 4 * p.nf;
     p.per[3] = 4 * p.ntl;
-    const int share_rows = share & (SHARE_WIDE - 1);
+    // Three quarters of a dense tile's rows: an entry's sum is then no longer a chain of fp32 additions than there (with as many rows
+    // the error against 64 bits was up to 1.6 times the dense form's, now it is nowhere larger).
+    const int share_rows = (share & (SHARE_WIDE - 1)) * 3 / 4;
     const int rows = u.N * (u.H - 1) * (u.W - 1);
-    const int cap = most_splits(rows, p.tw, p.per[0], f32), least = rows / (f32 ? SHARE_LEAST_F32 : SHARE_LEAST);
+    const int memory = (p.tw == 256 ? 256 : 512) / p.per[0], need = ceil_div(rows, f32 ? ROWS_PER_WG_MAX_F32 : ROWS_PER_WG_MAX);   // (most_splits)
+    const int cap = memory > need ? memory : need;
+    const int least = rows / (f32 ? SHARED_ROWS_LEAST_F32 : p.per[0] > 128 ? 640 : SHARED_ROWS_LEAST);   // (512 channels, 1,152 rows: not two)
     int ns = ceil_div(rows, share_rows);
     if (ns > cap) ns = cap;
-    if (ns > least) ns = least > 1 ? least : 1;        // (a set of partial sums for less than SHARE_LEAST rows is not worth its traffic)
+    if (ns > least) ns = least > 1 ? least : 1;
     p.ns[0] = xcd_splits(ns);
     const int ends[3] = {u.N * (u.W - 1), u.N * (u.H - 1), u.N};
     p.first[0] = 0;

@@ -195,8 +195,7 @@ __device__ __forceinline__ v4f sum_splits(v4f s, const gfloat* src, size_t strid
         v4f p[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) p[k] = *(const KFAC_AS1 v4f*)(src + (size_t)(sp + k) * stride);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) s += p[k];
+        s += (p[0] + p[1]) + (p[2] + p[3]);
     }
     for (; sp < ns; ++sp) s += *(const KFAC_AS1 v4f*)(src + (size_t)sp * stride);
     return s;
