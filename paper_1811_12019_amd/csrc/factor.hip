@@ -241,7 +241,7 @@ static FactorPlan plan_generic(const Unfold& u) {
     FactorPlan p;
     p.tiles_dim = ceil_div(u.d, GT);
     p.ntiles = p.tiles_dim * (p.tiles_dim + 1) / 2;
-    int want = ceil_div(2048, p.ntiles);
+    int want = ceil_div(1024, p.ntiles);                       // (four workgroups to a CU)
     int max_split = ceil_div(u.R, 4 * GK);
     p.nsplit = want < 1 ? 1 : (want > max_split ? max_split : want);
     if (p.nsplit < 1) p.nsplit = 1;
@@ -299,7 +299,7 @@ static size_t tiles_ws_bytes(const View& v) {
         const int td = ceil_div(D, tw), nt = td * (td + 1) / 2;
         const int least = f32 ? SHARE_LEAST_F32 : tw == 256 ? ROWS_PER_WG_MAX : SHARE_LEAST;
         const int ns = xcd_splits(std::min(most_splits(R, tw, nt, f32), ceil_div(R, least)));
-        if (ns > 1) need = std::max(need, (size_t)ns * ((size_t)nt * tw * tw + (size_t)td * tw) * sizeof(float));
+        if (ns > 1) need = std::max(need, (size_t)ns * ((size_t)nt * tile_floats(tw, nt) + (size_t)td * tw) * sizeof(float));
     }
     return need;
 }

@@ -14,6 +14,7 @@ struct FactorPlan {
     int ntiles;      // lower-triangular tiles
     int nsplit;
     int rows_per_split;
+    int tile_floats; // partial sums of a tile of one split (matrix-core builds)
     size_t ws_bytes;
 };
 
@@ -87,7 +88,8 @@ static inline __host__ __device__ FactorPlan plan_tiles(const View& v, int share
     ns = xcd_splits(ns);
     p.rows_per_split = ceil_div(ceil_div(R, ns), 64) * 64;
     p.nsplit = ceil_div(R, p.rows_per_split);
-    p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * ((size_t)p.ntiles * p.tw * p.tw + (size_t)p.tiles_dim * p.tw) * sizeof(float) : 0;
+    p.tile_floats = tile_floats(p.tw, p.ntiles);
+    p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * ((size_t)p.ntiles * p.tile_floats + (size_t)p.tiles_dim * p.tw) * sizeof(float) : 0;
     return p;
 }
 
@@ -95,7 +97,7 @@ static inline __host__ __device__ FactorPlan plan_tiles(const View& v, int share
 static inline __host__ __device__ Partial partial_of(const View& v, const FactorPlan& p, void* ws) {
     Partial q;
     q.tiles = (gfloat*)(ws ? (unsigned char*)ws + repack_bytes(v) : nullptr);
-    q.sums = q.tiles + (size_t)p.nsplit * p.ntiles * p.tw * p.tw;
+    q.sums = q.tiles + (size_t)p.nsplit * p.ntiles * p.tile_floats;
     return q;
 }
 

@@ -54,8 +54,8 @@ __device__ __forceinline__ void reduce_partials(const View& v, const FactorPlan&
     const int row0 = I * T + si * 32, col0 = J * T + sj * 32;
     if (row0 < col0 || row0 >= D || col0 >= D) return;               // above the diagonal, or outside the matrix
     const bool dg = row0 == col0, packed = os.mode == OUT_PACKED;
-    const gfloat* src = part.tiles + (size_t)tile * (T * T) + (si * SB + sj) * 1024;
-    const size_t stride = (size_t)pl.ntiles * (T * T);
+    const gfloat* src = part.tiles + (size_t)tile * pl.tile_floats + (pl.ntiles == 1 ? si * (si + 1) / 2 + sj : si * SB + sj) * 1024;
+    const size_t stride = (size_t)pl.ntiles * pl.tile_floats;
     gfloat* __restrict__ out = os.dst;
     float (*tr)[33] = (float (*)[33])lds;
     if constexpr (many) {

@@ -157,6 +157,7 @@ __device__ __forceinline__ void shared_tile(const View& v, const KFAC_AS1 unsign
     job.r_end = min(vw.u.R, job.r_begin + rows_per);
     if (job.r_end < job.r_begin) job.r_begin = job.r_end;           // (rounding up may leave the last split empty: it stores zeros)
     job.split = true;
+    job.lower = false;
     job.scale = 1.f;
     job.tile_dst = ws + (size_t)unit * (TW * TW);
     job.first_pixel = w.y0 * v.u.W + w.x0;

@@ -180,10 +180,16 @@ template <int TW, int ES> constexpr int tile_threads() { return 64 * TileShape<T
 // Where a tile's partial sums go when the rows are split: the tiles of a split one after another, then (all splits' tiles
 // done) the column sums of every split.
 struct Partial {
-    gfloat* tiles;        // [nsplit][ntiles][TW * TW]: 32 x 32 blocks row by row, each as the MFMA leaves it in the registers:
+    gfloat* tiles;        // [nsplit][ntiles][tile_floats]: 32 x 32 blocks row by row (of a matrix that is one tile, only those on
+                          // and below the diagonal), each as the MFMA leaves it in the registers:
                           // float 256 q + 4 lane + i is row 8 q + 4 (lane / 32) + i, column lane % 32
     gfloat* sums;         // [nsplit][tiles_dim * TW]
 };
+
+static inline __host__ __device__ int tile_floats(int tw, int ntiles) {
+    const int n = tw / 32;
+    return (ntiles == 1 ? n * (n + 1) / 2 : n * n) * 1024;
+}
 
 template <int TW, int ES> constexpr int tile_ring_bytes() { return TileShape<TW, ES>::NS * 2 * TileShape<TW, ES>::DK * TW * ES; }
 template <int TW, int ES> constexpr int tile_lds_bytes() { return tile_ring_bytes<TW, ES>() + 4 * TW * 4; }
@@ -196,6 +202,7 @@ struct TileJob {
     int r_begin, r_end;
     float scale;
     bool split;              // partial sums: the tile goes to tile_dst, the column sums of a diagonal one to sums_dst
+    bool lower;              // the matrix is this tile: only its blocks on and below the diagonal are kept
     gfloat *tile_dst, *sums_dst;
     int first_pixel, partner;  // FEED_WINDOW: the rectangle's first pixel, and how many pixels behind a row's pixel the one of the
                                // tile's columns lies
@@ -504,12 +511,14 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
 #pragma unroll
         for (int p = 0; p < S::MB; ++p)
 #pragma unroll
-            for (int n = 0; n < S::NB; ++n)
+            for (int n = 0; n < S::NB; ++n) {
+                const int rb = wm * S::MB + p, cb = wn * S::NB + n;
+                if (DIAG && cb > rb) continue;                     // (uniform)
+                gfloat* blk = dst + (DIAG && job.lower ? rb * (rb + 1) / 2 + cb : rb * (TW / 32) + cb) * 1024;
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    const v4f o = {acc[p][n][4 * q4], acc[p][n][4 * q4 + 1], acc[p][n][4 * q4 + 2], acc[p][n][4 * q4 + 3]};
-                    *(KFAC_AS1 v4f*)(dst + ((wm * S::MB + p) * (TW / 32) + wn * S::NB + n) * 1024 + q4 * 256) = o;
-                }
+                for (int q4 = 0; q4 < 4; ++q4)
+                    *(KFAC_AS1 v4f*)(blk + q4 * 256) = v4f{acc[p][n][4 * q4], acc[p][n][4 * q4 + 1], acc[p][n][4 * q4 + 2], acc[p][n][4 * q4 + 3]};
+            }
         return;
     }
     // One 32-row block row at a time through LDS (this wavefront's own part of it): its rows go out along result rows, then
@@ -653,7 +662,8 @@ __device__ __forceinline__ void factor_tile(const View& v, const KFAC_AS1 unsign
     job.r_begin = sp * rows_per_split;
     job.r_end = min(v.u.R, job.r_begin + rows_per_split);
     job.split = nsplit > 1;
-    job.tile_dst = part.tiles + ((size_t)sp * ntiles + tile) * (TW * TW);
+    job.lower = ntiles == 1;
+    job.tile_dst = part.tiles + ((size_t)sp * ntiles + tile) * tile_floats(TW, ntiles);
     job.sums_dst = part.sums + (size_t)sp * (tiles_dim * TW);
     job.scale = scale;
     job.first_pixel = job.partner = 0;
