@@ -3,7 +3,8 @@
 // unfolded patch matrix is never materialised: tiles of it are gathered on the fly into LDS.
 //
 // Kernels:
-//   factor_tile_kernel     matrix cores, channels-last tensors of any dtype (factor_tile.h); many builds share one launch
+//   factor_tile_kernel     matrix cores, channels-last tensors of any dtype, and NCHW ones whose rows are their pixels, as they lie
+//                          (factor_tile.h); many builds share one launch
 //                          (workgroup -> (build, tile) through a prefix table).
 //   factor_repack_kernel   brings tensors in other layouts, or with channel counts that are no multiple of a 16-byte
 //                          vector, into that form first (factor_repack.h).
@@ -275,7 +276,7 @@ static void add_work(TileWork& w, const View& v) {
 // Width: a 256-wide tile halves the operand traffic per product, but a workgroup fills a CU, its epilogue overlaps with
 // nothing and a matrix is padded to multiples of 256.  It is the better one only for a lot of work with little padding (third
 // stage at 25,088 rows: 1385 us against 1600 us), or for so much that padding and the launch's end do not show (all of the
-// network at 128 images: 5.1 against 5.4 ms; at 64 both 2.55 ms, at 32 1480 us against 1350 us).
+// network at 128 images: 5.1 against 5.4 ms; at 64 both 2.55 ms, at 32 1480 us against 1350 us; all tiles dense then).
 constexpr double WIDE_PER_SLOT = 24000;
 static int share_of(const TileWork& w, bool f32) {
     const double per_slot = w.narrow / 768;
@@ -287,8 +288,8 @@ static int share_of(const TileWork& w, bool f32) {
 }
 
 // An upper bound of plan_tiles' workspace over all shares that share_of gives: the partial sums of as many splits as the fewest
-// rows to a workgroup make.  (The factors of ResNet-50 from channels-last bf16 tensors: 2.9 GB
-// at batch 32, 3.9 GB at batch 128; most_splits alone would ask for 3.5 and 5.2 GB.)
+// rows to a workgroup make.  (The factors of ResNet-50 from channels-last bf16 tensors: 1.9 GB
+// at batch 32, 2.5 GB at batch 128.)
 static size_t tiles_ws_bytes(const View& v) {
     const int D = v.u.d, R = v.u.R;
     const bool f32 = v.u.dtype == KFAC_F32;
@@ -306,29 +307,9 @@ static size_t tiles_ws_bytes(const View& v) {
 
 // Whether the matrix-core kernels take a build whose tensor lies at x.
 static bool tile_eligible(const Unfold& u, const void* x, View* v) {
-    return make_view(u, v) && ((uintptr_t)x & (v->repack ? (u.dtype == KFAC_F32 ? 3 : 1) : 15)) == 0;
-}
-
-// (128 and 64 wide: three workgroups of four wavefronts per CU; 256 wide: one of eight)
-template <int TW, int KIND>
-__global__ __launch_bounds__((tile_threads<TW, KIND == 2 ? 4 : 2>())) __attribute__((amdgpu_waves_per_eu(TW == 256 ? 2 : 3, 8)))
-void factor_tile_kernel(FBatch b) {
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    int local;
-    const int m = fbatch_locate(b, blockIdx.x, local);
-    kfac_factor_item it;
-    Unfold u;
-    View v;
-    fbatch_item(b, m, it, u, v);
-    const KFAC_AS1 unsigned char* x = (const KFAC_AS1 unsigned char*)(v.repack ? it.ws : it.x);
-    if (v.shared) {
-        shared_tile<TW, KIND>(v, x, plan_shared(v, b.share[m]), shared_ws(v, it.ws), local, smem);
-        return;
-    }
-    const FactorPlan p = plan_tiles(v, b.share[m]);
-    const float scale = it.scale == 0.f ? 1.0f / (float)u.R : it.scale;
-    factor_tile<TW, KIND>(v, x, scale, out_spec(it), partial_of(v, p, it.ws), p.rows_per_split, p.tiles_dim, p.ntiles, p.nsplit,
-                          local, smem);
+    if (!make_view(u, v)) return false;
+    if (reads_planes(u, x)) planes_view(u, v);
+    return ((uintptr_t)x & (v->repack ? (u.dtype == KFAC_F32 ? 3 : 1) : 15)) == 0;
 }
 
 __global__ __launch_bounds__(256) void factor_repack_kernel(FBatch b) {
@@ -338,7 +319,7 @@ __global__ __launch_bounds__(256) void factor_repack_kernel(FBatch b) {
     kfac_factor_item it;
     Unfold u;
     View v;
-    fbatch_item(b, m, it, u, v);
+    fbatch_item<false>(b, m, it, u, v);
     if (v.rows) repack_rows(u, v, (const KFAC_AS1 unsigned short*)it.x, (KFAC_AS1 unsigned*)it.ws, local);
     else if (u.dtype == KFAC_F32) repack_tile<float>(u, v, (const gfloat*)it.x, (KFAC_AS1 unsigned*)it.ws, local, smem);
     else repack_tile<unsigned short>(u, v, (const KFAC_AS1 unsigned short*)it.x, (KFAC_AS1 unsigned*)it.ws, local, smem);
@@ -353,7 +334,7 @@ static bool item_unfold(const kfac_factor_item& it, Unfold* u) {
 static size_t item_ws_bytes(const Unfold& u) {
     size_t need = plan_generic(u).ws_bytes;                    // any kernel may serve the build
     View v;
-    if (make_view(u, &v)) {
+    if (make_view(u, &v)) {                                    // (with the place of a repacked copy: the address decides whether there is one)
         need = std::max(need, repack_bytes(v) + tiles_ws_bytes(v));
     }
     return align_up(need, 256);
@@ -367,26 +348,6 @@ static int check_item(const kfac_factor_item& it, Unfold* u) {
     if (it.packed != 0 && it.packed != 1) return KFAC_ERR_INVALID_ARG;
     const size_t need = item_ws_bytes(*u);
     if (need > 0 && (!it.ws || ((uintptr_t)it.ws & 255) || it.ws_bytes < need)) return KFAC_ERR_WORKSPACE;
-    return KFAC_OK;
-}
-
-template <int TW, int KIND>
-static int launch_tiles(const FBatch& b, hipStream_t stream) {
-    constexpr int LDS = tile_lds_bytes<TW, KIND == 2 ? 4 : 2>();
-    // More than 64 KB of LDS have to be asked for, on every device anew: the 256-wide kernels' launches do, each for the device it
-    // goes to (nothing to remember between calls; their work is milliseconds).
-    if constexpr (LDS > 64 * 1024) {
-        if (hipFuncSetAttribute((const void*)factor_tile_kernel<TW, KIND>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS) != hipSuccess)
-            return KFAC_ERR_HIP;
-    }
-    void* tok = nullptr;
-    static const char* const name = KIND == 2 ? (TW == 64 ? "factor_tile_kernel<64, f32>" : "factor_tile_kernel<128, f32>")
-                                  : TW == 64 ? "factor_tile_kernel<64, 16-bit>"
-                                  : TW == 128 ? "factor_tile_kernel<128, 16-bit>" : "factor_tile_kernel<256, 16-bit>";
-    if (timing_enabled()) timing_begin(name, stream, &tok);
-    hipLaunchKernelGGL((factor_tile_kernel<TW, KIND>), dim3(b.prefix[b.count]), dim3(tile_threads<TW, KIND == 2 ? 4 : 2>()), LDS, stream, b);
-    if (tok) timing_end(stream, tok);
-    if (hipGetLastError() != hipSuccess) return KFAC_ERR_HIP;
     return KFAC_OK;
 }
 
@@ -410,9 +371,15 @@ enum Route { ROUTE_TILE, ROUTE_GENERIC };
 // builds share the repacking and tile launches.
 constexpr long long GENERIC_MACS = 1 << 25;
 
+// Planes read as they lie save the repacking, but not the second launch: small builds of few rows stay there too (fp32, 512 rows of 32
+// columns 12.6 us as a tile and 12.8, of 128 columns 19.2 and 17.1; its chains of 64 rows are also the shorter ones: 2,048 rows of 64
+// columns in bf16 err by 8.8e-8 against 1.2e-7).  From 4,096 rows on the tile is the faster one (6,272 rows of 64 columns 13.7 us and
+// 22.3) and the more accurate one (7.8e-8 and 1.5e-7).
+constexpr int GENERIC_PLANE_ROWS = 4096;
+
 static Route route_of(const Unfold& u, const void* x, bool many, View* v) {
     if (!tile_eligible(u, x, v)) return ROUTE_GENERIC;
-    return v->repack && !many && (long long)u.R * u.d * u.d <= GENERIC_MACS ? ROUTE_GENERIC : ROUTE_TILE;
+    return (v->repack || (v->planes && u.R < GENERIC_PLANE_ROWS)) && !many && (long long)u.R * u.d * u.d <= GENERIC_MACS ? ROUTE_GENERIC : ROUTE_TILE;
 }
 
 static void fbatch_clear(FBatch& b, const kfac_factor_item* dev) {
@@ -454,10 +421,11 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
     // of 63 us).
     auto share_for = [&](const View& v) -> int {
         const bool f32 = v.u.dtype == KFAC_F32;
-        if (many) return f32 ? share32 : share16;
+        const int flag = v.planes ? SHARE_PLANES : 0;
+        if (many) return (f32 ? share32 : share16) | flag;
         TileWork own = {0, 0};
         add_work(own, v);
-        return share_of(own, f32);
+        return share_of(own, f32) | flag;
     };
     FBatch b, fin[FINISH_LISTS];                       // fin: second passes, after all tiles
     auto finish = [&](int k) -> int {
@@ -494,6 +462,7 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
             fbatch_clear(b, dev);
             struct Pick { int item, share, rows, wgs, finish, list; } pick[FMAXB];
             int n = 0;
+            bool planes = false;
             for (; next < count && n < FMAXB; ++next) {
                 Unfold u;
                 View v;
@@ -508,6 +477,7 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
                 }
                 const FactorPlan p = plan_tiles(v, share);
                 if (p.tw != VAR_TW[var]) continue;
+                planes = planes || v.planes;
                 pick[n++] = {next, share, p.rows_per_split, (int)align_up(p.ntiles * p.nsplit, 8),   // (a multiple of 8: see factor_tile)
                              p.nsplit > 1 ? reduce_wgs(v, p) : 0, p.nsplit >= MANY_SPLITS ? FINISH_MANY : FINISH_FEW};
             }
@@ -515,16 +485,9 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
             // the longest workgroups first: the short ones fill the end of the launch
             std::stable_sort(pick, pick + n, [](const Pick& a, const Pick& c) { return a.rows > c.rows; });
             for (int i = 0; i < n; ++i) fbatch_add(b, host, pick[i].item, pick[i].share, pick[i].wgs);
-            switch (var) {
-                case 0: rc = launch_tiles<64, 0>(b, stream); break;
-                case 1: rc = launch_tiles<64, 1>(b, stream); break;
-                case 2: rc = launch_tiles<128, 0>(b, stream); break;
-                case 3: rc = launch_tiles<128, 1>(b, stream); break;
-                case 4: rc = launch_tiles<256, 0>(b, stream); break;
-                case 5: rc = launch_tiles<256, 1>(b, stream); break;
-                case 6: rc = launch_tiles<64, 2>(b, stream); break;
-                default: rc = launch_tiles<128, 2>(b, stream); break;
-            }
+            rc = VAR_DTYPE[var] == KFAC_BF16 ? launch_tiles<0>(VAR_TW[var], planes, b, stream)
+               : VAR_DTYPE[var] == KFAC_F16 ? launch_tiles<1>(VAR_TW[var], planes, b, stream)
+                                            : launch_tiles<2>(VAR_TW[var], planes, b, stream);
             if (rc != KFAC_OK) return rc;
             for (int i = 0; i < n; ++i) {
                 if (!pick[i].finish) continue;

@@ -19,9 +19,10 @@ struct FactorPlan {
 };
 
 // Tile width and row split of a matrix-core build.  `share`: how the builds of a call are cut (share_of): the rows of a
-// workgroup, plus SHARE_WIDE if matrices of more than 128 columns get 256-wide tiles.  A matrix of up to 128 (64) columns is
-// one tile of that width.
-constexpr int SHARE_WIDE = 1 << 20;
+// workgroup, plus SHARE_WIDE if matrices of more than 128 columns get 256-wide tiles, plus SHARE_PLANES if the tensor is read as
+// planes (the address decides that, once, on the host: worked out by the kernels it cost each launch 0.2 to 0.5 us).  A matrix of up to
+// 128 (64) columns is one tile of that width.
+constexpr int SHARE_WIDE = 1 << 20, SHARE_PLANES = 1 << 21;
 constexpr int ROWS_PER_WG_MAX = 6400, ROWS_PER_WG_MAX_F32 = 1600;
 constexpr int ROWS_PER_WG_MIN = 512, ROWS_PER_WG_MIN_F32 = 64;
 constexpr int SHARE_LEAST = 1024, SHARE_LEAST_F32 = 128;           // the fewest rows share_of gives a workgroup
@@ -135,11 +136,18 @@ __device__ __forceinline__ int fbatch_locate(const FBatch& b, int wg, int& local
     return lo;
 }
 
+// (a launch of builds that are not read as planes: PLANES = false)
+template <bool PLANES = true>
 __device__ __forceinline__ void fbatch_item(const FBatch& b, int m, kfac_factor_item& it, Unfold& u, View& v) {
     it = b.table ? b.table[b.index[m]] : b.single;
     if (it.op == KFAC_OP_FACTOR_A) make_unfold_A(&it.desc, &u); else make_unfold_G(&it.desc, &u);
     make_view(u, &v);
+    if (PLANES && (b.share[m] & SHARE_PLANES)) planes_view(u, &v);
 }
+
+// Tiles of the builds of `b`; KIND 0: bf16, 1: fp16, 2: fp32 (factor_launch.h).
+template <int KIND>
+int launch_tiles(int tw, bool planes, const FBatch& b, hipStream_t stream);
 
 // Second passes of the builds of `b` (factor_finish.hip): builds of few row ranges or shared sums, of many ranges, of shared sums in
 // (channel, tap) order.

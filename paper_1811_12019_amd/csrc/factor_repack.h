@@ -1,7 +1,7 @@
 // Repacking of a tensor that the matrix-core factor builder cannot read as it lies: NCHW -> channels last, and channel
 // counts that are no multiple of a 16-byte vector -> padded with zero channels.  One read and one write of the tensor
-// (HBM bound), against a gather of every tap of every element by every tile.  All tensors of ResNet-50 from NCHW: bf16 at batch 32
-// (2.8 GB moved) 587 us = 4.7 TB/s, fp32 at batch 8 276 us = 5.0 TB/s.
+// (HBM bound), against a gather of every tap of every element by every tile.  All tensors of ResNet-50 from NCHW took, in bf16 at
+// batch 32 (2.8 GB moved), 587 us = 4.7 TB/s, in fp32 at batch 8 276 us = 5.0 TB/s; most are read as they lie now (reads_planes).
 // Workgroup = 64 pixels x 64 channels of one image, transposed through LDS: loads run along pixels, stores along channels.
 #pragma once
 
@@ -57,7 +57,6 @@ __device__ __forceinline__ void repack_tile(const Unfold& u, const View& v, cons
     __syncthreads();
     constexpr int VPR = RP_T / (4 * EPD);                           // 16-byte vectors per pixel of the tile
     const unsigned* td = (const unsigned*)smem;
-    typedef unsigned v4u __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int e = 0; e < RP_T * VPR / 256; ++e) {
         const int p = (t + 256 * e) / VPR, q = (t + 256 * e) % VPR;
@@ -85,7 +84,6 @@ __device__ __forceinline__ void repack_rows(const Unfold& u, const View& v, cons
         val[e] = ok ? 1u : 0u;
         val[e] *= x[ok ? at : 0];
     }
-    typedef unsigned v4u __attribute__((ext_vector_type(4)));
     const v4u o = {val[0] | val[1] << 16, val[2] | val[3] << 16, val[4] | val[5] << 16, val[6] | val[7] << 16};
     *(KFAC_AS1 v4u*)(dst + (size_t)id * 4) = o;
 }

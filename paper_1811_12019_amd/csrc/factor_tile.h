@@ -1,5 +1,5 @@
-// Matrix-core factor builder: tiles of  Xbar^T Xbar  straight from a channels-last tensor, Xbar the implicitly unfolded
-// patch matrix, for 16-bit (v_mfma_f32_32x32x16) and fp32 (v_mfma_f32_32x32x2_f32) inputs.
+// Matrix-core factor builder: tiles of  Xbar^T Xbar  straight from a channels-last tensor (or NCHW planes: FEED_PLANES), Xbar the
+// implicitly unfolded patch matrix, for 16-bit (v_mfma_f32_32x32x16) and fp32 (v_mfma_f32_32x32x2_f32) inputs.
 //
 // One TW x TW tile (on or below the diagonal) of one range of unfolded rows per workgroup.  The contraction index (the
 // unfolded row) is the slow index in memory, and the 16-bit MFMA wants it contiguous per lane; gfx950 has exactly the two
@@ -17,12 +17,13 @@
 // CU) for TW^2 multiply-adds, so with 128-wide tiles the copies alone take as many cycles as the matrix cores: where there
 // is enough work (share_of), wide matrices get 256-wide tiles (8 wavefronts of 128 x 64, a ring of four 32-row slabs), which
 // halves that.  Matrices of up to 128 (64) columns get one tile of that width.
-// Measured (bf16, channels last, ResNet-50): batch 32, 128-wide: 925 GFLOP of products in 1.11 ms, matrix cores busy in 39 % of the
-// cycles in which a CU holds a workgroup, LDS in 23 %; batch 128, 256-wide: 3.99 TFLOP in 4.0 ms, 51 % and 20 %.  The rest is
+// Measured (ResNet-50, channels last, dense tiles only): batch 32, 128-wide: 925 GFLOP of products in 1.11 ms, matrix cores busy in 39 %
+// of the cycles in which a CU holds a workgroup, LDS in 23 %; batch 128, 256-wide: 3.99 TFLOP in 4.0 ms, 51 % and 20 %.  The rest is
 // wavefronts waiting at the slabs' barriers (a quarter of their time), the row addresses between the products, and a tile's
-// epilogue, beside which a 256-wide workgroup has nothing else on its CU.  fp32, NCHW, batch 8: 2.25 ms beside 0.28 ms of repacking,
-// 89 TFLOP/s of the 155 that v_mfma_f32_32x32x2_f32 reaches.  26 (128-wide) and 64 (256-wide) registers live in scratch memory, all of
-// them used outside the product loops.
+// epilogue, beside which a 256-wide workgroup has nothing else on its CU.  With the sums that tap pairs share (factor_shared.h) the
+// 256-wide launch takes 2.1 ms.  All factors from NCHW: bf16 at batch 32 2090 -> 1804 us with shared sums, 1515 with planes read as
+// they lie; fp32 at batch 8 2555 -> 1974 -> 1766.  16 (128-wide) and 56 (256-wide) registers live in scratch memory, all of them
+// used outside the product loops.
 //
 // The bias column is not part of the tiled matrix (2048 + 1 columns would cost a ninth row of 256-wide tiles for one
 // column): its row of the result is the column sums, which the wavefronts of a diagonal tile whose part lies above the
@@ -45,6 +46,7 @@ namespace kfac {
 static __device__ uint4 g_zero_chunk = {0u, 0u, 0u, 0u};
 
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 #define KFAC_TR_READ(dst, addr, off) \
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off))
@@ -71,6 +73,7 @@ struct View {
                      // run is whole.  The view's kw is 1, its pad 0.
     int kw;          // the layer's kernel width
     int shared;      // tap pairs at the same offset share their sums (factor_shared.h)
+    int planes;      // the caller's NCHW tensor is read as it lies: a column is a channel's plane, 16 bytes are V of its rows
 };
 
 // Whether a 3 x 3 layer of stride 1 and padding 1 is built from the sums that its tap pairs share (factor_shared.h): 13 C x C
@@ -86,6 +89,8 @@ static inline __host__ __device__ bool taps_shared(const Unfold& u) {
     const long long dense = n * (n + 1) / 2 * 4, parts = u.C <= 64 ? 13 * 2 : 4 * (m * (m + 1) / 2 + 12 * m * m);
     return 2 * parts <= dense;
 }
+
+static inline __host__ __device__ bool is_plain(const Unfold& u) { return u.kh == 1 && u.kw == 1 && u.stride == 1 && u.pad == 0; }
 
 // False: the matrix-core kernels cannot take the build.
 static inline __host__ __device__ bool make_view(const Unfold& u, View* v) {
@@ -111,10 +116,24 @@ static inline __host__ __device__ bool make_view(const Unfold& u, View* v) {
     v->mapped = v->chunked || Cp != u.C || rows;
     v->shared = !rows && taps_shared(v->u);
     v->repack = (u.layout == KFAC_NCHW && u.H * u.W > 1) || Cp != u.C || rows;
+    v->planes = 0;
     return (long long)u.N * v->u.H * v->u.W * Cp <= 0x7fffffffLL;            // 32-bit element offsets
 }
 
-__device__ __forceinline__ bool is_plain(const Unfold& u) { return u.kh == 1 && u.kw == 1 && u.stride == 1 && u.pad == 0; }
+// Whether the rows of an NCHW tensor at x are read as they lie (FEED_PLANES): they are its pixels, and every 16 bytes of a plane
+// are aligned and of one image.  Against repacking first, all factors of ResNet-50: bf16 at batch 32 1804 -> 1515 us (1.2 GB less
+// written and read again), fp32 at batch 8 1974 -> 1766 us.
+static inline bool reads_planes(const Unfold& u, const void* x) {
+    const int hw = u.H * u.W;
+    return u.layout == KFAC_NCHW && hw > 1 && is_plain(u) && hw % (u.dtype == KFAC_F32 ? 4 : 8) == 0 && ((uintptr_t)x & 15) == 0;
+}
+// The view (make_view's) of such a build.
+static inline __host__ __device__ void planes_view(const Unfold& u, View* v) {
+    v->u = u;
+    v->u.d = v->run = u.C;
+    v->mapped = v->repack = 0;
+    v->planes = 1;
+}
 
 // Result index of internal data column p, or -1 for a padding column.
 __device__ __forceinline__ int result_index(const View& v, int p) {
@@ -210,14 +229,25 @@ struct TileJob {
 
 // Where the rows come from.  PATCHES: unfolded patches of any geometry.  PIXELS: a row is a pixel, all of the tensor in order.
 // WINDOW: a row is a pair of pixels at a fixed offset, the first for the tile's rows, the second for its columns; the first ones
-// are an Ho x Wo rectangle of each image (factor_shared.h).
-enum { FEED_PATCHES, FEED_PIXELS, FEED_WINDOW };
+// are an Ho x Wo rectangle of each image (factor_shared.h).  PLANES: a row is a pixel of an NCHW tensor: the contraction index is
+// the fast one in memory, as the MFMA wants it, and a lane's operand is one 16-byte read.
+enum { FEED_PATCHES, FEED_PIXELS, FEED_WINDOW, FEED_PLANES };
+
+// An operand of one K step of a 32-column block: read in pieces of two registers, or (PLANES) in one of four.
+template <bool PLANES, int PIECES> struct OperandRegs { typedef v2u type[PIECES]; };
+template <int PIECES> struct OperandRegs<true, PIECES> { typedef v4u type; };
+template <int P> __device__ __forceinline__ v2u first_half(const v2u (&r)[P]) { return r[0]; }
+template <int P> __device__ __forceinline__ v2u second_half(const v2u (&r)[P]) { return r[P - 1]; }
+__device__ __forceinline__ v2u first_half(const v4u& r) { return v2u{r.x, r.y}; }
+__device__ __forceinline__ v2u second_half(const v4u& r) { return v2u{r.z, r.w}; }
+template <int P> __device__ __forceinline__ float operand_float(const v2u (&r)[P], int e) { return __uint_as_float(r[0][e]); }
+__device__ __forceinline__ float operand_float(const v4u& r, int e) { return __uint_as_float(r[e]); }
 
 // One tile.  KIND 0: bf16, 1: fp16, 2: fp32.
 template <int TW, int KIND, int FEED, bool DIAG>
 __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 unsigned char* x, const TileJob& job,
                                                 const OutSpec& os, unsigned char* smem) {
-    constexpr bool PLAIN = FEED == FEED_PIXELS, WINDOW = FEED == FEED_WINDOW;
+    constexpr bool PLAIN = FEED == FEED_PIXELS, WINDOW = FEED == FEED_WINDOW, PLANES = FEED == FEED_PLANES;
     constexpr int ES = KIND == 2 ? 4 : 2, V = 16 / ES;
     typedef TileShape<TW, ES> S;
     constexpr int NW = S::WM * S::WN, DK = S::DK;
@@ -243,10 +273,18 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     // 16-lane transposed read is then a contiguous 128-byte run.  fp32 slab: row-major.
     const int pan = DIAG ? 0 : wave / PW;
     const int b0 = wave % PW;
-    int row0, q;                                               // row inside the slab for block b0, vector
+    // PLANES: slot = column CH + (16 bytes of its DK rows ^ a number that differs in any 16 columns read at once): a lane's row is
+    // b0's in all blocks, its column CSTEP further on from block to block.
+    constexpr int CH = DK / V, CSTEP = PW * 64 / CH, FLIP = 16 / CH;
+    static_assert(CSTEP % 16 == 0, "the flip is the same in all blocks");
+    int row0, q;                                               // row inside the slab for block b0, vector (PLANES: column)
     constexpr int ROWSTEP = ES == 4 ? PW * 64 / (TW / 4) : PW * 64 / (TW / 2) * 4;    // rows from one block of this wavefront to the next
     static_assert(ES == 4 ? (PW * 64) % (TW / 4) == 0 : (PW * 64) % (TW / 2) == 0, "a lane keeps its column vector from block to block");
-    if constexpr (ES == 4) {
+    if constexpr (PLANES) {
+        const int L = b0 * 64 + lane;
+        q = L / CH;
+        row0 = ((L % CH) ^ (q / FLIP % CH)) * V;
+    } else if constexpr (ES == 4) {
         const int L = b0 * 64 + lane;
         row0 = L / (TW / 4);
         q = L % (TW / 4);
@@ -261,11 +299,29 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
         g.off = (pan == 0 ? I : J) * TW + q * V;
         g.data = g.off < D;
         g.off += pan == 0 ? job.first_pixel * u.C : (job.first_pixel + job.partner) * u.C;
+    } else if constexpr (PLANES) {
+        g.ki = g.kj = 0;
+        g.off = (pan == 0 ? I : J) * TW + q;
+        g.data = g.off < D;
     } else {
         g = decode_group(v, (pan == 0 ? I : J) * TW + q * V);
     }
     lds_byte* lds0 = (lds_byte*)smem + pan * PANEL + b0 * 1024;
     const unsigned long long zero_addr = (unsigned long long)(const KFAC_AS1 unsigned char*)&g_zero_chunk;
+
+    // PLANES: this lane's 16 bytes of column q, advanced by DK pixels from slab to slab: pn images and pp pixels, with at most one carry.
+    unsigned long long plane_at = 0, plane_step = 0, plane_carry = 0;
+    const long long column_step = (long long)ES * CSTEP * u.H * u.W;
+    int plane_px = 0, plane_dx = 0;
+    const int columns_left = D - g.off;                        // (column j: there while above j CSTEP)
+    if constexpr (PLANES) {
+        const int size = u.H * u.W, R = r_begin + row0, n = R / size;
+        plane_px = R - n * size;
+        plane_dx = DK % size;
+        plane_at = (unsigned long long)x + (unsigned long long)(ES * (((long long)n * u.C + g.off) * size + plane_px));
+        plane_step = (unsigned long long)(ES * ((long long)(DK / size) * u.C * size + plane_dx));
+        plane_carry = (unsigned long long)(ES * ((long long)u.C - 1) * size);
+    }
 
     // The NI rows whose vectors this lane copies, advanced by DK rows from slab to slab without divisions: DK rows are
     // dn images, dy image rows and dx pixels, each with at most one carry into the next.
@@ -281,7 +337,8 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
         const int R = r_begin + row0 + j * ROWSTEP;
-        if constexpr (PLAIN) {
+        if constexpr (PLANES) {
+        } else if constexpr (PLAIN) {
             at[j] = (unsigned long long)x + (unsigned long long)((long long)R * px + (long long)ES * g.off);
         } else {
             const int n = R / hw, rem = R - n * hw, yo = rem / u.Wo, xo = rem - yo * u.Wo;
@@ -297,6 +354,16 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     // copies of the next slab into the ring at stage_off (branch-free; slabs are issued in order)
     auto issue = [&](int stage_off) {
         unsigned long long src[NI];
+        if constexpr (PLANES) {
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+                src[j] = ((rows_left > 0) & (columns_left > j * CSTEP)) ? plane_at + (unsigned long long)(j * column_step) : zero_addr;
+            plane_at += plane_step;
+            plane_px += plane_dx;
+            const bool carry = plane_px >= u.H * u.W;
+            plane_px -= carry ? u.H * u.W : 0;
+            plane_at += carry ? plane_carry : 0;
+        } else
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             bool ok = rows_left > j * ROWSTEP;
@@ -325,7 +392,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     // (read: starts them into one of two register sets; multiply: uses a set).  The barrier sits before a slab's last step:
     // this wavefront has then read all of the slab, so that once everybody is there the slab's place is refilled, and
     // the first operands of the next slab, whose copies have landed, are read during the last step's products.
-    constexpr int STEPS = ES == 2 ? DK / 16 : DK / 4;
+    constexpr int STEPS = ES == 2 ? DK / 16 : PLANES ? DK / 8 : DK / 4;
     static_assert(STEPS % 2 == 0, "the register sets alternate across slabs");
     // (The scheduling fences keep a step's products between the waits: left alone, they sink below the next ones.)
     auto pipeline = [&](auto reads_per_step, auto&& read, auto&& arrived, auto&& multiply) {
@@ -366,7 +433,9 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
 
     // ---- consumer: LDS byte address of this lane's operand pieces in stage 0, from tile column c0 on ----
     auto operand_addr = [&](int c0) -> unsigned {
-        if constexpr (ES == 2) {
+        if constexpr (PLANES) {
+            return (unsigned)((c0 + lm) * CH + (h ^ (lm / FLIP % CH))) * 16;
+        } else if constexpr (ES == 2) {
             const int grp = lane >> 4, p = lane & 15, r = p >> 2, cg4 = p & 3;
             return (unsigned)((2 * (grp >> 1)) * RGS + (2 * r + (cg4 >> 1)) * 16 + (cg4 & 1) * 8 + (grp & 1) * 128 + c0 / 16 * 128);
         } else {
@@ -374,12 +443,16 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
         }
     };
     // operands of N 32-column blocks for the e-th K step of a slab: 16-bit: 16 rows; fp32: the 4 rows of two
-    // v_mfma_f32_32x32x2_f32 (k = 2 s + h), one read bringing the operands of both
-    constexpr int PIECES = ES == 2 ? 2 : 1;
+    // v_mfma_f32_32x32x2_f32 (k = 2 s + h), one read bringing the operands of both.  PLANES: 16 bytes of rows of each half-wave.
+    constexpr int PIECES = PLANES ? 1 : ES == 2 ? 2 : 1;
+    constexpr int PRODUCTS = ES == 2 ? 1 : PLANES ? 4 : 2;     // MFMAs of a step and block
+    typedef typename OperandRegs<PLANES, PIECES>::type Regs;
     constexpr int U = TW / 64;                                 // fp32: units of 256 bytes per slab row
 #define KFAC_TILE_READ(dst, i, addr, step)                                                                                        \
     do {                                                                                                                         \
-        if constexpr (ES == 2) {                                                                                                 \
+        if constexpr (PLANES) {                                                                                                  \
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst[i]) : "v"((addr) ^ (32u * decltype(step)::value)), "n"((i) * 32 * CH * 16)); \
+        } else if constexpr (ES == 2) {                                                                                          \
             KFAC_TR_READ(dst[i][0], addr, (i) * 256 + (4 * decltype(step)::value + 0) * RGS);                                                       \
             KFAC_TR_READ(dst[i][PIECES - 1], addr, (i) * 256 + (4 * decltype(step)::value + 1) * RGS);                                              \
         } else {                                                                                                                 \
@@ -389,7 +462,8 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     } while (0)
 #define KFAC_TILE_ARRIVED(dst, i)                                                                                                \
     do {                                                                                                                         \
-        asm volatile("" : "+v"(dst[i][0]));                                                                                      \
+        if constexpr (PLANES) asm volatile("" : "+v"(dst[i]));                                                                    \
+        else asm volatile("" : "+v"(dst[i][0]));                                                                                 \
         if constexpr (PIECES == 2) asm volatile("" : "+v"(dst[i][PIECES - 1]));                                                   \
     } while (0)
 
@@ -428,7 +502,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
         const unsigned addr0 = operand_addr(c0);
-        v2u b[2][BB][PIECES];
+        Regs b[2][BB];
         pipeline(StaticInt<BB * PIECES>{}, [&](unsigned stage_off, auto e, int set) {
             const unsigned ba = addr0 + stage_off;
 #pragma unroll
@@ -442,10 +516,11 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
                 if constexpr (ES == 2) {
                     const unsigned one2 = KIND == 1 ? 0x3C003C00u : 0x3F803F80u;
                     const v2u ones = {one2, one2};
-                    acc[i] = mfma16_halves<KIND == 1>(ones, ones, b[set][i][0], b[set][i][PIECES - 1], acc[i]);
+                    acc[i] = mfma16_halves<KIND == 1>(ones, ones, first_half(b[set][i]), second_half(b[set][i]), acc[i]);
                 } else {
-                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(1.0f, __uint_as_float(b[set][i][0][0]), acc[i], 0, 0, 0);
-                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(1.0f, __uint_as_float(b[set][i][0][1]), acc[i], 0, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < PRODUCTS; ++e)
+                        acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(1.0f, operand_float(b[set][i], e), acc[i], 0, 0, 0);
                 }
             }
         });
@@ -477,7 +552,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][n][r] = 0.f;
     const unsigned a_addr = operand_addr(wr), b_addr = operand_addr(wc) + (DIAG ? 0u : (unsigned)PANEL);
-    v2u a[2][S::MB][PIECES], b[2][S::NB][PIECES];
+    Regs a[2][S::MB], b[2][S::NB];
     pipeline(StaticInt<(S::MB + S::NB) * PIECES>{}, [&](unsigned stage_off, auto e, int set) {
         const unsigned aa = a_addr + stage_off, ba = b_addr + stage_off;
 #pragma unroll
@@ -491,15 +566,15 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
         for (int i = 0; i < S::MB; ++i) KFAC_TILE_ARRIVED(a[set], i);
     }, [&](int set) {
 #pragma unroll
-        for (int e = 0; e < (ES == 2 ? 1 : 2); ++e)
+        for (int e = 0; e < PRODUCTS; ++e)
 #pragma unroll
             for (int i = 0; i < S::MB; ++i)
 #pragma unroll
                 for (int n = 0; n < S::NB; ++n) {
                     if constexpr (ES == 2)
-                        acc[i][n] = mfma16_halves<KIND == 1>(a[set][i][0], a[set][i][PIECES - 1], b[set][n][0], b[set][n][PIECES - 1], acc[i][n]);
+                        acc[i][n] = mfma16_halves<KIND == 1>(first_half(a[set][i]), second_half(a[set][i]), first_half(b[set][n]), second_half(b[set][n]), acc[i][n]);
                     else
-                        acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[set][i][0][e]), __uint_as_float(b[set][n][0][e]), acc[i][n], 0, 0, 0);
+                        acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(operand_float(a[set][i], e), operand_float(b[set][n], e), acc[i][n], 0, 0, 0);
                 }
     });
 
@@ -640,7 +715,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
 }
 
 // One tile (workgroup `wg` of ntiles * nsplit, padded to a multiple of 8) of one factor build.
-template <int TW, int KIND>
+template <int TW, int KIND, bool PLANES>
 __device__ __forceinline__ void factor_tile(const View& v, const KFAC_AS1 unsigned char* x, float scale, const OutSpec& os,
                                             const Partial& part, int rows_per_split, int tiles_dim, int ntiles, int nsplit,
                                             int wg, unsigned char* smem) {
@@ -669,10 +744,12 @@ __device__ __forceinline__ void factor_tile(const View& v, const KFAC_AS1 unsign
     job.first_pixel = job.partner = 0;
     const bool plain = is_plain(v.u);
     if (job.I == job.J) {
-        if (plain) factor_tile_run<TW, KIND, FEED_PIXELS, true>(v, x, job, os, smem);
+        if (PLANES && v.planes) factor_tile_run<TW, KIND, PLANES ? FEED_PLANES : FEED_PIXELS, true>(v, x, job, os, smem);
+        else if (plain) factor_tile_run<TW, KIND, FEED_PIXELS, true>(v, x, job, os, smem);
         else factor_tile_run<TW, KIND, FEED_PATCHES, true>(v, x, job, os, smem);
     } else if constexpr (TW > 64) {                                // (64-wide matrices are one tile)
-        if (plain) factor_tile_run<TW, KIND, FEED_PIXELS, false>(v, x, job, os, smem);
+        if (PLANES && v.planes) factor_tile_run<TW, KIND, PLANES ? FEED_PLANES : FEED_PIXELS, false>(v, x, job, os, smem);
+        else if (plain) factor_tile_run<TW, KIND, FEED_PIXELS, false>(v, x, job, os, smem);
         else factor_tile_run<TW, KIND, FEED_PATCHES, false>(v, x, job, os, smem);
     }
 }

@@ -24,8 +24,8 @@
 // largest one.  The last step's panel is a launch, and one launch for the whole batch writes the outputs (inv_out_kernel).
 // Bound: one matrix alone by the look-ahead pivot's workgroup (its update 11.8 us, the sweep 15.3, write-out 1.9, from launch to
 // launch 2.5; half slabs are done after 13 to 25): 31.5 us a step, 40 when panel and tiles were launches of their own.  One matrix
-// alone, us: 145 columns 81 -> 64, 1000 328 -> 281, 2049 632 -> 565, 4609 1501 -> 1370; ten ragged ones (10 to 1153 columns) with
-// their preconditioning 557 -> 453.  Batches of wide matrices are bound by their tile visits.
+// alone, us: 145 columns 81 -> 64, 1000 328 -> 281, 2049 632 -> 565, 4609 1501 -> 1370 (the working copy still in rows then); ten
+// ragged ones (10 to 1153 columns) with their preconditioning 557 -> 453, 400 with all of it.  Batches of wide matrices are bound by their tile visits.
 // Products: the panel on the bf16 matrix cores with operands split three ways; the updates on the fp16 matrix cores
 // from operands that the panel launch has already scaled per half slab (64 rows) and split two ways, stored as planes that
 // go to LDS by DMA (gemm_split.h); both to fp32 accuracy.

@@ -104,7 +104,7 @@ class _Wave:
         self.pi_batch = kb.PiBatch(src[0::2], src[1::2], device=device) if pi_split else None
         lam_dev = ([self.pi_batch.address(i // 2, i % 2) for i in range(len(src))] if pi_split else None)
         # The inversions are independent, so they are dealt (largest first, to the least loaded group, by d^3) into a
-        # few groups that run on streams of their own: the latency-bound pivot / panel kernels of one group then
+        # few groups that run on streams of their own: the latency-bound steps of one group then
         # overlap with the throughput-bound updates of the others.  (Grouping by block count instead, so that a
         # group's launches are all equally long, measured 2 % slower.)
         n_groups = max(1, min(n_groups, len(src)))
@@ -126,7 +126,7 @@ class KfacNetworkStep:
 
     The stage methods (build_factors, update_running, invert, precondition) run one stage for the whole network.
     step() strings them together when pipelined is False.  By default it works in two waves instead: the inversion of
-    a 4609-wide factor is a chain of ~75 small dependent launches (1.5 of the step's 5.8 ms if it runs alone) that leaves
+    a 4609-wide factor is a chain of ~40 dependent launches (1.2 of the step's 5.1 ms if it runs alone) that leaves
     most of the GPU idle, so the factors of the layers with a factor of long_dim or more are built first and their
     inversions started on the side streams at once; the other layers' stages run on the launch stream beside them,
     and each wave is preconditioned when its inverses are done."""
