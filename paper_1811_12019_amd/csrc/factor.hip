@@ -274,9 +274,10 @@ static void add_work(TileWork& w, const View& v) {
 // as much traffic as a finished tile, for nothing (the third stage's 18 layers at 1568 rows: 151 us unsplit, 334 us in two).  When
 // there is little work the launch of the second pass weighs too.
 // Width: a 256-wide tile halves the operand traffic per product, but a workgroup fills a CU, its epilogue overlaps with
-// nothing and a matrix is padded to multiples of 256.  It is the better one only for a lot of work with little padding (third
-// stage at 25,088 rows: 1385 us against 1600 us), or for so much that padding and the launch's end do not show (all of the
-// network at 128 images: 5.1 against 5.4 ms; at 64 both 2.55 ms, at 32 1480 us against 1350 us; all tiles dense then).
+// nothing and a matrix is padded to multiples of 256.  It is the better one only for a lot of work with little padding
+// (third stage at 25,088 rows, dense: 1385 us against 1600 us; all of the network, 24 images 1039 us against 984, 32 1192 against 1205 and
+// in (channel, tap) order 1255 against 1430, 64 1920 against 2035, 96 2622 against 2957), or for so much that padding and the launch's
+// end do not show.
 constexpr double WIDE_PER_SLOT = 24000;
 static int share_of(const TileWork& w, bool f32) {
     const double per_slot = w.narrow / 768;
