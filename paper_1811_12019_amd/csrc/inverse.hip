@@ -37,10 +37,10 @@
 // block row k.  Only the last launch writes the caller's dense output, both triangles, exactly symmetric (the upper one is a copy of
 // the lower one).
 #include "gemm_split.h"
+#include "inverse_plan.h"
 
 namespace kfac {
 
-constexpr int NB = 128;          // elimination block = tile edge
 constexpr int MAXB = 64;         // matrices per launch of the kernels that read S (bounded by the 4 KB of kernel arguments)
 constexpr int CMAXB = 112;       // matrices per launch of the sweep's per-step kernels, whose argument block is leaner
 constexpr int UPD_WAVES = 3;     // wavefronts per SIMD the update kernel is compiled for (register budget)
@@ -120,7 +120,6 @@ __device__ __forceinline__ void locate(const B& b, int wg, int& m, int& local) {
     local = wg - b.prefix[m];
 }
 
-static inline __host__ __device__ int nblk_of(int dim) { return (dim + NB - 1) / NB; }
 static inline __host__ __device__ size_t working_copy_floats(int dim) { return (size_t)nblk_of(dim) * (nblk_of(dim) + 1) / 2 * NB * NB; }
 
 // Optional second form of the result, for the products that consume the inverse (preconditioning): the matrix cut
@@ -137,112 +136,9 @@ static inline __host__ __device__ size_t inverse_planes_bytes(int dim) {
 __device__ __forceinline__ float inverse_plane_scale(float damping) {
     return damping > 0.f ? ldexpf(1.0f, 8 + ilogbf(damping)) : 1.0f;
 }
-// Steps are taken in groups of up to GM consecutive blocks, none of them the matrix's last.  Inside a group only what the chain
-// needs is brought up to date; every other tile receives the group's rank-128 updates together, in one visit during the next
-// group's launches, which cuts the traffic of the working copy by the group size.  The arithmetic per tile is the same sequence
-// of fp32 operations as step-by-step updating.
-constexpr int GM = 4;
-struct Group {
-    int g0;      // first step of a run of steps
-    int m;       // its size (1 .. GM)
-    int j;       // the last of them that a tile is to see, minus g0
-};
-// What the launch of a stage does for a matrix of n blocks (n >= 2).  Stage k <= n - 2 is step k, of the group [g0, g0 + GM):
-//   * `slabs` half slabs (of pivot block k + 1's own only T).  Tile (I, k + 1) owes, in one visit, all steps from chain_from(k + 1) on.
-//     The slabs of block k + 2 also bring their diagonal tile, which is kept up to date through step k - 2, up to step k.
-//   * Diagonal tiles of the blocks the next pivots need are kept up to date one step behind, so that a look-ahead pivot never owes
-//     more than one product: in a group's first launch blocks g0 + 3 .. g0 + 6 receive the whole group before, in the others
-//     blocks k + 3 .. g0 + 6 step k - 1.
-//   * The bulk: every other tile without an index inside the group receives the whole group before, in the group's launches but its
-//     fourth (whose panel k + 1 takes the buffer of the first step of the group before).  The tiles of blocks g0 + 2 and g0 + 3
-//     come first, in the group's first launch ("early" tiles): the panels k + 1 of the group's second and third launch read them.
-//     (Block g0 + 1, whose panel the first launch forms, owes the group before and step g0: chain_from.)
-// Stage n - 1: the panel of the last step, beside the tiles of all other blocks, which receive what the last group owes them, unless
-// the output launch, which follows, is to do that (OUT_OWED).
-struct Plan {
-    Group g;             // the run of steps that the tiles see
-    int slabs;           // workgroups of half slabs
-    int d_begin, diag;   // diagonal tiles, from block d_begin on
-    bool single;         // they see only the run's last step
-    int g0, w;           // the group's first block and how many blocks it takes out of the bulk
-    int early;           // number of early tiles of the group; early and lag tiles are one list, of which this launch takes
-    int off, bulk;       // `bulk` tiles from `off` on
-    int tiles;           // stage n - 1: all tiles but the last block's (left out where the output launch takes their updates)
-};
-
-static inline __host__ __device__ Plan plan_of(int dim, int stage) {
-    const int n = nblk_of(dim);
-    Plan p;
-    p.d_begin = p.diag = p.g0 = p.w = p.early = p.off = p.bulk = p.tiles = 0;
-    p.single = false;
-    if (stage == n - 1) {
-        p.slabs = 2 * (n - 1);
-        p.tiles = n * (n - 1) / 2;
-        p.g.g0 = (n - 2) / GM * GM;
-        p.g.m = n - 1 - p.g.g0;
-        p.g.j = p.g.m - 1;
-        return p;
-    }
-    p.slabs = 2 * n;
-    const int k = stage, g0 = k / GM * GM, j = k - g0, m = min(GM, n - 1 - g0);
-    p.g0 = g0;
-    p.w = min(GM, n - g0);
-    if (j > 0) {
-        p.g.g0 = g0;
-        p.g.m = m;
-        p.g.j = j - 1;
-        p.single = true;
-        p.d_begin = k + 3;
-    } else {
-        p.g.g0 = g0 - GM;
-        p.g.m = GM;
-        p.g.j = GM - 1;
-        p.d_begin = g0 + 3;
-    }
-    if (k > 0) p.diag = max(0, min(g0 + 6, n - 1) - p.d_begin + 1);
-    if (g0 > 0) {
-        const int others = n - p.w, columns = max(0, p.w - 2);
-        p.early = columns * others + (columns == 2);
-        const int total = p.early + others * (others + 1) / 2, launches = min(m, GM - 1);
-        const int first = launches == 1 ? total : max(p.early, (total + launches - 1) / launches);
-        if (j == 0) {
-            p.bulk = first;
-        } else if (j < launches) {
-            const int per = (total - first + launches - 2) / (launches - 1);
-            p.off = first + (j - 1) * per;
-            p.bulk = max(0, min(per, total - p.off));
-        }
-    }
-    return p;
-}
-static inline int plan_workgroups(const Plan& p, bool out_owed) { return p.slabs + p.diag + p.bulk + (out_owed ? 0 : p.tiles); }
-// The first step that the tiles of block column / row c owe when panel c is formed (by the launch of step c - 1): the working copy
-// holds them through the step before it.
-static inline __host__ __device__ int chain_from(int c) {
-    const int r = c % GM;
-    return max(0, r == 0 ? c - GM : r == 1 ? c - 1 - GM : c - r);
-}
-// index in the list of early and lag tiles -> (I, J): tiles of blocks g0 + 2 and g0 + 3, then the triangle over the blocks outside
-// the group
-__host__ __device__ __forceinline__ void bulk_decode(int n, int g0, int w, int early, int t, int& I, int& J) {
-    const int others = n - w;
-    if (t >= early) {
-        tri_decode_blocked(others, t - early, I, J);
-        if (I >= g0) I += w;
-        if (J >= g0) J += w;
-        return;
-    }
-    const int ci = t / others;
-    if (ci >= w - 2) { I = g0 + 3; J = g0 + 2; return; }     // (the one tile of both)
-    const int c = g0 + 2 + ci, o = t - ci * others, x = o < g0 ? o : o + w;
-    I = max(c, x);
-    J = min(c, x);
-}
-
 // Panels of one step, kept in buffer (step % NBUF): the fp32 copy U of block column k as it was before the step (all
 // rows, assembled from both triangles), the fp32 product T = U P, and the scaled fp16 pieces of both (the negated T and
 // U, each as a plane of high and a plane of low pieces in the layout of gemm_split.h), which the tile updates multiply.
-constexpr int NBUF = 2 * GM;
 struct WsView {
     gfloat* W;      // working copy: lower tiles row by row, 64 KB each: 4 x 4 blocks of 32 x 32, float 256 q + 4 lane + i of a block
                     // being row 8 q + 4 (lane / 32) + i, column lane % 32
@@ -846,11 +742,9 @@ __device__ __forceinline__ void product_f32(const gfloat* __restrict__ T, const 
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");            // ring idle: the LDS may be reused
 }
 
-// Where a tile's old values come from: the working copy, or the T panel of the step that eliminated one of its blocks, as it lies
-// (block column) or transposed (block row).
-enum { OLD_W, OLD_T, OLD_T_TURNED };
+// Where a tile's old values come from.
 struct OldSrc {
-    int kind;
+    int kind;                // OLD_W, OLD_T, OLD_T_TURNED
     const gfloat* base;      // the tile, or the first of the slab's rows
 };
 
@@ -886,6 +780,7 @@ __device__ __forceinline__ void load_old(const OldSrc& o, bool dead, TileAcc& ac
 // half slab and split two ways (gemm_split.h): the accumulators start as the tile's old values, the negated products are added,
 // and the result is stored from the registers: nothing is staged in LDS.
 constexpr int MAXRUN = GM;               // a tile owes at most one whole group (the group before, or its own so far)
+static_assert(HALF_MAXN == GM + 1, "a half slab owes at most the group before and one step (chain_from)");
 typedef SplitRun<MAXRUN> PanelRun;
 
 // The products of tile (I, J) with the panels of the n consecutive steps first_step .. first_step + n - 1 (buffer =
@@ -1271,20 +1166,14 @@ __device__ __forceinline__ void step_pivot(const Item& it, int step, float* __re
     pivot_write(acc, lds, it, ws, k0, nb, k0 + NB >= d, false);
 }
 
-// The first step that tile (I, J) owes of the steps lo .. hi, and where its old values are: the working copy, unless one of its blocks
-// is among lo .. hi.  Such a tile was kept up to date until its later such block c was eliminated (when it became part of panel c:
-// T_I for a tile of block column c, T_J transposed for one of block row c, neither written to the working copy then), and owes the
-// steps after c; the diagonal tile (c, c) is -P_c, which the pivot code did write.
+// The first step that tile (I, J) owes of the steps lo .. hi, and where its old values are (owed_first).
 __device__ __forceinline__ int owed_from(const WsView& ws, int I, int J, int lo, int hi, OldSrc& o) {
-    if (I >= lo && I <= hi) {                            // I is the later block (I >= J)
-        if (I != J) o = OldSrc{OLD_T_TURNED, ws.T(I % NBUF) + (size_t)J * (NB * NB)};
-        return I + 1;
-    }
-    if (J >= lo && J <= hi) {                            // I lies beyond
-        o = OldSrc{OLD_T, ws.T(J % NBUF) + (size_t)I * (NB * NB)};
-        return J + 1;
-    }
-    return lo;
+    int kind;
+    const int first = owed_first(I, J, lo, hi, kind);
+    o = OldSrc{OLD_W, ws.tile(I, J)};
+    if (kind == OLD_T_TURNED) o = OldSrc{kind, ws.T(I % NBUF) + (size_t)J * (NB * NB)};
+    if (kind == OLD_T) o = OldSrc{kind, ws.T(J % NBUF) + (size_t)I * (NB * NB)};
+    return first;
 }
 
 // Tile (I, J) of a step that is not the matrix's last: brings it up to date through step g.g0 + g.j.
@@ -1367,23 +1256,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UPD_WAVES, 
         else last_slab(it, stage, slab, half, lds, red);
         return;
     }
-    tile -= pl.slabs;
     int I, J;
-    bool single = false;
-    Group g = pl.g;
-    if (stage == n - 1) {
-        tri_decode_blocked(n - 1, tile, I, J);
-        if (I == J && I == n - 2) return;                // -P of the group's last step
-    } else if (tile < pl.diag) {
-        I = J = pl.d_begin + tile;
-        single = pl.single;
-    } else {
-        bulk_decode(n, pl.g0, pl.w, pl.early, pl.off + tile - pl.diag, I, J);
-        // -P of the group's last step; the diagonal tiles above
-        if (I == J && (I == pl.g0 - 1 || (I > pl.g0 && I <= pl.g0 + 6))) return;
-        g.g0 = pl.g0 - GM;                               // (the whole group before, whatever the diagonal tiles see)
-        g.j = GM - 1;
-    }
+    bool single;
+    Group g;
+    if (!stage_tile(pl, n, stage, tile - pl.slabs, I, J, g, single)) return;
     group_tile(ws_view(it.ws, it.dim), I, J, g, single, lds);
 }
 
@@ -1616,10 +1492,7 @@ static int run_group(const kfac_inverse_item* h, int count, hipStream_t stream) 
     const int launches = nblk_of(h[0].dim);
     for (int l = 0; l < launches; ++l) {
         for (int i = 0; i < n_multi; ++i) {
-            // (a matrix's last stage touches all of its tiles: matrices with fewer blocks than the largest take it at different
-            // launches, none with the largest ones)
-            const int n = nblk_of(h[i].dim), span = n == launches ? n : max(n, launches - 1 - i % 6);
-            const bool run = l < span && (l + 1) * n / span > l * n / span;
+            const bool run = takes_stage(nblk_of(h[i].dim), launches, i, l);
             c.stage[i] = run ? done[i] : -1;
             c.prefix[i + 1] = c.prefix[i] + (run ? plan_workgroups(plan_of(h[i].dim, done[i]), out_owed) : 0);
             done[i] += run;
