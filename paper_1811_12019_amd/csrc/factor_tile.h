@@ -79,8 +79,19 @@ struct View {
 // Whether a 3 x 3 layer of stride 1 and padding 1 is built from the sums that its tap pairs share (factor_shared.h): 13 C x C
 // blocks (offset (0, 0): its lower half) instead of the lower half of a 9 C x 9 C matrix, in whole tiles.  A 64-wide tile
 // moves twice as many bytes per product as a 128-wide one.  At most half as many: the strips and the second launch cost something
-// too.  Little work is left to the dense form, whose tiles then need no second launch: at 1,568 rows 128 channels take 29 us against
-// 31, 16 such builds in a call 80 against 75; 64 channels at 6,272 rows 24 against 30.
+// too.  A build's form depends on its shape alone, so that a call of few builds gives the single calls' bits.
+// Time of the shared form over the dense one's, one build and 16 in a call, bf16, (tap, channel) order:
+//     rows     64 channels    128            256            512
+//     784      0.64  0.92     0.85  1.22     0.91  1.28     0.99  1.38
+//     1176                    0.90  1.16     0.62  1.15     0.89  1.26
+//     1568     0.80  0.65     0.92  1.03     0.62  1.14     0.84  1.11
+//     2352                    0.87  0.53     0.58  0.95     0.74  0.92
+//     3136     0.78  0.66     0.85  0.52     0.55  0.87     0.70  0.82
+// ((channel, tap) order: 128 channels 0.97 and 1.08, 512 channels 1.11 and 0.90 at 1,176 rows; fp32 0.3 to 0.9 everywhere.)  The line in
+// rows, 1,024, lies where a single dense build starts to need a second launch too.  From there to 2,000 rows a call of many builds of 128
+// and more channels would be faster dense, by up to 30 %, whole networks of such batches (6 to 8 and 24 to 28 images) by 1 to 4 % of their
+// factor builds; but dense chains of so many rows err twice as much (256 channels, 1,568 rows: 1.5e-7 against 7.6e-8; 512: 1.46e-7
+// against 1.15e-7), so they are not.  The line in elements keeps 64 channels dense below 2,048 rows; the shared form is the faster one there.
 static inline __host__ __device__ bool taps_shared(const Unfold& u) {
     if (u.kh != 3 || u.kw != 3 || u.stride != 1 || u.pad != 1 || u.H < 4 || u.W < 4 || u.R < SHARED_ROWS_MIN ||
         (long long)u.R * u.C < SHARED_INPUT_MIN)
