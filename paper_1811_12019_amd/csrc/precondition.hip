@@ -141,8 +141,12 @@ __global__ __launch_bounds__(256) void pre_split_kernel(PBatch b) {
 
 // phase 1: Yt[dA x dG] = Ainv . gradW^T (written as planes)      phase 2: out[dG x dA] = Ginv . Yt^T
 // A workgroup makes a 128 x 128 tile, or (HALF) 64 x 128 of one.  Full tiles move 2 / 3 of the bytes per product; half tiles take half
-// as long, which is what counts while there are not enough tiles for the chip (HALF_TILES).
-constexpr int HALF_TILES = 256;          // launches of up to so many tiles (one to a CU) are made of half tiles
+// as long, which is what counts while the chip holds all of them at a time: three workgroups on each of 256 CUs, 384 tiles.  Both forms
+// err alike.  Whole calls, full and half tiles, us: 192 tiles of 1024 x 1024 layers 89 and 76, 240 of 256 x 1153 91 and 86, 272 of
+// 1000 x 2049 176 and 151, 304 of 512 x 2305 178 and 163, 384 of 1024 x 1024 121 and 114, of 130 x 1000 103 and 101; many small layers of
+// short contractions lose up to 9 % (255 tiles of 64 x 577 69 and 75).  Behind the line: 400 of 256 x 1153 129 and 144, of 2048 x 513 165 and
+// 183, 444 of 512 x 4609 370 and 405.
+constexpr int HALF_TILES = 384;          // launches of up to so many tiles are made of half tiles
 
 template <bool HALF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void gemm_nt_kernel(PBatch b, int phase) {

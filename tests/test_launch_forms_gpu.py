@@ -1,5 +1,5 @@
 """The forms that inversions and preconditioning take by the size of a call: block counts around the groups of four elimination steps,
-batches on both sides of 512 tiles (from which on the last group's updates come with the outputs), and products of up to 256 tiles, which
+batches on both sides of 512 tiles (from which on the last group's updates come with the outputs), and products of up to 384 tiles, which
 are made of half tiles.  Against float64 on the host, with the scratch's end guarded and the outputs off the 16-byte grid."""
 import numpy as np
 import pytest
@@ -50,11 +50,14 @@ def test_inverse_launch_forms(dims):
         assert bool((w[n:] == MARK).all()) and bool((p[-GUARD:] == MARK).all()), d
 
 
-# (d_G, d_A): a few rows, ragged both ways, long contractions; all of them together 139 tiles, with the last shape 411
+# (d_G, d_A): a few rows, ragged both ways, long contractions; all of them together 139 tiles, with more shapes 384 (the last call of
+# half tiles), 385 and 411
 SHAPES = [(1, 10), (5, 129), (64, 577), (129, 64), (255, 257), (512, 1153), (300, 2049), (1000, 500)]
+MORE = SHAPES + [(1920, 2048), (128, 640)]
 
 
-@pytest.mark.parametrize("shapes", [SHAPES[:4], SHAPES, SHAPES + [(2048, 2049)]], ids=["few", "139", "411"])
+@pytest.mark.parametrize("shapes", [SHAPES[:4], SHAPES, MORE, MORE + [(100, 100)], SHAPES + [(2048, 2049)]],
+                         ids=["few", "139", "384", "385", "411"])
 @pytest.mark.parametrize("with_planes", [False, True])
 def test_precondition_launch_forms(shapes, with_planes):
     rng = np.random.default_rng(9)
