@@ -23,9 +23,9 @@
 // Every matrix of a batch carries its own stage, so that matrices with fewer blocks spread their launches over those of the
 // largest one.  The last step's panel is a launch, and one launch for the whole batch writes the outputs (inv_out_kernel).
 // Bound: one matrix alone by the look-ahead pivot's workgroup (its update 11.8 us, the sweep 15.3, write-out 1.9, from launch to
-// launch 2.5; half slabs are done after 13 to 25): 31.5 us a step, 40 when panel and tiles were launches of their own.  One matrix
-// alone, us: 145 columns 81 -> 64, 1000 328 -> 281, 2049 632 -> 565, 4609 1501 -> 1370 (the working copy still in rows then); ten
-// ragged ones (10 to 1153 columns) with their preconditioning 557 -> 453, 400 with all of it.  Batches of wide matrices are bound by their tile visits.
+// launch 2.5; half slabs are done after 13 to 25): 31 us a step, 40 when panel and tiles were launches of their own.  One matrix
+// alone, us, then and now: 145 columns 81 and 63, 1000 328 and 272, 2049 632 and 532, 4609 1501 and 1258; ten ragged ones (10 to 1153
+// columns) with their preconditioning 557 and 400.  Batches of wide matrices are bound by their tile visits.
 // Products: the panel on the bf16 matrix cores with operands split three ways; the updates on the fp16 matrix cores
 // from operands that the panel launch has already scaled per half slab (64 rows) and split two ways, stored as planes that
 // go to LDS by DMA (gemm_split.h); both to fp32 accuracy.
@@ -1203,7 +1203,10 @@ __device__ __forceinline__ void group_tile(const WsView& ws, int I, int J, const
 
 // How the work list is dealt to the XCDs: equal shares, but where few matrices' look-ahead pivots run on few XCDs and the others can
 // take the rest, the pivots' hosts get no more than they have compute units left (a tile's workgroup beside the pivot's lengthens
-// the chain by 5 us a step).
+// the chain by 5 us a step).  With and without, us: one matrix of 4609 columns 1258 and 1325, two of 3073 878 and 919, three of 2305 666
+// and 695, four of 2049 626 and 650; up to 325 tiles a matrix, where launches stay below a workgroup to a CU, the same within 0.5 %.
+// Beyond the lines the other XCDs' second and third workgroups cost more: six matrices of 2049 columns 866 instead of 706, four of 3073
+// 1292 instead of 1142, two of 4609 1661 instead of 1640 (one of 6001 columns would gain: 1768 instead of 1864).
 constexpr int XCD_CUS = 32;
 struct XcdShare {
     int hosts, host, other;      // XCDs 0 .. hosts - 1 get `host` workgroups each, the others `other`
@@ -1266,9 +1269,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UPD_WAVES, 
 // ---- output ----------------------------------------------------------------------------------------------------------
 // One launch for all matrices of a call: every lower tile receives the last step's update (fp32 products of its nb columns), in large
 // batches after the last group's (one trip through memory less; small ones, where a launch is as long as its longest workgroup, have
-// these in the launch before: ten ragged matrices of 200 tiles 451 us, 474 with them here; the long inversions of ResNet-50 and what
-// runs beside them 5.33 ms without, 5.23 with), and its negative goes to the caller's output, with its mirror image, and, if asked for, to the piece planes.  (With
-// these in launches of the sweep and the planes in a pass over the finished inverses, every tile went through memory twice more.)
+// these in the launch before), and its negative goes to the caller's output, with its mirror image, and, if asked for, to the piece
+// planes.  (With these in launches of the sweep and the planes in a pass over the finished inverses, every tile went through memory
+// twice more.)  The last group's updates here against in the launch before, us: 36 tiles (1000 columns) 284 and 273, 120 (eight
+// matrices of 513) 169 and 167, 156 (two of 1500) 406 and 397, 390 (five of 1500) 450 and 441; 440 (eight of 1153) 360 and 357, 495 (nine)
+// 381 and 384, 510 (34 of 513) 223 and 225, 550 (ten of 1153) 401 and 406, 561 (one of 4097) 1090 and 1104, 720 (48 of 513) 276 and 284, 1100 (twenty of
+// 1153) 571 and 586; the long inversions of ResNet-50 and what runs beside them 5.23 and 5.33 ms.
 // Bound: HBM.
 constexpr int OMAXB = 90;
 constexpr int OUT_OWED = 512;        // lower tiles of a batch from which on the output launch takes the last group's updates too
