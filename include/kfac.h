@@ -77,13 +77,15 @@ const char* kfac_status_string(int status);
 
 /* Workspace a factor build needs, op = KFAC_OP_FACTOR_A / _G: partial sums of its row ranges, as many as any call it may be
  * part of makes, and a channels-last copy of the tensor if it is NCHW or its channels are not whole 16-byte vectors (padded to
- * such, so up to 8 / C times the tensor).  Enough for every alignment of the tensor.  0 on a bad descriptor. */
+ * such, so up to 8 / C times the tensor).  Enough for every alignment of the tensor: an NCHW tensor whose rows are its pixels is read as
+ * it lies if its address allows that, and the copy's place then is not used.  0 on a bad descriptor. */
 size_t kfac_factor_workspace_bytes(int op, const kfac_layer_desc* desc);
 
 /* Stage 1.  A[d_A x d_A] = scale * sum_r abar_r abar_r^T over the R unfolded input patches abar_r of `act`
  * (zero padding outside the image, a trailing 1 if has_bias); scale = 0 selects 1/R, the mini-batch
  * mean of Sec. 3.1.  `act` holds N*C_in*H*W elements of desc->dtype in desc->layout.  Accumulation is fp32.  A non-finite input
- * makes its entries non-finite; whether 0 (padding) times infinity is formed is not specified. */
+ * makes every entry non-finite in which it meets a value inside the image or the bias, the diagonal of its columns among them.  Where it
+ * meets nothing but padding, 0 times it may or may not be formed (3 x 3 layers of stride 1 and padding 1 with many rows do not). */
 int kfac_factor_A(const kfac_layer_desc* desc, const void* act, float scale, float* A,
                   void* ws, size_t ws_bytes, void* stream);
 

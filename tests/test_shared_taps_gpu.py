@@ -117,3 +117,33 @@ def test_non_finite_input():
     assert not torch.isfinite(A[met, -1]).any() and not torch.isfinite(A[met, met]).any()
     rest = [t * 64 + 3 for t in (2, 5, 6, 7, 8)]
     assert torch.isfinite(A[rest][:, rest]).all()
+
+
+@pytest.mark.parametrize("N", [2, 8], ids=["dense", "shared"])
+@pytest.mark.parametrize("order", [KKC, CKK])
+@pytest.mark.parametrize("pixel", [(0, 0), (19, 7), (9, 19), (11, 4)], ids=["corner", "last row", "last column", "inside"])
+def test_where_a_non_finite_input_shows(N, order, pixel):
+    """Every entry in which an infinity meets a value inside the image (any value: 0 times it is NaN) or the bias is not finite; entries of
+    taps that never see it are."""
+    s, c = layer(N, 64, 20, 20), 3
+    act = _NP_ROUND[kb.KFAC_BF16](synth.make_act(s, 6))
+    act[1, c, pixel[0], pixel[1]] = np.inf
+    desc = kb.make_desc(s, NHWC, kb.KFAC_BF16, order)
+    A = torch.zeros((s.d_A, s.d_A), device=DEV)
+    kb.kfac_factor_A(desc, kb.to_device_tensor(act, NHWC, kb.KFAC_BF16, DEV), 0.0, A,
+                     kb.alloc_workspace(kb.kfac_factor_workspace_bytes(kb.KFAC_OP_FACTOR_A, desc), DEV))
+    A = A.cpu()
+    columns = lambda tap: torch.arange(64) + 64 * tap if order == KKC else torch.arange(64) * 9 + tap
+    inside = lambda y, x: 0 <= y < 20 and 0 <= x < 20
+    blind = []
+    for t1 in range(9):
+        y, x = pixel[0] - (t1 // 3 - 1), pixel[1] - (t1 % 3 - 1)          # the output pixel at which tap t1 sees the infinity
+        row = int(columns(t1)[c])
+        if not inside(y, x):
+            blind.append(row)
+            continue
+        assert not torch.isfinite(A[row, -1]) and not torch.isfinite(A[row, row])
+        for t2 in range(9):
+            if inside(y + t2 // 3 - 1, x + t2 % 3 - 1):
+                assert not torch.isfinite(A[row, columns(t2)]).any() and not torch.isfinite(A[columns(t2), row]).any(), (t1, t2)
+    assert torch.isfinite(A[blind][:, blind]).all()
