@@ -39,6 +39,27 @@ PEAK = {"mfma_bf16": 2500.0, "mfma_f32": 157.3, "hbm": 8000.0}   # TFLOP/s, TFLO
 PEAK["mfma_f16x2"] = round(PEAK["mfma_bf16"] / 3, 1)
 
 
+# 3 x 3 layers of stride 1 are built from the sums that their tap pairs share, from so many rows and input elements on
+SHARED_ROWS, SHARED_ELEMENTS = 1024, 1 << 17
+DENSE_BASIS = "flops of the dense form, R d (d + 1) of every factor, of which factor_formed_tflops counts the products that are formed"
+
+
+def formed_factor_work(s):
+    """(columns of the products, flops) of each factor of a layer as it is built: a factor A of a 3 x 3 layer of stride 1 and padding 1 from
+    the C x C sums that its tap pairs share (12.5 of them, with the symmetric one's half, instead of 40.5); every other one R d (d + 1)."""
+    a = (s.d_A - s.has_bias, kstep.factor_flops(s.R, s.d_A))
+    if (s.kh, s.kw, s.stride, s.pad) == (3, 3, 1, 1) and s.C_in % 64 == 0 and s.R >= SHARED_ROWS and s.R * s.C_in >= SHARED_ELEMENTS:
+        a = (s.C_in, 25.0 * s.R * s.C_in * s.C_in)
+    return a, (s.d_G, kstep.factor_flops(s.R, s.d_G))
+
+
+def factor_rates(layers, ms):
+    """The factor stage's rate on the dense form's flops, and on those of the products that are formed."""
+    dense = sum(kstep.factor_flops(s.R, s.d_A) + kstep.factor_flops(s.R, s.d_G) for s in layers)
+    formed = sum(flops for s in layers for _, flops in formed_factor_work(s))
+    return dense / (ms * 1e-3) / 1e12, formed / (ms * 1e-3) / 1e12
+
+
 def kernel_work(net: kstep.KfacNetworkStep, kernels):
     """Algorithmic work of each kernel over ONE step of the whole network: (bound, peak, unit, amount).  kernels: the names of
     those that ran (which width of tiles the wide factors were built with is the library's choice)."""
@@ -46,15 +67,11 @@ def kernel_work(net: kstep.KfacNetworkStep, kernels):
     dims = [d for s in shapes for d in (s.d_A, s.d_G)]
 
     # every factor is built by the tile kernel: up to 64 columns (without the bias) by the 64-wide one, up to 128 by the 128-wide
-    # one, wider ones all by the 128- or all by the 256-wide one; 3 x 3 layers of stride 1 from the C x C sums that their tap pairs
-    # share (12.5 of them, with the symmetric one's half)
+    # one, wider ones all by the 128- or all by the 256-wide one
     wide = 256 if "factor_tile_kernel<256, 16-bit>" in kernels else 128
     fac_tile = {64: 0.0, 128: 0.0, 256: 0.0}
     for s in shapes:
-        for d, columns in ((s.d_A, s.d_A - s.has_bias), (s.d_G, s.d_G)):
-            flops = kstep.factor_flops(s.R, d)
-            if d == s.d_A and (s.kh, s.kw, s.stride, s.pad) == (3, 3, 1, 1) and s.C_in % 64 == 0:
-                columns, flops = s.C_in, 25.0 * s.R * s.C_in * s.C_in
+        for columns, flops in formed_factor_work(s):
             fac_tile[64 if columns <= 64 else 128 if columns <= 128 else wide] += flops
     w = {
         # all steps of all matrices in one kernel: rank-128 updates (fp16 pieces), panel products (2 d nb^2 a step, bf16 pieces) and
@@ -278,7 +295,7 @@ def run_cfg4(args):
     fresh_ms = avg(lambda: net.step(refresh_inverse=True), 3)
     stale_ms = avg(lambda: net.step(refresh_inverse=False), 5)
     assert int(net.inverse_info().abs().max()) == 0
-    fac_flops = sum(kstep.factor_flops(s.R, s.d_A) + kstep.factor_flops(s.R, s.d_G) for s in layers)
+    dense_rate, formed_rate = factor_rates(layers, stale_ms)
     print(json.dumps({
         "metric": "ResNet-50 K-FAC step ms/GPU @ batch 128, inverses every 10th step (amortised over 20 steps)",
         "value": round(total_ms / steps, 3), "unit": "ms", "n_gpus": 1, "steps": steps, "warmup": args.warmup,
@@ -287,7 +304,8 @@ def run_cfg4(args):
         "config": {"workload": "resnet50_kfac_step_all54layers_batch128_inverse_every10", "per_gpu_batch": 128,
                    "layers": len(layers), "decay": 0.95, "gamma": 1e-4, "refresh_steps": [0, 10]},
         "step_with_refresh_ms": round(fresh_ms, 3), "stale_step_ms": round(stale_ms, 3),
-        "factor_tflops_stale_step_bound": round(fac_flops / (stale_ms * 1e-3) / 1e12, 1)}))
+        "factor_tflops_stale_step_bound": round(dense_rate, 1), "factor_tflops_basis": DENSE_BASIS,
+        "factor_formed_tflops": round(formed_rate, 1)}))
 
 
 # what each stage computes in (the whole path stores and accumulates in fp32)
@@ -383,7 +401,7 @@ def main():
                 "traffic_source": traffic["source"] if traffic else None,
                 "avg_launch_us": dom["avg_launch_us"], "launches_per_step": dom["launches_per_step"]}
 
-    fac_flops = sum(kstep.factor_flops(s.R, s.d_A) + kstep.factor_flops(s.R, s.d_G) for s in layers)
+    dense_rate, formed_rate = factor_rates(layers, stages["factors"])
     fac_ideal_ms = factor_shape_roofline_ms(layers)
     out = {
         "metric": "ResNet-50 K-FAC step ms/GPU @ batch 32; factor TFLOP/s & % MFMA peak",
@@ -396,8 +414,9 @@ def main():
         # chains of the widest layers start first and everything else runs beside them), so value < their sum
         "stage_ms": {k: round(v, 3) for k, v in stages.items()},
         "schedule": f"{len(net.waves)} waves" if net.pipelined and net.waves else "stage by stage",
-        "factor_tflops": round(fac_flops / (stages["factors"] * 1e-3) / 1e12, 2),
-        "factor_frac_of_bf16_mfma_peak": round(fac_flops / (stages["factors"] * 1e-3) / 1e12 / PEAK["mfma_bf16"], 4),
+        "factor_tflops": round(dense_rate, 2), "factor_frac_of_bf16_mfma_peak": round(dense_rate / PEAK["mfma_bf16"], 4),
+        "factor_tflops_basis": DENSE_BASIS,
+        "factor_formed_tflops": round(formed_rate, 2), "factor_formed_frac_of_bf16_mfma_peak": round(formed_rate / PEAK["mfma_bf16"], 4),
         # many factors are bandwidth- rather than matrix-core-bound (narrow ones over many rows): the sum over all 108
         # of the larger of their two ideal times, against the stage
         "factor_shape_roofline_ms": round(fac_ideal_ms, 4),
