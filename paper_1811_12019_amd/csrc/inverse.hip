@@ -1166,14 +1166,9 @@ __device__ __forceinline__ void step_pivot(const Item& it, int step, float* __re
     pivot_write(acc, lds, it, ws, k0, nb, k0 + NB >= d, false);
 }
 
-// The first step that tile (I, J) owes of the steps lo .. hi, and where its old values are (owed_first).
+// The first step that tile (I, J) owes of the steps lo .. hi, and where its old values are if not where `o` says (owed_first).
 __device__ __forceinline__ int owed_from(const WsView& ws, int I, int J, int lo, int hi, OldSrc& o) {
-    int kind;
-    const int first = owed_first(I, J, lo, hi, kind);
-    o = OldSrc{OLD_W, ws.tile(I, J)};
-    if (kind == OLD_T_TURNED) o = OldSrc{kind, ws.T(I % NBUF) + (size_t)J * (NB * NB)};
-    if (kind == OLD_T) o = OldSrc{kind, ws.T(J % NBUF) + (size_t)I * (NB * NB)};
-    return first;
+    return owed_first(I, J, lo, hi, [&](int kind, int step, int slab) { o = OldSrc{kind, ws.T(step % NBUF) + (size_t)slab * (NB * NB)}; });
 }
 
 // Tile (I, J) of a step that is not the matrix's last: brings it up to date through step g.g0 + g.j.

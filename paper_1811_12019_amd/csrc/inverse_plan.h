@@ -118,18 +118,18 @@ constexpr int NBUF = 2 * GM;     // panel buffers: buffer = step % NBUF
 // (block column) or transposed (block row).
 enum { OLD_W, OLD_T, OLD_T_TURNED };
 
-// The first step that tile (I, J) owes of the steps lo .. hi, and where its old values are: the working copy, unless one of its blocks
-// is among lo .. hi.  Such a tile was kept up to date until its later such block c was eliminated (when it became part of panel c:
-// T_I (OLD_T) for a tile of block column c, T_J transposed (OLD_T_TURNED) for one of block row c, neither written to the working copy
-// then), and owes the steps after c; the diagonal tile (c, c) is -P_c, which the pivot code did write.
-static inline __host__ __device__ int owed_first(int I, int J, int lo, int hi, int& kind) {
-    kind = OLD_W;
+// The first step that tile (I, J) owes of the steps lo .. hi.  Its old values are in the working copy, unless one of its blocks is among
+// lo .. hi: such a tile was kept up to date until its later such block c was eliminated (when it became part of panel c: T_I (OLD_T) for a
+// tile of block column c, T_J transposed (OLD_T_TURNED) for one of block row c, neither written to the working copy then), and owes
+// the steps after c; old_in(kind, c, slab) is called with what that is.  The diagonal tile (c, c) is -P_c, which the pivot code did write.
+template <class F>
+__host__ __device__ __forceinline__ int owed_first(int I, int J, int lo, int hi, F&& old_in) {
     if (I >= lo && I <= hi) {                            // I is the later block (I >= J)
-        if (I != J) kind = OLD_T_TURNED;
+        if (I != J) old_in(OLD_T_TURNED, I, J);
         return I + 1;
     }
     if (J >= lo && J <= hi) {                            // I lies beyond
-        kind = OLD_T;
+        old_in(OLD_T, J, I);
         return J + 1;
     }
     return lo;

@@ -48,8 +48,15 @@ struct Matrix {
     Cell& t(int step, int I) { return T[step % NBUF * n + I]; }
     Cell& u(int step, int I) { return U[step % NBUF * n + I]; }
 
-    double old_of(int I, int J, int kind) {
-        return kind == OLD_T_TURNED ? t(I, J).read("old value in block row's T") : kind == OLD_T ? t(J, I).read("old value in T") : w(I, J).read("old value");
+    // the first step that a tile owes, and its old value
+    int owed(int I, int J, int lo, int hi, double& old) {
+        bool in_panel = false;
+        const int first = owed_first(I, J, lo, hi, [&](int, int step, int slab) {
+            in_panel = true;
+            old = t(step, slab).read("old value in T");
+        });
+        if (!in_panel) old = w(I, J).read("old value");
+        return first;
     }
     double products(int first, int last, int I, int J, double x) {
         for (int q = first; q <= last; ++q) x -= t(q, I).read("tile's T") * u(q, J).read("tile's U");
@@ -57,9 +64,11 @@ struct Matrix {
     }
     void tile(int I, int J, const Group& g, bool single) {
         const int last = g.g0 + g.j;
-        int kind = OLD_W, first = last;
-        if (!single) first = owed_first(I, J, g.g0, last, kind);
-        w(I, J).write(products(first, last, I, J, old_of(I, J, kind)), "tile");
+        double old;
+        int first = last;
+        if (single) old = w(I, J).read("old value");
+        else first = owed(I, J, g.g0, last, old);
+        w(I, J).write(products(first, last, I, J, old), "tile");
     }
     void begin() {
         launch = -1;
@@ -128,7 +137,7 @@ struct Matrix {
             else tile(I, J, g, single);
         }
     }
-    void outputs(bool owed) {
+    void outputs(bool out_owed) {
         launch = n;
         const int s = n - 1;
         for (int e = 0; e < n * (n + 1) / 2; ++e) {
@@ -139,10 +148,12 @@ struct Matrix {
             if (I == s) {
                 x = t(s, J).read("last T of the block row");
             } else {
-                int kind = OLD_W;
-                const int first = owed ? owed_first(I, J, (s - 1) / GM * GM, s - 1, kind) : s;
+                double old;
+                int first = s;
+                if (out_owed) first = owed(I, J, (s - 1) / GM * GM, s - 1, old);
+                else old = w(I, J).read("old value");
                 if (s - first > GM) fault("products of an output tile");
-                x = products(first, s, I, J, old_of(I, J, kind));
+                x = products(first, s, I, J, old);
             }
             out[I * n + J].write(-x, "output");
         }
@@ -177,11 +188,11 @@ int main(int argc, char** argv) {
     for (blocks = lo; blocks <= hi; ++blocks) {
         launch = -1;
         check_schedule(blocks);
-        for (int owed = 0; owed < 2; ++owed) {
+        for (int out_owed = 0; out_owed < 2; ++out_owed) {
             Matrix m(blocks);
             m.begin();
-            for (int s = 0; s < blocks; ++s) m.stage(s, owed);
-            m.outputs(owed);
+            for (int s = 0; s < blocks; ++s) m.stage(s, out_owed);
+            m.outputs(out_owed);
             m.check();
         }
     }
