@@ -55,6 +55,20 @@ __device__ __forceinline__ KFAC_AS1 T* as_global(T* p) {
     return (KFAC_AS1 T*)p;
 }
 
+// A value that is the same in all lanes but was loaded by vector instructions (a descriptor in memory), dword by dword in scalar
+// registers: what is worked out from it costs no vector registers and no vector instructions.
+template <class T>
+__device__ __forceinline__ T uniform(const T& x) {
+    static_assert(sizeof(T) % 4 == 0, "dwords");
+    int w[sizeof(T) / 4];
+    __builtin_memcpy(w, &x, sizeof(T));
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(T) / 4; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+    T y;
+    __builtin_memcpy(&y, w, sizeof(T));
+    return y;
+}
+
 // Where a symmetric d x d result goes (the factor builders' epilogues):
 //   plain    dst = the d x d square, both triangles written
 //   ema      dst = the running average S, updated in place: S <- decay S + (1 - decay) value   (both triangles)

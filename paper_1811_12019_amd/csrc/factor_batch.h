@@ -139,7 +139,8 @@ __device__ __forceinline__ int fbatch_locate(const FBatch& b, int wg, int& local
 // (a launch of builds that are not read as planes: PLANES = false)
 template <bool PLANES = true>
 __device__ __forceinline__ void fbatch_item(const FBatch& b, int m, kfac_factor_item& it, Unfold& u, View& v) {
-    it = b.table ? b.table[b.index[m]] : b.single;
+    if (b.table) it = uniform(b.table[b.index[m]]);
+    else it = b.single;
     if (it.op == KFAC_OP_FACTOR_A) make_unfold_A(&it.desc, &u); else make_unfold_G(&it.desc, &u);
     make_view(u, &v);
     if (PLANES && (b.share[m] & SHARE_PLANES)) planes_view(u, &v);

@@ -244,6 +244,10 @@ struct TileJob {
 // the fast one in memory, as the MFMA wants it, and a lane's operand is one 16-byte read.
 enum { FEED_PATCHES, FEED_PIXELS, FEED_WINDOW, FEED_PLANES };
 
+// Where a copy comes from: an offset from the tensor (16-bit), or an address.
+template <int ES> struct TileAddr { typedef unsigned type; };
+template <> struct TileAddr<4> { typedef unsigned long long type; };
+
 // An operand of one K step of a 32-column block: read in pieces of two registers, or (PLANES) in one of four.
 template <bool PLANES, int PIECES> struct OperandRegs { typedef v2u type[PIECES]; };
 template <int PIECES> struct OperandRegs<true, PIECES> { typedef v4u type; };
@@ -265,9 +269,10 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     constexpr int PANEL = DK * TW * ES;                        // bytes of one operand panel of one slab
     constexpr int STAGE = DIAG ? PANEL : 2 * PANEL;
     constexpr int NS = DIAG ? 2 * S::NS : S::NS;
-    constexpr int PW = DIAG ? NW : NW / 2;                     // wavefronts that fill a panel
-    constexpr int NI = PANEL / 1024 / PW;                      // copies (1 KB each) per wavefront and slab
-    static_assert(NI * PW * 1024 == PANEL && NI >= 1 && (NS - 2) * NI < 64, "every wavefront issues the same number of copies");
+    constexpr int NP = DIAG ? 1 : 2;                           // panels
+    constexpr int NB2 = PANEL / 1024 / NW;                     // copies (1 KB each) per wavefront, slab and panel
+    constexpr int NI = NP * NB2;
+    static_assert(NB2 == 2 && NB2 * NW * 1024 == PANEL && (NS - 2) * NI < 64, "every wavefront issues two copies a panel");
     constexpr int RGS = 8 * TW;                                // 16-bit: bytes of four rows
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
     const Unfold& u = v.u;
@@ -279,123 +284,175 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     const int nst = (r_end - r_begin + DK - 1) / DK;
     const int wr = wm * S::MB * 32, wc = wn * S::NB * 32;      // this wavefront's part of the tile
 
-    // ---- producer: this wavefront fills blocks b0, b0 + PW, ... of panel `pan`; block = 64 consecutive 16-byte slots ----
+    // ---- producer: this wavefront fills blocks block(0) and block(1) of every panel; block = 64 consecutive 16-byte slots ----
     // 16-bit slab: slot (row r, vector q) of four rows 4 rg .. 4 rg + 3 is rg (TW / 2) + 8 (q / 2) + 2 (r % 4) + q % 2: every
     // 16-lane transposed read is then a contiguous 128-byte run.  fp32 slab: row-major.
-    const int pan = DIAG ? 0 : wave / PW;
-    const int b0 = wave % PW;
+    // A lane copies the same rows of both panels: one row (two vectors of each panel) of a 256-wide slab, else two rows, so that
+    // most of the address arithmetic, which runs on the pipes the matrix cores are issued from, is done once for two or four copies.
     // PLANES: slot = column CH + (16 bytes of its DK rows ^ a number that differs in any 16 columns read at once): a lane's row is
-    // b0's in all blocks, its column CSTEP further on from block to block.
-    constexpr int CH = DK / V, CSTEP = PW * 64 / CH, FLIP = 16 / CH;
+    // the same in all blocks, its column CSTEP further on from block to block.
+    constexpr bool PAIR = !PLANES && TW == 256;                // both blocks hold the same four rows
+    constexpr int NR = PLANES || PAIR ? 1 : 2, NC = PAIR ? 2 : 1;      // rows, and vectors of a panel's row, of a lane
+    constexpr int CH = DK / V, CSTEP = NW * 64 / CH, FLIP = 16 / CH;
     static_assert(CSTEP % 16 == 0, "the flip is the same in all blocks");
-    int row0, q;                                               // row inside the slab for block b0, vector (PLANES: column)
-    constexpr int ROWSTEP = ES == 4 ? PW * 64 / (TW / 4) : PW * 64 / (TW / 2) * 4;    // rows from one block of this wavefront to the next
-    static_assert(ES == 4 ? (PW * 64) % (TW / 4) == 0 : (PW * 64) % (TW / 2) == 0, "a lane keeps its column vector from block to block");
-    if constexpr (PLANES) {
-        const int L = b0 * 64 + lane;
-        q = L / CH;
-        row0 = ((L % CH) ^ (q / FLIP % CH)) * V;
-    } else if constexpr (ES == 4) {
-        const int L = b0 * 64 + lane;
-        row0 = L / (TW / 4);
-        q = L % (TW / 4);
-    } else {
-        const int L = b0 * 64 + lane, s = L % (TW / 2);
-        row0 = 4 * (L / (TW / 2)) + ((s & 7) >> 1);
-        q = 2 * (s >> 3) + (s & 1);
+    auto block = [&](int j) { return PAIR ? 2 * wave + j : wave + NW * j; };
+    int row0, q;                                               // row inside the slab, vector (PLANES: column) of block 0
+    constexpr int ROWSTEP = ES == 4 ? NW * 64 / (TW / 4) : NW * 64 / (TW / 2) * 4;    // rows from block 0 to block 1 (not PAIR)
+    {
+        const int L = block(0) * 64 + lane;
+        if constexpr (PLANES) {
+            q = L / CH;
+            row0 = ((L % CH) ^ (q / FLIP % CH)) * V;
+        } else if constexpr (ES == 4) {
+            row0 = L / (TW / 4);
+            q = L % (TW / 4);
+        } else {
+            const int s = L % (TW / 2);
+            row0 = 4 * (L / (TW / 2)) + ((s & 7) >> 1);
+            q = 2 * (s >> 3) + (s & 1);
+        }
     }
-    ColGroup g;
-    if constexpr (WINDOW) {
-        g.ki = g.kj = 0;
-        g.off = (pan == 0 ? I : J) * TW + q * V;
-        g.data = g.off < D;
-        g.off += pan == 0 ? job.first_pixel * u.C : (job.first_pixel + job.partner) * u.C;
-    } else if constexpr (PLANES) {
-        g.ki = g.kj = 0;
-        g.off = (pan == 0 ? I : J) * TW + q;
-        g.data = g.off < D;
-    } else {
-        g = decode_group(v, (pan == 0 ? I : J) * TW + q * V);
+    lds_byte* lds0 = (lds_byte*)smem;
+    // 16-bit tensors stay below 4 GB (make_view): byte offsets of 32 bits, and what is to be zero lies outside the buffer, for which
+    // the hardware gives zeros.  fp32 ones need 64 bits, and a block of zeros.
+    typedef typename TileAddr<ES>::type addr_t;
+    const unsigned bytes = (unsigned)(ES * ((long long)u.N * u.H * u.W * u.C));
+    const __amdgpu_buffer_rsrc_t tensor = __builtin_amdgcn_make_buffer_rsrc((void*)x, 0, bytes, 0x00027000);
+    const addr_t base = ES == 2 ? (addr_t)0 : (addr_t)(unsigned long long)x;
+    const addr_t nowhere = ES == 2 ? (addr_t)0xFFFFFFF0u : (addr_t)(unsigned long long)(const KFAC_AS1 unsigned char*)&g_zero_chunk;
+    int left = r_end - r_begin - row0;                         // the lane's (first) row is there while this is positive
+
+    // Columns: of the lane's vectors, the byte offset behind the row's, the tap (PATCHES; never in the image if the vector lies beyond
+    // the matrix), and what `left` has to exceed (the others; -> never).
+    addr_t coff[NP][NC];
+    int cki[NP][NC], ckj[NP][NC], need[NP][NC];
+    if constexpr (!PLANES) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const int col = (p == 0 ? I : J) * TW + (q + c * 16) * V;
+                ColGroup g;
+                if constexpr (WINDOW) {
+                    g.ki = g.kj = 0;
+                    g.data = col < D;
+                    g.off = col + (p == 0 ? job.first_pixel : job.first_pixel + job.partner) * u.C;
+                } else {
+                    g = decode_group(v, col);
+                }
+                coff[p][c] = (addr_t)((long long)ES * g.off);
+                cki[p][c] = g.data ? g.ki - u.pad : 0x40000000;
+                ckj[p][c] = g.kj - u.pad;
+                need[p][c] = g.data ? 0 : 0x7fffffff;
+            }
     }
-    lds_byte* lds0 = (lds_byte*)smem + pan * PANEL + b0 * 1024;
-    const unsigned long long zero_addr = (unsigned long long)(const KFAC_AS1 unsigned char*)&g_zero_chunk;
 
     // PLANES: this lane's 16 bytes of column q, advanced by DK pixels from slab to slab: pn images and pp pixels, with at most one carry.
-    unsigned long long plane_at = 0, plane_step = 0, plane_carry = 0;
-    const long long column_step = (long long)ES * CSTEP * u.H * u.W;
+    addr_t plane_at = 0, plane_step = 0, plane_carry = 0, plane_col[NP][2];
     int plane_px = 0, plane_dx = 0;
-    const int columns_left = D - g.off;                        // (column j: there while above j CSTEP)
     if constexpr (PLANES) {
         const int size = u.H * u.W, R = r_begin + row0, n = R / size;
         plane_px = R - n * size;
         plane_dx = DK % size;
-        plane_at = (unsigned long long)x + (unsigned long long)(ES * (((long long)n * u.C + g.off) * size + plane_px));
-        plane_step = (unsigned long long)(ES * ((long long)(DK / size) * u.C * size + plane_dx));
-        plane_carry = (unsigned long long)(ES * ((long long)u.C - 1) * size);
+        plane_at = base + (addr_t)((long long)ES * ((long long)n * u.C * size + plane_px));
+        plane_step = (addr_t)(ES * ((long long)(DK / size) * u.C * size + plane_dx));
+        plane_carry = (addr_t)(ES * ((long long)u.C - 1) * size);
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int col = (p == 0 ? I : J) * TW + q + j * CSTEP;
+                plane_col[p][j] = (addr_t)((long long)ES * col * size);
+                need[p][0] = 0;
+                if (j == 0) cki[p][0] = D - col;               // (column j: there while above j CSTEP)
+            }
     }
 
-    // The NI rows whose vectors this lane copies, advanced by DK rows from slab to slab without divisions: DK rows are
+    // The rows whose vectors this lane copies, advanced by DK rows from slab to slab without divisions: DK rows are
     // dn images, dy image rows and dx pixels, each with at most one carry into the next.
-    unsigned long long at[NI];                                 // address of the row's vector (patch origin + tap + channels)
-    int ty[NI], tx[NI];                                        // where in the image the row's tap lies
+    addr_t at[NR];                                             // address of the row's patch origin
+    int ty[NR], tx[NR];                                        // the patch origin's place in the (padded) image
     const int hw = u.Ho * u.Wo;
     const int dn = DK / hw, dyr = DK % hw, dy = dyr / u.Wo, dx = dyr % u.Wo;
     const long long px = (long long)ES * u.C;                  // bytes of a pixel
     const int st_x = dx * u.stride, st_y = dy * u.stride, wrap_x = u.Wo * u.stride, wrap_y = u.Ho * u.stride;
-    const int end_x = wrap_x - u.pad + g.kj, end_y = wrap_y - u.pad + g.ki;
-    const long long step_bytes = PLAIN ? DK * px : px * ((long long)dn * u.H * u.W + (long long)st_y * u.W + st_x);
-    const long long carry_x = px * ((long long)u.stride * u.W - wrap_x), carry_y = px * ((long long)u.H * u.W - (long long)wrap_y * u.W);
+    const addr_t step_bytes = (addr_t)(PLAIN ? DK * px : px * ((long long)dn * u.H * u.W + (long long)st_y * u.W + st_x));
+    const addr_t carry_x = (addr_t)(px * ((long long)u.stride * u.W - wrap_x));
+    const addr_t carry_y = (addr_t)(px * ((long long)u.H * u.W - (long long)wrap_y * u.W));
+    if constexpr (!PLANES) {
 #pragma unroll
-    for (int j = 0; j < NI; ++j) {
-        const int R = r_begin + row0 + j * ROWSTEP;
-        if constexpr (PLANES) {
-        } else if constexpr (PLAIN) {
-            at[j] = (unsigned long long)x + (unsigned long long)((long long)R * px + (long long)ES * g.off);
-        } else {
-            const int n = R / hw, rem = R - n * hw, yo = rem / u.Wo, xo = rem - yo * u.Wo;
-            const int y0 = yo * u.stride - u.pad, x0 = xo * u.stride - u.pad;
-            ty[j] = y0 + g.ki;
-            tx[j] = x0 + g.kj;
-            at[j] = (unsigned long long)x + (unsigned long long)(px * (((long long)n * u.H + y0) * u.W + x0) + (long long)ES * g.off);
+        for (int j = 0; j < NR; ++j) {
+            const int R = r_begin + row0 + j * ROWSTEP;
+            if constexpr (PLAIN) {
+                at[j] = base + (addr_t)((long long)R * px);
+            } else {
+                const int n = R / hw, rem = R - n * hw, yo = rem / u.Wo, xo = rem - yo * u.Wo;
+                ty[j] = yo * u.stride;
+                tx[j] = xo * u.stride;
+                at[j] = base + (addr_t)(px * (((long long)n * u.H + ty[j] - u.pad) * u.W + tx[j] - u.pad));
+            }
         }
     }
-    int rows_left = r_end - r_begin - row0;                    // valid while positive (row j: while above j ROWSTEP)
-    if (!g.data) rows_left = -0x40000000;                      // a column vector beyond the matrix: never
 
-    // copies of the next slab into the ring at stage_off (branch-free; slabs are issued in order)
-    auto issue = [&](int stage_off) {
-        unsigned long long src[NI];
+    // Where the next slab's copies come from (branch-free; slabs in order), and the copies themselves, into the ring at stage_off.
+    auto sources = [&](addr_t (&src)[NP][2]) {
         if constexpr (PLANES) {
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
-                src[j] = ((rows_left > 0) & (columns_left > j * CSTEP)) ? plane_at + (unsigned long long)(j * column_step) : zero_addr;
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    src[p][j] = ((left > 0) & (cki[p][0] > j * CSTEP)) ? plane_at + plane_col[p][j] : nowhere;
             plane_at += plane_step;
             plane_px += plane_dx;
             const bool carry = plane_px >= u.H * u.W;
             plane_px -= carry ? u.H * u.W : 0;
             plane_at += carry ? plane_carry : 0;
-        } else
+        } else {
 #pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            bool ok = rows_left > j * ROWSTEP;
-            if constexpr (FEED == FEED_PATCHES) ok = ok & ((unsigned)ty[j] < (unsigned)u.H) & ((unsigned)tx[j] < (unsigned)u.W);
-            src[j] = ok ? at[j] : zero_addr;
-            at[j] += (unsigned long long)step_bytes;
-            if constexpr (!PLAIN) {
-                tx[j] += st_x;
-                const bool cx = tx[j] >= end_x;
-                tx[j] -= cx ? wrap_x : 0;
-                ty[j] += st_y + (cx ? u.stride : 0);
-                const bool cy = ty[j] >= end_y;
-                ty[j] -= cy ? wrap_y : 0;
-                at[j] += (unsigned long long)((cx ? carry_x : 0) + (cy ? carry_y : 0));
+            for (int j = 0; j < NR; ++j) {
+#pragma unroll
+                for (int p = 0; p < NP; ++p)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) {
+                        bool ok;
+                        if constexpr (FEED == FEED_PATCHES)
+                            ok = (left > j * ROWSTEP) & ((unsigned)(ty[j] + cki[p][c]) < (unsigned)u.H) & ((unsigned)(tx[j] + ckj[p][c]) < (unsigned)u.W);
+                        else
+                            ok = left - j * ROWSTEP > need[p][c];
+                        src[p][PAIR ? c : j] = ok ? at[j] + coff[p][c] : nowhere;
+                    }
+                if constexpr (PLAIN) {
+                    at[j] += step_bytes;
+                } else {
+                    tx[j] += st_x;
+                    const bool cx = tx[j] >= wrap_x;
+                    tx[j] -= cx ? wrap_x : 0;
+                    ty[j] += st_y + (cx ? u.stride : 0);
+                    const bool cy = ty[j] >= wrap_y;
+                    ty[j] -= cy ? wrap_y : 0;
+                    at[j] += step_bytes + (cx ? carry_x : 0) + (cy ? carry_y : 0);
+                }
             }
         }
-        rows_left -= DK;
+        left -= DK;
+    };
+    auto copy = [&](const addr_t (&src)[NP][2], int stage_off) {
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src[j],
-                                             (__attribute__((address_space(3))) void*)(lds0 + stage_off + j * PW * 1024), 16, 0, 0);
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                __attribute__((address_space(3))) void* dst =
+                    (__attribute__((address_space(3))) void*)(lds0 + stage_off + p * PANEL + block(j) * 1024);
+                if constexpr (ES == 2)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(tensor, dst, 16, (int)src[p][j], 0, 0, 0);
+                else
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src[p][j], dst, 16, 0, 0);
+            }
+    };
+    auto issue = [&](int stage_off) {
+        addr_t src[NP][2];
+        sources(src);
+        copy(src, stage_off);
     };
 
     // ---- pipeline ----
