@@ -225,6 +225,13 @@ template <int TW, int ES> constexpr int tile_ring_bytes() { return TileShape<TW,
 template <int TW, int ES> constexpr int tile_lds_bytes() { return tile_ring_bytes<TW, ES>() + 4 * TW * 4; }
 
 template <int N> struct StaticInt { static constexpr int value = N; };
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {              // f(StaticInt<0>{}) .. f(StaticInt<N - 1>{})
+    if constexpr (I < N) {
+        f(StaticInt<I>{});
+        static_for<N, I + 1>(f);
+    }
+}
 
 // What a tile's workgroup works on.
 struct TileJob {
@@ -279,8 +286,8 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     const int t = threadIdx.x;
     const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave / S::WN, wn = wave % S::WN;
     const int lm = lane & 31, h = lane >> 5;
-    const int I = job.I, J = job.J, D = u.d;
-    const int r_begin = job.r_begin, r_end = job.r_end;
+    const int I = __builtin_amdgcn_readfirstlane(job.I), J = __builtin_amdgcn_readfirstlane(job.J), D = u.d;
+    const int r_begin = __builtin_amdgcn_readfirstlane(job.r_begin), r_end = __builtin_amdgcn_readfirstlane(job.r_end);
     const int nst = (r_end - r_begin + DK - 1) / DK;
     const int wr = wm * S::MB * 32, wc = wn * S::NB * 32;      // this wavefront's part of the tile
 
@@ -394,14 +401,23 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
         }
     }
 
-    // Where the next slab's copies come from (branch-free; slabs in order), and the copies themselves, into the ring at stage_off.
-    auto sources = [&](addr_t (&src)[NP][2]) {
+    // Where copy i of the next slab comes from (branch-free; slabs in order; i = 2 p + block), the step on to the slab after it, and the
+    // copy itself, into the ring at stage_off.
+    auto source = [&](auto i) -> addr_t {
+        constexpr int p = decltype(i)::value / 2, b = decltype(i)::value % 2, j = NR == 2 ? b : 0, c = PAIR ? b : 0;
         if constexpr (PLANES) {
-#pragma unroll
-            for (int p = 0; p < NP; ++p)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    src[p][j] = ((left > 0) & (cki[p][0] > j * CSTEP)) ? plane_at + plane_col[p][j] : nowhere;
+            return ((left > 0) & (cki[p][0] > b * CSTEP)) ? plane_at + plane_col[p][b] : nowhere;
+        } else {
+            bool ok;
+            if constexpr (FEED == FEED_PATCHES)
+                ok = (left > j * ROWSTEP) & ((unsigned)(ty[j] + cki[p][c]) < (unsigned)u.H) & ((unsigned)(tx[j] + ckj[p][c]) < (unsigned)u.W);
+            else
+                ok = left - j * ROWSTEP > need[p][c];
+            return ok ? at[j] + coff[p][c] : nowhere;
+        }
+    };
+    auto advance = [&]() {
+        if constexpr (PLANES) {
             plane_at += plane_step;
             plane_px += plane_dx;
             const bool carry = plane_px >= u.H * u.W;
@@ -410,17 +426,6 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
         } else {
 #pragma unroll
             for (int j = 0; j < NR; ++j) {
-#pragma unroll
-                for (int p = 0; p < NP; ++p)
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        bool ok;
-                        if constexpr (FEED == FEED_PATCHES)
-                            ok = (left > j * ROWSTEP) & ((unsigned)(ty[j] + cki[p][c]) < (unsigned)u.H) & ((unsigned)(tx[j] + ckj[p][c]) < (unsigned)u.W);
-                        else
-                            ok = left - j * ROWSTEP > need[p][c];
-                        src[p][PAIR ? c : j] = ok ? at[j] + coff[p][c] : nowhere;
-                    }
                 if constexpr (PLAIN) {
                     at[j] += step_bytes;
                 } else {
@@ -436,63 +441,67 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
         }
         left -= DK;
     };
-    auto copy = [&](const addr_t (&src)[NP][2], int stage_off) {
-#pragma unroll
-        for (int p = 0; p < NP; ++p)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                __attribute__((address_space(3))) void* dst =
-                    (__attribute__((address_space(3))) void*)(lds0 + stage_off + p * PANEL + block(j) * 1024);
-                if constexpr (ES == 2)
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(tensor, dst, 16, (int)src[p][j], 0, 0, 0);
-                else
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src[p][j], dst, 16, 0, 0);
-            }
-    };
-    auto issue = [&](int stage_off) {
-        addr_t src[NP][2];
-        sources(src);
-        copy(src, stage_off);
+    auto copy = [&](addr_t src, auto i, int stage_off) {
+        __attribute__((address_space(3))) void* dst =
+            (__attribute__((address_space(3))) void*)(lds0 + stage_off + decltype(i)::value / 2 * PANEL + block(decltype(i)::value % 2) * 1024);
+        if constexpr (ES == 2)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(tensor, dst, 16, (int)src, 0, 0, 0);
+        else
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, dst, 16, 0, 0);
     };
 
     // ---- pipeline ----
     // A slab is multiplied in STEPS steps; the operands of the next step are on their way from LDS while one is multiplied
-    // (read: starts them into one of two register sets; multiply: uses a set).  The barrier sits before a slab's last step:
-    // this wavefront has then read all of the slab, so that once everybody is there the slab's place is refilled, and
-    // the first operands of the next slab, whose copies have landed, are read during the last step's products.
+    // (read: starts one of READS operand reads into one of two register sets; multiply: one of the MULS products of a set).  The barrier
+    // sits before a slab's last step: this wavefront has then read all of the slab, so that once everybody is there the slab's place may
+    // be refilled, which the next slab's first step does, and the first operands of the next slab, whose copies have landed, are read
+    // during the last step's products.  A product occupies the matrix cores for 32 cycles (fp32: 64): reads, address arithmetic and
+    // copies are dealt out between the products, one fenced group after each (left alone, they gather before or behind them, in all
+    // wavefronts at the same time).
     constexpr int STEPS = ES == 2 ? DK / 16 : PLANES ? DK / 8 : DK / 4;
     static_assert(STEPS % 2 == 0, "the register sets alternate across slabs");
-    // (The scheduling fences keep a step's products between the waits: left alone, they sink below the next ones.)
-    auto pipeline = [&](auto reads_per_step, auto&& read, auto&& arrived, auto&& multiply) {
+    auto pipeline = [&](auto muls, auto reads, auto&& read, auto&& arrived, auto&& multiply) {
+        constexpr int MULS = decltype(muls)::value, READS = decltype(reads)::value;
+        constexpr int SLOTS = MULS > 0 ? MULS : 1, LAST = SLOTS - SLOTS / 4;        // reads go behind the first LAST products
+        constexpr int CPS = (NI + 1 + SLOTS - 1) / SLOTS;                           // copies (and the step on) to a slot
+        auto step = [&](auto e, int next_off, int freed) {                          // multiply step e, read step e + 1, refill `freed`
+            constexpr int E = decltype(e)::value, NEXT = (E + 1) % STEPS;
+            arrived(E & 1);
+            static_for<SLOTS>([&](auto m) {
+                constexpr int M = decltype(m)::value;
+                if constexpr (MULS > 0) multiply(m, E & 1);
+                if constexpr (M < LAST)
+                    static_for<READS * (M + 1) / LAST - READS * M / LAST>([&](auto k) {
+                        read(StaticInt<READS * M / LAST + decltype(k)::value>{}, (unsigned)next_off, StaticInt<NEXT>{}, NEXT & 1);
+                    });
+                if constexpr (E == 0)
+                    static_for<CPS>([&](auto k) {
+                        constexpr int C = M * CPS + decltype(k)::value;
+                        if constexpr (C < NI) copy(source(StaticInt<C>{}), StaticInt<C>{}, freed);
+                        if constexpr (C == NI) advance();
+                    });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        };
 #pragma unroll
-        for (int s = 0; s < NS; ++s) issue(s * STAGE);
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((NS - 1) * NI) : "memory");
-        read(0u, StaticInt<0>{}, 0);
-        int cur = 0;                                            // ring offset of slab s
+        for (int s = 0; s < NS - 1; ++s) {
+            static_for<NI>([&](auto i) { copy(source(i), i, s * STAGE); });
+            advance();
+        }
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((NS - 2) * NI) : "memory");
+        static_for<READS>([&](auto k) { read(k, 0u, StaticInt<0>{}, 0); });
+        int cur = 0, freed = (NS - 1) * STAGE;                  // ring offset of slab s, and of the place to refill
         for (int s = 0; s < nst; ++s) {
-            auto step = [&](auto e) {                           // multiply step e, fetch the operands of step e + 1
-                if constexpr (decltype(e)::value + 1 < STEPS) {
-                    read((unsigned)cur, StaticInt<decltype(e)::value + 1>{}, (decltype(e)::value + 1) & 1);
-                    asm volatile("s_waitcnt lgkmcnt(%0)" :: "n"(decltype(reads_per_step)::value));
-                    arrived(decltype(e)::value & 1);
-                    multiply(decltype(e)::value & 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            };
-            step(StaticInt<0>{}); step(StaticInt<1>{}); step(StaticInt<2>{}); step(StaticInt<3>{}); step(StaticInt<4>{});
-            step(StaticInt<5>{}); step(StaticInt<6>{});
-            static_assert(STEPS <= 8, "steps written out above");
+            static_for<STEPS - 1>([&](auto e) {
+                asm volatile("s_waitcnt lgkmcnt(0)");
+                step(e, cur, freed);
+            });
             // everything of this slab is in registers, this wavefront's copies of the next one have landed (NS - 2 later slabs
             // may still be in flight), and so for everybody
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((NS - 2) * NI) : "memory");
-            arrived(1);
-            const int freed = cur;
+            freed = cur;
             cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
-            read((unsigned)cur, StaticInt<0>{}, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(1);
-            __builtin_amdgcn_sched_barrier(0);
-            issue(freed);                                       // (after the products: before them, 3 to 5 % slower)
+            step(StaticInt<STEPS - 1>{}, cur, 0);
         }
         // trailing (all-zero) slabs must not land later, and everybody is done with the ring
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -561,7 +570,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     if (above) {
         const int c0 = (wn - FIRST_ABOVE) * BB * 32;
         if (!u.has_bias || J * TW + c0 >= D) {
-            pipeline(StaticInt<0>{}, [](unsigned, auto, int) {}, [](int) {}, [](int) {});
+            pipeline(StaticInt<0>{}, StaticInt<0>{}, [](auto, unsigned, auto, int) {}, [](int) {}, [](auto, int) {});
             return;
         }
         v16f acc[BB];
@@ -571,25 +580,19 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
             for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
         const unsigned addr0 = operand_addr(c0);
         Regs b[2][BB];
-        pipeline(StaticInt<BB * PIECES>{}, [&](unsigned stage_off, auto e, int set) {
-            const unsigned ba = addr0 + stage_off;
-#pragma unroll
-            for (int i = 0; i < BB; ++i) KFAC_TILE_READ(b[set], i, ba, e);
+        pipeline(StaticInt<BB * (ES == 2 ? 1 : PRODUCTS)>{}, StaticInt<BB>{}, [&](auto k, unsigned stage_off, auto e, int set) {
+            KFAC_TILE_READ(b[set], decltype(k)::value, addr0 + stage_off, e);
         }, [&](int set) {
 #pragma unroll
             for (int i = 0; i < BB; ++i) KFAC_TILE_ARRIVED(b[set], i);
-        }, [&](int set) {
-#pragma unroll
-            for (int i = 0; i < BB; ++i) {
-                if constexpr (ES == 2) {
-                    const unsigned one2 = KIND == 1 ? 0x3C003C00u : 0x3F803F80u;
-                    const v2u ones = {one2, one2};
-                    acc[i] = mfma16_halves<KIND == 1>(ones, ones, first_half(b[set][i]), second_half(b[set][i]), acc[i]);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < PRODUCTS; ++e)
-                        acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(1.0f, operand_float(b[set][i], e), acc[i], 0, 0, 0);
-                }
+        }, [&](auto m, int set) {
+            constexpr int i = decltype(m)::value % BB, e = decltype(m)::value / BB;
+            if constexpr (ES == 2) {
+                const unsigned one2 = KIND == 1 ? 0x3C003C00u : 0x3F803F80u;
+                const v2u ones = {one2, one2};
+                acc[i] = mfma16_halves<KIND == 1>(ones, ones, first_half(b[set][i]), second_half(b[set][i]), acc[i]);
+            } else {
+                acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(1.0f, operand_float(b[set][i], e), acc[i], 0, 0, 0);
             }
         });
         if (h == 0) {                                           // (all rows of the products are the sums)
@@ -609,7 +612,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
         return;
     }
     if (I * TW + wr >= D || J * TW + wc >= D) {
-        pipeline(StaticInt<0>{}, [](unsigned, auto, int) {}, [](int) {}, [](int) {});
+        pipeline(StaticInt<0>{}, StaticInt<0>{}, [](auto, unsigned, auto, int) {}, [](int) {}, [](auto, int) {});
         return;
     }
     v16f acc[S::MB][S::NB];
@@ -621,29 +624,21 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
             for (int r = 0; r < 16; ++r) acc[i][n][r] = 0.f;
     const unsigned a_addr = operand_addr(wr), b_addr = operand_addr(wc) + (DIAG ? 0u : (unsigned)PANEL);
     Regs a[2][S::MB], b[2][S::NB];
-    pipeline(StaticInt<(S::MB + S::NB) * PIECES>{}, [&](unsigned stage_off, auto e, int set) {
-        const unsigned aa = a_addr + stage_off, ba = b_addr + stage_off;
-#pragma unroll
-        for (int i = 0; i < S::NB; ++i) KFAC_TILE_READ(b[set], i, ba, e);
-#pragma unroll
-        for (int i = 0; i < S::MB; ++i) KFAC_TILE_READ(a[set], i, aa, e);
+    pipeline(StaticInt<S::MB * S::NB * PRODUCTS>{}, StaticInt<S::MB + S::NB>{}, [&](auto k, unsigned stage_off, auto e, int set) {
+        constexpr int K = decltype(k)::value;
+        if constexpr (K < S::NB) KFAC_TILE_READ(b[set], K, b_addr + stage_off, e);
+        else KFAC_TILE_READ(a[set], K - S::NB, a_addr + stage_off, e);
     }, [&](int set) {
 #pragma unroll
         for (int i = 0; i < S::NB; ++i) KFAC_TILE_ARRIVED(b[set], i);
 #pragma unroll
         for (int i = 0; i < S::MB; ++i) KFAC_TILE_ARRIVED(a[set], i);
-    }, [&](int set) {
-#pragma unroll
-        for (int e = 0; e < PRODUCTS; ++e)
-#pragma unroll
-            for (int i = 0; i < S::MB; ++i)
-#pragma unroll
-                for (int n = 0; n < S::NB; ++n) {
-                    if constexpr (ES == 2)
-                        acc[i][n] = mfma16_halves<KIND == 1>(first_half(a[set][i]), second_half(a[set][i]), first_half(b[set][n]), second_half(b[set][n]), acc[i][n]);
-                    else
-                        acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(operand_float(a[set][i], e), operand_float(b[set][n], e), acc[i][n], 0, 0, 0);
-                }
+    }, [&](auto m, int set) {
+        constexpr int B = S::MB * S::NB, e = decltype(m)::value / B, i = decltype(m)::value % B / S::NB, n = decltype(m)::value % S::NB;
+        if constexpr (ES == 2)
+            acc[i][n] = mfma16_halves<KIND == 1>(first_half(a[set][i]), second_half(a[set][i]), first_half(b[set][n]), second_half(b[set][n]), acc[i][n]);
+        else
+            acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(operand_float(a[set][i], e), operand_float(b[set][n], e), acc[i][n], 0, 0, 0);
     });
 
     // ---- epilogue ----
