@@ -461,7 +461,7 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
         int next = 0;
         while (next < count) {
             fbatch_clear(b, dev);
-            struct Pick { int item, share, rows, wgs, finish, list; } pick[FMAXB];
+            struct Pick { int item, share, rows, work, wgs, finish, list; } pick[FMAXB];
             int n = 0;
             bool planes = false;
             for (; next < count && n < FMAXB; ++next) {
@@ -472,20 +472,24 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
                 const int share = share_for(v);
                 if (v.shared) {
                     const SharedPlan p = plan_shared(v, share);
-                    if (p.tw == VAR_TW[var]) pick[n++] = {next, share, p.rows, shared_workgroups(p), shared_assemble_wgs(v),
+                    if (p.tw == VAR_TW[var]) pick[n++] = {next, share, p.rows, p.first[4], shared_workgroups(p), shared_assemble_wgs(v),
                                                            v.chunked ? FINISH_CHANNELS : FINISH_FEW};
                     continue;
                 }
                 const FactorPlan p = plan_tiles(v, share);
                 if (p.tw != VAR_TW[var]) continue;
                 planes = planes || v.planes;
-                pick[n++] = {next, share, p.rows_per_split, (int)align_up(p.ntiles * p.nsplit, 8),   // (a multiple of 8: see factor_tile)
+                pick[n++] = {next, share, p.rows_per_split, p.ntiles * p.nsplit, (int)align_up(p.ntiles * p.nsplit, 8),   // (see unit_of)
                              p.nsplit > 1 ? reduce_wgs(v, p) : 0, p.nsplit >= MANY_SPLITS ? FINISH_MANY : FINISH_FEW};
             }
             if (n == 0) continue;
             // the longest workgroups first: the short ones fill the end of the launch
             std::stable_sort(pick, pick + n, [](const Pick& a, const Pick& c) { return a.rows > c.rows; });
-            for (int i = 0; i < n; ++i) fbatch_add(b, host, pick[i].item, pick[i].share, pick[i].wgs);
+            int turn = 0;
+            for (int i = 0; i < n; ++i) {
+                fbatch_add(b, host, pick[i].item, pick[i].share | turn << SHARE_TURN_SHIFT, pick[i].wgs);
+                turn = next_turn(turn, pick[i].work);
+            }
             rc = VAR_DTYPE[var] == KFAC_BF16 ? launch_tiles<0>(VAR_TW[var], planes, b, stream)
                : VAR_DTYPE[var] == KFAC_F16 ? launch_tiles<1>(VAR_TW[var], planes, b, stream)
                                             : launch_tiles<2>(VAR_TW[var], planes, b, stream);

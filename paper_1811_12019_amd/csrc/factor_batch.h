@@ -23,6 +23,7 @@ struct FactorPlan {
 // planes (the address decides that, once, on the host: worked out by the kernels it cost each launch 0.2 to 0.5 us).  A matrix of up to
 // 128 (64) columns is one tile of that width.
 constexpr int SHARE_WIDE = 1 << 20, SHARE_PLANES = 1 << 21;
+constexpr int SHARE_TURN_SHIFT = 24;         // (for the tile kernel: the build's `turn`, see unit_of)
 constexpr int ROWS_PER_WG_MAX = 6400, ROWS_PER_WG_MAX_F32 = 1600;
 constexpr int ROWS_PER_WG_MIN = 512, ROWS_PER_WG_MIN_F32 = 64;
 constexpr int SHARE_LEAST = 1024, SHARE_LEAST_F32 = 128;           // the fewest rows share_of gives a workgroup

@@ -22,14 +22,15 @@ void factor_tile_kernel(FBatch b) {
     View v;
     fbatch_item<PLANES>(b, m, it, u, v);
     const KFAC_AS1 unsigned char* x = (const KFAC_AS1 unsigned char*)(v.repack ? it.ws : it.x);
+    const int turn = b.share[m] >> SHARE_TURN_SHIFT;
     if (v.shared) {
-        shared_tile<TW, KIND>(v, x, plan_shared(v, b.share[m]), shared_ws(v, it.ws), local, smem);
+        shared_tile<TW, KIND>(v, x, plan_shared(v, b.share[m]), shared_ws(v, it.ws), local, turn, smem);
         return;
     }
     const FactorPlan p = plan_tiles(v, b.share[m]);
     const float scale = it.scale == 0.f ? 1.0f / (float)u.R : it.scale;
     factor_tile<TW, KIND, PLANES>(v, x, scale, out_spec(it), partial_of(v, p, it.ws), p.rows_per_split, p.tiles_dim, p.ntiles, p.nsplit,
-                                  local, smem);
+                                  local, turn, smem);
 }
 
 template <int TW, int KIND, bool PLANES>

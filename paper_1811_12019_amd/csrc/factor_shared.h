@@ -113,19 +113,18 @@ __device__ __forceinline__ size_t split_stride(const SharedPlan& p, int cls) {
 // One tile of one part: workgroup `wg` of shared_workgroups.
 template <int TW, int KIND>
 __device__ __forceinline__ void shared_tile(const View& v, const KFAC_AS1 unsigned char* x, const SharedPlan& p, gfloat* ws, int wg,
-                                            unsigned char* smem) {
-    // wg % 8 is the XCD.  The middles (long) and the strips (short) are dealt apart, so that every XCD gets its share of both;
-    // inside, an XCD takes a contiguous eighth, in which the units of a row range lie together.
+                                            int turn, unsigned char* smem) {
+    // The middles (long) and the strips (short) are dealt to the XCDs apart (unit_of), so that every XCD gets its share of both.
     int base = 0, work = p.first[1];
     const int mid_wgs = (work + 7) >> 3 << 3;
     if (wg >= mid_wgs) {
         wg -= mid_wgs;
         base = work;
+        turn = next_turn(turn, work);
         work = p.first[4] - work;
     }
-    const int per_xcd = (work + 7) >> 3;
-    const int in = (wg & 7) * per_xcd + (wg >> 3);
-    if ((wg >> 3) >= per_xcd || in >= work) return;                 // padding workgroup (uniform, before any barrier)
+    const int in = unit_of(work, wg, turn);
+    if (in < 0) return;                                             // (uniform, before any barrier)
     const int unit = base + in;
     const int cls = unit < p.first[1] ? 0 : unit < p.first[2] ? 1 : unit < p.first[3] ? 2 : 3;
     const int sym = cls == 0 ? 1 : cls == 3 ? 4 : 2;
