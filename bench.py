@@ -66,13 +66,13 @@ def kernel_work(net: kstep.KfacNetworkStep, kernels):
     shapes = [l.shape for l in net.layers]
     dims = [d for s in shapes for d in (s.d_A, s.d_G)]
 
-    # every factor is built by the tile kernel: up to 64 columns (without the bias) by the 64-wide one, up to 128 by the 128-wide
-    # one, wider ones all by the 128- or all by the 256-wide one
+    # every factor is built by the tile kernel: up to 128 columns (without the bias) by the 128-wide one, which makes 64-wide tiles too,
+    # wider ones all by the 128- or all by the 256-wide one
     wide = 256 if "factor_tile_kernel<256, 16-bit>" in kernels else 128
-    fac_tile = {64: 0.0, 128: 0.0, 256: 0.0}
+    fac_tile = {128: 0.0, 256: 0.0}
     for s in shapes:
         for columns, flops in formed_factor_work(s):
-            fac_tile[64 if columns <= 64 else 128 if columns <= 128 else wide] += flops
+            fac_tile[128 if columns <= 128 else wide] += flops
     w = {
         # all steps of all matrices in one kernel: rank-128 updates (fp16 pieces), panel products (2 d nb^2 a step, bf16 pieces) and
         # the later pivot blocks' inversions (fp32)

@@ -454,30 +454,32 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
     }
     int rc = repack();
     if (rc != KFAC_OK) return rc;
-    // kernel variants: tile width x dtype
-    static const int VAR_TW[8] = {64, 64, 128, 128, 256, 256, 64, 128};
-    static const int VAR_DTYPE[8] = {KFAC_BF16, KFAC_F16, KFAC_BF16, KFAC_F16, KFAC_BF16, KFAC_F16, KFAC_F32, KFAC_F32};
-    for (int var = 0; var < 8; ++var) {
+    // kernel variants: tile widths x dtype
+    static const struct { bool wide; int dtype; } VAR[5] = {{false, KFAC_BF16}, {false, KFAC_F16}, {true, KFAC_BF16}, {true, KFAC_F16}, {false, KFAC_F32}};
+    for (int var = 0; var < 5; ++var) {
         int next = 0;
         while (next < count) {
             fbatch_clear(b, dev);
             struct Pick { int item, share, rows, work, wgs, finish, list; } pick[FMAXB];
-            int n = 0;
+            int n = 0, widest = 0;
             bool planes = false;
             for (; next < count && n < FMAXB; ++next) {
                 Unfold u;
                 View v;
                 item_unfold(host[next], &u);
-                if (u.dtype != VAR_DTYPE[var] || route_of(u, host[next].x, many, &v) != ROUTE_TILE) continue;
+                if (u.dtype != VAR[var].dtype || route_of(u, host[next].x, many, &v) != ROUTE_TILE) continue;
                 const int share = share_for(v);
                 if (v.shared) {
                     const SharedPlan p = plan_shared(v, share);
-                    if (p.tw == VAR_TW[var]) pick[n++] = {next, share, p.rows, p.first[4], shared_workgroups(p), shared_assemble_wgs(v),
-                                                           v.chunked ? FINISH_CHANNELS : FINISH_FEW};
+                    if ((p.tw == 256) != VAR[var].wide) continue;
+                    widest = std::max(widest, p.tw);
+                    pick[n++] = {next, share, p.rows, p.first[4], shared_workgroups(p), shared_assemble_wgs(v),
+                                 v.chunked ? FINISH_CHANNELS : FINISH_FEW};
                     continue;
                 }
                 const FactorPlan p = plan_tiles(v, share);
-                if (p.tw != VAR_TW[var]) continue;
+                if ((p.tw == 256) != VAR[var].wide) continue;
+                widest = std::max(widest, p.tw);
                 planes = planes || v.planes;
                 pick[n++] = {next, share, p.rows_per_split, p.ntiles * p.nsplit, (int)align_up(p.ntiles * p.nsplit, 8),   // (see unit_of)
                              p.nsplit > 1 ? reduce_wgs(v, p) : 0, p.nsplit >= MANY_SPLITS ? FINISH_MANY : FINISH_FEW};
@@ -490,9 +492,9 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
                 fbatch_add(b, host, pick[i].item, pick[i].share | turn << SHARE_TURN_SHIFT, pick[i].wgs);
                 turn = next_turn(turn, pick[i].work);
             }
-            rc = VAR_DTYPE[var] == KFAC_BF16 ? launch_tiles<0>(VAR_TW[var], planes, b, stream)
-               : VAR_DTYPE[var] == KFAC_F16 ? launch_tiles<1>(VAR_TW[var], planes, b, stream)
-                                            : launch_tiles<2>(VAR_TW[var], planes, b, stream);
+            rc = VAR[var].dtype == KFAC_BF16 ? launch_tiles<0>(widest, planes, b, stream)
+               : VAR[var].dtype == KFAC_F16 ? launch_tiles<1>(widest, planes, b, stream)
+                                            : launch_tiles<2>(widest, planes, b, stream);
             if (rc != KFAC_OK) return rc;
             for (int i = 0; i < n; ++i) {
                 if (!pick[i].finish) continue;
