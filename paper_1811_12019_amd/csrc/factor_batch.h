@@ -63,15 +63,16 @@ static inline __host__ __device__ SharedPlan plan_shared(const View& v, int shar
     if (ns > cap) ns = cap;
     if (ns > least) ns = least > 1 ? least : 1;
     p.ns[0] = xcd_splits(ns);
-    const int ends[3] = {u.N * (u.W - 1), u.N * (u.H - 1), u.N};
+    // (written out: as a loop over the classes the plan stays an array in scratch memory, which every workgroup waits for)
+    auto strips = [&](int rows_of_class) { const int n = ceil_div(rows_of_class, share_rows); return n < p.ns[0] ? n : p.ns[0]; };
+    p.ns[1] = strips(u.N * (u.W - 1));
+    p.ns[2] = strips(u.N * (u.H - 1));
+    p.ns[3] = strips(u.N);
     p.first[0] = 0;
     p.first[1] = p.ns[0] * p.per[0];
-#pragma unroll
-    for (int c = 1; c < 4; ++c) {
-        const int n = ceil_div(ends[c - 1], share_rows);
-        p.ns[c] = n < p.ns[0] ? n : p.ns[0];
-        p.first[c + 1] = p.first[c] + p.ns[c] * p.per[c];
-    }
+    p.first[2] = p.first[1] + p.ns[1] * p.per[1];
+    p.first[3] = p.first[2] + p.ns[2] * p.per[2];
+    p.first[4] = p.first[3] + p.ns[3] * p.per[3];
     p.rows = ceil_div(rows, p.ns[0]);
     p.ws_bytes = ((size_t)p.first[4] * p.tw * p.tw + (size_t)9 * p.ns[0] * p.T * p.tw) * sizeof(float);
     return p;

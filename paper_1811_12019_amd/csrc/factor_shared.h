@@ -90,10 +90,17 @@ static inline __host__ __device__ void part_of(int dy, int dx, int ys, int xs, i
 
 static inline __host__ __device__ bool member_symmetric(int cls, int member) { return cls == 3 || (cls == 0 ? member == 0 : member < 2); }
 
+// (One of four plan values: taken out of the plan first, all of them.  Left to itself the compiler chooses between their addresses, and
+// the plan goes to scratch memory.)
+__device__ __forceinline__ int of_class(int cls, int v0, int v1, int v2, int v3) {
+    const int a = uniform(v0), b = uniform(v1), c = uniform(v2), d = uniform(v3);
+    return cls == 0 ? a : cls == 1 ? b : cls == 2 ? c : d;
+}
+
 // Unit of (class, member, split 0, tile 0); splits are per[cls] units apart.
-static inline __host__ __device__ int shared_unit(const SharedPlan& p, int cls, int member) {
+__device__ __forceinline__ int shared_unit(const SharedPlan& p, int cls, int member) {
     const int sym = cls == 0 ? 1 : cls == 3 ? 4 : 2;
-    return p.first[cls] + (member < sym ? member * p.ntl : sym * p.ntl + (member - sym) * p.nf);
+    return of_class(cls, p.first[0], p.first[1], p.first[2], p.first[3]) + (member < sym ? member * p.ntl : sym * p.ntl + (member - sym) * p.nf);
 }
 
 static inline __host__ __device__ int shared_workgroups(const SharedPlan& p) {
@@ -103,11 +110,9 @@ static inline __host__ __device__ int shared_workgroups(const SharedPlan& p) {
 // The workspace: the units' tiles (Partial's order inside a tile), then the column sums of offset (0, 0)'s nine parts.
 static inline __host__ __device__ size_t shared_sums_at(const SharedPlan& p) { return (size_t)p.first[4] * p.tw * p.tw; }
 
-__device__ __forceinline__ int splits_of(const SharedPlan& p, int cls) {
-    return cls == 0 ? p.ns[0] : cls == 1 ? p.ns[1] : cls == 2 ? p.ns[2] : p.ns[3];
-}
+__device__ __forceinline__ int splits_of(const SharedPlan& p, int cls) { return of_class(cls, p.ns[0], p.ns[1], p.ns[2], p.ns[3]); }
 __device__ __forceinline__ size_t split_stride(const SharedPlan& p, int cls) {
-    return (size_t)(cls == 0 ? p.per[0] : cls == 3 ? p.per[3] : p.per[1]) * p.tw * p.tw;
+    return (size_t)of_class(cls, p.per[0], p.per[1], p.per[2], p.per[3]) * p.tw * p.tw;
 }
 
 // One tile of one part: workgroup `wg` of shared_workgroups.
@@ -128,7 +133,8 @@ __device__ __forceinline__ void shared_tile(const View& v, const KFAC_AS1 unsign
     const int unit = base + in;
     const int cls = unit < p.first[1] ? 0 : unit < p.first[2] ? 1 : unit < p.first[3] ? 2 : 3;
     const int sym = cls == 0 ? 1 : cls == 3 ? 4 : 2;
-    const int ns = splits_of(p, cls);
+    // (not through of_class: with it 180 registers of the 128-wide kernel's epilogues went to scratch memory)
+    const int ns = cls == 0 ? p.ns[0] : cls == 1 ? p.ns[1] : cls == 2 ? p.ns[2] : p.ns[3];
     const int per = cls == 0 ? p.per[0] : cls == 3 ? p.per[3] : p.per[1];
     const int at = unit - (cls == 0 ? 0 : cls == 1 ? p.first[1] : cls == 2 ? p.first[2] : p.first[3]);
     const int split = at / per, idx = at - split * per;

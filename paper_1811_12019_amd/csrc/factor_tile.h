@@ -673,38 +673,55 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     };
     constexpr int VPR = W / 4;                                     // vectors per row
     const int vr = lane / VPR, vc = lane % VPR * 4;                // this lane's vector of the first rows
-    gfloat* direct0 = out + (size_t)(I * TW + wr + vr) * d + J * TW + wc + vc;
-    const size_t row_step = (size_t)(64 / VPR) * d;
     // Running average: the old values of block row p, fetched one block row ahead, so that a tile waits for memory once
     // and not once per block row.  (Two ahead do not fit the registers beside the accumulators.)
     v4f old[2][NV];
+    // Byte offsets into the result: the lane's, and, the same in all lanes, what to add for a block row and a pass.  (Addresses of 64 bits
+    // for every pass do not fit the registers beside the accumulators and the old values.)
+    const unsigned out_bytes = packed ? 2u * d * (d + 1) : 4u * d * d;      // (d < 32768)
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)out, 0, out_bytes, 0x00027000);
+    const unsigned ud = 4u * d;
+    const unsigned direct0 = (I * TW + wr + vr) * ud + 4u * (J * TW + wc + vc);
+    const unsigned mirror0 = (J * TW + wc + (lane >> 3)) * ud + 4u * (I * TW + wr + (lane & 7) * 4);
+    auto direct_step = [&](int p, int k) { return (p * 32 + k * (64 / VPR)) * ud; };
+    auto mirror_step = [&](int p, int k) { return k * 8 * ud + 4u * (p * 32); };
+    // (without a branch, also where the old values are not wanted: what lies outside the buffer is not fetched)
+    const unsigned old0 = ema ? direct0 : 0xFFFFFFF0u;
     auto fetch_old = [&](int p, v4f (&o)[NV]) {
-        if (!whole(p)) return;
-        const gfloat* src = direct0 + (size_t)(p * 32) * d;
 #pragma unroll
-        for (int k = 0; k < NV; ++k) o[k] = *(const KFAC_AS1 v4f_a4*)(src + k * row_step);
+        for (int k = 0; k < NV; ++k) {
+            const v4u x = __builtin_amdgcn_raw_buffer_load_b128(rsrc, old0, direct_step(p, k), 0);
+            __builtin_memcpy(&o[k], &x, 16);
+        }
+    };
+    // (The step is added by the vector unit: of a 16-byte store with its step in a scalar register the third dword was now and then
+    // the next vector instruction's result, in the last four lanes of 16.  The compiler keeps the two apart in this form only.)
+    auto put_vector = [&](unsigned off, unsigned step, const v4f& val) {
+        v4u x;
+        __builtin_memcpy(&x, &val, 16);
+        __builtin_amdgcn_raw_buffer_store_b128(x, rsrc, off + step, 0, 0);
     };
     // Elsewhere: element by element.  Elements that are not there (beyond the matrix, padding, the other half of a diagonal
     // tile) get an offset outside the buffer, which the hardware drops: no branches, so that many are in flight.
     const int dc = lane % W, dr = lane / W;
     constexpr int RPP = 64 / W;                                    // rows per pass of the wavefront's lanes
     const int cod = cmap[wc + dc];
-    const unsigned out_bytes = packed ? 2u * d * (d + 1) : 4u * d * d;      // (d < 32768)
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)out, 0, out_bytes, 0x00027000);
     auto direct_off = [&](int rl, int rd) -> unsigned {            // element (row rl of the tile, this lane's column)
         return rd >= 0 && cod >= 0 && !(DIAG && rl < wc + dc) ? (unsigned)(rd + cod) * 4u : ~0u;
     };
-    if (ema) fetch_old(0, old[0]);
+    fetch_old(0, old[0]);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int p = 0; p < S::MB; ++p) {
         const int rb = wr + p * 32;
+        asm volatile("" ::: "memory");                             // (nothing read from the maps is kept for the next block row)
 #pragma unroll
         for (int n = 0; n < S::NB; ++n)
 #pragma unroll
             for (int r = 0; r < 16; ++r) epi[((r >> 2) * 8 + h * 4 + (r & 3)) * LD + n * 32 + lm] = acc[p][n][r] * job.scale;
-        if (ema && p + 1 < S::MB) fetch_old(p + 1, old[(p + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
         if (whole(p)) {
-            gfloat* dst = direct0 + (size_t)(p * 32) * d;
+            if (p + 1 < S::MB) fetch_old(p + 1, old[(p + 1) & 1]);
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
                 float* e = &epi[(k * (64 / VPR) + vr) * LD + vc];
@@ -714,15 +731,14 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
                     for (int i = 0; i < 4; ++i) val[i] = fmaf(os.decay, old[p & 1][k][i], os.one_minus * val[i]);
                     *(v4f*)e = val;                                // (the mirror image gets the same new values)
                 }
-                *(KFAC_AS1 v4f_a4*)(dst + k * row_step) = val;
+                put_vector(direct0, direct_step(p, k), val);
             }
             // mirror image: lane = four rows of one column, eight columns per pass
-            gfloat* mir = out + (size_t)(J * TW + wc + (lane >> 3)) * d + I * TW + rb + (lane & 7) * 4;
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
                 const float* e = &epi[(lane & 7) * 4 * LD + k * 8 + (lane >> 3)];
                 const v4f val = {e[0], e[LD], e[2 * LD], e[3 * LD]};
-                *(KFAC_AS1 v4f_a4*)(mir + (size_t)(k * 8) * d) = val;
+                put_vector(mirror0, mirror_step(p, k), val);
             }
             __builtin_amdgcn_sched_barrier(0);
             continue;
@@ -774,6 +790,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (p + 1 < S::MB) fetch_old(p + 1, old[(p + 1) & 1]);         // (here the registers hold no more before)
     }
 }
 
