@@ -41,6 +41,30 @@ __device__ __forceinline__ v4f load4_guard(const gfloat* p, bool row_ok, int k, 
     return v;
 }
 
+// 16 rows (first, first + 8, ..) of columns k .. k + 3 of a row-major matrix at X, rows x cols elements, zero outside it.  No load
+// stands under a condition (each would be waited for before the next one): rows beyond the matrix read its last one, and columns at a
+// row's end are read from inside the row and moved into place.
+__device__ __forceinline__ v4f tail4(v4f x, int shift) {             // elements shift .. of x, then zeros
+    x = shift & 1 ? v4f{x.y, x.z, x.w, 0.f} : x;
+    x = shift & 2 ? v4f{x.z, x.w, 0.f, 0.f} : x;
+    return shift > 3 ? v4f{0.f, 0.f, 0.f, 0.f} : x;
+}
+__device__ __forceinline__ void load_rows_edge(const gfloat* X, int rows, int cols, int first, int k, v4f (&v)[16]) {
+    if (cols < 4) {                                      // (uniform)
+#pragma unroll
+        for (int p = 0; p < 16; ++p) {
+            const int row = first + 8 * p;
+            v[p] = load4_guard(X + (size_t)(row < rows ? row : 0) * cols, row < rows, k, cols);
+        }
+        return;
+    }
+    const int start = min(k, cols - 4), shift = k - start;
+#pragma unroll
+    for (int p = 0; p < 16; ++p) v[p] = *(const KFAC_AS1 v4f_a4*)(X + (size_t)min(first + 8 * p, rows - 1) * cols + start);
+#pragma unroll
+    for (int p = 0; p < 16; ++p) v[p] = tail4(v[p], first + 8 * p < rows ? shift : 4);
+}
+
 // A: first row of the tile's A operand, lda floats between rows, arows (<=128) valid rows; same for B.
 __device__ __forceinline__ void tile_mma_nt(const gfloat* __restrict__ A, int lda, int arows,
                                             const gfloat* __restrict__ B, int ldb, int brows, int K,

@@ -1339,11 +1339,7 @@ __device__ __forceinline__ void out_diagonal_planes(const gfloat* __restrict__ o
 #pragma unroll
         for (int p = 0; p < 16; ++p) v[p] = *(const KFAC_AS1 v4f_a4*)(out + (size_t)(r0 + rr + 8 * p) * d + r0 + c4);
     } else {
-#pragma unroll
-        for (int p = 0; p < 16; ++p) {
-            const int row = r0 + rr + 8 * p;
-            v[p] = load4_guard(out + (size_t)(row < d ? row : 0) * d, row < d, r0 + c4, d);
-        }
+        load_rows_edge(out, d, d, r0 + rr, r0 + c4, v);
     }
 #pragma unroll
     for (int p = 0; p < 16; ++p) store_split4_h2(dst, dst + pl.plane, rr + 8 * p, c4, v[p] * pl.scale);

@@ -130,11 +130,7 @@ __global__ __launch_bounds__(256) void pre_split_kernel(PBatch b) {
 #pragma unroll
         for (int p = 0; p < 16; ++p) v[p] = *(const KFAC_AS1 v4f_a4*)(X + (size_t)(r0 + rr + 8 * p) * cols + k0 + c4);
     } else {
-#pragma unroll
-        for (int p = 0; p < 16; ++p) {
-            const int row = r0 + rr + 8 * p;
-            v[p] = load4_guard(X + (size_t)(row < rows ? row : 0) * cols, row < rows, k0 + c4, cols);
-        }
+        load_rows_edge(X, rows, cols, r0 + rr, k0 + c4, v);
     }
     emit_block(v, set.hi + (size_t)local * PRE_SLAB, set.plane, set.scales() + local, red);
 }
