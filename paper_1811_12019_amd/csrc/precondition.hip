@@ -84,7 +84,8 @@ __device__ __forceinline__ kfac_precond_item locate_item(const PBatch& b, int wg
         if (b.prefix[mid] <= wg) lo = mid; else hi = mid;
     }
     local = wg - b.prefix[lo];
-    return b.table ? b.table[b.first + b.order[lo]] : b.single;
+    if (b.table) return uniform(b.table[b.first + b.order[lo]]);
+    return b.single;
 }
 
 // 128 rows (row0 ..) x 128 columns of fp32 values held one float4 per thread and pass (thread t: columns 4 (t % 32) ..,
