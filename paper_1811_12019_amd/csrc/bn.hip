@@ -68,7 +68,7 @@ struct BnReduceBatch {
 // NHWC, channels whole vectors.  Both tensors are read once, 16 bytes per thread and load, eight loads in flight.
 // (fp32 went through the general kernel before, one 4-byte load after the other: the gradients and the diagonal form of 53 layers
 // at batch 2 19.2 ms, now 0.25 ms.)
-template <int DTYPE>
+template <int DTYPE, bool STREAM>
 __global__ __launch_bounds__(256) void bn_partial_kernel(BnBatch b) {
     constexpr int V = DTYPE == KFAC_F32 ? 4 : 8;
     __shared__ float red[256 * 2 * V];                   // [position lane][half][vector][V]
@@ -98,8 +98,8 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(BnBatch b) {
                 const int su = s + u * lanes;
                 const bool ok = su < s1;
                 const size_t at = (row0 + (ok ? su : s)) * cv + vec;
-                xv[u] = X[at];
-                gv[u] = G[at];
+                xv[u] = STREAM ? __builtin_nontemporal_load(X + at) : X[at];
+                gv[u] = STREAM ? __builtin_nontemporal_load(G + at) : G[at];
                 if (!ok) gv[u] = v4u{0u, 0u, 0u, 0u};
             }
 #pragma unroll
@@ -260,6 +260,7 @@ extern "C" int kfac_bn_sample_grads_batched(const kfac_bn_item* items_host, int3
         BnBatch lists[3];                                 // the fp32, bf16 and fp16 layers of this group
         BnReduceBatch rb;
         unsigned wgs[3] = {0, 0, 0}, nred = 0;
+        size_t bytes[3] = {0, 0, 0};                      // of both tensors
         lists[KFAC_F32].count = lists[KFAC_BF16].count = lists[KFAC_F16].count = rb.count = 0;
         for (int i = 0; i < cnt; ++i) {
             const kfac_bn_item& it = items_host[first + i];
@@ -282,6 +283,7 @@ extern "C" int kfac_bn_sample_grads_batched(const kfac_bn_item* items_host, int3
                 b.C[k] = it.C; b.HW[k] = it.HW; b.sp[k] = p.sp; b.nchunk[k] = p.nchunk;
                 b.x[k] = it.xhat; b.gout[k] = it.gout; b.dst[k] = dst;
                 units += (unsigned)it.N * p.nchunk * p.ncb;
+                bytes[it.dtype] += (size_t)it.N * it.C * it.HW * (it.dtype == KFAC_F32 ? 8 : 4);
             } else {
                 KFAC_LAUNCH(bn_partial_generic_kernel, dim3(p.nchunk, it.N), dim3(256), (hipStream_t)stream, it.xhat, it.gout,
                             (int)it.dtype, (int)it.C, (int)it.HW, p.nchunk, dst);
@@ -291,9 +293,15 @@ extern "C" int kfac_bn_sample_grads_batched(const kfac_bn_item* items_host, int3
             BnBatch& b = lists[dt];
             if (b.count == 0) continue;
             b.prefix[b.count] = wgs[dt];
-            if (dt == KFAC_F32) KFAC_LAUNCH(bn_partial_kernel<KFAC_F32>, dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b);
-            else if (dt == KFAC_BF16) KFAC_LAUNCH(bn_partial_kernel<KFAC_BF16>, dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b);
-            else KFAC_LAUNCH(bn_partial_kernel<KFAC_F16>, dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b);
+#define KFAC_BN_LAUNCH(DTYPE, name)                                                                                                   \
+    do {                                                                                                                            \
+        if (bytes[dt] > STREAM_BYTES) KFAC_LAUNCH_AS(name, (bn_partial_kernel<DTYPE, true>), dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b); \
+        else KFAC_LAUNCH_AS(name, (bn_partial_kernel<DTYPE, false>), dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b);                  \
+    } while (0)
+            if (dt == KFAC_F32) KFAC_BN_LAUNCH(KFAC_F32, "bn_partial_kernel<KFAC_F32>");
+            else if (dt == KFAC_BF16) KFAC_BN_LAUNCH(KFAC_BF16, "bn_partial_kernel<KFAC_BF16>");
+            else KFAC_BN_LAUNCH(KFAC_F16, "bn_partial_kernel<KFAC_F16>");
+#undef KFAC_BN_LAUNCH
         }
         if (rb.count) {
             rb.prefix[rb.count] = nred;

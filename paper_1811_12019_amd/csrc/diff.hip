@@ -25,6 +25,7 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+template <bool STREAM>
 __global__ __launch_bounds__(256) void diff_partial_kernel(DiffBatch b, double* partial_) {
     __shared__ double red[2][4];
     const int t = threadIdx.x;
@@ -41,8 +42,8 @@ __global__ __launch_bounds__(256) void diff_partial_kernel(DiffBatch b, double* 
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const size_t i = base + (size_t)(j * 256 + t) * 4;
-            xv[j] = *(const KFAC_AS1 v4f*)(X + i);
-            yv[j] = *(const KFAC_AS1 v4f*)(Y + i);
+            xv[j] = stream_load4<STREAM>(X + i);
+            yv[j] = stream_load4<STREAM>(Y + i);
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j)
@@ -135,7 +136,8 @@ static int diff_run(const kfac_diff_item* items_host, int32_t count, float* out,
             chunks += chunks_of(it.dim);
         }
         b.prefix[cnt] = chunks;
-        KFAC_LAUNCH(diff_partial_kernel, dim3(chunks), dim3(256), stream, b, partial);
+        if (chunks * (size_t)DF_CHUNK * 8 > STREAM_BYTES) KFAC_LAUNCH_AS("diff_partial_kernel", diff_partial_kernel<true>, dim3(chunks), dim3(256), stream, b, partial);
+        else KFAC_LAUNCH_AS("diff_partial_kernel", diff_partial_kernel<false>, dim3(chunks), dim3(256), stream, b, partial);
         KFAC_LAUNCH(diff_final_kernel, dim3(cnt), dim3(256), stream, b, (const double*)partial, out + first);
         partial += 2 * (size_t)chunks;
     }

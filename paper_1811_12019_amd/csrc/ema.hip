@@ -38,6 +38,7 @@ struct EmaBatch {
     const float* fresh[EMA_MAX];
 };
 
+template <bool STREAM>
 __global__ __launch_bounds__(256) void ema_batched_kernel(EmaBatch b, float decay, float one_minus) {
     const int t = threadIdx.x;
     const unsigned wg = blockIdx.x;
@@ -52,8 +53,8 @@ __global__ __launch_bounds__(256) void ema_batched_kernel(EmaBatch b, float deca
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const size_t i = base + (size_t)(j * 256 + t) * 4;
-            s[j] = *(const KFAC_AS1 v4f*)(run + i);
-            x[j] = *(const KFAC_AS1 v4f*)(fre + i);
+            s[j] = stream_load4<STREAM>(run + i);
+            x[j] = stream_load4<STREAM>(fre + i);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -63,7 +64,7 @@ __global__ __launch_bounds__(256) void ema_batched_kernel(EmaBatch b, float deca
             o.y = fmaf(decay, s[j].y, one_minus * x[j].y);
             o.z = fmaf(decay, s[j].z, one_minus * x[j].z);
             o.w = fmaf(decay, s[j].w, one_minus * x[j].w);
-            *(KFAC_AS1 v4f*)(run + i) = o;
+            stream_store4<STREAM>(run + i, o);
         }
     } else {
         for (size_t i = base + t; i < n && i < base + EMA_CHUNK; i += 256) run[i] = fmaf(decay, run[i], one_minus * fre[i]);
@@ -109,7 +110,10 @@ extern "C" int kfac_ema_batched(const kfac_ema_item* items_host, int32_t count, 
             chunks += (unsigned)((b.n[i] + kfac::EMA_CHUNK - 1) / kfac::EMA_CHUNK);
         }
         b.prefix[cnt] = chunks;
-        KFAC_LAUNCH(kfac::ema_batched_kernel, dim3(chunks), dim3(256), (hipStream_t)stream, b, decay, 1.0f - decay);
+        if (chunks * (size_t)kfac::EMA_CHUNK * 8 > kfac::STREAM_BYTES)
+            KFAC_LAUNCH_AS("kfac::ema_batched_kernel", kfac::ema_batched_kernel<true>, dim3(chunks), dim3(256), (hipStream_t)stream, b, decay, 1.0f - decay);
+        else
+            KFAC_LAUNCH_AS("kfac::ema_batched_kernel", kfac::ema_batched_kernel<false>, dim3(chunks), dim3(256), (hipStream_t)stream, b, decay, 1.0f - decay);
     }
     return KFAC_OK;
 }

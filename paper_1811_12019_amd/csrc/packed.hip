@@ -69,6 +69,7 @@ __device__ __forceinline__ int pk_row_of(size_t p, int n) {
 // packed <- upper triangle of full.  The packed array is walked linearly, four elements (one aligned 16-byte store)
 // per thread; their sources are consecutive in a row of the matrix except where a row ends.
 constexpr unsigned PK_CHUNK = 4096;       // packed elements per workgroup
+template <bool STREAM>
 __global__ __launch_bounds__(256) void pack_upper_kernel(PackBatch b) {
     const unsigned wg = blockIdx.x;
     const int t = threadIdx.x;
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(256) void pack_upper_kernel(PackBatch b) {
         int i = pk_row_of(p, n);
         int j = i + (int)(p - pk_row_start(i, n));
         if (aligned && p + 3 < total && j + 3 < n) {
-            *(KFAC_AS1 v4f*)(P + p) = *(const KFAC_AS1 v4f_a4*)(S + (size_t)i * n + j);
+            stream_store4<STREAM>(P + p, stream_load4<STREAM>(S + (size_t)i * n + j));
         } else {
             for (int e = 0; e < 4 && p + e < total; ++e) {
                 P[p + e] = S[(size_t)i * n + j];
@@ -101,6 +102,8 @@ constexpr int PK_TPR = PK_T / 4;            // threads per tile row
 constexpr int PK_RPP = 256 / PK_TPR;        // tile rows per pass
 constexpr int PK_NP = PK_T / PK_RPP;        // passes
 constexpr int PK_GROUP = 8;                 // passes whose loads are in flight together
+// (Not as a stream: rows begin anywhere in a cache line, and the pieces of a line that two tiles share go to memory apart then: 336 us
+// instead of 281 for all 108 factors of ResNet-50; loads alone 309.)
 __global__ __launch_bounds__(256) void ema_packed_kernel(PackBatch b, float decay, float one_minus) {
     __shared__ float tile[PK_T][PK_T + 1];
     int m, I, J;
@@ -167,6 +170,13 @@ static int fill_pack(PackBatch& b, const int* dims, float* const* full, float* c
     return (int)wgs;
 }
 
+// Elements of a launch's matrices: packing reads half of them and writes their packed copies, 4 bytes an element together.
+static size_t pk_elements(const int* dims, int cnt) {
+    size_t n = 0;
+    for (int i = 0; i < cnt; ++i) n += (size_t)dims[i] * dims[i];
+    return n;
+}
+
 }  // namespace kfac
 
 using namespace kfac;
@@ -193,7 +203,8 @@ extern "C" int kfac_pack_upper_batched(const kfac_pack_item* items_host, int32_t
         }
         PackBatch b;
         const int wgs = fill_pack(b, dims, full, packed, cnt, false);
-        KFAC_LAUNCH(pack_upper_kernel, dim3(wgs), dim3(256), (hipStream_t)stream, b);
+        if (pk_elements(dims, cnt) * 4 > STREAM_BYTES) KFAC_LAUNCH_AS("pack_upper_kernel", pack_upper_kernel<true>, dim3(wgs), dim3(256), (hipStream_t)stream, b);
+        else KFAC_LAUNCH_AS("pack_upper_kernel", pack_upper_kernel<false>, dim3(wgs), dim3(256), (hipStream_t)stream, b);
     }
     return KFAC_OK;
 }
