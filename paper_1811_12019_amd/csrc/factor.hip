@@ -251,7 +251,9 @@ static FactorPlan plan_generic(const Unfold& u) {
     p.tiles_dim = ceil_div(u.d, GT);
     p.ntiles = p.tiles_dim * (p.tiles_dim + 1) / 2;
     int want = ceil_div(1024, p.ntiles);                       // (four workgroups to a CU)
-    int max_split = ceil_div(u.R, 4 * GK);
+    // Two slabs to a workgroup, whose time is the latency of its few trips to memory (512 rows of 145 columns: four slabs 11.8 us, two
+    // 8.1, one 6.1 and 0.8 more for the second pass); up to 64 rows stay in one, without that pass.
+    int max_split = u.R <= 4 * GK ? 1 : ceil_div(u.R, 2 * GK);
     p.nsplit = want < 1 ? 1 : (want > max_split ? max_split : want);
     if (p.nsplit < 1) p.nsplit = 1;
     p.rows_per_split = ceil_div(ceil_div(u.R, p.nsplit), GK) * GK;
