@@ -190,15 +190,18 @@ __device__ __forceinline__ void factor_reduce_block(const gfloat* __restrict__ p
     if (row < d && col < d) {
         const gfloat* src = partial + (size_t)tile * (T * T) + trow * T + tcol;
         const size_t stride = (size_t)ntiles * (T * T);
+        auto at = [&](int sp) { return *(const KFAC_AS1 v4f*)(src + (size_t)sp * stride); };
         int sp = 0;
-        for (; sp + 4 <= nsplit; sp += 4) {
-            v4f a = *(const KFAC_AS1 v4f*)(src + (size_t)sp * stride);
-            v4f b = *(const KFAC_AS1 v4f*)(src + (size_t)(sp + 1) * stride);
-            v4f c = *(const KFAC_AS1 v4f*)(src + (size_t)(sp + 2) * stride);
-            v4f e = *(const KFAC_AS1 v4f*)(src + (size_t)(sp + 3) * stride);
-            s += a; s += b; s += c; s += e;
+        for (; sp + 8 <= nsplit; sp += 8) {
+            const v4f a = at(sp), b = at(sp + 1), c = at(sp + 2), e = at(sp + 3), f = at(sp + 4), g = at(sp + 5), h = at(sp + 6), k = at(sp + 7);
+            s += ((a + b) + (c + e)) + ((f + g) + (h + k));
         }
-        for (; sp < nsplit; ++sp) s += *(const KFAC_AS1 v4f*)(src + (size_t)sp * stride);
+        if (sp + 4 <= nsplit) {
+            const v4f a = at(sp), b = at(sp + 1), c = at(sp + 2), e = at(sp + 3);
+            s += (a + b) + (c + e);
+            sp += 4;
+        }
+        for (; sp < nsplit; ++sp) s += at(sp);
         s *= scale;
         gfloat* __restrict__ out = os.dst;
         if (os.mode == OUT_PACKED) {                                 // only elements on or above the diagonal exist
