@@ -52,17 +52,15 @@ __device__ __forceinline__ ColInfo decode_col(const Unfold& u, int col) {
 constexpr int GT = 64;   // generic kernel: output tile edge
 constexpr int GK = 16;   // unfolded rows per LDS stage
 
-__global__ __launch_bounds__(256) void factor_generic_kernel(Unfold u, const void* __restrict__ x, float scale,
-                                                             OutSpec os, float* __restrict__ partial,
-                                                             int rows_per_split) {
+__device__ __forceinline__ void generic_tile(const Unfold& u, const KFAC_AS1 void* __restrict__ x, float scale, const OutSpec& os,
+                                             gfloat* __restrict__ partial, int rows_per_split, int tile, int ntiles, int split, int nsplit) {
     __shared__ float As[GK][GT + 4];
     __shared__ float Bs[GK][GT + 4];
     __shared__ int rowN[2][GK], rowY[2][GK], rowX[2][GK];
 
     const int t = threadIdx.x;
     int I, J;
-    tri_decode(blockIdx.x, I, J);
-    const int split = blockIdx.y;
+    tri_decode(tile, I, J);
     const int r_begin = split * rows_per_split;
     const int r_end = min(u.R, r_begin + rows_per_split);
 
@@ -101,15 +99,15 @@ __global__ __launch_bounds__(256) void factor_generic_kernel(Unfold u, const voi
         if (u.dtype == KFAC_F32) {                               // (uniform)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                va[e] = ((const float*)x)[max(ia[e], 0)];
-                vb[e] = ((const float*)x)[max(ib[e], 0)];
+                va[e] = ((const gfloat*)x)[max(ia[e], 0)];
+                vb[e] = ((const gfloat*)x)[max(ib[e], 0)];
             }
         } else {
             uint16_t ha[4], hb[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                ha[e] = ((const uint16_t*)x)[max(ia[e], 0)];
-                hb[e] = ((const uint16_t*)x)[max(ib[e], 0)];
+                ha[e] = ((const KFAC_AS1 uint16_t*)x)[max(ia[e], 0)];
+                hb[e] = ((const KFAC_AS1 uint16_t*)x)[max(ib[e], 0)];
             }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -154,7 +152,7 @@ __global__ __launch_bounds__(256) void factor_generic_kernel(Unfold u, const voi
         __syncthreads();
     }
 
-    if (gridDim.y == 1) {
+    if (nsplit == 1) {
 #pragma unroll
         for (int p = 0; p < 4; ++p)
 #pragma unroll
@@ -163,7 +161,7 @@ __global__ __launch_bounds__(256) void factor_generic_kernel(Unfold u, const voi
                 if (row < u.d && col < u.d) emit_sym(os, u.d, row, col, acc[p][q] * scale, I != J);
             }
     } else {
-        float* dst = partial + ((size_t)split * gridDim.x + blockIdx.x) * (GT * GT);
+        gfloat* dst = partial + ((size_t)split * ntiles + tile) * (GT * GT);
 #pragma unroll
         for (int p = 0; p < 4; ++p)
 #pragma unroll
@@ -242,27 +240,65 @@ __device__ __forceinline__ void factor_reduce_block(const gfloat* __restrict__ p
     }
 }
 
-template <int T>
-__global__ __launch_bounds__(256) void factor_reduce_kernel(const float* __restrict__ partial, int nsplit, int d,
-                                                            float scale, OutSpec os) {
-    __shared__ float tr[32][33];
-    factor_reduce_block<T>(as_global(partial), nsplit, gridDim.x, blockIdx.x, blockIdx.y, d, scale, os, tr);
-}
-
-static FactorPlan plan_generic(const Unfold& u) {
+// (at most: the second pass reads them all; 12,544 rows of 28 columns with 392 29.2 us, with 160 23.1, with 96 26.7)
+constexpr int GENERIC_SPLITS = 160;
+static inline __host__ __device__ FactorPlan plan_generic(const Unfold& u) {
     FactorPlan p;
     p.tiles_dim = ceil_div(u.d, GT);
     p.ntiles = p.tiles_dim * (p.tiles_dim + 1) / 2;
     int want = ceil_div(1024, p.ntiles);                       // (four workgroups to a CU)
     // Two slabs to a workgroup, whose time is the latency of its few trips to memory (512 rows of 145 columns: four slabs 11.8 us, two
     // 8.1, one 6.1 and 0.8 more for the second pass); up to 64 rows stay in one, without that pass.
-    int max_split = u.R <= 4 * GK ? 1 : ceil_div(u.R, 2 * GK);
+    const int max_split = u.R <= 4 * GK ? 1 : min(ceil_div(u.R, 2 * GK), GENERIC_SPLITS);
     p.nsplit = want < 1 ? 1 : (want > max_split ? max_split : want);
     if (p.nsplit < 1) p.nsplit = 1;
     p.rows_per_split = ceil_div(ceil_div(u.R, p.nsplit), GK) * GK;
     p.nsplit = ceil_div(u.R, p.rows_per_split);
     p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * p.ntiles * GT * GT * sizeof(float) : 0;
     return p;
+}
+
+// One build (its plan worked out by the host), and the builds of a call in one launch (one by one, two launches each, they would follow
+// each other's ends: eight builds of 512 rows of 145 columns 88.8 us, now 20.4; fifteen of 75 rows of 71 columns 155.6, now 14.0).
+__global__ __launch_bounds__(256) void factor_generic_kernel(Unfold u, const void* x, float scale, OutSpec os, float* partial,
+                                                             int rows_per_split) {
+    generic_tile(u, (const KFAC_AS1 void*)x, scale, os, as_global(partial), rows_per_split, blockIdx.x, gridDim.x, blockIdx.y, gridDim.y);
+}
+
+constexpr int GENERIC_SUBS = (GT / 32) * (GT / 32);          // workgroups of the second pass to a tile
+__global__ __launch_bounds__(256) void factor_reduce_kernel(const float* partial, int nsplit, int d, float scale, OutSpec os) {
+    __shared__ float tr[32][33];
+    factor_reduce_block<GT>(as_global(partial), nsplit, gridDim.x, blockIdx.x, blockIdx.y, d, scale, os, tr);
+}
+
+__device__ __forceinline__ void generic_item(const FBatch& b, int m, kfac_factor_item& it, Unfold& u, FactorPlan& p, float& scale) {
+    it = uniform(b.table[b.index[m]]);
+    if (it.op == KFAC_OP_FACTOR_A) make_unfold_A(&it.desc, &u); else make_unfold_G(&it.desc, &u);
+    p = plan_generic(u);
+    scale = it.scale == 0.f ? 1.0f / (float)u.R : it.scale;
+}
+__global__ __launch_bounds__(256) void factor_generic_batch_kernel(FBatch b) {
+    int local;
+    const int m = fbatch_locate(b, blockIdx.x, local);
+    kfac_factor_item it;
+    Unfold u;
+    FactorPlan p;
+    float scale;
+    generic_item(b, m, it, u, p, scale);
+    const int split = local / p.ntiles;
+    generic_tile(u, (const KFAC_AS1 void*)it.x, scale, out_spec(it), (gfloat*)it.ws, p.rows_per_split, local - split * p.ntiles, p.ntiles,
+                 split, p.nsplit);
+}
+__global__ __launch_bounds__(256) void factor_reduce_batch_kernel(FBatch b) {
+    __shared__ float tr[32][33];
+    int local;
+    const int m = fbatch_locate(b, blockIdx.x, local);
+    kfac_factor_item it;
+    Unfold u;
+    FactorPlan p;
+    float scale;
+    generic_item(b, m, it, u, p, scale);
+    factor_reduce_block<GT>((const gfloat*)it.ws, p.nsplit, p.ntiles, local / GENERIC_SUBS, local % GENERIC_SUBS, u.d, scale, out_spec(it), tr);
 }
 
 // The work of a call's builds of one element size, in rows of 128 x 128 tiles, cut into 128- and into 256-wide tiles.
@@ -370,30 +406,31 @@ static int run_generic(const Unfold& u, const kfac_factor_item& it, hipStream_t 
     FactorPlan p = plan_generic(u);
     dim3 grid(p.ntiles, p.nsplit);
     KFAC_LAUNCH(factor_generic_kernel, grid, dim3(256), stream, u, it.x, scale, out_spec(it), (float*)it.ws, p.rows_per_split);
-    if (p.nsplit > 1) {
-        KFAC_LAUNCH(factor_reduce_kernel<GT>, dim3(p.ntiles, (GT / 32) * (GT / 32)), dim3(256), stream,
-                    (const float*)it.ws, p.nsplit, u.d, scale, out_spec(it));
-    }
+    if (p.nsplit > 1)
+        KFAC_LAUNCH(factor_reduce_kernel, dim3(p.ntiles, GENERIC_SUBS), dim3(256), stream, (const float*)it.ws, p.nsplit, u.d, scale, out_spec(it));
     return KFAC_OK;
 }
 
 // How a build is served.
 enum Route { ROUTE_TILE, ROUTE_GENERIC };
 
-// A build that would have to be repacked first is left to the generic kernel while it is so small that the launch this
-// saves weighs more than the arithmetic (512 rows x 145 columns: 13.6 + 3.7 us against 4.6 + 12.4 + 6.3), unless many
-// builds share the repacking and tile launches.
+// A build that would have to be repacked first is left to the generic kernel while it is so small that the launch this saves weighs more
+// than the arithmetic (bf16, 512 rows of 145 columns: 10.9 us, and 20.9 repacked; 256 of 289 11.0 and 20.9), unless many builds share the
+// repacking and tile launches.  A single build would be the faster for it up to four times that size (512 of 289 12.6 and 26.8), but not
+// a call of several, whose builds are cut as they would be alone (six of them 30.4 and 27.9; six of 98 rows of 1,025 columns 57.6 and
+// 25.6).  Of many rows the second pass reads too many sums (49,000 rows of 6 columns 60.7 us, as a tile 20.4;
+// 12,544 rows of 28 columns of a 3x3 layer 23.1 and 30.2).
 constexpr long long GENERIC_MACS = 1 << 25;
+constexpr int GENERIC_ROWS = 16384;
 
-// Planes read as they lie save the repacking, but not the second launch: small builds of few rows stay there too (fp32, 512 rows of 32
-// columns 12.6 us as a tile and 12.8, of 128 columns 19.2 and 17.1; its chains of 64 rows are also the shorter ones: 2,048 rows of 64
-// columns in bf16 err by 8.8e-8 against 1.2e-7).  From 4,096 rows on the tile is the faster one (6,272 rows of 64 columns 13.7 us and
-// 22.3) and the more accurate one (7.8e-8 and 1.5e-7).
+// Planes read as they lie save the repacking, but not the second launch: small builds of few rows stay there too (bf16, 2,048 rows of 63
+// columns 14.3 us, 1,024 of 145 12.1).  From 4,096 rows on the tile is the faster one (8,192 rows of 63 columns 14.1 us).
 constexpr int GENERIC_PLANE_ROWS = 4096;
 
 static Route route_of(const Unfold& u, const void* x, bool many, View* v) {
     if (!tile_eligible(u, x, v)) return ROUTE_GENERIC;
-    return (v->repack || (v->planes && u.R < GENERIC_PLANE_ROWS)) && !many && (long long)u.R * u.d * u.d <= GENERIC_MACS ? ROUTE_GENERIC : ROUTE_TILE;
+    const int rows = v->repack ? GENERIC_ROWS : v->planes ? GENERIC_PLANE_ROWS : 0;
+    return !many && u.R < rows && (long long)u.R * u.d * u.d <= GENERIC_MACS ? ROUTE_GENERIC : ROUTE_TILE;
 }
 
 static void fbatch_clear(FBatch& b, const kfac_factor_item* dev) {
@@ -519,15 +556,34 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
     }
     for (int k = 0; k < FINISH_LISTS; ++k)
         if ((rc = finish(k)) != KFAC_OK) return rc;
+    FBatch red;                                        // second passes of the generic builds
+    auto generic = [&]() -> int {
+        if (b.count == 1) {                            // (the kernels that need not look the build up)
+            Unfold u;
+            item_unfold(host[b.index[0]], &u);
+            const int rc = run_generic(u, host[b.index[0]], stream);
+            if (rc != KFAC_OK) return rc;
+        } else if (b.count) {
+            KFAC_LAUNCH(factor_generic_batch_kernel, dim3(b.prefix[b.count]), dim3(256), stream, b);
+            if (red.count) KFAC_LAUNCH(factor_reduce_batch_kernel, dim3(red.prefix[red.count]), dim3(256), stream, red);
+        }
+        fbatch_clear(b, dev);
+        fbatch_clear(red, dev);
+        return KFAC_OK;
+    };
+    fbatch_clear(b, dev);
+    fbatch_clear(red, dev);
     for (int i = 0; i < count; ++i) {
         Unfold u;
         View v;
         item_unfold(host[i], &u);
         if (route_of(u, host[i].x, many, &v) == ROUTE_TILE) continue;
-        rc = run_generic(u, host[i], stream);
-        if (rc != KFAC_OK) return rc;
+        const FactorPlan p = plan_generic(u);
+        fbatch_add(b, host, i, 0, p.ntiles * p.nsplit);
+        if (p.nsplit > 1) fbatch_add(red, host, i, 0, p.ntiles * GENERIC_SUBS);
+        if (b.count == FMAXB && (rc = generic()) != KFAC_OK) return rc;
     }
-    return KFAC_OK;
+    return generic();
 }
 
 }  // namespace kfac
