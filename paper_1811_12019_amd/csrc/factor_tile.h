@@ -802,9 +802,9 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
 // XCDs alike.  (With the extra ones always from XCD 0 on, and whole eighths rounded up, its CUs held a workgroup in 68 % of the
 // cycles: all factors of ResNet-50 from NCHW.)  Index in the list, or -1: a padding workgroup.
 static inline __host__ __device__ int next_turn(int turn, int work) { return (turn + work) & 7; }
-__device__ __forceinline__ int unit_of(int work, int wg, int turn) {
+static inline __host__ __device__ int unit_of(int work, int wg, int turn) {
     const int y = ((wg & 7) - turn) & 7, in = wg >> 3, each = work >> 3, extra = work & 7;
-    return in < each + (y < extra) ? y * each + min(y, extra) + in : -1;
+    return in < each + (y < extra) ? y * each + (y < extra ? y : extra) + in : -1;
 }
 
 // One tile (workgroup `wg` of ntiles * nsplit, padded to a multiple of 8) of one factor build.

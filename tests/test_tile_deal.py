@@ -1,0 +1,13 @@
+"""The dealing of the factor builds' work lists, counted on the CPU (tile_deal_check.cpp)."""
+import os
+import subprocess
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+def test_every_unit_is_dealt_once(tmp_path):
+    exe = str(tmp_path / "tile_deal_check")
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "hip", "--offload-arch=gfx950", "--offload-host-only", "-std=c++17", "-O2",
+                    "-I", os.path.join(HERE, "..", "include"), os.path.join(HERE, "tile_deal_check.cpp"), "-o", exe], check=True, capture_output=True)
+    done = subprocess.run([exe], capture_output=True, text=True)
+    assert done.returncode == 0 and done.stdout == "0 faults\n", done.stdout
