@@ -17,13 +17,13 @@
 // CU) for TW^2 multiply-adds, so with 128-wide tiles the copies alone take as many cycles as the matrix cores: where there
 // is enough work (share_of), wide matrices get 256-wide tiles (8 wavefronts of 128 x 64, a ring of four 32-row slabs), which
 // halves that.  Matrices of up to 128 (64) columns get one tile of that width.
-// Measured (ResNet-50, channels last, dense tiles only): batch 32, 128-wide: 925 GFLOP of products in 1.11 ms, matrix cores busy in 39 %
-// of the cycles in which a CU holds a workgroup, LDS in 23 %; batch 128, 256-wide: 3.99 TFLOP in 4.0 ms, 51 % and 20 %.  The rest is
-// wavefronts waiting at the slabs' barriers (a quarter of their time), the row addresses between the products, and a tile's
-// epilogue, beside which a 256-wide workgroup has nothing else on its CU.  With the sums that tap pairs share (factor_shared.h) the
-// 256-wide launch takes 2.1 ms.  All factors from NCHW: bf16 at batch 32 2090 -> 1804 us with shared sums, 1515 with planes read as
-// they lie; fp32 at batch 8 2555 -> 1974 -> 1766.  16 (128-wide) and 56 (256-wide) registers live in scratch memory, all of them
-// used outside the product loops.
+// Measured (ResNet-50, channels last, shared tap sums): batch 128, 256-wide: 1.85 TFLOP executed in 1.67 ms, matrix cores busy in 68 % of
+// the cycles in which a CU holds a workgroup (53 % with the copies' addresses between the products and flat epilogues), LDS in 27 %; 128- and
+// 64-wide: 31 % and 20 %.  The rest is wavefronts waiting at the slabs' barriers and a tile's epilogue, beside which a 256-wide
+// workgroup has nothing else on its CU; at that load the clock falls to about 1.9 GHz.  All factors from NCHW: bf16 at batch 32
+// 2090 -> 1804 us with shared sums, 1515 with planes read as they lie, 1272 with both sides of a slab's work interleaved, work dealt evenly
+// to the XCDs and epilogues from 32-bit offsets; fp32 at batch 8 2555 -> 1974 -> 1766 -> 1600.  128-wide no registers live in
+// scratch memory (fp32 planes: 8), 256-wide 2 (planes: 9), all of them used outside the product loops.
 //
 // The bias column is not part of the tiled matrix (2048 + 1 columns would cost a ninth row of 256-wide tiles for one
 // column): its row of the result is the column sums, which the wavefronts of a diagonal tile whose part lies above the
