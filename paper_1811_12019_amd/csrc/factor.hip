@@ -301,20 +301,24 @@ __global__ __launch_bounds__(256) void factor_reduce_batch_kernel(FBatch b) {
     factor_reduce_block<GT>((const gfloat*)it.ws, p.nsplit, p.ntiles, local / GENERIC_SUBS, local % GENERIC_SUBS, u.d, scale, out_spec(it), tr);
 }
 
-// The work of a call's builds of one element size, in rows of 128 x 128 tiles, cut into 128- and into 256-wide tiles.
+// The work of a call's builds of one element size, in rows of 128 x 128 tiles, cut into 128- and into 256-wide tiles; of the
+// builds that would be cut into 256-wide ones, in 128-wide tiles, and in rows and workgroups of 256-wide ones (add_wide_work).
 struct TileWork {
-    double narrow, wide;
+    double narrow = 0, wide = 0, over = 0, wide_rows = 0;
+    int wide_wgs = 0;
 };
 static void add_work(TileWork& w, const View& v) {
     if (v.shared) {
-        const double n = ceil_div(v.u.C, 128), m = ceil_div(v.u.C, 256);
-        w.narrow += (v.u.C <= 64 ? 13 * 0.5 : 0.5 * n * (n + 1) + 12 * n * n) * v.u.R;
-        w.wide += (v.u.C <= 64 ? 13 * 0.5 : v.u.C <= 128 ? 13 : 2.0 * m * (m + 1) + 48 * m * m) * v.u.R;
+        const double n = ceil_div(v.u.C, 128), m = ceil_div(v.u.C, 256), tiles = v.u.C <= 64 ? 13 * 0.5 : 0.5 * n * (n + 1) + 12 * n * n;
+        w.narrow += tiles * v.u.R;
+        w.wide += (v.u.C <= 128 ? tiles : 2.0 * m * (m + 1) + 48 * m * m) * v.u.R;
+        if (v.u.C > 128) w.over += tiles * v.u.R;
         return;
     }
-    const double n = ceil_div(v.u.d, 128), m = ceil_div(v.u.d, 256);
-    w.narrow += 0.5 * n * (n + 1) * v.u.R;
-    w.wide += (v.u.d <= 128 ? 1.0 : 2.0 * m * (m + 1)) * v.u.R;
+    const double n = ceil_div(v.u.d, 128), m = ceil_div(v.u.d, 256), tiles = 0.5 * n * (n + 1);
+    w.narrow += tiles * v.u.R;
+    w.wide += (v.u.d <= 128 ? tiles : 2.0 * m * (m + 1)) * v.u.R;
+    if (v.u.d > 128) w.over += tiles * v.u.R;
 }
 
 // How they are cut (in a call of few builds each by its own work: run_factor_items).  The rows of a workgroup: half of what
@@ -322,33 +326,57 @@ static void add_work(TileWork& w, const View& v) {
 // last ones (18,816 rows of the first stage's layers at 3200 to a workgroup 119 us, at 6400 181 us), less adds partial sums, each
 // as much traffic as a finished tile, for nothing (the third stage's 18 layers at 1568 rows: 151 us unsplit, 334 us in two).  When
 // there is little work the launch of the second pass weighs too.
-// Width: a 256-wide tile halves the operand traffic per product, but a workgroup fills a CU, its epilogue overlaps with
-// nothing and a matrix is padded to multiples of 256.  It is the better one only for a lot of work with little padding
-// (third stage at 25,088 rows, dense: 1385 us against 1600 us; all of the network, 24 images 1039 us against 984, 32 1192 against 1205 and
-// in (channel, tap) order 1255 against 1430, 64 1920 against 2035, 96 2622 against 2957), or for so much that padding and the launch's
-// end do not show.
-constexpr double WIDE_PER_SLOT = 24000;
-static int share_of(const TileWork& w, bool f32) {
+static int rows_of(const TileWork& w, bool f32) {
     const double per_slot = w.narrow / 768;
-    const double least = f32 ? (per_slot < 100 ? SHARE_LEAST_F32 : 256) : (per_slot < 512 ? SHARE_LEAST : 1600);
-    const double rows = std::min(std::max(0.52 * per_slot, least), (double)(f32 ? ROWS_PER_WG_MAX_F32 : ROWS_PER_WG_MAX));
-    static_assert(0.52 * WIDE_PER_SLOT >= ROWS_PER_WG_MAX, "256-wide tiles always come with the most rows (tiles_ws_bytes)");
-    const bool wide = per_slot >= (w.wide <= 1.15 * w.narrow ? WIDE_PER_SLOT : 100000);
-    return (int)rows + (wide && !f32 ? SHARE_WIDE : 0);
+    const double least = f32 ? (per_slot < 100 ? SHARE_LEAST_F32 : 256) : (per_slot < 512 ? SHARE_LEAST : SHARE_LEAST_WIDE);
+    return (int)std::min(std::max(0.52 * per_slot, least), (double)(f32 ? ROWS_PER_WG_MAX_F32 : ROWS_PER_WG_MAX));
 }
 
-// An upper bound of plan_tiles' workspace over all shares that share_of gives: the partial sums of as many splits as the fewest
-// rows to a workgroup make.  (The factors of ResNet-50 from channels-last bf16 tensors: 1.9 GB
-// at batch 32, 2.5 GB at batch 128.)
+static void add_wide_work(TileWork& w, const View& v, int rows) {
+    if (v.shared) {
+        if (v.u.C <= 128) return;
+        const SharedPlan p = plan_shared(v, rows | SHARE_WIDE);
+        w.wide_rows += (double)p.per[0] * v.u.R;
+        w.wide_wgs += p.first[4];
+    } else if (v.u.d > 128) {
+        const FactorPlan p = plan_tiles(v, rows | SHARE_WIDE);
+        w.wide_rows += (double)p.ntiles * v.u.R;
+        w.wide_wgs += p.ntiles * p.nsplit;
+    }
+}
+
+// Width (16-bit inputs): a 256-wide tile halves the operand traffic per product, but a workgroup fills a CU, its epilogue overlaps with
+// nothing and a matrix is padded to multiples of 256.  It is the better one for workgroups enough to give most CUs one, of rows enough to
+// outweigh the epilogue, with little padding, and if most of the call's work is in matrices of more than 128 columns, or much is.  The rows
+// of a range, and so the error, are those of 128-wide tiles.  Runs of ResNet-50's layers in bf16, 128- and 256-wide, us:
+//     all 54, batch 12 562 and 570, 18 719 and 676, 24 926 and 819, 32 1117 and 960      (workgroups of 1,444, 2,072, 2,785, 3,265 rows)
+//     layers 23 to 43, batch 8 169 and 199, 16 285 and 277, 32 408 and 368, 64 725 and 545            (1,046, 1,408, 2,817, 5,021 rows)
+//     layers 43 to 53, batch 16 227 and 257, 32 297 and 295, 64 404 and 353                                  (766, 1,254, 2,508 rows)
+//     one 3x3 layer of 256 channels at 14 x 14, batch 32 33 and 37, 256 115 and 99, 512 193 and 159             (77, 272, 272 workgroups)
+//     the first 12 (0.48 of the work in wide matrices), batch 32 302 and 317, 64 544 and 563, 128 1103 and 981 (1.1, 2.2, 4.4 M tile rows)
+// Against the lines before it (24,000 rows of 128-wide tiles to one of 768 slots, padding below 15 %) 63 of 204 runs of 1 to 54 layers,
+// 5 to 512 images and both layouts are faster by 2 to 94 %, the others within the spread of repeated runs.  (Always 6,400 rows to a 256-wide
+// workgroup fill fewer CUs and add up longer chains.)
+constexpr int WIDE_WGS = 150, WIDE_ROWS = 1900;
+constexpr double WIDE_PADDING = 1.25, WIDE_PART = 0.7, WIDE_MUCH = 2.5e6, WIDE_ALWAYS = 100000 * 768.0;
+static bool takes_wide(const TileWork& w, int rows) {
+    if (w.narrow >= WIDE_ALWAYS) return true;                    // so much that padding and the launch's end do not show
+    return rows >= SHARE_LEAST_WIDE && w.wide_wgs >= WIDE_WGS && w.wide_rows >= (double)WIDE_ROWS * w.wide_wgs && w.wide <= WIDE_PADDING * w.narrow &&
+           (w.over >= WIDE_PART * w.narrow || w.wide_rows >= WIDE_MUCH);
+}
+
+// An upper bound of plan_tiles' workspace over all shares that run_factor_items gives: the partial sums of as many splits as the fewest
+// rows to a workgroup make.  (The factors of ResNet-50 from channels-last bf16 tensors: 1.8 GB
+// at batch 32, 3.0 GB at batch 128.)
 static size_t tiles_ws_bytes(const View& v) {
     const int D = v.u.d, R = v.u.R;
     const bool f32 = v.u.dtype == KFAC_F32;
     if (v.shared)
-        return std::max(plan_shared(v, f32 ? SHARE_LEAST_F32 : SHARE_LEAST).ws_bytes, f32 ? 0 : plan_shared(v, ROWS_PER_WG_MAX + SHARE_WIDE).ws_bytes);
+        return std::max(plan_shared(v, f32 ? SHARE_LEAST_F32 : SHARE_LEAST).ws_bytes, f32 ? 0 : plan_shared(v, SHARE_LEAST_WIDE | SHARE_WIDE).ws_bytes);
     size_t need = 0;
     for (int tw = D <= 64 ? 64 : 128; tw <= (D <= 128 || f32 ? 128 : 256) && !(D <= 64 && tw > 64); tw *= 2) {
         const int td = ceil_div(D, tw), nt = td * (td + 1) / 2;
-        const int least = f32 ? SHARE_LEAST_F32 : tw == 256 ? ROWS_PER_WG_MAX : SHARE_LEAST;
+        const int least = f32 ? SHARE_LEAST_F32 : tw == 256 ? SHARE_LEAST_WIDE : SHARE_LEAST;
         const int ns = xcd_splits(std::min(most_splits(R, tw, nt, f32), ceil_div(R, least)));
         if (ns > 1) need = std::max(need, (size_t)ns * ((size_t)nt * tile_floats(tw, nt) + (size_t)td * tw) * sizeof(float));
     }
@@ -458,14 +486,23 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
         n_tile += route_of(u, host[i].x, true, &v) == ROUTE_TILE;
     }
     const bool many = n_tile >= 16;
-    TileWork work16 = {0, 0}, work32 = {0, 0};
-    for (int i = 0; i < count; ++i) {
-        Unfold u;
-        View v;
-        item_unfold(host[i], &u);
-        if (route_of(u, host[i].x, many, &v) == ROUTE_TILE) add_work(u.dtype == KFAC_F32 ? work32 : work16, v);
+    int share16 = 0, share32 = 0;
+    if (many) {
+        TileWork work16, work32;
+        for (int pass = 0; pass < 2; ++pass) {
+            for (int i = 0; i < count; ++i) {
+                Unfold u;
+                View v;
+                item_unfold(host[i], &u);
+                if (route_of(u, host[i].x, many, &v) != ROUTE_TILE || (pass && u.dtype == KFAC_F32)) continue;
+                if (pass) add_wide_work(work16, v, share16);
+                else add_work(u.dtype == KFAC_F32 ? work32 : work16, v);
+            }
+            share16 = rows_of(work16, false);
+        }
+        share32 = rows_of(work32, true);
+        if (takes_wide(work16, share16)) share16 |= SHARE_WIDE;
     }
-    const int share16 = share_of(work16, false), share32 = share_of(work32, true);
     // Few builds: each is cut as it would be in a call of its own, so that its result is the same to the last bit (kfac.h).  By
     // the work of the whole call, one to seven layers of ResNet-50 at batch 2 to 32 take between 26 % less time (five layers of the
     // third stage at batch 8: 52 instead of 70 us) and 11 % more (four layers around the second stage's start at batch 8: 70 instead
@@ -474,9 +511,12 @@ static int run_factor_items(const kfac_factor_item* host, const kfac_factor_item
         const bool f32 = v.u.dtype == KFAC_F32;
         const int flag = v.planes ? SHARE_PLANES : 0;
         if (many) return (f32 ? share32 : share16) | flag;
-        TileWork own = {0, 0};
+        TileWork own;
         add_work(own, v);
-        return share_of(own, f32) | flag;
+        const int rows = rows_of(own, f32);
+        if (f32) return rows | flag;
+        add_wide_work(own, v, rows);
+        return rows | flag | (takes_wide(own, rows) ? SHARE_WIDE : 0);
     };
     FBatch b, fin[FINISH_LISTS];                       // fin: second passes, after all tiles
     auto finish = [&](int k) -> int {

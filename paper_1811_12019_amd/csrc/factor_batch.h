@@ -18,7 +18,7 @@ struct FactorPlan {
     size_t ws_bytes;
 };
 
-// Tile width and row split of a matrix-core build.  `share`: how the builds of a call are cut (share_of): the rows of a
+// Tile width and row split of a matrix-core build.  `share`: how the builds of a call are cut (rows_of, takes_wide): the rows of a
 // workgroup, plus SHARE_WIDE if matrices of more than 128 columns get 256-wide tiles, plus SHARE_PLANES if the tensor is read as
 // planes (the address decides that, once, on the host: worked out by the kernels it cost each launch 0.2 to 0.5 us).  A matrix of up to
 // 128 (64) columns is one tile of that width.
@@ -26,7 +26,7 @@ constexpr int SHARE_WIDE = 1 << 20, SHARE_PLANES = 1 << 21;
 constexpr int SHARE_TURN_SHIFT = 24;         // (for the tile kernel: the build's `turn`, see unit_of)
 constexpr int ROWS_PER_WG_MAX = 6400, ROWS_PER_WG_MAX_F32 = 1600;
 constexpr int ROWS_PER_WG_MIN = 512, ROWS_PER_WG_MIN_F32 = 64;
-constexpr int SHARE_LEAST = 1024, SHARE_LEAST_F32 = 128;           // the fewest rows share_of gives a workgroup
+constexpr int SHARE_LEAST = 1024, SHARE_LEAST_WIDE = 1600, SHARE_LEAST_F32 = 128;    // the fewest rows rows_of gives a workgroup (256-wide)
 
 // splits that keep a build's partial sums below 34 MB (256-wide tiles: 67 MB), unless a workgroup's rows would pass the maximum
 static inline __host__ __device__ int most_splits(int R, int tw, int ntiles, bool f32) {

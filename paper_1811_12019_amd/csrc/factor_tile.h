@@ -15,7 +15,7 @@
 //
 // What bounds it and how it is cut.  A TW x TW tile moves 2 TW elements per row through the L1 (64 bytes per cycle and
 // CU) for TW^2 multiply-adds, so with 128-wide tiles the copies alone take as many cycles as the matrix cores: where there
-// is enough work (share_of), wide matrices get 256-wide tiles (8 wavefronts of 128 x 64, a ring of four 32-row slabs), which
+// is enough work (takes_wide), wide matrices get 256-wide tiles (8 wavefronts of 128 x 64, a ring of four 32-row slabs), which
 // halves that.  Matrices of up to 128 (64) columns get one tile of that width.
 // Measured (ResNet-50, channels last, shared tap sums): batch 128, 256-wide: 1.85 TFLOP executed in 1.67 ms, matrix cores busy in 68 % of
 // the cycles in which a CU holds a workgroup (53 % with the copies' addresses between the products and flat epilogues), LDS in 27 %; 128- and
