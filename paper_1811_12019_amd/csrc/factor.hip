@@ -305,9 +305,15 @@ __global__ __launch_bounds__(256) void factor_reduce_batch_kernel(FBatch b) {
 // builds that would be cut into 256-wide ones, in 128-wide tiles, and in rows and workgroups of 256-wide ones (add_wide_work).
 struct TileWork {
     double narrow = 0, wide = 0, over = 0, wide_rows = 0;
+    double area = 0, filled = 0;                                 // their columns, padded to multiples of 256 and not, squared, times rows
     int wide_wgs = 0;
 };
 static void add_work(TileWork& w, const View& v) {
+    const double cols = v.shared ? v.u.C : v.u.d, padded = 256.0 * ceil_div((int)cols, 256);
+    if (cols > 128) {
+        w.area += padded * padded * v.u.R;
+        w.filled += cols * cols * v.u.R;
+    }
     if (v.shared) {
         const double n = ceil_div(v.u.C, 128), m = ceil_div(v.u.C, 256), tiles = v.u.C <= 64 ? 13 * 0.5 : 0.5 * n * (n + 1) + 12 * n * n;
         w.narrow += tiles * v.u.R;
@@ -352,16 +358,19 @@ static void add_wide_work(TileWork& w, const View& v, int rows) {
 //     all 54, batch 12 562 and 570, 18 719 and 676, 24 926 and 819, 32 1117 and 960      (workgroups of 1,444, 2,072, 2,785, 3,265 rows)
 //     layers 23 to 43, batch 8 169 and 199, 16 285 and 277, 32 408 and 368, 64 725 and 545            (1,046, 1,408, 2,817, 5,021 rows)
 //     layers 43 to 53, batch 16 227 and 257, 32 297 and 295, 64 404 and 353                                  (766, 1,254, 2,508 rows)
+//     one 1x1 layer of 256 columns (a third more work in 256-wide tiles, but full ones) at 56 x 56, batch 64 114 and 108, 256 351 and 310
+//     the first convolution (224 of 256 columns; narrow), batch 64 111 and 120, 256 374 and 413                   (256 and 492 workgroups)
 //     one 3x3 layer of 256 channels at 14 x 14, batch 32 33 and 37, 256 115 and 99, 512 193 and 159             (77, 272, 272 workgroups)
 //     the first 12 (0.48 of the work in wide matrices), batch 32 302 and 317, 64 544 and 563, 128 1103 and 981 (1.1, 2.2, 4.4 M tile rows)
 // Against the lines before it (24,000 rows of 128-wide tiles to one of 768 slots, padding below 15 %) 63 of 204 runs of 1 to 54 layers,
 // 5 to 512 images and both layouts are faster by 2 to 94 %, the others within the spread of repeated runs.  (Always 6,400 rows to a 256-wide
 // workgroup fill fewer CUs and add up longer chains.)
 constexpr int WIDE_WGS = 150, WIDE_ROWS = 1900;
-constexpr double WIDE_PADDING = 1.25, WIDE_PART = 0.7, WIDE_MUCH = 2.5e6, WIDE_ALWAYS = 100000 * 768.0;
+constexpr double WIDE_PADDING = 1.25, WIDE_PADDING_FULL = 1.34, WIDE_PART = 0.7, WIDE_MUCH = 2.5e6, WIDE_ALWAYS = 100000 * 768.0;
 static bool takes_wide(const TileWork& w, int rows) {
     if (w.narrow >= WIDE_ALWAYS) return true;                    // so much that padding and the launch's end do not show
-    return rows >= SHARE_LEAST_WIDE && w.wide_wgs >= WIDE_WGS && w.wide_rows >= (double)WIDE_ROWS * w.wide_wgs && w.wide <= WIDE_PADDING * w.narrow &&
+    return rows >= SHARE_LEAST_WIDE && w.wide_wgs >= WIDE_WGS && w.wide_rows >= (double)WIDE_ROWS * w.wide_wgs &&
+           (w.wide <= WIDE_PADDING * w.narrow || (w.wide <= WIDE_PADDING_FULL * w.narrow && w.area <= WIDE_PADDING * w.filled)) &&
            (w.over >= WIDE_PART * w.narrow || w.wide_rows >= WIDE_MUCH);
 }
 
