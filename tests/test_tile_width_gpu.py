@@ -25,11 +25,13 @@ def reference(x, s):
 
 # 1,024 columns are ten 256-wide tiles; 30,400 rows make 16 ranges of 1,900 on average, the fewest that are taken, 30,336 ones of 1,896;
 # ragged rows and columns: 36,792 rows are 23 ranges of 1,600, of which a multiple of 8 is kept, 16 of 2,300 (from 36,801 rows on it would be
-# 24 of 1,534: narrow); shared tap sums: 272 workgroups
+# 24 of 1,534: narrow); one full tile of 256 columns, a third more work, in as many ranges as scratch allows, 256 of 1,911; shared tap
+# sums: 272 workgroups
 @pytest.mark.parametrize("shape,wide", [
     (synth.LayerShape("line", 30400, 1024, 1, 1, 8, 1, 1, 1, 0), True),
     (synth.LayerShape("under", 30336, 1024, 1, 1, 8, 1, 1, 1, 0), False),
     (synth.LayerShape("ragged", 4088, 1000, 1, 9, 8, 1, 1, 1, 0), True),
+    (synth.LayerShape("full", 156, 256, 56, 56, 8, 1, 1, 1, 0), True),
     (synth.LayerShape("shared", 256, 256, 14, 14, 8, 3, 3, 1, 1), True)], ids=lambda v: getattr(v, "name", str(v)))
 @pytest.mark.parametrize("dtype", [kb.KFAC_BF16, kb.KFAC_F16])
 def test_width_of_one_build_and_of_many(shape, wide, dtype):
