@@ -233,6 +233,25 @@ __device__ __forceinline__ void static_for(F&& f) {              // f(StaticInt<
     }
 }
 
+// The old values of a running average, 16-byte vectors of a block of 32 rows x w columns of the result, which lies in a buffer of its own
+// size: a lane's byte offset and the bytes of a row, by which the passes step on in a scalar register.  A block that is not whole (the
+// others fetch theirs element by element) gets an offset outside every result (d < 32768) and no steps: a step in a scalar register is not
+// part of what the buffer's size is compared with, so that none may lead behind the matrix.
+constexpr unsigned OUTSIDE = 0xFFFFFFF0u;
+struct OldAt {
+    unsigned offset, row;
+};
+static inline __host__ __device__ OldAt old_at(bool whole, unsigned offset, unsigned row_bytes) {
+    return OldAt{whole ? offset : OUTSIDE, whole ? row_bytes : 0u};
+}
+// (at row, col of the tile that begins at row0, col0 of the matrix of D data columns; diag: on the diagonal, whose tiles' upper half is a
+// mirror image.  Here and where it is asked, no operator that stops at the first answer: the branches cost the product loop registers.)
+static inline __host__ __device__ bool block_whole(bool diag, int row0, int row, int col0, int col, int w, int D) {
+    return (row0 + row + 32 <= D) & (col0 + col + w <= D) & (!diag | (row >= col + w));
+}
+// Row of the block row p's pass k (lane / (w / 4) further rows in it).
+static inline __host__ __device__ int pass_row(int w, int p, int k) { return p * 32 + k * (64 / (w / 4)); }
+
 // What a tile's workgroup works on.
 struct TileJob {
     int I, J;
@@ -668,8 +687,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     constexpr int NV = 32 * W / 256;                               // 16-byte vectors per lane of one block row
     // A block row that is all there, below the diagonal and in the caller's column order (nearly all of a large factor's).
     auto whole = [&](int p) {
-        const int rb = wr + p * 32;
-        return !v.mapped && !packed && I * TW + rb + 32 <= D && J * TW + wc + W <= D && (!DIAG || rb >= wc + W);
+        return !v.mapped & !packed & block_whole(DIAG, I * TW, wr + p * 32, J * TW, wc, W, D);
     };
     constexpr int VPR = W / 4;                                     // vectors per row
     const int vr = lane / VPR, vc = lane % VPR * 4;                // this lane's vector of the first rows
@@ -683,14 +701,14 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     const unsigned ud = 4u * d;
     const unsigned direct0 = (I * TW + wr + vr) * ud + 4u * (J * TW + wc + vc);
     const unsigned mirror0 = (J * TW + wc + (lane >> 3)) * ud + 4u * (I * TW + wr + (lane & 7) * 4);
-    auto direct_step = [&](int p, int k) { return (p * 32 + k * (64 / VPR)) * ud; };
+    auto direct_step = [&](int p, int k) { return pass_row(W, p, k) * ud; };
     auto mirror_step = [&](int p, int k) { return k * 8 * ud + 4u * (p * 32); };
-    // (without a branch, also where the old values are not wanted: what lies outside the buffer is not fetched)
-    const unsigned old0 = ema ? direct0 : 0xFFFFFFF0u;
+    // (without a branch, also where the old values are not wanted)
     auto fetch_old = [&](int p, v4f (&o)[NV]) {
+        const OldAt at = old_at(ema & whole(p), direct0, ud);
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
-            const v4u x = __builtin_amdgcn_raw_buffer_load_b128(rsrc, old0, direct_step(p, k), 0);
+            const v4u x = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at.offset, pass_row(W, p, k) * at.row, 0);
             __builtin_memcpy(&o[k], &x, 16);
         }
     };
