@@ -49,9 +49,6 @@ __device__ __forceinline__ ColInfo decode_col(const Unfold& u, int col) {
     return ci;
 }
 
-constexpr int GT = 64;   // generic kernel: output tile edge
-constexpr int GK = 16;   // unfolded rows per LDS stage
-
 __device__ __forceinline__ void generic_tile(const Unfold& u, const KFAC_AS1 void* __restrict__ x, float scale, const OutSpec& os,
                                              gfloat* __restrict__ partial, int rows_per_split, int tile, int ntiles, int split, int nsplit) {
     __shared__ float As[GK][GT + 4];
@@ -238,24 +235,6 @@ __device__ __forceinline__ void factor_reduce_block(const gfloat* __restrict__ p
         for (int q = 0; q < 4; ++q)
             if (mcol + q < d) mout[mcol + q] = tr[lc + q][lr];
     }
-}
-
-// (at most: the second pass reads them all; 12,544 rows of 28 columns with 392 29.2 us, with 160 23.1, with 96 26.7)
-constexpr int GENERIC_SPLITS = 160;
-static inline __host__ __device__ FactorPlan plan_generic(const Unfold& u) {
-    FactorPlan p;
-    p.tiles_dim = ceil_div(u.d, GT);
-    p.ntiles = p.tiles_dim * (p.tiles_dim + 1) / 2;
-    int want = ceil_div(1024, p.ntiles);                       // (four workgroups to a CU)
-    // Two slabs to a workgroup, whose time is the latency of its few trips to memory (512 rows of 145 columns: four slabs 11.8 us, two
-    // 8.1, one 6.1 and 0.8 more for the second pass); up to 64 rows stay in one, without that pass.
-    const int max_split = u.R <= 4 * GK ? 1 : min(ceil_div(u.R, 2 * GK), GENERIC_SPLITS);
-    p.nsplit = want < 1 ? 1 : (want > max_split ? max_split : want);
-    if (p.nsplit < 1) p.nsplit = 1;
-    p.rows_per_split = ceil_div(ceil_div(u.R, p.nsplit), GK) * GK;
-    p.nsplit = ceil_div(u.R, p.rows_per_split);
-    p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * p.ntiles * GT * GT * sizeof(float) : 0;
-    return p;
 }
 
 // One build (its plan worked out by the host), and the builds of a call in one launch (one by one, two launches each, they would follow

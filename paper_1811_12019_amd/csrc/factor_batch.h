@@ -96,6 +96,30 @@ static inline __host__ __device__ FactorPlan plan_tiles(const View& v, int share
     return p;
 }
 
+// The generic kernel's builds (factor.hip).
+constexpr int GT = 64;   // output tile edge
+constexpr int GK = 16;   // unfolded rows per LDS stage
+// Row ranges: at most 160, since the second pass reads them all (12,544 rows of 28 columns with 392 29.2 us, with 160 23.1, with 96 26.7), but
+// as many as keep a range, which is one chain of fp32 additions, at 128 rows or below.  Channels-last tensors off the 16-byte grid, bf16, 64
+// columns, with 160 ranges and so: 50,176 rows 50 us, error against 64 bits 5.3e-7, and 44, 1.9e-7; 401,408 301, 3.9e-6, and 127, 8.1e-7.
+constexpr int GENERIC_SPLITS = 160, GENERIC_RANGE = 128;
+static inline __host__ __device__ FactorPlan plan_generic(const Unfold& u) {
+    FactorPlan p;
+    p.tiles_dim = ceil_div(u.d, GT);
+    p.ntiles = p.tiles_dim * (p.tiles_dim + 1) / 2;
+    int want = ceil_div(1024, p.ntiles);                       // (four workgroups to a CU)
+    // Two slabs to a workgroup, whose time is the latency of its few trips to memory (512 rows of 145 columns: four slabs 11.8 us, two
+    // 8.1, one 6.1 and 0.8 more for the second pass); up to 64 rows stay in one, without that pass.
+    const int most = ceil_div(u.R, GENERIC_RANGE) > GENERIC_SPLITS ? ceil_div(u.R, GENERIC_RANGE) : GENERIC_SPLITS;
+    const int slabs = ceil_div(u.R, 2 * GK), max_split = u.R <= 4 * GK ? 1 : slabs < most ? slabs : most;
+    p.nsplit = want < 1 ? 1 : (want > max_split ? max_split : want);
+    if (p.nsplit < 1) p.nsplit = 1;
+    p.rows_per_split = ceil_div(ceil_div(u.R, p.nsplit), GK) * GK;
+    p.nsplit = ceil_div(u.R, p.rows_per_split);
+    p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * p.ntiles * GT * GT * sizeof(float) : 0;
+    return p;
+}
+
 // The workspace of a matrix-core build: the repacked tensor, if there is one, then the partial sums.
 static inline __host__ __device__ Partial partial_of(const View& v, const FactorPlan& p, void* ws) {
     Partial q;

@@ -79,3 +79,38 @@ def test_more_small_builds_than_a_launch_holds():
         X = torch.cat([x.double().view(-1, s.C_in), torch.ones(s.R, 1, dtype=torch.float64, device=DEV)], 1)
         ref = (X.t() @ X / s.R).cpu().numpy()
         assert rel_fro(got.cpu().numpy(), ref) < FACTOR_TOL
+
+
+def chained(X, rows):
+    """X^T X of a few columns, in float32, as the kernel adds it: a chain of fused multiply-adds for every range of `rows` rows (a product of
+    16-bit values is exact, and so is its sum with a partial sum in float64), then the ranges' sums eight at a time."""
+    R, C = X.shape
+    n = -(-R // rows)
+    P = np.zeros((n * rows, C))
+    P[:R] = X
+    P = P.reshape(n, rows, C)
+    acc = np.zeros((n, C, C), np.float32)
+    for k in range(rows):
+        acc = (acc + P[:, k, :, None] * P[:, k, None, :]).astype(np.float32)
+    total, i = np.zeros((C, C), np.float32), 0
+    while i + 8 <= n:
+        a = acc[i:i + 8]
+        total, i = total + (((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]))), i + 8
+    for a in acc[i:]:
+        total = total + a
+    return total
+
+
+@pytest.mark.parametrize("rows,longest", [(50176, 128), (401408, 400)])
+def test_many_rows_off_the_vector_alignment(rows, longest):
+    """Builds of many rows that the matrix cores cannot take: the error of chains of at most 128 rows, or of what 1,024 workgroups make, and no
+    more (what the order of the ranges' last additions and the scale add stays below 2^-23)."""
+    s = synth.LayerShape("rows", rows // 64, 64, 8, 8, 4, 1, 1, 1, 0, has_bias=False)
+    desc = kb.make_desc(s, NHWC, kb.KFAC_BF16, KKC)
+    x = torch.randn(rows * 64 + 1, device=DEV, generator=torch.Generator(device=DEV).manual_seed(5)).bfloat16()[1:]
+    out = torch.full((s.d_A, s.d_A), float("nan"), device=DEV)
+    kb.kfac_factor_A(desc, x, 0.0, out, kb.alloc_workspace(kb.kfac_factor_workspace_bytes(kb.KFAC_OP_FACTOR_A, desc), DEV))
+    X = x.float().cpu().numpy().reshape(rows, 64)[:, :8].astype(np.float64)
+    ref = X.T @ X / rows
+    bound = rel_fro(chained(X, longest) / np.float64(rows), ref) + 2.0 ** -23
+    assert rel_fro(out[:8, :8].cpu().numpy(), ref) < bound
