@@ -88,6 +88,7 @@ def kernel_work(net: kstep.KfacNetworkStep, kernels):
         "inv_out_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(10.0 * d * d for d in dims)),
         "kfac::ema_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(12.0 * d * d for d in dims)),
         "kfac::ema_batched_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(12.0 * d * d for d in dims)),
+        "kfac::ema_batched_kernel<stream>": ("hbm", PEAK["hbm"], "GB/s", sum(12.0 * d * d for d in dims)),
         "inv_init_kernel": ("hbm", PEAK["hbm"], "GB/s", sum(4.0 * d * (d + 1) for d in dims if d > kstep.INVERSE_BLOCK)),
     }
     for width, flops in fac_tile.items():

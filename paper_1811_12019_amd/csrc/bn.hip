@@ -293,14 +293,14 @@ extern "C" int kfac_bn_sample_grads_batched(const kfac_bn_item* items_host, int3
             BnBatch& b = lists[dt];
             if (b.count == 0) continue;
             b.prefix[b.count] = wgs[dt];
-#define KFAC_BN_LAUNCH(DTYPE, name)                                                                                                   \
+#define KFAC_BN_LAUNCH(DTYPE)                                                                                                   \
     do {                                                                                                                            \
-        if (bytes[dt] > STREAM_BYTES) KFAC_LAUNCH_AS(name, (bn_partial_kernel<DTYPE, true>), dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b); \
-        else KFAC_LAUNCH_AS(name, (bn_partial_kernel<DTYPE, false>), dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b);                  \
+        if (bytes[dt] > STREAM_BYTES) KFAC_LAUNCH_AS("bn_partial_kernel<" #DTYPE ", stream>", (bn_partial_kernel<DTYPE, true>), dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b); \
+        else KFAC_LAUNCH_AS("bn_partial_kernel<" #DTYPE ">", (bn_partial_kernel<DTYPE, false>), dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b);                  \
     } while (0)
-            if (dt == KFAC_F32) KFAC_BN_LAUNCH(KFAC_F32, "bn_partial_kernel<KFAC_F32>");
-            else if (dt == KFAC_BF16) KFAC_BN_LAUNCH(KFAC_BF16, "bn_partial_kernel<KFAC_BF16>");
-            else KFAC_BN_LAUNCH(KFAC_F16, "bn_partial_kernel<KFAC_F16>");
+            if (dt == KFAC_F32) KFAC_BN_LAUNCH(KFAC_F32);
+            else if (dt == KFAC_BF16) KFAC_BN_LAUNCH(KFAC_BF16);
+            else KFAC_BN_LAUNCH(KFAC_F16);
 #undef KFAC_BN_LAUNCH
         }
         if (rb.count) {

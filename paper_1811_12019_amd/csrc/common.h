@@ -17,8 +17,8 @@
         if (hipGetLastError() != hipSuccess) return KFAC_ERR_HIP; \
     } while (0)
 
-// Launch `kernel` and return KFAC_ERR_HIP from the enclosing function if the launch is rejected; _AS: timed under another name (of
-// kernels that are one to whoever reads the timings).
+// Launch `kernel` and return KFAC_ERR_HIP from the enclosing function if the launch is rejected; _AS: timed under another name (a
+// template's forms, of which the timings tell apart what their reader does).
 #define KFAC_LAUNCH(kernel, grid, block, stream, ...) KFAC_LAUNCH_AS(#kernel, kernel, grid, block, stream, __VA_ARGS__)
 #define KFAC_LAUNCH_AS(name, kernel, grid, block, stream, ...)                     \
     do {                                                                           \

@@ -136,7 +136,7 @@ static int diff_run(const kfac_diff_item* items_host, int32_t count, float* out,
             chunks += chunks_of(it.dim);
         }
         b.prefix[cnt] = chunks;
-        if (chunks * (size_t)DF_CHUNK * 8 > STREAM_BYTES) KFAC_LAUNCH_AS("diff_partial_kernel", diff_partial_kernel<true>, dim3(chunks), dim3(256), stream, b, partial);
+        if (chunks * (size_t)DF_CHUNK * 8 > STREAM_BYTES) KFAC_LAUNCH_AS("diff_partial_kernel<stream>", diff_partial_kernel<true>, dim3(chunks), dim3(256), stream, b, partial);
         else KFAC_LAUNCH_AS("diff_partial_kernel", diff_partial_kernel<false>, dim3(chunks), dim3(256), stream, b, partial);
         KFAC_LAUNCH(diff_final_kernel, dim3(cnt), dim3(256), stream, b, (const double*)partial, out + first);
         partial += 2 * (size_t)chunks;

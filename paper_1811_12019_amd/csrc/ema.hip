@@ -111,7 +111,7 @@ extern "C" int kfac_ema_batched(const kfac_ema_item* items_host, int32_t count, 
         }
         b.prefix[cnt] = chunks;
         if (chunks * (size_t)kfac::EMA_CHUNK * 8 > kfac::STREAM_BYTES)
-            KFAC_LAUNCH_AS("kfac::ema_batched_kernel", kfac::ema_batched_kernel<true>, dim3(chunks), dim3(256), (hipStream_t)stream, b, decay, 1.0f - decay);
+            KFAC_LAUNCH_AS("kfac::ema_batched_kernel<stream>", kfac::ema_batched_kernel<true>, dim3(chunks), dim3(256), (hipStream_t)stream, b, decay, 1.0f - decay);
         else
             KFAC_LAUNCH_AS("kfac::ema_batched_kernel", kfac::ema_batched_kernel<false>, dim3(chunks), dim3(256), (hipStream_t)stream, b, decay, 1.0f - decay);
     }

@@ -203,7 +203,7 @@ extern "C" int kfac_pack_upper_batched(const kfac_pack_item* items_host, int32_t
         }
         PackBatch b;
         const int wgs = fill_pack(b, dims, full, packed, cnt, false);
-        if (pk_elements(dims, cnt) * 4 > STREAM_BYTES) KFAC_LAUNCH_AS("pack_upper_kernel", pack_upper_kernel<true>, dim3(wgs), dim3(256), (hipStream_t)stream, b);
+        if (pk_elements(dims, cnt) * 4 > STREAM_BYTES) KFAC_LAUNCH_AS("pack_upper_kernel<stream>", pack_upper_kernel<true>, dim3(wgs), dim3(256), (hipStream_t)stream, b);
         else KFAC_LAUNCH_AS("pack_upper_kernel", pack_upper_kernel<false>, dim3(wgs), dim3(256), (hipStream_t)stream, b);
     }
     return KFAC_OK;
