@@ -256,12 +256,12 @@ def peaks():
             ms = timed(lambda: kb.kfac_probe_mfma(dt, wgs, iters, out))
             best = max(best, wgs * 4.0 * iters * 4 * flops / ms / 1e9)
         res[name + "_tflops"] = round(best, 1)
-    src = torch.ones(1 << 29, dtype=torch.float32, device="cuda")       # 2 GiB
+    src = torch.ones(1 << 28, dtype=torch.float32, device="cuda")       # 1 GiB, past the caches
     dst = torch.empty_like(src)
     sink = torch.zeros(1, device="cuda")
     nbytes = src.numel() * 4
     bc = br = 0.0
-    for wgs in (1024, 4096, 16384):
+    for wgs in (1024, 2048, 4096, 16384):
         bc = max(bc, 2.0 * nbytes / timed(lambda: kb.kfac_probe_copy(src, dst, wgs)) / 1e6)
         br = max(br, 1.0 * nbytes / timed(lambda: kb.kfac_probe_read(src, sink, wgs)) / 1e6)
     res["copy_gbs_read_plus_write"] = round(bc, 1)

@@ -58,8 +58,8 @@ __device__ __forceinline__ KFAC_AS1 T* as_global(T* p) {
 }
 
 // Streams.  Arrays that a kernel touches once and that do not fit the 256 MB memory-side cache are read and written past the caches
-// (non-temporal): 616 MB copied at 6.3 instead of 5.5 TB/s, read at 7.1 instead of 6.2, updated in place from another array at 6.0
-// instead of 5.35 (either alone, loads or stores, brings little).  Calls below the line find their data in that cache, or leave it
+// (non-temporal): 616 MB copied at 6.2 instead of 5.75 TB/s, read at 7.1 instead of 6.4 (the probes in runtime.hip, best of four launch
+// sizes), updated in place from another array at 6.2 instead of 5.3 (either alone, loads or stores, brings little).  Calls below the line find their data in that cache, or leave it
 // there for the next one: they are not streams.
 constexpr size_t STREAM_BYTES = (size_t)256 << 20;
 template <bool STREAM>

@@ -104,6 +104,11 @@ static void add_wide_work(TileWork& w, const View& v, int rows) {
 //     the first convolution (224 of 256 columns; narrow), batch 64 111 and 120, 256 374 and 413                   (256 and 492 workgroups)
 //     one 3x3 layer of 256 channels at 14 x 14, batch 32 33 and 37, 256 115 and 99, 512 193 and 159             (77, 272, 272 workgroups)
 //     the first 12 (0.48 of the work in wide matrices), batch 32 302 and 317, 64 544 and 563, 128 1103 and 981 (1.1, 2.2, 4.4 M tile rows)
+// One matrix, near the lines (workgroups of rows on average): 132 of 1,853 60 and 66, 144 of 1,568 46 and 49, 160 of 1,960 76 and 59, 181 of
+// 1,663 61 and 56, 180 of 1,436 60 and 62, 236 of 1,209 64 and 61, 225 of 1,666 95 and 72: there the line in rows leaves up to a quarter;
+// just more workgroups than CUs, 270 of 6,272, 272 and 288.  Runs with 0.4 to 0.6 of the work in wide matrices, by tile rows: 1.1 M 281 and
+// 301, 1.4 324 and 293, 1.7 386 and 368, 2.0 447 and 456, 2.2 488 and 518, 2.7 587 and 531, 2.8 658 and 590, 3.3 785 and 779.  A call of few
+// builds that take both widths has two launches: layers 7 to 13 at batch 55 291 us, all narrow 273.
 // Against the lines before it (24,000 rows of 128-wide tiles to one of 768 slots, padding below 15 %) 63 of 204 runs of 1 to 54 layers,
 // 5 to 512 images and both layouts are faster by 2 to 94 %, the others within the spread of repeated runs.  (Always 6,400 rows to a 256-wide
 // workgroup fill fewer CUs and add up longer chains.)

@@ -4,14 +4,14 @@
 // One TW x TW tile (on or below the diagonal) of one range of unfolded rows per workgroup.  The contraction index (the
 // unfolded row) is the slow index in memory, and the 16-bit MFMA wants it contiguous per lane; gfx950 has exactly the two
 // instructions that make this cheap:
-//   * global_load_lds_dwordx4 copies 16 bytes per lane from global memory straight into LDS (lane i lands at
-//     base + 16 i) without passing through registers, so a ring of row slabs can be kept in flight with no register
-//     cost and a single barrier per slab;
+//   * a load to LDS copies 16 bytes per lane from global memory (lane i lands at base + 16 i) without passing through registers, so a ring
+//     of row slabs can be kept in flight with no register cost and a single barrier per slab: buffer_load_dwordx4 .. lds from 32-bit offsets
+//     for 16-bit tensors, global_load_lds_dwordx4 from addresses for fp32 ones, which may pass 4 GB;
 //   * ds_read_b64_tr_b16 reads a 16 x 4 block of 16-bit values transposed: within 16 lanes, lane j receives
 //     element (j % 4) of lanes j/4, j/4 + 4, j/4 + 8, j/4 + 12.  With lanes pointed at 4 rows x 4 column groups
 //     of a raw slab, lane j gets four consecutive unfolded rows of column j: an MFMA operand half.
-// Rows outside a workgroup's range, taps that fall into the zero padding and columns beyond the matrix are fetched from a
-// 16-byte block of zeros, so the slab in LDS is always complete and the inner loop has no special cases.
+// Rows outside a workgroup's range, taps that fall into the zero padding and columns beyond the matrix lie outside the buffer, which reads as
+// zeros (fp32: are fetched from a 16-byte block of zeros), so the slab in LDS is always complete and the inner loop has no special cases.
 //
 // What bounds it and how it is cut.  A TW x TW tile moves 2 TW elements per row through the L1 (64 bytes per cycle and
 // CU) for TW^2 multiply-adds, so with 128-wide tiles the copies alone take as many cycles as the matrix cores: where there
@@ -22,8 +22,8 @@
 // 64-wide: 31 % and 20 %.  The rest is wavefronts waiting at the slabs' barriers and a tile's epilogue, beside which a 256-wide
 // workgroup has nothing else on its CU; at that load the clock falls to about 1.9 GHz.  All factors from NCHW: bf16 at batch 32
 // 2090 -> 1804 us with shared sums, 1515 with planes read as they lie, 1272 with both sides of a slab's work interleaved, work dealt evenly
-// to the XCDs and epilogues from 32-bit offsets; fp32 at batch 8 2555 -> 1974 -> 1766 -> 1600.  128-wide no registers live in
-// scratch memory (fp32 planes: 8), 256-wide 2 (planes: 9), all of them used outside the product loops.
+// to the XCDs and epilogues from 32-bit offsets; fp32 at batch 8 2555 -> 1974 -> 1766 -> 1600.  No registers live in scratch memory but 2 of
+// the 256-wide kernel without planes, used outside the product loops.
 //
 // The bias column is not part of the tiled matrix (2048 + 1 columns would cost a ninth row of 256-wide tiles for one
 // column): its row of the result is the column sums, which the wavefronts of a diagonal tile whose part lies above the

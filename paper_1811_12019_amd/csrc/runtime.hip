@@ -83,15 +83,18 @@ __global__ __launch_bounds__(256) void probe_mfma_kernel(float* __restrict__ out
     out[(size_t)blockIdx.x * 256 + threadIdx.x] = c0[0] + c1[1] + c2[2] + c3[3];
 }
 
-// Streaming copy / read of 16-byte vectors, grid-stride.
-__global__ __launch_bounds__(256) void probe_copy_kernel(const v4f* __restrict__ in, v4f* __restrict__ out, size_t n) {
+// Streaming copy / read of 16-byte vectors, grid-stride; past the caches where the library's own passes go past them (STREAM_BYTES).
+template <bool STREAM>
+__global__ __launch_bounds__(256) void probe_copy_kernel(const float* __restrict__ in, float* __restrict__ out, size_t n) {
     const size_t stride = (size_t)gridDim.x * 256;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) out[i] = in[i];
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride)
+        stream_store4<STREAM>(as_global(out) + 4 * i, stream_load4<STREAM>(as_global(in) + 4 * i));
 }
-__global__ __launch_bounds__(256) void probe_read_kernel(const v4f* __restrict__ in, float* __restrict__ out, size_t n) {
+template <bool STREAM>
+__global__ __launch_bounds__(256) void probe_read_kernel(const float* __restrict__ in, float* __restrict__ out, size_t n) {
     const size_t stride = (size_t)gridDim.x * 256;
     v4f s = {0.f, 0.f, 0.f, 0.f};
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) s += in[i];
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) s += stream_load4<STREAM>(as_global(in) + 4 * i);
     if (s.x + s.y + s.z + s.w == 12345.678f) out[0] = 1.f;      // (keeps the loads alive)
 }
 
@@ -111,15 +114,17 @@ extern "C" int kfac_probe_copy(const void* src, void* dst, size_t bytes, int32_t
     if (!src || bytes == 0 || (bytes & 15) || workgroups <= 0 || workgroups > (1 << 20)) return KFAC_ERR_INVALID_ARG;
     if (((uintptr_t)src | (uintptr_t)dst) & 15) return KFAC_ERR_INVALID_ARG;
     hipStream_t st = (hipStream_t)stream;
-    if (dst) hipLaunchKernelGGL(kfac::probe_copy_kernel, dim3(workgroups), dim3(256), 0, st, (const kfac::v4f*)src, (kfac::v4f*)dst, bytes / 16);
-    else return KFAC_ERR_INVALID_ARG;
+    if (!dst) return KFAC_ERR_INVALID_ARG;
+    hipLaunchKernelGGL(bytes * 2 > kfac::STREAM_BYTES ? kfac::probe_copy_kernel<true> : kfac::probe_copy_kernel<false>, dim3(workgroups), dim3(256), 0, st,
+                       (const float*)src, (float*)dst, bytes / 16);
     return hipGetLastError() == hipSuccess ? KFAC_OK : KFAC_ERR_HIP;
 }
 
 extern "C" int kfac_probe_read(const void* src, float* sink, size_t bytes, int32_t workgroups, void* stream) {
     if (!src || !sink || bytes == 0 || (bytes & 15) || ((uintptr_t)src & 15) || workgroups <= 0 || workgroups > (1 << 20))
         return KFAC_ERR_INVALID_ARG;
-    hipLaunchKernelGGL(kfac::probe_read_kernel, dim3(workgroups), dim3(256), 0, (hipStream_t)stream, (const kfac::v4f*)src, sink, bytes / 16);
+    hipLaunchKernelGGL(bytes > kfac::STREAM_BYTES ? kfac::probe_read_kernel<true> : kfac::probe_read_kernel<false>, dim3(workgroups), dim3(256), 0,
+                       (hipStream_t)stream, (const float*)src, sink, bytes / 16);
     return hipGetLastError() == hipSuccess ? KFAC_OK : KFAC_ERR_HIP;
 }
 

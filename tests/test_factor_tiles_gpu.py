@@ -1,6 +1,6 @@
 """Matrix-core factor builder at the sizes where it can go wrong: tile widths 64 / 128 / 256 and one column either side,
 padded channels, both column orders and layouts, every dtype, split and unsplit rows, every kind of output.  256-wide tiles are
-only taken in calls of much work (test_wide_tiles); the other tests run 64- and 128-wide ones."""
+taken by calls with workgroups and rows enough for them (takes_wide): test_wide_tiles makes such calls, the other tests' are too small."""
 import numpy as np
 import pytest
 import torch
@@ -120,8 +120,8 @@ WIDE_SHAPES = [
 @pytest.mark.parametrize("layout,dtype,order", [
     (NHWC, kb.KFAC_BF16, KKC), (NHWC, kb.KFAC_F16, CKK), (NCHW, kb.KFAC_BF16, CKK), (NCHW, kb.KFAC_F16, KKC)])
 def test_wide_tiles(layout, dtype, order):
-    """256-wide tiles, which the library takes for calls of 24,000 and more rows of 128 x 128 tiles to a workgroup slot with little
-    padding: 16 builds of 8,704 rows x 2,048 columns beside the shapes above make such a call.  Plain results against the oracle;
+    """256-wide tiles, which the library takes for calls with at least 150 workgroups of 1,900 rows on average and little padding: 16 builds of
+    8,704 rows x 2,048 columns beside the shapes above make such a call.  Plain results against the oracle;
     running average and packed triangle against the plain ones, bit for bit; nothing is written beyond the scratch that
     kfac_factor_workspace_bytes asks for."""
     def anchor_build():
