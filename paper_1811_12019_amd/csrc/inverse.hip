@@ -22,10 +22,10 @@
 //   * tiles of the rest of the matrix, which receive the updates of finished steps in one visit for a group of GM steps (Plan).
 // Every matrix of a batch carries its own stage, so that matrices with fewer blocks spread their launches over those of the
 // largest one.  The last step's panel is a launch, and one launch for the whole batch writes the outputs (inv_out_kernel).
-// Bound: one matrix alone by the look-ahead pivot's workgroup (its update 11.8 us, the sweep 15.3, write-out 1.9, from launch to
-// launch 2.5; half slabs are done after 13 to 25): 31 us a step, 40 when panel and tiles were launches of their own.  One matrix
-// alone, us, then and now: 145 columns 81 and 63, 1000 328 and 272, 2049 632 and 532, 4609 1501 and 1258; ten ragged ones (10 to 1153
-// columns) with their preconditioning 557 and 400.  Batches of wide matrices are bound by their tile visits.
+// Bound: one matrix alone by the look-ahead pivot's workgroup (its update 13 us, the sweep 10.8, write-out 1.9, from launch to
+// launch 1.7; half slabs are done after 12 to 23): 27 us a step, 31 with a sweep of 15.3, 40 when panel and tiles were launches of their
+// own.  One matrix alone, us, with the sweep of 15.3 and now: 145 columns 62 and 58, 1000 270 and 244, 2049 530 and 480, 4609 1236 and
+// 1158; ten ragged ones (10 to 1153 columns) with their preconditioning 393 and 370.  Batches of wide matrices are bound by their tile visits.
 // Products: the panel on the bf16 matrix cores with operands split three ways; the updates on the fp16 matrix cores
 // from operands that the panel launch has already scaled per half slab (64 rows) and split two ways, stored as planes that
 // go to LDS by DMA (gemm_split.h); both to fp32 accuracy.
@@ -192,17 +192,18 @@ __device__ __forceinline__ void store_block(gfloat* blk, const v16f& acc) {
 
 // ---- pivot block -----------------------------------------------------------------------------------------------
 // Inverse of the (at most 128 x 128) pivot block by a symmetric sweep in 16-wide sub-blocks.  The lower triangle of the
-// block D lives in registers in MFMA accumulator layout (wavefronts 0, 2, 3: the 64 x 64 quadrants on and below the
-// diagonal, as whole 32 x 32 blocks); wavefront 1, whose quadrant lies above the diagonal, looks ahead: it inverts the next
-// 16 x 16 diagonal sub-block while the others update D.  Per sub-block j:
-//   * wavefronts 0, 2, 3: T16 = U16 . P16 (U16 = D's columns j, in LDS; the rows of the sub-block itself become -P16); then
-//     D -= T16 . U16^T on the matrix cores, columns / rows j of D become T16, and the owners copy
-//     columns / rows j + 1 and diagonal sub-block j + 2 to LDS for the next round;
+// block D lives in registers as 16 x 16 blocks in MFMA accumulator layout (lane l holds rows 4 (l / 16) + i of column l % 16), three
+// wavefronts owning whole block rows (PIV_ROW), which deals the products out evenly; wavefront 1 looks ahead: it inverts the next
+// 16 x 16 diagonal sub-block while the others update D.  Per sub-block j, one barrier:
+//   * wavefronts 0, 2, 3: T16 = U16 . P16 for their own rows (U16 = D's columns j, in LDS) and, straight from these registers,
+//     D -= T16 . U16^T on the matrix cores; columns / rows j of D become T16, the sub-block itself -P16 (row j, which needs other
+//     wavefronts' T16, a round later); columns / rows j + 1 and diagonal sub-block j + 2 go to LDS for the next round;
 //   * wavefront 1: takes sub-block j + 1, which the round before left in LDS, through this round's update, with a T16 of its own,
 //     and inverts it.
 // Padding with the identity makes ragged blocks (fewer than 128 rows) need no special cases.
-// One workgroup, bound by its chain of dependent steps: 1.75 us a sub-block, of which wavefront 2, with four 32 x 32 blocks to
-// update, takes 1.2 for them (v_mfma_f32_32x32x2_f32), and wavefront 1 takes 1.4 in all.
+// One workgroup, bound by its chain of dependent steps: 3,100 cycles a sub-block, the time of wavefront 1, of which the inversion is
+// 2,450; the owners are done after 1,300 to 3,000.  4,100 with 32 x 32 blocks in quadrants (one wavefront had 16 of 40 to update), two
+// barriers and a rank-1 update per elimination; a loop over the sub-blocks that is not unrolled takes 4,100 too (branches, copies).
 constexpr int PSB = 16;          // sub-block
 constexpr int PLD = 20;          // LDS row stride of the 16-wide panels (float4 aligned)
 
@@ -220,53 +221,75 @@ __device__ __forceinline__ float group_bcast(float x) {
     return __uint_as_float(b[G & 1]);
 }
 
-// One elimination step of invert16_wave.  With r = 1 / sqrt(p) and u = r E(., S) the rank-1 update is -u u^T, the same
-// product on both sides of the diagonal: E stays symmetric to the last bit, so that row S may stand for column S.  (Rows and
-// columns that drift apart by rounding cost an ill-conditioned block most of its accuracy.)
+__device__ __forceinline__ float rsqrt_newton(float p) {
+    const float r = __builtin_amdgcn_rsqf(p);              // 1 ulp estimate + one Newton step
+    return fmaf(0.5f * r, fmaf(-p * r, r, 1.0f), r);
+}
+
+// Four elimination steps of invert16_wave, columns 4 S .. + 3.  With L the Cholesky factor of the 4 x 4 pivot block (formed by all lanes
+// alike) and W = V L^-T, V being the four columns with minus the identity in the pivot rows, all that the sweep does is E - W W^T,
+// where E counts as zero in the pivot rows and columns: -V P V^T beside them, V P and P V^T in them, -P where they cross.  One
+// matrix-core product, and the same bits on both sides of the diagonal: E stays symmetric.  (Rows and columns that drift apart by
+// rounding cost an ill-conditioned block most of its accuracy.)
 template <int S>
-__device__ __forceinline__ void invert16_step(float (&E)[4], int i, int g, float (&piv)[16]) {
-    constexpr int gs = S >> 2, qs = S & 3;
-    const float vi = group_bcast<gs>(E[qs]);               // E(i, S)
-    const float p = row_bcast<S>(vi);                      // E(S, S)
-    piv[S] = p;
-    float r = __builtin_amdgcn_rsqf(p);                    // 1 ulp estimate + one Newton step
-    r = fmaf(0.5f * r, fmaf(-p * r, r, 1.0f), r);
-    const bool prow = i == S;
-    const float u = vi * r, m = prow ? r : -u;             // row S becomes u r, the others lose u times it
+__device__ __forceinline__ void invert16_step4(v4f& E, int i, int g, const float (&unit)[4], float (&piv)[16]) {
+    float v[4], u[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) E[q] = fmaf(row_bcast<S>(E[q]) * r, m, prow ? 0.f : E[q]);
-    float col = -m * r;                                    // -1 / p in row S, u r in the others
-    asm("" : "+v"(col));                                   // (a value, not an expression: the compiler would branch around it)
-    E[qs] = g == gs ? col : E[qs];
+    for (int q = 0; q < 4; ++q) v[q] = group_bcast<S>(E[q]);          // E(i, 4 S + q)
+    const float a00 = row_bcast<4 * S>(v[0]);
+    float a10 = row_bcast<4 * S + 1>(v[0]), a20 = row_bcast<4 * S + 2>(v[0]), a30 = row_bcast<4 * S + 3>(v[0]);
+    float a11 = row_bcast<4 * S + 1>(v[1]), a21 = row_bcast<4 * S + 2>(v[1]), a31 = row_bcast<4 * S + 3>(v[1]);
+    float a22 = row_bcast<4 * S + 2>(v[2]), a32 = row_bcast<4 * S + 3>(v[2]), a33 = row_bcast<4 * S + 3>(v[3]);
+    const bool prow = (i >> 2) == S;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = prow ? unit[q] : v[q];
+    const float r0 = rsqrt_newton(a00);
+    a10 *= r0; a20 *= r0; a30 *= r0;
+    a11 = fmaf(-a10, a10, a11); a21 = fmaf(-a20, a10, a21); a31 = fmaf(-a30, a10, a31);
+    a22 = fmaf(-a20, a20, a22); a32 = fmaf(-a30, a20, a32); a33 = fmaf(-a30, a30, a33);
+    u[0] = v[0] * r0;
+    const float r1 = rsqrt_newton(a11);
+    a21 *= r1; a31 *= r1;
+    a22 = fmaf(-a21, a21, a22); a32 = fmaf(-a31, a21, a32); a33 = fmaf(-a31, a31, a33);
+    u[1] = fmaf(-a10, u[0], v[1]) * r1;
+    const float r2 = rsqrt_newton(a22);
+    a32 *= r2;
+    a33 = fmaf(-a32, a32, a33);
+    u[2] = fmaf(-a21, u[1], fmaf(-a20, u[0], v[2])) * r2;
+    const float r3 = rsqrt_newton(a33);
+    u[3] = fmaf(-a32, u[2], fmaf(-a31, u[1], fmaf(-a30, u[0], v[3]))) * r3;
+    piv[4 * S] = a00; piv[4 * S + 1] = a11; piv[4 * S + 2] = a22; piv[4 * S + 3] = a33;
+    const float lo = (g & 1) ? u[1] : u[0], hi = (g & 1) ? u[3] : u[2], w = (g & 2) ? hi : lo;
+    const bool zero = prow || g == S;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) E[q] = zero ? 0.f : E[q];
+    E = __builtin_amdgcn_mfma_f32_16x16x4f32(-w, w, E, 0, 0, 0);
 }
 
 // One wavefront: Ps = inverse of the symmetric positive definite 16 x 16 block whose element (i, 4 g + q) lane
-// (i = lane % 16, g = lane / 16) holds in E[q], lower triangle taken as the truth; E becomes minus the inverse.  Returns the 1-based
-// index of the first non-positive pivot, or 0.  A step is about 30 instructions, none of them through LDS.  midway(): called
-// after a few steps.
-template <class F>
-__device__ __forceinline__ int invert16_wave(float (&E)[4], float* __restrict__ Ps, F&& midway) {
+// (i = lane % 16, g = lane / 16) holds in E[q] (of two that mirror each other the lower one counts); E becomes minus the inverse.
+// Returns the 1-based index of the first non-positive pivot, or 0.  Nothing goes through LDS on the way.
+__device__ __forceinline__ int invert16_wave(v4f& E, float* __restrict__ Ps) {
     const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
-    float piv[16];
-    *(v4f*)&Ps[i * PLD + 4 * g] = v4f{E[0], E[1], E[2], E[3]};
+    float piv[16], unit[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) E[q] = Ps[max(i, 4 * g + q) * PLD + min(i, 4 * g + q)];
-    invert16_step<0>(E, i, g, piv);  invert16_step<1>(E, i, g, piv);  invert16_step<2>(E, i, g, piv);  invert16_step<3>(E, i, g, piv);
-    midway();
-    invert16_step<4>(E, i, g, piv);  invert16_step<5>(E, i, g, piv);  invert16_step<6>(E, i, g, piv);  invert16_step<7>(E, i, g, piv);
-    invert16_step<8>(E, i, g, piv);  invert16_step<9>(E, i, g, piv);  invert16_step<10>(E, i, g, piv); invert16_step<11>(E, i, g, piv);
-    invert16_step<12>(E, i, g, piv); invert16_step<13>(E, i, g, piv); invert16_step<14>(E, i, g, piv); invert16_step<15>(E, i, g, piv);
-    *(v4f*)&Ps[i * PLD + 4 * g] = v4f{-E[0], -E[1], -E[2], -E[3]};
+    for (int q = 0; q < 4; ++q) unit[q] = (i & 3) == q ? -1.f : 0.f;
+    invert16_step4<0>(E, i, g, unit, piv);
+    invert16_step4<1>(E, i, g, unit, piv);
+    invert16_step4<2>(E, i, g, unit, piv);
+    invert16_step4<3>(E, i, g, unit, piv);
+    *(v4f*)&Ps[i * PLD + 4 * g] = -E;
+    if (piv[15] > 0.f) return 0;                           // (a pivot that is not positive makes all later ones NaN)
     int bad = 0;
 #pragma unroll
     for (int s = 15; s >= 0; --s) bad = piv[s] > 0.f ? bad : s + 1;
     return bad;
 }
 
-// LDS of the pivot code: the sweep's panels (U16 and P16 of two sub-blocks, T16, two diagonal sub-blocks); before and after
+// LDS of the pivot code: the sweep's panels (U16, T16, P16 and a diagonal sub-block, of two rounds each); before and after
 // it, in the same memory, the block's packed lower triangle (row r holds columns 0..r).
 constexpr int TRI_FLOATS = NB * (NB + 1) / 2;
-constexpr int PIV_US = 0, PIV_TS = 2 * NB * PLD, PIV_PS = 3 * NB * PLD, PIV_DG = PIV_PS + 2 * PSB * PLD,
+constexpr int PIV_US = 0, PIV_TS = 2 * NB * PLD, PIV_PS = 4 * NB * PLD, PIV_DG = PIV_PS + 2 * PSB * PLD,
               PIV_BAD = PIV_DG + 2 * PSB * PSB;
 constexpr int PIV_LDS_FLOATS = PIV_BAD + 4;
 static_assert(TRI_FLOATS <= PIV_LDS_FLOATS, "one buffer serves both uses");
@@ -274,238 +297,228 @@ static_assert(TRI_FLOATS <= PIV_LDS_FLOATS, "one buffer serves both uses");
 __device__ __forceinline__ int tri_at(int r, int c) { return ((r * (r + 1)) >> 1) + c; }          // r >= c
 __device__ __forceinline__ int tri_sym(int r, int c) { return r >= c ? tri_at(r, c) : tri_at(c, r); }
 
-// identity beyond nb
-__device__ __forceinline__ void pivot_border(v16f (&acc)[2][2], int nb) {
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = acc_row(wm, mb, r, lane), col = acc_col(wn, nbk, lane);
-                if (!(row < nb && col < nb)) acc[mb][nbk][r] = row == col ? 1.f : 0.f;
-            }
-}
+// Block rows of the three owners (wavefronts 0, 2, 3): 7 4 / 6 3 0 / 5 2 1, which are 13, 12 and 11 blocks to update and 2, 3 and 3 of
+// T16 to form: 15, 15 and 14 products of 16 x 16 x 16.  (Quadrants of 32 x 32 blocks left one wavefront with 16 of 40.)
+constexpr int PIV_BLOCKS = 13;
+constexpr int piv_rows(int role) { return role == 0 ? 2 : 3; }
+constexpr int piv_row(int role, int x) { return x == 0 ? 7 - role : x == 1 ? 4 - role : role - 1; }
+constexpr int piv_slot(int role, int x) { return x == 0 ? 0 : piv_slot(role, x - 1) + piv_row(role, x - 1) + 1; }
+static_assert(piv_slot(0, 2) == 13 && piv_slot(1, 3) == 12 && piv_slot(2, 3) == 11, "all 36 blocks, no more than a wavefront holds");
+typedef v4f PivotBlocks[PIV_BLOCKS];
 
-// T16 = U16 . P16 for row blocks rb0 .. rb0 + N - 1 (below 8): formed as its transpose P16 . U16^T with v_mfma_f32_16x16x4_f32 (lane l
-// supplies A[l % 16][l / 16] and B[l / 16][l % 16] and receives C[4 (l / 16) + i][l % 16], i < 4), the contraction index in the order
-// 4 (l / 16) + kk, so that operands and result are four neighbours of one row; the rows of sub-block jb itself become -P16.
-template <int N>
-__device__ __forceinline__ void sweep_panel(const float* __restrict__ Us, const float* __restrict__ Ps, float* __restrict__ Ts,
-                                            int lane, int rb0, int jb) {
-    const int l16 = lane & 15, lq = lane >> 4;
-    const v4f p = *(const v4f*)&Ps[l16 * PLD + 4 * lq];
-    v4f u[N], c[N];
-#pragma unroll
-    for (int e = 0; e < N; ++e) {
-        u[e] = *(const v4f*)&Us[((rb0 + e) * PSB + l16) * PLD + 4 * lq];
-        c[e] = v4f{0.f, 0.f, 0.f, 0.f};
+#define KFAC_INLINE __attribute__((always_inline))
+template <int V> struct Int { static constexpr int value = V; constexpr operator int() const { return V; } };
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {                      // f(Int<0>()), ..: registers want constant indices
+    if constexpr (N > 0) {
+        static_for<N - 1>(f);
+        f(Int<N - 1>());
     }
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-        for (int e = 0; e < N; ++e) c[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[kk], u[e][kk], c[e], 0, 0, 0);
-#pragma unroll
-    for (int e = 0; e < N; ++e) *(v4f*)&Ts[((rb0 + e) * PSB + l16) * PLD + 4 * lq] = rb0 + e == jb ? -p : c[e];
+}
+template <class F>
+__device__ __forceinline__ void with_role(int wave, F&& f) {             // wave: uniform; nothing for wavefront 1
+    if (wave == 0) f(Int<0>());
+    else if (wave == 2) f(Int<1>());
+    else if (wave == 3) f(Int<2>());
+}
+// f(block row, block column, the block) for every block of the wavefront (row and column: uniform values, so that all owners share the
+// code and a register has the same index in it)
+template <class F>
+__device__ __forceinline__ void each_block(int wave, PivotBlocks& D, F&& f) {
+    if (wave == 1) return;
+    const int role = max(0, wave - 1), r0 = 7 - role, r1 = 4 - role, r2 = role - 1;      // (piv_row)
+    static_for<PIV_BLOCKS>([&](auto slot) KFAC_INLINE {
+        const int s1 = slot - (r0 + 1), s2 = s1 - (r1 + 1);
+        const int r = s1 < 0 ? r0 : s2 < 0 ? r1 : r2, c = s1 < 0 ? slot : s2 < 0 ? s1 : s2;
+        if (slot < 11 || c <= r) f(r, c, D[slot]);
+    });
+}
+// Where a lane's four values of 16 x 16 block (r, c) lie in the 32 x 32 block (r / 2, c / 2) in register order (WsView::tile).
+__device__ __forceinline__ int sub_block_at(int r, int c, int lane) {
+    return (2 * (r & 1) + (lane >> 5)) * 256 + (((lane >> 4) & 1) * 32 + (c & 1) * 16 + (lane & 15)) * 4;
 }
 
-// Between the phases of the sweep: everybody's LDS accesses are done.
+// identity beyond nb
+__device__ __forceinline__ void pivot_border(PivotBlocks& D, int wave, int nb) {
+    const int lane = threadIdx.x & 63;
+    each_block(wave, D, [&](int r, int c, v4f& b) KFAC_INLINE {
+        const int col = c * PSB + (lane & 15), row = r * PSB + 4 * (lane >> 4);
+        auto at = [&](int i, float x) KFAC_INLINE { return row + i < nb && col < nb ? x : row + i == col ? 1.f : 0.f; };
+        b = v4f{at(0, b.x), at(1, b.y), at(2, b.z), at(3, b.w)};
+    });
+}
+
+// Between the rounds of the sweep: everybody's LDS accesses are done.
 __device__ __forceinline__ void sweep_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// U16 of sub-block jb: D's columns 16 jb .. + 15, rows above the 32 x 32 diagonal block from D's rows (transposed).
-__device__ __forceinline__ void sweep_publish(const v16f (&acc)[2][2], int lane, int wm, int wn, int jb, float* __restrict__ Us) {
-    const int lm = lane & 31, h = lane >> 5;
-    const int ow = jb >> 2, ob = (jb >> 1) & 1, oh = jb & 1;   // wavefront row / column, block inside it, half of the block
-    if (wn == ow && wm >= ow && (lm >> 4) == oh) {
+// An owner's part of the sweep.  What the next round needs (columns / rows j + 1, the "strip", and diagonal sub-block j + 2) is brought
+// up to date first and handed over; the other blocks follow after the barrier, beside the next round's reads and the inversion of
+// wavefront 1, which sets the pace.
+template <int RL>
+__device__ __forceinline__ void sweep_rows(PivotBlocks& blocks, int nsb, float* __restrict__ lds) {
+    PivotBlocks D;                                         // (a copy: the compiler would let the owners' branches share accesses, by address)
+    static_for<PIV_BLOCKS>([&](auto s) KFAC_INLINE { D[s] = blocks[s]; });
+    constexpr int NR = piv_rows(RL), LAST = piv_row(RL, 0);              // (the first row is the longest)
+    const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+    float* __restrict__ nat = lds + l16 * PLD + 4 * lq;                  // (l16, 4 lq ..) and (4 lq .., l16) of a panel's 16-row block
+    float* __restrict__ turned = lds + 4 * lq * PLD + l16;
+    float* __restrict__ diag = lds + PIV_DG + lane * 4;
+    constexpr int ROWS = PSB * PLD, PANEL = NB * PLD;
+    auto put_turned = [&](int at, const v4f& x) KFAC_INLINE {
+        turned[at] = x.x; turned[at + PLD] = x.y; turned[at + 2 * PLD] = x.z; turned[at + 3 * PLD] = x.w;
+    };
+    v4f T[NR], u[LAST + 1], own[NR], p;
+    auto update = [&](auto x, auto c) KFAC_INLINE {        // one 16 x 16 block (T: negated)
+        constexpr int at = piv_slot(RL, x) + c, cc = c;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-            if (wm > ow || mb >= ob) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) Us[acc_row(wm, mb, r, lane) * PLD + (lm & 15)] = acc[mb][ob][r];
-            }
-    }
-    if (wm == ow && wn <= ow) {
-#pragma unroll
-        for (int nbk = 0; nbk < 2; ++nbk)
-            if (wn < ow || nbk < ob) {
-#pragma unroll
-                for (int r8 = 0; r8 < 8; r8 += 4) {            // four consecutive rows of D: one 16-byte store
-                    const v4f x = {acc[ob][nbk][oh * 8 + r8], acc[ob][nbk][oh * 8 + r8 + 1], acc[ob][nbk][oh * 8 + r8 + 2], acc[ob][nbk][oh * 8 + r8 + 3]};
-                    *(v4f*)&Us[acc_col(wn, nbk, lane) * PLD + (r8 >> 2) * 8 + h * 4] = x;
-                }
-            }
-    }
-}
-
-// Diagonal sub-block jb, as v_mfma_f32_16x16x4_f32 would leave it: float 4 lane + i is row 4 (lane / 16) + i, column lane % 16.
-__device__ __forceinline__ void sweep_publish_diagonal(const v16f (&acc)[2][2], int lane, int wm, int wn, int jb, float* __restrict__ DG) {
-    const int lm = lane & 31, h = lane >> 5;
-    const int ob = (jb >> 1) & 1, oh = jb & 1;
-    if (wm == (jb >> 2) && wn == wm && (lm >> 4) == oh) {
-#pragma unroll
-        for (int r8 = 0; r8 < 8; r8 += 4) {
-            const int r = oh * 8 + r8;
-            const v4f x = {acc[ob][ob][r], acc[ob][ob][r + 1], acc[ob][ob][r + 2], acc[ob][ob][r + 3]};
-            *(v4f*)&DG[(((r8 >> 2) * 2 + h) * 16 + (lm & 15)) * 4] = x;
+        for (int kk = 0; kk < 4; ++kk) D[at] = __builtin_amdgcn_mfma_f32_16x16x4f32(T[x][kk], u[cc][kk], D[at], 0, 0, 0);
+    };
+    static_for<NR>([&](auto x) KFAC_INLINE {
+        constexpr int r = piv_row(RL, x), at = piv_slot(RL, x);
+        if constexpr (r > 0) put_turned(PIV_US + r * ROWS, D[at]);
+        if constexpr (r < 2) *(v4f*)&diag[r * (PSB * PSB)] = D[at + r];
+    });
+    sweep_barrier();
+    sweep_barrier();                                       // wavefront 1 has inverted the first diagonal sub-block
+    static_for<NB / PSB + 1>([&](auto round) KFAC_INLINE {
+        constexpr int j = round, US = PIV_US + (j & 1) * PANEL, TS = PIV_TS + (j & 1) * PANEL, USN = PIV_US + (~j & 1) * PANEL;
+        if (j < nsb) {                                     // (uniform)
+            p = *(const v4f*)&nat[PIV_PS + (j & 1) * ROWS];
+            static_for<NR>([&](auto x) KFAC_INLINE { own[x] = *(const v4f*)&nat[US + piv_row(RL, x) * ROWS]; });
         }
-    }
+        if constexpr (j > 0) {
+            if (j - 1 < nsb) {                             // the rest of the round before
+                constexpr int k = j - 1, TSK = PIV_TS + (k & 1) * PANEL;
+                static_for<NR>([&](auto x) KFAC_INLINE {
+                    constexpr int r = piv_row(RL, x), at = piv_slot(RL, x);
+                    if constexpr (r == k) {                // row k <- T16^T
+                        static_for<r>([&](auto c) KFAC_INLINE { D[at + c] = *(const v4f*)&nat[TSK + c * ROWS]; });
+                    } else if constexpr (r > k) {          // column k <- T16
+                        const float* from = &turned[TSK + r * ROWS];
+                        D[at + k] = v4f{from[0], from[PLD], from[2 * PLD], from[3 * PLD]};
+                    }
+                });
+                static_for<NR>([&](auto x) KFAC_INLINE {
+                    constexpr int r = piv_row(RL, x);
+                    static_for<r + 1>([&](auto c) KFAC_INLINE {
+                        if constexpr (r != k && r != j && c != k && c != j && !(c == r && r == k + 2)) update(x, c);
+                    });
+                });
+            }
+        }
+        if (j < nsb) {
+            if constexpr (j < NB / PSB) {
+                static_for<LAST + 1>([&](auto c) KFAC_INLINE { u[c] = *(const v4f*)&nat[US + c * ROWS]; });
+                // T16 as its transpose P16 . U16^T with v_mfma_f32_16x16x4_f32 (lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]
+                // and receives C[4 (l / 16) + i][l % 16], i < 4), the contraction index in the order 4 (l / 16) + kk, so that operands
+                // and result are four neighbours of one row: the result is the update's operand.
+                static_for<NR>([&](auto x) KFAC_INLINE { T[x] = v4f{0.f, 0.f, 0.f, 0.f}; });
+                static_for<4>([&](auto kk) KFAC_INLINE {
+                    static_for<NR>([&](auto x) KFAC_INLINE {
+                        if constexpr (piv_row(RL, x) != j) T[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[(int)kk], own[x][(int)kk], T[x], 0, 0, 0);
+                    });
+                });
+                static_for<NR>([&](auto x) KFAC_INLINE {
+                    constexpr int r = piv_row(RL, x), at = piv_slot(RL, x);
+                    if constexpr (r == j) {
+                        D[at + r] = -p;
+                    } else {
+                        *(v4f*)&nat[TS + r * ROWS] = T[x];
+                        if constexpr (r == j + 1) put_turned(USN + j * ROWS, T[x]);      // (block (j + 1, j) of the strip)
+                        T[x] = -T[x];
+                    }
+                });
+                // the strip: blocks (r, j + 1), r > j + 1, and (j + 1, c), c < j; the diagonal sub-block j + 2.  (The one of j + 1 is
+                // wavefront 1's: here it is not needed any more.)
+                static_for<NR>([&](auto x) KFAC_INLINE {
+                    constexpr int r = piv_row(RL, x);
+                    if constexpr (r > j + 1) {
+                        update(x, Int<j + 1>());
+                        if constexpr (r == j + 2) update(x, Int<r>());
+                    } else if constexpr (r == j + 1) {
+                        static_for<j>([&](auto c) KFAC_INLINE { update(x, c); });
+                    }
+                });
+                static_for<NR>([&](auto x) KFAC_INLINE {
+                    constexpr int r = piv_row(RL, x), at = piv_slot(RL, x);
+                    if constexpr (r > j + 1) {
+                        put_turned(USN + r * ROWS, D[at + j + 1]);
+                        if constexpr (r == j + 2) *(v4f*)&diag[(r & 1) * (PSB * PSB)] = D[at + r];
+                    } else if constexpr (r == j + 1) {
+                        static_for<j>([&](auto c) KFAC_INLINE { *(v4f*)&nat[USN + c * ROWS] = D[at + c]; });
+                    }
+                });
+                sweep_barrier();
+            }
+        }
+    });
+    static_for<PIV_BLOCKS>([&](auto s) KFAC_INLINE { blocks[s] = D[s]; });
 }
 
 // The symmetric sweep of D in 16-wide sub-blocks (see above); lds: PIV_LDS_FLOATS floats, free on entry.  Returns (to every
 // thread) the 1-based index inside the block of the first non-positive pivot, or 0.  Ends with a barrier.
-// Of acc, the 32 x 32 blocks on and below the diagonal are used and valid afterwards.
-__device__ __forceinline__ int pivot_sweep(v16f (&acc)[2][2], int nb, float* __restrict__ lds) {
-    float* __restrict__ Ts = lds + PIV_TS;
-    float* __restrict__ DG = lds + PIV_DG;
+__device__ __forceinline__ int pivot_sweep(PivotBlocks& D, int wave, int nb, float* __restrict__ lds) {
     int* bad = (int*)(lds + PIV_BAD);
-    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1;
     const int nsb = (nb + PSB - 1) / PSB;
     if (wave == 1) {
-        const int lane = t & 63, l16 = lane & 15, lq = lane >> 4;
+        const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
         sweep_barrier();                                       // the first U16 and the diagonal sub-blocks are there
-        float E[4];
-        {
-            const v4f c4 = *(const v4f*)&DG[lane * 4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) E[i] = c4[i];
-        }
-        int first_bad = invert16_wave(E, lds + PIV_PS, [] {});
+        v4f E = *(const v4f*)&lds[PIV_DG + lane * 4];
+        int first_bad = invert16_wave(E, lds + PIV_PS);
         sweep_barrier();
 #pragma unroll 1
-        for (int jb = 0; jb < nsb; ++jb) {
-            const int n = jb + 1;
-            if (n < nsb) {                                     // diagonal sub-block n -= T16 . U16^T, and its inverse
-                // (E: minus the inverse of sub-block jb; T16 as in sweep_panel, for these 16 rows, stays in registers)
-                const v4f u = *(const v4f*)&lds[PIV_US + (jb & 1) * (NB * PLD) + (n * PSB + l16) * PLD + 4 * lq];
-                v4f c4 = *(const v4f*)&DG[(n & 1) * (PSB * PSB) + lane * 4], tt = {0.f, 0.f, 0.f, 0.f};
+        for (int n = 1; n < nsb; ++n) {                        // diagonal sub-block n -= T16 . U16^T, and its inverse
+            // (E: minus the inverse of the sub-block before; T16 as in sweep_rows, for these 16 rows, stays in registers)
+            const v4f u = *(const v4f*)&lds[PIV_US + ((n - 1) & 1) * (NB * PLD) + (n * PSB + l16) * PLD + 4 * lq];
+            v4f c4 = *(const v4f*)&lds[PIV_DG + (n & 1) * (PSB * PSB) + lane * 4], tt = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) tt = __builtin_amdgcn_mfma_f32_16x16x4f32(E[kk], u[kk], tt, 0, 0, 0);
+            for (int kk = 0; kk < 4; ++kk) tt = __builtin_amdgcn_mfma_f32_16x16x4f32(E[kk], u[kk], tt, 0, 0, 0);
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) c4 = __builtin_amdgcn_mfma_f32_16x16x4f32(tt[kk], u[kk], c4, 0, 0, 0);
-                // the accumulator layout holds (row 4 lq + i, column l16): by symmetry element (l16, 4 lq + i)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) E[i] = c4[i];
-                const int f = invert16_wave(E, lds + PIV_PS + (n & 1) * (PSB * PLD), [] { sweep_barrier(); });
-                first_bad = f != 0 && first_bad == 0 ? n * PSB + f : first_bad;
-            } else {
-                sweep_barrier();
-            }
-            if (jb + 1 == nsb && lane == 0) *bad = first_bad;
+            for (int kk = 0; kk < 4; ++kk) c4 = __builtin_amdgcn_mfma_f32_16x16x4f32(tt[kk], u[kk], c4, 0, 0, 0);
+            // the accumulator layout holds (row 4 lq + i, column l16): by symmetry element (l16, 4 lq + i)
+            E = c4;
+            const int f = invert16_wave(E, lds + PIV_PS + (n & 1) * (PSB * PLD));
+            first_bad = f != 0 && first_bad == 0 ? n * PSB + f : first_bad;
             sweep_barrier();
         }
-    } else {
-        int lane = t & 63;
-        sweep_publish(acc, lane, wm, wn, 0, lds + PIV_US);
-        sweep_publish_diagonal(acc, lane, wm, wn, 0, DG);
-        sweep_publish_diagonal(acc, lane, wm, wn, 1, DG + PSB * PSB);
+        if (lane == 0) *bad = first_bad;
         sweep_barrier();
-        sweep_barrier();                                       // wavefront 1 has inverted the first diagonal sub-block
-#pragma unroll
-        for (int jb = 0; jb < NB / PSB; ++jb) {
-            if (jb >= nsb) break;                              // uniform
-            // Addresses are worked out anew for each sub-block: kept over the unrolled loop they would not fit beside D, and
-            // every phase would begin by waiting for one from scratch memory.
-            asm volatile("" : "+v"(lane));
-            const int lm = lane & 31, h = lane >> 5;
-            const float* Us = lds + PIV_US + (jb & 1) * (NB * PLD);
-            const float* Ps = lds + PIV_PS + (jb & 1) * (PSB * PLD);
-            if (wave == 0) sweep_panel<3>(Us, Ps, Ts, lane, 0, jb);
-            else if (wave == 2) sweep_panel<2>(Us, Ps, Ts, lane, 3, jb);     // (has a block more in the update)
-            else sweep_panel<3>(Us, Ps, Ts, lane, 5, jb);
-            sweep_barrier();
-            // D -= T16 . U16^T  (lane (lm, h) takes k = 8s + 4h .. +3 of both operands), then the fix-ups
-#pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2) {
-                v4f a[2], bb[2];
-#pragma unroll
-                for (int mb = 0; mb < 2; ++mb) a[mb] = *(const v4f*)&Ts[(wm * 64 + mb * 32 + lm) * PLD + 8 * s2 + 4 * h];
-#pragma unroll
-                for (int nbk = 0; nbk < 2; ++nbk) bb[nbk] = *(const v4f*)&Us[(wn * 64 + nbk * 32 + lm) * PLD + 8 * s2 + 4 * h];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-#pragma unroll
-                    for (int mb = 0; mb < 2; ++mb)
-                        acc[mb][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(-a[mb][i], bb[0][i], acc[mb][0], 0, 0, 0);
-                    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(-a[1][i], bb[1][i], acc[1][1], 0, 0, 0);
-                }
-                if (wm != wn) {                                // (uniform: the quadrant below the diagonal has four blocks)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(-a[0][i], bb[1][i], acc[0][1], 0, 0, 0);
-                }
-            }
-            const int ow = jb >> 2, ob = (jb >> 1) & 1, oh = jb & 1;
-            // columns j of D <- T16 (and -P16 on the sub-block's own rows)
-            if (wn == ow && wm >= ow && (lm >> 4) == oh) {
-#pragma unroll
-                for (int mb = 0; mb < 2; ++mb)
-                    if (wm > ow || mb >= ob) {
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[mb][ob][r] = Ts[acc_row(wm, mb, r, lane) * PLD + (lm & 15)];
-                    }
-            }
-            // rows j of D <- T16^T
-            if (wm == ow && wn <= ow) {
-#pragma unroll
-                for (int nbk = 0; nbk < 2; ++nbk)
-                    if (wn < ow || nbk <= ob) {
-#pragma unroll
-                        for (int r8 = 0; r8 < 8; r8 += 4) {
-                            const v4f x = *(const v4f*)&Ts[acc_col(wn, nbk, lane) * PLD + (r8 >> 2) * 8 + h * 4];
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) acc[ob][nbk][oh * 8 + r8 + i] = x[i];
-                        }
-                    }
-            }
-            if (jb + 1 < NB / PSB) sweep_publish(acc, lane, wm, wn, jb + 1, lds + PIV_US + ((jb + 1) & 1) * (NB * PLD));
-            if (jb + 2 < NB / PSB) sweep_publish_diagonal(acc, lane, wm, wn, jb + 2, DG + (jb & 1) * (PSB * PSB));
-            sweep_barrier();
-        }
+    } else {
+        with_role(wave, [&](auto role) KFAC_INLINE { sweep_rows<role>(D, nsb, lds); });
     }
     const int f = *bad;
-    sweep_barrier();                                           // everybody has read the flag: the memory may be reused
+    sweep_barrier();                                           // everybody has read what there is to read: the memory may be reused
     return f;
 }
 
-// D holds -P up to rounding asymmetry in its lower 32 x 32 blocks.  The working copy gets -P; on the matrix's last step the
+// D holds -P up to rounding asymmetry on and below the diagonal.  The working copy gets -P; on the matrix's last step the
 // caller's output gets +P (the final sign flip; lower triangle taken as the truth, so that it is exactly symmetric) instead.
 // The workspace gets +P for the panel product, all of it.
-__device__ __forceinline__ void pivot_write(const v16f (&acc)[2][2], float* __restrict__ tri, const Item& it,
+__device__ __forceinline__ void pivot_write(PivotBlocks& D, int wave, float* __restrict__ tri, const Item& it,
                                             const WsView& ws, int k0, int nb, bool last, bool from_S) {
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+    const int t = threadIdx.x, lane = t & 63, l16 = lane & 15, lq = lane >> 4;
     const int d = it.dim;
     gfloat* P = ws.P(k0 / NB);
     if (!last) {                                           // (then the block is full)
-        // A full block inside the sweep (the look-ahead pivot's usual case) goes out as it lies in the registers: a half-wave's
-        // 32 lanes hold 32 consecutive floats of a row, and four registers four consecutive floats of the mirror image's.
-        if (wave == 1) return;
+        // A full block inside the sweep (the look-ahead pivot's usual case) goes out as it lies in the registers: 16 lanes hold 16
+        // consecutive floats of a row, and a lane four consecutive floats of the mirror image's.
+        gfloat* tile = ws.tile(k0 / NB, k0 / NB);
+        each_block(wave, D, [&](int r, int c, const v4f& b) KFAC_INLINE {
+            *(KFAC_AS1 v4f*)(tile_block(tile, r >> 1, c >> 1) + sub_block_at(r, c, lane)) = b;
+            *(KFAC_AS1 v4f*)&P[(c * PSB + l16) * NB + r * PSB + 4 * lq] = -b;
+            if (r == c) return;                            // a block on the diagonal is its own mirror image
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk) {
-                if (wm == wn && nbk > mb) continue;            // above the diagonal: not kept
-                store_block(tile_block(ws.tile(k0 / NB, k0 / NB), 2 * wm + mb, 2 * wn + nbk), acc[mb][nbk]);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) P[acc_row(wm, mb, r, lane) * NB + acc_col(wn, nbk, lane)] = -acc[mb][nbk][r];
-                if (wm == wn && nbk == mb) continue;           // a block on the diagonal is its own mirror image
-#pragma unroll
-                for (int r = 0; r < 16; r += 4) {
-                    const v4f x = {-acc[mb][nbk][r], -acc[mb][nbk][r + 1], -acc[mb][nbk][r + 2], -acc[mb][nbk][r + 3]};
-                    *(KFAC_AS1 v4f*)&P[acc_col(wn, nbk, lane) * NB + acc_row(wm, mb, r, lane)] = x;
-                }
-            }
+            for (int i = 0; i < 4; ++i) P[(r * PSB + 4 * lq + i) * NB + c * PSB + l16] = -b[i];
+        });
         return;
     }
+    each_block(wave, D, [&](int r, int c, const v4f& b) KFAC_INLINE {
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = acc_row(wm, mb, r, lane), col = acc_col(wn, nbk, lane);
-                if (row >= col) tri[tri_at(row, col)] = acc[mb][nbk][r];
-            }
+        for (int i = 0; i < 4; ++i) {
+            const int row = r * PSB + 4 * lq + i, col = c * PSB + l16;
+            if (row >= col) tri[tri_at(row, col)] = b[i];
+        }
+    });
     __syncthreads();
     // thread = four consecutive columns of one row, 8 rows per pass: 16-byte stores (the working copy and the P
     // buffer are 16-byte aligned; the caller's output need not be)
@@ -528,32 +541,27 @@ __device__ __forceinline__ void pivot_write(const v16f (&acc)[2][2], float* __re
 __device__ __forceinline__ void begin_pivot(const Item& it, float* __restrict__ lds) {
     const int d = it.dim, nb = min(NB, d);
     const bool single = d <= NB;
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const WsView ws = ws_view(it.ws, d);
-    // straight into the accumulators, of the lower triangle (wavefront 1's quadrant lies above it); indices clamped, not guarded, so
-    // that all loads go out together
-    v16f acc[2][2];
-    const int lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
-    if (wave != 1) {
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = min(acc_row(wm, mb, r, lane), nb - 1), col = min(acc_col(wn, nbk, lane), nb - 1);
-                    acc[mb][nbk][r] = it.S[(size_t)max(row, col) * d + min(row, col)];
-                }
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (wm == wn && acc_row(wm, mb, r, lane) == acc_col(wn, mb, lane)) acc[mb][mb][r] += it.damping;
-    }
-    if (nb < NB) pivot_border(acc, nb);
-    const int f = pivot_sweep(acc, nb, lds);
-    if (t == 0 && it.info) *it.info = f;                 // (later pivots: upd_next_pivot)
-    pivot_write(acc, lds, it, ws, 0, nb, single, single);
+    // straight into the accumulators, of the lower triangle; indices clamped, not guarded, so that all loads go out together
+    PivotBlocks D;
+    const int l16 = lane & 15, l4 = 4 * (lane >> 4);
+    each_block(wave, D, [&](int r, int c, v4f& b) KFAC_INLINE {
+        auto at = [&](int i) KFAC_INLINE {
+            const int row = min(r * PSB + l4 + i, nb - 1), col = min(c * PSB + l16, nb - 1);
+            return it.S[(size_t)max(row, col) * d + min(row, col)];
+        };
+        b = v4f{at(0), at(1), at(2), at(3)};
+    });
+    const v4f lambda = {l4 == l16 ? it.damping : 0.f, l4 + 1 == l16 ? it.damping : 0.f, l4 + 2 == l16 ? it.damping : 0.f,
+                        l4 + 3 == l16 ? it.damping : 0.f};
+    each_block(wave, D, [&](int r, int c, v4f& b) KFAC_INLINE {
+        if (r == c) b += lambda;
+    });
+    if (nb < NB) pivot_border(D, wave, nb);
+    const int f = pivot_sweep(D, wave, nb, lds);
+    if (t == 0 && it.info) *it.info = f;                 // (later pivots: step_pivot)
+    pivot_write(D, wave, lds, it, ws, 0, nb, single, single);
 }
 
 // A quarter (32 rows) of tile (I, J) of the working copy: W(lower) = S(lower) + lambda I.  Tiles on the diagonal get both
@@ -979,7 +987,7 @@ __device__ __forceinline__ void last_slab(const Item& it, int k, int I, int half
 constexpr int PUP_RING = PANEL_B_LDS;                    // LDS: P's pieces (panel_stash), then three slices of U's; later six
 static_assert(PUP_RING + 3 * 2 * PRE_BLOCK <= UPD_LDS_BYTES && 10 * 4096 <= UPD_LDS_BYTES, "the kernel's LDS");
 
-__device__ __forceinline__ void pivot_update(const WsView& ws, int step, unsigned char* __restrict__ lds, v16f (&acc)[2][2]) {
+__device__ __forceinline__ void pivot_update(const WsView& ws, int step, unsigned char* __restrict__ lds, PivotBlocks& D) {
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
     const int kn = step + 1, q = step % NBUF;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), lm = lane & 31, h = lane >> 5;
@@ -1115,15 +1123,8 @@ __device__ __forceinline__ void pivot_update(const WsView& ws, int step, unsigne
     __syncthreads();
 #pragma unroll
     for (int s = 6; s < 8; ++s) slice(s, PUP_RING + (s - 6) * 2 * PRE_BLOCK);
-    const int wm = wave >> 1, wn = wave & 1;
-    if (wave != 1) {
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk)
-                if (2 * wn + nbk <= 2 * wm + mb) load_block(tile_block(wtile, 2 * wm + mb, 2 * wn + nbk), acc[mb][nbk]);
-    }
-    // ---- to the wavefronts that hold the quadrants, block by block in register order
+    each_block(wave, D, [&](int r, int c, v4f& b) KFAC_INLINE { b = *(const KFAC_AS1 v4f*)(tile_block(wtile, r >> 1, c >> 1) + sub_block_at(r, c, lane)); });
+    // ---- to the wavefronts that own the block rows, 32 x 32 block by block in register order
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");          // U's pieces are done with
     float* blocks = (float*)lds;
 #pragma unroll
@@ -1137,33 +1138,23 @@ __device__ __forceinline__ void pivot_update(const WsView& ws, int step, unsigne
         }
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (wave != 1) {
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nbk = 0; nbk < 2; ++nbk) {
-                const int rb = 2 * wm + mb, cb = 2 * wn + nbk;
-                if (cb > rb) continue;
-#pragma unroll
-                for (int r = 0; r < 16; r += 4) {
-                    const v4f x = *(const v4f*)&blocks[(rb * (rb + 1) / 2 + cb) * 1024 + r * 64 + lane * 4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[mb][nbk][r + i] -= x[i];
-                }
-            }
-    }
+    each_block(wave, D, [&](int r, int c, v4f& b) KFAC_INLINE {
+        const int rb = r >> 1, cb = c >> 1;
+        b -= *(const v4f*)&blocks[(rb * (rb + 1) / 2 + cb) * 1024 + sub_block_at(r, c, lane)];
+    });
     __syncthreads();
 }
 
 __device__ __forceinline__ void step_pivot(const Item& it, int step, float* __restrict__ lds) {
     const int d = it.dim, k0 = (step + 1) * NB, nb = min(NB, d - k0);
     const WsView ws = ws_view(it.ws, d);
-    v16f acc[2][2];
-    pivot_update(ws, step, (unsigned char*)lds, acc);
-    if (nb < NB) pivot_border(acc, nb);                  // (uniform)
-    const int f = pivot_sweep(acc, nb, lds);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    PivotBlocks D;
+    pivot_update(ws, step, (unsigned char*)lds, D);
+    if (nb < NB) pivot_border(D, wave, nb);              // (uniform)
+    const int f = pivot_sweep(D, wave, nb, lds);
     if (threadIdx.x == 0 && it.info && f != 0) atomicCAS((int*)it.info, 0, k0 + f);
-    pivot_write(acc, lds, it, ws, k0, nb, k0 + NB >= d, false);
+    pivot_write(D, wave, lds, it, ws, k0, nb, k0 + NB >= d, false);
 }
 
 // The first step that tile (I, J) owes of the steps lo .. hi, and where its old values are if not where `o` says (owed_first).
