@@ -261,9 +261,9 @@ __device__ __forceinline__ void invert16_step4(v4f& E, int i, int g, const float
     piv[4 * S] = a00; piv[4 * S + 1] = a11; piv[4 * S + 2] = a22; piv[4 * S + 3] = a33;
     const float lo = (g & 1) ? u[1] : u[0], hi = (g & 1) ? u[3] : u[2], w = (g & 2) ? hi : lo;
     const bool zero = prow || g == S;
+    const v4f sum = __builtin_amdgcn_mfma_f32_16x16x4f32(w, w, v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);   // (rounded to E's size once)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) E[q] = zero ? 0.f : E[q];
-    E = __builtin_amdgcn_mfma_f32_16x16x4f32(-w, w, E, 0, 0, 0);
+    for (int q = 0; q < 4; ++q) E[q] = (zero ? 0.f : E[q]) - sum[q];
 }
 
 // One wavefront: Ps = inverse of the symmetric positive definite 16 x 16 block whose element (i, 4 g + q) lane
@@ -468,15 +468,17 @@ __device__ __forceinline__ int pivot_sweep(PivotBlocks& D, int wave, int nb, flo
         sweep_barrier();
 #pragma unroll 1
         for (int n = 1; n < nsb; ++n) {                        // diagonal sub-block n -= T16 . U16^T, and its inverse
-            // (E: minus the inverse of the sub-block before; T16 as in sweep_rows, for these 16 rows, stays in registers)
+            // (E: minus the inverse of the sub-block before; T16 as in sweep_rows, for these 16 rows, stays in registers; the sum is
+            // formed by itself and added at once: most of it cancels)
             const v4f u = *(const v4f*)&lds[PIV_US + ((n - 1) & 1) * (NB * PLD) + (n * PSB + l16) * PLD + 4 * lq];
-            v4f c4 = *(const v4f*)&lds[PIV_DG + (n & 1) * (PSB * PSB) + lane * 4], tt = {0.f, 0.f, 0.f, 0.f};
+            const v4f old = *(const v4f*)&lds[PIV_DG + (n & 1) * (PSB * PSB) + lane * 4];
+            v4f tt = {0.f, 0.f, 0.f, 0.f}, sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) tt = __builtin_amdgcn_mfma_f32_16x16x4f32(E[kk], u[kk], tt, 0, 0, 0);
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) c4 = __builtin_amdgcn_mfma_f32_16x16x4f32(tt[kk], u[kk], c4, 0, 0, 0);
+            for (int kk = 0; kk < 4; ++kk) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(tt[kk], u[kk], sum, 0, 0, 0);
             // the accumulator layout holds (row 4 lq + i, column l16): by symmetry element (l16, 4 lq + i)
-            E = c4;
+            E = old + sum;
             const int f = invert16_wave(E, lds + PIV_PS + (n & 1) * (PSB * PLD));
             first_bad = f != 0 && first_bad == 0 ? n * PSB + f : first_bad;
             sweep_barrier();
@@ -1029,6 +1031,7 @@ __device__ __forceinline__ void pivot_update(const WsView& ws, int step, unsigne
     // the tile's old values, into this XCD's L2: two of its 512 cache lines a thread
     gfloat* wtile = ws.tile(kn, kn);
     const float touch[2] = {wtile[t * 64], wtile[t * 64 + 32]};
+    const float su[2] = {ws.scaleU(q, 2 * kn), ws.scaleU(q, 2 * kn + 1)};
     unsigned a_off[4];
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) a_off[kb] = (unsigned)split_plane_offset(kb * 32 + lm, h);
@@ -1130,7 +1133,7 @@ __device__ __forceinline__ void pivot_update(const WsView& ws, int step, unsigne
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
         if (cb > wave) continue;
-        const float back = 1.0f / (st * ws.scaleU(q, 2 * kn + (cb >> 1)));
+        const float back = 1.0f / (st * su[cb >> 1]);
 #pragma unroll
         for (int r = 0; r < 16; r += 4) {
             const v4f x = {dd[cb][r] * back, dd[cb][r + 1] * back, dd[cb][r + 2] * back, dd[cb][r + 3] * back};
