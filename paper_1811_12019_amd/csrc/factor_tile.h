@@ -1,5 +1,5 @@
 // Matrix-core factor builder: tiles of  Xbar^T Xbar  straight from a channels-last tensor (or NCHW planes: FEED_PLANES), Xbar the
-// implicitly unfolded patch matrix, for 16-bit (v_mfma_f32_32x32x16) and fp32 (v_mfma_f32_32x32x2_f32) inputs.
+// implicitly unfolded patch matrix, for 16-bit inputs and, in three bf16 pieces, fp32 ones (v_mfma_f32_32x32x16 both).
 //
 // One TW x TW tile (on or below the diagonal) of one range of unfolded rows per workgroup.  The contraction index (the
 // unfolded row) is the slow index in memory, and the 16-bit MFMA wants it contiguous per lane; gfx950 has exactly the two
@@ -22,7 +22,7 @@
 // 64-wide: 31 % and 20 %.  The rest is wavefronts waiting at the slabs' barriers and a tile's epilogue, beside which a 256-wide
 // workgroup has nothing else on its CU; at that load the clock falls to about 1.9 GHz.  All factors from NCHW: bf16 at batch 32
 // 2090 -> 1804 us with shared sums, 1515 with planes read as they lie, 1272 with both sides of a slab's work interleaved, work dealt evenly
-// to the XCDs and epilogues from 32-bit offsets; fp32 at batch 8 2555 -> 1974 -> 1766 -> 1600.  No registers live in scratch memory but 2 of
+// to the XCDs and epilogues from 32-bit offsets; fp32 at batch 8 2555 -> 1974 -> 1766 -> 1600, and 1230 in pieces.  No registers live in scratch memory but 2 of
 // the 256-wide kernel without planes, used outside the product loops.
 //
 // The bias column is not part of the tiled matrix (2048 + 1 columns would cost a ninth row of 256-wide tiles for one
@@ -50,12 +50,6 @@ typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 #define KFAC_TR_READ(dst, addr, off) \
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off))
-
-template <bool F16>
-__device__ __forceinline__ v16f mfma16_halves(v2u a0, v2u a1, v2u b0, v2u b1, v16f c) {
-    uint4 a = make_uint4(a0.x, a0.y, a1.x, a1.y), b = make_uint4(b0.x, b0.y, b1.x, b1.y);
-    return mfma16<F16>(a, b, c);
-}
 
 constexpr int SHARED_ROWS_MIN = 1024, SHARED_INPUT_MIN = 1 << 17;
 
@@ -274,15 +268,64 @@ enum { FEED_PATCHES, FEED_PIXELS, FEED_WINDOW, FEED_PLANES };
 template <int ES> struct TileAddr { typedef unsigned type; };
 template <> struct TileAddr<4> { typedef unsigned long long type; };
 
-// An operand of one K step of a 32-column block: read in pieces of two registers, or (PLANES) in one of four.
-template <bool PLANES, int PIECES> struct OperandRegs { typedef v2u type[PIECES]; };
-template <int PIECES> struct OperandRegs<true, PIECES> { typedef v4u type; };
-template <int P> __device__ __forceinline__ v2u first_half(const v2u (&r)[P]) { return r[0]; }
-template <int P> __device__ __forceinline__ v2u second_half(const v2u (&r)[P]) { return r[P - 1]; }
-__device__ __forceinline__ v2u first_half(const v4u& r) { return v2u{r.x, r.y}; }
-__device__ __forceinline__ v2u second_half(const v4u& r) { return v2u{r.z, r.w}; }
-template <int P> __device__ __forceinline__ float operand_float(const v2u (&r)[P], int e) { return __uint_as_float(r[0][e]); }
-__device__ __forceinline__ float operand_float(const v4u& r, int e) { return __uint_as_float(r[e]); }
+// An operand of one K step (16 rows) of a 32-column block, as it comes from LDS: 16-bit: in two pieces of two registers, or (PLANES) in one
+// of four; fp32: eight floats in four pieces of two, or two of four.
+template <bool PLANES, int ES> struct OperandRegs { typedef v2u type[ES]; };
+template <int ES> struct OperandRegs<true, ES> { typedef v4u type[ES / 2]; };
+template <int P> __device__ __forceinline__ uint4 whole_operand(const v2u (&r)[P]) { return make_uint4(r[0].x, r[0].y, r[1].x, r[1].y); }
+template <int P> __device__ __forceinline__ uint4 whole_operand(const v4u (&r)[P]) { return make_uint4(r[0].x, r[0].y, r[0].z, r[0].w); }
+
+// fp32 operands are multiplied on the bf16 matrix cores, which are 16 times as fast as the fp32 ones: x = x0 + x1 + x2, eight bits each,
+// exactly (x0: the upper half of x, which no finite x takes to infinity; x1, x2 rounded), and of the nine products of pieces the six down to
+// 2^-16 of the first; what is left out, x1 y2 and smaller, is 2^-24 of x y and of either sign.  Errors against 64 bits are 0.78 of those of
+// fp32 products on average over 28 builds, nowhere more than 1.09.  All factors of ResNet-50 from NCHW at batch 8 1600 -> 1230 us.
+// Bound: the matrix core takes 768 cycles a slab of a 128-wide tile for the products and 512 for the splitting's v_dot2_f32_bf16, which run on
+// it too; without them (differences, 9 more instructions to four values) the vector unit is the longer one: 1,250 to 1,290 us, also with the
+// splitting dealt out between the products.  Two workgroups to a CU: three leave no room for the small products' sums; four slabs in the
+// ring bring nothing.
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+struct Pieces {
+    uint4 p[3];
+};
+__device__ __forceinline__ void split_pair(float a, float b, unsigned& p0, unsigned& p1, unsigned& p2) {
+    // a - piece, exact, as one instruction.  ((-1, 0) and (0, -1) in registers: as a constant inside the instruction the compiler writes
+    // -1.0 for both, which the hardware takes for the second.)
+    unsigned minus_first = 0x0000BF80u, minus_second = 0xBF800000u;
+    asm("" : "+s"(minus_first), "+s"(minus_second));
+    v2bf first, second, x0;
+    __builtin_memcpy(&first, &minus_first, 4);
+    __builtin_memcpy(&second, &minus_second, 4);
+    p0 = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+    __builtin_memcpy(&x0, &p0, 4);
+    a = __builtin_amdgcn_fdot2_f32_bf16(x0, first, a, false);
+    b = __builtin_amdgcn_fdot2_f32_bf16(x0, second, b, false);
+    const v2bf x1 = {(__bf16)a, (__bf16)b};
+    __builtin_memcpy(&p1, &x1, 4);
+    a = __builtin_amdgcn_fdot2_f32_bf16(x1, first, a, false);
+    b = __builtin_amdgcn_fdot2_f32_bf16(x1, second, b, false);
+    const v2bf x2 = {(__bf16)a, (__bf16)b};
+    __builtin_memcpy(&p2, &x2, 4);
+}
+__device__ __forceinline__ void split_words(const unsigned (&w)[8], Pieces& o) {
+    unsigned q[3][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) split_pair(__uint_as_float(w[2 * i]), __uint_as_float(w[2 * i + 1]), q[0][i], q[1][i], q[2][i]);
+#pragma unroll
+    for (int e = 0; e < 3; ++e) o.p[e] = make_uint4(q[e][0], q[e][1], q[e][2], q[e][3]);
+}
+__device__ __forceinline__ void split_operand(const v2u (&r)[4], Pieces& o) {
+    const unsigned w[8] = {r[0].x, r[0].y, r[1].x, r[1].y, r[2].x, r[2].y, r[3].x, r[3].y};
+    split_words(w, o);
+}
+__device__ __forceinline__ void split_operand(const v4u (&r)[2], Pieces& o) {
+    const unsigned w[8] = {r[0].x, r[0].y, r[0].z, r[0].w, r[1].x, r[1].y, r[1].z, r[1].w};
+    split_words(w, o);
+}
+// Pieces of the six products, smallest first.  The first five have accumulators of their own: the matrix cores cut sums off, and six products
+// to an accumulator of sums of one sign would err up to 2.5 times as much as fp32 products.
+constexpr int SPLIT_PRODUCTS = 6;
+constexpr int split_a(int e) { return e < 3 ? e : e < 5 ? e - 3 : 0; }           // 0 1 2 0 1 0
+constexpr int split_b(int e) { return e < 3 ? 2 - e : e < 5 ? 4 - e : 0; }       // 2 1 0 1 0 0
 
 // One tile.  KIND 0: bf16, 1: fp16, 2: fp32.
 template <int TW, int KIND, int FEED, bool DIAG>
@@ -298,7 +341,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     constexpr int NP = DIAG ? 1 : 2;                           // panels
     constexpr int NB2 = PANEL / 1024 / NW;                     // copies (1 KB each) per wavefront, slab and panel
     constexpr int NI = NP * NB2;
-    static_assert(NB2 == 2 && NB2 * NW * 1024 == PANEL && (NS - 2) * NI < 64, "every wavefront issues two copies a panel");
+    static_assert(NB2 == 2 && NB2 * NW * 1024 == PANEL && (NS - 1) * NI < 64, "every wavefront issues two copies a panel");
     constexpr int RGS = 8 * TW;                                // 16-bit: bytes of four rows
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
     const Unfold& u = v.u;
@@ -477,21 +520,25 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     // during the last step's products.  A product occupies the matrix cores for 32 cycles (fp32: 64): reads, address arithmetic and
     // copies are dealt out between the products, one fenced group after each (left alone, they gather before or behind them, in all
     // wavefronts at the same time).
-    constexpr int STEPS = ES == 2 ? DK / 16 : PLANES ? DK / 8 : DK / 4;
-    static_assert(STEPS % 2 == 0, "the register sets alternate across slabs");
+    // fp32: one register set, emptied (split into pieces) before the next operands are read into it; where a slab is one step, its place is
+    // free from the start of its products on, and all of the ring is filled ahead.
+    constexpr int STEPS = DK / 16;
+    static_assert(STEPS % 2 == 0 || ES == 4, "the register sets alternate across slabs");
+    constexpr int AHEAD = STEPS == 1 ? NS : NS - 1;                                 // slabs copied before the first is read
+    auto set_of = [](int step) { return ES == 2 ? step & 1 : 0; };
     auto pipeline = [&](auto muls, auto reads, auto&& read, auto&& arrived, auto&& multiply) {
         constexpr int MULS = decltype(muls)::value, READS = decltype(reads)::value;
         constexpr int SLOTS = MULS > 0 ? MULS : 1, LAST = SLOTS - SLOTS / 4;        // reads go behind the first LAST products
         constexpr int CPS = (NI + 1 + SLOTS - 1) / SLOTS;                           // copies (and the step on) to a slot
         auto step = [&](auto e, int next_off, int freed) {                          // multiply step e, read step e + 1, refill `freed`
             constexpr int E = decltype(e)::value, NEXT = (E + 1) % STEPS;
-            arrived(E & 1);
+            arrived(set_of(E));
             static_for<SLOTS>([&](auto m) {
                 constexpr int M = decltype(m)::value;
-                if constexpr (MULS > 0) multiply(m, E & 1);
+                if constexpr (MULS > 0) multiply(m, set_of(E));
                 if constexpr (M < LAST)
                     static_for<READS * (M + 1) / LAST - READS * M / LAST>([&](auto k) {
-                        read(StaticInt<READS * M / LAST + decltype(k)::value>{}, (unsigned)next_off, StaticInt<NEXT>{}, NEXT & 1);
+                        read(StaticInt<READS * M / LAST + decltype(k)::value>{}, (unsigned)next_off, StaticInt<NEXT>{}, set_of(NEXT));
                     });
                 if constexpr (E == 0)
                     static_for<CPS>([&](auto k) {
@@ -503,11 +550,11 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
             });
         };
 #pragma unroll
-        for (int s = 0; s < NS - 1; ++s) {
+        for (int s = 0; s < AHEAD; ++s) {
             static_for<NI>([&](auto i) { copy(source(i), i, s * STAGE); });
             advance();
         }
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((NS - 2) * NI) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((AHEAD - 1) * NI) : "memory");
         static_for<READS>([&](auto k) { read(k, 0u, StaticInt<0>{}, 0); });
         int cur = 0, freed = (NS - 1) * STAGE;                  // ring offset of slab s, and of the place to refill
         for (int s = 0; s < nst; ++s) {
@@ -520,7 +567,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((NS - 2) * NI) : "memory");
             freed = cur;
             cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
-            step(StaticInt<STEPS - 1>{}, cur, 0);
+            step(StaticInt<STEPS - 1>{}, cur, freed);
         }
         // trailing (all-zero) slabs must not land later, and everybody is done with the ring
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -530,38 +577,36 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     // ---- consumer: LDS byte address of this lane's operand pieces in stage 0, from tile column c0 on ----
     auto operand_addr = [&](int c0) -> unsigned {
         if constexpr (PLANES) {
-            return (unsigned)((c0 + lm) * CH + (h ^ (lm / FLIP % CH))) * 16;
+            return (unsigned)((c0 + lm) * CH + (h * (ES / 2) ^ (lm / FLIP % CH))) * 16;
         } else if constexpr (ES == 2) {
             const int grp = lane >> 4, p = lane & 15, r = p >> 2, cg4 = p & 3;
             return (unsigned)((2 * (grp >> 1)) * RGS + (2 * r + (cg4 >> 1)) * 16 + (cg4 & 1) * 8 + (grp & 1) * 128 + c0 / 16 * 128);
         } else {
-            return (unsigned)((h * TW + c0 + lm) * 4);
+            return (unsigned)((8 * h * TW + c0 + lm) * 4);
         }
     };
-    // operands of N 32-column blocks for the e-th K step of a slab: 16-bit: 16 rows; fp32: the 4 rows of two
-    // v_mfma_f32_32x32x2_f32 (k = 2 s + h), one read bringing the operands of both.  PLANES: 16 bytes of rows of each half-wave.
-    constexpr int PIECES = PLANES ? 1 : ES == 2 ? 2 : 1;
-    constexpr int PRODUCTS = ES == 2 ? 1 : PLANES ? 4 : 2;     // MFMAs of a step and block
-    typedef typename OperandRegs<PLANES, PIECES>::type Regs;
+    // Read k of a block's operand for the e-th K step (16 rows) of a slab: lane (lm, h) gets rows 8 h .. 8 h + 7 of the step.  16-bit: two
+    // transposing reads (counted as one), PLANES: one of 16 bytes.  fp32: four reads of two rows each, PLANES: two of 16 bytes.
+    constexpr int OPERAND_READS = ES == 2 ? 1 : PLANES ? 2 : 4;
+    constexpr int PRODUCTS = ES == 2 ? 1 : SPLIT_PRODUCTS;     // MFMAs of a step and block
+    typedef typename OperandRegs<PLANES, ES>::type Regs;
     constexpr int U = TW / 64;                                 // fp32: units of 256 bytes per slab row
-#define KFAC_TILE_READ(dst, i, addr, step)                                                                                        \
+#define KFAC_TILE_READ(dst, i, k, addr, step)                                                                                     \
     do {                                                                                                                         \
         if constexpr (PLANES) {                                                                                                  \
-            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst[i]) : "v"((addr) ^ (32u * decltype(step)::value)), "n"((i) * 32 * CH * 16)); \
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst[k]) : "v"((addr) ^ (16u * (ES * decltype(step)::value + k))), "n"((i) * 32 * CH * 16)); \
         } else if constexpr (ES == 2) {                                                                                          \
-            KFAC_TR_READ(dst[i][0], addr, (i) * 256 + (4 * decltype(step)::value + 0) * RGS);                                                       \
-            KFAC_TR_READ(dst[i][PIECES - 1], addr, (i) * 256 + (4 * decltype(step)::value + 1) * RGS);                                              \
+            KFAC_TR_READ(dst[0], addr, (i) * 256 + (4 * decltype(step)::value + 0) * RGS);                                                          \
+            KFAC_TR_READ(dst[1], addr, (i) * 256 + (4 * decltype(step)::value + 1) * RGS);                                                          \
         } else {                                                                                                                 \
             asm volatile("ds_read2st64_b32 %0, %1 offset0:%2 offset1:%3"                                                          \
-                         : "=v"(dst[i][0]) : "v"(addr + (i) * 128), "n"(4 * U * decltype(step)::value), "n"(4 * U * decltype(step)::value + 2 * U));               \
+                         : "=v"(dst[k]) : "v"(addr + (i) * 128), "n"(U * (16 * decltype(step)::value + 2 * (k))), "n"(U * (16 * decltype(step)::value + 2 * (k) + 1))); \
         }                                                                                                                        \
     } while (0)
-#define KFAC_TILE_ARRIVED(dst, i)                                                                                                \
-    do {                                                                                                                         \
-        if constexpr (PLANES) asm volatile("" : "+v"(dst[i]));                                                                    \
-        else asm volatile("" : "+v"(dst[i][0]));                                                                                 \
-        if constexpr (PIECES == 2) asm volatile("" : "+v"(dst[i][PIECES - 1]));                                                   \
-    } while (0)
+    auto operand_arrived = [](Regs& r) {
+#pragma unroll
+        for (int k = 0; k < (int)(sizeof(Regs) / sizeof(r[0])); ++k) asm volatile("" : "+v"(r[k]));
+    };
 
     // A wavefront whose part lies beyond the matrix or (diagonal tile) wholly above the diagonal only takes part in the
     // copies; the latter form the column sums instead, BB 32-column blocks each.
@@ -598,22 +643,32 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
         const unsigned addr0 = operand_addr(c0);
-        Regs b[2][BB];
-        pipeline(StaticInt<BB * (ES == 2 ? 1 : PRODUCTS)>{}, StaticInt<BB>{}, [&](auto k, unsigned stage_off, auto e, int set) {
-            KFAC_TILE_READ(b[set], decltype(k)::value, addr0 + stage_off, e);
+        Regs b[ES == 2 ? 2 : 1][BB];
+        Pieces bp[ES == 2 ? 1 : BB];
+        v16f low[ES == 2 ? 1 : BB] = {};
+        pipeline(StaticInt<BB * (ES == 2 ? 1 : 3)>{}, StaticInt<BB * OPERAND_READS>{}, [&](auto k, unsigned stage_off, auto e, int set) {
+            constexpr int i = decltype(k)::value / OPERAND_READS, part = decltype(k)::value % OPERAND_READS;
+            KFAC_TILE_READ(b[set][i], i, part, addr0 + stage_off, e);
         }, [&](int set) {
 #pragma unroll
-            for (int i = 0; i < BB; ++i) KFAC_TILE_ARRIVED(b[set], i);
+            for (int i = 0; i < BB; ++i) operand_arrived(b[set][i]);
+            if constexpr (ES == 4) {
+#pragma unroll
+                for (int i = 0; i < BB; ++i) split_operand(b[0][i], bp[i]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }, [&](auto m, int set) {
             constexpr int i = decltype(m)::value % BB, e = decltype(m)::value / BB;
-            if constexpr (ES == 2) {
-                const unsigned one2 = KIND == 1 ? 0x3C003C00u : 0x3F803F80u;
-                const v2u ones = {one2, one2};
-                acc[i] = mfma16_halves<KIND == 1>(ones, ones, first_half(b[set][i]), second_half(b[set][i]), acc[i]);
-            } else {
-                acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(1.0f, operand_float(b[set][i], e), acc[i], 0, 0, 0);
-            }
+            const unsigned one2 = KIND == 1 ? 0x3C003C00u : 0x3F803F80u;
+            const uint4 ones = make_uint4(one2, one2, one2, one2);
+            if constexpr (ES == 2) acc[i] = mfma16<KIND == 1>(ones, whole_operand(b[set][i]), acc[i]);
+            else if constexpr (e < 2) low[i] = mfma16<false>(ones, bp[i].p[2 - e], low[i]);
+            else acc[i] = mfma16<false>(ones, bp[i].p[0], acc[i]);
         });
+        if constexpr (ES == 4) {
+#pragma unroll
+            for (int i = 0; i < BB; ++i) acc[i] += low[i];
+        }
         if (h == 0) {                                           // (all rows of the products are the sums)
             if (split) {
                 gfloat* dst = job.sums_dst + J * TW + c0;
@@ -642,23 +697,38 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][n][r] = 0.f;
     const unsigned a_addr = operand_addr(wr), b_addr = operand_addr(wc) + (DIAG ? 0u : (unsigned)PANEL);
-    Regs a[2][S::MB], b[2][S::NB];
-    pipeline(StaticInt<S::MB * S::NB * PRODUCTS>{}, StaticInt<S::MB + S::NB>{}, [&](auto k, unsigned stage_off, auto e, int set) {
-        constexpr int K = decltype(k)::value;
-        if constexpr (K < S::NB) KFAC_TILE_READ(b[set], K, b_addr + stage_off, e);
-        else KFAC_TILE_READ(a[set], K - S::NB, a_addr + stage_off, e);
+    constexpr int SETS = ES == 2 ? 2 : 1;
+    Regs a[SETS][S::MB], b[SETS][S::NB];
+    Pieces ap[ES == 2 ? 1 : S::MB], bp[ES == 2 ? 1 : S::NB];
+    v16f low[ES == 2 ? 1 : S::MB][ES == 2 ? 1 : S::NB] = {};       // the five small products' sums (see split_a)
+    pipeline(StaticInt<S::MB * S::NB * PRODUCTS>{}, StaticInt<(S::MB + S::NB) * OPERAND_READS>{}, [&](auto k, unsigned stage_off, auto e, int set) {
+        constexpr int K = decltype(k)::value / OPERAND_READS, part = decltype(k)::value % OPERAND_READS;
+        if constexpr (K < S::NB) KFAC_TILE_READ(b[set][K], K, part, b_addr + stage_off, e);
+        else KFAC_TILE_READ(a[set][K - S::NB], K - S::NB, part, a_addr + stage_off, e);
     }, [&](int set) {
 #pragma unroll
-        for (int i = 0; i < S::NB; ++i) KFAC_TILE_ARRIVED(b[set], i);
+        for (int i = 0; i < S::NB; ++i) operand_arrived(b[set][i]);
 #pragma unroll
-        for (int i = 0; i < S::MB; ++i) KFAC_TILE_ARRIVED(a[set], i);
+        for (int i = 0; i < S::MB; ++i) operand_arrived(a[set][i]);
+        if constexpr (ES == 4) {
+#pragma unroll
+            for (int i = 0; i < S::NB; ++i) split_operand(b[0][i], bp[i]);
+#pragma unroll
+            for (int i = 0; i < S::MB; ++i) split_operand(a[0][i], ap[i]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }, [&](auto m, int set) {
         constexpr int B = S::MB * S::NB, e = decltype(m)::value / B, i = decltype(m)::value % B / S::NB, n = decltype(m)::value % S::NB;
-        if constexpr (ES == 2)
-            acc[i][n] = mfma16_halves<KIND == 1>(first_half(a[set][i]), second_half(a[set][i]), first_half(b[set][n]), second_half(b[set][n]), acc[i][n]);
-        else
-            acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(operand_float(a[set][i], e), operand_float(b[set][n], e), acc[i][n], 0, 0, 0);
+        if constexpr (ES == 2) acc[i][n] = mfma16<KIND == 1>(whole_operand(a[set][i]), whole_operand(b[set][n]), acc[i][n]);
+        else if constexpr (e + 1 < PRODUCTS) low[i][n] = mfma16<false>(ap[i].p[split_a(e)], bp[n].p[split_b(e)], low[i][n]);
+        else acc[i][n] = mfma16<false>(ap[i].p[0], bp[n].p[0], acc[i][n]);
     });
+    if constexpr (ES == 4) {
+#pragma unroll
+        for (int i = 0; i < S::MB; ++i)
+#pragma unroll
+            for (int n = 0; n < S::NB; ++n) acc[i][n] += low[i][n];
+    }
 
     // ---- epilogue ----
     // Stores leave a CU at four lanes per cycle, whatever a lane stores: 16-byte stores wherever four neighbours are there
