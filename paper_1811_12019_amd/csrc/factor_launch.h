@@ -7,9 +7,9 @@
 
 namespace kfac {
 
-// (256 wide: one workgroup of eight wavefronts per CU.  128 wide: three of four, of fp32 tiles, which have twice the accumulators, two; and with them the builds of 64-wide tiles, whose workgroups
-// are of the same size: a launch of their own ended as raggedly as it began.  The first convolution's two factors 79.6 -> 71 us, all of
-// ResNet-50 at batch 32 from NCHW bf16 1342 -> 1315.)
+// (256 wide: one workgroup of eight wavefronts per CU.  128 wide: three of four, of fp32 tiles, which have twice the accumulators, two; and
+// with them the builds of 64-wide tiles, whose workgroups are of the same size: a launch of their own ended as raggedly as it began.  The
+// first convolution's two factors 79.6 -> 71 us, all of ResNet-50 at batch 32 from NCHW bf16 1342 -> 1315.)
 // PLANES: with builds that are read as planes among the others.  (A kernel of its own for launches without them: with the form in it
 // it cost each launch 0.2 to 0.5 us, the first convolution's two factors 94.1 -> 95.2.  Launches of planes only, beside those of the
 // others, leave more ends of launches: all factors of ResNet-50 in bf16 at batch 32 1,639 us instead of 1,514.)
