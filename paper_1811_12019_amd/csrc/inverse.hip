@@ -212,13 +212,16 @@ template <int S>
 __device__ __forceinline__ float row_bcast(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + S, 0xf, 0xf, true));
 }
-// x of the same lane of row G (of the four rows of 16 lanes), in every row
+// x and y of the same lane of row G (of the four rows of 16 lanes), in every row
 template <int G>
-__device__ __forceinline__ float group_bcast(float x) {
-    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);   // rows 0 1 0 1 / 2 3 2 3
-    const unsigned y = a[G >> 1];
-    const auto b = __builtin_amdgcn_permlane16_swap(y, y, false, false);                                     // the even / the odd one
-    return __uint_as_float(b[G & 1]);
+__device__ __forceinline__ void group_bcast2(float& x, float& y) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);   // x's rows 0 1, y's 0 1 / 2 3, 2 3
+    const unsigned r = a[G >> 1];
+    const auto b = __builtin_amdgcn_permlane16_swap(r, r, false, false);                                     // the even / the odd one, twice each
+    const unsigned q = b[G & 1];
+    const auto c = __builtin_amdgcn_permlane32_swap(q, q, false, false);
+    x = __uint_as_float(c[0]);
+    y = __uint_as_float(c[1]);
 }
 
 __device__ __forceinline__ float rsqrt_newton(float p) {
@@ -235,7 +238,9 @@ template <int S>
 __device__ __forceinline__ void invert16_step4(v4f& E, int i, int g, const float (&unit)[4], float (&piv)[16]) {
     float v[4], u[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = group_bcast<S>(E[q]);          // E(i, 4 S + q)
+    for (int q = 0; q < 4; ++q) v[q] = E[q];
+    group_bcast2<S>(v[0], v[1]);                                      // E(i, 4 S + q)
+    group_bcast2<S>(v[2], v[3]);
     const float a00 = row_bcast<4 * S>(v[0]);
     float a10 = row_bcast<4 * S + 1>(v[0]), a20 = row_bcast<4 * S + 2>(v[0]), a30 = row_bcast<4 * S + 3>(v[0]);
     float a11 = row_bcast<4 * S + 1>(v[1]), a21 = row_bcast<4 * S + 2>(v[1]), a31 = row_bcast<4 * S + 3>(v[1]);
@@ -260,10 +265,10 @@ __device__ __forceinline__ void invert16_step4(v4f& E, int i, int g, const float
     u[3] = fmaf(-a32, u[2], fmaf(-a31, u[1], fmaf(-a30, u[0], v[3]))) * r3;
     piv[4 * S] = a00; piv[4 * S + 1] = a11; piv[4 * S + 2] = a22; piv[4 * S + 3] = a33;
     const float lo = (g & 1) ? u[1] : u[0], hi = (g & 1) ? u[3] : u[2], w = (g & 2) ? hi : lo;
-    const bool zero = prow || g == S;
+    const float keep = prow || g == S ? 0.f : 1.f;
     const v4f sum = __builtin_amdgcn_mfma_f32_16x16x4f32(w, w, v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);   // (rounded to E's size once)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) E[q] = (zero ? 0.f : E[q]) - sum[q];
+    for (int q = 0; q < 4; ++q) E[q] = fmaf(E[q], keep, -sum[q]);
 }
 
 // One wavefront: Ps = inverse of the symmetric positive definite 16 x 16 block whose element (i, 4 g + q) lane
