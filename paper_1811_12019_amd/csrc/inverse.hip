@@ -22,10 +22,10 @@
 //   * tiles of the rest of the matrix, which receive the updates of finished steps in one visit for a group of GM steps (Plan).
 // Every matrix of a batch carries its own stage, so that matrices with fewer blocks spread their launches over those of the
 // largest one.  The last step's panel is a launch, and one launch for the whole batch writes the outputs (inv_out_kernel).
-// Bound: one matrix alone by the look-ahead pivot's workgroup (its update 13 us, the sweep 10.8, write-out 1.9, from launch to
-// launch 1.7; half slabs are done after 12 to 23): 27 us a step, 31 with a sweep of 15.3, 40 when panel and tiles were launches of their
-// own.  One matrix alone, us, with the sweep of 15.3 and now: 145 columns 62 and 58, 1000 270 and 244, 2049 530 and 480, 4609 1236 and
-// 1158; ten ragged ones (10 to 1153 columns) with their preconditioning 393 and 370.  Batches of wide matrices are bound by their tile visits.
+// Bound: one matrix alone by the look-ahead pivot's workgroup (loads 2.9 us, its T 4.9, update 5.3, the sweep 10, write-out 1.9, from
+// launch to launch 1.7; half slabs are done after 12 to 23): 26 us a step, 31 with a sweep of 15.3, 40 when panel and tiles were launches
+// of their own.  One matrix alone, us, with the sweep of 15.3 and now: 145 columns 62 and 58, 1000 270 and 240, 2049 530 and 468, 4609 1236
+// and 1159; ten ragged ones (10 to 1153 columns) with their preconditioning 393 and 361.  Batches of wide matrices are bound by their tile visits.
 // Products: the panel on the bf16 matrix cores with operands split three ways; the updates on the fp16 matrix cores
 // from operands that the panel launch has already scaled per half slab (64 rows) and split two ways, stored as planes that
 // go to LDS by DMA (gemm_split.h); both to fp32 accuracy.
@@ -202,7 +202,7 @@ __device__ __forceinline__ void store_block(gfloat* blk, const v16f& acc) {
 //     and inverts it.
 // Padding with the identity makes ragged blocks (fewer than 128 rows) need no special cases.
 // One workgroup, bound by its chain of dependent steps: 3,100 cycles a sub-block, the time of wavefront 1, of which the inversion is
-// 2,450; the owners are done after 1,300 to 3,000.  4,100 with 32 x 32 blocks in quadrants (one wavefront had 16 of 40 to update), two
+// 2,450 (less 200 since its columns are spread in pairs); the owners are done after 1,300 to 3,000.  4,100 with 32 x 32 blocks in quadrants (one wavefront had 16 of 40 to update), two
 // barriers and a rank-1 update per elimination; a loop over the sub-blocks that is not unrolled takes 4,100 too (branches, copies).
 constexpr int PSB = 16;          // sub-block
 constexpr int PLD = 20;          // LDS row stride of the 16-wide panels (float4 aligned)
