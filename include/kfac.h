@@ -83,7 +83,8 @@ size_t kfac_factor_workspace_bytes(int op, const kfac_layer_desc* desc);
 
 /* Stage 1.  A[d_A x d_A] = scale * sum_r abar_r abar_r^T over the R unfolded input patches abar_r of `act`
  * (zero padding outside the image, a trailing 1 if has_bias); scale = 0 selects 1/R, the mini-batch
- * mean of Sec. 3.1.  `act` holds N*C_in*H*W elements of desc->dtype in desc->layout.  Accumulation is fp32.  A non-finite input
+ * mean of Sec. 3.1.  `act` holds N*C_in*H*W elements of desc->dtype in desc->layout.  Accumulation is fp32.  fp32 inputs below 2^-110 in
+ * magnitude (7.7e-34) may count as the nearest multiple of 2^-133; all others are multiplied with all of their bits.  A non-finite input
  * makes every entry non-finite in which it meets a value inside the image or the bias, the diagonal of its columns among them.  Where it
  * meets nothing but padding, 0 times it may or may not be formed (3 x 3 layers of stride 1 and padding 1 with many rows do not). */
 int kfac_factor_A(const kfac_layer_desc* desc, const void* act, float scale, float* A,

@@ -22,7 +22,7 @@
 // 64-wide: 31 % and 20 %.  The rest is wavefronts waiting at the slabs' barriers and a tile's epilogue, beside which a 256-wide
 // workgroup has nothing else on its CU; at that load the clock falls to about 1.9 GHz.  All factors from NCHW: bf16 at batch 32
 // 2090 -> 1804 us with shared sums, 1515 with planes read as they lie, 1272 with both sides of a slab's work interleaved, work dealt evenly
-// to the XCDs and epilogues from 32-bit offsets; fp32 at batch 8 2555 -> 1974 -> 1766 -> 1600, and 1230 in pieces.  No registers live in scratch memory but 2 of
+// to the XCDs and epilogues from 32-bit offsets; fp32 at batch 8 2555 -> 1974 -> 1766 -> 1600, and 1424 in pieces.  No registers live in scratch memory but 2 of
 // the 256-wide kernel without planes, used outside the product loops.
 //
 // The bias column is not part of the tiled matrix (2048 + 1 columns would cost a ninth row of 256-wide tiles for one
@@ -279,14 +279,16 @@ template <int ES> struct OperandRegs<true, ES> { typedef v4u type[ES / 2]; };
 template <int P> __device__ __forceinline__ uint4 whole_operand(const v2u (&r)[P]) { return make_uint4(r[0].x, r[0].y, r[1].x, r[1].y); }
 template <int P> __device__ __forceinline__ uint4 whole_operand(const v4u (&r)[P]) { return make_uint4(r[0].x, r[0].y, r[0].z, r[0].w); }
 
-// fp32 operands are multiplied on the bf16 matrix cores, which are 16 times as fast as the fp32 ones: x = x0 + x1 + x2, eight bits each,
-// exactly (x0: the upper half of x, which no finite x takes to infinity; x1, x2 rounded), and of the nine products of pieces the six down to
-// 2^-16 of the first; what is left out, x1 y2 and smaller, is 2^-24 of x y and of either sign.  Errors against 64 bits are 0.78 of those of
-// fp32 products on average over 28 builds, nowhere more than 1.09.  All factors of ResNet-50 from NCHW at batch 8 1600 -> 1230 us.
-// Bound: the matrix core takes 768 cycles a slab of a 128-wide tile for the products and 512 for the splitting's v_dot2_f32_bf16, which run on
-// it too; without them (differences, 9 more instructions to four values) the vector unit is the longer one: 1,250 to 1,290 us, also with the
-// splitting dealt out between the products.  Two workgroups to a CU: three leave no room for the small products' sums; four slabs in the
-// ring bring nothing.
+// fp32 operands are multiplied on the bf16 matrix cores, which are 16 times as fast as the fp32 ones: x = x0 + x1 + x2, eight bits each (x0: the
+// upper half of x, which no finite x takes to infinity; x1, x2 rounded, at most 2^-7 and 2^-16 of x), exactly from 2^-110 up (below, pieces
+// end at bf16's last bit, 2^-133), and all products of pieces but x2 y2, which is at most 2^-32 of x y.  Errors against 64 bits, over those of
+// fp32 products: 1.00 for one row, less for more (normal and ReLU'd values, up to 25,088 rows: 0.03 to 0.99; of 95 % zeros 0.84 to 1.05).  Without
+// x1 y2 and x2 y1 up to 4.0 * 2^-24 of a product is lost, in a column of one value always the same way: errors of up to 8 rows, and of
+// 95 % zeros, were 1.3 to 1.5 times those of fp32 products.  All factors of ResNet-50 from NCHW at batch 8: fp32 products 1616 us, six
+// products of pieces 1260, these eight 1424; six with x0 rounded (and kept finite) 1390, single products 1.02 to 1.05 times the error.
+// Bound: the matrix core takes 1,024 cycles a slab of a 128-wide tile for the products and 512 for the splitting's v_dot2_f32_bf16, which run
+// on it too; without them (differences, 9 more instructions to four values) 1,431 us.  Two workgroups to a CU: three leave no room for the
+// small products' sums.
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 struct Pieces {
     uint4 p[3];
@@ -325,11 +327,11 @@ __device__ __forceinline__ void split_operand(const v4u (&r)[2], Pieces& o) {
     const unsigned w[8] = {r[0].x, r[0].y, r[0].z, r[0].w, r[1].x, r[1].y, r[1].z, r[1].w};
     split_words(w, o);
 }
-// Pieces of the six products, smallest first.  The first five have accumulators of their own: the matrix cores cut sums off, and six products
-// to an accumulator of sums of one sign would err up to 2.5 times as much as fp32 products.
-constexpr int SPLIT_PRODUCTS = 6;
-constexpr int split_a(int e) { return e < 3 ? e : e < 5 ? e - 3 : 0; }           // 0 1 2 0 1 0
-constexpr int split_b(int e) { return e < 3 ? 2 - e : e < 5 ? 4 - e : 0; }       // 2 1 0 1 0 0
+// Pieces of the eight products, smallest first.  The first seven have accumulators of their own: the matrix cores cut sums off, and all
+// products to an accumulator of sums of one sign would err up to 2.5 times as much as fp32 products.
+constexpr int SPLIT_PRODUCTS = 8;
+constexpr int split_a(int e) { return e < 2 ? e + 1 : e < 5 ? e - 2 : e < 7 ? e - 5 : 0; }       // 1 2 0 1 2 0 1 0
+constexpr int split_b(int e) { return e < 2 ? 2 - e : e < 5 ? 4 - e : e < 7 ? 6 - e : 0; }       // 2 1 2 1 0 1 0 0
 
 // One tile.  KIND 0: bf16, 1: fp16, 2: fp32.
 template <int TW, int KIND, int FEED, bool DIAG>
@@ -704,7 +706,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     constexpr int SETS = ES == 2 ? 2 : 1;
     Regs a[SETS][S::MB], b[SETS][S::NB];
     Pieces ap[ES == 2 ? 1 : S::MB], bp[ES == 2 ? 1 : S::NB];
-    v16f low[ES == 2 ? 1 : S::MB][ES == 2 ? 1 : S::NB] = {};       // the five small products' sums (see split_a)
+    v16f low[ES == 2 ? 1 : S::MB][ES == 2 ? 1 : S::NB] = {};       // the seven small products' sums (see split_a)
     pipeline(StaticInt<S::MB * S::NB * PRODUCTS>{}, StaticInt<(S::MB + S::NB) * OPERAND_READS>{}, [&](auto k, unsigned stage_off, auto e, int set) {
         constexpr int K = decltype(k)::value / OPERAND_READS, part = decltype(k)::value % OPERAND_READS;
         if constexpr (K < S::NB) KFAC_TILE_READ(b[set][K], K, part, b_addr + stage_off, e);
