@@ -229,61 +229,64 @@ __device__ __forceinline__ float rsqrt_newton(float p) {
     return fmaf(0.5f * r, fmaf(-p * r, r, 1.0f), r);
 }
 
-// Four elimination steps of invert16_wave, columns 4 S .. + 3.  With L the Cholesky factor of the 4 x 4 pivot block (formed by all lanes
-// alike) and W = V L^-T, V being the four columns with minus the identity in the pivot rows, all that the sweep does is E - W W^T,
-// where E counts as zero in the pivot rows and columns: -V P V^T beside them, V P and P V^T in them, -P where they cross.  One
-// matrix-core product, and the same bits on both sides of the diagonal: E stays symmetric.  (Rows and columns that drift apart by
-// rounding cost an ill-conditioned block most of its accuracy.)
+// Four elimination steps of invert16_wave, columns 4 S .. + 3; N: minus the matrix E that is swept.  With L the Cholesky factor of the 4 x 4
+// pivot block (formed by all lanes alike) and W = V L^-T, V being the four columns of E with minus the identity in the pivot rows, all that
+// the sweep does is E - W W^T, where E counts as zero in the pivot rows and columns: -V P V^T beside them, V P and P V^T in them, -P where
+// they cross.  One matrix-core product, and the same bits on both sides of the diagonal: E stays symmetric.  (Rows and columns that drift
+// apart by rounding cost an ill-conditioned block most of its accuracy.)  It is added to N, which the matrix core does one elimination after
+// the other: what each leaves is rounded at its own size.  Their sum, formed first, is rounded at the size of what cancels: inverses of up to 16
+// columns with condition numbers from 1e4 on erred 1.1 to 1.7 times as much.
 template <int S>
-__device__ __forceinline__ void invert16_step4(v4f& E, int i, int g, const float (&unit)[4], float (&piv)[16]) {
+__device__ __forceinline__ void invert16_step4(v4f& N, int i, int g, const float (&unit)[4], float (&piv)[16]) {
     float v[4], u[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = E[q];
-    group_bcast2<S>(v[0], v[1]);                                      // E(i, 4 S + q)
+    for (int q = 0; q < 4; ++q) v[q] = N[q];
+    group_bcast2<S>(v[0], v[1]);                                      // N(i, 4 S + q)
     group_bcast2<S>(v[2], v[3]);
-    const float a00 = row_bcast<4 * S>(v[0]);
-    float a10 = row_bcast<4 * S + 1>(v[0]), a20 = row_bcast<4 * S + 2>(v[0]), a30 = row_bcast<4 * S + 3>(v[0]);
-    float a11 = row_bcast<4 * S + 1>(v[1]), a21 = row_bcast<4 * S + 2>(v[1]), a31 = row_bcast<4 * S + 3>(v[1]);
-    float a22 = row_bcast<4 * S + 2>(v[2]), a32 = row_bcast<4 * S + 3>(v[2]), a33 = row_bcast<4 * S + 3>(v[3]);
+    const float a00 = -row_bcast<4 * S>(v[0]);
+    float a10 = -row_bcast<4 * S + 1>(v[0]), a20 = -row_bcast<4 * S + 2>(v[0]), a30 = -row_bcast<4 * S + 3>(v[0]);
+    float a11 = -row_bcast<4 * S + 1>(v[1]), a21 = -row_bcast<4 * S + 2>(v[1]), a31 = -row_bcast<4 * S + 3>(v[1]);
+    float a22 = -row_bcast<4 * S + 2>(v[2]), a32 = -row_bcast<4 * S + 3>(v[2]), a33 = -row_bcast<4 * S + 3>(v[3]);
     const bool prow = (i >> 2) == S;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = prow ? unit[q] : v[q];
+    for (int q = 0; q < 4; ++q) v[q] = prow ? unit[q] : v[q];         // -V
     const float r0 = rsqrt_newton(a00);
     a10 *= r0; a20 *= r0; a30 *= r0;
     a11 = fmaf(-a10, a10, a11); a21 = fmaf(-a20, a10, a21); a31 = fmaf(-a30, a10, a31);
     a22 = fmaf(-a20, a20, a22); a32 = fmaf(-a30, a20, a32); a33 = fmaf(-a30, a30, a33);
-    u[0] = v[0] * r0;
+    u[0] = -v[0] * r0;
     const float r1 = rsqrt_newton(a11);
     a21 *= r1; a31 *= r1;
     a22 = fmaf(-a21, a21, a22); a32 = fmaf(-a31, a21, a32); a33 = fmaf(-a31, a31, a33);
-    u[1] = fmaf(-a10, u[0], v[1]) * r1;
+    u[1] = fmaf(-a10, u[0], -v[1]) * r1;
     const float r2 = rsqrt_newton(a22);
     a32 *= r2;
     a33 = fmaf(-a32, a32, a33);
-    u[2] = fmaf(-a21, u[1], fmaf(-a20, u[0], v[2])) * r2;
+    u[2] = fmaf(-a21, u[1], fmaf(-a20, u[0], -v[2])) * r2;
     const float r3 = rsqrt_newton(a33);
-    u[3] = fmaf(-a32, u[2], fmaf(-a31, u[1], fmaf(-a30, u[0], v[3]))) * r3;
+    u[3] = fmaf(-a32, u[2], fmaf(-a31, u[1], fmaf(-a30, u[0], -v[3]))) * r3;
     piv[4 * S] = a00; piv[4 * S + 1] = a11; piv[4 * S + 2] = a22; piv[4 * S + 3] = a33;
     const float lo = (g & 1) ? u[1] : u[0], hi = (g & 1) ? u[3] : u[2], w = (g & 2) ? hi : lo;
-    const float keep = prow || g == S ? 0.f : 1.f;
-    const v4f sum = __builtin_amdgcn_mfma_f32_16x16x4f32(w, w, v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);   // (rounded to E's size once)
+    const bool gone = prow || g == S;
+    v4f rest;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) E[q] = fmaf(E[q], keep, -sum[q]);
+    for (int q = 0; q < 4; ++q) rest[q] = gone ? 0.f : N[q];
+    N = __builtin_amdgcn_mfma_f32_16x16x4f32(w, w, rest, 0, 0, 0);
 }
 
-// One wavefront: Ps = inverse of the symmetric positive definite 16 x 16 block whose element (i, 4 g + q) lane
-// (i = lane % 16, g = lane / 16) holds in E[q] (of two that mirror each other the lower one counts); E becomes minus the inverse.
+// One wavefront: Ps = inverse of the symmetric positive definite 16 x 16 block whose element (i, 4 g + q), negated, lane
+// (i = lane % 16, g = lane / 16) holds in N[q] (of two that mirror each other the lower one counts); N becomes the inverse.
 // Returns the 1-based index of the first non-positive pivot, or 0.  Nothing goes through LDS on the way.
-__device__ __forceinline__ int invert16_wave(v4f& E, float* __restrict__ Ps) {
+__device__ __forceinline__ int invert16_wave(v4f& N, float* __restrict__ Ps) {
     const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
     float piv[16], unit[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) unit[q] = (i & 3) == q ? -1.f : 0.f;
-    invert16_step4<0>(E, i, g, unit, piv);
-    invert16_step4<1>(E, i, g, unit, piv);
-    invert16_step4<2>(E, i, g, unit, piv);
-    invert16_step4<3>(E, i, g, unit, piv);
-    *(v4f*)&Ps[i * PLD + 4 * g] = -E;
+    for (int q = 0; q < 4; ++q) unit[q] = (i & 3) == q ? 1.f : 0.f;
+    invert16_step4<0>(N, i, g, unit, piv);
+    invert16_step4<1>(N, i, g, unit, piv);
+    invert16_step4<2>(N, i, g, unit, piv);
+    invert16_step4<3>(N, i, g, unit, piv);
+    *(v4f*)&Ps[i * PLD + 4 * g] = N;
     if (piv[15] > 0.f) return 0;                           // (a pivot that is not positive makes all later ones NaN)
     int bad = 0;
 #pragma unroll
@@ -468,23 +471,23 @@ __device__ __forceinline__ int pivot_sweep(PivotBlocks& D, int wave, int nb, flo
     if (wave == 1) {
         const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
         sweep_barrier();                                       // the first U16 and the diagonal sub-blocks are there
-        v4f E = *(const v4f*)&lds[PIV_DG + lane * 4];
-        int first_bad = invert16_wave(E, lds + PIV_PS);
+        v4f N = -*(const v4f*)&lds[PIV_DG + lane * 4];
+        int first_bad = invert16_wave(N, lds + PIV_PS);
         sweep_barrier();
 #pragma unroll 1
         for (int n = 1; n < nsb; ++n) {                        // diagonal sub-block n -= T16 . U16^T, and its inverse
-            // (E: minus the inverse of the sub-block before; T16 as in sweep_rows, for these 16 rows, stays in registers; the sum is
+            // (N: the inverse of the sub-block before; T16 as in sweep_rows, for these 16 rows, stays in registers; the sum is
             // formed by itself and added at once: most of it cancels)
             const v4f u = *(const v4f*)&lds[PIV_US + ((n - 1) & 1) * (NB * PLD) + (n * PSB + l16) * PLD + 4 * lq];
             const v4f old = *(const v4f*)&lds[PIV_DG + (n & 1) * (PSB * PSB) + lane * 4];
             v4f tt = {0.f, 0.f, 0.f, 0.f}, sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) tt = __builtin_amdgcn_mfma_f32_16x16x4f32(E[kk], u[kk], tt, 0, 0, 0);
+            for (int kk = 0; kk < 4; ++kk) tt = __builtin_amdgcn_mfma_f32_16x16x4f32(N[kk], u[kk], tt, 0, 0, 0);
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(tt[kk], u[kk], sum, 0, 0, 0);
             // the accumulator layout holds (row 4 lq + i, column l16): by symmetry element (l16, 4 lq + i)
-            E = old + sum;
-            const int f = invert16_wave(E, lds + PIV_PS + (n & 1) * (PSB * PLD));
+            N = sum - old;
+            const int f = invert16_wave(N, lds + PIV_PS + (n & 1) * (PSB * PLD));
             first_bad = f != 0 && first_bad == 0 ? n * PSB + f : first_bad;
             sweep_barrier();
         }
