@@ -12,10 +12,11 @@
 namespace kfac {
 
 constexpr int BN_MAX = 64;            // layers per launch (argument block under 4 KB)
-// Elements of each tensor per workgroup of the vector kernel.  The 53 layers of ResNet-50 at batch 1, 4 and 32 in bf16 and 8 in fp32, us: 32768
-// 19.0, 37.7, 249 and 122, 65536 16.5, 34.8, 235 and 122, 131072 18.5, 32.5, 231 and 118; but single layers (64 channels of 56 x 56, one
-// and 32 samples) 9.8 and 10.9, 9.9 and 11.6, 12.2 and 13.7.
-constexpr int BN_UNIT = 65536;
+// Elements of each tensor per workgroup of the vector kernel, at most, and in one sum: a workgroup's positions are summed in two halves, so that
+// chains of additions are as long as with workgroups of half the size (as one sum, errors were up to 1.16 times as large).  The 53 layers of
+// ResNet-50 at batch 1, 4 and 32 in bf16 and 8 in fp32, us: workgroups of 32,768 elements 18.8, 37.7, 249 and 119, of 65,536 16.8, 35.6, 235 and
+// 118, of 131,072 (as one sum) 18.5, 32.5, 231 and 118, but then single layers take up to 25 % more.
+constexpr int BN_UNIT = 65536, BN_SUM = 32768;
 constexpr int BN_CVW = 64;            // 16-byte vectors side by side in a workgroup, at most
 constexpr int BN_SP_GENERIC = 512;    // positions per workgroup of the general kernel
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
@@ -28,26 +29,37 @@ static inline __host__ __device__ int bn_vec(int dtype) { return dtype == KFAC_F
 // channels of `sp` positions.
 struct BnPlan {
     int cvw, ncb, sp, nchunk;
+    int half;         // positions in a workgroup's first sum, of two (sp: there is one)
+    bool halves;      // a call of few workgroups may give each half to one of its own: the sums, and so the result, are the same
 };
 
+// Calls of few workgroups are bound by what one CU reads: with halves apart 64 channels of 56 x 56 take 8.0 us for one sample and 8.3 for four in
+// fp32, whole 9.4 and 9.8; 512 of 28 x 28 in bf16 (seven chunks) 9.6 and 10.8.  From 13 chunks on (64 channels of 112 x 112) the sums
+// over the halves take as long as this saves (12.1 and 12.0; four samples 12.9 and 12.6), and from about 200 workgroups on (all layers at batch
+// 1: 211) the chip is busy without (17.2 and 16.7).
+constexpr int BN_HALVES_MOST = 7, BN_HALVES_WGS = 128;
 static BnPlan bn_plan(int C, int HW, int dtype, bool vec) {
     BnPlan p;
     if (!vec) {
         p.cvw = 0; p.ncb = 1;
         p.nchunk = (HW + BN_SP_GENERIC - 1) / BN_SP_GENERIC;
-        p.sp = BN_SP_GENERIC;
+        p.sp = p.half = BN_SP_GENERIC;
+        p.halves = false;
         return p;
     }
     const int cv = C / bn_vec(dtype);
     p.cvw = cv < BN_CVW ? cv : BN_CVW;
     p.ncb = (cv + p.cvw - 1) / p.cvw;
     const int lanes = 256 / p.cvw;
-    // (in elements, not bytes: an fp32 layer is then never cut into more chunks than a 16-bit one of its shape, whose scratch it
-    // shares where only the shape is known)
+    // (in elements, not bytes)
     int sp = BN_UNIT / (p.cvw * bn_vec(dtype));
     if (sp < 4 * lanes) sp = 4 * lanes;
     p.nchunk = (HW + sp - 1) / sp;
     p.sp = (HW + p.nchunk - 1) / p.nchunk;            // even chunks, no short tail
+    // (whole rounds of loads: a second sum then costs none)
+    p.half = p.sp * p.cvw * bn_vec(dtype) > BN_SUM ? std::max((p.sp / 2 + 2 * lanes) / (4 * lanes), 1) * (4 * lanes) : p.sp;
+    p.half = std::min(p.half, p.sp);
+    p.halves = p.half < p.sp && p.nchunk > 1 && p.nchunk <= BN_HALVES_MOST;
     return p;
 }
 
@@ -55,6 +67,7 @@ struct BnBatch {
     int count;
     unsigned prefix[BN_MAX + 1];      // first workgroup of layer i
     int C[BN_MAX], HW[BN_MAX], sp[BN_MAX], nchunk[BN_MAX];
+    int half[BN_MAX];                 // BnPlan::half; negative: a workgroup has one half of a chunk (nchunk: halves)
     const void* x[BN_MAX];
     const void* gout[BN_MAX];
     float* dst[BN_MAX];               // nchunk == 1: g itself; else the layer's partial sums [n][chunk][2C]
@@ -63,7 +76,8 @@ struct BnBatch {
 struct BnReduceBatch {
     int count;
     unsigned prefix[BN_MAX + 1];      // first workgroup of layer i; one workgroup = 256 columns of one sample
-    int C2[BN_MAX], nchunk[BN_MAX];
+    int C2[BN_MAX];
+    int nchunk[BN_MAX];               // negative: that many halves
     const float* partial[BN_MAX];
     float* g[BN_MAX];
 };
@@ -74,10 +88,11 @@ struct BnReduceBatch {
 template <int DTYPE, bool STREAM>
 __global__ __launch_bounds__(256) void bn_partial_kernel(BnBatch b) {
     constexpr int V = DTYPE == KFAC_F32 ? 4 : 8;
-    __shared__ float red[256 * 2 * V];                   // [position lane][half][vector][V]
+    __shared__ float red[2 * 256 * 2 * V];               // [sum][position lane][scale, shift][vector][V]
     const int t = threadIdx.x;
     const int m = __syncthreads_count(t < b.count - 1 && b.prefix[t + 1] <= blockIdx.x);
-    const int C = b.C[m], HW = b.HW[m], sp = b.sp[m], nchunk = b.nchunk[m];
+    const int C = b.C[m], HW = b.HW[m], sp = b.sp[m], half = abs(b.half[m]), nchunk = b.nchunk[m];
+    const bool halves = b.half[m] < 0;
     const int cv = C / V;
     const int cvw = cv < BN_CVW ? cv : BN_CVW;
     const int ncb = (cv + cvw - 1) / cvw;
@@ -90,69 +105,75 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(BnBatch b) {
     const KFAC_AS1 v4u* __restrict__ G = (const KFAC_AS1 v4u*)b.gout[m];
     const int vec0 = t % cvw, pl = t / cvw;
     const int vec = cb * cvw + vec0;
-    const int s0 = chunk * sp, s1 = min(HW, s0 + sp);
-    // (fp32: two sums of half the length each, whose rounding would show)
-    constexpr int SUMS = DTYPE == KFAC_F32 ? 2 : 1;
-    float ds[V] = {}, db[V] = {}, ds2[V] = {}, db2[V] = {};
-    if (pl < lanes && vec < cv) {
-        const size_t row0 = (size_t)n * HW;
-        for (int s = s0 + pl; s < s1; s += 4 * lanes) {
-            v4u xv[4], gv[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {                // masked, branch free: a position past the end re-reads s
-                const int su = s + u * lanes;
-                const bool ok = su < s1;
-                const size_t at = (row0 + (ok ? su : s)) * cv + vec;
-                xv[u] = STREAM ? __builtin_nontemporal_load(X + at) : X[at];
-                gv[u] = STREAM ? __builtin_nontemporal_load(G + at) : G[at];
-                if (!ok) gv[u] = v4u{0u, 0u, 0u, 0u};
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const unsigned xw = xv[u][k], gw = gv[u][k];
-                    if constexpr (DTYPE == KFAC_F32) {
-                        const float g = __uint_as_float(gw);
-                        float& s = u % SUMS ? ds2[k] : ds[k];
-                        s = fmaf(g, __uint_as_float(xw), s);
-                        (u % SUMS ? db2[k] : db[k]) += g;
-                        continue;
-                    }
-                    float x0, x1, g0, g1;
-                    if constexpr (DTYPE == KFAC_F16) {
-                        x0 = half_bits_to_float((uint16_t)(xw & 0xffff)); x1 = half_bits_to_float((uint16_t)(xw >> 16));
-                        g0 = half_bits_to_float((uint16_t)(gw & 0xffff)); g1 = half_bits_to_float((uint16_t)(gw >> 16));
-                    } else {
-                        x0 = __uint_as_float(xw << 16); x1 = __uint_as_float(xw & 0xffff0000u);
-                        g0 = __uint_as_float(gw << 16); g1 = __uint_as_float(gw & 0xffff0000u);
-                    }
-                    ds[2 * k % V] = fmaf(g0, x0, ds[2 * k % V]);             db[2 * k % V] += g0;
-                    ds[(2 * k + 1) % V] = fmaf(g1, x1, ds[(2 * k + 1) % V]); db[(2 * k + 1) % V] += g1;
-                }
-        }
-    }
-    if constexpr (SUMS == 2) {
-#pragma unroll
-        for (int e = 0; e < V; ++e) {
-            ds[e] += ds2[e];
-            db[e] += db2[e];
-        }
-    }
-    // sum over the position lanes in a fixed order; every thread takes part
     const int w8 = cvw * V;                              // channels of this workgroup
-    if (pl < lanes) {
+    const int first = halves ? chunk >> 1 : chunk, part = halves ? chunk & 1 : 0;
+    const int sums = halves || half == sp ? 1 : 2;
+    int i = 0;
+    do {
+        const int s0 = min(HW, first * sp + (part + i) * half), s1 = min(HW, first * sp + (part + i == 0 ? half : sp));
+        float ds[V] = {}, db[V] = {};
+        if (pl < lanes && vec < cv) {
+            const size_t row0 = (size_t)n * HW;
+            for (int s = s0 + pl; s < s1; s += 4 * lanes) {
+                v4u xv[4], gv[4];
 #pragma unroll
-        for (int e = 0; e < V; ++e) {
-            red[pl * 2 * w8 + vec0 * V + e] = ds[e];
-            red[pl * 2 * w8 + w8 + vec0 * V + e] = db[e];
+                for (int u = 0; u < 4; ++u) {                // masked, branch free: a position past the end re-reads s
+                    const int su = s + u * lanes;
+                    const bool ok = su < s1;
+                    const size_t at = (row0 + (ok ? su : s)) * cv + vec;
+                    xv[u] = STREAM ? __builtin_nontemporal_load(X + at) : X[at];
+                    gv[u] = STREAM ? __builtin_nontemporal_load(G + at) : G[at];
+                    if (!ok) gv[u] = v4u{0u, 0u, 0u, 0u};
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const unsigned xw = xv[u][k], gw = gv[u][k];
+                        if constexpr (DTYPE == KFAC_F32) {
+                            const float g = __uint_as_float(gw);
+                            ds[k] = fmaf(g, __uint_as_float(xw), ds[k]);
+                            db[k] += g;
+                            continue;
+                        }
+                        float x0, x1, g0, g1;
+                        if constexpr (DTYPE == KFAC_F16) {
+                            x0 = half_bits_to_float((uint16_t)(xw & 0xffff)); x1 = half_bits_to_float((uint16_t)(xw >> 16));
+                            g0 = half_bits_to_float((uint16_t)(gw & 0xffff)); g1 = half_bits_to_float((uint16_t)(gw >> 16));
+                        } else {
+                            x0 = __uint_as_float(xw << 16); x1 = __uint_as_float(xw & 0xffff0000u);
+                            g0 = __uint_as_float(gw << 16); g1 = __uint_as_float(gw & 0xffff0000u);
+                        }
+                        ds[2 * k % V] = fmaf(g0, x0, ds[2 * k % V]);             db[2 * k % V] += g0;
+                        ds[(2 * k + 1) % V] = fmaf(g1, x1, ds[(2 * k + 1) % V]); db[(2 * k + 1) % V] += g1;
+                    }
+            }
         }
-    }
+        if (pl < lanes) {
+            float* to = red + i * (lanes * 2 * w8) + pl * 2 * w8 + vec0 * V;
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                to[e] = ds[e];
+                to[w8 + e] = db[e];
+            }
+        }
+    } while (++i < sums);
+    // sum over the position lanes in a fixed order; every thread takes part
     __syncthreads();
     gfloat* dst = as_global(b.dst[m]) + ((size_t)n * nchunk + chunk) * (2 * C);
     for (int e = t; e < 2 * w8; e += 256) {
         float a = red[e];
-        for (int q = 1; q < lanes; ++q) a += red[q * 2 * w8 + e];
+        if (sums == 2) {                                 // (side by side: each is a chain of LDS reads)
+            const float* second = red + lanes * 2 * w8;
+            float a2 = second[e];
+            for (int q = 1; q < lanes; ++q) {
+                a += red[q * 2 * w8 + e];
+                a2 += second[q * 2 * w8 + e];
+            }
+            a += a2;
+        } else {
+            for (int q = 1; q < lanes; ++q) a += red[q * 2 * w8 + e];
+        }
         const int half = e >= w8, c = cb * w8 + (e - half * w8);
         if (c < C) dst[half * C + c] = a;
     }
@@ -187,14 +208,18 @@ __global__ __launch_bounds__(256) void bn_partial_generic_kernel(const void* xha
 __global__ __launch_bounds__(256) void bn_reduce_kernel(BnReduceBatch b) {
     const int t = threadIdx.x;
     const int m = __syncthreads_count(t < b.count - 1 && b.prefix[t + 1] <= blockIdx.x);
-    const int C2 = b.C2[m], nchunk = b.nchunk[m];
+    const int C2 = b.C2[m], nchunk = abs(b.nchunk[m]);
     const int cblocks = (C2 + 255) >> 8;
     const unsigned local = blockIdx.x - b.prefix[m];
     const int n = local / cblocks, j = (local % cblocks) * 256 + t;
     if (j >= C2) return;
     const gfloat* __restrict__ partial = as_global(b.partial[m]);
     float s = 0.f;
-    for (int q = 0; q < nchunk; ++q) s += partial[((size_t)n * nchunk + q) * C2 + j];
+    auto at = [&](int q) { return partial[((size_t)n * nchunk + q) * C2 + j]; };
+    if (b.nchunk[m] < 0)                                     // (an even number)
+        for (int q = 0; q < nchunk; q += 2) s += at(q) + at(q + 1);
+    else
+        for (int q = 0; q < nchunk; ++q) s += at(q);
     as_global(b.g[m])[(size_t)n * C2 + j] = s;
 }
 
@@ -240,11 +265,15 @@ static bool bn_item_vec(const kfac_bn_item& it) {
     return it.C % bn_vec(it.dtype) == 0 && (((uintptr_t)it.xhat | (uintptr_t)it.gout) & 15) == 0;
 }
 
-// bytes of partial sums one layer needs (none when a single chunk covers all positions).  The 16-byte alignment of the
-// tensors is not known when only the shape is: both cuttings are covered.
+// bytes of partial sums one layer needs (none when a single chunk covers all positions).  Neither the 16-byte alignment of the
+// tensors nor the call's other layers are known when only the shape is, nor, of a single layer, the dtype: every cutting is covered.
 static size_t bn_item_ws(int N, int C, int HW, int dtype) {
     int nchunk = bn_plan(C, HW, dtype, false).nchunk;
-    if (C % bn_vec(dtype) == 0) nchunk = std::max(nchunk, bn_plan(C, HW, dtype, true).nchunk);
+    for (int dt : {dtype, (int)KFAC_F32, (int)KFAC_BF16})
+        if (C % bn_vec(dtype) == 0 && C % bn_vec(dt) == 0) {
+            const BnPlan p = bn_plan(C, HW, dt, true);
+            nchunk = std::max(nchunk, p.halves ? 2 * p.nchunk : p.nchunk);
+        }
     return nchunk > 1 ? align_up((size_t)N * nchunk * 2 * C * sizeof(float), 256) : 0;
 }
 
@@ -275,16 +304,24 @@ extern "C" int kfac_bn_sample_grads_batched(const kfac_bn_item* items_host, int3
         unsigned wgs[3] = {0, 0, 0}, nred = 0;
         size_t bytes[3] = {0, 0, 0};                      // of both tensors
         lists[KFAC_F32].count = lists[KFAC_BF16].count = lists[KFAC_F16].count = rb.count = 0;
+        long long whole = 0;                              // workgroups with whole chunks
+        for (int i = 0; i < cnt; ++i) {
+            const kfac_bn_item& it = items_host[first + i];
+            const BnPlan p = bn_plan(it.C, it.HW, it.dtype, bn_item_vec(it));
+            whole += (long long)it.N * p.nchunk * p.ncb;
+        }
         for (int i = 0; i < cnt; ++i) {
             const kfac_bn_item& it = items_host[first + i];
             const bool vec = bn_item_vec(it);
-            const BnPlan p = bn_plan(it.C, it.HW, it.dtype, vec);
+            BnPlan p = bn_plan(it.C, it.HW, it.dtype, vec);
+            const bool halves = p.halves && whole <= BN_HALVES_WGS;
+            if (halves) p.nchunk *= 2;
             float* dst = it.g;
             if (p.nchunk > 1) {
                 dst = (float*)wsp;
                 const int k = rb.count++;
                 rb.prefix[k] = nred;
-                rb.C2[k] = 2 * it.C; rb.nchunk[k] = p.nchunk; rb.partial[k] = dst; rb.g[k] = it.g;
+                rb.C2[k] = 2 * it.C; rb.nchunk[k] = halves ? -p.nchunk : p.nchunk; rb.partial[k] = dst; rb.g[k] = it.g;
                 nred += (unsigned)it.N * ((2 * it.C + 255) / 256);
             }
             wsp += bn_item_ws(it.N, it.C, it.HW, it.dtype);
@@ -293,7 +330,7 @@ extern "C" int kfac_bn_sample_grads_batched(const kfac_bn_item* items_host, int3
                 unsigned& units = wgs[it.dtype];
                 const int k = b.count++;
                 b.prefix[k] = units;
-                b.C[k] = it.C; b.HW[k] = it.HW; b.sp[k] = p.sp; b.nchunk[k] = p.nchunk;
+                b.C[k] = it.C; b.HW[k] = it.HW; b.sp[k] = p.sp; b.half[k] = halves ? -p.half : p.half; b.nchunk[k] = p.nchunk;
                 b.x[k] = it.xhat; b.gout[k] = it.gout; b.dst[k] = dst;
                 units += (unsigned)it.N * p.nchunk * p.ncb;
                 bytes[it.dtype] += (size_t)it.N * it.C * it.HW * (it.dtype == KFAC_F32 ? 8 : 4);
