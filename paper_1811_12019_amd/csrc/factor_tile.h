@@ -22,8 +22,8 @@
 // 64-wide: 31 % and 20 %.  The rest is wavefronts waiting at the slabs' barriers and a tile's epilogue, beside which a 256-wide
 // workgroup has nothing else on its CU; at that load the clock falls to about 1.9 GHz.  All factors from NCHW: bf16 at batch 32
 // 2090 -> 1804 us with shared sums, 1515 with planes read as they lie, 1272 with both sides of a slab's work interleaved, work dealt evenly
-// to the XCDs and epilogues from 32-bit offsets; fp32 at batch 8 2555 -> 1974 -> 1766 -> 1600, and 1424 in pieces.  No registers live in scratch memory but 2 of
-// the 256-wide kernel without planes, used outside the product loops.
+// to the XCDs and epilogues from 32-bit offsets; fp32 at batch 8 2555 -> 1974 -> 1766 -> 1600, and 1424 in pieces.  No vector registers live in
+// scratch memory but one of the 128-wide kernel with planes (16-bit), used outside the product loops.
 //
 // The bias column is not part of the tiled matrix (2048 + 1 columns would cost a ninth row of 256-wide tiles for one
 // column): its row of the result is the column sums, which the wavefronts of a diagonal tile whose part lies above the
@@ -800,7 +800,10 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
         __builtin_amdgcn_raw_buffer_store_b128(x, rsrc, off + step, 0, 0);
     };
     // Elsewhere: element by element.  Elements that are not there (beyond the matrix, padding, the other half of a diagonal
-    // tile) get an offset outside the buffer, which the hardware drops: no branches, so that many are in flight.
+    // tile) get an offset outside the buffer, which the hardware drops: no branches, so that many are in flight.  (One body for the mirror
+    // image and the packed triangle, with && and ?: in it, was compiled to a branch around each element; it cost the forms above scalar
+    // registers, too.  49 rows of a 3x3 layer of 256 channels, bf16: (channel, tap) order 18.9 -> 15.5 us, packed 15.5 -> 11.8; one of
+    // 64 channels 16.4 -> 12.7 and 13.9 -> 10.2.)
     const int dc = lane % W, dr = lane / W;
     constexpr int RPP = 64 / W;                                    // rows per pass of the wavefront's lanes
     const int cod = cmap[wc + dc];
@@ -842,13 +845,15 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
             continue;
         }
         if (in_vectors(p)) {
-            const int left = DIAG ? rb - wc : W;                   // columns left of the diagonal block
-            const int rows = min(32, D - I * TW - rb), cols = min(W, left + rows);
+            // (Worked out here and not ahead: neither the lanes' addresses nor, for all block rows, these scalars fit the registers.)
+            int ln = lane, top = I * TW + rb, end = D, side = J * TW + wc;
+            unsigned ud = 4u * d;
+            asm volatile("" : "+v"(ln), "+s"(top), "+s"(end), "+s"(ud), "+s"(side));
+            const int left = DIAG ? top - side : W;                // columns left of the diagonal block
+            const int rows = min(32, end - top), cols = min(W, left + rows);
             if (left >= 0 && rows > 0) {                           // (else nothing of it is there, or all above the diagonal)
-                int ln = lane;
-                asm volatile("" : "+v"(ln));                       // (addresses that were worked out ahead would not fit the registers)
                 const int xr = ln / VPR, xc = ln % VPR * 4;
-                const unsigned corner = (I * TW + rb) * ud + 4u * (J * TW + wc);
+                const unsigned corner = top * ud + 4u * side;
                 if (ema) {                                         // (lanes beyond what is there fetch its last vectors)
 #pragma unroll
                     for (int k = 0; k < NV; ++k) {
@@ -876,7 +881,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
                     put_vector((int)there & (int)(r < rows) ? corner + r * ud + 4u * xc : OUTSIDE, 0, val);
                 }
                 const int mr = (ln & 7) * 4, mc = ln >> 3;
-                const unsigned mirror = (J * TW + wc + mc) * ud + 4u * (I * TW + rb + mr);
+                const unsigned mirror = (side + mc) * ud + 4u * (top + mr);
 #pragma unroll 2
                 for (int k = 0; k < min(W, left) / 8; ++k) {
                     const float* e = &epi[mr * LD + k * 8 + mc];
@@ -915,26 +920,33 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        const int row = rb + lm, ro = rmap[row];
+        // the mirror image, or the packed triangle
+        int ln = lane;
+        asm volatile("" : "+v"(ln));                               // (what the block rows have in common is worked out for each)
+        const int row = rb + (ln & 31), first = wc + (ln >> 5), ro = rmap[row];
+        const float* from = &epi[(ln & 31) * LD + (ln >> 5)];
+        auto columns = [&](auto is_packed) __attribute__((always_inline)) {
+            constexpr bool PACKED = decltype(is_packed)::value;
+#pragma unroll 1
+            for (int c0 = 0; c0 < W; c0 += 32) {
+                int cd[16];
+                float val[16];
 #pragma unroll
-        for (int c0 = 0; c0 < W; c0 += 32) {
-            int cd[16];
-            float val[16];
+                for (int k = 0; k < 16; ++k) {
+                    cd[k] = (PACKED ? cmap : cmapd)[first + c0 + 2 * k];
+                    val[k] = from[c0 + 2 * k];
+                }
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const int c = c0 + 2 * k + h;
-                cd[k] = (packed ? cmap : cmapd)[wc + c];
-                val[k] = epi[lm * LD + c];
+                for (int k = 0; k < 16; ++k) {
+                    const bool ok = (ro >= 0) & (cd[k] >= 0) & (!DIAG | (row >= first + c0 + 2 * k + !PACKED));
+                    const unsigned e = PACKED ? (unsigned)(packed_row_base(min(ro, cd[k]), d) + max(ro, cd[k])) : (unsigned)(cd[k] + ro);
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val[k]), rsrc, ok ? e * 4u : ~0u, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const int col = wc + c0 + 2 * k + h;
-                const bool ok = ro >= 0 && cd[k] >= 0 && !(DIAG && (packed ? row < col : row <= col));
-                const unsigned e = packed ? (unsigned)(packed_row_base(min(ro, cd[k]), d) + max(ro, cd[k])) : (unsigned)(cd[k] + ro);
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val[k]), rsrc, ok ? e * 4u : ~0u, 0, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        };
+        if (packed) columns(StaticInt<1>{});
+        else columns(StaticInt<0>{});
         if (p + 1 < S::MB) fetch_old(p + 1, old[(p + 1) & 1]);         // (here the registers hold no more before)
     }
 }
