@@ -277,7 +277,7 @@ __device__ __forceinline__ void invert16_step4(v4f& N, int i, int g, const float
 // One wavefront: Ps = inverse of the symmetric positive definite 16 x 16 block whose element (i, 4 g + q), negated, lane
 // (i = lane % 16, g = lane / 16) holds in N[q] (of two that mirror each other the lower one counts); N becomes the inverse.
 // Returns the 1-based index of the first non-positive pivot, or 0.  Nothing goes through LDS on the way.
-__device__ __forceinline__ int invert16_wave(v4f& N, float* __restrict__ Ps) {
+__device__ __forceinline__ int invert16_wave(v4f& N, float* Ps) {
     const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
     float piv[16], unit[4];
 #pragma unroll
@@ -362,15 +362,16 @@ __device__ __forceinline__ void sweep_barrier() { asm volatile("s_waitcnt lgkmcn
 // An owner's part of the sweep.  What the next round needs (columns / rows j + 1, the "strip", and diagonal sub-block j + 2) is brought
 // up to date first and handed over; the other blocks follow after the barrier, beside the next round's reads and the inversion of
 // wavefront 1, which sets the pace.
+// (lds and what is derived from it without __restrict__: what is written through one of them is read through another, also by other wavefronts.)
 template <int RL>
-__device__ __forceinline__ void sweep_rows(PivotBlocks& blocks, int nsb, float* __restrict__ lds) {
+__device__ __forceinline__ void sweep_rows(PivotBlocks& blocks, int nsb, float* lds) {
     PivotBlocks D;                                         // (a copy: the compiler would let the owners' branches share accesses, by address)
     static_for<PIV_BLOCKS>([&](auto s) KFAC_INLINE { D[s] = blocks[s]; });
     constexpr int NR = piv_rows(RL), LAST = piv_row(RL, 0);              // (the first row is the longest)
     const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
-    float* __restrict__ nat = lds + l16 * PLD + 4 * lq;                  // (l16, 4 lq ..) and (4 lq .., l16) of a panel's 16-row block
-    float* __restrict__ turned = lds + 4 * lq * PLD + l16;
-    float* __restrict__ diag = lds + PIV_DG + lane * 4;
+    float* nat = lds + l16 * PLD + 4 * lq;                               // (l16, 4 lq ..) and (4 lq .., l16) of a panel's 16-row block
+    float* turned = lds + 4 * lq * PLD + l16;
+    float* diag = lds + PIV_DG + lane * 4;
     constexpr int ROWS = PSB * PLD, PANEL = NB * PLD;
     auto put_turned = [&](int at, const v4f& x) KFAC_INLINE {
         turned[at] = x.x; turned[at + PLD] = x.y; turned[at + 2 * PLD] = x.z; turned[at + 3 * PLD] = x.w;
@@ -465,7 +466,7 @@ __device__ __forceinline__ void sweep_rows(PivotBlocks& blocks, int nsb, float* 
 
 // The symmetric sweep of D in 16-wide sub-blocks (see above); lds: PIV_LDS_FLOATS floats, free on entry.  Returns (to every
 // thread) the 1-based index inside the block of the first non-positive pivot, or 0.  Ends with a barrier.
-__device__ __forceinline__ int pivot_sweep(PivotBlocks& D, int wave, int nb, float* __restrict__ lds) {
+__device__ __forceinline__ int pivot_sweep(PivotBlocks& D, int wave, int nb, float* lds) {
     int* bad = (int*)(lds + PIV_BAD);
     const int nsb = (nb + PSB - 1) / PSB;
     if (wave == 1) {
@@ -504,7 +505,7 @@ __device__ __forceinline__ int pivot_sweep(PivotBlocks& D, int wave, int nb, flo
 // D holds -P up to rounding asymmetry on and below the diagonal.  The working copy gets -P; on the matrix's last step the
 // caller's output gets +P (the final sign flip; lower triangle taken as the truth, so that it is exactly symmetric) instead.
 // The workspace gets +P for the panel product, all of it.
-__device__ __forceinline__ void pivot_write(PivotBlocks& D, int wave, float* __restrict__ tri, const Item& it,
+__device__ __forceinline__ void pivot_write(PivotBlocks& D, int wave, float* tri, const Item& it,
                                             const WsView& ws, int k0, int nb, bool last, bool from_S) {
     const int t = threadIdx.x, lane = t & 63, l16 = lane & 15, lq = lane >> 4;
     const int d = it.dim;
@@ -548,7 +549,7 @@ __device__ __forceinline__ void pivot_write(PivotBlocks& D, int wave, float* __r
 }
 
 // The first pivot block of a matrix, S + lambda I; the only one of a single-block matrix, whose output this writes.
-__device__ __forceinline__ void begin_pivot(const Item& it, float* __restrict__ lds) {
+__device__ __forceinline__ void begin_pivot(const Item& it, float* lds) {
     const int d = it.dim, nb = min(NB, d);
     const bool single = d <= NB;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -997,7 +998,7 @@ __device__ __forceinline__ void last_slab(const Item& it, int k, int I, int half
 constexpr int PUP_RING = PANEL_B_LDS;                    // LDS: P's pieces (panel_stash), then three slices of U's; later six
 static_assert(PUP_RING + 3 * 2 * PRE_BLOCK <= UPD_LDS_BYTES && 10 * 4096 <= UPD_LDS_BYTES, "the kernel's LDS");
 
-__device__ __forceinline__ void pivot_update(const WsView& ws, int step, unsigned char* __restrict__ lds, PivotBlocks& D) {
+__device__ __forceinline__ void pivot_update(const WsView& ws, int step, unsigned char* lds, PivotBlocks& D) {
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
     const int kn = step + 1, q = step % NBUF;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), lm = lane & 31, h = lane >> 5;
@@ -1156,7 +1157,7 @@ __device__ __forceinline__ void pivot_update(const WsView& ws, int step, unsigne
     __syncthreads();
 }
 
-__device__ __forceinline__ void step_pivot(const Item& it, int step, float* __restrict__ lds) {
+__device__ __forceinline__ void step_pivot(const Item& it, int step, float* lds) {
     const int d = it.dim, k0 = (step + 1) * NB, nb = min(NB, d - k0);
     const WsView ws = ws_view(it.ws, d);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
