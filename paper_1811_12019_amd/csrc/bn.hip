@@ -85,14 +85,16 @@ struct BnReduceBatch {
 // NHWC, channels whole vectors.  Both tensors are read once, 16 bytes per thread and load, eight loads in flight.
 // (fp32 went through the general kernel before, one 4-byte load after the other: the gradients and the diagonal form of 53 layers
 // at batch 2 19.2 ms, now 0.25 ms, most of it the 53 launches.)
-template <int DTYPE, bool STREAM>
+// TWO: some layer of the launch has two sums to a workgroup, or halves.  (Asked for each workgroup, this costs launches without any 0.1 to
+// 0.2 us: 2,048 channels of 7 x 7 4.2 us instead of 4.0 in fp32, 5.4 instead of 5.2 in bf16.)
+template <int DTYPE, bool STREAM, bool TWO>
 __global__ __launch_bounds__(256) void bn_partial_kernel(BnBatch b) {
     constexpr int V = DTYPE == KFAC_F32 ? 4 : 8;
-    __shared__ float red[2 * 256 * 2 * V];               // [sum][position lane][scale, shift][vector][V]
+    __shared__ float red[(TWO ? 2 : 1) * 256 * 2 * V];   // [sum][position lane][scale, shift][vector][V]
     const int t = threadIdx.x;
     const int m = __syncthreads_count(t < b.count - 1 && b.prefix[t + 1] <= blockIdx.x);
-    const int C = b.C[m], HW = b.HW[m], sp = b.sp[m], half = abs(b.half[m]), nchunk = b.nchunk[m];
-    const bool halves = b.half[m] < 0;
+    const int C = b.C[m], HW = b.HW[m], sp = b.sp[m], half = TWO ? abs(b.half[m]) : sp, nchunk = b.nchunk[m];
+    const bool halves = TWO && b.half[m] < 0;
     const int cv = C / V;
     const int cvw = cv < BN_CVW ? cv : BN_CVW;
     const int ncb = (cv + cvw - 1) / cvw;
@@ -107,10 +109,10 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(BnBatch b) {
     const int vec = cb * cvw + vec0;
     const int w8 = cvw * V;                              // channels of this workgroup
     const int first = halves ? chunk >> 1 : chunk, part = halves ? chunk & 1 : 0;
-    const int sums = halves || half == sp ? 1 : 2;
+    const int sums = !TWO || halves || half == sp ? 1 : 2;
     int i = 0;
     do {
-        const int s0 = min(HW, first * sp + (part + i) * half), s1 = min(HW, first * sp + (part + i == 0 ? half : sp));
+        const int s0 = min(HW, first * sp + (TWO ? (part + i) * half : 0)), s1 = min(HW, first * sp + (part + i == 0 ? half : sp));
         float ds[V] = {}, db[V] = {};
         if (pl < lanes && vec < cv) {
             const size_t row0 = (size_t)n * HW;
@@ -302,6 +304,7 @@ extern "C" int kfac_bn_sample_grads_batched(const kfac_bn_item* items_host, int3
         BnBatch lists[3];                                 // the fp32, bf16 and fp16 layers of this group
         BnReduceBatch rb;
         unsigned wgs[3] = {0, 0, 0}, nred = 0;
+        bool two[3] = {false, false, false};
         size_t bytes[3] = {0, 0, 0};                      // of both tensors
         lists[KFAC_F32].count = lists[KFAC_BF16].count = lists[KFAC_F16].count = rb.count = 0;
         long long whole = 0;                              // workgroups with whole chunks
@@ -333,6 +336,7 @@ extern "C" int kfac_bn_sample_grads_batched(const kfac_bn_item* items_host, int3
                 b.C[k] = it.C; b.HW[k] = it.HW; b.sp[k] = p.sp; b.half[k] = halves ? -p.half : p.half; b.nchunk[k] = p.nchunk;
                 b.x[k] = it.xhat; b.gout[k] = it.gout; b.dst[k] = dst;
                 units += (unsigned)it.N * p.nchunk * p.ncb;
+                two[it.dtype] |= p.half < p.sp;
                 bytes[it.dtype] += (size_t)it.N * it.C * it.HW * (it.dtype == KFAC_F32 ? 8 : 4);
             } else {
                 KFAC_LAUNCH(bn_partial_generic_kernel, dim3(p.nchunk, it.N), dim3(256), (hipStream_t)stream, it.xhat, it.gout,
@@ -343,14 +347,22 @@ extern "C" int kfac_bn_sample_grads_batched(const kfac_bn_item* items_host, int3
             BnBatch& b = lists[dt];
             if (b.count == 0) continue;
             b.prefix[b.count] = wgs[dt];
-#define KFAC_BN_LAUNCH(DTYPE)                                                                                                   \
+#define KFAC_BN_LAUNCH_AS(DTYPE, NAME, STREAM, TWO)                                                                                 \
+    KFAC_LAUNCH_AS("bn_partial_kernel<" #DTYPE NAME ">", (bn_partial_kernel<DTYPE, STREAM, TWO>), dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b)
+#define KFAC_BN_LAUNCH(DTYPE)                                                                                                       \
     do {                                                                                                                            \
-        if (bytes[dt] > STREAM_BYTES) KFAC_LAUNCH_AS("bn_partial_kernel<" #DTYPE ", stream>", (bn_partial_kernel<DTYPE, true>), dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b); \
-        else KFAC_LAUNCH_AS("bn_partial_kernel<" #DTYPE ">", (bn_partial_kernel<DTYPE, false>), dim3(wgs[dt]), dim3(256), (hipStream_t)stream, b);                  \
+        if (bytes[dt] > STREAM_BYTES) {                                                                                             \
+            if (two[dt]) KFAC_BN_LAUNCH_AS(DTYPE, ", stream", true, true);                                                \
+            else KFAC_BN_LAUNCH_AS(DTYPE, ", stream", true, false);                                                                 \
+        } else {                                                                                                                    \
+            if (two[dt]) KFAC_BN_LAUNCH_AS(DTYPE, "", false, true);                                                       \
+            else KFAC_BN_LAUNCH_AS(DTYPE, "", false, false);                                                                        \
+        }                                                                                                                           \
     } while (0)
             if (dt == KFAC_F32) KFAC_BN_LAUNCH(KFAC_F32);
             else if (dt == KFAC_BF16) KFAC_BN_LAUNCH(KFAC_BF16);
             else KFAC_BN_LAUNCH(KFAC_F16);
+#undef KFAC_BN_LAUNCH_AS
 #undef KFAC_BN_LAUNCH
         }
         if (rb.count) {
