@@ -33,11 +33,10 @@ struct BnPlan {
     bool halves;      // a call of few workgroups may give each half to one of its own: the sums, and so the result, are the same
 };
 
-// Calls of few workgroups are bound by what one CU reads: with halves apart 64 channels of 56 x 56 take 8.0 us for one sample and 8.3 for four in
-// fp32, whole 9.4 and 9.8; 512 of 28 x 28 in bf16 (seven chunks) 9.6 and 10.8.  From 13 chunks on (64 channels of 112 x 112) the sums
-// over the halves take as long as this saves (12.1 and 12.0; four samples 12.9 and 12.6), and from about 200 workgroups on (all layers at batch
-// 1: 211) the chip is busy without (17.2 and 16.7).
-constexpr int BN_HALVES_MOST = 7, BN_HALVES_WGS = 128;
+// Calls of few workgroups are bound by what one CU reads.  Of inputs that no cache holds, halves apart and whole, us: 64 channels of 56 x 56,
+// two samples, fp32 10.8 and 13.7; of 112 x 112 in fp32 13.2 and 17.2, eight samples 20.1 and 26.8, bf16 12.1 and 14.7, 16.1 and 19.4; of 224 x 224
+// (49 chunks) fp32 25.1 and 31.1.  With 208 workgroups (112 x 112, 16 samples) halves take 31.2 and 29.2.
+constexpr int BN_HALVES_WGS = 128;
 static BnPlan bn_plan(int C, int HW, int dtype, bool vec) {
     BnPlan p;
     if (!vec) {
@@ -59,7 +58,7 @@ static BnPlan bn_plan(int C, int HW, int dtype, bool vec) {
     // (whole rounds of loads: a second sum then costs none)
     p.half = p.sp * p.cvw * bn_vec(dtype) > BN_SUM ? std::max((p.sp / 2 + 2 * lanes) / (4 * lanes), 1) * (4 * lanes) : p.sp;
     p.half = std::min(p.half, p.sp);
-    p.halves = p.half < p.sp && p.nchunk > 1 && p.nchunk <= BN_HALVES_MOST;
+    p.halves = p.half < p.sp && p.nchunk > 1;
     return p;
 }
 
