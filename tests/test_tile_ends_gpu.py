@@ -68,8 +68,67 @@ def test_ends(cols, dtype, bias):
                 if form != "packed":
                     np.testing.assert_array_equal(full, full.T)
             np.testing.assert_array_equal(got, first)
-    # alone: the same bits for few builds as for one
+    # fewer than 16 builds: the bits of a call of its own, in every form
     one = torch.empty((d, d), device=DEV)
     kb.kfac_factor_A(desc, xt, 0.0, one, ws)
     torch.cuda.synchronize()
-    assert rel_fro(one.cpu().numpy(), ref) < FACTOR_TOL
+    alone = one.cpu().numpy()
+    assert rel_fro(alone, ref) < FACTOR_TOL and rel_max(alone, ref) < FACTOR_TOL
+    np.testing.assert_array_equal(alone, alone.T)
+    few = [torch.empty((d, d), device=DEV) for _ in range(3)]
+    kb.kfac_factor_batched(kb.FactorBatch([(kb.KFAC_OP_FACTOR_A, desc, xt, o, 0.0) for o in few], device=DEV))
+    assert all(torch.equal(o, one) for o in few)
+    tri = [torch.empty(d * (d + 1) // 2, device=DEV) for _ in range(3)]
+    kb.kfac_factor_batched(kb.FactorBatch([(kb.KFAC_OP_FACTOR_A, desc, xt, o, 0.0) for o in tri], device=DEV, packed=True))
+    packed = torch.from_numpy(ko.pack_upper(alone).astype(np.float32)).to(DEV)
+    assert all(torch.equal(o, packed) for o in tri)
+    run = [torch.from_numpy(old).to(DEV) for _ in range(3)]
+    kb.kfac_factor_batched(kb.FactorBatch([(kb.KFAC_OP_FACTOR_A, desc, xt, o, 0.0) for o in few], device=DEV, running=run, decay=DECAY))
+    want = torch.from_numpy(old).to(DEV)
+    kb.kfac_ema(want, one, d, DECAY)
+    assert all(torch.equal(o, want) for o in run)
+
+
+# 44 builds of 1,960 rows: 256-wide tiles, each of all rows, so that their epilogues write the results.  1,000 columns end inside a block row,
+# on a vector; 1,001 inside a vector; 1,008 in (channel, tap) order go element by element.
+@pytest.mark.parametrize("shape", [
+    synth.LayerShape("vectors", 10, 1000, 14, 14, 8, 1, 1, 1, 0), synth.LayerShape("elements", 10, 1001, 14, 14, 8, 1, 1, 1, 0),
+    synth.LayerShape("mapped", 10, 112, 28, 28, 8, 3, 3, 2, 1)], ids=lambda s: s.name)
+def test_ends_of_whole_256_wide_tiles(shape):
+    s, n = shape, 44
+    g = torch.Generator(device=DEV).manual_seed(3)
+    x = torch.randn((s.N, s.H, s.W, s.C_in), device=DEV, generator=g).clamp_(min=0).bfloat16()
+    X = torch.nn.functional.unfold(x.permute(0, 3, 1, 2).double(), s.kh, padding=s.pad, stride=s.stride).transpose(1, 2).reshape(-1, s.d_A - 1)
+    X = torch.cat([X, torch.ones((X.shape[0], 1), dtype=torch.float64, device=DEV)], 1)
+    ref, d = X.t() @ X / X.shape[0], s.d_A
+    desc = kb.make_desc(s, kb.KFAC_NHWC, kb.KFAC_BF16, kb.KFAC_ORDER_C_KH_KW)
+    old = torch.randn((d, d), device=DEV, generator=g)
+    old = old + old.t()
+    upper = torch.triu_indices(d, d, device=DEV)
+    for form in ("square", "running", "packed"):
+        bufs, outs = zip(*(guarded(upper.shape[1] if form == "packed" else d * d) for _ in range(n)))
+        more = {}
+        fresh = [o if form == "packed" else o.view(d, d) for o in outs]
+        if form == "running":
+            for o in outs:
+                o.copy_(old.flatten())
+            more = {"running": fresh, "decay": DECAY}
+            fresh = [torch.empty((d, d), device=DEV) for _ in range(n)]
+        batch = kb.FactorBatch([(kb.KFAC_OP_FACTOR_A, desc, x, o, 0.0) for o in fresh], device=DEV, packed=form == "packed", **more)
+        kb.kfac_kernel_timing_enable(True)
+        try:
+            kb.kfac_factor_batched(batch)
+            kernels = kb.kfac_kernel_timing_report()
+        finally:
+            kb.kfac_kernel_timing_enable(False)
+        assert [k for k in kernels if k.startswith("factor_tile_kernel<")] == ["factor_tile_kernel<256, 16-bit>"], kernels
+        assert not any("reduce" in k or "finish" in k for k in kernels), kernels        # (no partial sums)
+        want = DECAY * old.double() + (1 - DECAY) * ref if form == "running" else ref
+        want = want[upper[0], upper[1]] if form == "packed" else want
+        for buf, o in zip(bufs, outs):
+            assert bool((buf[:GUARD + 1] == 7).all()) and bool((buf[GUARD + 1 + o.numel():] == 7).all()), form
+            assert torch.equal(o, outs[0]), form
+        got = outs[0].view(want.shape)
+        assert float((got - want).norm() / want.norm()) < FACTOR_TOL and float((got - want).abs().max() / want.abs().max()) < FACTOR_TOL, form
+        if form != "packed":
+            assert torch.equal(got, got.t())
