@@ -74,6 +74,9 @@ static void add_work(TileWork& w, const View& v) {
 // last ones (18,816 rows of the first stage's layers at 3200 to a workgroup 119 us, at 6400 181 us), less adds partial sums, each
 // as much traffic as a finished tile, for nothing (the third stage's 18 layers at 1568 rows: 151 us unsplit, 334 us in two).  When
 // there is little work the launch of the second pass weighs too.
+// (768: three workgroups to a CU, as 16-bit tiles run.  Of fp32 ones two do, and the line is from when it was three: of 239 fp32 calls,
+// counted in 512, most take the same time within 3 % and calls of little work less, layers 12 to 30 of ResNet-50 at batch 2 198 us instead of
+// 250, all at batch 1 466 and 495; but chains of additions, and the errors, would be up to half as long again.)
 static int rows_of(const TileWork& w, bool f32) {
     const double per_slot = w.narrow / 768;
     const double least = f32 ? (per_slot < 100 ? SHARE_LEAST_F32 : 256) : (per_slot < 512 ? SHARE_LEAST : SHARE_LEAST_WIDE);

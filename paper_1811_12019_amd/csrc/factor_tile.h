@@ -232,8 +232,8 @@ __device__ __forceinline__ void static_for(F&& f) {              // f(StaticInt<
 }
 
 // The old values of a running average, 16-byte vectors of a block of 32 rows x w columns of the result, which lies in a buffer of its own
-// size: a lane's byte offset and the bytes of a row, by which the passes step on in a scalar register.  A block that is not whole (the
-// others fetch theirs element by element) gets an offset outside every result (d < 32768) and no steps: a step in a scalar register is not
+// size: a lane's byte offset and the bytes of a row, by which the passes step on in a scalar register.  A block that is not whole (they
+// fetch theirs where they are written) gets an offset outside every result (d < 32768) and no steps: a step in a scalar register is not
 // part of what the buffer's size is compared with, so that none may lead behind the matrix.
 constexpr unsigned OUTSIDE = 0xFFFFFFF0u;
 struct OldAt {
@@ -523,7 +523,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     // (read: starts one of READS operand reads into one of two register sets; multiply: one of the MULS products of a set).  The barrier
     // sits before a slab's last step: this wavefront has then read all of the slab, so that once everybody is there the slab's place may
     // be refilled, which the next slab's first step does, and the first operands of the next slab, whose copies have landed, are read
-    // during the last step's products.  A product occupies the matrix cores for 32 cycles (fp32: 64): reads, address arithmetic and
+    // during the last step's products.  A product occupies the matrix cores for 32 cycles: reads, address arithmetic and
     // copies are dealt out between the products, one fenced group after each (left alone, they gather before or behind them, in all
     // wavefronts at the same time).
     // fp32: one register set, emptied (split into pieces) before the next operands are read into it; where a slab is one step, its place is

@@ -673,7 +673,7 @@ __global__ __launch_bounds__(256) void inv_init_kernel(Batch b) {
     __shared__ float red[4];
     begin_tile_of(b, blockIdx.x, red);
 }
-constexpr int BEGIN_TOGETHER = 768;      // three workgroups to a CU
+constexpr int BEGIN_TOGETHER = 768;      // workgroups; a CU runs one at a time of inv_begin_kernel, which has the pivot's registers
 
 // acc = T . U^T of a matrix's last step, fp32, with both operand slabs (128 rows x nb floats, row stride 128, zero beyond nb)
 // streamed through a 3-stage LDS ring by global_load_lds_dwordx4 (lane i's 16 bytes land at block base + 16 i), so
