@@ -280,12 +280,12 @@ template <int P> __device__ __forceinline__ uint4 whole_operand(const v2u (&r)[P
 template <int P> __device__ __forceinline__ uint4 whole_operand(const v4u (&r)[P]) { return make_uint4(r[0].x, r[0].y, r[0].z, r[0].w); }
 
 // fp32 operands are multiplied on the bf16 matrix cores, which are 16 times as fast as the fp32 ones: x = x0 + x1 + x2, eight bits each (x0: the
-// upper half of x, which no finite x takes to infinity; x1, x2 rounded, at most 2^-7 and 2^-16 of x), exactly from 2^-110 up (below, pieces
-// end at bf16's last bit, 2^-133), and all products of pieces but x2 y2, which is at most 2^-32 of x y.  Errors against 64 bits, over those of
-// fp32 products: 1.00 for one row, less for more (normal and ReLU'd values, up to 25,088 rows: 0.03 to 0.99; of 95 % zeros 0.84 to 1.05).  Without
+// upper half of x, which no finite x takes to infinity; x1, x2 rounded, at most 2^-6 and 2^-15 of x), exactly from 2^-110 up (below, pieces
+// end at bf16's last bit, 2^-133), and all products of pieces but x2 y2, which is at most 2^-31 of x y.  Errors against 64 bits, over those of
+// fp32 products: 1.00 for one row, less for more (normal and ReLU'd values, up to 25,088 rows: 0.03 to 1.00; of 75 to 98 % zeros 0.80 to 1.05).  Without
 // x1 y2 and x2 y1 up to 4.0 * 2^-24 of a product is lost, in a column of one value always the same way: errors of up to 8 rows, and of
 // 95 % zeros, were 1.3 to 1.5 times those of fp32 products.  All factors of ResNet-50 from NCHW at batch 8: fp32 products 1616 us, six
-// products of pieces 1260, these eight 1424; six with x0 rounded (and kept finite) 1390, single products 1.02 to 1.05 times the error.
+// products of pieces 1260, these eight 1424, now 1400; six with x0 rounded (and kept finite) 1390, single products 1.02 to 1.05 times the error.
 // Bound: the matrix core takes 1,024 cycles a slab of a 128-wide tile for the products and 512 for the splitting's v_dot2_f32_bf16, which run
 // on it too; without them (differences, 9 more instructions to four values) 1,431 us.  Two workgroups to a CU: three leave no room for the
 // small products' sums.
@@ -293,6 +293,11 @@ typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 struct Pieces {
     uint4 p[3];
 };
+// LESS: x0 is one less in magnitude in its last bit (zero stays), for one of a product's operands.  Squares are 0, 1 or 4 modulo 8, so that sums
+// of x0 x0 lie unevenly between two fp32 numbers and are rounded up or down more often, by how many there are: the diagonal of a 3x3 layer of
+// 64 channels of 28 x 28, 32 images, was off by +0.8 * 2^-24 on average, of 75 % zeros by -1.2 (1.5 times the error of fp32 products); with
+// a (a - 1), even and else evenly spread, by less than 0.2.
+template <bool LESS>
 __device__ __forceinline__ void split_pair(float a, float b, unsigned& p0, unsigned& p1, unsigned& p2) {
     // a - piece, exact, as one instruction.  ((-1, 0) and (0, -1) in registers: as a constant inside the instruction the compiler writes
     // -1.0 for both, which the hardware takes for the second.)
@@ -302,6 +307,12 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned& p0, unsig
     __builtin_memcpy(&first, &minus_first, 4);
     __builtin_memcpy(&second, &minus_second, 4);
     p0 = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+    if constexpr (LESS) {
+        unsigned up, down;                                         // (neither wraps but one at +0, the other at -0: both give 0 there)
+        asm("v_pk_sub_u16 %0, %1, 1 op_sel_hi:[1,0] clamp" : "=v"(up) : "v"(p0));
+        asm("v_pk_sub_i16 %0, %1, 1 op_sel_hi:[1,0] clamp" : "=v"(down) : "v"(p0));
+        p0 = up & down;
+    }
     __builtin_memcpy(&x0, &p0, 4);
     a = __builtin_amdgcn_fdot2_f32_bf16(x0, first, a, false);
     b = __builtin_amdgcn_fdot2_f32_bf16(x0, second, b, false);
@@ -312,20 +323,23 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned& p0, unsig
     const v2bf x2 = {(__bf16)a, (__bf16)b};
     __builtin_memcpy(&p2, &x2, 4);
 }
+template <bool LESS>
 __device__ __forceinline__ void split_words(const unsigned (&w)[8], Pieces& o) {
     unsigned q[3][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) split_pair(__uint_as_float(w[2 * i]), __uint_as_float(w[2 * i + 1]), q[0][i], q[1][i], q[2][i]);
+    for (int i = 0; i < 4; ++i) split_pair<LESS>(__uint_as_float(w[2 * i]), __uint_as_float(w[2 * i + 1]), q[0][i], q[1][i], q[2][i]);
 #pragma unroll
     for (int e = 0; e < 3; ++e) o.p[e] = make_uint4(q[e][0], q[e][1], q[e][2], q[e][3]);
 }
+template <bool LESS>
 __device__ __forceinline__ void split_operand(const v2u (&r)[4], Pieces& o) {
     const unsigned w[8] = {r[0].x, r[0].y, r[1].x, r[1].y, r[2].x, r[2].y, r[3].x, r[3].y};
-    split_words(w, o);
+    split_words<LESS>(w, o);
 }
+template <bool LESS>
 __device__ __forceinline__ void split_operand(const v4u (&r)[2], Pieces& o) {
     const unsigned w[8] = {r[0].x, r[0].y, r[0].z, r[0].w, r[1].x, r[1].y, r[1].z, r[1].w};
-    split_words(w, o);
+    split_words<LESS>(w, o);
 }
 // Pieces of the eight products, smallest first.  The first seven have accumulators of their own: the matrix cores cut sums off, and all
 // products to an accumulator of sums of one sign would err up to 2.5 times as much as fp32 products.
@@ -368,7 +382,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     // the same in all blocks, its column CSTEP further on from block to block.
     constexpr bool PAIR = !PLANES && TW == 256;                // both blocks hold the same four rows
     constexpr int NR = PLANES || PAIR ? 1 : 2, NC = PAIR ? 2 : 1;      // rows, and vectors of a panel's row, of a lane
-    constexpr int CH = DK / V, CSTEP = NW * 64 / CH, FLIP = 16 / CH;
+    constexpr int CH = DK / V, CSTEP = NW * 64 / CH, LESS = 16 / CH;
     static_assert(CSTEP % 16 == 0, "the flip is the same in all blocks");
     auto block = [&](int j) { return PAIR ? 2 * wave + j : wave + NW * j; };
     int row0, q;                                               // row inside the slab, vector (PLANES: column) of block 0
@@ -377,7 +391,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
         const int L = block(0) * 64 + lane;
         if constexpr (PLANES) {
             q = L / CH;
-            row0 = ((L % CH) ^ (q / FLIP % CH)) * V;
+            row0 = ((L % CH) ^ (q / LESS % CH)) * V;
         } else if constexpr (ES == 4) {
             row0 = L / (TW / 4);
             q = L % (TW / 4);
@@ -583,7 +597,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
     // ---- consumer: LDS byte address of this lane's operand pieces in stage 0, from tile column c0 on ----
     auto operand_addr = [&](int c0) -> unsigned {
         if constexpr (PLANES) {
-            return (unsigned)((c0 + lm) * CH + (h * (ES / 2) ^ (lm / FLIP % CH))) * 16;
+            return (unsigned)((c0 + lm) * CH + (h * (ES / 2) ^ (lm / LESS % CH))) * 16;
         } else if constexpr (ES == 2) {
             const int grp = lane >> 4, p = lane & 15, r = p >> 2, cg4 = p & 3;
             return (unsigned)((2 * (grp >> 1)) * RGS + (2 * r + (cg4 >> 1)) * 16 + (cg4 & 1) * 8 + (grp & 1) * 128 + c0 / 16 * 128);
@@ -660,7 +674,7 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
             for (int i = 0; i < BB; ++i) operand_arrived(b[set][i]);
             if constexpr (ES == 4) {
 #pragma unroll
-                for (int i = 0; i < BB; ++i) split_operand(b[0][i], bp[i]);
+                for (int i = 0; i < BB; ++i) split_operand<false>(b[0][i], bp[i]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }, [&](auto m, int set) {
@@ -718,9 +732,9 @@ __device__ __forceinline__ void factor_tile_run(const View& v, const KFAC_AS1 un
         for (int i = 0; i < S::MB; ++i) operand_arrived(a[set][i]);
         if constexpr (ES == 4) {
 #pragma unroll
-            for (int i = 0; i < S::NB; ++i) split_operand(b[0][i], bp[i]);
+            for (int i = 0; i < S::NB; ++i) split_operand<true>(b[0][i], bp[i]);
 #pragma unroll
-            for (int i = 0; i < S::MB; ++i) split_operand(a[0][i], ap[i]);
+            for (int i = 0; i < S::MB; ++i) split_operand<false>(a[0][i], ap[i]);
             __builtin_amdgcn_sched_barrier(0);
         }
     }, [&](auto m, int set) {
